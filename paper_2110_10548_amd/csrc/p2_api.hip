@@ -152,7 +152,8 @@ struct Ctx {
     ~Ctx();
     void release();
     DevBuf rows, rows_hdr;
-    DevBuf blob, valid, rerun, sorted, progs, costs, counters, topk_scratch, topk_pos, topk_in, topk_jobs, lit_scratch, post;
+    DevBuf blob, valid, rerun, sorted, progs, costs, counters, topk_scratch, topk_control, topk_pos, topk_in, topk_jobs, lit_scratch, post;
+    bool topk_control_clear = false;                        // the words that the blocks of a selection share are zero
     DevBuf sel_progs, sel_costs, gather;                    // the rows that shortlists picked, and whose they are
     HostBuf h_gather;
     DevBuf f_finish;                                        // frontier engine: what every query's rows are written from
@@ -164,11 +165,17 @@ struct Ctx {
     hipStream_t spare_streams[kSpareStreams] = {};          // created beside the slots' streams and found to share a queue with one: never used
     DevBuf probe_sink;
     hipError_t open_slot_streams();
+    hipError_t open_topk_control(hipStream_t stream) {
+        const void* before = topk_control.p;
+        hipError_t e = topk_control.ensure(p2::topk_control_bytes());
+        if (e == hipSuccess && (topk_control.p != before || !topk_control_clear)) e = hipMemsetAsync(topk_control.p, 0, p2::topk_control_bytes(), stream);
+        return e;
+    }
     hipEvent_t front_go = nullptr;                          // the call's stream has reached the enumerations
     HostBuf h_rows, h_rows_hdr;
     hipStream_t copy_stream = nullptr;      // uploads that overlap with the kernels of the call's stream
     hipEvent_t copy_done = nullptr;
-    HostBuf h_blob, h_counters, h_progs, h_costs, h_pos, h_post, h_topk_jobs, h_fshare;
+    HostBuf h_blob, h_counters, h_progs, h_costs, h_pos, h_post, h_topk_jobs, h_topk_nan, h_fshare;
 };
 thread_local Ctx g_ctx;
 
@@ -250,7 +257,7 @@ thread_local Prof g_prof;
 const std::thread::id g_loader_thread = std::this_thread::get_id();
 
 void Ctx::release() {
-    DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_pos,
+    DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_control, &topk_pos,
                      &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink};
     for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
     for (auto* v : {&f_evalid, &f_egsums}) {
@@ -259,7 +266,7 @@ void Ctx::release() {
     }
     for (FrontSlot& sl : slots) sl.release();
     for (hipStream_t& sp : spare_streams) { if (sp) (void)hipStreamDestroy(sp); sp = nullptr; }
-    HostBuf* host[] = {&h_rows, &h_rows_hdr, &h_blob, &h_counters, &h_progs, &h_costs, &h_pos, &h_post, &h_topk_jobs, &h_fshare, &h_gather, &h_finish};
+    HostBuf* host[] = {&h_rows, &h_rows_hdr, &h_blob, &h_counters, &h_progs, &h_costs, &h_pos, &h_post, &h_topk_jobs, &h_topk_nan, &h_fshare, &h_gather, &h_finish};
     for (HostBuf* b : host) { if (b->p) (void)hipHostFree(b->p); b->p = nullptr; b->cap = 0; }
     if (front_go) { (void)hipEventDestroy(front_go); front_go = nullptr; }
     if (copy_done) { (void)hipEventDestroy(copy_done); copy_done = nullptr; }
@@ -303,9 +310,9 @@ struct CallScope {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Selections over at most this many valid programs go into one launch for the whole batch
-// (one wavefront each); longer lists take the two-stage selection, one query at a time.
-constexpr size_t kTopkJobMax = 8192;
+// Selections over at most this many valid programs go into one launch for the whole batch (one block each: 30 tiles
+// of 8192 at the most, some 40 us); longer lists are selected from by the whole chip, one query at a time.
+constexpr size_t kTopkJobMax = 1 << 18;
 
 struct QueryRun {
     p2::Plan plan;
@@ -1312,13 +1319,14 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     for (auto& r : runs)
         if (r.topk > 0 && r.n_valid > 0) {
             topk_rows += (size_t)n_msg * std::min<size_t>(r.topk, r.n_valid);
-            topk_scratch = std::max(topk_scratch, topk_scratch_bytes(r.n_valid, r.topk));
+            if (r.n_valid > kTopkJobMax) topk_scratch = std::max(topk_scratch, topk_scratch_bytes(r.n_valid, r.topk));
         }
     P2_HIP(C.topk_pos.ensure(sizeof(long long) * std::max<size_t>(topk_rows, 1)));
     P2_HIP(C.topk_scratch.ensure(std::max<size_t>(topk_scratch, 256)));
     int post_launches = 0;
-    std::vector<DevTopkJob> topk_jobs, topk_big;          // short lists (a block each); long lists (cut into shares)
-    int topk_jobs_k = 0, topk_big_k = 0;
+    std::vector<DevTopkJob> topk_jobs, topk_big;          // a block each; long lists, all blocks for one after the other
+    int topk_jobs_k = 0;
+    long long topk_jobs_n = 0;
     // ordering and costing: one launch per kernel and state-size class
     std::vector<PostLaunch> sort_launches, ccost_launches, scost_launches, lcost_launches;
     for (int i = 0; i < n_queries; ++i) {
@@ -1446,46 +1454,38 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         if (r.topk > 0) {
             const size_t kk = std::min<size_t>(r.topk, r.n_valid);
             for (int m = 0; m < n_msg; ++m) {
-                long long* out_pos = static_cast<long long*>(C.topk_pos.p) + pos_off;
-                uint32_t* nan_flag = &static_cast<DevCounters*>(C.counters.p)[i].nan_seen;
-                if (r.n_valid <= kTopkJobMax) {            // short lists: one launch for all of them, below
-                    DevTopkJob J;
-                    J.cost = costs + m; J.index = sorted; J.out_pos = out_pos; J.nan_flag = nan_flag;
-                    J.n = (long long)r.n_valid; J.stride = n_msg; J.k = r.topk; J.pad = 0;
+                DevTopkJob J;
+                J.cost = costs + m; J.index = sorted; J.out_pos = static_cast<long long*>(C.topk_pos.p) + pos_off;
+                J.nan_flag = &static_cast<DevCounters*>(C.counters.p)[i].nan_seen;
+                J.n = (long long)r.n_valid; J.stride = n_msg; J.k = r.topk; J.pad = 0;
+                pos_off += kk;
+                if (r.n_valid <= kTopkJobMax) {            // one launch for all of them, below
                     topk_jobs.push_back(J);
                     topk_jobs_k = std::max(topk_jobs_k, r.topk);
+                    topk_jobs_n = std::max(topk_jobs_n, J.n);
                 } else {
-                    DevTopkJob J;
-                    J.cost = costs + m; J.index = sorted; J.out_pos = out_pos; J.nan_flag = nan_flag;
-                    J.n = (long long)r.n_valid; J.stride = n_msg; J.k = r.topk; J.pad = 0;
                     topk_big.push_back(J);
-                    topk_big_k = std::max(topk_big_k, r.topk);
                 }
-                pos_off += kk;
             }
         }
     }
-    if (!topk_jobs.empty() || !topk_big.empty()) {
-        const size_t n_small = topk_jobs.size(), n_big = topk_big.size();
-        const size_t bytes = sizeof(DevTopkJob) * (n_small + n_big);
+    if (!topk_jobs.empty()) {
+        const size_t bytes = sizeof(DevTopkJob) * topk_jobs.size();
         P2_HIP(C.topk_jobs.ensure(bytes));
         P2_HIP(C.h_topk_jobs.ensure(bytes));
-        DevTopkJob* hj = static_cast<DevTopkJob*>(C.h_topk_jobs.p);
-        if (n_small) std::memcpy(hj, topk_jobs.data(), sizeof(DevTopkJob) * n_small);
-        if (n_big) std::memcpy(hj + n_small, topk_big.data(), sizeof(DevTopkJob) * n_big);
+        std::memcpy(C.h_topk_jobs.p, topk_jobs.data(), bytes);
         P2_HIP(hipMemcpyAsync(C.topk_jobs.p, C.h_topk_jobs.p, bytes, hipMemcpyHostToDevice, stream));
-        const DevTopkJob* dj = static_cast<const DevTopkJob*>(C.topk_jobs.p);
-        if (n_small) {
+        ++post_launches;
+        P2_HIP(launch_topk_jobs(static_cast<const DevTopkJob*>(C.topk_jobs.p), (unsigned)topk_jobs.size(), topk_jobs_k, topk_jobs_n, stream));
+    }
+    if (!topk_big.empty()) {
+        P2_HIP(C.open_topk_control(stream));
+        C.topk_control_clear = false;
+        for (const DevTopkJob& J : topk_big) {
             ++post_launches;
-            P2_HIP(launch_topk_jobs(dj, (unsigned)n_small, topk_jobs_k, stream));
+            P2_HIP(launch_topk(J.cost, J.stride, J.index, J.n, J.k, J.out_pos, C.topk_scratch.p, C.topk_control.p, J.nan_flag, stream));
         }
-        // long lists: two launches per 16384 of them
-        for (size_t at = 0; at < n_big; at += 16384) {
-            const unsigned n = (unsigned)std::min<size_t>(16384, n_big - at);
-            P2_HIP(C.topk_scratch.ensure(topk_big_scratch_bytes(n, topk_big_k)));
-            post_launches += 2;
-            P2_HIP(launch_topk_big(dj + n_small + at, n, topk_big_k, C.topk_scratch.p, stream));
-        }
+        C.topk_control_clear = true;
     }
     if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = post_launches; }
     P2_HIP(C.h_pos.ensure(sizeof(long long) * std::max<size_t>(topk_rows, 1)));
@@ -1782,15 +1782,16 @@ int32_t p2_topk_device(const double* cost, int64_t cost_stride, const uint64_t* 
     hipStream_t stream = (hipStream_t)stream_;
     Ctx& C = g_ctx;
     P2_HIP(C.topk_scratch.ensure(topk_scratch_bytes(n, k)));
-    P2_HIP(C.counters.ensure(sizeof(DevCounters)));
-    P2_HIP(C.h_counters.ensure(sizeof(DevCounters)));
-    P2_HIP(hipMemsetAsync(C.counters.p, 0, sizeof(DevCounters), stream));
-    DevCounters* dc = static_cast<DevCounters*>(C.counters.p);
+    P2_HIP(C.h_topk_nan.ensure(sizeof(uint32_t)));
+    P2_HIP(C.open_topk_control(stream));
+    C.topk_control_clear = false;                       // (until the kernels are known to have run to their end)
+    uint32_t* nan = static_cast<uint32_t*>(C.h_topk_nan.p);
+    *nan = 0u;
     P2_HIP(launch_topk(cost, cost_stride, reinterpret_cast<const unsigned long long*>(index), n, k,
-                       reinterpret_cast<long long*>(out_pos), C.topk_scratch.p, &dc->nan_seen, stream));
-    P2_HIP(launch_copy_out(C.h_counters.p, C.counters.p, sizeof(DevCounters), stream));
+                       reinterpret_cast<long long*>(out_pos), C.topk_scratch.p, C.topk_control.p, nan, stream));
     P2_HIP(hipStreamSynchronize(stream));
-    if (static_cast<const DevCounters*>(C.h_counters.p)->nan_seen) return fail(P2_EINVAL, "NaN cost");
+    C.topk_control_clear = true;
+    if (*static_cast<volatile uint32_t*>(nan)) return fail(P2_EINVAL, "NaN cost");
     return P2_OK;
 }
 

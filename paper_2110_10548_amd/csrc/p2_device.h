@@ -393,8 +393,8 @@ struct DevTopkJob {
     int k;
     int pad;
 };
-// Block b of the launch does jobs[b] alone: meant for many selections of a few thousand entries each.
-hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, hipStream_t stream);
+// Block b of the launch does jobs[b] alone (at most max_n entries, at most max_k kept).
+hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, long long max_n, hipStream_t stream);
 // The rows that the selections of a batch picked, gathered so that only they go back to the host: segment s (one
 // per query) has `rows` positions from pos[pos_first] on, relative to row out_first of the batch-wide program and
 // cost arrays; selected row pos_first + t gets program and costs of row out_first + pos[pos_first + t].
@@ -404,11 +404,6 @@ struct DevGatherSeg {
 };
 hipError_t launch_gather_rows(const DevGatherSeg* segs, unsigned n_segs, const p2_program* progs, const double* costs, int n_cost,
                               const long long* pos, p2_program* sel_progs, double* sel_costs, hipStream_t stream);
-// Many selections of many entries each: two launches for all of them (every job cut into strided shares, then a
-// merge per job).  scratch: topk_big_scratch_bytes(n_jobs, max_k) bytes.  Grid limit: n_jobs <= 65535.
-size_t topk_big_scratch_bytes(unsigned n_jobs, int max_k);
-hipError_t launch_topk_big(const DevTopkJob* jobs, unsigned n_jobs, int max_k, void* scratch, hipStream_t stream);
-
 // Results to the host: a kernel copies `bytes` (rounded up to 16; both buffers must hold that) from device
 // memory to pinned, device-accessible host memory.  Used instead of hipMemcpyAsync, whose queueing of a
 // device-to-host copy was seen to take 0.1 ms longer in some processes (never in others).
@@ -418,13 +413,16 @@ hipError_t launch_copy_out3(void* dst0, const void* src0, size_t bytes0, void* d
                             void* dst2, const void* src2, size_t bytes2, hipStream_t stream);
 
 // Top-k of (cost[i * stride], index[i]) over i < n: positions into out_pos[min(k, n)].
-// scratch: device buffer of topk_scratch_bytes(n, k) bytes.  nan_flag: device uint32 set to 1 on NaN.
+// scratch: device buffer of topk_scratch_bytes(n, k) bytes; control: topk_control_bytes() of device memory that are
+// zero before the first call and that every call leaves zero again.  nan_out (device or pinned host memory, may be
+// null): set to 1 if a cost is NaN, else left alone.
 size_t topk_scratch_bytes(long long n, int k);
+size_t topk_control_bytes();
 hipError_t launch_topk(const double* cost, long long stride, const unsigned long long* index, long long n, int k,
-                       long long* out_pos, void* scratch, uint32_t* nan_flag, hipStream_t stream);
+                       long long* out_pos, void* scratch, void* control, uint32_t* nan_out, hipStream_t stream);
 
-// The same selection with the stage-1 lists in a fixed array of the device image (no allocation): k at most
-// topk_fixed_max_k(); nan_flag (device, may be null) is cleared and then set to 1 when a cost is NaN.
+// The same selection with its scratch in a fixed array of the device image (no allocation): k at most
+// topk_fixed_max_k(); nan_flag (device, may be null) is set to 1 if a cost is NaN, else to 0.
 // Only queues kernels.  hipErrorInvalidValue when k is too large.
 int topk_fixed_max_k();
 hipError_t launch_topk_fixed(const double* cost, long long stride, const unsigned long long* index, long long n, int k,

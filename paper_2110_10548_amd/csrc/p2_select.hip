@@ -1,5 +1,5 @@
 // Ordering kernels: rank-sort of the (few) valid candidate indices, and top-k selection of
-// (cost, index) pairs by wavefront-level filtered insertion (the simulator's shortlist, Sec. 5).
+// (cost, index) pairs by filtering against a bound (the simulator's shortlist, Sec. 5).
 #include "p2_device.h"
 
 #include <mutex>
@@ -35,204 +35,546 @@ __global__ __launch_bounds__(256) void k_rank_sort(const unsigned long long* __r
     if (i < n) sorted[seg.out_off + rank] = key;
 }
 
-struct Item {
-    double c;
-    unsigned long long idx;
-    long long pos;
-};
-
-__device__ inline bool item_less(const Item& a, const Item& b) {
-    if (a.c < b.c) return true;
-    if (a.c > b.c) return false;
-    if (a.idx != b.idx) return a.idx < b.idx;
-    return a.pos < b.pos;
+// A barrier for what the block keeps in LDS.  __syncthreads() also waits for every global load in flight (loads and
+// stores share a counter), which would end the loads ahead of a walk at each of its barriers.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-struct TopList {
-    double* c;
-    unsigned long long* idx;
-    long long* pos;
-};
+// ---- selection of the K smallest (cost, index, position) triples --------------------------------------------
+// One block walks its share of the list a tile at a time (NT threads x kSelUnroll costs each, the next tile in flight)
+// and keeps in a buffer in LDS what does not lie above a bound: a cost with at least K entries at or below it.  A first
+// bound costs no sort: every lane keeps the smallest cost it has met, a wavefront sorts its 64 of them in registers, and
+// the largest over the wavefronts of the ceil(K / wavefronts)-th smallest has K entries at or below it whatever the data.
+// When the buffer cannot take a tile's entries, a histogram over both (equal steps of the costs' bit patterns between the
+// smallest and the largest) gives the next bound, which some K entries pass; costs that a histogram does not tell apart
+// are sorted instead.  Only entries that are sorted or handed on have their index read: a list entry costs 8 bytes.
+constexpr int kSelUnroll = 8;
 
-// Insert `it` (same value in all lanes) into the wavefront's sorted list of at most K entries.
-__device__ inline void list_insert(const TopList& L, int& cnt, int K, const Item& it, int lane) {
-    int below = 0;
-    for (int j = lane; j < cnt; j += kWave) {
-        Item e{L.c[j], L.idx[j], L.pos[j]};
-        below += item_less(e, it) ? 1 : 0;
-    }
-    for (int off = 32; off > 0; off >>= 1) below += __shfl_xor(below, off, kWave);
-    const int p = below;
-    if (p >= K) return;
-    const int newcnt = cnt < K ? cnt + 1 : K;
-    // shift entries p .. newcnt-2 one place up, highest chunk first
-    for (int hi = newcnt - 1; hi > p; hi -= kWave) {
-        const int j = hi - lane;                // destination
-        Item e{0.0, 0ull, 0ll};
-        const bool act = j > p;
-        if (act) e = Item{L.c[j - 1], L.idx[j - 1], L.pos[j - 1]};
-        __syncthreads();
-        if (act) { L.c[j] = e.c; L.idx[j] = e.idx; L.pos[j] = e.pos; }
-        __syncthreads();
-    }
-    if (lane == 0) { L.c[p] = it.c; L.idx[p] = it.idx; L.pos[p] = it.pos; }
-    __syncthreads();
-    cnt = newcnt;
+// costs in ascending order as unsigned integers (-0 and +0 compare equal), and back
+__device__ inline unsigned long long cost_key(double c) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(c + 0.0);
+    return b ^ ((unsigned long long)((long long)b >> 63) | 0x8000000000000000ull);
+}
+__device__ inline double key_cost(unsigned long long k) {
+    return __longlong_as_double((long long)((k >> 63) ? k ^ 0x8000000000000000ull : ~k));
 }
 
-// Feed one item per lane (valid = lane has one) through the list.
-__device__ inline void list_offer(const TopList& L, int& cnt, int K, Item mine, bool valid, int lane) {
+// The buffer: an entry is its cost as a key and its place in what is read; idx is filled for a sort.
+template <int NT, int B>
+struct SelShared {
+    unsigned long long key[B], idx[B], pos[B];
+    uint32_t bound[NT / kWave];
+    unsigned long long lo[NT / kWave], hi[NT / kWave];
+    uint32_t rank[B];                      // ranks, places or the bins of a histogram
+    uint32_t sum[NT / kWave];
+    uint32_t total[3];
+    uint32_t flag, edge;
+};
+
+// What a block goes by: entries above (cost, index) = (Tc, Ti) are out.
+struct SelState {
+    uint32_t cnt;
+    double Tc;
+    unsigned long long Ti;
+};
+
+// What a selection reads: costs `stride` apart with a candidate index each; their positions are where they stand, or in
+// `pos`.  chunk > 1: of every chunk x 64 entries only the first 64 (whole lines: a sample costs its share of the bytes).
+struct SelSource {
+    const double* cost;
+    const unsigned long long *idx, *pos;
+    long long stride, chunk;
+    __device__ unsigned long long position(unsigned long long e) const { return pos ? pos[e] : e; }
+};
+
+// The value of lane (own lane xor J): a move within a row of 16 lanes where J allows it (the exchange networks below are
+// chains of these, and a trip through LDS takes several times as long), else through LDS.
+template <int J>
+__device__ inline uint32_t lane_xor(uint32_t v) {
+    const int x = (int)v;
+    if constexpr (J == 1) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);            // quad_perm [1,0,3,2]
+    if constexpr (J == 2) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, true);            // quad_perm [2,3,0,1]
+    if constexpr (J == 4)                                                                               // (xor 7, then xor 3)
+        return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+    if constexpr (J == 8) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true);           // row_ror:8
+    return (uint32_t)__shfl_xor(x, J, kWave);
+}
+template <int J>
+__device__ inline unsigned long long lane_xor(unsigned long long v) {
+    return (unsigned long long)lane_xor<J>((uint32_t)v) | (unsigned long long)lane_xor<J>((uint32_t)(v >> 32)) << 32;
+}
+
+// Over a row of 16 lanes: every lane gets the largest value / the sum.
+__device__ inline uint32_t row_max(uint32_t v) {
+    uint32_t o;
+    o = lane_xor<1>(v); v = o > v ? o : v; o = lane_xor<2>(v); v = o > v ? o : v;
+    o = lane_xor<4>(v); v = o > v ? o : v; o = lane_xor<8>(v); return o > v ? o : v;
+}
+__device__ inline uint32_t row_sum(uint32_t v) {
+    v += lane_xor<1>(v); v += lane_xor<2>(v); v += lane_xor<4>(v);
+    return v + lane_xor<8>(v);
+}
+
+// Bitonic sort of a wavefront's 64 values.
+template <int K, int J>
+__device__ inline void wave_merge(uint32_t& v, uint32_t lane) {
+    const uint32_t o = lane_xor<J>(v);
+    v = ((lane & (uint32_t)J) == 0u) == ((lane & (uint32_t)K) == 0u) ? (o < v ? o : v) : (o > v ? o : v);
+    if constexpr (J > 1) wave_merge<K, J / 2>(v, lane);
+}
+__device__ inline void wave_sort(uint32_t& v, uint32_t lane) {
+    wave_merge<2, 1>(v, lane); wave_merge<4, 2>(v, lane); wave_merge<8, 4>(v, lane);
+    wave_merge<16, 8>(v, lane); wave_merge<32, 16>(v, lane); wave_merge<64, 32>(v, lane);
+}
+
+// Bitonic sort of the buffer (E entries per thread, entry r * NT + thread), keys and buffer places in registers: an
+// exchange over fewer than 64 places is one between lanes, over fewer than NT goes through LDS, and over NT stays in the
+// thread.  Equal keys are told apart by what the places hold.
+template <int NT, int B, int E>
+struct SelBitonic {
+    SelShared<NT, B>& S;
+    const SelSource& src;
+    uint32_t cnt, tid;
+    unsigned long long key[E];
+    uint32_t at[E];
+    __device__ bool less(unsigned long long ka, uint32_t pa, unsigned long long kb, uint32_t pb) const {
+        if (__builtin_expect(ka != kb, 1)) return ka < kb;
+        if (pa >= cnt || pb >= cnt) return pa < pb;
+        const unsigned long long ia = S.idx[pa], ib = S.idx[pb];
+        return ia != ib ? ia < ib : src.position(S.pos[pa]) < src.position(S.pos[pb]);
+    }
+    __device__ void take(int r, unsigned long long ko, uint32_t po, uint32_t k, uint32_t j) {
+        const uint32_t a = (uint32_t)r * NT + tid;
+        const bool low = ((a & j) == 0u) == ((a & k) == 0u);
+        if (less(ko, po, key[r], at[r]) == low) { key[r] = ko; at[r] = po; }
+    }
+    template <int J>
+    __device__ void lanes(uint32_t k) {
+        if (k > (uint32_t)J)
+#pragma unroll
+            for (int r = 0; r < E; ++r) take(r, lane_xor<J>(key[r]), lane_xor<J>(at[r]), k, (uint32_t)J);
+    }
+    __device__ void run() {
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            at[r] = (uint32_t)r * NT + tid;
+            key[r] = at[r] < cnt ? S.key[at[r]] : ~0ull;
+        }
+        lds_barrier();                                 // (S.key and S.rank are the exchange area from here on)
+#pragma unroll 1
+        for (uint32_t k = 2; k <= (uint32_t)(E * NT); k *= 2) {
+#pragma unroll 1
+            for (uint32_t j = k / 2; j >= 64u; j /= 2) {
+                if (E == 2 && j == (uint32_t)NT) {       // (the last merge: ascending)
+                    if (less(key[E - 1], at[E - 1], key[0], at[0])) {
+                        const unsigned long long kt = key[0]; key[0] = key[E - 1]; key[E - 1] = kt;
+                        const uint32_t pt = at[0]; at[0] = at[E - 1]; at[E - 1] = pt;
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int r = 0; r < E; ++r) { S.key[(uint32_t)r * NT + tid] = key[r]; S.rank[(uint32_t)r * NT + tid] = at[r]; }
+                lds_barrier();
+                unsigned long long ko[E];
+                uint32_t po[E];
+#pragma unroll
+                for (int r = 0; r < E; ++r) { ko[r] = S.key[(uint32_t)r * NT + (tid ^ j)]; po[r] = S.rank[(uint32_t)r * NT + (tid ^ j)]; }
+                lds_barrier();
+#pragma unroll
+                for (int r = 0; r < E; ++r) take(r, ko[r], po[r], k, j);
+            }
+            lanes<32>(k); lanes<16>(k); lanes<8>(k); lanes<4>(k); lanes<2>(k); lanes<1>(k);
+        }
+        unsigned long long p[E];
+#pragma unroll
+        for (int r = 0; r < E; ++r) p[r] = at[r] < cnt ? S.pos[at[r]] : 0ull;
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            const uint32_t a = (uint32_t)r * NT + tid;
+            if (a < cnt) { S.key[a] = key[r]; S.pos[a] = p[r]; }
+        }
+    }
+};
+
+// The buffer in ascending order, cut to K.
+template <int NT, int B>
+__device__ inline void sel_sort(SelShared<NT, B>& S, SelState& st, const SelSource& src, uint32_t K) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    lds_barrier();
+    {   // what came in before the bound was as low as it is now goes first
+        constexpr int kOwn = B / NT;
+        unsigned long long k[kOwn], p[kOwn];
+        bool in[kOwn];
+        const unsigned long long top = cost_key(st.Tc);
+#pragma unroll
+        for (int r = 0; r < kOwn; ++r) {
+            const uint32_t j = (uint32_t)r * NT + tid;
+            k[r] = j < st.cnt ? S.key[j] : ~0ull; p[r] = j < st.cnt ? S.pos[j] : 0ull;
+            in[r] = j < st.cnt && k[r] <= top;
+        }
+        if (tid == 0) S.flag = 0u;
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < kOwn; ++r) {
+            const unsigned long long m = __ballot(in[r]);
+            uint32_t at = 0;
+            if (lane == 0 && m) at = atomicAdd(&S.flag, (uint32_t)__popcll(m));
+            at = (uint32_t)__shfl((int)at, 0, kWave) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            if (in[r]) { S.key[at] = k[r]; S.pos[at] = p[r]; }
+        }
+        lds_barrier();
+    }
+    const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag);
+    if (cnt <= (uint32_t)NT / 2u) {
+        // few entries: everyone's rank is counted, the threads that share an entry take turns through the others (upper
+        // halves first; candidate indices are read only if some of those are equal)
+        uint32_t P = 32;
+        while (P < cnt) P *= 2;
+        const uint32_t item = tid & (P - 1u), part = tid / P, parts = (uint32_t)NT / P;
+        if (tid < cnt) S.rank[tid] = 0u;
+        const unsigned long long k = item < cnt ? S.key[item] : 0ull, p = item < cnt ? S.pos[item] : 0ull;
+        const uint32_t kh = (uint32_t)(k >> 32);
+        const uint32_t* upper = reinterpret_cast<const uint32_t*>(S.key) + 1;
+        uint32_t below = 0, equal = 0;
+        if (item < cnt)
+#pragma unroll 8
+            for (uint32_t j = part; j < cnt; j += parts) {
+                const uint32_t o = upper[2u * j];
+                below += o < kh ? 1u : 0u;
+                equal += o == kh ? 1u : 0u;
+            }
+        const bool ties = item < cnt && equal > (item % parts == part ? 1u : 0u);
+        if (__syncthreads_or(ties ? 1 : 0)) {
+            for (uint32_t j = tid; j < cnt; j += NT) S.idx[j] = src.idx[S.pos[j]];
+            lds_barrier();
+            if (ties) {
+                const unsigned long long i = S.idx[item];
+                for (uint32_t j = part; j < cnt; j += parts) {
+                    const unsigned long long o = S.key[j];
+                    if ((uint32_t)(o >> 32) != kh || j == item) continue;
+                    const unsigned long long ij = S.idx[j];
+                    below += o != k ? (o < k ? 1u : 0u) : ij != i ? (ij < i ? 1u : 0u) : src.position(S.pos[j]) < src.position(p) ? 1u : 0u;
+                }
+            }
+        }
+        if (below) atomicAdd(&S.rank[item], below);
+        lds_barrier();
+        if (part == 0 && item < cnt) {
+            const uint32_t r = S.rank[item];
+            S.key[r] = k; S.pos[r] = p;
+        }
+    } else {
+        for (uint32_t j = tid; j < cnt; j += NT) S.idx[j] = src.idx[S.pos[j]];
+        if (cnt <= (uint32_t)NT) SelBitonic<NT, B, 1>{S, src, cnt, tid, {}, {}}.run();
+        else SelBitonic<NT, B, B / NT>{S, src, cnt, tid, {}, {}}.run();
+    }
+    lds_barrier();
+    st.cnt = cnt < K ? cnt : K;
+    if (st.cnt == K && key_cost(S.key[K - 1u]) <= st.Tc) { st.Tc = key_cost(S.key[K - 1u]); st.Ti = src.idx[S.pos[K - 1u]]; }
+}
+
+// A bound that some K of the buffer's entries and the tile's (kSelUnroll keys per thread, ~0 where there is none) pass,
+// and what passes it into the buffer.  False, with nothing changed: too many would stay.
+template <int NT, int B, class Key, class Place>
+__device__ inline bool sel_cut(SelShared<NT, B>& S, SelState& st, uint32_t K, Key key, Place place) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    constexpr int kOwn = B / NT;
+    unsigned long long lo = ~0ull, hi = 0ull;
+    lds_barrier();
+    unsigned long long own[kOwn];
+#pragma unroll
+    for (int r = 0; r < kOwn; ++r) own[r] = (uint32_t)r * NT + tid < st.cnt ? S.key[(uint32_t)r * NT + tid] : ~0ull;
+    auto see = [&](unsigned long long v) { lo = v < lo ? v : lo; hi = v != ~0ull && v > hi ? v : hi; };
+#pragma unroll
+    for (int r = 0; r < kOwn; ++r) see(own[r]);
+#pragma unroll
+    for (int u = 0; u < kSelUnroll; ++u) see(key(u));
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long a = __shfl_xor(lo, o, kWave), b = __shfl_xor(hi, o, kWave);
+        lo = a < lo ? a : lo; hi = b > hi ? b : hi;
+    }
+    if (lane == 0) { S.lo[wave] = lo; S.hi[wave] = hi; }
+    for (uint32_t j = tid; j < (uint32_t)B; j += NT) S.rank[j] = 0u;
+    lds_barrier();
+    for (int w = 0; w < NT / kWave; ++w) { lo = S.lo[w] < lo ? S.lo[w] : lo; hi = S.hi[w] > hi ? S.hi[w] : hi; }
+    const int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 0;
+    const int shift = bits > __builtin_ctz(B) ? bits - __builtin_ctz(B) : 0;
+    auto count = [&](unsigned long long v) { if (v != ~0ull) atomicAdd(&S.rank[(uint32_t)((v - lo) >> shift)], 1u); };
+#pragma unroll
+    for (int r = 0; r < kOwn; ++r) count(own[r]);
+#pragma unroll
+    for (int u = 0; u < kSelUnroll; ++u) count(key(u));
+    lds_barrier();
+    // the first bin up to which there are K entries: B / NT bins per thread
+    uint32_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < kOwn; ++r) mine += S.rank[tid * kOwn + (uint32_t)r];
+    uint32_t upto = mine;
+    for (int o = 1; o < 64; o <<= 1) { const uint32_t v = (uint32_t)__shfl_up((int)upto, o, kWave); if (lane >= (uint32_t)o) upto += v; }
+    if (lane == 63u) S.sum[wave] = upto;
+    lds_barrier();
+    { const uint32_t w = lane & 15u; upto += row_sum(w < wave ? S.sum[w] : 0u); }
+    uint32_t before = upto - mine;
+    if (before < K && upto >= K)
+#pragma unroll
+        for (int r = 0; r < kOwn; ++r) {
+            const uint32_t h = S.rank[tid * kOwn + (uint32_t)r];
+            if (before < K && before + h >= K) { S.edge = tid * kOwn + (uint32_t)r; S.flag = before + h; }
+            before += h;
+        }
+    lds_barrier();
+    const uint32_t stay = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag), edge = S.edge;
+    lds_barrier();
+    if (stay > (uint32_t)B) return false;
+    unsigned long long at[kOwn];
+#pragma unroll
+    for (int r = 0; r < kOwn; ++r) at[r] = (uint32_t)r * NT + tid < st.cnt ? S.pos[(uint32_t)r * NT + tid] : 0ull;
+    if (tid == 0) S.flag = 0u;
+    lds_barrier();
+    auto keep = [&](unsigned long long v, unsigned long long e) {
+        const bool ok = v != ~0ull && (uint32_t)((v - lo) >> shift) <= edge;
+        const unsigned long long m = __ballot(ok);
+        if (m == 0ull) return;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&S.flag, (uint32_t)__popcll(m));
+        base = (uint32_t)__shfl((int)base, 0, kWave);
+        if (ok) {
+            const uint32_t o = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            S.key[o] = v; S.pos[o] = e;
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < kOwn; ++r) keep(own[r], at[r]);
+#pragma unroll
+    for (int u = 0; u < kSelUnroll; ++u) keep(key(u), place(u));
+    const unsigned long long last = lo + ((((unsigned long long)edge + 1ull) << shift) - 1ull);
+    st.cnt = stay;
+    st.Tc = fmin(st.Tc, key_cost(last < lo || last > hi ? hi : last));
+    st.Ti = ~0ull;
+    return true;
+}
+
+// Tiles first, first + step, ... of the source's n entries go through the buffer; true: a NaN was among this lane's.
+template <int NT, int B>
+__device__ inline bool sel_consume(SelShared<NT, B>& S, SelState& st, const SelSource& src, long long n, long long first, long long step,
+                                   uint32_t K, bool bounded) {
+    constexpr long long kTile = (long long)NT * kSelUnroll;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    if (tid < 3u) S.total[tid] = 0u;
+    lds_barrier();
+    const long long lane_off = (long long)lane * src.stride, row_off = src.chunk * 64ll * src.stride;
+    double next[kSelUnroll];
+    uint32_t mine = ~0u;                                 // upper half of the smallest key so far
+    bool nan = false;
+    // (entries 64 by 64: row `at / 64` of a wavefront is a base that all its lanes share)
+    auto rest_of = [&](long long t, int u) { return n - (t * kTile + (long long)u * NT + (long long)wave * 64ll); };
+    auto load = [&](long long t) {
+#pragma unroll
+        for (int u = 0; u < kSelUnroll; ++u) {           // (loads without a condition: all of them in flight together)
+            const long long rest = rest_of(t, u);
+            const long long row = rest > 0 ? ((n - rest) >> 6) : 0ll;
+            const double* p = src.cost + row * row_off;
+            next[u] = p[(long long)lane < rest ? lane_off : 0ll];
+        }
+    };
+    const long long tiles = (n + kTile - 1) / kTile;
+    uint32_t round = 0;
+    if (first < tiles) load(first);
+#pragma unroll 1
+    for (long long t = first; t < tiles; t += step, ++round) {
+        double c[kSelUnroll];
+#pragma unroll
+        for (int u = 0; u < kSelUnroll; ++u) {
+            c[u] = (long long)lane < rest_of(t, u) ? next[u] : __longlong_as_double(0x7ff8000000000000ll);
+            nan |= c[u] != c[u] && (long long)lane < rest_of(t, u);
+            const uint32_t h = (uint32_t)__double2hiint(c[u]), k = c[u] == c[u] ? h ^ ((uint32_t)((int)h >> 31) | 0x80000000u) : ~0u;
+            mine = k < mine ? k : mine;
+        }
+        if (t + step < tiles) load(t + step);
+        if (!bounded && (round & (round + 1u)) == 0u) {  // after 1, 2, 4, ... tiles
+            const long long seen = round > 0u ? kTile : n - t * kTile;
+            const uint32_t waves = seen >= NT ? NT / kWave : (uint32_t)((seen + kWave - 1) / kWave);
+            const uint32_t r = (K + waves - 1u) / waves;
+            if (r <= 64u) {
+                uint32_t v = mine;
+                wave_sort(v, lane);
+                if (lane == r - 1u) S.bound[wave] = v;
+                lds_barrier();
+                const uint32_t w = lane & (uint32_t)(NT / kWave - 1);
+                const uint32_t T = row_max(w < waves ? S.bound[w] : 0u);
+                const double Tc = key_cost((unsigned long long)T << 32 | 0xffffffffull);      // (a NaN where T says nothing)
+                if (Tc < st.Tc) { st.Tc = Tc; st.Ti = ~0ull; }
+            }
+        }
+        auto entry = [&](int u) { return ((n - rest_of(t, u)) >> 6) * (src.chunk * 64ll) + (long long)lane; };
+        auto passes = [&](int u, double v) {
+            bool ok = v <= st.Tc;                        // (false for a NaN and past the end)
+            if (st.Ti != ~0ull && __ballot(ok && v == st.Tc) != 0ull) ok = ok && (v < st.Tc || src.idx[entry(u)] <= st.Ti);
+            return ok;
+        };
+        uint32_t in = 0, n_wave = 0;
+#pragma unroll
+        for (int u = 0; u < kSelUnroll; ++u) {
+            const bool ok = passes(u, c[u]);
+            in |= ok ? 1u << u : 0u;
+            n_wave += (uint32_t)__popcll(__ballot(ok));
+        }
+        uint32_t base = 0;
+        if (n_wave) {
+            if (lane == 0) base = atomicAdd(&S.total[round % 3u], n_wave);
+            base = (uint32_t)__shfl((int)base, 0, kWave);
+        }
+        lds_barrier();
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.total[round % 3u]);
+        if (tid == 0) S.total[(round + 2u) % 3u] = 0u;   // (last read before the barrier, used again in two rounds)
+        if (__builtin_expect(st.cnt + total <= (uint32_t)B, 1)) {
+            if (n_wave) {
+                uint32_t at = st.cnt + base;
+#pragma unroll
+                for (int u = 0; u < kSelUnroll; ++u) {
+                    const unsigned long long m = __ballot((in >> u) & 1u);
+                    if ((in >> u) & 1u) {
+                        const uint32_t o = at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                        S.key[o] = cost_key(c[u]); S.pos[o] = (unsigned long long)entry(u);
+                    }
+                    at += (uint32_t)__popcll(m);
+                }
+            }
+            st.cnt += total;
+        } else if (sel_cut(S, st, K, [&](int u) { return (in >> u) & 1u ? cost_key(c[u]) : ~0ull; },
+                           [&](int u) { return (unsigned long long)entry(u); })) {
+        } else {
+            // too many alike: NT at a time, the buffer sorted and cut to K where even those do not fit
+#pragma unroll 1
+            for (int u = 0; u < kSelUnroll; ++u) {
+                unsigned long long m;
+                uint32_t at, more;
+                const double v = (long long)lane < rest_of(t, u) ? src.cost[entry(u) * src.stride] : __longlong_as_double(0x7ff8000000000000ll);
+                bool ok;
+#pragma unroll 1
+                for (;;) {
+                    lds_barrier();
+                    if (tid == 0) S.flag = 0u;
+                    lds_barrier();
+                    ok = passes(u, v);
+                    m = __ballot(ok);
+                    at = 0;
+                    if (lane == 0 && m) at = atomicAdd(&S.flag, (uint32_t)__popcll(m));
+                    at = (uint32_t)__shfl((int)at, 0, kWave);
+                    lds_barrier();
+                    more = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag);
+                    if (st.cnt + more <= (uint32_t)B) break;
+                    sel_sort(S, st, src, K);                // (leaves room for NT: this happens once)
+                }
+                if (ok) {
+                    const uint32_t o = st.cnt + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                    S.key[o] = cost_key(v); S.pos[o] = (unsigned long long)entry(u);
+                }
+                st.cnt += more;
+            }
+        }
+    }
+    return nan;
+}
+
+// Words that the blocks of a launch share.  All zero between launches (the last block leaves them so).
+struct SelControl {
+    uint32_t done, cursor, nan, pad;
+    double bound;                      // a cost with K entries at or below it, left by a launch over a sample
+};
+
+constexpr int kSelThreads = 1024, kSelBuffer = 2048;
+constexpr long long kSelTile = (long long)kSelThreads * kSelUnroll;
+// Blocks of a launch: a tile each, at most one per compute unit (a block keeps 64 KiB of loads in flight, and the registers
+// of 1024 threads with 8 costs at hand and 8 on their way leave no room for a second one).  One block where two tiles are
+// all there is: no lists, no hand-over (10 007 entries: 25 us; the hand-over alone takes 5).
+inline unsigned sel_blocks(long long n) {
+    const long long tiles = (n + kSelTile - 1) / kSelTile;
+    return tiles <= 2 ? 1u : (unsigned)(tiles < 256 ? tiles : 256);
+}
+// Entries that one block may leave for the last one: not cut to K as long as they are few (a sort saved).
+inline __host__ __device__ uint32_t sel_share(int K) {
+    const uint32_t c = 3u * (uint32_t)K + 128u;
+    return c < (uint32_t)kSelBuffer ? c : (uint32_t)kSelBuffer;
+}
+// Long columns are looked at twice: first one entry in 64 (64 in a row, so that whole lines are used), which leaves a
+// bound that some 64 K entries pass; without it every one of the blocks keeps K of its own, and the last block walks
+// them all.  A second launch and its wait for the first cost some 40 us: 1.3 M entries, K = 64 (159 lists) takes 41 us of
+// kernel time without, and K * blocks of 32 768 is where the last block's walk takes as long as the sample.
+constexpr long long kSelSample = 64;
+inline bool sel_sampled(long long n, int K) { return n >= (1ll << 22) || (n >= (1ll << 18) && (long long)sel_blocks(n) * K >= 32768); }
+
+// Measured (a whole p2_topk_device call, host wait included; before: one wavefront per block inserting into a sorted list
+// of K, then one wavefront walking all the lists): 10 007 entries, K = 10: 89 -> 25 us, of which the kernel is 15, a chain
+// of some ten memory and barrier latencies; 1.3 M of stride 3, K = 64: 1190 -> 56 us, half of it the last block's walk;
+// 50 M, K = 100: 3170 -> 160 us, of which 100 read 400 MB at 4 TB/s (a large copy reaches 4.9) and 40 find the bound.
+// K smallest of a column by all blocks together: every block leaves what it kept, the last one to finish goes through
+// that and writes the positions (or, over a sample, the bound).
+__global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long long n, int K, int sample, int bounded,
+                                                             SelControl* __restrict__ ctl, double* lc, unsigned long long* li,
+                                                             unsigned long long* lp, long long* __restrict__ out_pos, long long n_out,
+                                                             uint32_t* __restrict__ nan_out) {
+    __shared__ SelShared<kSelThreads, kSelBuffer> S;
+    const uint32_t tid = threadIdx.x;
+    SelState st{0u, __longlong_as_double(0x7ff0000000000000ll), ~0ull};
+    if (bounded) st.Tc = ctl->bound;
+    long long first = blockIdx.x, step = gridDim.x;
+    bool last = gridDim.x == 1u, nan = false;
     for (;;) {
-        bool want = valid;
-        if (want && cnt == K) {
-            Item last{L.c[K - 1], L.idx[K - 1], L.pos[K - 1]};
-            want = item_less(mine, last);
+        nan |= sel_consume(S, st, src, n, first, step, (uint32_t)K, bounded != 0);
+        if (last || st.cnt > sel_share(K)) sel_sort(S, st, src, (uint32_t)K);
+        if (last) break;
+        if (nan) __hip_atomic_fetch_or(&ctl->nan, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (tid == 0) S.flag = st.cnt ? __hip_atomic_fetch_add(&ctl->cursor, st.cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        __syncthreads();
+        const uint32_t base = S.flag;
+        for (uint32_t j = tid; j < st.cnt; j += kSelThreads) {
+            const unsigned long long e = S.pos[j];
+            lc[base + j] = key_cost(S.key[j]); li[base + j] = src.idx[e]; lp[base + j] = e;
         }
-        const unsigned long long m = __ballot(want);
-        if (m == 0ull) break;
-        const int src = __ffsll((long long)m) - 1;
-        Item it;
-        it.c = __shfl(mine.c, src, kWave);
-        it.idx = __shfl(mine.idx, src, kWave);
-        it.pos = __shfl(mine.pos, src, kWave);
-        list_insert(L, cnt, K, it, lane);
-        if (lane == src) valid = false;
-    }
-}
-
-// Stage 1: block b keeps the K best of its strided share of the input; stage 2 (one block) merges
-// the block lists.  part_* hold gridDim.x lists of K entries (pos = -1 marks an unused slot).
-__global__ __launch_bounds__(kWave) void k_topk_partial(const double* __restrict__ cost, long long stride,
-                                                        const unsigned long long* __restrict__ index, long long n, int K,
-                                                        double* __restrict__ part_c, unsigned long long* __restrict__ part_i,
-                                                        long long* __restrict__ part_p, uint32_t* __restrict__ nan_flag) {
-    extern __shared__ unsigned char raw[];
-    TopList L;
-    L.c = reinterpret_cast<double*>(raw);
-    L.idx = reinterpret_cast<unsigned long long*>(L.c + K);
-    L.pos = reinterpret_cast<long long*>(L.idx + K);
-    const int lane = threadIdx.x;
-    int cnt = 0;
-    bool nan = false;
-    for (long long t0 = (long long)blockIdx.x * kWave; t0 < n; t0 += (long long)gridDim.x * kWave) {
-        const long long i = t0 + lane;
-        Item mine{0.0, 0ull, i};
-        const bool valid = i < n;
-        if (valid) { mine.c = cost[i * stride]; mine.idx = index[i]; nan |= mine.c != mine.c; }
-        list_offer(L, cnt, K, mine, valid && !(mine.c != mine.c), lane);
-    }
-    if (nan) atomicOr(nan_flag, 1u);
-    __syncthreads();
-    for (int j = lane; j < K; j += kWave) {
-        const size_t o = (size_t)blockIdx.x * K + j;
-        part_c[o] = j < cnt ? L.c[j] : 0.0;
-        part_i[o] = j < cnt ? L.idx[j] : 0ull;
-        part_p[o] = j < cnt ? L.pos[j] : -1ll;
-    }
-}
-
-__global__ __launch_bounds__(kWave) void k_topk_merge(const double* __restrict__ part_c,
-                                                      const unsigned long long* __restrict__ part_i,
-                                                      const long long* __restrict__ part_p, long long total, int K,
-                                                      long long* __restrict__ out_pos, long long n_out) {
-    extern __shared__ unsigned char raw[];
-    TopList L;
-    L.c = reinterpret_cast<double*>(raw);
-    L.idx = reinterpret_cast<unsigned long long*>(L.c + K);
-    L.pos = reinterpret_cast<long long*>(L.idx + K);
-    const int lane = threadIdx.x;
-    int cnt = 0;
-    for (long long t0 = 0; t0 < total; t0 += kWave) {
-        const long long i = t0 + lane;
-        Item mine{0.0, 0ull, -1ll};
-        if (i < total) mine = Item{part_c[i], part_i[i], part_p[i]};
-        list_offer(L, cnt, K, mine, i < total && mine.pos >= 0, lane);
-    }
-    __syncthreads();
-    for (int j = lane; j < n_out; j += kWave) out_pos[j] = j < cnt ? L.pos[j] : -1ll;
-}
-
-// Many small selections in one launch: block b does job b from start to end (the list of K best of
-// jobs[b].n entries) and writes the positions itself.
-__global__ __launch_bounds__(kWave) void k_topk_jobs(const DevTopkJob* __restrict__ jobs) {
-    extern __shared__ unsigned char raw[];
-    const DevTopkJob J = jobs[blockIdx.x];
-    const int K = J.k;
-    TopList L;
-    L.c = reinterpret_cast<double*>(raw);
-    L.idx = reinterpret_cast<unsigned long long*>(L.c + K);
-    L.pos = reinterpret_cast<long long*>(L.idx + K);
-    const int lane = threadIdx.x;
-    int cnt = 0;
-    bool nan = false;
-    for (long long t0 = 0; t0 < J.n; t0 += kWave) {
-        const long long i = t0 + lane;
-        Item mine{0.0, 0ull, i};
-        const bool valid = i < J.n;
-        if (valid) { mine.c = J.cost[i * J.stride]; mine.idx = J.index[i]; nan |= mine.c != mine.c; }
-        list_offer(L, cnt, K, mine, valid && !(mine.c != mine.c), lane);
-    }
-    if (nan) atomicOr(J.nan_flag, 1u);
-    __syncthreads();
-    const long long n_out = K < J.n ? K : J.n;
-    for (int j = lane; j < n_out; j += kWave) J.out_pos[j] = j < cnt ? L.pos[j] : -1ll;
-}
-
-// Many large selections in two launches: job j is cut into kBigParts strided shares, block (part, j) keeps the K best
-// of its share in the job's piece of the scratch buffer (kBigParts lists of max_k entries), then block j of the
-// second launch merges the job's lists.
-constexpr int kBigParts = 64;
-__global__ __launch_bounds__(kWave) void k_topk_big_partial(const DevTopkJob* __restrict__ jobs, int max_k, double* __restrict__ part_c,
-                                                            unsigned long long* __restrict__ part_i, long long* __restrict__ part_p) {
-    extern __shared__ unsigned char raw[];
-    const DevTopkJob J = jobs[blockIdx.y];
-    const int K = J.k;
-    TopList L;
-    L.c = reinterpret_cast<double*>(raw);
-    L.idx = reinterpret_cast<unsigned long long*>(L.c + K);
-    L.pos = reinterpret_cast<long long*>(L.idx + K);
-    const int lane = threadIdx.x;
-    int cnt = 0;
-    bool nan = false;
-    for (long long t0 = (long long)blockIdx.x * kWave; t0 < J.n; t0 += (long long)kBigParts * kWave) {
-        const long long i = t0 + lane;
-        Item mine{0.0, 0ull, i};
-        const bool valid = i < J.n;
-        if (valid) { mine.c = J.cost[i * J.stride]; mine.idx = J.index[i]; nan |= mine.c != mine.c; }
-        list_offer(L, cnt, K, mine, valid && !(mine.c != mine.c), lane);
-    }
-    if (nan) atomicOr(J.nan_flag, 1u);
-    __syncthreads();
-    const size_t o0 = ((size_t)blockIdx.y * kBigParts + blockIdx.x) * (size_t)max_k;
-    for (int j = lane; j < K; j += kWave) {
-        part_c[o0 + j] = j < cnt ? L.c[j] : 0.0;
-        part_i[o0 + j] = j < cnt ? L.idx[j] : 0ull;
-        part_p[o0 + j] = j < cnt ? L.pos[j] : -1ll;
-    }
-}
-__global__ __launch_bounds__(kWave) void k_topk_big_merge(const DevTopkJob* __restrict__ jobs, int max_k, const double* __restrict__ part_c,
-                                                          const unsigned long long* __restrict__ part_i,
-                                                          const long long* __restrict__ part_p) {
-    extern __shared__ unsigned char raw[];
-    const DevTopkJob J = jobs[blockIdx.x];
-    const int K = J.k;
-    TopList L;
-    L.c = reinterpret_cast<double*>(raw);
-    L.idx = reinterpret_cast<unsigned long long*>(L.c + K);
-    L.pos = reinterpret_cast<long long*>(L.idx + K);
-    const int lane = threadIdx.x;
-    int cnt = 0;
-    const size_t o0 = (size_t)blockIdx.x * kBigParts * (size_t)max_k;
-    for (int part = 0; part < kBigParts; ++part)
-        for (int t0 = 0; t0 < K; t0 += kWave) {
-            const int j = t0 + lane;
-            Item mine{0.0, 0ull, -1ll};
-            if (j < K) { const size_t o = o0 + (size_t)part * max_k + j; mine = Item{part_c[o], part_i[o], part_p[o]}; }
-            list_offer(L, cnt, K, mine, j < K && mine.pos >= 0, lane);
+        __syncthreads();                                 // (the block's stores have been made; thread 0 hands them over)
+        if (tid == 0) {
+            __threadfence();
+            S.flag = __hip_atomic_fetch_add(&ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence();
         }
-    __syncthreads();
-    const long long n_out = K < J.n ? K : J.n;
-    for (int j = lane; j < n_out; j += kWave) J.out_pos[j] = j < cnt ? L.pos[j] : -1ll;
+        __syncthreads();
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag) != gridDim.x - 1u) return;
+        // the last block goes through what all of them have left, its own entries among it; its bound still holds
+        n = (long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&ctl->cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        st.cnt = 0u;
+        src = SelSource{lc, li, lp, 1, 1};
+        first = 0; step = 1; bounded = 0;
+        last = true;
+    }
+    if (!sample)
+        for (long long j = tid; j < n_out; j += kSelThreads) out_pos[j] = j < (long long)st.cnt ? (long long)src.position(S.pos[j]) : -1ll;
+    const bool any = __syncthreads_or(nan ? 1 : 0) != 0;
+    if (tid == 0) {
+        ctl->bound = sample && st.cnt == (uint32_t)K ? key_cost(S.key[K - 1]) : __longlong_as_double(0x7ff0000000000000ll);
+        const uint32_t other = __hip_atomic_load(&ctl->nan, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (nan_out && (other || any)) *nan_out = 1u;
+        ctl->nan = 0u; ctl->done = 0u; ctl->cursor = 0u;
+    }
+}
+
+// Many selections in one launch: block b does job b from start to end.  A tile of a short list (at most 2048 entries,
+// K <= 256) is 256 threads wide, so that several jobs share a compute unit; longer lists take 1024.
+template <int NT, int B>
+__global__ __launch_bounds__(NT) void k_topk_jobs(const DevTopkJob* __restrict__ jobs) {
+    __shared__ SelShared<NT, B> S;
+    const DevTopkJob J = jobs[blockIdx.x];
+    SelState st{0u, __longlong_as_double(0x7ff0000000000000ll), ~0ull};
+    const SelSource src{J.cost, J.index, nullptr, J.stride, 1};
+    if (sel_consume(S, st, src, J.n, 0, 1, (uint32_t)J.k, false)) atomicOr(J.nan_flag, 1u);
+    sel_sort(S, st, src, (uint32_t)J.k);
+    const long long n_out = J.k < J.n ? J.k : J.n;
+    for (long long j = threadIdx.x; j < n_out; j += NT) J.out_pos[j] = j < (long long)st.cnt ? (long long)S.pos[j] : -1ll;
 }
 
 // Device memory -> pinned host memory, written by the GPU itself in 16-byte words.
@@ -249,13 +591,6 @@ __global__ __launch_bounds__(256) void k_copy_out3(CopyOut a, CopyOut b, CopyOut
         else if (i < ab) b.dst[i - a.n16] = b.src[i - a.n16];
         else c.dst[i - ab] = c.src[i - ab];
     }
-}
-
-inline unsigned topk_blocks(long long n) {
-    long long b = (n + 64 * 16 - 1) / (64 * 16);      // at least 16 tiles per block
-    if (b < 1) b = 1;
-    if (b > 2048) b = 2048;
-    return (unsigned)b;
 }
 
 }  // namespace
@@ -290,11 +625,10 @@ hipError_t launch_rank_sort(const unsigned long long* valid, const unsigned long
     return hipGetLastError();
 }
 
-size_t topk_scratch_bytes(long long n, int k) { return (size_t)topk_blocks(n) * (size_t)k * 24; }
-
-hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, hipStream_t stream) {
+hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, long long max_n, hipStream_t stream) {
     if (n_jobs == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_topk_jobs, dim3(n_jobs), dim3(kWave), (size_t)max_k * 24, stream, jobs);
+    if (max_k <= 256 && max_n <= 2048) hipLaunchKernelGGL((k_topk_jobs<256, 512>), dim3(n_jobs), dim3(256), 0, stream, jobs);
+    else hipLaunchKernelGGL((k_topk_jobs<kSelThreads, kSelBuffer>), dim3(n_jobs), dim3(kSelThreads), 0, stream, jobs);
     return hipGetLastError();
 }
 
@@ -318,54 +652,49 @@ hipError_t launch_gather_rows(const DevGatherSeg* segs, unsigned n_segs, const p
     return hipGetLastError();
 }
 
-size_t topk_big_scratch_bytes(unsigned n_jobs, int max_k) { return (size_t)n_jobs * kBigParts * (size_t)max_k * 24; }
-
-hipError_t launch_topk_big(const DevTopkJob* jobs, unsigned n_jobs, int max_k, void* scratch, hipStream_t stream) {
-    if (n_jobs == 0) return hipSuccess;
-    const size_t per = (size_t)n_jobs * kBigParts * (size_t)max_k;
-    double* pc = reinterpret_cast<double*>(scratch);
-    unsigned long long* pi = reinterpret_cast<unsigned long long*>(pc + per);
-    long long* pp = reinterpret_cast<long long*>(pi + per);
-    const size_t lds = (size_t)max_k * 24;
-    hipLaunchKernelGGL(k_topk_big_partial, dim3(kBigParts, n_jobs), dim3(kWave), lds, stream, jobs, max_k, pc, pi, pp);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_topk_big_merge, dim3(n_jobs), dim3(kWave), lds, stream, jobs, max_k, pc, pi, pp);
-    return hipGetLastError();
-}
+size_t topk_control_bytes() { return sizeof(SelControl); }
+size_t topk_scratch_bytes(long long n, int k) { return (size_t)sel_blocks(n) * (size_t)sel_share(k) * 24; }
 
 hipError_t launch_topk(const double* cost, long long stride, const unsigned long long* index, long long n, int k,
-                       long long* out_pos, void* scratch, uint32_t* nan_flag, hipStream_t stream) {
+                       long long* out_pos, void* scratch, void* control, uint32_t* nan_out, hipStream_t stream) {
     if (n <= 0 || k <= 0) return hipSuccess;
-    const unsigned blocks = topk_blocks(n);
-    double* pc = reinterpret_cast<double*>(scratch);
-    unsigned long long* pi = reinterpret_cast<unsigned long long*>(pc + (size_t)blocks * k);
-    long long* pp = reinterpret_cast<long long*>(pi + (size_t)blocks * k);
-    const size_t lds = (size_t)k * 24;
-    hipLaunchKernelGGL(k_topk_partial, dim3(blocks), dim3(kWave), lds, stream, cost, stride, index, n, k, pc, pi, pp, nan_flag);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const long long n_out = k < n ? k : n;
-    hipLaunchKernelGGL(k_topk_merge, dim3(1), dim3(kWave), lds, stream, pc, pi, pp, (long long)blocks * k, k, out_pos, n_out);
+    const unsigned blocks = sel_blocks(n);
+    const size_t cap = (size_t)blocks * sel_share(k);
+    double* lc = static_cast<double*>(scratch);
+    unsigned long long* li = static_cast<unsigned long long*>(scratch) + cap;
+    SelControl* ctl = static_cast<SelControl*>(control);
+    const bool sampled = sel_sampled(n, k);
+    if (sampled) {
+        const long long m = n / (kSelSample * 64) * 64;
+        hipLaunchKernelGGL(k_topk_column, dim3(sel_blocks(m)), dim3(kSelThreads), 0, stream, SelSource{cost, index, nullptr, stride, kSelSample}, m, k,
+                           1, 0, ctl, lc, li, li + cap, nullptr, 0ll, nullptr);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_topk_column, dim3(blocks), dim3(kSelThreads), 0, stream, SelSource{cost, index, nullptr, stride, 1}, n, k, 0, sampled ? 1 : 0, ctl,
+                       lc, li, li + cap, out_pos, (long long)(k < n ? k : n), nan_out);
     return hipGetLastError();
 }
 
 // ---- selection without any allocation ------------------------------------------------------------
-// The two-stage selection keeps its stage-1 lists (blocks x k entries of 24 bytes) in device memory.  For
-// callers that may not allocate, that memory is a fixed array in the library's device image: every GPU the
+// What the blocks of a selection leave for the last one (24 bytes an entry) and the words they share lie in device
+// memory.  For callers that may not allocate, that memory is a fixed array in the library's device image: every GPU the
 // library runs on holds its own copy at its own address for the life of the process, and all calls on one
 // GPU share it.  Host code never uses the array's name as an address: the device address is asked for once
 // per device and kept.
 constexpr int kFixedTopkMaxK = 64;
-constexpr size_t kFixedTopkListBytes = (size_t)2048 * kFixedTopkMaxK * 24;     // topk_blocks() <= 2048
-static __device__ __align__(256) unsigned char scratch[kFixedTopkListBytes + 256];   // lists, then a flag word
+constexpr size_t kFixedTopkListBytes = (size_t)3 << 20;                        // 256 blocks x 320 entries x 24 B fit
+static __device__ __align__(256) unsigned char scratch[kFixedTopkListBytes + 256];   // lists, then the shared words
 
 namespace {
 constexpr int kMaxGpus = 64;
 std::mutex g_fixed_mutex;
 void* g_fixed_ptr[kMaxGpus] = {nullptr};
 
-__global__ void k_clear_word(uint32_t* w) { *w = 0u; }
+__global__ void k_clear_control(SelControl* c, uint32_t* flag) {
+    *c = SelControl{0u, 0u, 0u, 0u, 0.0};
+    if (flag) *flag = 0u;
+}
 
 // Device address of `scratch` on the current device.
 hipError_t fixed_scratch(void** out) {
@@ -395,13 +724,13 @@ hipError_t launch_topk_fixed(const double* cost, long long stride, const unsigne
     void* base = nullptr;
     hipError_t e = fixed_scratch(&base);
     if (e != hipSuccess) return e;
-    // the flag starts at zero for this call (a fill kernel, so that the call can be recorded into a graph)
-    uint32_t* flag = nan_flag ? nan_flag : reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(base) + kFixedTopkListBytes);
-    hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, stream, flag);
+    // (the shared words are cleared here although a call leaves them clear: calls that overlapped against the rule must
+    //  not spoil the ones after them.  A fill kernel, so that the call can be recorded into a graph)
+    SelControl* ctl = reinterpret_cast<SelControl*>(static_cast<unsigned char*>(base) + kFixedTopkListBytes);
+    hipLaunchKernelGGL(k_clear_control, dim3(1), dim3(1), 0, stream, ctl, nan_flag);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // (stage 1 writes every slot of the lists it hands to stage 2, so the lists need no clearing)
-    return launch_topk(cost, stride, index, n, k, out_pos, base, flag, stream);
+    return launch_topk(cost, stride, index, n, k, out_pos, base, ctl, nan_flag, stream);
 }
 
 }  // namespace p2

@@ -1,0 +1,67 @@
+"""The selection kernels at the sizes where their walk changes: edges of tiles, one block or many, a sampled bound or none,
+buffers that overflow, costs that a histogram does not tell apart."""
+import numpy as np
+import pytest
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2110_10548_amd import binding
+    binding.lib()
+    return binding
+
+
+def _costs(kind, n, rng):
+    if kind == "random":
+        c = rng.normal(size=n)
+        if n > 2:
+            c[n // 2], c[n - 1] = -np.inf, np.inf
+        return c
+    if kind == "ties":
+        return np.round(rng.random(n), 2)
+    if kind == "falling":
+        return np.arange(n, 0, -1).astype(np.float64)
+    c = np.zeros(n)                      # nothing but zeros of both signs: the candidate indices decide
+    c[::3] = -0.0
+    return c
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,kind", [(1, 1, "random"), (65, 64, "ties"), (1023, 1024, "random"), (8192, 7, "random"), (8193, 300, "zeros"),
+                                      (16384, 1024, "random"), (16385, 1024, "falling"), (100003, 513, "ties"), (262144, 1024, "random"),
+                                      (300001, 128, "zeros"), (4194304, 33, "random"), (4200001, 1000, "falling")])
+def test_selection_at_the_edges_of_its_walk(B, n, k, kind):
+    import torch
+    rng = np.random.default_rng(n + k)
+    cost, index = _costs(kind, n, rng), rng.permutation(n).astype(np.int64)
+    want = np.lexsort((np.arange(n), index, cost))[:k]
+    wide = np.zeros((n, 3))
+    wide[:, 2] = cost
+    di = torch.from_numpy(index).cuda()
+    out = torch.full((min(k, n),), -5, dtype=torch.int64, device="cuda")
+    for data, stride, shift in ((cost, 1, 0), (wide, 3, 16)):
+        dc = torch.from_numpy(data).cuda()
+        for _ in range(2):               # (the second call finds the words that the blocks share as the first one left them)
+            B.p2_topk_device(dc.data_ptr() + shift, stride, di.data_ptr(), n, k, out.data_ptr())
+            assert np.array_equal(out.cpu().numpy(), want)
+        if k <= 64:
+            out.fill_(-5)
+            B.p2_topk_device_noalloc(dc.data_ptr() + shift, stride, di.data_ptr(), n, k, out.data_ptr())
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("topk", [1, 300])
+def test_shortlists_are_the_heads_of_the_sorted_lists(B, topk):
+    """Both block widths of the per-query selections (few short lists, long lists), several message sizes."""
+    links = dict(bw=[25e9, 100e9, 300e9], alpha=[20e-6, 10e-6, 5e-6])
+    for card, max_len in (([4, 2, 4], 4), ([2, 4, 8], 5)):
+        n = int(np.prod(card))
+        q = dict(card=card, axes=[n], placement=[card], reduce_axes=[0], max_len=max_len, **links)
+        msg = [1e6, 3e7, 5e8]
+        full, short = B.p2_synthesize_batch([q], msg)[0], B.p2_synthesize_batch([dict(q, topk=topk)], msg)[0]
+        kk = min(topk, len(full["programs"]))
+        for m in range(len(msg)):
+            want = np.lexsort((full["programs"]["index"], full["cost"][:, m]))[:kk]
+            assert np.array_equal(short["programs"]["index"][m * kk:(m + 1) * kk], full["programs"]["index"][want])
