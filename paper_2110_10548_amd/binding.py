@@ -203,8 +203,20 @@ def p2_num_patterns(card, axes, placement, reduce_axes, form_mask=7, hierarchy=0
     return npat.value
 
 
+_STATS_FIELDS = tuple(k for k, _ in p2_stats._fields_)
+_STATS_DTYPE = np.dtype(p2_stats)
+
+
 def _stats_dict(s):
-    return {k: getattr(s, k) for k, _ in p2_stats._fields_}
+    return {k: getattr(s, k) for k in _STATS_FIELDS}
+
+
+# Rows that a first call has room for where the number of valid programs is not bounded beforehand.  A call without room
+# evaluates every candidate and hands back only the number of rows, and the evaluation is all but the whole of a call
+# (one query of 8 devices: 165 us with a sizing call, 85 without).  The room is memory that nobody touches until rows
+# are written to it, so it may be generous: four levels of synthesis hierarchy have 83 920 valid programs of six
+# instructions.  Longer lists still take the second call.
+_FIRST_ROWS = 1 << 18
 
 
 class Batch:
@@ -228,23 +240,22 @@ class Batch:
         self.n_msg = len(self._msg)
         self._offs = np.zeros(self.nq + 1, dtype=np.int64)
         self._stats = (p2_stats * self.nq)()
-        # with a shortlist asked for in every query the number of rows is bounded beforehand, and the
-        # first call has room for them; otherwise a first call without room returns the counts
+        # with a shortlist asked for in every query the number of rows is bounded beforehand
         topks = [int(q.get("topk", 0)) for q in queries]
-        self._alloc(sum(topks) * self.n_msg if all(t > 0 for t in topks) and self.n_msg > 0 else 0)
+        self._alloc(sum(topks) * self.n_msg if all(t > 0 for t in topks) and self.n_msg > 0 else _FIRST_ROWS)
 
     def _alloc(self, cap):
         self.cap = cap
         self._progs = np.zeros(max(cap, 1), dtype=PROGRAM_DTYPE)
         self._cost = np.zeros((max(cap, 1), max(self.n_msg, 1)), dtype=np.float64)
+        self._args = (self._arr, self.nq, _p(self._msg, C.c_double), self.n_msg,
+                      self._progs.ctypes.data_as(C.c_void_p) if cap else None,
+                      _p(self._cost, C.c_double) if cap else None, cap, _p(self._offs, C.c_int64), self._stats)
 
     def run_raw(self):
         """One p2_synthesize_batch call (two if the output buffers had to grow)."""
         while True:
-            rc = lib().p2_synthesize_batch(self._arr, self.nq, _p(self._msg, C.c_double), self.n_msg,
-                                           self._progs.ctypes.data_as(C.c_void_p) if self.cap else None,
-                                           _p(self._cost, C.c_double) if self.cap else None, self.cap,
-                                           _p(self._offs, C.c_int64), self._stats)
+            rc = lib().p2_synthesize_batch(*self._args)
             if rc == P2_ENOSPC or (rc == P2_OK and self.cap == 0 and self._offs[self.nq] > 0):
                 self._alloc(int(self._offs[self.nq]))
                 continue
@@ -252,12 +263,12 @@ class Batch:
             return
 
     def results(self):
-        out = []
-        for i in range(self.nq):
-            a, b = int(self._offs[i]), int(self._offs[i + 1])
-            out.append({"programs": self._progs[a:b].copy(), "cost": self._cost[a:b, :self.n_msg].copy(),
-                        "stats": _stats_dict(self._stats[i])})
-        return out
+        # one copy of all rows (the buffers are written again by the next call), a piece of it per query
+        offs = self._offs.tolist()
+        progs, cost = self._progs[:offs[-1]].copy(), self._cost[:offs[-1], :self.n_msg].copy()
+        names = _STATS_FIELDS
+        return [{"programs": progs[a:b], "cost": cost[a:b], "stats": dict(zip(names, row))}
+                for a, b, row in zip(offs, offs[1:], np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist())]
 
     def run(self):
         self.run_raw()
@@ -293,12 +304,15 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
         return lib().p2_synthesize(C.byref(h.c), _p(axes_a, C.c_int32), len(axes_a), _p(pl, C.c_int32), _p(red, C.c_int32),
                                    len(red), max_len, _p(msg, C.c_double), n_msg, C.byref(opt), progs_p, cost_p, cap_,
                                    C.byref(count), C.byref(cands), C.byref(st))
-    if cap is None:
-        _check(call(None, None, 0), allow=(P2_ENOSPC,))
-        cap = count.value
-    progs = np.zeros(max(cap, 1), dtype=PROGRAM_DTYPE)
-    cost = np.zeros((max(cap, 1), max(n_msg, 1)), dtype=np.float64)
-    _check(call(progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double), cap))
+    rows = cap if cap is not None else topk * n_msg if topk > 0 and n_msg > 0 else _FIRST_ROWS
+    while True:
+        progs = np.zeros(max(rows, 1), dtype=PROGRAM_DTYPE)
+        cost = np.zeros((max(rows, 1), max(n_msg, 1)), dtype=np.float64)
+        rc = call(progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double), rows)
+        if rc != P2_ENOSPC or cap is not None:
+            break
+        rows = count.value
+    _check(rc)
     n = count.value
     return {"programs": progs[:n].copy(), "cost": cost[:n, :n_msg].copy(), "candidates": cands.value,
             "stats": _stats_dict(st)}
