@@ -6,6 +6,7 @@ or __graft_entry__.build()).
 """
 import ctypes as C
 import os
+import threading
 
 import numpy as np
 
@@ -212,11 +213,22 @@ def _stats_dict(s):
 
 
 # Rows that a first call has room for where the number of valid programs is not bounded beforehand.  A call without room
-# evaluates every candidate and hands back only the number of rows, and the evaluation is all but the whole of a call
-# (one query of 8 devices: 165 us with a sizing call, 85 without).  The room is memory that nobody touches until rows
-# are written to it, so it may be generous: four levels of synthesis hierarchy have 83 920 valid programs of six
-# instructions.  Longer lists still take the second call.
-_FIRST_ROWS = 1 << 18
+# evaluates every candidate and hands back only the number of rows, and the evaluation is all but the whole of a call.
+# Four levels of synthesis hierarchy have 83 920 valid programs of six instructions; longer lists take a second call.
+_FIRST_ROWS = 1 << 17
+_FIRST_ROWS_PER_QUERY = 4096           # (in a batch: three levels, five instructions have 2 549)
+_own = threading.local()               # rows of this thread's last single-query call: results are copies of them
+
+
+def _room(rows, n_msg):
+    """Buffers for so many rows, the ones of the thread's last call where they are large enough (a fresh mapping of the
+    first call's room costs more than evaluating a small query)."""
+    if getattr(_own, "rows", 0) < rows or _own.cost.shape[1] != n_msg:
+        progs, cost = np.zeros(rows, dtype=PROGRAM_DTYPE), np.zeros((rows, n_msg), dtype=np.float64)
+        if rows > _FIRST_ROWS:
+            return progs, cost
+        _own.progs, _own.cost, _own.rows = progs, cost, rows
+    return _own.progs, _own.cost
 
 
 class Batch:
@@ -242,7 +254,8 @@ class Batch:
         self._stats = (p2_stats * self.nq)()
         # with a shortlist asked for in every query the number of rows is bounded beforehand
         topks = [int(q.get("topk", 0)) for q in queries]
-        self._alloc(sum(topks) * self.n_msg if all(t > 0 for t in topks) and self.n_msg > 0 else _FIRST_ROWS)
+        self._alloc(sum(topks) * self.n_msg if all(t > 0 for t in topks) and self.n_msg > 0
+                    else min(_FIRST_ROWS_PER_QUERY * self.nq, 2 * _FIRST_ROWS))
 
     def _alloc(self, cap):
         self.cap = cap
@@ -306,8 +319,7 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
                                    C.byref(count), C.byref(cands), C.byref(st))
     rows = cap if cap is not None else topk * n_msg if topk > 0 and n_msg > 0 else _FIRST_ROWS
     while True:
-        progs = np.zeros(max(rows, 1), dtype=PROGRAM_DTYPE)
-        cost = np.zeros((max(rows, 1), max(n_msg, 1)), dtype=np.float64)
+        progs, cost = _room(max(rows, 1), max(n_msg, 1))
         rc = call(progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double), rows)
         if rc != P2_ENOSPC or cap is not None:
             break
@@ -366,6 +378,7 @@ def p2_measure_lds_peak(reps=5, stream=None):
 
 
 def p2_release_thread():
+    _own.__dict__.clear()
     _check(lib().p2_release_thread())
 
 

@@ -314,10 +314,27 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // of 8192 at the most, some 40 us); longer lists are selected from by the whole chip, one query at a time.
 constexpr size_t kTopkJobMax = 1 << 18;
 
+// Engine AUTO walks candidate spaces of at most this many programs index by index ...
+constexpr unsigned long long kWalkMax = 1ull << 30;
+// ... where the shared-prefix engine can (its kernels need at most 64 devices and power-of-two patterns).  What is left
+// for the compact engine, one candidate per lane with its state in LDS, is faster enumerated by size with pruning once the
+// candidates or the states are many: the enumeration takes some 200 us plus 70 us a level whatever the candidates (3 x 4 x 6
+// devices, 4.2 M programs: 0.55 ms against 14.3 ms; 16 x 12, 168 420: 0.59 against 11.6; 12 x 12, 420: 0.32 against
+// 0.70), the compact engine less than that only for few devices and candidates (6 x 8 devices, 168 420 programs: 0.37 ms
+// against 0.47; 3.4 M: 1.25 against 0.56; 3 x 4, 3.4 M: 0.32 against 0.52; 80 devices, 30 programs: 0.28 against 0.27).
+bool pruned_is_faster(const p2::Plan& pl) {
+    bool shared = pl.R <= 64;
+    for (const p2::Pattern& p : pl.patterns) shared = shared && p2::reg_shape_of(p.g, p.s, p.master, 6) >= 0;
+    if (shared) return false;
+    if (pl.R > 64) return pl.n_candidates >= 100;
+    return pl.n_candidates * (unsigned long long)pl.R >= 80000000ull;
+}
+
 struct QueryRun {
     p2::Plan plan;
     int engine = P2_ENGINE_LITERAL;       // engine evaluating the bulk (LITERAL or COMPACT)
     bool frontier = false;                // enumeration by size with pruning instead of index by index
+    bool flat_counts = false;             // ... in place of a walk (engine AUTO): the stats count what a walk executes
     bool regs = false;                    // per-candidate small-group engine (steps computed in registers)
     bool shared = false;                  // shared-prefix engine (the common instructions of a group applied once)
     bool auto_groups = false;             // its handed-over groups are picked up by the device-driven literal launch
@@ -397,9 +414,12 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         } else if (want == P2_ENGINE_LITERAL) {
             if (!lit_ok) return fail(P2_EUNSUPPORTED, "state too large for the literal engine");
             runs[i].engine = P2_ENGINE_LITERAL;
-        } else if (want == P2_ENGINE_FRONTIER || (want == P2_ENGINE_AUTO && pl.n_candidates > (1ull << 30))) {
+        } else if (want == P2_ENGINE_FRONTIER || (want == P2_ENGINE_AUTO && pl.n_candidates > kWalkMax)) {
             runs[i].engine = P2_ENGINE_COMPACT;      // its programs are costed like the compact engine's
             runs[i].frontier = true;
+        } else if (want == P2_ENGINE_AUTO && pruned_is_faster(pl)) {
+            runs[i].engine = P2_ENGINE_COMPACT;
+            runs[i].frontier = runs[i].flat_counts = true;
         } else if (want == P2_ENGINE_COMPACT || want == P2_ENGINE_AUTO || want == P2_ENGINE_SMALL || want == P2_ENGINE_SHARED) {
             // power-of-two patterns: the shared-prefix engine holds up to 64 devices, the per-candidate
             // small-group engine up to 32 devices and 32 chunks
@@ -883,6 +903,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         std::vector<int32_t> members;
         size_t off_valid = 0, off_share = 0;     // element offsets into f_rank, f_share
         uint32_t n_valid = 0, n_goal_literal = 0;
+        unsigned long long flat_instr = 0;       // instructions that a walk of every candidate applies, over the alphabet's size
     };
     std::vector<Enum> enums;
     for (int i = 0; i < n_queries; ++i) {
@@ -896,7 +917,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             const Plan& o = runs[enums[e].leader].plan;
             if (o.R != pl.R || o.k != pl.k || o.max_len != pl.max_len || o.alphabet != pl.alphabet || o.n_ops != pl.n_ops ||
                 o.patterns.size() != pl.patterns.size() || o.n_candidates != pl.n_candidates ||
-                o.max_row_classes != pl.max_row_classes || o.frontier_pairs != pl.frontier_pairs)
+                o.max_row_classes != pl.max_row_classes || o.frontier_pairs != pl.frontier_pairs || runs[enums[e].leader].flat_counts != r.flat_counts)
                 continue;
             bool eq = true;
             for (int t = 0; t < pl.n_ops && eq; ++t) eq = o.ops[t] == pl.ops[t];
@@ -928,6 +949,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         const Plan& pl = r.plan;
         const int n_share = (int)E.members.size();
         const size_t sum_doubles = n_msg > 0 ? (size_t)2 * n_share : 0;      // per prefix / per goal
+        const size_t step_doubles = r.flat_counts ? 2 * sum_doubles : sum_doubles;      // per child: what its step adds
         const DevQuery* dq = reinterpret_cast<const DevQuery*>(db + r.off_query);
         const size_t sw = frontier_state_words(pl.R, pl.k);
         // words of a device's (chunk set, mask) pair, and the devices that the alphabet's patterns visit per prefix
@@ -966,10 +988,17 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             P2_HIP(hipStreamSynchronize(S.stream));
             n_l = 1;
         }
+        uint32_t goals_before = 0;                   // programs of the level's length
+        auto behind = [&](int len) {                 // candidates behind a prefix of len instructions and one more
+            unsigned long long per = 0, power = 1;
+            for (int l = len; l < pl.max_len; ++l) { per += power; power *= (unsigned long long)pl.alphabet; }
+            return per;
+        };
         void* gs = nullptr;
         const int handover = fp == P2_FRONTIER_PAIRS_TWO_HANDOVER ? 1 : 0;
         bool ctr_clean = true;                       // (all of the counters were cleared above)
-        for (int len = 0; len < pl.max_len && (n_c > 0 || n_c2 > 0 || n_l > 0); ++len) {
+        int len = 0;
+        for (; len < pl.max_len && (n_c > 0 || n_c2 > 0 || n_l > 0); ++len) {
             const int keep = len + 1 < pl.max_len ? 1 : 0;
             size_t cap_c = std::max<size_t>(1024, ((size_t)n_c + n_c2) * pl.alphabet / 8);
             size_t cap_l = std::max<size_t>(1024, ((size_t)n_l + n_c2 / 8) * pl.alphabet / 2);
@@ -1093,6 +1122,9 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                 S.prof_state_bytes += planes * pl.R * pair_words * 4.0;
                 S.prof_lane_ops += planes * pattern_members * pair_words * 4.0;
             }
+            // A walk applies, to every candidate that starts with a valid prefix of this length, one more instruction
+            // (a program that has reached the goal is not valid with one more: every rule fails there).
+            E.flat_instr += behind(len) * ((unsigned long long)n_c + n_c2 + n_l + goals_before);
             const uint32_t n_surv = (uint32_t)hctr->surv_goal, n_surv_l = hctr->n_surv_literal;
             const uint32_t n_goal_pair = (uint32_t)(hctr->surv_goal >> 32), n_goal_lit = hctr->n_goal, n_goal = n_goal_pair + n_goal_lit;
             const uint32_t n_prefix = (uint32_t)hctr->pref_pref2, n_prefix2 = (uint32_t)(hctr->pref_pref2 >> 32), n_plit = hctr->n_prefix_literal;
@@ -1117,9 +1149,9 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             P2_HIP(S.f_states2[nxt].ensure(std::max<size_t>(t2, 1) * sw * 8));
             P2_HIP(S.f_hash[nxt].ensure(std::max<size_t>(t1, 1) * sizeof(unsigned long long)));
             P2_HIP(S.f_hash2[nxt].ensure(std::max<size_t>(t2, 1) * sizeof(unsigned long long)));
-            P2_HIP(S.f_delta[0].ensure(std::max<size_t>((size_t)t1 * sum_doubles, 1) * 8));
-            P2_HIP(S.f_delta[1].ensure(std::max<size_t>((size_t)t2 * sum_doubles, 1) * 8));
-            P2_HIP(S.f_delta[2].ensure(std::max<size_t>((size_t)tg * sum_doubles, 1) * 8));
+            P2_HIP(S.f_delta[0].ensure(std::max<size_t>((size_t)t1 * step_doubles, 1) * 8));
+            P2_HIP(S.f_delta[1].ensure(std::max<size_t>((size_t)t2 * step_doubles, 1) * 8));
+            P2_HIP(S.f_delta[2].ensure(std::max<size_t>((size_t)tg * step_doubles, 1) * 8));
             P2_HIP(S.f_ssurv.ensure(std::max<size_t>(n_ss, 1) * sizeof(FrontSurvivor)));
             for (int li = 0; li < 2; ++li) P2_HIP(S.f_childof[li].ensure(std::max<size_t>((size_t)n_s[li] * pl.alphabet, 1) * sizeof(uint32_t)));
             if (n_ss > 0) P2_HIP(S.spans.begin(SpanRec::kGroup, S.stream));
@@ -1146,6 +1178,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             lv.next_hash1 = static_cast<unsigned long long*>(S.f_hash[nxt].p); lv.next_hash2 = static_cast<unsigned long long*>(S.f_hash2[nxt].p);
             lv.delta1 = static_cast<double*>(S.f_delta[0].p); lv.delta2 = static_cast<double*>(S.f_delta[1].p);
             lv.delta_goal = static_cast<double*>(S.f_delta[2].p);
+            lv.factors = r.flat_counts ? 1 : 0;
             if (n_ss > 0) P2_HIP(S.spans.begin(SpanRec::kMaterialize, S.stream));
             P2_HIP(launch_front_materialize(reinterpret_cast<const DevQuery*>(db), pl.R, pl.k, lv, S.stream));
             if (n_ss > 0) {
@@ -1195,7 +1228,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             px.child_of1 = static_cast<const uint32_t*>(S.f_childof[0].p); px.child_of2 = static_cast<const uint32_t*>(S.f_childof[1].p);
             px.rep1 = grouped_next[0] ? static_cast<const uint32_t*>(S.f_rep[0].p) : nullptr;
             px.rep2 = grouped_next[1] ? static_cast<const uint32_t*>(S.f_rep[1].p) : nullptr;
-            px.delta1 = lv.delta1; px.delta2 = lv.delta2; px.delta_goal = lv.delta_goal;
+            px.delta1 = lv.delta1; px.delta2 = lv.delta2; px.delta_goal = lv.delta_goal; px.factors = lv.factors;
             px.next_entries1 = static_cast<FrontEntry*>(S.f_entries[nxt].p); px.next_sid1 = static_cast<uint32_t*>(S.f_sid[nxt].p);
             px.next_sums1 = static_cast<double*>(S.f_sums[nxt].p);
             px.next_entries2 = static_cast<FrontEntry*>(S.f_entries2[nxt].p); px.next_sid2 = static_cast<uint32_t*>(S.f_sid2[nxt].p);
@@ -1212,6 +1245,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                                      static_cast<const FrontSurvivor*>(S.f_surv_literal.p) + n_surv_l_first, n_surv_l - n_surv_l_first, len, keep,
                                      static_cast<FrontEntry*>(S.f_literal[nxt].p), vout_lit, gsums_lit, (int)sum_doubles / 2, dctr, S.stream));
             E.n_valid += n_goal;
+            goals_before = n_goal;
             n_c = keep ? n_prefix : 0;
             n_c2 = keep ? n_prefix2 : 0;
             n_l = keep ? n_plit : 0;
@@ -1219,6 +1253,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             grouped[0] = grouped_next[0]; grouped[1] = grouped_next[1];
             cur = nxt;
         }
+        E.flat_instr += behind(len) * goals_before;
         // steps of the last level
         P2_HIP(launch_copy_out(S.h_fctr.p, dctr, sizeof(FrontCounters), S.stream));
         P2_HIP(hipStreamSynchronize(S.stream));
@@ -1582,6 +1617,12 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             s.literal_reruns = r.shared ? (uint64_t)r.n_rerun_groups * (uint64_t)r.plan.alphabet : r.n_rerun;
             s.steps_evaluated = r.shared ? r.evaluated : r.steps;
             s.members_evaluated = r.shared ? r.evaluated_members : r.members;
+            if (r.flat_counts && r.enum_id >= 0) {
+                unsigned long long per_alphabet = 0;
+                for (const Pattern& p : r.plan.patterns) per_alphabet += (unsigned long long)p.g * p.n_groups * r.plan.n_ops;
+                s.steps_executed = enums[r.enum_id].flat_instr * (unsigned long long)r.plan.alphabet;
+                s.member_visits = enums[r.enum_id].flat_instr * per_alphabet;
+            }
             s.valid = r.n_valid; s.group_size = r.plan.R; s.n_patterns = (int32_t)r.plan.patterns.size();
             s.evaluated_with = r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
             s.reserved0 = 0;

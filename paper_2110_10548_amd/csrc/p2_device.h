@@ -287,7 +287,9 @@ struct FrontLevel {
                                    // follows adds up); null: left alone
     uint32_t* next_states1; uint32_t* next_states2;
     unsigned long long* next_hash1; unsigned long long* next_hash2;      // hash of every child's state (zero on entry)
-    double* delta1; double* delta2; double* delta_goal;   // [child][n_share][2]: what the step adds to the cost sums
+    double* delta1; double* delta2; double* delta_goal;   // [child][n_share][2]: what the step adds to the cost sums;
+                                                           // with `factors` [child][n_share][4]: both terms as factors
+    int32_t factors;
 };
 // For the kernel that writes the prefixes of the next level (and the goals) from the survivors of this level's prefixes:
 struct FrontPrefixes {
@@ -300,6 +302,9 @@ struct FrontPrefixes {
     const uint32_t* child_of1; const uint32_t* child_of2;  // [state][instruction] -> child (place of its kind)
     const uint32_t* rep1; const uint32_t* rep2;            // next state lists: child -> the state that stands for it (null: itself)
     const double* delta1; const double* delta2; const double* delta_goal;
+    int32_t factors;               // the steps' terms come as factors: multiplied and added with one rounding, as the kernels
+                                   // do that cost a program by running it (the costs of engine AUTO do not depend on which
+                                   // engine it takes, to the last bit)
     FrontEntry* next_entries1; uint32_t* next_sid1; double* next_sums1;
     FrontEntry* next_entries2; uint32_t* next_sid2; double* next_sums2;
     FrontEntry* next_literal;

@@ -1155,6 +1155,12 @@ __device__ inline void canonical_slot(uint4& a, uint4& b, bool is_row, bool is_m
     if (l1 < l0) { const uint4 t = a; a = b; b = t; }
 }
 
+// What a step adds to query j's two sums: the products, or their factors.
+__device__ inline void put_terms(double* out, int j, bool factors, double a0, double a1, double b0, double b1) {
+    if (factors) { out[4 * j] = a0; out[4 * j + 1] = a1; out[4 * j + 2] = b0; out[4 * j + 3] = b1; }
+    else { out[2 * j] = a0 * a1; out[2 * j + 1] = b0 * b1; }
+}
+
 // A block per survivor of the one-pair and two-pair frontiers at a time: the parent's planes come into LDS with
 // 128-bit loads, the instruction is applied there in place (a lane is (slot, quad) as in the classification; the
 // slots of a wavefront take 8 groups side by side, or share the members of a group where the pattern has fewer
@@ -1361,7 +1367,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
         }
         // ---- the step's time for every query of the enumeration (alpha-beta model: latency steps of the
         //      slowest group's link; bytes through the busiest uplink, from the query's bandwidth rows)
-        double* out = (code == CODE_GOAL ? A.delta_goal : code == CODE_PREFIX2 ? A.delta2 : A.delta1) + (size_t)place * 2 * A.n_share;
+        double* out = (code == CODE_GOAL ? A.delta_goal : code == CODE_PREFIX2 ? A.delta2 : A.delta1) + (size_t)place * (A.factors ? 4 : 2) * A.n_share;
         // Where every group holds the same number of rows c (the usual case), the busiest unit of a hardware level
         // carries c times the largest multiplicity sum of that level's rows, which the row tables carry per pattern:
         // the same maximum, term by term, without walking the rows; a lane per query then.
@@ -1378,8 +1384,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                     best = fmax(best, (double)((long long)c0 * (long long)rw.level_max[pid][l]) * cq.inv_bw[l]);
                 double ring_steps, mult;
                 step_factors(op, P.g, cq.algo, ring_steps, mult);
-                out[2 * j] = ring_steps * cq.alpha[cq.pat[pid].span_level];
-                out[2 * j + 1] = (mult / (double)cq.k) * best;
+                put_terms(out, j, A.factors != 0, ring_steps, cq.alpha[cq.pat[pid].span_level], mult / (double)cq.k, best);
             }
         } else if (A.n_msg > 0) {
             for (int j = wave; j < A.n_share; j += (NT / 64)) {
@@ -1409,8 +1414,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                 if (lane == 0) {
                     double ring_steps, mult;
                     step_factors(op, P.g, cq.algo, ring_steps, mult);
-                    out[2 * j] = ring_steps * cq.alpha[cq.pat[pid].span_level];
-                    out[2 * j + 1] = (mult / (double)cq.k) * best;
+                    put_terms(out, j, A.factors != 0, ring_steps, cq.alpha[cq.pat[pid].span_level], mult / (double)cq.k, best);
                 }
             }
         }
@@ -1554,9 +1558,10 @@ __global__ __launch_bounds__(256) void k_front_prefixes(const DevQuery* __restri
         const uint32_t t = (two ? A.child_of2 : A.child_of1)[(size_t)st * I + sv.digit];
         if (A.n_msg > 0) {
             const double parent = (two ? A.sums2 : A.sums1)[(size_t)sv.entry * per + j];
-            const double step = (code == CODE_GOAL ? A.delta_goal : code == CODE_PREFIX2 ? A.delta2 : A.delta1)[(size_t)t * per + j];
+            const double* delta = code == CODE_GOAL ? A.delta_goal : code == CODE_PREFIX2 ? A.delta2 : A.delta1;
             double* out = code == CODE_GOAL ? A.goal_sums : code == CODE_PREFIX2 ? A.next_sums2 : A.next_sums1;
-            out[(size_t)place * per + j] = parent + step;
+            const size_t d = (size_t)t * per + j;
+            out[(size_t)place * per + j] = A.factors ? fma(delta[2 * d], delta[2 * d + 1], parent) : parent + delta[d];
         }
         if (j != 0) continue;
         const FrontEntry pe = (two ? A.entries2 : A.entries1)[sv.entry];
