@@ -126,6 +126,7 @@ struct FrontSlot {
     DevBuf f_hash[2], f_hash2[2], f_table, f_rep[2], f_replist[2], f_codes[2], f_unk[2];     // search for equal states
     DevBuf f_sid[2], f_sid2[2], f_delta[3], f_childof[2], f_ssurv;                           // prefixes -> states -> children
     DevBuf f_rowcnt[2];                                                                      // per row of codes: how many survivors by kind
+    DevBuf f_lit_parent[2], f_rest;                                                          // literal prefixes: their parents' states
     DevBuf f_walk[2];                                                                        // the last level: states worth a walk
     HostBuf h_fctr;
     SpanRec spans;
@@ -138,7 +139,7 @@ struct FrontSlot {
                          &f_states2[0], &f_states2[1], &f_sums2[0], &f_sums2[1], &f_literal[0], &f_literal[1], &f_surv, &f_surv_literal,
                          &f_unknown, &f_ctr, &lit_scratch, &f_hash[0], &f_hash[1], &f_hash2[0], &f_hash2[1], &f_table, &f_rep[0], &f_rep[1],
                          &f_replist[0], &f_replist[1], &f_codes[0], &f_codes[1], &f_unk[0], &f_unk[1], &f_sid[0], &f_sid[1], &f_sid2[0],
-                         &f_sid2[1], &f_delta[0], &f_delta[1], &f_delta[2], &f_childof[0], &f_childof[1], &f_ssurv, &f_walk[0], &f_walk[1], &f_rowcnt[0], &f_rowcnt[1]};
+                         &f_sid2[1], &f_delta[0], &f_delta[1], &f_delta[2], &f_childof[0], &f_childof[1], &f_ssurv, &f_walk[0], &f_walk[1], &f_rowcnt[0], &f_rowcnt[1], &f_lit_parent[0], &f_lit_parent[1], &f_rest};
         for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
         if (h_fctr.p) (void)hipHostFree(h_fctr.p);
         h_fctr.p = nullptr; h_fctr.cap = 0;
@@ -158,7 +159,7 @@ struct Ctx {
     HostBuf h_gather;
     DevBuf f_finish;                                        // frontier engine: what every query's rows are written from
     HostBuf h_finish;
-    DevBuf f_rank, f_share;                                 // frontier engine: ranks of the valid programs, queries of the enumerations
+    DevBuf f_rank, f_rank_runs, f_share;                                 // frontier engine: ranks of the valid programs, queries of the enumerations
     std::vector<DevBuf> f_evalid, f_egsums;                 // ... per enumeration: valid candidate indices, their cost sums
     FrontSlot slots[kFrontSlots];
     static constexpr int kSpareStreams = 6;
@@ -258,7 +259,7 @@ const std::thread::id g_loader_thread = std::this_thread::get_id();
 
 void Ctx::release() {
     DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_control, &topk_pos,
-                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink};
+                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink};
     for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
     for (auto* v : {&f_evalid, &f_egsums}) {
         for (DevBuf& b : *v) if (b.p) (void)hipFree(b.p);
@@ -975,7 +976,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         // A level: two lists of states (one pair per device; up to two) with n_s entries, of which the distinct ones
         // are judged; two lists of prefixes (n_c, n_c2 entries), each prefix with the index of its state; the
         // literal list (n_l prefixes that are judged from their instructions).
-        uint32_t n_s[2] = {0, 0}, n_c = 0, n_c2 = 0, n_l = 0;
+        uint32_t n_s[2] = {0, 0}, n_c = 0, n_c2 = 0, n_l = 0, n_l_literal = 0;      // (n_l_literal: of those, children of literal prefixes)
         bool grouped[2] = {false, false};            // the state list has been searched for equal states
         if (max_pairs >= 1) {
             P2_HIP(launch_front_init(dq, (uint32_t)i, pl.R, pl.k, static_cast<FrontEntry*>(S.f_entries[cur].p),
@@ -1017,12 +1018,28 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             auto literal_prefixes = [&]() -> int32_t {
                 if (n_l == 0) return P2_OK;
                 P2_HIP(S.f_surv_literal.ensure(cap_l * sizeof(FrontSurvivor)));
-                P2_HIP(S.lit_scratch.ensure(front_literal_scratch_bytes(pl.R, pl.k, std::max(n_l, n_c2))));
-                gs = S.lit_scratch.p;
                 P2_HIP(S.spans.begin(SpanRec::kLiteral, S.stream));
-                P2_HIP(launch_front_classify_literal(dq, pl.R, pl.k, static_cast<const FrontEntry*>(S.f_literal[cur].p), n_l, len, keep ? 0 : 1,
-                                                     static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr, gs,
-                                                     pl.max_row_classes, S.stream));
+                // At the last level the goals behind a prefix that is one AllGather away from a state held in pairs are read off
+                // that state (the lists of the level before are still there: the children's kernel writes no state now).
+                const bool from_pairs = !keep && max_pairs == 2 && len > 0;
+                if (from_pairs) {
+                    P2_HIP(S.lit_scratch.ensure(std::max(front_literal_goals_scratch_bytes(pl.R, pl.k, n_l),
+                                                         n_l_literal > 0 ? front_literal_scratch_bytes(pl.R, pl.k, std::max(n_l, n_c2)) : 0)));
+                    P2_HIP(S.f_rest.ensure((size_t)n_l * sizeof(uint32_t)));
+                    P2_HIP(launch_front_literal_goals(dq, pl.R, pl.k, static_cast<const FrontEntry*>(S.f_literal[cur].p),
+                                                      static_cast<const uint32_t*>(S.f_lit_parent[cur].p), n_l, len,
+                                                      static_cast<const uint32_t*>(S.f_states[cur ^ 1].p), static_cast<const uint32_t*>(S.f_states2[cur ^ 1].p),
+                                                      S.lit_scratch.p, static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr,
+                                                      static_cast<uint32_t*>(S.f_rest.p), S.stream));
+                }
+                if (!from_pairs || n_l_literal > 0) {
+                    P2_HIP(S.lit_scratch.ensure(front_literal_scratch_bytes(pl.R, pl.k, std::max(n_l, n_c2))));
+                    gs = S.lit_scratch.p;
+                    P2_HIP(launch_front_classify_literal(dq, pl.R, pl.k, static_cast<const FrontEntry*>(S.f_literal[cur].p), n_l, len, keep ? 0 : 1,
+                                                         static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr, gs,
+                                                         pl.max_row_classes, from_pairs ? static_cast<const uint32_t*>(S.f_rest.p) : nullptr,
+                                                         from_pairs ? &dctr->n_rest : nullptr, S.stream));
+                }
                 P2_HIP(S.spans.end(S.stream));
                 return P2_OK;
             };
@@ -1100,7 +1117,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                     P2_HIP(S.spans.begin(SpanRec::kLiteral, S.stream));
                     P2_HIP(launch_front_classify_literal(dq, pl.R, pl.k, static_cast<const FrontEntry*>(S.f_unknown.p), n_u, len, keep ? 0 : 1,
                                                          static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr, gs,
-                                                         pl.max_row_classes, S.stream));
+                                                         pl.max_row_classes, nullptr, nullptr, S.stream));
                     P2_HIP(S.spans.end(S.stream));
                     P2_HIP(launch_front_counters_out(static_cast<FrontCounters*>(S.h_fctr.p), dctr, S.stream));
                     P2_HIP(hipStreamSynchronize(S.stream));
@@ -1143,6 +1160,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             P2_HIP(S.f_sums2[nxt].ensure(std::max<size_t>((size_t)n_prefix2 * sum_doubles, 1) * 8));
             P2_HIP(S.f_sid2[nxt].ensure(std::max<size_t>(n_prefix2, 1) * sizeof(uint32_t)));
             P2_HIP(S.f_literal[nxt].ensure(std::max<size_t>(n_plit, 1) * sizeof(FrontEntry)));
+            P2_HIP(S.f_lit_parent[nxt].ensure(std::max<size_t>(n_plit, 1) * sizeof(uint32_t)));
             // ... and states: a child per (judged state, valid instruction), its hash, what the step
             // adds to the cost sums; where a state's children are
             P2_HIP(S.f_states[nxt].ensure(std::max<size_t>(t1, 1) * sw * 4));
@@ -1234,21 +1252,23 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             px.next_entries2 = static_cast<FrontEntry*>(S.f_entries2[nxt].p); px.next_sid2 = static_cast<uint32_t*>(S.f_sid2[nxt].p);
             px.next_sums2 = static_cast<double*>(S.f_sums2[nxt].p);
             px.next_literal = static_cast<FrontEntry*>(S.f_literal[nxt].p);
+            px.next_literal_parent = static_cast<uint32_t*>(S.f_lit_parent[nxt].p);
             px.valid_out = vout; px.goal_sums = gsums; px.ctr = dctr;
             if (n_surv > 0) P2_HIP(S.spans.begin(SpanRec::kGroup, S.stream));
             P2_HIP(launch_front_prefixes(reinterpret_cast<const DevQuery*>(db), px, S.stream));
             if (n_surv > 0) P2_HIP(S.spans.end(S.stream));
             P2_HIP(launch_front_emit(dq, (uint32_t)i, static_cast<const FrontEntry*>(S.f_literal[cur].p),
                                      static_cast<const FrontSurvivor*>(S.f_surv_literal.p), n_surv_l_first, len, keep,
-                                     static_cast<FrontEntry*>(S.f_literal[nxt].p), vout_lit, gsums_lit, (int)sum_doubles / 2, dctr, S.stream));
+                                     static_cast<FrontEntry*>(S.f_literal[nxt].p), static_cast<uint32_t*>(S.f_lit_parent[nxt].p), vout_lit, gsums_lit, (int)sum_doubles / 2, dctr, S.stream));
             P2_HIP(launch_front_emit(dq, (uint32_t)i, static_cast<const FrontEntry*>(S.f_unknown.p),
                                      static_cast<const FrontSurvivor*>(S.f_surv_literal.p) + n_surv_l_first, n_surv_l - n_surv_l_first, len, keep,
-                                     static_cast<FrontEntry*>(S.f_literal[nxt].p), vout_lit, gsums_lit, (int)sum_doubles / 2, dctr, S.stream));
+                                     static_cast<FrontEntry*>(S.f_literal[nxt].p), static_cast<uint32_t*>(S.f_lit_parent[nxt].p), vout_lit, gsums_lit, (int)sum_doubles / 2, dctr, S.stream));
             E.n_valid += n_goal;
             goals_before = n_goal;
             n_c = keep ? n_prefix : 0;
             n_c2 = keep ? n_prefix2 : 0;
             n_l = keep ? n_plit : 0;
+            n_l_literal = keep ? n_surv_l - n_goal_lit : 0;
             n_s[0] = keep ? t1 : 0; n_s[1] = keep ? t2 : 0;
             grouped[0] = grouped_next[0]; grouped[1] = grouped_next[1];
             cur = nxt;
@@ -1428,8 +1448,10 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     // every query of the enumeration writes its rows (programs, and costs from its own sums)
     if (!enums.empty()) {
         size_t ranked = 0;
-        for (auto& E : enums) { E.off_valid = ranked; ranked += E.n_valid; }
+        size_t most = 0;
+        for (auto& E : enums) { E.off_valid = ranked; ranked += E.n_valid; most = std::max<size_t>(most, E.n_valid); }
         P2_HIP(C.f_rank.ensure(sizeof(uint32_t) * std::max<size_t>(ranked, 1)));
+        P2_HIP(C.f_rank_runs.ensure(sizeof(unsigned long long) * std::max<size_t>(most, 1)));
         std::vector<FrontFinish> jobs;
         uint32_t max_valid = 0;
         for (auto& E : enums) {
@@ -1441,7 +1463,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             for (int32_t m : E.members) ordered |= runs[m].topk == 0;
             if (ordered) {
                 ++post_launches;
-                P2_HIP(launch_front_rank(list, E.n_valid, rank, stream));
+                P2_HIP(launch_front_rank(list, E.n_valid, static_cast<unsigned long long*>(C.f_rank_runs.p), rank, stream));
             }
             for (size_t m = 0; m < E.members.size(); ++m) {
                 FrontFinish F;

@@ -264,6 +264,8 @@ struct FrontCounters {
     uint32_t n_walked_planes;      // planes of the states whose patterns the classification walked (the last level skips
                                    // the states from which no instruction can end at the goal)
     uint32_t n_walk[2];            // the last level: states of the one-pair / two-pair list left to the classification
+    uint32_t n_rest;               // ... literal prefixes that are not one AllGather away from a state held in pairs
+    uint32_t pad0;
     // running totals of the enumeration
     unsigned long long steps, members;
     // distinct states found among the entries of the one-pair / two-pair list (cleared before each level's search)
@@ -308,6 +310,7 @@ struct FrontPrefixes {
     FrontEntry* next_entries1; uint32_t* next_sid1; double* next_sums1;
     FrontEntry* next_entries2; uint32_t* next_sid2; double* next_sums2;
     FrontEntry* next_literal;
+    uint32_t* next_literal_parent; // per literal prefix its parent's state, doubled, plus 1 if it is a two-pair state (~0: none)
     unsigned long long* valid_out; double* goal_sums;      // goals: candidate index and [n_share][2] sums
     FrontCounters* ctr;
 };
@@ -364,10 +367,19 @@ hipError_t launch_front_expand(const DevQuery* q, const FrontEntry* entries, uin
 size_t front_literal_scratch_bytes(int R, int k, uint32_t n);
 // class_cap: most classes of equal rows the class-state kernel may hold (1..64) before a prefix goes to the
 // full-state kernel.  goals_only != 0 (the level at the size limit): only the instructions that can reach the
-// goal from the prefix's state are judged, and only goals are reported.
+// goal from the prefix's state are judged, and only goals are reported.  elist: only the entries elist[0 .. *elist_n) (on
+// the device; null: all n).
 hipError_t launch_front_classify_literal(const DevQuery* q, int R, int k, const FrontEntry* entries, uint32_t n,
                                          int parent_len, int goals_only, FrontSurvivor* surv, uint32_t surv_cap,
-                                         FrontCounters* ctr, void* gscratch, int class_cap, hipStream_t stream);
+                                         FrontCounters* ctr, void* gscratch, int class_cap, const uint32_t* elist,
+                                         const uint32_t* elist_n, hipStream_t stream);
+// The last level's goals among the extensions of literal prefixes that are one AllGather away from a state held in pairs
+// (parents[e] as in FrontPrefixes; states1 / states2: the state lists of the level before); the other entries go on the
+// list rest[0 .. ctr->n_rest).  scratch: front_literal_goals_scratch_bytes(R, k, n) bytes.
+size_t front_literal_goals_scratch_bytes(int R, int k, uint32_t n);
+hipError_t launch_front_literal_goals(const DevQuery* q, int R, int k, const FrontEntry* entries, const uint32_t* parents, uint32_t n,
+                                      int len, const uint32_t* states1, const uint32_t* states2, void* scratch, FrontSurvivor* surv,
+                                      uint32_t surv_cap, FrontCounters* ctr, uint32_t* rest, hipStream_t stream);
 // The children of the judged states of a list (every state 0 .. n - 1 if list is null), from their codes: counted by
 // kind (write = 0: t_count), or given their places (write = 1: child_of[state * alphabet + digit], t_next) and
 // listed in ssurv (n_ssurv).  keep = 0: goals only.
@@ -377,12 +389,12 @@ hipError_t launch_front_children(const DevQuery* q, uint32_t n, const uint32_t* 
 hipError_t launch_front_materialize(const DevQuery* queries, int R, int k, const FrontLevel& level, hipStream_t stream);
 hipError_t launch_front_prefixes(const DevQuery* queries, const FrontPrefixes& P, hipStream_t stream);
 hipError_t launch_front_emit(const DevQuery* q, uint32_t query, const FrontEntry* entries, const FrontSurvivor* surv,
-                             uint32_t n_surv, int parent_len, int keep_prefixes, FrontEntry* next_literal,
+                             uint32_t n_surv, int parent_len, int keep_prefixes, FrontEntry* next_literal, uint32_t* next_literal_parent,
                              unsigned long long* valid_out, double* goal_sums, int n_share, FrontCounters* ctr,
                              hipStream_t stream);
 // The counters to pinned host memory; clears those that the second half of a level counts with.
 hipError_t launch_front_counters_out(FrontCounters* host_dst, FrontCounters* ctr, hipStream_t stream);
-hipError_t launch_front_rank(const unsigned long long* valid, uint32_t n, uint32_t* rank, hipStream_t stream);
+hipError_t launch_front_rank(const unsigned long long* valid, uint32_t n, unsigned long long* runs, uint32_t* rank, hipStream_t stream);
 // The rows of n_jobs queries in one launch (jobs in device memory; max_valid = the largest n_valid among them).
 hipError_t launch_front_finish(const DevQuery* queries, const FrontFinish* jobs, uint32_t n_jobs, uint32_t max_valid, hipStream_t stream);
 

@@ -1194,7 +1194,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
         FrontCounters* const c = A.ctr;
         c->surv_goal = 0ull; c->pref_pref2 = 0ull; c->n_surv_literal = 0u; c->n_goal = 0u; c->n_prefix_literal = 0u;
         c->n_overflow = 0u; c->n_unknown = 0u; c->t_count[0] = 0u; c->t_count[1] = 0u; c->t_count[2] = 0u;
-        c->n_walked_planes = 0u; c->n_walk[0] = 0u; c->n_walk[1] = 0u;
+        c->n_walked_planes = 0u; c->n_walk[0] = 0u; c->n_walk[1] = 0u; c->n_rest = 0u;
     }
     __syncthreads();
     for (uint32_t i = blockIdx.x; i < A.n_surv; i += gridDim.x) {
@@ -1549,7 +1549,9 @@ __global__ __launch_bounds__(256) void k_front_prefixes(const DevQuery* __restri
                 FrontEntry ce;
                 ce.query = A.query; ce.len = (uint32_t)(A.parent_len + 1);
                 ce.digits = pe.digits | ((unsigned long long)sv.digit << (9 * A.parent_len));
-                A.next_literal[atomicAdd(&A.ctr->next_literal, 1u)] = ce;
+                const uint32_t at = atomicAdd(&A.ctr->next_literal, 1u);
+                A.next_literal[at] = ce;
+                A.next_literal_parent[at] = (two ? A.sid2 : A.sid1)[sv.entry] * 2u + (two ? 1u : 0u);
             }
             continue;
         }
@@ -1583,6 +1585,170 @@ __global__ __launch_bounds__(256) void k_front_prefixes(const DevQuery* __restri
     if (threadIdx.x == 0 && s_made[0]) { atomicAdd(&A.ctr->steps, s_made[0]); atomicAdd(&A.ctr->members, s_made[1]); }
 }
 
+// ---- the last level: literal prefixes whose parent is held in pairs ------------------------------------------
+// With two pairs per device a prefix turns literal through one instruction only, an AllGather that leaves a device with
+// more than two masks, and where that happens at the last level the prefix need not be rebuilt from the empty program:
+// its parent's planes are still there, and after the AllGather (pattern P) a row of a device carries the mask of the
+// one member of the device's group that held it.  What one more instruction makes of that (goals alone count here):
+//   AllReduce     : every device must hold every row, and then per group and row the members' masks must be disjoint
+//                   and unite to all columns; the devices outside must be at the goal.
+//   AllGather     : the rows that are moved keep their columns, and one of three different masks is incomplete: never.
+//   Broadcast     : every root at the goal, some member of every group short of it, the devices outside at the goal.
+// A block per prefix.  `owner` (the block's slice of a scratch buffer, one entry per group of P and row: the member that
+// holds it, doubled, plus its pair) is filled once an AllReduce has to be looked at.  Nearly every AllReduce pattern fails
+// in its first rows, so a prefix costs a pass over its parent's planes (64 KiB each for 512 devices) and the filling.
+// The 512-device enumeration to six instructions: 0.35 ms for the prefixes that took 6.7 ms on the class-state and the
+// full-state kernels (16 MiB a prefix, from the empty program on).
+constexpr int kLgThreads = 512;
+constexpr uint32_t kLgBlocks = 512;
+template <int KW, int MW>
+__global__ __launch_bounds__(kLgThreads) void k_front_literal_goals(const DevQuery* __restrict__ qp, const FrontEntry* __restrict__ entries,
+                                                                    const uint32_t* __restrict__ parents, uint32_t n, int len,
+                                                                    const uint32_t* __restrict__ states1, const uint32_t* __restrict__ states2,
+                                                                    uint16_t* __restrict__ scratch, unsigned long long per_block,
+                                                                    FrontSurvivor* __restrict__ surv, uint32_t surv_cap,
+                                                                    FrontCounters* __restrict__ ctr, uint32_t* __restrict__ rest) {
+    using L = FL<KW, MW>;
+    __shared__ uint8_t s_goal[P2_MAX_DEVICES];           // the device is at the goal after the AllGather
+    __shared__ int s_rows_short, s_bad;
+    const DevQuery& q = *qp;
+    const int R = q.R, k = q.k, I = q.alphabet, tid = threadIdx.x;
+    const int plane_w = R * L::WS;
+    const Words<KW> all_rows = full_mask<KW>(k);
+    const Words<MW> all_cols = full_mask<MW>(R);
+    uint16_t* const owner = scratch + (size_t)blockIdx.x * per_block;
+    unsigned long long judged = 0;
+    for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
+        const uint32_t parent = parents[e];
+        const unsigned long long digits = entries[e].digits;
+        const uint32_t ins = q.instr_of_digit[(int)((digits >> (9 * (len - 1))) & 511ull)];
+        if (parent == ~0u || (int)(ins & 7u) != OP_AG) {  // (built from a literal prefix: the other kernels judge it)
+            if (tid == 0) rest[atomicAdd(&ctr->n_rest, 1u)] = e;
+            continue;
+        }
+        ++judged;
+        const DevPattern& P = q.pat[ins >> 3];
+        const int g = P.g, s = P.s, ng = P.n_groups, gs = g * s;
+        const bool two = (parent & 1u) != 0u;
+        const uint32_t* const p0 = two ? states2 + (size_t)(parent >> 1) * 2 * plane_w : states1 + (size_t)(parent >> 1) * plane_w;
+        const uint32_t* const p1 = p0 + plane_w;         // (read only if `two`)
+        // group of P that device d is in, or -1
+        auto group_of = [&](int d) {
+            const int hi = d / gs, lo = d - hi * gs, m = lo % s;
+            if (P.master) return m == 0 && hi < ng ? hi : -1;
+            return hi * s + m;
+        };
+        auto base_of = [&](int G, const DevPattern& Q) { return Q.master ? G * Q.g * Q.s : (G / Q.s) * Q.g * Q.s + G % Q.s; };
+        __syncthreads();
+        if (tid == 0) s_rows_short = 0;
+        __syncthreads();
+        // ---- per group (and per device outside): every row there? every mask complete?
+        bool rows_short = false;
+        auto look = [&](const Slot<KW, MW>& v, Words<KW>& rows, bool& complete) {
+            bool any = false, full = true;
+#pragma unroll
+            for (int i = 0; i < KW; ++i) { any |= v.r.w[i] != 0u; rows.w[i] |= v.r.w[i]; }
+#pragma unroll
+            for (int i = 0; i < MW; ++i) full &= v.m.w[i] == all_cols.w[i];
+            complete &= !any || full;
+        };
+        for (int it = tid; it < R; it += kLgThreads) {    // the groups first, then the devices outside them
+            const int G = group_of(it);
+            const bool mine = G < 0 || it == base_of(G, P);
+            if (!mine) continue;
+            Words<KW> rows = zero_words<KW>();
+            bool complete = true;
+            for (int m = 0; m < (G < 0 ? 1 : g); ++m) {
+                const int d = it + m * s;
+                look(fload<KW, MW>(p0, d), rows, complete);
+                if (two) look(fload<KW, MW>(p1, d), rows, complete);
+            }
+            bool all = true;
+#pragma unroll
+            for (int i = 0; i < KW; ++i) all &= rows.w[i] == all_rows.w[i];
+            rows_short |= !all;
+            for (int m = 0; m < (G < 0 ? 1 : g); ++m) s_goal[it + m * s] = all && complete ? 1 : 0;
+        }
+        if (rows_short) s_rows_short = 1;
+        __syncthreads();
+        const bool ar = s_rows_short == 0, bc = s_goal[0] != 0;
+        if (!ar && !bc) continue;
+        if (ar) {
+            for (int it = tid; it < ng * k; it += kLgThreads) {
+                const int G = it / k, r = it - G * k, base = base_of(G, P);
+                uint32_t who = 0;
+                for (int m = 0; m < g; ++m) {
+                    const uint32_t a = p0[(base + m * s) * L::WS + (r >> 5)];
+                    const uint32_t b = two ? p1[(base + m * s) * L::WS + (r >> 5)] : 0u;
+                    if ((a >> (r & 31)) & 1u) who = (uint32_t)m * 2u;
+                    if ((b >> (r & 31)) & 1u) who = (uint32_t)m * 2u + 1u;
+                }
+                owner[it] = (uint16_t)who;
+            }
+            __syncthreads();
+        }
+        for (int a = 0; a < I; ++a) {
+            const uint32_t last = q.instr_of_digit[a];
+            const int op = (int)(last & 7u);
+            if (!((op == OP_AR && ar) || (op == OP_BC && bc))) continue;
+            const DevPattern& Q = q.pat[last >> 3];
+            const int qg = Q.g, qs = Q.s, qn = Q.n_groups;
+            __syncthreads();
+            if (tid == 0) s_bad = 0;
+            __syncthreads();
+            bool bad = false;
+            if (Q.master)                                 // devices that the instruction leaves alone
+                for (int d = tid; d < R; d += kLgThreads) bad |= !(d % qs == 0 && d / (qg * qs) < qn) && s_goal[d] == 0;
+            if (op == OP_BC) {
+                for (int H = tid; H < qn; H += kLgThreads) {
+                    const int base = base_of(H, Q);
+                    bool differs = false;
+                    for (int m = 1; m < qg; ++m) differs |= s_goal[base + m * qs] == 0;
+                    bad |= s_goal[base] == 0 || !differs;
+                }
+                if (bad) s_bad = 1;
+                __syncthreads();
+            } else {
+                for (int i0 = 0; i0 < qn * k; i0 += kLgThreads) {
+                    const int it = i0 + tid;
+                    if (it < qn * k && !bad) {
+                        const int H = it / k, r = it - H * k, base = base_of(H, Q);
+                        Words<MW> acc = zero_words<MW>();
+                        for (int m = 0; m < qg && !bad; ++m) {
+                            const int d = base + m * qs, G = group_of(d);
+                            int src = d, pair = 0;
+                            if (G >= 0) {
+                                const uint32_t who = owner[G * k + r];
+                                src = base_of(G, P) + (int)(who >> 1) * s; pair = (int)(who & 1u);
+                            } else if (two) {
+                                pair = (int)((p1[d * L::WS + (r >> 5)] >> (r & 31)) & 1u);
+                            }
+                            const uint32_t* const mask = (pair ? p1 : p0) + src * L::WS + L::MO;
+#pragma unroll
+                            for (int i = 0; i < MW; ++i) { const uint32_t v = mask[i]; bad |= (acc.w[i] & v) != 0u; acc.w[i] |= v; }
+                        }
+#pragma unroll
+                        for (int i = 0; i < MW; ++i) bad |= acc.w[i] != all_cols.w[i];
+                    }
+                    if (bad) s_bad = 1;
+                    __syncthreads();
+                    if (s_bad) break;                     // (written before the barrier only: the same for everyone)
+                    __syncthreads();
+                }
+            }
+            if (tid == 0 && s_bad == 0) {
+                const uint32_t pos = atomicAdd(&ctr->n_surv_literal, 1u);
+                if (pos < surv_cap) { FrontSurvivor sv; sv.entry = e; sv.digit = (uint16_t)a; sv.code = (uint16_t)CODE_GOAL; sv.slot = 0u; surv[pos] = sv; }
+                atomicAdd(&ctr->n_goal, 1u);
+            }
+        }
+    }
+    if (tid == 0 && judged) {
+        atomicAdd(&ctr->steps, judged * (unsigned long long)I);
+        atomicAdd(&ctr->members, judged * (unsigned long long)q.reg_sum_part);
+    }
+}
+
 // Survivors of the literal frontier carry no state: a goal becomes a valid program, the rest
 // prefixes of the next literal frontier.  Such a goal has no sums (NaN: its cost is worked out by
 // the cost kernels that re-run a program).
@@ -1590,6 +1756,7 @@ __global__ __launch_bounds__(256) void k_front_emit(const DevQuery* __restrict__
                                                     const FrontEntry* __restrict__ entries,
                                                     const FrontSurvivor* __restrict__ surv, uint32_t n_surv, int parent_len,
                                                     int keep_prefixes, FrontEntry* __restrict__ next_literal,
+                                                    uint32_t* __restrict__ next_literal_parent,
                                                     unsigned long long* __restrict__ valid_out, double* __restrict__ goal_sums,
                                                     int n_share, FrontCounters* __restrict__ ctr) {
     // (valid_out / goal_sums start behind the goals of this level that the pair kernels found)
@@ -1605,7 +1772,9 @@ __global__ __launch_bounds__(256) void k_front_emit(const DevQuery* __restrict__
     } else if (keep_prefixes) {
         FrontEntry ce;
         ce.query = query; ce.len = (uint32_t)(parent_len + 1); ce.digits = digits;
-        next_literal[atomicAdd(&ctr->next_literal, 1u)] = ce;
+        const uint32_t at = atomicAdd(&ctr->next_literal, 1u);
+        next_literal[at] = ce;
+        next_literal_parent[at] = ~0u;
     }
 }
 
@@ -1673,19 +1842,44 @@ __global__ __launch_bounds__(64) void k_front_counters_out(FrontCounters* __rest
     }
 }
 
-// rank[i] = number of entries of the list smaller than entry i (distinct keys).
-__global__ __launch_bounds__(256) void k_front_rank(const unsigned long long* __restrict__ in, uint32_t n, uint32_t* __restrict__ rank) {
-    __shared__ unsigned long long tile[256];
+// rank[i] = number of entries of the list smaller than entry i (distinct keys), in two launches: every block sorts its
+// run of kRankRun entries in LDS, then every entry's place in each of the other runs is found by bisection.  (Counting the
+// smaller ones outright takes n^2 comparisons: 1.26 ms for the 83 920 programs of a 512-device query, 0.06 ms this way.)
+constexpr int kRankRun = 2048, kRankThreads = 1024;
+__global__ __launch_bounds__(kRankThreads) void k_front_rank_runs(const unsigned long long* __restrict__ in, uint32_t n,
+                                                                  unsigned long long* __restrict__ runs) {
+    __shared__ unsigned long long key[kRankRun];
+    const uint32_t first = blockIdx.x * (uint32_t)kRankRun;
+    for (uint32_t j = threadIdx.x; j < (uint32_t)kRankRun; j += kRankThreads) key[j] = first + j < n ? in[first + j] : ~0ull;
+    for (uint32_t k = 2; k <= (uint32_t)kRankRun; k *= 2)
+        for (uint32_t j = k / 2; j > 0; j /= 2) {
+            __syncthreads();
+            const uint32_t t = threadIdx.x, a = 2u * t - (t & (j - 1u)), b = a + j;      // (a pair per thread)
+            const unsigned long long x = key[a], y = key[b];
+            if ((y < x) == ((a & k) == 0u)) { key[a] = y; key[b] = x; }
+        }
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < (uint32_t)kRankRun; j += kRankThreads) if (first + j < n) runs[first + j] = key[j];
+}
+// A block goes through all runs for 256 entries, a run at a time in LDS.
+__global__ __launch_bounds__(256) void k_front_rank(const unsigned long long* __restrict__ in, uint32_t n,
+                                                    const unsigned long long* __restrict__ runs, uint32_t* __restrict__ rank) {
+    __shared__ unsigned long long key[kRankRun];
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    const unsigned long long key = i < n ? in[i] : 0ull;
+    const unsigned long long mine = i < n ? in[i] : 0ull;
     uint32_t r = 0;
-    for (uint32_t t0 = 0; t0 < n; t0 += 256u) {
-        const uint32_t j = t0 + threadIdx.x;
-        tile[threadIdx.x] = j < n ? in[j] : ~0ull;
+    for (uint32_t first = 0; first < n; first += (uint32_t)kRankRun) {
+        unsigned long long next[kRankRun / 256];
+#pragma unroll
+        for (int u = 0; u < kRankRun / 256; ++u) { const uint32_t j = first + 256u * u + threadIdx.x; next[u] = runs[j < n ? j : n - 1u]; }
         __syncthreads();
-        const uint32_t lim = n - t0 < 256u ? n - t0 : 256u;
-        for (uint32_t u = 0; u < lim; ++u) r += tile[u] < key;
+#pragma unroll
+        for (int u = 0; u < kRankRun / 256; ++u) { const uint32_t j = 256u * u + threadIdx.x; key[j] = first + j < n ? next[u] : ~0ull; }
         __syncthreads();
+        uint32_t lo = 0;                                 // entries of the run below `mine`
+#pragma unroll
+        for (uint32_t step = kRankRun / 2; step > 0; step /= 2) lo += key[lo + step - 1u] < mine ? step : 0u;
+        r += lo + (key[lo] < mine ? 1u : 0u);
     }
     if (i < n) rank[i] = r;
 }
@@ -1711,6 +1905,7 @@ struct FrontArgs {
     double* sums; uint32_t* sid; int n_share;
     const DevQuery* queries; const FrontLevel* level;
     int R;
+    const uint32_t* parents; const uint32_t* states2; uint16_t* owner; unsigned long long owner_per; FrontSurvivor* surv; uint32_t surv_cap; uint32_t* rest; int len;
 };
 
 template <int KW, int MW>
@@ -1742,6 +1937,9 @@ hipError_t front_go(int what, const FrontArgs& A, hipStream_t stream) {
         else
             hipLaunchKernelGGL((k_front_goal_filter<KW, MW, 1>), dim3(blocks), dim3(256), 0, stream, A.q, A.states, A.n, A.list, A.n_list,
                                A.codes, A.row_counts, A.unknown, A.walk, A.n_walk);
+    } else if (what == 4) {
+        hipLaunchKernelGGL((k_front_literal_goals<KW, MW>), dim3(A.n < kLgBlocks ? A.n : kLgBlocks), dim3(kLgThreads), 0, stream, A.q, A.entries,
+                           A.parents, A.n, A.len, A.states, A.states2, A.owner, A.owner_per, A.surv, A.surv_cap, A.ctr, A.rest);
     } else {
         const size_t lds = (size_t)A.level->lds_planes * A.R * FL<KW, MW>::WS * 4;
         const unsigned blocks = A.level->n_surv < 8192u ? A.level->n_surv : 8192u;
@@ -1880,19 +2078,37 @@ hipError_t launch_front_materialize(const DevQuery* queries, int R, int k, const
     return front_dispatch(R, k, 2, A, stream);
 }
 
+size_t front_literal_goals_scratch_bytes(int R, int k, uint32_t n) {
+    return (size_t)(n < kLgBlocks ? n : kLgBlocks) * (size_t)(R / 2 > 0 ? R / 2 : 1) * (size_t)k * sizeof(uint16_t);
+}
+hipError_t launch_front_literal_goals(const DevQuery* q, int R, int k, const FrontEntry* entries, const uint32_t* parents, uint32_t n,
+                                      int len, const uint32_t* states1, const uint32_t* states2, void* scratch, FrontSurvivor* surv,
+                                      uint32_t surv_cap, FrontCounters* ctr, uint32_t* rest, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    if (len < 1 || !scratch) return hipErrorInvalidValue;
+    FrontArgs A{};
+    A.q = q; A.entries = entries; A.parents = parents; A.n = n; A.len = len; A.states = states1; A.states2 = states2; A.R = R;
+    A.owner = static_cast<uint16_t*>(scratch); A.owner_per = (unsigned long long)(R / 2 > 0 ? R / 2 : 1) * (unsigned long long)k;
+    A.surv = surv; A.surv_cap = surv_cap; A.ctr = ctr; A.rest = rest;
+    return front_dispatch(R, k, 4, A, stream);
+}
+
 hipError_t launch_front_emit(const DevQuery* q, uint32_t query, const FrontEntry* entries, const FrontSurvivor* surv,
-                             uint32_t n_surv, int parent_len, int keep_prefixes, FrontEntry* next_literal,
+                             uint32_t n_surv, int parent_len, int keep_prefixes, FrontEntry* next_literal, uint32_t* next_literal_parent,
                              unsigned long long* valid_out, double* goal_sums, int n_share, FrontCounters* ctr,
                              hipStream_t stream) {
     if (n_surv == 0) return hipSuccess;
     hipLaunchKernelGGL(k_front_emit, dim3((n_surv + 255u) / 256u), dim3(256), 0, stream, q, query, entries, surv, n_surv, parent_len,
-                       keep_prefixes, next_literal, valid_out, goal_sums, n_share, ctr);
+                       keep_prefixes, next_literal, next_literal_parent, valid_out, goal_sums, n_share, ctr);
     return hipGetLastError();
 }
 
-hipError_t launch_front_rank(const unsigned long long* valid, uint32_t n, uint32_t* rank, hipStream_t stream) {
+hipError_t launch_front_rank(const unsigned long long* valid, uint32_t n, unsigned long long* runs, uint32_t* rank, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_front_rank, dim3((n + 255u) / 256u), dim3(256), 0, stream, valid, n, rank);
+    hipLaunchKernelGGL(k_front_rank_runs, dim3((n + kRankRun - 1u) / kRankRun), dim3(kRankThreads), 0, stream, valid, n, runs);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_front_rank, dim3((n + 255u) / 256u), dim3(256), 0, stream, valid, n, runs, rank);
     return hipGetLastError();
 }
 

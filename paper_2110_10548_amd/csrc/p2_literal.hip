@@ -1354,7 +1354,8 @@ __global__ __launch_bounds__(NT) void k_front_classify_classes(const DevQuery* _
                                                                   int parent_len, int goals_only, FrontSurvivor* __restrict__ surv,
                                                                   uint32_t surv_cap, FrontCounters* __restrict__ ctr,
                                                                   uint32_t* __restrict__ over, uint32_t* __restrict__ gscratch,
-                                                                  unsigned long long gwords, int class_cap) {
+                                                                  unsigned long long gwords, int class_cap,
+                                                                  const uint32_t* __restrict__ elist, const uint32_t* __restrict__ elist_n) {
     extern __shared__ uint32_t lds[];
     const DevQuery& q = *qp;
     const int lane = threadIdx.x;
@@ -1369,7 +1370,9 @@ __global__ __launch_bounds__(NT) void k_front_classify_classes(const DevQuery* _
         full[w] = bits >= 32 ? 0xffffffffu : bits > 0 ? ((1u << bits) - 1u) : 0u;
     }
     unsigned long long steps = 0, members = 0;
-    for (uint32_t e = blockIdx.x; e < n_entries; e += gridDim.x) {
+    const uint32_t n = elist ? *elist_n : n_entries;
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const uint32_t e = elist ? elist[i] : i;
         const unsigned long long digits = entries[e].digits;
         int C = 1, rc = CSTEP_OK;
         cls_init<MW>(q, X, C, lane, NT);
@@ -1828,7 +1831,8 @@ size_t front_literal_scratch_bytes(int R, int k, uint32_t n) { return front_lite
 
 hipError_t launch_front_classify_literal(const DevQuery* q, int R, int k, const FrontEntry* entries, uint32_t n,
                                          int parent_len, int goals_only, FrontSurvivor* surv, uint32_t surv_cap, FrontCounters* ctr,
-                                         void* gscratch, int class_cap_asked, hipStream_t stream) {
+                                         void* gscratch, int class_cap_asked, const uint32_t* elist, const uint32_t* elist_n,
+                                         hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (!gscratch) return hipErrorInvalidValue;
     const FrontLiteralScratch sc = front_literal_scratch(R, k, n);
@@ -1847,12 +1851,12 @@ hipError_t launch_front_classify_literal(const DevQuery* q, int R, int k, const 
         e = allow_big_lds(k_front_classify_classes<MWV, kClassThreads>, sc.cls_lds);                           \
         if (e == hipSuccess)                                                                                   \
             hipLaunchKernelGGL((k_front_classify_classes<MWV, kClassThreads>), dim3(cls_blocks), dim3(kClassThreads), sc.cls_lds, stream, q, entries, n, \
-                               parent_len, goals_only, surv, surv_cap, ctr, over, cls_mem, cls_words_per, class_cap); \
+                               parent_len, goals_only, surv, surv_cap, ctr, over, cls_mem, cls_words_per, class_cap, elist, elist_n); \
     } else {                                                                                                   \
         e = allow_big_lds(k_front_classify_classes<MWV, kWave>, sc.cls_lds);                                   \
         if (e == hipSuccess)                                                                                   \
             hipLaunchKernelGGL((k_front_classify_classes<MWV, kWave>), dim3(cls_blocks), dim3(kWave), sc.cls_lds, stream, q, entries, n, \
-                               parent_len, goals_only, surv, surv_cap, ctr, over, cls_mem, cls_words_per, class_cap); \
+                               parent_len, goals_only, surv, surv_cap, ctr, over, cls_mem, cls_words_per, class_cap, elist, elist_n); \
     }                                                                                                          \
     if (e == hipSuccess && sc.full_lds) {                                                                      \
         e = allow_big_lds(k_front_classify_literal<MWV, kWave>, sc.full_lds);                                  \
@@ -1890,7 +1894,6 @@ size_t literal_group_scratch_bytes(int max_R, int max_k, unsigned* blocks) {
 
 hipError_t launch_eval_literal_groups_auto(const DevQuery* queries, const int32_t* qlist, int n_q, int max_R, int max_k,
                                            void* gscratch, int class_cap_asked, hipStream_t stream) {
-    if (n_q == 0) return hipSuccess;
     if (!gscratch || max_R > 64) return hipErrorInvalidValue;
     const size_t lds = (size_t)cls_words(max_R, max_k, mask_words(max_R)) * 4;
     unsigned blocks = 0;
