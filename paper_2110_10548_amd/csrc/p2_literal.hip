@@ -1894,6 +1894,7 @@ size_t literal_group_scratch_bytes(int max_R, int max_k, unsigned* blocks) {
 
 hipError_t launch_eval_literal_groups_auto(const DevQuery* queries, const int32_t* qlist, int n_q, int max_R, int max_k,
                                            void* gscratch, int class_cap_asked, hipStream_t stream) {
+    if (n_q == 0) return hipSuccess;
     if (!gscratch || max_R > 64) return hipErrorInvalidValue;
     const size_t lds = (size_t)cls_words(max_R, max_k, mask_words(max_R)) * 4;
     unsigned blocks = 0;
