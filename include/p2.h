@@ -70,12 +70,14 @@ int32_t p2_enumerate_placements(const p2_hierarchy* h, const int32_t* axes, int3
 /* Evaluation engines.  All give identical results; they differ in the state they keep. */
 #define P2_ENGINE_AUTO 0      /* shared-prefix engine where it applies, else the compact engine; the
                                  literal engine for the candidates they cannot hold; the frontier
-                                 engine above 2^30 candidates                                     */
+                                 engine above 2^30 candidates, and in place of the compact engine
+                                 where that is slower (more than 64 devices from 100 candidates on;
+                                 otherwise from 8e7 candidates x devices on)                      */
 #define P2_ENGINE_LITERAL 1   /* R x k masks of R bits per candidate in LDS, one wavefront each   */
 #define P2_ENGINE_COMPACT 2   /* per device one chunk set and one contribution mask, in LDS; one
                                  candidate per lane                                               */
 #define P2_ENGINE_FRONTIER 3  /* enumeration by program size with pruning (Sec. 3.5): only valid
-                                 prefixes are extended; AUTO picks it above 2^30 candidates.
+                                 prefixes are extended; AUTO: see P2_ENGINE_AUTO.
                                  Queries of one batch with the same reduction-group size, chunk
                                  count, patterns, alphabet and size limit are enumerated once (the
                                  later ones report the first one's counts in their stats)        */
@@ -176,7 +178,10 @@ typedef struct {
     uint64_t steps_executed;   /* instructions applied, counted per candidate (a candidate stops at
                                   its first bad step): what evaluating every candidate on its own
                                   executes, whichever engine ran                                  */
-    uint64_t literal_reruns;   /* candidates the compact engine handed to the literal engine      */
+    uint64_t literal_reruns;   /* candidates the compact engine handed to the literal engine; frontier
+                                  engine: prefixes judged outside the pair form, plus, where the
+                                  last level rebuilds such a prefix, its extensions that pass the
+                                  goal filter and miss the goal                                   */
     uint64_t member_visits;    /* sum over applied instructions of the devices taking part in them */
     int64_t valid;             /* valid programs found                                            */
     int32_t group_size;        /* R: devices in one reduction group                               */
