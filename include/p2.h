@@ -310,7 +310,9 @@ int32_t p2_topk_device(const double* cost, int64_t cost_stride, const uint64_t* 
  * set to 0 by the call and to 1 by its kernels when a cost is NaN (NaN entries are then left out and
  * trailing positions are -1); nothing is reported to the host.  k > 64 => P2_EUNSUPPORTED.
  * Every GPU holds one copy of the array until the process ends and all calls on a GPU share it: calls that
- * overlap on one GPU (different streams or host threads) race; calls on one stream are safe. */
+ * overlap on one GPU (different streams or host threads) race; calls on one stream are safe.  A call that was
+ * raced may return the wrong entries (each out_pos is -1 or a position in [0, n) all the same) and the wrong
+ * flag; it writes nothing but its own out_pos and out_nan, and later calls are not affected. */
 int32_t p2_topk_device_noalloc(const double* cost, int64_t cost_stride, const uint64_t* index, int64_t n, int32_t k,
                                int64_t* out_pos, uint32_t* out_nan, void* stream);
 

@@ -513,13 +513,17 @@ inline bool sel_sampled(long long n, int K) { return n >= (1ll << 22) || (n >= (
 // of some ten memory and barrier latencies; 1.3 M of stride 3, K = 64: 1190 -> 56 us, half of it the last block's walk;
 // 50 M, K = 100: 3170 -> 160 us, of which 100 read 400 MB at 4 TB/s (a large copy reaches 4.9) and 40 find the bound.
 // K smallest of a column by all blocks together: every block leaves what it kept, the last one to finish goes through
-// that and writes the positions (or, over a sample, the bound).
+// that and writes the positions (or, over a sample, the bound).  The lists hold `cap` entries, all that the blocks of one
+// call can leave; calls that overlap on one scratch against the rule (the fixed one below) add to the same cursor, so the
+// cursor is held against `cap` before a store and after the hand-over, and what comes out is a position of this column
+// or -1 also where the lists were another call's: a wrong answer then, never an access out of range.
 __global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long long n, int K, int sample, int bounded,
                                                              SelControl* __restrict__ ctl, double* lc, unsigned long long* li,
-                                                             unsigned long long* lp, long long* __restrict__ out_pos, long long n_out,
-                                                             uint32_t* __restrict__ nan_out) {
+                                                             unsigned long long* lp, uint32_t cap, long long* __restrict__ out_pos,
+                                                             long long n_out, uint32_t* __restrict__ nan_out) {
     __shared__ SelShared<kSelThreads, kSelBuffer> S;
     const uint32_t tid = threadIdx.x;
+    const unsigned long long n_column = (unsigned long long)n;
     SelState st{0u, __longlong_as_double(0x7ff0000000000000ll), ~0ull};
     if (bounded) st.Tc = ctl->bound;
     long long first = blockIdx.x, step = gridDim.x;
@@ -533,7 +537,8 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long
         if (tid == 0) S.flag = st.cnt ? __hip_atomic_fetch_add(&ctl->cursor, st.cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
         __syncthreads();
         const uint32_t base = S.flag;
-        for (uint32_t j = tid; j < st.cnt; j += kSelThreads) {
+        const uint32_t room = base < cap ? cap - base : 0u;
+        for (uint32_t j = tid; j < (st.cnt < room ? st.cnt : room); j += kSelThreads) {
             const unsigned long long e = S.pos[j];
             lc[base + j] = key_cost(S.key[j]); li[base + j] = src.idx[e]; lp[base + j] = e;
         }
@@ -546,14 +551,18 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long
         __syncthreads();
         if ((uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag) != gridDim.x - 1u) return;
         // the last block goes through what all of them have left, its own entries among it; its bound still holds
-        n = (long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&ctl->cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const uint32_t left = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&ctl->cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        n = (long long)(left < cap ? left : cap);
         st.cnt = 0u;
         src = SelSource{lc, li, lp, 1, 1};
         first = 0; step = 1; bounded = 0;
         last = true;
     }
     if (!sample)
-        for (long long j = tid; j < n_out; j += kSelThreads) out_pos[j] = j < (long long)st.cnt ? (long long)src.position(S.pos[j]) : -1ll;
+        for (long long j = tid; j < n_out; j += kSelThreads) {
+            const unsigned long long p = j < (long long)st.cnt ? src.position(S.pos[j]) : ~0ull;
+            out_pos[j] = p < n_column ? (long long)p : -1ll;
+        }
     const bool any = __syncthreads_or(nan ? 1 : 0) != 0;
     if (tid == 0) {
         ctl->bound = sample && st.cnt == (uint32_t)K ? key_cost(S.key[K - 1]) : __longlong_as_double(0x7ff0000000000000ll);
@@ -667,12 +676,12 @@ hipError_t launch_topk(const double* cost, long long stride, const unsigned long
     if (sampled) {
         const long long m = n / (kSelSample * 64) * 64;
         hipLaunchKernelGGL(k_topk_column, dim3(sel_blocks(m)), dim3(kSelThreads), 0, stream, SelSource{cost, index, nullptr, stride, kSelSample}, m, k,
-                           1, 0, ctl, lc, li, li + cap, nullptr, 0ll, nullptr);
+                           1, 0, ctl, lc, li, li + cap, (uint32_t)cap, nullptr, 0ll, nullptr);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_topk_column, dim3(blocks), dim3(kSelThreads), 0, stream, SelSource{cost, index, nullptr, stride, 1}, n, k, 0, sampled ? 1 : 0, ctl,
-                       lc, li, li + cap, out_pos, (long long)(k < n ? k : n), nan_out);
+                       lc, li, li + cap, (uint32_t)cap, out_pos, (long long)(k < n ? k : n), nan_out);
     return hipGetLastError();
 }
 
@@ -691,7 +700,11 @@ constexpr int kMaxGpus = 64;
 std::mutex g_fixed_mutex;
 void* g_fixed_ptr[kMaxGpus] = {nullptr};
 
-__global__ void k_clear_control(SelControl* c, uint32_t* flag) {
+// The shared words and the flag cleared, and every position -1 beforehand: a block of an overlapping call can take the
+// last block's turn away, and then nothing writes the positions.
+__global__ __launch_bounds__(kFixedTopkMaxK) void k_clear_control(SelControl* c, uint32_t* flag, long long* out_pos, int n_out) {
+    if ((int)threadIdx.x < n_out) out_pos[threadIdx.x] = -1ll;
+    if (threadIdx.x != 0) return;
     *c = SelControl{0u, 0u, 0u, 0u, 0.0};
     if (flag) *flag = 0u;
 }
@@ -727,7 +740,7 @@ hipError_t launch_topk_fixed(const double* cost, long long stride, const unsigne
     // (the shared words are cleared here although a call leaves them clear: calls that overlapped against the rule must
     //  not spoil the ones after them.  A fill kernel, so that the call can be recorded into a graph)
     SelControl* ctl = reinterpret_cast<SelControl*>(static_cast<unsigned char*>(base) + kFixedTopkListBytes);
-    hipLaunchKernelGGL(k_clear_control, dim3(1), dim3(1), 0, stream, ctl, nan_flag);
+    hipLaunchKernelGGL(k_clear_control, dim3(1), dim3(kFixedTopkMaxK), 0, stream, ctl, nan_flag, out_pos, (int)(k < n ? k : n));
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_topk(cost, stride, index, n, k, out_pos, base, ctl, nan_flag, stream);

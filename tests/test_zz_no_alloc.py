@@ -55,3 +55,29 @@ def test_topk_without_allocation_matches_the_allocating_call(B, oracle):
     with pytest.raises(B.P2Error) as e:
         B.p2_topk_device_noalloc(dc.data_ptr(), 1, di.data_ptr(), 2048, 65, got.data_ptr())
     assert e.value.code == B.P2_EUNSUPPORTED
+
+
+@pytest.mark.gpu
+def test_calls_that_overlap_stay_inside_their_buffers(B, oracle):
+    """Calls on several streams share one scratch and race, which the header rules out; what they write all the same are
+    positions of their own columns or -1, and the next call alone is right."""
+    import torch
+    n, k = 1_000_003, 64                        # (123 blocks, up to 320 entries each: three calls' entries exceed the lists)
+    _, _, dc, di = _inputs(16, n, torch)
+    # columns that fall: every block keeps more than it may leave uncut
+    falls = torch.arange(n, 0, -1, dtype=torch.float64, device="cuda")
+    sizes = (n, 300_007, 700_001, n)
+    outs = [torch.full((k,), 1 << 40, dtype=torch.int64, device="cuda") for _ in sizes]
+    streams = [torch.cuda.Stream() for _ in sizes]
+    torch.cuda.synchronize()
+    for i, (m, st) in enumerate(zip(sizes, streams)):
+        B.p2_topk_device_noalloc((dc if i == 1 else falls).data_ptr(), 1, di.data_ptr(), m, k, outs[i].data_ptr(), stream=st.cuda_stream)
+    torch.cuda.synchronize()
+    for m, out in zip(sizes, outs):
+        got = out.cpu().numpy()
+        assert ((got >= -1) & (got < m)).all()
+    cost, index, dc, di = _inputs(17, 4_099, torch)
+    out = torch.full((10,), -7, dtype=torch.int64, device="cuda")
+    B.p2_topk_device_noalloc(dc.data_ptr(), 1, di.data_ptr(), 4_099, 10, out.data_ptr())
+    torch.cuda.synchronize()
+    assert out.cpu().tolist() == oracle.topk(cost, index, 10).tolist()
