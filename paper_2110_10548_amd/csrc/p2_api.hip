@@ -1542,7 +1542,6 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             ++post_launches;
             P2_HIP(launch_topk(J.cost, J.stride, J.index, J.n, J.k, J.out_pos, C.topk_scratch.p, C.topk_control.p, J.nan_flag, stream));
         }
-        C.topk_control_clear = true;
     }
     if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = post_launches; }
     P2_HIP(C.h_pos.ensure(sizeof(long long) * std::max<size_t>(topk_rows, 1)));
@@ -1583,6 +1582,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     if (topk_rows > 0)      // the selections flag a NaN cost in their query's counters
         P2_HIP(launch_copy_out(C.h_counters.p, C.counters.p, sizeof(DevCounters) * (size_t)n_queries, stream));
     P2_HIP(hipStreamSynchronize(stream));
+    if (!topk_big.empty()) C.topk_control_clear = true;      // (only now have the kernels run to their end)
     if (topk_rows > 0) {
         const DevCounters* hc = static_cast<const DevCounters*>(C.h_counters.p);
         for (int i = 0; i < n_queries; ++i)

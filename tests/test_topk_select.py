@@ -65,3 +65,24 @@ def test_shortlists_are_the_heads_of_the_sorted_lists(B, topk):
         for m in range(len(msg)):
             want = np.lexsort((full["programs"]["index"], full["cost"][:, m]))[:kk]
             assert np.array_equal(short["programs"]["index"][m * kk:(m + 1) * kk], full["programs"]["index"][want])
+
+
+@pytest.mark.gpu
+def test_shortlists_of_long_lists_in_a_batch(B):
+    """Queries with more than 2^18 valid programs: all blocks for one selection after the other, several of them (two
+    queries of different length, two message sizes) on one set of lists and shared words."""
+    def query(card, max_len, **more):
+        n, levels = int(np.prod(card)), len(card)
+        return dict(dict(card=card, axes=[n], placement=[card], reduce_axes=[0], max_len=max_len,
+                         bw=[12.7e9, 30e9, 50.3e9, 151e9, 307e9][-levels:], alpha=[2.3e-5, 1.5e-5, 1.1e-5, 5.7e-6, 1.9e-6][-levels:]), **more)
+    msg = [1e6, 5e8]
+    asked = [([2, 2, 2, 2], 7, 700), ([2, 2, 2, 2, 2], 6, 9), ([2, 2, 2], 4, 20)]
+    full = B.p2_synthesize_batch([query(card, max_len) for card, max_len, _ in asked], msg)
+    assert [len(f["programs"]) > 1 << 18 for f in full] == [True, True, False]
+    for _ in range(2):                       # (the second call finds the shared words as the first one left them)
+        short = B.p2_synthesize_batch([query(card, max_len, topk=k) for card, max_len, k in asked], msg)
+        for f, s, (_, _, k) in zip(full, short, asked):
+            for m in range(2):
+                want = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:k]
+                assert np.array_equal(s["programs"][m * k:(m + 1) * k], f["programs"][want])
+                assert np.array_equal(s["cost"][m * k:(m + 1) * k], f["cost"][want])
