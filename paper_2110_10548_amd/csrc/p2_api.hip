@@ -1015,14 +1015,14 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             }
             // The literal prefixes of the level.  (On a second stream of the slot they would overlap with the pair states'
             // kernels only if that stream had a hardware queue to itself, which it would take from another slot.)
+            // At the last level the goals behind a prefix that is one AllGather away from a state held in pairs are read off
+            // that state (the lists of the level before are still there: the children's kernel writes no state now).
+            const bool goals_from_pairs = !keep && max_pairs == 2 && len > 0 && n_l > 0;
             auto literal_prefixes = [&]() -> int32_t {
                 if (n_l == 0) return P2_OK;
                 P2_HIP(S.f_surv_literal.ensure(cap_l * sizeof(FrontSurvivor)));
                 P2_HIP(S.spans.begin(SpanRec::kLiteral, S.stream));
-                // At the last level the goals behind a prefix that is one AllGather away from a state held in pairs are read off
-                // that state (the lists of the level before are still there: the children's kernel writes no state now).
-                const bool from_pairs = !keep && max_pairs == 2 && len > 0;
-                if (from_pairs) {
+                if (goals_from_pairs) {
                     P2_HIP(S.lit_scratch.ensure(std::max(front_literal_goals_scratch_bytes(pl.R, pl.k, n_l),
                                                          n_l_literal > 0 ? front_literal_scratch_bytes(pl.R, pl.k, std::max(n_l, n_c2)) : 0)));
                     P2_HIP(S.f_rest.ensure((size_t)n_l * sizeof(uint32_t)));
@@ -1032,13 +1032,13 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                                                       S.lit_scratch.p, static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr,
                                                       static_cast<uint32_t*>(S.f_rest.p), S.stream));
                 }
-                if (!from_pairs || n_l_literal > 0) {
+                if (!goals_from_pairs || n_l_literal > 0) {
                     P2_HIP(S.lit_scratch.ensure(front_literal_scratch_bytes(pl.R, pl.k, std::max(n_l, n_c2))));
                     gs = S.lit_scratch.p;
                     P2_HIP(launch_front_classify_literal(dq, pl.R, pl.k, static_cast<const FrontEntry*>(S.f_literal[cur].p), n_l, len, keep ? 0 : 1,
                                                          static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr, gs,
-                                                         pl.max_row_classes, from_pairs ? static_cast<const uint32_t*>(S.f_rest.p) : nullptr,
-                                                         from_pairs ? &dctr->n_rest : nullptr, S.stream));
+                                                         pl.max_row_classes, goals_from_pairs ? static_cast<const uint32_t*>(S.f_rest.p) : nullptr,
+                                                         goals_from_pairs ? &dctr->n_rest : nullptr, S.stream));
                 }
                 P2_HIP(S.spans.end(S.stream));
                 return P2_OK;
@@ -1130,6 +1130,11 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                 P2_HIP(hipMemcpyAsync(dctr, &fix, sizeof(FrontCounters), hipMemcpyHostToDevice, S.stream));
                 P2_HIP(hipStreamSynchronize(S.stream));
             }
+            // The goals kernel and this function tell by rules of their own which literal prefixes are left to the literal
+            // kernels; where the rules part, some are judged by neither.
+            if (goals_from_pairs && hctr->n_rest != n_l_literal)
+                return fail(P2_EDEVICE, "internal: " + std::to_string(hctr->n_rest) + " literal prefixes left over at the last level, " +
+                                            std::to_string(n_l_literal) + " expected");
             {   // what the classification launches of this level worked on
                 const double j1 = grouped[0] ? (double)hctr->n_reps[0] : (double)n_s[0], j2 = grouped[1] ? (double)hctr->n_reps[1] : (double)n_s[1];
                 // (at the last level only the states from which an instruction can still end at the goal are walked)
