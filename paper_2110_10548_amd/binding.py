@@ -217,7 +217,17 @@ def _stats_dict(s):
 # Four levels of synthesis hierarchy have 83 920 valid programs of six instructions; longer lists take a second call.
 _FIRST_ROWS = 1 << 17
 _FIRST_ROWS_PER_QUERY = 4096           # (in a batch: three levels, five instructions have 2 549)
+_MAX_MSG, _MAX_TOPK = 64, 1024         # what a call may ask for: the library refuses more, and no room is made for it
 _own = threading.local()               # rows of this thread's last single-query call: results are copies of them
+
+
+def _first_rows(topks, n_msg, otherwise):
+    """Rows that the first call for these queries gets room for."""
+    if n_msg > _MAX_MSG or any(t > _MAX_TOPK for t in topks):
+        return 0
+    if n_msg > 0 and all(t > 0 for t in topks):       # (a shortlist in every query bounds the number)
+        return sum(topks) * n_msg
+    return otherwise
 
 
 def _room(rows, n_msg):
@@ -252,10 +262,8 @@ class Batch:
         self.n_msg = len(self._msg)
         self._offs = np.zeros(self.nq + 1, dtype=np.int64)
         self._stats = (p2_stats * self.nq)()
-        # with a shortlist asked for in every query the number of rows is bounded beforehand
-        topks = [int(q.get("topk", 0)) for q in queries]
-        self._alloc(sum(topks) * self.n_msg if all(t > 0 for t in topks) and self.n_msg > 0
-                    else min(_FIRST_ROWS_PER_QUERY * self.nq, 2 * _FIRST_ROWS))
+        self._alloc(_first_rows([int(q.get("topk", 0)) for q in queries], self.n_msg,
+                                min(_FIRST_ROWS_PER_QUERY * self.nq, 2 * _FIRST_ROWS)))
 
     def _alloc(self, cap):
         self.cap = cap
@@ -317,7 +325,7 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
         return lib().p2_synthesize(C.byref(h.c), _p(axes_a, C.c_int32), len(axes_a), _p(pl, C.c_int32), _p(red, C.c_int32),
                                    len(red), max_len, _p(msg, C.c_double), n_msg, C.byref(opt), progs_p, cost_p, cap_,
                                    C.byref(count), C.byref(cands), C.byref(st))
-    rows = cap if cap is not None else topk * n_msg if topk > 0 and n_msg > 0 else _FIRST_ROWS
+    rows = cap if cap is not None else _first_rows([topk], n_msg, _FIRST_ROWS)
     while True:
         progs, cost = _room(max(rows, 1), max(n_msg, 1))
         rc = call(progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double), rows)

@@ -127,3 +127,15 @@ def test_workloads_are_seeded(B):
                                                                                   workloads.config(i)["axes"])))
               for i in (1, 2, 3, 4)]
     assert counts == [2, 10, 84, 140]
+
+
+def test_what_the_library_refuses_gets_no_room(B):
+    """More message sizes or a longer shortlist than a call may ask for: the library's error, not the lack of memory for it."""
+    q = dict(card=[2, 2], axes=[4], placement=[[2, 2]], reduce_axes=[0], max_len=2, bw=[1e9, 1e10], alpha=[1e-5, 1e-6])
+    for msg, topk in (([1.0] * 100_000, 0), ([1.0] * 64, 2 ** 31 - 1)):
+        with pytest.raises(B.P2Error) as e:
+            B.p2_synthesize(**q, msg_bytes=msg, topk=topk)
+        assert e.value.code == B.P2_EUNSUPPORTED
+        with pytest.raises(B.P2Error) as e:
+            B.p2_synthesize_batch([dict(q, topk=topk)] * 3, msg)
+        assert e.value.code == B.P2_EUNSUPPORTED
