@@ -4,6 +4,7 @@ Every step of the evaluation runs inside the library's kernels.  Importing this 
 fails loudly if the library has not been built (python paper_2110_10548_amd/build.py,
 or __graft_entry__.build()).
 """
+import bisect
 import ctypes as C
 import os
 import threading
@@ -218,6 +219,7 @@ def _stats_dict(s):
 _FIRST_ROWS = 1 << 17
 _FIRST_ROWS_PER_QUERY = 4096           # (in a batch: three levels, five instructions have 2 549)
 _MAX_MSG, _MAX_TOPK = 64, 1024         # what a call may ask for: the library refuses more, and no room is made for it
+_PIECE_BYTES = 1 << 20                 # rows of several queries of a batch share copies of at most this size
 _own = threading.local()               # rows of this thread's last single-query call: results are copies of them
 
 
@@ -284,12 +286,18 @@ class Batch:
             return
 
     def results(self):
-        # one copy of all rows (the buffers are written again by the next call), a piece of it per query
+        # the rows are copied (the buffers are written again by the next call) a megabyte at a time, and a query gets its
+        # piece of a copy: whoever keeps one query's rows keeps no more than that beside them
         offs = self._offs.tolist()
-        progs, cost = self._progs[:offs[-1]].copy(), self._cost[:offs[-1], :self.n_msg].copy()
-        names = _STATS_FIELDS
-        return [{"programs": progs[a:b], "cost": cost[a:b], "stats": dict(zip(names, row))}
-                for a, b, row in zip(offs, offs[1:], np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist())]
+        limit = _PIECE_BYTES // (PROGRAM_DTYPE.itemsize + 8 * self.n_msg)
+        out, first, end, progs, cost = [], 0, -1, None, None
+        for i, row in enumerate(np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist()):
+            a, b = offs[i], offs[i + 1]
+            if b > end:
+                first, end = a, offs[max(i + 1, bisect.bisect_right(offs, a + limit) - 1)]
+                progs, cost = self._progs[first:end].copy(), self._cost[first:end, :self.n_msg].copy()
+            out.append({"programs": progs[a - first:b - first], "cost": cost[a - first:b - first], "stats": dict(zip(_STATS_FIELDS, row))})
+        return out
 
     def run(self):
         self.run_raw()

@@ -139,3 +139,23 @@ def test_what_the_library_refuses_gets_no_room(B):
         with pytest.raises(B.P2Error) as e:
             B.p2_synthesize_batch([dict(q, topk=topk)] * 3, msg)
         assert e.value.code == B.P2_EUNSUPPORTED
+
+
+def test_a_kept_result_keeps_no_more_than_a_megabyte_beside_it(B):
+    q = dict(card=[2, 2], axes=[4], placement=[[2, 2]], reduce_axes=[0], max_len=2)
+    b = B.Batch([q] * 400, [1.0, 2.0, 3.0])
+    rows = np.random.default_rng(5).choice([0, 0, 3, 700, 5000], size=400)
+    rows[:2], rows[200] = 0, 60_000                     # (nothing at first; one query with more than a megabyte)
+    offs = np.concatenate([[0], np.cumsum(rows)])
+    b._alloc(int(offs[-1]) + 10)
+    b._offs[:] = offs
+    b._progs["index"] = np.arange(len(b._progs))
+    b._cost[:] = np.arange(len(b._progs))[:, None] * [1, 2, 3]
+    out = b.results()
+    b._progs["index"], b._cost[:] = 7, 7.0              # (the results are copies)
+    assert len(out) == 400
+    for i, r in enumerate(out):
+        want = np.arange(offs[i], offs[i + 1])
+        assert np.array_equal(r["programs"]["index"], want) and np.array_equal(r["cost"], want[:, None] * [1, 2, 3])
+        beside = r["programs"].base.nbytes + r["cost"].base.nbytes - r["programs"].nbytes - r["cost"].nbytes
+        assert beside <= 1 << 20
