@@ -220,7 +220,8 @@ _FIRST_ROWS = 1 << 17
 _FIRST_ROWS_PER_QUERY = 4096           # (in a batch: three levels, five instructions have 2 549)
 _MAX_MSG, _MAX_TOPK = 64, 1024         # what a call may ask for: the library refuses more, and no room is made for it
 _PIECE_BYTES = 1 << 20                 # rows of several queries of a batch share copies of at most this size
-_own = threading.local()               # rows of this thread's last single-query call: results are copies of them
+_KEEP_BYTES = 1 << 24                  # buffers that a call has filled further than this are not kept
+_own = threading.local()               # where this thread's single-query calls have their rows put: results are copies
 
 
 def _first_rows(topks, n_msg, otherwise):
@@ -232,15 +233,21 @@ def _first_rows(topks, n_msg, otherwise):
     return otherwise
 
 
-def _room(rows, n_msg):
-    """Buffers for so many rows, the ones of the thread's last call where they are large enough (a fresh mapping of the
-    first call's room costs more than evaluating a small query)."""
-    if getattr(_own, "rows", 0) < rows or _own.cost.shape[1] != n_msg:
-        progs, cost = np.zeros(rows, dtype=PROGRAM_DTYPE), np.zeros((rows, n_msg), dtype=np.float64)
-        if rows > _FIRST_ROWS:
-            return progs, cost
-        _own.progs, _own.cost, _own.rows = progs, cost, rows
-    return _own.progs, _own.cost
+def _take_room(rows, n_msg):
+    """Buffers for so many rows: the thread's, where they are large enough (a fresh mapping of the first call's room costs
+    more than evaluating a small query).  They are the caller's until it hands them to _keep_room."""
+    progs, cost = _own.__dict__.pop("room", (None, None)) if rows <= _FIRST_ROWS else (None, None)
+    if progs is None or len(progs) < rows:
+        progs = np.zeros(rows, dtype=PROGRAM_DTYPE)
+    if cost is None or len(cost) < rows * n_msg:
+        cost = np.zeros(rows * n_msg, dtype=np.float64)
+    return progs, cost
+
+
+def _keep_room(progs, cost, filled):
+    """The buffers for the thread's next call (until p2_release_thread), unless they are large."""
+    if len(progs) <= _FIRST_ROWS and len(cost) <= _FIRST_ROWS * _MAX_MSG and filled <= _KEEP_BYTES:
+        _own.room = progs, cost
 
 
 class Batch:
@@ -335,15 +342,16 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
                                    C.byref(count), C.byref(cands), C.byref(st))
     rows = cap if cap is not None else _first_rows([topk], n_msg, _FIRST_ROWS)
     while True:
-        progs, cost = _room(max(rows, 1), max(n_msg, 1))
+        progs, cost = _take_room(max(rows, 1), max(n_msg, 1))
         rc = call(progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double), rows)
+        n = count.value if rc == P2_OK else 0
+        out = progs[:n].copy(), cost[:n * n_msg].reshape(n, n_msg).copy()
+        _keep_room(progs, cost, n * (PROGRAM_DTYPE.itemsize + 8 * n_msg))
         if rc != P2_ENOSPC or cap is not None:
             break
         rows = count.value
     _check(rc)
-    n = count.value
-    return {"programs": progs[:n].copy(), "cost": cost[:n, :n_msg].copy(), "candidates": cands.value,
-            "stats": _stats_dict(st)}
+    return {"programs": out[0], "cost": out[1], "candidates": cands.value, "stats": _stats_dict(st)}
 
 
 def p2_search_placements(card, axes, reduce_sets, max_len, msg_bytes, bw=None, alpha=None, weights=None, n_chunks=0,
