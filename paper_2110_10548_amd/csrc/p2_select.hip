@@ -572,8 +572,9 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long
     }
 }
 
-// Many selections in one launch: block b does job b from start to end.  A tile of a short list (at most 2048 entries,
-// K <= 256) is 256 threads wide, so that several jobs share a compute unit; longer lists take 1024.
+// Many selections in one launch: block b does job b from start to end.  A launch of lists of at most 512 entries (a tile,
+// K <= 64) takes a wavefront each: nothing there is worth a barrier between wavefronts.  A tile of lists of at most 2048
+// entries (K <= 256) is 256 threads wide, so that several jobs share a compute unit; longer lists take 1024.
 template <int NT, int B>
 __global__ __launch_bounds__(NT) void k_topk_jobs(const DevTopkJob* __restrict__ jobs) {
     __shared__ SelShared<NT, B> S;
@@ -636,7 +637,8 @@ hipError_t launch_rank_sort(const unsigned long long* valid, const unsigned long
 
 hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, long long max_n, hipStream_t stream) {
     if (n_jobs == 0) return hipSuccess;
-    if (max_k <= 256 && max_n <= 2048) hipLaunchKernelGGL((k_topk_jobs<256, 512>), dim3(n_jobs), dim3(256), 0, stream, jobs);
+    if (max_k <= 64 && max_n <= 512) hipLaunchKernelGGL((k_topk_jobs<kWave, 128>), dim3(n_jobs), dim3(kWave), 0, stream, jobs);
+    else if (max_k <= 256 && max_n <= 2048) hipLaunchKernelGGL((k_topk_jobs<256, 512>), dim3(n_jobs), dim3(256), 0, stream, jobs);
     else hipLaunchKernelGGL((k_topk_jobs<kSelThreads, kSelBuffer>), dim3(n_jobs), dim3(kSelThreads), 0, stream, jobs);
     return hipGetLastError();
 }

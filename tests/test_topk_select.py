@@ -86,3 +86,25 @@ def test_shortlists_of_long_lists_in_a_batch(B):
                 want = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:k]
                 assert np.array_equal(s["programs"][m * k:(m + 1) * k], f["programs"][want])
                 assert np.array_equal(s["cost"][m * k:(m + 1) * k], f["cost"][want])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("topk", [1, 10, 64, 65])
+@pytest.mark.parametrize("engine", [0, 3])
+def test_shortlists_of_short_lists(B, topk, engine):
+    """Lists of at most 512 programs all over the batch: a wavefront each up to 64 kept (a list within a wavefront, of two,
+    and one entry alone), wider blocks above.  Equal links and no latency make many costs equal: indices decide."""
+    queries = []
+    for card, max_len in (([4], 1), ([4], 2), ([2, 4], 3), ([2, 4], 5), ([2, 2, 2, 2], 3)):
+        n, levels = int(np.prod(card)), len(card)
+        for bw, alpha in (([25e9] * levels, [0.0] * levels), ([25e9, 100e9, 200e9, 300e9][:levels], [20e-6, 10e-6, 5e-6, 2e-6][:levels])):
+            queries.append(dict(card=card, axes=[n], placement=[card], reduce_axes=[0], max_len=max_len, bw=bw, alpha=alpha, engine=engine))
+    msg = [1e6, 5e8]
+    full, short = B.p2_synthesize_batch(queries, msg), B.p2_synthesize_batch([dict(q, topk=topk) for q in queries], msg)
+    assert [len(f["programs"]) for f in full][::2] == [1, 3, 35, 110, 138]
+    for f, s in zip(full, short):
+        kk = min(topk, len(f["programs"]))
+        for m in range(len(msg)):
+            want = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:kk]
+            assert np.array_equal(s["programs"][m * kk:(m + 1) * kk], f["programs"][want])
+            assert np.array_equal(s["cost"][m * kk:(m + 1) * kk], f["cost"][want])
