@@ -1467,7 +1467,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             bool ordered = false;
             for (int32_t m : E.members) ordered |= runs[m].topk == 0;
             if (ordered) {
-                ++post_launches;
+                post_launches += front_rank_launches(E.n_valid);
                 P2_HIP(launch_front_rank(list, E.n_valid, static_cast<unsigned long long*>(C.f_rank_runs.p), rank, stream));
             }
             for (size_t m = 0; m < E.members.size(); ++m) {

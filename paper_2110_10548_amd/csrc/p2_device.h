@@ -394,7 +394,9 @@ hipError_t launch_front_emit(const DevQuery* q, uint32_t query, const FrontEntry
                              hipStream_t stream);
 // The counters to pinned host memory; clears those that the second half of a level counts with.
 hipError_t launch_front_counters_out(FrontCounters* host_dst, FrontCounters* ctr, hipStream_t stream);
+// runs: n words of scratch.
 hipError_t launch_front_rank(const unsigned long long* valid, uint32_t n, unsigned long long* runs, uint32_t* rank, hipStream_t stream);
+int front_rank_launches(uint32_t n);
 // The rows of n_jobs queries in one launch (jobs in device memory; max_valid = the largest n_valid among them).
 hipError_t launch_front_finish(const DevQuery* queries, const FrontFinish* jobs, uint32_t n_jobs, uint32_t max_valid, hipStream_t stream);
 

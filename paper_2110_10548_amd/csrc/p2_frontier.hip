@@ -1842,9 +1842,26 @@ __global__ __launch_bounds__(64) void k_front_counters_out(FrontCounters* __rest
     }
 }
 
-// rank[i] = number of entries of the list smaller than entry i (distinct keys), in two launches: every block sorts its
-// run of kRankRun entries in LDS, then every entry's place in each of the other runs is found by bisection.  (Counting the
-// smaller ones outright takes n^2 comparisons: 1.26 ms for the 83 920 programs of a 512-device query, 0.06 ms this way.)
+// rank[i] = number of entries of the list smaller than entry i (distinct keys).  Short lists: the smaller ones are
+// counted outright, n comparisons an entry in a chain (up to 256 programs 3 us, 571 11, 1 646 27, 83 920 1 260).
+__global__ __launch_bounds__(256) void k_front_rank_few(const unsigned long long* __restrict__ in, uint32_t n, uint32_t* __restrict__ rank) {
+    __shared__ unsigned long long tile[256];
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    const unsigned long long mine = i < n ? in[i] : 0ull;
+    uint32_t r = 0;
+    for (uint32_t first = 0; first < n; first += 256u) {
+        const uint32_t j = first + threadIdx.x, left = n - first < 256u ? n - first : 256u;
+        tile[threadIdx.x] = j < n ? in[j] : ~0ull;
+        __syncthreads();
+        for (uint32_t u = 0; u < left; ++u) r += tile[u] < mine ? 1u : 0u;
+        __syncthreads();
+    }
+    if (i < n) rank[i] = r;
+}
+// Longer lists, in two launches: every block sorts its run of kRankRun entries in LDS (15 us, a chain of 66 exchanges that
+// takes as long for a run of few entries), then every entry's place in each of the other runs is found by bisection (4 us
+// for a run or two; 83 920 programs 60 us in all).  Counting takes these 19 us at some 1 200 entries.
+constexpr uint32_t kRankFew = 1024;
 constexpr int kRankRun = 2048, kRankThreads = 1024;
 __global__ __launch_bounds__(kRankThreads) void k_front_rank_runs(const unsigned long long* __restrict__ in, uint32_t n,
                                                                   unsigned long long* __restrict__ runs) {
@@ -2103,8 +2120,13 @@ hipError_t launch_front_emit(const DevQuery* q, uint32_t query, const FrontEntry
     return hipGetLastError();
 }
 
+int front_rank_launches(uint32_t n) { return n == 0 ? 0 : n <= kRankFew ? 1 : 2; }
 hipError_t launch_front_rank(const unsigned long long* valid, uint32_t n, unsigned long long* runs, uint32_t* rank, hipStream_t stream) {
     if (n == 0) return hipSuccess;
+    if (n <= kRankFew) {
+        hipLaunchKernelGGL(k_front_rank_few, dim3((n + 255u) / 256u), dim3(256), 0, stream, valid, n, rank);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_front_rank_runs, dim3((n + kRankRun - 1u) / kRankRun), dim3(kRankThreads), 0, stream, valid, n, runs);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
