@@ -120,7 +120,7 @@ struct SpanRec {
 // the chip where one does not.
 constexpr int kFrontSlots = 4;
 struct FrontSlot {
-    hipStream_t stream = nullptr;         // (created by Ctx::open_slot_streams, together with those of the other slots)
+    hipStream_t stream = nullptr;         // (created by Ctx::open_slot_streams)
     DevBuf f_entries[2], f_states[2], f_sums[2], f_entries2[2], f_states2[2], f_sums2[2], f_literal[2];
     DevBuf f_surv, f_surv_literal, f_unknown, f_ctr, lit_scratch;
     DevBuf f_hash[2], f_hash2[2], f_table, f_rep[2], f_replist[2], f_codes[2], f_unk[2];     // search for equal states
@@ -165,7 +165,7 @@ struct Ctx {
     static constexpr int kSpareStreams = 6;
     hipStream_t spare_streams[kSpareStreams] = {};          // created beside the slots' streams and found to share a queue with one: never used
     DevBuf probe_sink;
-    hipError_t open_slot_streams();
+    hipError_t open_slot_streams(int n_slots);
     hipError_t open_topk_control(hipStream_t stream) {
         const void* before = topk_control.p;
         hipError_t e = topk_control.ensure(p2::topk_control_bytes());
@@ -187,18 +187,22 @@ thread_local Ctx g_ctx;
 // of two) and gives the slots streams that do not take turns with each other; the other streams stay unused.  With
 // fewer independent queues than slots the remaining slots share.  Only the overlap depends on this, never a result;
 // a pair that is wrongly taken to share (the host thread lost its turn while timing) costs overlap and nothing else.
+// The look takes some 5 ms, once per thread, and a call with one enumeration has nothing to overlap: it opens slot 0's
+// stream alone, and the look waits for the first call that uses a second slot (which starts from that stream).
 __global__ __launch_bounds__(64) void k_queue_probe(uint32_t* sink, int n) {
     uint32_t x = threadIdx.x + 1u;
     for (int i = 0; i < n; ++i) x = x * 1664525u + 1013904223u;
     if (x == 0x9e3779b9u) sink[0] = x;               // (keeps the loop; the sink is the library's own word)
 }
-hipError_t Ctx::open_slot_streams() {
-    if (slots[0].stream) return hipSuccess;
+hipError_t Ctx::open_slot_streams(int n_slots) {
+    if (slots[n_slots > 1 ? 1 : 0].stream) return hipSuccess;
+    if (n_slots == 1) return hipStreamCreateWithFlags(&slots[0].stream, hipStreamNonBlocking);
     constexpr int kCandidates = kFrontSlots + kSpareStreams;
     constexpr int kProbeSteps = 8000;                 // some 0.1 ms: several times what a launch and a wait take
     hipStream_t made[kCandidates] = {};
     hipError_t e = probe_sink.ensure(256);
-    for (int i = 0; i < kCandidates && e == hipSuccess; ++i) e = hipStreamCreateWithFlags(&made[i], hipStreamNonBlocking);
+    made[0] = slots[0].stream;                       // (of an earlier call with one enumeration)
+    for (int i = made[0] ? 1 : 0; i < kCandidates && e == hipSuccess; ++i) e = hipStreamCreateWithFlags(&made[i], hipStreamNonBlocking);
     auto timed = [&](hipStream_t a, hipStream_t b, double& ms) -> hipError_t {
         const auto t0 = std::chrono::steady_clock::now();
         hipLaunchKernelGGL(k_queue_probe, dim3(1), dim3(64), 0, a, static_cast<uint32_t*>(probe_sink.p), kProbeSteps);
@@ -230,7 +234,7 @@ hipError_t Ctx::open_slot_streams() {
             if (!taken[c]) { chosen[n_chosen++] = c; taken[c] = true; }
     }
     if (e != hipSuccess) {
-        for (hipStream_t st : made) if (st) (void)hipStreamDestroy(st);
+        for (hipStream_t st : made) if (st && st != slots[0].stream) (void)hipStreamDestroy(st);
         return e;
     }
     for (int t = 0; t < kFrontSlots; ++t) slots[t].stream = made[chosen[t]];
@@ -1302,11 +1306,11 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             one_at_a_time |= queries[i].opt && (queries[i].opt->flags & P2_FLAG_ONE_ENUMERATION_AT_A_TIME) != 0u;
         const int n_slots = one_at_a_time ? 1 : (int)std::min<size_t>(kFrontSlots, enums.size());
         P2_HIP(hipEventRecord(C.front_go, stream));
-        if (!C.slots[0].stream) {            // (first time: the streams are chosen by timing, on a quiet device)
+        if (n_slots > 1 && !C.slots[1].stream) {     // (first time: the streams are chosen by timing, on a quiet device)
             P2_HIP(hipStreamSynchronize(stream));
             P2_HIP(hipStreamSynchronize(C.copy_stream));
         }
-        P2_HIP(C.open_slot_streams());
+        P2_HIP(C.open_slot_streams(n_slots));
         for (int t = 0; t < n_slots; ++t) {
             FrontSlot& S = C.slots[t];
             P2_HIP(hipStreamWaitEvent(S.stream, C.front_go, 0));
