@@ -71,8 +71,10 @@ int32_t p2_enumerate_placements(const p2_hierarchy* h, const int32_t* axes, int3
 #define P2_ENGINE_AUTO 0      /* shared-prefix engine where it applies, else the compact engine; the
                                  literal engine for the candidates they cannot hold; the frontier
                                  engine above 2^30 candidates, and in place of the compact engine
-                                 where that is slower (more than 64 devices from 100 candidates on;
-                                 otherwise from 8e7 candidates x devices on)                      */
+                                 where that is slower (more than 64 devices from 100 candidates on,
+                                 unless a batch has more than four of them that differ in structure
+                                 and walking all of them is the faster; otherwise from 8e7
+                                 candidates x devices on)                                         */
 #define P2_ENGINE_LITERAL 1   /* R x k masks of R bits per candidate in LDS, one wavefront each   */
 #define P2_ENGINE_COMPACT 2   /* per device one chunk set and one contribution mask, in LDS; one
                                  candidate per lane                                               */

@@ -327,12 +327,48 @@ constexpr unsigned long long kWalkMax = 1ull << 30;
 // devices, 4.2 M programs: 0.55 ms against 14.3 ms; 16 x 12, 168 420: 0.59 against 11.6; 12 x 12, 420: 0.32 against
 // 0.70), the compact engine less than that only for few devices and candidates (6 x 8 devices, 168 420 programs: 0.37 ms
 // against 0.47; 3.4 M: 1.25 against 0.56; 3 x 4, 3.4 M: 0.32 against 0.52; 80 devices, 30 programs: 0.28 against 0.27).
+// This is a query by itself; what a batch of them does, walks_together() says.
 bool pruned_is_faster(const p2::Plan& pl) {
     bool shared = pl.R <= 64;
     for (const p2::Pattern& p : pl.patterns) shared = shared && p2::reg_shape_of(p.g, p.s, p.master, 6) >= 0;
     if (shared) return false;
     if (pl.R > 64) return pl.n_candidates >= 100;
     return pl.n_candidates * (unsigned long long)pl.R >= 80000000ull;
+}
+
+// What decides about validity is the same for both: group, chunks, patterns, alphabet and size limit.
+bool same_structure(const p2::Plan& a, const p2::Plan& b) {
+    if (a.R != b.R || a.k != b.k || a.max_len != b.max_len || a.alphabet != b.alphabet || a.n_ops != b.n_ops ||
+        a.patterns.size() != b.patterns.size() || a.n_candidates != b.n_candidates)
+        return false;
+    for (int t = 0; t < a.n_ops; ++t)
+        if (a.ops[t] != b.ops[t]) return false;
+    for (size_t t = 0; t < a.patterns.size(); ++t)
+        if (a.patterns[t].g != b.patterns[t].g || a.patterns[t].s != b.patterns[t].s || a.patterns[t].master != b.patterns[t].master ||
+            a.patterns[t].n_groups != b.patterns[t].n_groups)
+            return false;
+    return true;
+}
+
+// Engine AUTO, several groups of more than 64 devices that differ in structure (`plans`, one of each): the walk takes all
+// of them in a launch, the enumerations run four at a time.  Up to four enumerations cost no more than one, and each is
+// faster than its walk; beyond, the walks of small groups with few candidates are done first.  Both sides as they
+// were measured, in us (groups of 65 to 512 devices, one to three levels, 155 to 168 420 candidates, one to 32 of them):
+// a walk 2.5 per device of the largest group, for a candidate's chain of steps, and 2.6 per 10^6 candidates x devices x
+// devices (which a step visits, and whose masks are that long, or the chunk sets: the mean of the two counts stands for
+// both); an enumeration 20 and 22 a level, of which the programs of a single level, one pattern, use two.  Thirty-two groups of 65 to 128 devices: 420 candidates 0.69 ms walked, 1.90
+// enumerated; 2 070: 1.45 and 2.17; 8 420: 7.98 and 2.65.  Of 129 to 256: 155: 1.05 and 1.90; 780: 3.09 and 1.88.
+bool walks_together(const std::vector<const p2::Plan*>& plans) {
+    if (plans.size() <= (size_t)kFrontSlots) return false;
+    double walk = 0.0, pruned = 100.0, devices = 0.0;
+    for (const p2::Plan* pl : plans) {
+        if (p2::compact_lanes(pl->R, pl->k) == 0) return false;
+        const double wide = 0.5 * (pl->R + pl->k);
+        devices = std::max(devices, wide);
+        walk += 2.6e-6 * (double)pl->n_candidates * pl->R * wide;
+        pruned += 20.0 + 22.0 * (pl->patterns.size() == 1 ? std::min(pl->max_len, 2) : pl->max_len);
+    }
+    return walk + 2.5 * devices < pruned;
 }
 
 struct QueryRun {
@@ -399,6 +435,9 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         for (int i = 0; i < n_queries; ++i)
             if (plan_st[i] != P2_OK) return fail(plan_st[i], "query " + std::to_string(i) + ": " + plan_err[i]);
     }
+    bool share_validity = true;              // (see below)
+    for (int i = 0; i < n_queries; ++i)
+        if (queries[i].opt && (queries[i].opt->flags & P2_FLAG_EVALUATE_EVERY_QUERY)) share_validity = false;
     for (int i = 0; i < n_queries; ++i) {
         const p2_query& Q = queries[i];
         runs[i].topk = Q.opt ? Q.opt->topk : 0;
@@ -449,14 +488,24 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         for (const Pattern& p : pl.patterns) runs[i].wave_cost = runs[i].wave_cost && reg_shape_of(p.g, p.s, p.master, 6) >= 0;
     }
 
+    {
+        std::vector<const Plan*> large;              // groups of more than 64 devices that AUTO would enumerate, one of each structure
+        for (const QueryRun& r : runs) {
+            if (!r.flat_counts || r.plan.R <= 64) continue;
+            bool seen = false;
+            for (size_t t = 0; t < large.size() && !seen && share_validity; ++t) seen = same_structure(*large[t], r.plan);
+            if (!seen) large.push_back(&r.plan);
+        }
+        if (walks_together(large))
+            for (QueryRun& r : runs)
+                if (r.flat_counts && r.plan.R > 64) r.frontier = r.flat_counts = false;
+    }
+
     // Validity depends on the reduction group, the chunks, the patterns and the alphabet only (not on the
     // links, nor on where the placement puts the group in the system): a query that equals an earlier one of
     // the batch in these is not evaluated again; it takes over the list of valid programs and the counts, and
     // only its costs are worked out, from its own bandwidth rows.  (The frontier engine does the same further
     // down.)  P2_FLAG_EVALUATE_EVERY_QUERY in any query's options switches this off for the batch.
-    bool share_validity = true;
-    for (int i = 0; i < n_queries; ++i)
-        if (queries[i].opt && (queries[i].opt->flags & P2_FLAG_EVALUATE_EVERY_QUERY)) share_validity = false;
     {
         for (int i = 0; i < n_queries && share_validity; ++i) {
             QueryRun& r = runs[i];
@@ -464,17 +513,9 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             if (r.frontier || pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.n_candidates == 0) continue;
             for (int j = 0; j < i && r.same_as < 0; ++j) {
                 const QueryRun& c = runs[j];
-                const Plan& o = c.plan;
-                if (c.same_as >= 0 || c.frontier || o.hierarchy != P2_HIERARCHY_COLLAPSED || c.engine != r.engine || c.shared != r.shared ||
-                    c.regs != r.regs || o.R != pl.R || o.k != pl.k || o.max_len != pl.max_len || o.alphabet != pl.alphabet ||
-                    o.n_ops != pl.n_ops || o.patterns.size() != pl.patterns.size() || o.n_candidates != pl.n_candidates)
-                    continue;
-                bool eq = true;
-                for (int t = 0; t < pl.n_ops && eq; ++t) eq = o.ops[t] == pl.ops[t];
-                for (size_t t = 0; t < pl.patterns.size() && eq; ++t)
-                    eq = o.patterns[t].g == pl.patterns[t].g && o.patterns[t].s == pl.patterns[t].s &&
-                         o.patterns[t].master == pl.patterns[t].master && o.patterns[t].n_groups == pl.patterns[t].n_groups;
-                if (eq) r.same_as = j;
+                if (c.same_as < 0 && !c.frontier && c.plan.hierarchy == P2_HIERARCHY_COLLAPSED && c.engine == r.engine && c.shared == r.shared &&
+                    c.regs == r.regs && same_structure(c.plan, pl))
+                    r.same_as = j;
             }
         }
     }
@@ -920,16 +961,9 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         int found = -1;
         for (size_t e = 0; e < enums.size() && found < 0 && share_validity; ++e) {
             const Plan& o = runs[enums[e].leader].plan;
-            if (o.R != pl.R || o.k != pl.k || o.max_len != pl.max_len || o.alphabet != pl.alphabet || o.n_ops != pl.n_ops ||
-                o.patterns.size() != pl.patterns.size() || o.n_candidates != pl.n_candidates ||
-                o.max_row_classes != pl.max_row_classes || o.frontier_pairs != pl.frontier_pairs || runs[enums[e].leader].flat_counts != r.flat_counts)
-                continue;
-            bool eq = true;
-            for (int t = 0; t < pl.n_ops && eq; ++t) eq = o.ops[t] == pl.ops[t];
-            for (size_t t = 0; t < pl.patterns.size() && eq; ++t)
-                eq = o.patterns[t].g == pl.patterns[t].g && o.patterns[t].s == pl.patterns[t].s &&
-                     o.patterns[t].master == pl.patterns[t].master && o.patterns[t].n_groups == pl.patterns[t].n_groups;
-            if (eq) found = (int)e;
+            if (o.max_row_classes == pl.max_row_classes && o.frontier_pairs == pl.frontier_pairs &&
+                runs[enums[e].leader].flat_counts == r.flat_counts && same_structure(o, pl))
+                found = (int)e;
         }
         if (found < 0) { enums.emplace_back(); found = (int)enums.size() - 1; enums[found].leader = i; }
         r.enum_id = found;
