@@ -108,3 +108,56 @@ def test_shortlists_of_short_lists(B, topk, engine):
             want = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:kk]
             assert np.array_equal(s["programs"][m * kk:(m + 1) * kk], f["programs"][want])
             assert np.array_equal(s["cost"][m * kk:(m + 1) * kk], f["cost"][want])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,where", [(4_194_304, 33, "skipped"), (4_200_001, 64, "all but k - 1"), (300_001, 64, "all but k - 1"), (20_000, 7, "all but k - 1"),
+                                       (5_000, 64, "everywhere"), (4_194_304, 10, "everywhere")])
+def test_nan_costs(B, n, k, where):
+    """Columns with a bound from a sample (of every 4 096 entries the first 64), without, and of one block: a NaN is flagged
+    wherever it stands and never selected, and the words that the blocks share are left clean."""
+    import torch
+    rng = np.random.default_rng(n + k)
+    clean, index = rng.normal(size=n), rng.permutation(n).astype(np.int64)
+    cost = clean.copy()
+    if where == "skipped":
+        cost[[100, 4_096 + 64, n - 1]] = np.nan
+        cost[[64, n - 2]] = -np.inf                       # (and the cheapest ones beside them)
+    else:
+        keep = rng.choice(n, k - 1 if where == "all but k - 1" else 0, replace=False)
+        cost[:] = np.nan
+        cost[keep] = clean[keep]
+    def head(c):
+        ok = np.flatnonzero(c == c)
+        want = ok[np.lexsort((ok, index[ok], c[ok]))[:k]]
+        return np.concatenate([want, np.full(k - len(want), -1)]).tolist()
+    di, dc, good = (torch.from_numpy(a).cuda() for a in (index, cost, clean))
+    bad_head, good_head = head(cost), head(clean)
+    out, flag = torch.full((k,), -5, dtype=torch.int64, device="cuda"), torch.full((1,), 9, dtype=torch.int32, device="cuda")
+    for data, want, nan in ((dc, bad_head, True), (good, good_head, False), (dc, bad_head, True), (good, good_head, False)):
+        if nan:
+            with pytest.raises(B.P2Error) as e:
+                B.p2_topk_device(data.data_ptr(), 1, di.data_ptr(), n, k, out.data_ptr())
+            assert e.value.code == B.P2_EINVAL
+        else:
+            B.p2_topk_device(data.data_ptr(), 1, di.data_ptr(), n, k, out.data_ptr())
+            assert out.cpu().tolist() == want
+        out.fill_(-5)
+        B.p2_topk_device_noalloc(data.data_ptr(), 1, di.data_ptr(), n, k, out.data_ptr(), flag.data_ptr())
+        torch.cuda.synchronize()
+        assert out.cpu().tolist() == want and int(flag.item()) == int(nan)
+        out.fill_(-5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,topk", [([2, 2, 2, 2], 3, 1), ([2, 2, 2, 2], 3, 64), ([2, 2, 2, 2], 4, 1), ([2, 2, 2, 2], 4, 256),
+                                               ([2, 2, 2, 2], 6, 10), ([2, 2, 2, 2], 6, 1024)])
+def test_shortlists_of_equal_costs(B, card, max_len, topk):
+    """Every program costs nothing: more ties than the buffers of the three block widths hold (138, 1 646 and 83 920
+    programs), in one tile and in several; the candidate indices decide."""
+    n = int(np.prod(card))
+    q = dict(card=card, axes=[n], placement=[card], reduce_axes=[0], max_len=max_len, bw=[25e9] * len(card), alpha=[0.0] * len(card))
+    full, short = B.p2_synthesize_batch([q], [0.0, 0.0])[0], B.p2_synthesize_batch([dict(q, topk=topk)], [0.0, 0.0])[0]
+    assert len(full["programs"]) == {3: 138, 4: 1646, 6: 83920}[max_len] and not full["cost"].any()
+    for m in range(2):
+        assert np.array_equal(short["programs"][m * topk:(m + 1) * topk], full["programs"][:topk])
