@@ -434,11 +434,11 @@ hipError_t launch_copy_out3(void* dst0, const void* src0, size_t bytes0, void* d
 // Top-k of (cost[i * stride], index[i]) over i < n: positions into out_pos[min(k, n)].
 // scratch: device buffer of topk_scratch_bytes(n, k) bytes; control: topk_control_bytes() of device memory that are
 // zero before the first call and that every call leaves zero again.  nan_out (device or pinned host memory, may be
-// null): set to 1 if a cost is NaN, else left alone.
+// null): set to 1 if a cost is NaN, else left alone (fresh, where one block does it all: set to 0).
 size_t topk_scratch_bytes(long long n, int k);
 size_t topk_control_bytes();
 hipError_t launch_topk(const double* cost, long long stride, const unsigned long long* index, long long n, int k,
-                       long long* out_pos, void* scratch, void* control, uint32_t* nan_out, hipStream_t stream);
+                       long long* out_pos, void* scratch, void* control, uint32_t* nan_out, hipStream_t stream, int fresh = 0);
 
 // The same selection with its scratch in a fixed array of the device image (no allocation): k at most
 // topk_fixed_max_k(); nan_flag (device, may be null) is set to 1 if a cost is NaN, else to 0.

@@ -125,9 +125,12 @@ __device__ inline void wave_merge(uint32_t& v, uint32_t lane) {
     v = ((lane & (uint32_t)J) == 0u) == ((lane & (uint32_t)K) == 0u) ? (o < v ? o : v) : (o > v ? o : v);
     if constexpr (J > 1) wave_merge<K, J / 2>(v, lane);
 }
+__device__ inline void row_sort(uint32_t& v, uint32_t lane) {     // (of every 16; the first 16 ascending)
+    wave_merge<2, 1>(v, lane); wave_merge<4, 2>(v, lane); wave_merge<8, 4>(v, lane); wave_merge<16, 8>(v, lane);
+}
 __device__ inline void wave_sort(uint32_t& v, uint32_t lane) {
-    wave_merge<2, 1>(v, lane); wave_merge<4, 2>(v, lane); wave_merge<8, 4>(v, lane);
-    wave_merge<16, 8>(v, lane); wave_merge<32, 16>(v, lane); wave_merge<64, 32>(v, lane);
+    row_sort(v, lane);
+    wave_merge<32, 16>(v, lane); wave_merge<64, 32>(v, lane);
 }
 
 // Bitonic sort of the buffer (E entries per thread, entry r * NT + thread), keys and buffer places in registers: an
@@ -510,7 +513,7 @@ inline bool sel_sampled(long long n, int K) { return n >= (1ll << 22) || (n >= (
 
 // Measured (a whole p2_topk_device call, host wait included; before: one wavefront per block inserting into a sorted list
 // of K, then one wavefront walking all the lists): 10 007 entries, K = 10: 89 -> 25 us, of which the kernel is 15, a chain
-// of some ten memory and barrier latencies; 1.3 M of stride 3, K = 64: 1190 -> 56 us, half of it the last block's walk;
+// of some ten memory and barrier latencies (few entries to keep: below); 1.3 M of stride 3, K = 64: 1190 -> 56 us, half of it the last block's walk;
 // 50 M, K = 100: 3170 -> 160 us, of which 100 read 400 MB at 4 TB/s (a large copy reaches 4.9) and 40 find the bound.
 // K smallest of a column by all blocks together: every block leaves what it kept, the last one to finish goes through
 // that and writes the positions (or, over a sample, the bound).  The lists hold `cap` entries, all that the blocks of one
@@ -572,7 +575,7 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long
     }
 }
 
-// Many selections in one launch: block b does job b from start to end.  A launch of lists of at most 512 entries (a tile,
+// Many selections in one launch: block b does job b from start to end (k_few_jobs where few() says so).  A launch of lists of at most 512 entries (a tile,
 // K <= 64) takes a wavefront each: nothing there is worth a barrier between wavefronts.  A tile of lists of at most 2048
 // entries (K <= 256) is 256 threads wide, so that several jobs share a compute unit; longer lists take 1024.
 template <int NT, int B>
@@ -586,6 +589,254 @@ __global__ __launch_bounds__(NT) void k_topk_jobs(const DevTopkJob* __restrict__
     const long long n_out = J.k < J.n ? J.k : J.n;
     for (long long j = threadIdx.x; j < n_out; j += NT) J.out_pos[j] = j < (long long)st.cnt ? (long long)S.pos[j] : -1ll;
 }
+
+// ---- the same selection for a few entries -------------------------------------------------------------------
+// A shortlist of at most kFewMax entries fits in a wavefront's lanes, and then nothing depends on how the costs are spread
+// or ordered: a wavefront goes through tiles of 512 entries (the next one in flight) and, where a tile has an entry that
+// does not lie above the K-th so far, picks the K smallest of the tile and its list in K rounds of a minimum over the
+// lanes; indices are read for such tiles only.  The block's wavefronts share the lowest K-th through LDS and merge their
+// lists at the end.
+// Where the line to the buffers above lies (whole p2_topk_device calls, us, buffers / this form): they take longer where a
+// column is sorted or full of ties, 10 000 equal costs: K = 1 80 / 22, 4 81 / 30, 10 81 / 30, 1 M: 91 / 33, 103 / 43,
+// 104 / 85 (a sorted list with insertion, which ties in ascending order suit, took 25, 29, 36 and 34, 61, 120).  On random
+// costs both take the same up to 10 kept entries, 10 000: 24 / 20, 24 / 22, 24 / 23, while 16 took 24 / 37, and from 4 on
+// this form is the slower one for long columns, 1 M, 10 kept: 34 / 39.  So: up to 4, and up to 10 of 2^18.
+constexpr int kFewMax = 16, kFewUnroll = 8, kFewWaves = 16;
+constexpr long long kFewTile = (long long)kWave * kFewUnroll;
+
+struct FewList { unsigned long long key, idx, pos; };    // lane i: the i-th smallest (key ~0: none)
+struct FewShared {
+    unsigned long long key[kFewWaves * kFewMax], idx[kFewWaves * kFewMax], pos[kFewWaves * kFewMax];
+    unsigned long long bound;                            // a key that K of the block's entries do not exceed
+    uint32_t least[kFewWaves];
+    uint32_t flag;
+};
+
+__device__ inline unsigned long long of_lane(unsigned long long v, int lane) {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane) |
+           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32;
+}
+
+__device__ inline bool before(const FewList& a, const FewList& b) {
+    return a.key != b.key ? a.key < b.key : a.idx != b.idx ? a.idx < b.idx : a.pos < b.pos;
+}
+// Bitonic sort of a wavefront's entries.
+template <int K, int J>
+__device__ inline void few_merge_lanes(FewList& v, uint32_t lane) {
+    const FewList o{lane_xor<J>(v.key), lane_xor<J>(v.idx), lane_xor<J>(v.pos)};
+    if (before(o, v) == (((lane & (uint32_t)J) == 0u) == ((lane & (uint32_t)K) == 0u))) v = o;
+    if constexpr (J > 1) few_merge_lanes<K, J / 2>(v, lane);
+}
+__device__ inline uint32_t lane_below(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false); }      // row_shr:1
+__device__ inline unsigned long long lane_below(unsigned long long v) {
+    return (unsigned long long)lane_below((uint32_t)v) | (unsigned long long)lane_below((uint32_t)(v >> 32)) << 32;
+}
+
+template <int J>
+__device__ inline void few_least(FewList& v) {
+    const FewList o{lane_xor<J>(v.key), lane_xor<J>(v.idx), lane_xor<J>(v.pos)};
+    if (before(o, v)) v = o;
+    if constexpr (J > 1) few_least<J / 2>(v);
+}
+
+// The K smallest of the list L and E entries per lane (bit i of `left`: there is one).  Where some lanes have one they go
+// in one by one; otherwise the lanes' smallest, the list's among them, are sorted, and what a lane has besides goes in
+// where it lies before the K-th.
+template <int E>
+__device__ inline FewList few_pick(const FewList& L, const unsigned long long (&key)[E], const unsigned long long (&idx)[E],
+                                   const unsigned long long (&pos)[E], uint32_t left, int K) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const FewList none{~0ull, ~0ull, ~0ull};
+    uint32_t mine = 0u;
+    auto smallest = [&]() {
+        FewList b = none;
+        mine = 0u;
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const FewList e{key[i], idx[i], pos[i]};
+            if (((left >> i) & 1u) && before(e, b)) { b = e; mine = 1u << i; }
+        }
+        return b;
+    };
+    FewList out = L;
+    if (K == 1 || __popcll(__ballot(left != 0u)) > 6) {
+        FewList b = smallest();
+        if (before(L, b)) b = L; else { left &= ~mine; }
+        const bool held = K > 1 && lane < (uint32_t)K && L.key != ~0ull && b.pos != L.pos;       // (a list entry that its lane's own goes before)
+        out = b;
+        if (K == 1) {
+            few_least<32>(out);
+            if (lane != 0u) out = none;
+            return out;
+        }
+        few_merge_lanes<2, 1>(out, lane); few_merge_lanes<4, 2>(out, lane); few_merge_lanes<8, 4>(out, lane);
+        few_merge_lanes<16, 8>(out, lane); few_merge_lanes<32, 16>(out, lane); few_merge_lanes<64, 32>(out, lane);
+        if (lane >= (uint32_t)K) out = none;
+        left |= held ? 1u << E : 0u;
+    }
+#pragma unroll 1
+    for (;;) {
+        const FewList last{of_lane(out.key, K - 1), of_lane(out.idx, K - 1), of_lane(out.pos, K - 1)};
+        FewList b = smallest();
+        if (((left >> E) & 1u) && before(L, b)) { b = L; mine = 1u << E; }
+        const unsigned long long m = __ballot(before(b, last));
+        if (m == 0ull) return out;
+        const int w = __ffsll((long long)m) - 1;
+        const FewList it{of_lane(b.key, w), of_lane(b.idx, w), of_lane(b.pos, w)};
+        if ((int)lane == w) left &= ~mine;
+        const uint32_t at = (uint32_t)__popcll(__ballot(lane < (uint32_t)K && before(out, it)));
+        const FewList up{lane_below(out.key), lane_below(out.idx), lane_below(out.pos)};
+        if (lane == at) out = it;
+        else if (lane > at && lane < (uint32_t)K) out = up;
+    }
+}
+
+// Tiles first, first + step, ... go into the wavefront's list (all wavefronts of the block together); true: a NaN was
+// among this lane's entries.
+__device__ inline bool few_scan(FewShared& S, FewList& L, const SelSource& src, long long n, long long first, long long step, int K) {
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = blockDim.x >> 6;
+    const long long tiles = (n + kFewTile - 1) / kFewTile;
+    double next[kFewUnroll];
+    bool nan = false;
+    auto entry = [&](long long t, int u) { const long long e = t * kFewTile + (long long)u * 64 + (long long)lane; return e < n ? e : 0ll; };
+    auto there = [&](long long t, int u) { return t * kFewTile + (long long)u * 64 + (long long)lane < n; };
+    auto load = [&](long long t) {
+#pragma unroll
+        for (int u = 0; u < kFewUnroll; ++u) next[u] = src.cost[entry(t, u) * src.stride];
+    };
+    if (first < tiles) load(first);
+    bool begun = waves == 1u;
+#pragma unroll 1
+    for (long long t = first; t < tiles || !begun; t += step) {
+        unsigned long long key[kFewUnroll], idx[kFewUnroll], pos[kFewUnroll];
+        unsigned long long least = ~0ull;
+#pragma unroll
+        for (int u = 0; u < kFewUnroll; ++u) {
+            const double c = next[u];
+            const bool ok = there(t, u);
+            nan |= ok && c != c;
+            key[u] = ok && c == c ? cost_key(c) : ~0ull;
+            least = key[u] < least ? key[u] : least;
+        }
+        if (t + step < tiles) load(t + step);
+        if (!begun) {                                    // a first bound for the block, as above: so that few go into the lists
+            begun = true;
+            const uint32_t r = ((uint32_t)K + waves - 1u) / waves;
+            uint32_t v = (uint32_t)(least >> 32);
+            wave_sort(v, lane);
+            if (lane == r - 1u) S.least[wave] = v;
+            __syncthreads();
+            uint32_t T = lane < waves ? S.least[lane] : ~0u;
+            row_sort(T, lane);
+            T = (uint32_t)__builtin_amdgcn_readlane((int)T, (int)(((uint32_t)K + r - 1u) / r) - 1);
+            if (threadIdx.x == 0 && T != ~0u) __hip_atomic_fetch_min(&S.bound, (unsigned long long)T << 32 | 0xffffffffull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __syncthreads();
+        }
+        const unsigned long long kth = of_lane(L.key, K - 1), shared = __hip_atomic_load(&S.bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const unsigned long long bound = kth < shared ? kth : shared;
+        uint32_t left = 0u;
+#pragma unroll
+        for (int u = 0; u < kFewUnroll; ++u) left |= key[u] <= bound && key[u] != ~0ull ? 1u << u : 0u;
+        if (__ballot(left != 0u) == 0ull) continue;
+#pragma unroll
+        for (int u = 0; u < kFewUnroll; ++u) {
+            const unsigned long long e = (unsigned long long)entry(t, u);
+            idx[u] = src.idx[e]; pos[u] = src.position(e);
+        }
+        L = few_pick(L, key, idx, pos, left, K);
+        const unsigned long long now = of_lane(L.key, K - 1);
+        if (lane == 0u && now != ~0ull) __hip_atomic_fetch_min(&S.bound, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    return nan;
+}
+
+// The lists of the block's wavefronts into the first one's.
+__device__ inline void few_merge(FewShared& S, FewList& L, int K) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, n = (blockDim.x >> 6) * (uint32_t)K;
+    if (blockDim.x == (uint32_t)kWave) return;
+    if (lane < (uint32_t)K) { S.key[wave * K + lane] = L.key; S.idx[wave * K + lane] = L.idx; S.pos[wave * K + lane] = L.pos; }
+    __syncthreads();
+    if (wave == 0u) {
+        constexpr int kE = kFewWaves * kFewMax / kWave;
+        unsigned long long key[kE], idx[kE], pos[kE];
+#pragma unroll
+        for (int i = 0; i < kE; ++i) {
+            const uint32_t j = (uint32_t)i * 64u + lane;
+            key[i] = j < n ? S.key[j] : ~0ull; idx[i] = j < n ? S.idx[j] : ~0ull; pos[i] = j < n ? S.pos[j] : ~0ull;
+        }
+        uint32_t left = 0u;
+#pragma unroll
+        for (int i = 0; i < kE; ++i) left |= key[i] != ~0ull ? 1u << i : 0u;
+        L = few_pick(FewList{~0ull, ~0ull, ~0ull}, key, idx, pos, left, K);
+    }
+    __syncthreads();
+}
+
+// One column by all blocks: every block leaves its K in a slot of the lists, the last one to finish merges them.  `fresh`
+// (one block): the NaN word is written either way.
+__global__ __launch_bounds__(kWave * kFewWaves) void k_few_column(SelSource src, long long n, int K, SelControl* __restrict__ ctl, double* lc,
+                                                                  unsigned long long* li, unsigned long long* lp, long long* __restrict__ out_pos,
+                                                                  long long n_out, uint32_t* __restrict__ nan_out, int fresh) {
+    __shared__ FewShared S;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, waves = blockDim.x >> 6;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const unsigned long long n_column = (unsigned long long)n;
+    FewList L{~0ull, ~0ull, ~0ull};
+    if (tid == 0) S.bound = ~0ull;
+    __syncthreads();
+    const bool nan = few_scan(S, L, src, n, (long long)blockIdx.x * waves + wave, (long long)gridDim.x * waves, K);
+    few_merge(S, L, K);
+    if (gridDim.x > 1u) {
+        if (nan) __hip_atomic_fetch_or(&ctl->nan, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid < (uint32_t)K) {
+            const size_t o = (size_t)blockIdx.x * (size_t)K + tid;
+            lc[o] = L.key != ~0ull ? key_cost(L.key) : __longlong_as_double(0x7ff8000000000000ll); li[o] = L.idx; lp[o] = L.pos;
+        }
+        __syncthreads();                                 // (the block's stores have been made; thread 0 hands them over)
+        if (tid == 0) {
+            __threadfence();
+            S.flag = __hip_atomic_fetch_add(&ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence();
+            S.bound = ~0ull;
+        }
+        __syncthreads();
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag) != gridDim.x - 1u) return;
+        L = FewList{~0ull, ~0ull, ~0ull};
+        (void)few_scan(S, L, SelSource{lc, li, lp, 1, 1}, (long long)gridDim.x * K, wave, waves, K);      // (a slot that is empty holds a NaN)
+        few_merge(S, L, K);
+    }
+    if (wave == 0u && (long long)lane < n_out) out_pos[lane] = L.key != ~0ull && L.pos < n_column ? (long long)L.pos : -1ll;
+    const bool any = __syncthreads_or(nan ? 1 : 0) != 0;
+    if (tid != 0) return;
+    const uint32_t other = gridDim.x > 1u ? __hip_atomic_load(&ctl->nan, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (nan_out && (other || any || fresh)) *nan_out = other || any ? 1u : 0u;
+    if (gridDim.x > 1u) { ctl->nan = 0u; ctl->done = 0u; }
+}
+
+__global__ __launch_bounds__(kWave * kFewWaves) void k_few_jobs(const DevTopkJob* __restrict__ jobs) {
+    __shared__ FewShared S;
+    const DevTopkJob J = jobs[blockIdx.x];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    FewList L{~0ull, ~0ull, ~0ull};
+    if (tid == 0) S.bound = ~0ull;
+    __syncthreads();
+    if (few_scan(S, L, SelSource{J.cost, J.index, nullptr, J.stride, 1}, J.n, wave, blockDim.x >> 6, J.k)) atomicOr(J.nan_flag, 1u);
+    few_merge(S, L, J.k);
+    if (wave == 0u && (long long)lane < (J.k < J.n ? (long long)J.k : J.n)) J.out_pos[lane] = L.key != ~0ull ? (long long)L.pos : -1ll;
+}
+// Wavefronts of a block for so many entries, and blocks (one up to four tiles a wavefront: the hand-over takes as long as
+// several; at most one per compute unit).
+inline unsigned few_threads(long long n) {
+    const long long tiles = (n + kFewTile - 1) / kFewTile;
+    return (unsigned)(tiles < kFewWaves ? tiles : (long long)kFewWaves) * (unsigned)kWave;
+}
+inline unsigned few_blocks(long long n) {
+    const long long b = (n + kFewTile * kFewWaves - 1) / (kFewTile * kFewWaves);
+    return (unsigned)(b <= 4 ? 1 : b < 256 ? b : 256);
+}
+// (see above)
+inline bool few(long long n, int K) { return K <= 4 || (K <= 10 && n <= (1ll << 18)); }
 
 // Device memory -> pinned host memory, written by the GPU itself in 16-byte words.
 __global__ __launch_bounds__(256) void k_copy_out(uint4* __restrict__ dst, const uint4* __restrict__ src, size_t n16) {
@@ -637,7 +888,8 @@ hipError_t launch_rank_sort(const unsigned long long* valid, const unsigned long
 
 hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, long long max_n, hipStream_t stream) {
     if (n_jobs == 0) return hipSuccess;
-    if (max_k <= 64 && max_n <= 512) hipLaunchKernelGGL((k_topk_jobs<kWave, 128>), dim3(n_jobs), dim3(kWave), 0, stream, jobs);
+    if (few(max_n, max_k)) hipLaunchKernelGGL(k_few_jobs, dim3(n_jobs), dim3(few_threads(max_n)), 0, stream, jobs);
+    else if (max_k <= 64 && max_n <= 512) hipLaunchKernelGGL((k_topk_jobs<kWave, 128>), dim3(n_jobs), dim3(kWave), 0, stream, jobs);
     else if (max_k <= 256 && max_n <= 2048) hipLaunchKernelGGL((k_topk_jobs<256, 512>), dim3(n_jobs), dim3(256), 0, stream, jobs);
     else hipLaunchKernelGGL((k_topk_jobs<kSelThreads, kSelBuffer>), dim3(n_jobs), dim3(kSelThreads), 0, stream, jobs);
     return hipGetLastError();
@@ -667,13 +919,18 @@ size_t topk_control_bytes() { return sizeof(SelControl); }
 size_t topk_scratch_bytes(long long n, int k) { return (size_t)sel_blocks(n) * (size_t)sel_share(k) * 24; }
 
 hipError_t launch_topk(const double* cost, long long stride, const unsigned long long* index, long long n, int k,
-                       long long* out_pos, void* scratch, void* control, uint32_t* nan_out, hipStream_t stream) {
+                       long long* out_pos, void* scratch, void* control, uint32_t* nan_out, hipStream_t stream, int fresh) {
     if (n <= 0 || k <= 0) return hipSuccess;
     const unsigned blocks = sel_blocks(n);
     const size_t cap = (size_t)blocks * sel_share(k);
     double* lc = static_cast<double*>(scratch);
     unsigned long long* li = static_cast<unsigned long long*>(scratch) + cap;
     SelControl* ctl = static_cast<SelControl*>(control);
+    if (few(n, k)) {
+        hipLaunchKernelGGL(k_few_column, dim3(few_blocks(n)), dim3(few_threads(n)), 0, stream, SelSource{cost, index, nullptr, stride, 1}, n, k, ctl, lc, li,
+                           li + cap, out_pos, (long long)(k < n ? k : n), nan_out, fresh);
+        return hipGetLastError();
+    }
     const bool sampled = sel_sampled(n, k);
     if (sampled) {
         const long long m = n / (kSelSample * 64) * 64;
@@ -742,6 +999,7 @@ hipError_t launch_topk_fixed(const double* cost, long long stride, const unsigne
     // (the shared words are cleared here although a call leaves them clear: calls that overlapped against the rule must
     //  not spoil the ones after them.  A fill kernel, so that the call can be recorded into a graph)
     SelControl* ctl = reinterpret_cast<SelControl*>(static_cast<unsigned char*>(base) + kFixedTopkListBytes);
+    if (few(n, k) && few_blocks(n) == 1u) return launch_topk(cost, stride, index, n, k, out_pos, base, ctl, nan_flag, stream, 1);
     hipLaunchKernelGGL(k_clear_control, dim3(1), dim3(kFixedTopkMaxK), 0, stream, ctl, nan_flag, out_pos, (int)(k < n ? k : n));
     e = hipGetLastError();
     if (e != hipSuccess) return e;

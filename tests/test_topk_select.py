@@ -112,7 +112,8 @@ def test_shortlists_of_short_lists(B, topk, engine):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,k,where", [(4_194_304, 33, "skipped"), (4_200_001, 64, "all but k - 1"), (300_001, 64, "all but k - 1"), (20_000, 7, "all but k - 1"),
-                                       (5_000, 64, "everywhere"), (4_194_304, 10, "everywhere")])
+                                       (5_000, 64, "everywhere"), (4_194_304, 10, "everywhere"), (3_000, 4, "all but k - 1"), (500_000, 3, "all but k - 1"),
+                                       (200_000, 10, "skipped"), (40_000, 1, "everywhere")])
 def test_nan_costs(B, n, k, where):
     """Columns with a bound from a sample (of every 4 096 entries the first 64), without, and of one block: a NaN is flagged
     wherever it stands and never selected, and the words that the blocks share are left clean."""
@@ -161,3 +162,34 @@ def test_shortlists_of_equal_costs(B, card, max_len, topk):
     assert len(full["programs"]) == {3: 138, 4: 1646, 6: 83920}[max_len] and not full["cost"].any()
     for m in range(2):
         assert np.array_equal(short["programs"][m * topk:(m + 1) * topk], full["programs"][:topk])
+
+
+def _few_costs(kind, n, rng):
+    if kind == "one lane":               # the smallest ones 64 apart: a lane has all of them
+        c = 10.0 + rng.random(n)
+        at = np.arange(5, n, 64)
+        c[at] = rng.permutation(len(at)) / len(at)
+        return c
+    return {"rising": np.arange(n, dtype=np.float64), "ties": np.floor(4.0 * rng.random(n)), "equal": np.zeros(n)}.get(kind, rng.normal(size=n))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["random", "rising", "ties", "equal", "one lane"])
+@pytest.mark.parametrize("n,k", [(1, 4), (64, 1), (511, 10), (512, 1), (513, 2), (1024, 10), (8193, 4), (32_768, 10), (32_769, 1), (32_769, 10), (40_000, 3),
+                                 (262_144, 10), (262_145, 10), (2_100_001, 1), (2_100_001, 4)])
+def test_shortlists_of_few_entries(B, n, k, kind):
+    """Up to ten entries kept in the lanes of a wavefront: a wavefront, a block and several blocks; columns whose order or
+    ties leave nearly every entry below the bounds, with indices that rise, fall and are mixed."""
+    import torch
+    rng = np.random.default_rng(n + k)
+    cost = _few_costs(kind, n, rng)
+    dc, out = torch.from_numpy(cost).cuda(), torch.full((min(k, n),), -5, dtype=torch.int64, device="cuda")
+    for index in (np.arange(n), np.arange(n, 0, -1), rng.permutation(n) // 2):
+        index = index.astype(np.int64)
+        want = np.lexsort((np.arange(n), index, cost))[:k].tolist()
+        di = torch.from_numpy(index).cuda()
+        for call in (B.p2_topk_device, B.p2_topk_device_noalloc, B.p2_topk_device):
+            call(dc.data_ptr(), 1, di.data_ptr(), n, k, out.data_ptr())
+            torch.cuda.synchronize()
+            assert out.cpu().tolist() == want
+            out.fill_(-5)
