@@ -81,3 +81,43 @@ def test_calls_that_overlap_stay_inside_their_buffers(B, oracle):
     B.p2_topk_device_noalloc(dc.data_ptr(), 1, di.data_ptr(), 4_099, 10, out.data_ptr())
     torch.cuda.synchronize()
     assert out.cpu().tolist() == oracle.topk(cost, index, 10).tolist()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k", [(3_000, 4), (300_007, 3), (20_011, 64), (4_300_003, 64)])
+def test_recorded_into_a_graph(B, oracle, n, k):
+    """One block and several, a few entries and more, with a bound from a sample: every replay, on other inputs and with eager
+    calls in between, gives what the eager call gives."""
+    import torch
+    rng = np.random.default_rng(n)
+
+    def inputs():
+        return torch.from_numpy(rng.integers(0, 997, n) / 8.0).cuda(), torch.from_numpy(rng.integers(0, 1 << 40, n)).cuda()
+
+    dc, di = inputs()
+    out, nan = torch.full((k,), -7, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    eager = torch.full((k,), -7, dtype=torch.int64, device="cuda")
+
+    def call(into, flag):
+        B.p2_topk_device_noalloc(dc.data_ptr(), 1, di.data_ptr(), n, k, into.data_ptr(), flag, stream=torch.cuda.current_stream().cuda_stream)
+
+    call(eager, None)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out, nan.data_ptr())
+    for replay in range(4):
+        c, i = inputs()
+        dc.copy_(c)
+        di.copy_(i)
+        if replay == 2:
+            dc[n // 2] = float("nan")
+        out.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(nan.item()) == int(replay == 2)
+        call(eager, None)
+        torch.cuda.synchronize()
+        cost = dc.cpu().numpy()
+        cost[cost != cost] = np.inf
+        assert out.cpu().tolist() == eager.cpu().tolist() == oracle.topk(cost, di.cpu().numpy().view(np.uint64), k).tolist()
