@@ -234,20 +234,21 @@ def _first_rows(topks, n_msg, otherwise):
 
 
 def _take_room(rows, n_msg):
-    """Buffers for so many rows: the thread's, where they are large enough (a fresh mapping of the first call's room costs
-    more than evaluating a small query).  They are the caller's until it hands them to _keep_room."""
-    progs, cost = _own.__dict__.pop("room", (None, None)) if rows <= _FIRST_ROWS else (None, None)
+    """Buffers for so many rows, and pointers to them: the thread's, where they are large enough (a fresh mapping of the
+    first call's room costs more than evaluating a small query, and making a pointer 4 us).  They are the caller's until
+    it hands them to _keep_room."""
+    progs, cost, *at = _own.__dict__.pop("room", (None, None)) if rows <= _FIRST_ROWS else (None, None)
     if progs is None or len(progs) < rows:
-        progs = np.zeros(rows, dtype=PROGRAM_DTYPE)
+        progs, at = np.zeros(rows, dtype=PROGRAM_DTYPE), None
     if cost is None or len(cost) < rows * n_msg:
-        cost = np.zeros(rows * n_msg, dtype=np.float64)
-    return progs, cost
+        cost, at = np.zeros(rows * n_msg, dtype=np.float64), None
+    return (progs, cost, *(at or (progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double))))
 
 
-def _keep_room(progs, cost, filled):
+def _keep_room(room, filled):
     """The buffers for the thread's next call (until p2_release_thread), unless they are large."""
-    if len(progs) <= _FIRST_ROWS and len(cost) <= _FIRST_ROWS * _MAX_MSG and filled <= _KEEP_BYTES:
-        _own.room = progs, cost
+    if len(room[0]) <= _FIRST_ROWS and len(room[1]) <= _FIRST_ROWS * _MAX_MSG and filled <= _KEEP_BYTES:
+        _own.room = room
 
 
 class Batch:
@@ -342,11 +343,11 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
                                    C.byref(count), C.byref(cands), C.byref(st))
     rows = cap if cap is not None else _first_rows([topk], n_msg, _FIRST_ROWS)
     while True:
-        progs, cost = _take_room(max(rows, 1), max(n_msg, 1))
-        rc = call(progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double), rows)
+        room = _take_room(max(rows, 1), max(n_msg, 1))
+        rc = call(room[2], room[3], rows)
         n = count.value if rc == P2_OK else 0
-        out = progs[:n].copy(), cost[:n * n_msg].reshape(n, n_msg).copy()
-        _keep_room(progs, cost, n * (PROGRAM_DTYPE.itemsize + 8 * n_msg))
+        out = room[0][:n].copy(), room[1][:n * n_msg].reshape(n, n_msg).copy()
+        _keep_room(room, n * (PROGRAM_DTYPE.itemsize + 8 * n_msg))
         if rc != P2_ENOSPC or cap is not None:
             break
         rows = count.value

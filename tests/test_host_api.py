@@ -164,14 +164,17 @@ def test_a_kept_result_keeps_no_more_than_a_megabyte_beside_it(B):
 def test_room_for_rows_is_kept_per_thread_and_bounded(B):
     B._own.__dict__.clear()
     first = B._take_room(1 << 17, 2)
-    B._keep_room(*first, 100)
+    B._keep_room(first, 100)
     narrow = B._take_room(1 << 17, 1)                   # (another number of message sizes: the same buffers)
-    assert narrow[0] is first[0] and narrow[1] is first[1]
+    assert all(a is b for a, b in zip(narrow, first))
     assert "room" not in B._own.__dict__                # (nobody else gets them while a call writes to them)
     assert B._take_room(10, 1)[0] is not first[0]
-    B._keep_room(*narrow, 1 << 25)                      # a long list: given back
+    B._keep_room(narrow, 1 << 25)                       # a long list: given back
     assert "room" not in B._own.__dict__
-    B._keep_room(*narrow, 100)
+    B._keep_room(narrow, 100)
     large = B._take_room((1 << 17) + 1, 1)              # what a second call needs is not kept, the first call's room is
-    B._keep_room(*large, 100)
-    assert B._take_room(5, 2)[0] is first[0]
+    B._keep_room(large, 100)
+    wide = B._take_room(5, 1 << 17)                     # (more message sizes than there is room for: another buffer of costs)
+    assert wide[0] is first[0] and wide[1] is not first[1] and len(wide[1]) == 5 << 17
+    for progs, cost, progs_at, cost_at in (first, wide, large):
+        assert progs_at.value == progs.ctypes.data and ctypes.addressof(cost_at.contents) == cost.ctypes.data
