@@ -316,7 +316,7 @@ struct CallScope {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Selections over at most this many valid programs go into one launch for the whole batch (one block each, at most 32
-// tiles of 8192; the 11 of 83 920 programs take 45 us with 10 kept, 100 with 1024); longer lists are selected from by the
+// tiles of 8192; the 11 of 83 920 programs take 32 us with 10 kept, 100 with 1024); longer lists are selected from by the
 // whole chip, one after the other (371 970 programs: 50 and 135 us).
 constexpr size_t kTopkJobMax = 1 << 18;
 

@@ -203,8 +203,9 @@ struct SelBitonic {
     }
 };
 
-// The buffer in ascending order, cut to K.
-template <int NT, int B>
+// The buffer in ascending order, cut to K.  Ties: one cost alone may be all there is (where lists are sorted a block each that
+// test costs the others 15 %, 2 549 to 83 920 programs, K = 1024: 31 -> 36 and 101 -> 118 us, in registers that spill).
+template <bool Ties, int NT, int B>
 __device__ inline void sel_sort(SelShared<NT, B>& S, SelState& st, const SelSource& src, uint32_t K) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     lds_barrier();
@@ -275,8 +276,8 @@ __device__ inline void sel_sort(SelShared<NT, B>& S, SelState& st, const SelSour
         //  10 000 equal costs, K = 16: 81 -> 64 us in a p2_topk_device call)
         const unsigned long long one = S.key[0];
         bool differ = false;
-        for (uint32_t j = tid; j < cnt; j += NT) { S.idx[j] = src.idx[S.pos[j]]; differ |= S.key[j] != one; }
-        const bool same = __syncthreads_or(differ ? 1 : 0) == 0;
+        for (uint32_t j = tid; j < cnt; j += NT) { S.idx[j] = src.idx[S.pos[j]]; differ |= Ties && S.key[j] != one; }
+        const bool same = Ties && __syncthreads_or(differ ? 1 : 0) == 0;
         if (same) for (uint32_t j = tid; j < cnt; j += NT) S.key[j] = S.idx[j];
         if (cnt <= (uint32_t)NT) SelBitonic<NT, B, 1>{S, src, cnt, tid, {}, {}}.run();
         else SelBitonic<NT, B, B / NT>{S, src, cnt, tid, {}, {}}.run();
@@ -372,7 +373,7 @@ __device__ inline bool sel_cut(SelShared<NT, B>& S, SelState& st, uint32_t K, Ke
 }
 
 // Tiles first, first + step, ... of the source's n entries go through the buffer; true: a NaN was among this lane's.
-template <int NT, int B>
+template <bool Ties, int NT, int B>
 __device__ inline bool sel_consume(SelShared<NT, B>& S, SelState& st, const SelSource& src, long long n, long long first, long long step,
                                    uint32_t K, bool bounded) {
     constexpr long long kTile = (long long)NT * kSelUnroll;
@@ -481,7 +482,7 @@ __device__ inline bool sel_consume(SelShared<NT, B>& S, SelState& st, const SelS
                     lds_barrier();
                     more = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.flag);
                     if (st.cnt + more <= (uint32_t)B) break;
-                    sel_sort(S, st, src, K);                // (leaves room for NT: this happens once)
+                    sel_sort<Ties>(S, st, src, K);                // (leaves room for NT: this happens once)
                 }
                 if (ok) {
                     const uint32_t o = st.cnt + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
@@ -542,8 +543,8 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_column(SelSource src, long
     long long first = blockIdx.x, step = gridDim.x;
     bool last = gridDim.x == 1u, nan = false;
     for (;;) {
-        nan |= sel_consume(S, st, src, n, first, step, (uint32_t)K, bounded != 0);
-        if (last || st.cnt > sel_share(K)) sel_sort(S, st, src, (uint32_t)K);
+        nan |= sel_consume<true>(S, st, src, n, first, step, (uint32_t)K, bounded != 0);
+        if (last || st.cnt > sel_share(K)) sel_sort<true>(S, st, src, (uint32_t)K);
         if (last) break;
         if (nan) __hip_atomic_fetch_or(&ctl->nan, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -594,8 +595,8 @@ __global__ __launch_bounds__(NT) void k_topk_jobs(const DevTopkJob* __restrict__
     const DevTopkJob J = jobs[blockIdx.x];
     SelState st{0u, __longlong_as_double(0x7ff0000000000000ll), ~0ull};
     const SelSource src{J.cost, J.index, nullptr, J.stride, 1};
-    if (sel_consume(S, st, src, J.n, 0, 1, (uint32_t)J.k, false)) atomicOr(J.nan_flag, 1u);
-    sel_sort(S, st, src, (uint32_t)J.k);
+    if (sel_consume<false>(S, st, src, J.n, 0, 1, (uint32_t)J.k, false)) atomicOr(J.nan_flag, 1u);
+    sel_sort<false>(S, st, src, (uint32_t)J.k);
     const long long n_out = J.k < J.n ? J.k : J.n;
     for (long long j = threadIdx.x; j < n_out; j += NT) J.out_pos[j] = j < (long long)st.cnt ? (long long)S.pos[j] : -1ll;
 }
@@ -609,8 +610,9 @@ __global__ __launch_bounds__(NT) void k_topk_jobs(const DevTopkJob* __restrict__
 // Where the line to the buffers above lies (whole p2_topk_device calls, us, buffers / this form): they take longer where a
 // column is sorted or full of ties, 10 000 equal costs: K = 1 80 / 22, 4 81 / 30, 10 81 / 30, 1 M: 91 / 33, 103 / 43,
 // 104 / 85 (a sorted list with insertion, which ties in ascending order suit, took 25, 29, 36 and 34, 61, 120).  On random
-// costs both take the same up to 10 kept entries, 10 000: 24 / 20, 24 / 22, 24 / 23, while 16 took 24 / 37, and from 4 on
-// this form is the slower one for long columns, 1 M, 10 kept: 34 / 39.  So: up to 4, and up to 10 of 2^18.
+// costs both take about the same up to 10 kept entries, 3 000: 20 / 17, 20 / 19, 21 / 23, 10 000: 24 / 20, 24 / 22, 24 / 23,
+// while 16 took 24 / 37, and from 5 on this form is the slower one for long columns, 1 M, 10 kept: 34 / 39.  So: up to 4,
+// and up to 10 of 2^18.
 constexpr int kFewMax = 16, kFewUnroll = 8, kFewWaves = 16;
 constexpr long long kFewTile = (long long)kWave * kFewUnroll;
 
