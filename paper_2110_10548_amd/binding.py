@@ -298,13 +298,15 @@ class Batch:
         # piece of a copy: whoever keeps one query's rows keeps no more than that beside them
         offs = self._offs.tolist()
         limit = _PIECE_BYTES // (PROGRAM_DTYPE.itemsize + 8 * self.n_msg)
-        out, first, end, progs, cost = [], 0, -1, None, None
-        for i, row in enumerate(np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist()):
-            a, b = offs[i], offs[i + 1]
-            if b > end:
-                first, end = a, offs[max(i + 1, bisect.bisect_right(offs, a + limit) - 1)]
-                progs, cost = self._progs[first:end].copy(), self._cost[first:end, :self.n_msg].copy()
-            out.append({"programs": progs[a - first:b - first], "cost": cost[a - first:b - first], "stats": dict(zip(_STATS_FIELDS, row))})
+        stats = np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist()
+        out, i = [], 0
+        while i < self.nq:
+            first = offs[i]
+            j = max(i + 1, bisect.bisect_right(offs, first + limit) - 1)       # (queries i .. j - 1 share a copy)
+            progs, cost = self._progs[first:offs[j]].copy(), self._cost[first:offs[j], :self.n_msg].copy()
+            out += [{"programs": progs[a - first:b - first], "cost": cost[a - first:b - first], "stats": dict(zip(_STATS_FIELDS, row))}
+                    for a, b, row in zip(offs[i:j], offs[i + 1:j + 1], stats[i:j])]
+            i = j
         return out
 
     def run(self):
