@@ -68,7 +68,12 @@ int32_t p2_enumerate_placements(const p2_hierarchy* h, const int32_t* axes, int3
                                 int32_t* out, int64_t cap, int64_t* out_count);
 
 /* Evaluation engines.  All give identical results; they differ in the state they keep. */
-#define P2_ENGINE_AUTO 0      /* shared-prefix engine where it applies, else the compact engine; the
+#define P2_ENGINE_AUTO 0      /* where the shared-prefix engine applies and the chunks are a multiple of
+                                 the group's devices, or at most 64, the graph of the distinct states
+                                 that the programs pass through (up to 36 patterns, size limits of 7, 6,
+                                 5, 4 for up to 9, 16, 25, 36): reported as the engine it stands in for,
+                                 shared-prefix up to 2^30 candidates, frontier above.  Else the
+                                 shared-prefix engine where it applies, else the compact engine; the
                                  literal engine for the candidates they cannot hold; the frontier
                                  engine above 2^30 candidates, and in place of the compact engine
                                  where that is slower (more than 64 devices from 100 candidates on,
@@ -181,7 +186,8 @@ typedef struct {
                                   its first bad step): what evaluating every candidate on its own
                                   executes, whichever engine ran                                  */
     uint64_t literal_reruns;   /* candidates the compact engine handed to the literal engine; frontier
-                                  engine: prefixes judged outside the pair form, plus, where the
+                                  engine: prefixes judged outside the pair form (none under AUTO where a
+                                  state graph stands in for it), plus, where the
                                   last level rebuilds such a prefix, its extensions that pass the
                                   goal filter and miss the goal                                   */
     uint64_t member_visits;    /* sum over applied instructions of the devices taking part in them */
@@ -242,7 +248,8 @@ typedef struct {
  * under the shared-prefix engine).  P2_FLAG_EVALUATE_EVERY_QUERY in the options of any query of the
  * batch switches this off for the whole batch, on every engine.
  * The kernels of all queries share their launches; the call waits for the device twice: after
- * the evaluation (to size the result lists) and for the results.  Queries on the frontier engine
+ * the evaluation (to size the result lists) and for the results (once where engine AUTO answers every
+ * query from a state graph and none asks for a shortlist).  Queries on the frontier engine
  * run on streams of the library's own, up to four enumerations side by side, and the call waits
  * for them; the first call of a host thread with more than one enumeration also waits for the
  * caller's stream and spends a few milliseconds timing short kernels on a handful of new streams,

@@ -157,6 +157,8 @@ struct Ctx {
     bool topk_control_clear = false;                        // the words that the blocks of a selection share are zero
     DevBuf sel_progs, sel_costs, gather;                    // the rows that shortlists picked, and whose they are
     HostBuf h_gather;
+    DevBuf g_zero, g_mem, g_rows;                           // state-graph engine: what starts from zero, the lists, whose rows are written
+    HostBuf h_gctr, h_grows;
     DevBuf f_finish;                                        // frontier engine: what every query's rows are written from
     HostBuf h_finish;
     DevBuf f_rank, f_rank_runs, f_share;                                 // frontier engine: ranks of the valid programs, queries of the enumerations
@@ -263,7 +265,7 @@ const std::thread::id g_loader_thread = std::this_thread::get_id();
 
 void Ctx::release() {
     DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_control, &topk_pos,
-                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink};
+                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink, &g_zero, &g_mem, &g_rows};
     for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
     for (auto* v : {&f_evalid, &f_egsums}) {
         for (DevBuf& b : *v) if (b.p) (void)hipFree(b.p);
@@ -271,7 +273,7 @@ void Ctx::release() {
     }
     for (FrontSlot& sl : slots) sl.release();
     for (hipStream_t& sp : spare_streams) { if (sp) (void)hipStreamDestroy(sp); sp = nullptr; }
-    HostBuf* host[] = {&h_rows, &h_rows_hdr, &h_blob, &h_counters, &h_progs, &h_costs, &h_pos, &h_post, &h_topk_jobs, &h_topk_nan, &h_fshare, &h_gather, &h_finish};
+    HostBuf* host[] = {&h_rows, &h_rows_hdr, &h_blob, &h_counters, &h_progs, &h_costs, &h_pos, &h_post, &h_topk_jobs, &h_topk_nan, &h_fshare, &h_gather, &h_finish, &h_gctr, &h_grows};
     for (HostBuf* b : host) { if (b->p) (void)hipHostFree(b->p); b->p = nullptr; b->cap = 0; }
     if (front_go) { (void)hipEventDestroy(front_go); front_go = nullptr; }
     if (copy_done) { (void)hipEventDestroy(copy_done); copy_done = nullptr; }
@@ -337,6 +339,58 @@ bool pruned_is_faster(const p2::Plan& pl) {
     return pl.n_candidates * (unsigned long long)pl.R >= 80000000ull;
 }
 
+// Rows that the state-graph engine holds per device: one for every block of k / R chunks where the blocks come out even.
+int graph_rows(const p2::Plan& pl) { return pl.k % pl.R == 0 ? pl.R : pl.k; }
+// What the state-graph engine takes over from the others under AUTO: groups of up to 64 devices with power-of-two
+// patterns (a lane plays a device), up to 64 rows (a 64-bit word holds a set of them).  The number of states depends on
+// the levels and the size limit, hardly on the sizes of the levels: at most 42 for two levels, 1 000 for three, 17 300 for
+// four with six instructions, 50 300 for five with five, 29 600 for six with four; past these the counts of a
+// graph no longer fit in a compute unit's LDS.
+bool graph_applies(const p2::Plan& pl) {
+    if (pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.frontier_pairs != P2_FRONTIER_PAIRS_AUTO || pl.alphabet == 0) return false;
+    if (pl.R < 2 || pl.R > 64 || graph_rows(pl) > 64) return false;
+    const size_t n_pat = pl.patterns.size();
+    if (n_pat > (size_t)p2::kGraphPatterns || pl.max_len > (n_pat <= 9 ? 7 : n_pat <= 16 ? 6 : n_pat <= 25 ? 5 : 4)) return false;
+    for (const p2::Pattern& p : pl.patterns)
+        if (p2::reg_shape_of(p.g, p.s, p.master, 6) < 0) return false;
+    return true;
+}
+// Room for the states of a structure (see above), first guess; a structure that has more is met with four times as much.
+uint32_t graph_room(const p2::Plan& pl) {
+    static const uint32_t levels[5][P2_MAX_LEN + 1] = {{0, 96, 96, 96, 96, 96, 96, 96},
+                                                       {0, 64, 64, 256, 640, 1024, 1280, 1536},
+                                                       {0, 64, 128, 768, 3072, 10240, 20480, 32768},
+                                                       {0, 64, 256, 1536, 12288, 57344, 57344, 57344},
+                                                       {0, 64, 256, 3072, 16384, 16384, 16384, 16384}};
+    const size_t n = pl.patterns.size();
+    return levels[n <= 4 ? 0 : n <= 9 ? 1 : n <= 16 ? 2 : n <= 25 ? 3 : 4][pl.max_len];
+}
+bool same_graph(const p2::Plan& a, const p2::Plan& b) {
+    if (a.R != b.R || graph_rows(a) != graph_rows(b) || a.max_len != b.max_len || a.alphabet != b.alphabet || a.n_ops != b.n_ops ||
+        a.patterns.size() != b.patterns.size())
+        return false;
+    for (int t = 0; t < a.n_ops; ++t)
+        if (a.ops[t] != b.ops[t]) return false;
+    for (size_t t = 0; t < a.patterns.size(); ++t)
+        if (a.patterns[t].g != b.patterns[t].g || a.patterns[t].s != b.patterns[t].s || a.patterns[t].master != b.patterns[t].master)
+            return false;
+    return true;
+}
+// Valid programs to have room for before they are counted (more cost a second pass over the rows, nothing else).
+size_t graph_rows_guess(const p2::Plan& pl) {
+    static const uint32_t levels[6][P2_MAX_LEN + 1] = {{0, 3, 3, 3, 3, 3, 3, 3},
+                                                       {0, 1, 5, 35, 86, 110, 110, 110},
+                                                       {0, 7, 7, 80, 571, 2549, 6794, 16384},
+                                                       {0, 9, 9, 138, 1646, 16000, 83920, 83920},
+                                                       {0, 11, 11, 256, 4096, 45056, 45056, 45056},
+                                                       {0, 13, 13, 320, 4096, 4096, 4096, 4096}};
+    const size_t n = pl.patterns.size();
+    return levels[n <= 1 ? 0 : n <= 4 ? 1 : n <= 9 ? 2 : n <= 16 ? 3 : n <= 25 ? 4 : 5][pl.max_len];
+}
+// Lists of the state-graph engine beyond this size are left to the other engines (a batch that asks for every query to be
+// evaluated by itself can have hundreds of large structures).
+constexpr size_t kGraphBytesMax = (size_t)32 << 30;
+
 // What decides about validity is the same for both: group, chunks, patterns, alphabet and size limit.
 bool same_structure(const p2::Plan& a, const p2::Plan& b) {
     if (a.R != b.R || a.k != b.k || a.max_len != b.max_len || a.alphabet != b.alphabet || a.n_ops != b.n_ops ||
@@ -380,6 +434,9 @@ struct QueryRun {
     bool regs = false;                    // per-candidate small-group engine (steps computed in registers)
     bool shared = false;                  // shared-prefix engine (the common instructions of a group applied once)
     bool auto_groups = false;             // its handed-over groups are picked up by the device-driven literal launch
+    bool graph = false;                   // evaluated by the state-graph engine (AUTO), reported as the engine it stands in for
+    bool graph_frontier = false;          // ... the frontier engine, whose stats count the prefixes' instructions
+    int graph_id = -1, graph_pos = 0;     // ... its graph, and its place among the graph's queries
     bool wave_cost = false;               // valid programs costed by the wavefront-per-program kernel
     int enum_id = -1, share_pos = 0;      // frontier: its enumeration, and its place among the enumeration's queries
     int topk = 0;
@@ -395,8 +452,9 @@ struct QueryRun {
     size_t out_first = 0;                 // first row of this query in the sorted/prog/cost buffers
 };
 
-int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_bytes, int32_t n_msg,
-                  p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset, p2_stats* stats) {
+constexpr int32_t kWithoutGraphs = 1;      // (internal) the call is to be repeated without the state-graph engine
+int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* msg_bytes, int32_t n_msg,
+                     p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset, p2_stats* stats, bool graphs_allowed) {
     using namespace p2;
     if (!queries || n_queries < 1 || !out_offset) return fail(P2_EINVAL, "null or empty query list");
     if (n_msg < 0 || (n_msg > 0 && !msg_bytes)) return fail(P2_EINVAL, "bad message size list");
@@ -487,7 +545,36 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         // valid programs of these queries are costed one per wavefront, lanes as devices
         runs[i].wave_cost = runs[i].engine == P2_ENGINE_COMPACT && pl.R <= 64;
         for (const Pattern& p : pl.patterns) runs[i].wave_cost = runs[i].wave_cost && reg_shape_of(p.g, p.s, p.master, 6) >= 0;
+        if (graphs_allowed && want == P2_ENGINE_AUTO && graph_applies(pl)) {
+            runs[i].graph = true;
+            runs[i].graph_frontier = runs[i].frontier;
+            runs[i].frontier = runs[i].flat_counts = false;
+        }
     }
+    // queries of one reduction structure are answered from one graph
+    struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t cap_nodes = 0, cap_planes = 0, n_blocks = 0; bool small = false;
+                   size_t off_members = 0, at_table = 0, at_mem = 0; };
+    std::vector<Graph> graphs;
+    for (int i = 0; i < n_queries; ++i) {
+        QueryRun& r = runs[i];
+        if (!r.graph) continue;
+        for (size_t g = 0; g < graphs.size() && r.graph_id < 0 && share_validity; ++g)
+            if (runs[graphs[g].leader].graph_frontier == r.graph_frontier && same_graph(runs[graphs[g].leader].plan, r.plan)) r.graph_id = (int)g;
+        if (r.graph_id < 0) { r.graph_id = (int)graphs.size(); graphs.emplace_back(); graphs.back().leader = i; }
+        r.graph_pos = (int)graphs[r.graph_id].members.size();
+        graphs[r.graph_id].members.push_back(i);
+    }
+    size_t n_others = 0;                 // queries that other engines evaluate
+    bool any_topk = false;
+    for (const QueryRun& r : runs) { n_others += r.graph || r.plan.n_candidates == 0 ? 0 : 1; any_topk |= r.topk > 0; }
+    // Every query answered from a graph: the whole call is one stream of kernels, tables and results travel by kernels that
+    // read and write pinned host memory, and where no shortlist is asked for the rows go straight there.
+    const bool only_graphs = n_others == 0 && !graphs.empty();
+    size_t rows_guess = 0, emit_blocks = 0;
+    if (only_graphs)
+        for (const QueryRun& r : runs)
+            if (r.graph) { const size_t n = graph_rows_guess(r.plan); rows_guess += n; emit_blocks += (n + 255) / 256; }
+    bool direct = only_graphs && !any_topk && cap > 0;
 
     {
         std::vector<const Plan*> large;              // groups of more than 64 devices that AUTO would enumerate, one of each structure
@@ -511,10 +598,10 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         for (int i = 0; i < n_queries && share_validity; ++i) {
             QueryRun& r = runs[i];
             const Plan& pl = r.plan;
-            if (r.frontier || pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.n_candidates == 0) continue;
+            if (r.graph || r.frontier || pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.n_candidates == 0) continue;
             for (int j = 0; j < i && r.same_as < 0; ++j) {
                 const QueryRun& c = runs[j];
-                if (c.same_as < 0 && !c.frontier && c.plan.hierarchy == P2_HIERARCHY_COLLAPSED && c.engine == r.engine && c.shared == r.shared &&
+                if (c.same_as < 0 && !c.graph && !c.frontier && c.plan.hierarchy == P2_HIERARCHY_COLLAPSED && c.engine == r.engine && c.shared == r.shared &&
                     c.regs == r.regs && same_structure(c.plan, pl))
                     r.same_as = j;
             }
@@ -534,7 +621,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     std::vector<Launch> launches;
     auto word_class = [](int bits) { int w = (bits + 31) / 32; return w <= 1 ? 1 : w <= 2 ? 2 : w <= 4 ? 4 : w <= 8 ? 8 : 16; };
     for (int i = 0; i < n_queries; ++i) {
-        if (runs[i].engine != P2_ENGINE_COMPACT || runs[i].frontier || runs[i].same_as >= 0 || runs[i].plan.n_candidates == 0) continue;
+        if (runs[i].engine != P2_ENGINE_COMPACT || runs[i].graph || runs[i].frontier || runs[i].same_as >= 0 || runs[i].plan.n_candidates == 0) continue;
         const Plan& pl = runs[i].plan;
         const int kind = runs[i].shared ? 2 : runs[i].regs ? 1 : 0;
         const int kw = kind == 1 ? 1 : word_class(pl.k), mw = kind == 1 ? 1 : word_class(pl.R);
@@ -548,7 +635,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     unsigned long long shared_stems = 0;
     for (int i = 0; i < n_queries; ++i) {
         const Plan& pl = runs[i].plan;
-        if (!runs[i].shared || runs[i].frontier || runs[i].same_as >= 0 || pl.n_candidates == 0 || pl.alphabet == 0) continue;
+        if (!runs[i].shared || runs[i].graph || runs[i].frontier || runs[i].same_as >= 0 || pl.n_candidates == 0 || pl.alphabet == 0) continue;
         for (int len = 2; len <= pl.max_len; ++len)
             shared_stems += (pl.base[len + 1] - pl.base[len]) / ((unsigned long long)pl.alphabet * (unsigned long long)pl.alphabet);
     }
@@ -559,7 +646,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         unsigned long long blocks = 0;
         for (int i = 0; i < n_queries; ++i) {
             const Plan& pl = runs[i].plan;
-            if (runs[i].engine != P2_ENGINE_COMPACT || runs[i].frontier || runs[i].same_as >= 0 || pl.n_candidates == 0) continue;
+            if (runs[i].engine != P2_ENGINE_COMPACT || runs[i].graph || runs[i].frontier || runs[i].same_as >= 0 || pl.n_candidates == 0) continue;
             const int kind = runs[i].shared ? 2 : runs[i].regs ? 1 : 0;
             if (kind != L.kind || (kind == 1 ? 1 : word_class(pl.k)) != L.kw || (kind == 1 ? 1 : word_class(pl.R)) != L.mw) continue;
             for (int len = 1; len <= pl.max_len; ++len) {
@@ -617,7 +704,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     std::vector<AutoGroups> autos;
     for (int i = 0; i < n_queries; ++i) {
         QueryRun& r = runs[i];
-        if (!r.shared || r.frontier || r.same_as >= 0 || r.plan.n_candidates == 0) continue;
+        if (!r.shared || r.graph || r.frontier || r.same_as >= 0 || r.plan.n_candidates == 0) continue;
         const int mw = r.plan.R <= 32 ? 1 : 2;
         const int cls = mw;
         AutoGroups* A = nullptr;
@@ -637,6 +724,44 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         size_t n_rank = 0;
         for (const Pattern& p : r.plan.patterns) n_rank += p.rank.size();
         off += align_up(sizeof(int32_t) * n_rank, 256);
+    }
+    // the state graphs: their descriptions, which blocks work on which, and the queries that share each
+    size_t off_gasked = 0, off_graphs = 0, off_glevel = 0, off_gsteps = 0, off_gsmall = 0, off_glarge = 0;
+    std::vector<GraphBlock> glevel, gsteps;
+    std::vector<uint32_t> gsmall, glarge;
+    int graph_levels = 0;
+    if (!graphs.empty()) {
+        uint32_t n_by_size[3] = {0, 0, 0};                // up to two levels, three, more
+        auto size_of = [&](const Graph& G) { const size_t n = runs[G.leader].plan.patterns.size(); return n <= 4 ? 0 : n <= 9 ? 1 : 2; };
+        for (Graph& G : graphs) ++n_by_size[size_of(G)];
+        const bool alone = n_by_size[1] + n_by_size[2] == 0;      // (beside larger ones the small ones ride along in their launches)
+        for (size_t g = 0; g < graphs.size(); ++g) {
+            Graph& G = graphs[g];
+            const int sz = size_of(G);
+            // (blocks per level: three levels have some 280 states in the largest, four some 9 000; a launch of some 2 000
+            //  blocks fills the chip)
+            G.small = sz == 0 && alone && graph_alone_holds(graph_room(runs[G.leader].plan));
+            const uint32_t share = 2048u / std::max(1u, n_by_size[sz]);
+            G.n_blocks = G.small ? 1u : sz == 0 ? 12u : sz == 1 ? std::min(std::max(share, 16u), 160u) : std::min(std::max(share, 64u), 768u);
+            if (G.small) gsmall.push_back((uint32_t)g);
+            else {
+                glarge.push_back((uint32_t)g);
+                graph_levels = std::max(graph_levels, runs[G.leader].plan.max_len);
+                for (uint32_t b = 0; b < G.n_blocks; ++b) glevel.push_back(GraphBlock{(uint32_t)g, b, G.n_blocks, 0u});
+            }
+            // (four edges a block at a time; two levels have some 70 edges on the way to a goal, three 900, four 6 300)
+            const uint32_t nb = sz == 0 ? 18u : std::min(std::max(share, 16u), sz == 1 ? 160u : 512u);
+            for (uint32_t b = 0; n_msg > 0 && b < nb; ++b) gsteps.push_back(GraphBlock{(uint32_t)g, b, nb, 0u});
+            G.off_members = off;
+            off += align_up(sizeof(int32_t) * G.members.size(), 64);
+        }
+        off = align_up(off, 256);
+        off_gasked = off; off += align_up(sizeof(GraphQuery) * (size_t)n_queries, 256);
+        off_graphs = off; off += align_up(sizeof(DevGraph) * graphs.size(), 256);
+        off_glevel = off; off += align_up(sizeof(GraphBlock) * glevel.size(), 256);
+        off_gsteps = off; off += align_up(sizeof(GraphBlock) * gsteps.size(), 256);
+        off_gsmall = off; off += align_up(sizeof(uint32_t) * gsmall.size(), 256);
+        off_glarge = off; off += align_up(sizeof(uint32_t) * glarge.size(), 256);
     }
     const size_t off_msg = off;
     off += align_up(sizeof(double) * (size_t)std::max(n_msg, 1), 256);
@@ -708,6 +833,11 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             H.entries = reinterpret_cast<const uint32_t*>(dr + r.off_entries);
         });
         rows_ready = true;
+        if (only_graphs) {
+            const CopyPart up[2] = {{C.rows.p, C.h_rows.p, bytes}, {C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * (size_t)n_queries}};
+            P2_HIP(launch_copies(up, 2, stream));
+            return P2_OK;
+        }
         P2_HIP(hipMemcpyAsync(C.rows.p, C.h_rows.p, bytes, hipMemcpyHostToDevice, C.copy_stream));
         P2_HIP(hipMemcpyAsync(C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * (size_t)n_queries, hipMemcpyHostToDevice, C.copy_stream));
         P2_HIP(hipEventRecord(C.copy_done, C.copy_stream));
@@ -727,8 +857,8 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     };
     for (auto& r : runs) {
         const unsigned long long N = r.plan.n_candidates;
-        r.valid_cap = (r.frontier || r.same_as >= 0) ? 0u : (uint32_t)std::min<unsigned long long>(N, 1u << 15);
-        r.rerun_cap = (r.engine == P2_ENGINE_COMPACT && !r.frontier && r.same_as < 0) ? (uint32_t)std::min<unsigned long long>(N, 1u << 10) : 0u;
+        r.valid_cap = (r.graph || r.frontier || r.same_as >= 0) ? 0u : (uint32_t)std::min<unsigned long long>(N, 1u << 15);
+        r.rerun_cap = (r.engine == P2_ENGINE_COMPACT && !r.graph && !r.frontier && r.same_as < 0) ? (uint32_t)std::min<unsigned long long>(N, 1u << 10) : 0u;
     }
 
     // global state buffer for literal evaluations whose state does not fit in LDS
@@ -772,6 +902,84 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     auto mask_class = [](int R) { return R <= 32 ? 1 : R <= 64 ? 2 : R <= 128 ? 4 : R <= 256 ? 8 : 16; };
     char* hb = static_cast<char*>(C.h_blob.p);
     char* db = static_cast<char*>(C.blob.p);
+    // the lists of the state graphs, one graph after the other (grown and repeated like the others)
+    uint32_t graph_scale = 1;
+    size_t graph_zero = 0;
+    const size_t graph_nan = sizeof(GraphCounters) * graphs.size();      // behind the counters: a word per query, set where a cost is NaN
+    const size_t graph_back = graph_nan + sizeof(uint32_t) * (size_t)n_queries;
+    auto layout_graphs = [&](DevGraph* out) -> int32_t {
+        const size_t n_graphs = graphs.size();
+        size_t zero = align_up(graph_nan + sizeof(uint32_t) * (size_t)n_queries, 256), mem = 0;
+        auto take = [](size_t& at, size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
+        struct Place { size_t table, table_node, planes, state, found, links, use_id, first, use_ends, edges, edge_state, best; };
+        std::vector<Place> places(n_graphs);
+        for (size_t g = 0; g < n_graphs; ++g) {
+            const Graph& G = graphs[g];
+            const Plan& pl = runs[G.leader].plan;
+            DevGraph& D = out[g];
+            std::memset(&D, 0, sizeof D);
+            D.query = (uint32_t)G.leader;
+            D.R = pl.R; D.rows_kept = graph_rows(pl);
+            D.n_pat = (int)pl.patterns.size(); D.n_ops = pl.n_ops; D.alphabet = pl.alphabet; D.max_len = pl.max_len;
+            D.digit_words = (pl.alphabet + 63) / 64;
+            D.n_members = (int)G.members.size();
+            for (int o = 0; o < pl.n_ops; ++o) { D.op_mask |= 1u << pl.ops[o]; D.op_ranks |= (uint32_t)o << (4 * pl.ops[o]); }
+            for (int32_t m : G.members) D.split_check |= runs[m].plan.k != D.rows_kept ? 1u : 0u;
+            D.fused = runs[G.leader].graph_frontier ? 0u : 1u;
+            D.cap_nodes = graph_room(pl) * graph_scale;
+            // (twice as many children as nodes; a wavefront may leave the rest of what it reserved at every level)
+            D.cap_planes = D.cap_nodes * 2 + 16u * 4u * G.n_blocks * (uint32_t)pl.max_len / 2u + 1024u;
+            D.cap_found = D.cap_nodes * 3;
+            D.cap_edges = D.cap_nodes + 256;
+            uint32_t slots = 64;
+            while (slots < 2 * D.cap_nodes) slots *= 2;
+            D.table_mask = slots - 1;
+            for (size_t p = 0; p < pl.patterns.size(); ++p) {
+                const Pattern& pt = pl.patterns[p];
+                D.shape[p] = (uint8_t)reg_shape_of(pt.g, pt.s, 0, 6);
+                for (int d = 0; d < pl.R; ++d)
+                    if (!pt.master || d % pt.s == 0) D.part[p] |= 1ull << d;
+            }
+            D.all_rows = D.rows_kept >= 64 ? ~0ull : (1ull << D.rows_kept) - 1ull;
+            D.all_cols = pl.R >= 64 ? ~0ull : (1ull << pl.R) - 1ull;
+            Place& P = places[g];
+            P.table = take(zero, sizeof(unsigned long long) * slots);
+            P.table_node = take(zero, sizeof(uint32_t) * slots);
+            P.planes = take(mem, sizeof(ulonglong2) * (size_t)D.cap_planes * pl.R);
+            P.state = take(mem, sizeof(uint32_t) * D.cap_nodes);
+            P.found = take(mem, sizeof(uint4) * D.cap_found);
+            P.links = take(mem, sizeof(uint2) * D.cap_found);
+            P.use_id = take(mem, sizeof(uint32_t) * D.cap_nodes);
+            P.first = take(mem, sizeof(uint32_t) * ((size_t)D.cap_nodes + 1));
+            P.use_ends = take(mem, sizeof(uint32_t) * 8 * (size_t)D.cap_nodes);
+            P.edges = take(mem, sizeof(uint32_t) * D.cap_edges);
+            P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
+            P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
+        }
+        if (mem + zero > kGraphBytesMax) return kWithoutGraphs;
+        if (C.g_zero.ensure(zero) != hipSuccess || C.g_mem.ensure(mem) != hipSuccess) {      // (the other engines need less)
+            (void)hipGetLastError();
+            return kWithoutGraphs;
+        }
+        P2_HIP(C.h_gctr.ensure(graph_back + 16));
+        graph_zero = zero;
+        char* z = static_cast<char*>(C.g_zero.p);
+        char* m = static_cast<char*>(C.g_mem.p);
+        for (size_t g = 0; g < n_graphs; ++g) {
+            DevGraph& D = out[g];
+            const Place& P = places[g];
+            D.ctr = reinterpret_cast<GraphCounters*>(z) + g;
+            D.table = reinterpret_cast<unsigned long long*>(z + P.table); D.table_node = reinterpret_cast<uint32_t*>(z + P.table_node);
+            D.planes = reinterpret_cast<ulonglong2*>(m + P.planes); D.node_state = reinterpret_cast<uint32_t*>(m + P.state);
+            D.found = reinterpret_cast<uint4*>(m + P.found); D.links = reinterpret_cast<uint2*>(m + P.links);
+            D.use_id = reinterpret_cast<uint32_t*>(m + P.use_id); D.first_edge = reinterpret_cast<uint32_t*>(m + P.first);
+            D.use_ends = reinterpret_cast<uint32_t*>(m + P.use_ends);
+            D.edges = reinterpret_cast<uint32_t*>(m + P.edges); D.edge_state = reinterpret_cast<uint32_t*>(m + P.edge_state);
+            D.best = reinterpret_cast<double*>(m + P.best);
+            D.members = reinterpret_cast<const int32_t*>(static_cast<char*>(C.blob.p) + graphs[g].off_members);
+        }
+        return P2_OK;
+    };
     std::vector<char> done(n_queries, 0);
     for (int attempt = 0; attempt < 4; ++attempt) {
         auto tot = layout_lists();
@@ -849,11 +1057,47 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             if (!L.shares.empty()) std::memcpy(hb + L.off_shares, L.shares.data(), sizeof(DevShare) * L.shares.size());
         }
         for (auto& A : autos) std::memcpy(hb + A.off, A.qlist.data(), sizeof(int32_t) * A.qlist.size());
-        P2_HIP(hipMemcpyAsync(db, hb, blob_bytes, hipMemcpyHostToDevice, stream));
-        P2_HIP(hipMemsetAsync(C.counters.p, 0, sizeof(DevCounters) * (size_t)n_queries, stream));
+        if (!graphs.empty()) {
+            const int32_t rc = layout_graphs(reinterpret_cast<DevGraph*>(hb + off_graphs));
+            if (rc != P2_OK) return rc;
+            for (int i = 0; i < n_queries; ++i)
+                reinterpret_cast<GraphQuery*>(hb + off_gasked)[i] = GraphQuery{runs[i].graph ? (uint32_t)runs[i].graph_id : ~0u, (uint32_t)runs[i].graph_pos};
+            for (const Graph& G : graphs) std::memcpy(hb + G.off_members, G.members.data(), sizeof(int32_t) * G.members.size());
+            if (!glevel.empty()) std::memcpy(hb + off_glevel, glevel.data(), sizeof(GraphBlock) * glevel.size());
+            if (!gsteps.empty()) std::memcpy(hb + off_gsteps, gsteps.data(), sizeof(GraphBlock) * gsteps.size());
+            if (!gsmall.empty()) std::memcpy(hb + off_gsmall, gsmall.data(), sizeof(uint32_t) * gsmall.size());
+            if (!glarge.empty()) std::memcpy(hb + off_glarge, glarge.data(), sizeof(uint32_t) * glarge.size());
+        }
+        if (only_graphs) {
+            const CopyPart in[2] = {{db, hb, blob_bytes}, {C.g_zero.p, nullptr, graph_zero}};
+            P2_HIP(launch_copies(in, 2, stream));
+        } else {
+            P2_HIP(hipMemcpyAsync(db, hb, blob_bytes, hipMemcpyHostToDevice, stream));
+            P2_HIP(hipMemsetAsync(C.counters.p, 0, sizeof(DevCounters) * (size_t)n_queries, stream));
+            if (!graphs.empty()) P2_HIP(hipMemsetAsync(C.g_zero.p, 0, graph_zero, stream));
+        }
         // ---- evaluate every candidate of every query
         int eval_launches = 0;
         if (g_prof.on) P2_HIP(hipEventRecord(g_prof.ev[0], stream));
+        const DevQuery* const dqs = reinterpret_cast<const DevQuery*>(db);
+        const DevGraph* const dgs = reinterpret_cast<const DevGraph*>(db + off_graphs);
+        if (!gsmall.empty()) {
+            ++eval_launches;
+            int max_R = 1;
+            for (uint32_t g : gsmall) max_R = std::max(max_R, runs[graphs[g].leader].plan.R);
+            P2_HIP(launch_graph_alone(dgs, reinterpret_cast<const uint32_t*>(db + off_gsmall), (unsigned)gsmall.size(), max_R, stream));
+        }
+        if (!glarge.empty()) {
+            eval_launches += graph_levels + 1;
+            for (int level = 0; level < graph_levels; ++level)
+                P2_HIP(launch_graph_level(dgs, reinterpret_cast<const GraphBlock*>(db + off_glevel), (unsigned)glevel.size(), level, graph_levels, stream));
+            // (a byte per node, a word for every count of a node inside, two words per digit set of a node on the way to a goal:
+            //  less than ten bytes a node together where there are many, three words where there are few)
+            uint32_t most = 0;
+            for (uint32_t g : glarge) most = std::max(most, reinterpret_cast<const DevGraph*>(hb + off_graphs)[g].cap_nodes);
+            P2_HIP(launch_graph_finish(dgs, reinterpret_cast<const uint32_t*>(db + off_glarge), (unsigned)glarge.size(),
+                                       most <= 4096 ? (size_t)most * 12 + 4096 : (size_t)160 * 1024, stream));
+        }
         for (auto& L : launches) {
             ++eval_launches;
             if (L.kind == 2)
@@ -889,9 +1133,29 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             const int32_t rc = build_and_upload_rows();
             if (rc != P2_OK) return rc;
         }
-        P2_HIP(launch_copy_out(C.h_counters.p, C.counters.p, sizeof(DevCounters) * (size_t)n_queries, stream));
+        if (!gsteps.empty())
+            P2_HIP(launch_graph_steps(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gsteps), (unsigned)gsteps.size(), stream));
+        if (direct) {
+            P2_HIP(C.h_progs.ensure(sizeof(p2_program) * rows_guess));
+            P2_HIP(C.h_costs.ensure(sizeof(double) * rows_guess * (size_t)std::max(n_msg, 1)));
+            P2_HIP(launch_graph_emit(dqs, dgs, static_cast<const GraphCounters*>(C.g_zero.p), reinterpret_cast<const GraphQuery*>(db + off_gasked),
+                                     n_queries, nullptr, 0, (unsigned)emit_blocks + 1u, rows_guess, nullptr, static_cast<p2_program*>(C.h_progs.p),
+                                     static_cast<double*>(C.h_costs.p), C.h_gctr.p, (int)graphs.size(), stream));
+            if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = 2; }
+        } else {
+            const CopyPart back[2] = {{C.h_counters.p, C.counters.p, n_others > 0 ? sizeof(DevCounters) * (size_t)n_queries : 0},
+                                      {C.h_gctr.p, C.g_zero.p, graph_nan}};
+            P2_HIP(launch_copies(back, 2, stream));
+        }
         P2_HIP(hipStreamSynchronize(stream));
         bool again = false;
+        const GraphCounters* const hg = static_cast<const GraphCounters*>(C.h_gctr.p);
+        for (size_t g = 0; g < graphs.size(); ++g) {
+            if ((hg[g].flags & ~kGraphFull) != 0u || (hg[g].flags != 0u && attempt == 3)) return kWithoutGraphs;
+            if (hg[g].flags == 0u) continue;
+            again = true;
+        }
+        if (again) graph_scale *= 4;
         const DevCounters* hc = static_cast<const DevCounters*>(C.h_counters.p);
         // candidates whose state the compact engine could not hold go through the literal engine:
         // one launch per mask-width class for the states that fit in LDS, one per query otherwise
@@ -899,7 +1163,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         std::vector<PostLaunch> rerun_launches;
         for (int i = 0; i < n_queries; ++i) {
             QueryRun& r = runs[i];
-            if (hc[i].n_rerun == 0 || hc[i].n_rerun > r.rerun_cap || r.auto_groups) continue;
+            if (r.graph || hc[i].n_rerun == 0 || hc[i].n_rerun > r.rerun_cap || r.auto_groups) continue;
             reran = true;
             if (literal_lds_bytes(r.plan.R, r.plan.k) != 0) {
                 add_seg(rerun_launches, mask_class(r.plan.R), r.plan, i, hc[i].n_rerun, 1, r.off_rerun, 0);
@@ -922,6 +1186,32 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         }
         for (int i = 0; i < n_queries; ++i) {
             QueryRun& r = runs[i];
+            if (r.plan.n_candidates == 0) continue;       // (a reduction over one device: nothing was evaluated)
+            if (r.graph) {
+                const GraphCounters& gc = hg[r.graph_id];
+                const Plan& pl = r.plan;
+                // A walk applies, to every candidate that starts with a valid prefix, one more instruction (a program that
+                // has reached the goal is not valid with one more: every rule fails there); the enumeration by size applies
+                // the alphabet to every prefix.
+                unsigned long long walked = 0, listed = 0, valid = 0, per_alphabet = 0;
+                for (const Pattern& p : pl.patterns) per_alphabet += (unsigned long long)p.g * p.n_groups * pl.n_ops;
+                for (int len = 0; len < pl.max_len; ++len) {
+                    unsigned long long behind = 0, power = 1;
+                    for (int l = len; l < pl.max_len; ++l) { behind += power; power *= (unsigned long long)pl.alphabet; }
+                    const unsigned long long prefixes = len == 0 ? 1ull : gc.n_prefixes[len];
+                    walked += behind * (prefixes + (len > 0 ? gc.n_valid[len] : 0u));
+                    listed += prefixes;
+                }
+                for (int len = 1; len <= pl.max_len; ++len) valid += gc.n_valid[len];
+                if (valid > 0xffffffffull) return kWithoutGraphs;
+                r.n_valid = (uint32_t)valid; r.n_rerun = r.n_rerun_groups = 0;
+                const unsigned long long applied = r.graph_frontier ? listed : walked;
+                r.steps = applied * (unsigned long long)pl.alphabet; r.members = applied * per_alphabet;
+                const bool own = graphs[r.graph_id].leader == i;
+                r.evaluated = own ? (unsigned long long)gc.n_judged * (unsigned long long)pl.alphabet : 0ull;
+                r.evaluated_members = own ? (unsigned long long)gc.n_judged * per_alphabet : 0ull;
+                continue;
+            }
             r.n_valid = hc[i].n_valid; r.n_rerun = hc[i].n_rerun; r.n_rerun_groups = hc[i].n_rerun_groups;
             r.steps = 0; r.members = 0;
             for (int t = 0; t < kCounterStripes; ++t) { r.steps += hc[i].steps[t]; r.members += hc[i].members[t]; }
@@ -1410,7 +1700,8 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     bool only_shortlists = n_msg > 0;
     for (const auto& r : runs) only_shortlists = only_shortlists && (r.n_valid == 0 || r.topk > 0);
     size_t pos_off = 0;
-    if (store) {
+    direct = direct && store && total_valid <= rows_guess;       // (the rows are in host memory already)
+    if (store && !direct) {
     P2_HIP(C.sorted.ensure(sizeof(unsigned long long) * std::max<size_t>(total_valid, 1)));
     P2_HIP(C.progs.ensure(sizeof(p2_program) * std::max<size_t>(total_valid, 1)));
     P2_HIP(C.costs.ensure(sizeof(double) * std::max<size_t>(total_valid, 1) * nm));
@@ -1428,9 +1719,18 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     long long topk_jobs_n = 0;
     // ordering and costing: one launch per kernel and state-size class
     std::vector<PostLaunch> sort_launches, ccost_launches, scost_launches, lcost_launches;
+    std::vector<GraphRows> graph_rows_of;
+    unsigned graph_row_blocks = 0;
     for (int i = 0; i < n_queries; ++i) {
         QueryRun& r = runs[i];
         if (r.n_valid == 0) continue;
+        if (r.graph && only_graphs) continue;            // (one after the other, as the counts on the device say)
+        if (r.graph) {                                   // (the rows come out in order and costed)
+            graph_rows_of.push_back(GraphRows{graph_row_blocks, (uint32_t)i, (uint32_t)r.graph_id, (uint32_t)r.graph_pos, r.n_valid, 0u,
+                                              (unsigned long long)r.out_first});
+            graph_row_blocks += (r.n_valid + 255u) / 256u;
+            continue;
+        }
         if (r.frontier) {
             // ordered and costed from the enumeration's sums (below); programs that came from literal prefixes
             // have no sums and are costed by the literal kernel
@@ -1488,6 +1788,25 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                                   L.max_k, static_cast<unsigned long long*>(C.valid.p), nullptr,
                                   sorted_base, progs_base, costs_base, stream));
     }
+    if (only_graphs && total_valid > 0) {
+        size_t blocks = 0;
+        for (const QueryRun& r : runs) blocks += (r.n_valid + 255u) / 256u;
+        ++post_launches;
+        P2_HIP(launch_graph_emit(reinterpret_cast<const DevQuery*>(db), reinterpret_cast<const DevGraph*>(db + off_graphs),
+                                 static_cast<const GraphCounters*>(C.g_zero.p), reinterpret_cast<const GraphQuery*>(db + off_gasked), n_queries,
+                                 nullptr, 0, (unsigned)blocks, total_valid, sorted_base, progs_base, costs_base, nullptr, 0, stream));
+    }
+    if (!graph_rows_of.empty()) {
+        const size_t bytes = sizeof(GraphRows) * graph_rows_of.size();
+        P2_HIP(C.g_rows.ensure(bytes));
+        P2_HIP(C.h_grows.ensure(bytes));
+        std::memcpy(C.h_grows.p, graph_rows_of.data(), bytes);
+        P2_HIP(hipMemcpyAsync(C.g_rows.p, C.h_grows.p, bytes, hipMemcpyHostToDevice, stream));
+        ++post_launches;
+        P2_HIP(launch_graph_emit(reinterpret_cast<const DevQuery*>(db), reinterpret_cast<const DevGraph*>(db + off_graphs),
+                                 nullptr, nullptr, 0, static_cast<const GraphRows*>(C.g_rows.p), (int)graph_rows_of.size(), graph_row_blocks,
+                                 total_valid, sorted_base, progs_base, costs_base, nullptr, 0, stream));
+    }
     // frontier enumerations: the place of every program in ascending index order, once per enumeration; then
     // every query of the enumeration writes its rows (programs, and costs from its own sums)
     if (!enums.empty()) {
@@ -1543,7 +1862,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
         unsigned long long* sorted = sorted_base + r.out_first;
         p2_program* progs = progs_base + r.out_first;
         double* costs = costs_base + r.out_first * nm;
-        const bool lit_cost = r.frontier ? (enums[r.enum_id].n_goal_literal > 0 && n_msg > 0)
+        const bool lit_cost = r.graph ? false : r.frontier ? (enums[r.enum_id].n_goal_literal > 0 && n_msg > 0)
                                          : (r.engine == P2_ENGINE_LITERAL || (r.n_rerun > 0 && n_msg > 0));
         if (lit_cost && literal_lds_bytes(r.plan.R, r.plan.k) == 0) {      // literal state too large for LDS
             void* gs = nullptr;
@@ -1557,7 +1876,8 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             for (int m = 0; m < n_msg; ++m) {
                 DevTopkJob J;
                 J.cost = costs + m; J.index = sorted; J.out_pos = static_cast<long long*>(C.topk_pos.p) + pos_off;
-                J.nan_flag = &static_cast<DevCounters*>(C.counters.p)[i].nan_seen;
+                J.nan_flag = only_graphs ? reinterpret_cast<uint32_t*>(static_cast<char*>(C.g_zero.p) + graph_nan) + i
+                                         : &static_cast<DevCounters*>(C.counters.p)[i].nan_seen;
                 J.n = (long long)r.n_valid; J.stride = n_msg; J.k = r.topk; J.pad = 0;
                 pos_off += kk;
                 if (r.n_valid <= kTopkJobMax) {            // one launch for all of them, below
@@ -1570,12 +1890,29 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             }
         }
     }
+    std::vector<DevGatherSeg> gather_segs;               // (shortlists only: which rows go back)
+    if (only_shortlists) {
+        size_t at = 0;
+        for (int i = 0; i < n_queries; ++i) {
+            const QueryRun& r = runs[i];
+            if (r.n_valid == 0) continue;
+            const size_t rows = (size_t)n_msg * std::min<size_t>(r.topk, r.n_valid);
+            gather_segs.push_back(DevGatherSeg{(unsigned long long)r.out_first, (unsigned long long)at, (uint32_t)rows, 0u});
+            at += rows;
+        }
+    }
+    {
+        const size_t job_bytes = sizeof(DevTopkJob) * topk_jobs.size(), seg_bytes = sizeof(DevGatherSeg) * gather_segs.size();
+        P2_HIP(C.topk_jobs.ensure(job_bytes));
+        P2_HIP(C.h_topk_jobs.ensure(job_bytes));
+        P2_HIP(C.gather.ensure(seg_bytes));
+        P2_HIP(C.h_gather.ensure(seg_bytes));
+        if (job_bytes > 0) std::memcpy(C.h_topk_jobs.p, topk_jobs.data(), job_bytes);
+        if (seg_bytes > 0) std::memcpy(C.h_gather.p, gather_segs.data(), seg_bytes);
+        const CopyPart in[2] = {{C.topk_jobs.p, C.h_topk_jobs.p, job_bytes}, {C.gather.p, C.h_gather.p, seg_bytes}};
+        P2_HIP(launch_copies(in, 2, stream));
+    }
     if (!topk_jobs.empty()) {
-        const size_t bytes = sizeof(DevTopkJob) * topk_jobs.size();
-        P2_HIP(C.topk_jobs.ensure(bytes));
-        P2_HIP(C.h_topk_jobs.ensure(bytes));
-        std::memcpy(C.h_topk_jobs.p, topk_jobs.data(), bytes);
-        P2_HIP(hipMemcpyAsync(C.topk_jobs.p, C.h_topk_jobs.p, bytes, hipMemcpyHostToDevice, stream));
         ++post_launches;
         P2_HIP(launch_topk_jobs(static_cast<const DevTopkJob*>(C.topk_jobs.p), (unsigned)topk_jobs.size(), topk_jobs_k, topk_jobs_n, stream));
     }
@@ -1591,46 +1928,34 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     P2_HIP(C.h_pos.ensure(sizeof(long long) * std::max<size_t>(topk_rows, 1)));
     if (only_shortlists) {
         // every query asks for a shortlist: the rows that were picked are gathered on the device, and only they go back
-        std::vector<DevGatherSeg> segs;
-        size_t at = 0;
-        for (int i = 0; i < n_queries; ++i) {
-            const QueryRun& r = runs[i];
-            if (r.n_valid == 0) continue;
-            const size_t rows = (size_t)n_msg * std::min<size_t>(r.topk, r.n_valid);
-            segs.push_back(DevGatherSeg{(unsigned long long)r.out_first, (unsigned long long)at, (uint32_t)rows, 0u});
-            at += rows;
-        }
-        P2_HIP(C.gather.ensure(sizeof(DevGatherSeg) * std::max<size_t>(segs.size(), 1)));
-        P2_HIP(C.h_gather.ensure(sizeof(DevGatherSeg) * std::max<size_t>(segs.size(), 1)));
         P2_HIP(C.sel_progs.ensure(sizeof(p2_program) * std::max<size_t>(topk_rows, 1)));
         P2_HIP(C.sel_costs.ensure(sizeof(double) * std::max<size_t>(topk_rows, 1) * nm));
         P2_HIP(C.h_progs.ensure(sizeof(p2_program) * std::max<size_t>(topk_rows, 1)));
         P2_HIP(C.h_costs.ensure(sizeof(double) * std::max<size_t>(topk_rows, 1) * nm));
-        if (!segs.empty()) {
-            std::memcpy(C.h_gather.p, segs.data(), sizeof(DevGatherSeg) * segs.size());
-            P2_HIP(hipMemcpyAsync(C.gather.p, C.h_gather.p, sizeof(DevGatherSeg) * segs.size(), hipMemcpyHostToDevice, stream));
-            P2_HIP(launch_gather_rows(static_cast<const DevGatherSeg*>(C.gather.p), (unsigned)segs.size(), progs_base, costs_base, n_msg,
+        if (!gather_segs.empty())
+            P2_HIP(launch_gather_rows(static_cast<const DevGatherSeg*>(C.gather.p), (unsigned)gather_segs.size(), progs_base, costs_base, n_msg,
                                       static_cast<const long long*>(C.topk_pos.p), static_cast<p2_program*>(C.sel_progs.p),
                                       static_cast<double*>(C.sel_costs.p), stream));
-        }
-        P2_HIP(launch_copy_out3(C.h_progs.p, C.sel_progs.p, sizeof(p2_program) * topk_rows,
-                                C.h_costs.p, C.sel_costs.p, sizeof(double) * topk_rows * nm,
-                                C.h_pos.p, C.topk_pos.p, sizeof(long long) * topk_rows, stream));
     } else {
         P2_HIP(C.h_progs.ensure(sizeof(p2_program) * std::max<size_t>(total_valid, 1)));
         P2_HIP(C.h_costs.ensure(sizeof(double) * std::max<size_t>(total_valid, 1) * nm));
-        P2_HIP(launch_copy_out3(C.h_progs.p, C.progs.p, sizeof(p2_program) * total_valid,
-                                C.h_costs.p, C.costs.p, n_msg > 0 ? sizeof(double) * total_valid * nm : 0,
-                                C.h_pos.p, C.topk_pos.p, sizeof(long long) * topk_rows, stream));
     }
-    if (topk_rows > 0)      // the selections flag a NaN cost in their query's counters
-        P2_HIP(launch_copy_out(C.h_counters.p, C.counters.p, sizeof(DevCounters) * (size_t)n_queries, stream));
+    {   // (the selections flag a NaN cost in their query's counters)
+        const size_t rows = only_shortlists ? topk_rows : total_valid;
+        const CopyPart back[4] = {{C.h_progs.p, only_shortlists ? C.sel_progs.p : C.progs.p, sizeof(p2_program) * rows},
+                                 {C.h_costs.p, only_shortlists ? C.sel_costs.p : C.costs.p, n_msg > 0 ? sizeof(double) * rows * nm : 0},
+                                 {C.h_pos.p, C.topk_pos.p, sizeof(long long) * topk_rows},
+                                 {only_graphs ? C.h_gctr.p : C.h_counters.p, only_graphs ? C.g_zero.p : C.counters.p,
+                                  topk_rows == 0 ? 0 : only_graphs ? graph_back : sizeof(DevCounters) * (size_t)n_queries}};
+        P2_HIP(launch_copies(back, 4, stream));
+    }
     P2_HIP(hipStreamSynchronize(stream));
     if (!topk_big.empty()) C.topk_control_clear = true;      // (only now have the kernels run to their end)
     if (topk_rows > 0) {
         const DevCounters* hc = static_cast<const DevCounters*>(C.h_counters.p);
+        const uint32_t* gn = reinterpret_cast<const uint32_t*>(static_cast<const char*>(C.h_gctr.p) + graph_nan);
         for (int i = 0; i < n_queries; ++i)
-            if (runs[i].topk > 0 && hc[i].nan_seen)
+            if (runs[i].topk > 0 && runs[i].n_valid > 0 && (only_graphs ? gn[i] : hc[i].nan_seen))
                 return fail(P2_EINVAL, "query " + std::to_string(i) + ": NaN cost (a message size that is not finite?)");
     }
     }  // store
@@ -1638,7 +1963,7 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
     if (g_prof.on) {
         P2_HIP(hipEventElapsedTime(&g_prof.last.eval_ms, g_prof.ev[0], g_prof.ev[1]));
         g_prof.last.post_ms = 0.0f;
-        if (store) P2_HIP(hipEventElapsedTime(&g_prof.last.post_ms, g_prof.ev[4], g_prof.ev[2]));
+        if (store) P2_HIP(hipEventElapsedTime(&g_prof.last.post_ms, direct ? g_prof.ev[1] : g_prof.ev[4], g_prof.ev[2]));
         P2_HIP(hipEventSynchronize(g_prof.ev[4]));      // (a call that only sizes its result has not waited since)
         P2_HIP(hipEventElapsedTime(&g_prof.last.front_ms, g_prof.ev[3], g_prof.ev[4]));
         float ms[SpanRec::kKinds] = {0.f, 0.f, 0.f, 0.f};
@@ -1681,8 +2006,8 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
             p2_stats& s = stats[i];
             s.candidates = r.plan.n_candidates; s.steps_executed = r.steps; s.member_visits = r.members;
             s.literal_reruns = r.shared ? (uint64_t)r.n_rerun_groups * (uint64_t)r.plan.alphabet : r.n_rerun;
-            s.steps_evaluated = r.shared ? r.evaluated : r.steps;
-            s.members_evaluated = r.shared ? r.evaluated_members : r.members;
+            s.steps_evaluated = r.shared || r.graph ? r.evaluated : r.steps;
+            s.members_evaluated = r.shared || r.graph ? r.evaluated_members : r.members;
             if (r.flat_counts && r.enum_id >= 0) {
                 unsigned long long per_alphabet = 0;
                 for (const Pattern& p : r.plan.patterns) per_alphabet += (unsigned long long)p.g * p.n_groups * r.plan.n_ops;
@@ -1690,15 +2015,22 @@ int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_
                 s.member_visits = enums[r.enum_id].flat_instr * per_alphabet;
             }
             s.valid = r.n_valid; s.group_size = r.plan.R; s.n_patterns = (int32_t)r.plan.patterns.size();
-            s.evaluated_with = r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
+            s.evaluated_with = r.graph ? (graphs[r.graph_id].leader != i ? graphs[r.graph_id].leader : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
             s.reserved0 = 0;
-            s.alphabet = r.plan.alphabet; s.engine = r.frontier ? P2_ENGINE_FRONTIER : r.shared ? P2_ENGINE_SHARED : r.regs ? P2_ENGINE_SMALL : r.engine;
+            s.alphabet = r.plan.alphabet; s.engine = r.frontier || r.graph_frontier ? P2_ENGINE_FRONTIER : r.shared ? P2_ENGINE_SHARED : r.regs ? P2_ENGINE_SMALL : r.engine;
         }
     }
     out_offset[n_queries] = w;
     g_prof.last.host_total_ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t_begin).count();
     if (!store && need > 0) return fail(P2_ENOSPC, "output buffer too small: " + std::to_string(need) + " rows needed");
     return P2_OK;
+}
+
+int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_bytes, int32_t n_msg,
+                  p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset, p2_stats* stats) {
+    int32_t rc = run_batch_on(queries, n_queries, msg_bytes, n_msg, out_prog, out_cost, cap, out_offset, stats, true);
+    if (rc == kWithoutGraphs) rc = run_batch_on(queries, n_queries, msg_bytes, n_msg, out_prog, out_cost, cap, out_offset, stats, false);
+    return rc;
 }
 
 }  // namespace

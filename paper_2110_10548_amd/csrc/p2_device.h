@@ -400,6 +400,69 @@ int front_rank_launches(uint32_t n);
 // The rows of n_jobs queries in one launch (jobs in device memory; max_valid = the largest n_valid among them).
 hipError_t launch_front_finish(const DevQuery* queries, const FrontFinish* jobs, uint32_t n_jobs, uint32_t max_valid, hipStream_t stream);
 
+// ---- state-graph evaluation (p2_graph.hip) ------------------------------------------------------
+// Why a graph could not be completed: its lists were too small (the host repeats the call with larger ones); a device
+// would need more pairs than are kept; a ReduceScatter would cut a block of chunks that is held as one row; two states
+// with one hash (the last three: the query is evaluated by the other engines).
+enum : uint32_t { kGraphFull = 1u, kGraphPairs = 2u, kGraphSplit = 4u, kGraphCollision = 8u };
+struct GraphCounters {             // zero on entry
+    uint32_t flags, n_planes;
+    unsigned long long found[P2_MAX_LEN + 1];  // by programs of so many instructions: edges (high half), new states (low half)
+    uint32_t n_edges, n_judged;                // edges on the way to a goal; states judged
+    uint32_t n_valid[P2_MAX_LEN + 1], n_total, pad;      // valid programs of so many instructions, of any number
+    unsigned long long n_prefixes[P2_MAX_LEN + 1];   // programs of so many instructions whose rules all hold, short of the goal
+    unsigned long long pad2;       // (whole 16-byte words)
+};
+constexpr int kGraphPatterns = 36;
+// One reduction structure: what its kernels read and where they write.  A state is plane | pairs << 28, its pairs in
+// consecutive planes [R] of (rows, mask).
+struct DevGraph {
+    uint32_t query;                // the query whose patterns describe the structure
+    int32_t R, rows_kept;          // devices of the group; rows held per device (each a block of k / rows_kept chunks)
+    int32_t n_pat, n_ops, alphabet, max_len, digit_words;
+    int32_t n_members;             // queries that share the structure
+    uint32_t op_mask, op_ranks;    // enabled ops; four bits per op: its rank among them
+    uint32_t split_check;          // rows stand for blocks of several chunks
+    uint32_t fused;                // how a program's step costs are added up (see k_graph_emit)
+    uint32_t cap_nodes, cap_planes, cap_found, cap_edges, table_mask;
+    unsigned long long all_rows, all_cols;
+    GraphCounters* ctr;
+    unsigned long long* table;     // hash of a state, 0: free
+    uint32_t* table_node;          // its node + 1
+    ulonglong2* planes;
+    uint32_t* node_state;
+    uint4* found;                  // every edge: node | digit << 23, slot of the child in the table (0x7fffff: the goal), child's
+                                   // state, 1 if it is the first with its hash
+    uint2* links;                  // ... node | digit << 23, node of the child
+    uint32_t* use_id; uint32_t* first_edge; uint32_t* use_ends;           // the nodes on the way to a goal, renumbered; [node][8]: programs
+                                                                          // of exactly r more instructions that end at the goal
+    uint32_t* edges; uint32_t* edge_state;                                // digit << 23 | target; the state it starts from
+    double* best;                  // [edge][member]: most loaded uplink, bytes (in chunks) over bandwidth
+    const int32_t* members;
+    // its patterns: log2 g | log2 s << 4; bit d set iff device d takes part
+    uint8_t shape[kGraphPatterns + 4];
+    unsigned long long part[kGraphPatterns];
+};
+struct GraphBlock { uint32_t graph, index, count, pad; };                 // block `index` of the `count` that work on the graph
+struct GraphRows {                 // rows of one query: blocks [first_block, next segment's first_block), 256 rows each
+    uint32_t first_block, query, graph, member, count, pad;
+    unsigned long long out_first;
+};
+// Structures of few states (graph_alone_holds; list: numbers of graphs), a block each: levels, counts and edges in one launch.
+bool graph_alone_holds(uint32_t nodes);
+hipError_t launch_graph_alone(const DevGraph* graphs, const uint32_t* list, unsigned n, int max_R, hipStream_t stream);
+// The others: a launch per level, then one for the counts and the edges (lds_bytes: for the counts of the largest).
+hipError_t launch_graph_level(const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int level, int max_len, hipStream_t stream);
+hipError_t launch_graph_finish(const DevGraph* graphs, const uint32_t* list, unsigned n, size_t lds_bytes, hipStream_t stream);
+// What the edges add to the bandwidth sums of every query (needs the bandwidth rows).
+hipError_t launch_graph_steps(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream);
+// The rows of the valid programs.  Without segs every query of the call (asked[0 .. n_queries)) is answered from a graph:
+// the rows come one query after the other in that order, as far as cap_rows, and ctrs_out (may be null, host memory) gets
+// the counts of all graphs.  sorted may be null.
+struct GraphQuery { uint32_t graph, member; };           // graph ~0: a query without candidates
+hipError_t launch_graph_emit(const DevQuery* queries, const DevGraph* graphs, const GraphCounters* ctrs, const GraphQuery* asked, int n_queries,
+                             const GraphRows* segs, int n_segs, unsigned n_blocks, unsigned long long cap_rows, unsigned long long* sorted,
+                             p2_program* progs, double* costs, void* ctrs_out, int n_graphs, hipStream_t stream);
 // One selection of launch_topk_jobs: the k best of (cost[i * stride], index[i]), i < n, ties by index;
 // positions go to out_pos[min(k, n)], nan_flag is set to 1 when a cost is NaN.  All device pointers.
 struct DevTopkJob {
@@ -427,9 +490,10 @@ hipError_t launch_gather_rows(const DevGatherSeg* segs, unsigned n_segs, const p
 // memory to pinned, device-accessible host memory.  Used instead of hipMemcpyAsync, whose queueing of a
 // device-to-host copy was seen to take 0.1 ms longer in some processes (never in others).
 hipError_t launch_copy_out(void* dst_host, const void* src_dev, size_t bytes, hipStream_t stream);
-// Up to three of them in one launch (bytes may be 0).
-hipError_t launch_copy_out3(void* dst0, const void* src0, size_t bytes0, void* dst1, const void* src1, size_t bytes1,
-                            void* dst2, const void* src2, size_t bytes2, hipStream_t stream);
+// Up to four copies between device memory and pinned host memory, in either direction, or fills with zero (src null), in one
+// launch (bytes may be 0; rounded up to 16 like above).
+struct CopyPart { void* dst; const void* src; size_t bytes; };
+hipError_t launch_copies(const CopyPart* parts, int n, hipStream_t stream);
 
 // Top-k of (cost[i * stride], index[i]) over i < n: positions into out_pos[min(k, n)].
 // scratch: device buffer of topk_scratch_bytes(n, k) bytes; control: topk_control_bytes() of device memory that are

@@ -855,14 +855,20 @@ __global__ __launch_bounds__(256) void k_copy_out(uint4* __restrict__ dst, const
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
 
-// Up to three such copies in one launch (a call's programs, costs and shortlist positions).
 struct CopyOut { uint4* dst; const uint4* src; size_t n16; };
-__global__ __launch_bounds__(256) void k_copy_out3(CopyOut a, CopyOut b, CopyOut c) {
-    const size_t ab = a.n16 + b.n16, total = ab + c.n16;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        if (i < a.n16) a.dst[i] = a.src[i];
-        else if (i < ab) b.dst[i - a.n16] = b.src[i - a.n16];
-        else c.dst[i - ab] = c.src[i - ab];
+// Up to four copies between device memory and pinned host memory, or fills with zero, in one launch: a launch of its own
+// for each would cost a small call several microseconds apiece.
+constexpr int kCopyParts = 4;
+struct CopyArgs { CopyOut part[kCopyParts]; };
+__global__ __launch_bounds__(256) void k_copies(CopyArgs a) {
+    size_t before = 0;
+#pragma unroll
+    for (int p = 0; p < kCopyParts; ++p) {
+        // (a part's first word falls to the thread that follows the last one of the part before)
+        const size_t step = (size_t)gridDim.x * 256, me = (size_t)blockIdx.x * 256 + threadIdx.x;
+        for (size_t i = (me + step - before % step) % step; i < a.part[p].n16; i += step)
+            a.part[p].dst[i] = a.part[p].src ? a.part[p].src[i] : make_uint4(0u, 0u, 0u, 0u);
+        before += a.part[p].n16;
     }
 }
 
@@ -878,16 +884,19 @@ hipError_t launch_copy_out(void* dst_host, const void* src_dev, size_t bytes, hi
     return hipGetLastError();
 }
 
-hipError_t launch_copy_out3(void* dst0, const void* src0, size_t bytes0, void* dst1, const void* src1, size_t bytes1,
-                            void* dst2, const void* src2, size_t bytes2, hipStream_t stream) {
-    const CopyOut a{static_cast<uint4*>(dst0), static_cast<const uint4*>(src0), (bytes0 + 15) / 16};
-    const CopyOut b{static_cast<uint4*>(dst1), static_cast<const uint4*>(src1), (bytes1 + 15) / 16};
-    const CopyOut c{static_cast<uint4*>(dst2), static_cast<const uint4*>(src2), (bytes2 + 15) / 16};
-    const size_t n16 = a.n16 + b.n16 + c.n16;
+hipError_t launch_copies(const CopyPart* what, int n, hipStream_t stream) {
+    CopyArgs a;
+    size_t n16 = 0;
+    for (int i = 0; i < kCopyParts; ++i) {
+        const bool there = i < n && what[i].bytes > 0;
+        a.part[i] = CopyOut{there ? static_cast<uint4*>(what[i].dst) : nullptr, there ? static_cast<const uint4*>(what[i].src) : nullptr,
+                            there ? (what[i].bytes + 15) / 16 : 0};
+        n16 += a.part[i].n16;
+    }
+    if (n > kCopyParts) return hipErrorInvalidValue;
     if (n16 == 0) return hipSuccess;
     const size_t want = (n16 + 255) / 256;
-    const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
-    hipLaunchKernelGGL(k_copy_out3, dim3(blocks), dim3(256), 0, stream, a, b, c);
+    hipLaunchKernelGGL(k_copies, dim3((unsigned)(want < 2048 ? want : 2048)), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,94 @@
+"""The state graph that engine AUTO answers groups of up to 64 devices with power-of-two patterns from, beside the engines
+whose place it takes: the walk of every candidate (compact) and the enumeration by size (frontier)."""
+import numpy as np
+import pytest
+
+
+def _query(card, max_len, **more):
+    n = int(np.prod(card))
+    L = len(card)
+    return dict(dict(card=card, axes=[n], placement=[card], reduce_axes=[0], max_len=max_len,
+                     bw=[12.7e9, 30e9, 50.3e9, 151e9, 180e9, 307e9][:L], alpha=[2.3e-5, 1.5e-5, 1.1e-5, 5.7e-6, 3.1e-6, 1.9e-6][:L]), **more)
+
+
+MSG = [2.0 ** 20, 3.0e8]
+COUNTS = ("candidates", "steps_executed", "member_visits", "valid")
+
+# teams of 2 to 64 lanes; one block alone (up to two levels) and launches per level; size limits from 1; rows that are
+# blocks of chunks (a multiple of R), chunks that are not, a single one; alphabets that end inside a word and run over three
+WALKED = [([2], 1, {}), ([2], 4, {}), ([64], 3, {}), ([2, 2], 5, {}), ([4, 16], 3, {}), ([32, 2], 3, dict(n_chunks=128)), ([8, 8], 2, dict(n_chunks=3)),
+          ([2, 4], 4, dict(n_chunks=12)), ([2, 4], 3, dict(n_chunks=1)), ([4, 4], 4, dict(op_mask=0b10101)), ([4, 4], 4, dict(form_mask=3)),
+          ([2, 2, 2], 4, {}), ([4, 2, 8], 2, dict(n_chunks=8)), ([2, 4, 8], 3, dict(algo=1)), ([2, 2, 4], 4, dict(op_mask=0b00111, n_chunks=48)),
+          ([2, 2, 2, 2], 3, dict(form_mask=5)), ([2, 2, 2, 2, 2], 2, {}), ([2, 2, 2, 2, 2, 2], 2, dict(n_chunks=7)), ([4, 4, 4], 1, {})]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,more", WALKED)
+def test_graph_matches_the_walk(card, max_len, more):
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, **more)
+    auto, short, shared = B.p2_synthesize_batch([q, dict(q, topk=5), dict(q, bw=q["bw"][::-1], algo=1)], MSG)
+    walk, walk_b = B.p2_synthesize_batch([dict(q, engine=2), dict(q, engine=2, bw=q["bw"][::-1], algo=1)], MSG)
+    alone = B.p2_synthesize_batch([q], MSG)[0]           # (rows written straight to the host)
+    for a, w in ((auto, walk), (alone, walk), (shared, walk_b)):
+        assert a["stats"]["engine"] == 5 and np.array_equal(a["programs"], w["programs"])
+        assert np.array_equal(a["cost"], w["cost"])      # (to the last bit: shortlists with ties stay as they were)
+        for key in COUNTS:
+            assert a["stats"][key] == w["stats"][key], key
+        assert a["stats"]["steps_evaluated"] <= a["stats"]["steps_executed"]
+    kk = min(5, len(walk["programs"]))
+    for m in range(len(MSG)):
+        want = np.lexsort((walk["programs"]["index"], walk["cost"][:, m]))[:kk]
+        assert np.array_equal(short["programs"]["index"][m * kk:(m + 1) * kk], walk["programs"]["index"][want])
+    nothing = B.p2_synthesize_batch([q], [])[0]          # (no message size: validity alone)
+    assert np.array_equal(nothing["programs"], walk["programs"])
+
+
+# too many candidates to walk; three and four pairs on a device; more states than there is room for at first, more rows
+# than the call made room for (six levels)
+ENUMERATED = [([2, 2, 2], 7, {}), ([4, 4, 4], 6, {}), ([2, 2, 2, 2], 6, {}), ([2, 2, 2, 4], 5, dict(n_chunks=24)), ([2, 2, 2, 2, 2], 5, {}),
+              ([2, 2, 2, 2, 2, 2], 4, {})]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,more", ENUMERATED)
+def test_graph_matches_the_enumeration(card, max_len, more):
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, **more)
+    a = B.p2_synthesize_batch([q], MSG)[0]
+    b = B.p2_synthesize_batch([dict(q, engine=3)], MSG)[0]
+    assert np.array_equal(a["programs"], b["programs"]) and len(a["programs"]) > 1000
+    assert np.allclose(a["cost"], b["cost"], rtol=1e-14, atol=0.0)       # (a dozen additions in 64 bits)
+    if a["stats"]["engine"] == 3:
+        assert np.array_equal(a["cost"], b["cost"])
+        # (one step per valid prefix and instruction; the enumeration also counts what it applies again to rebuild a prefix)
+        assert a["stats"]["valid"] == b["stats"]["valid"] and 0 < a["stats"]["steps_executed"] <= b["stats"]["steps_executed"]
+
+
+@pytest.mark.gpu
+def test_graphs_beside_other_engines():
+    """Queries answered from graphs, walked and enumerated in one batch, each as alone."""
+    from paper_2110_10548_amd import binding as B
+    queries = [_query([2, 3], 3), _query([4, 4], 4), _query([80], 3, topk=4), _query([2, 4, 4], 3, topk=3), _query([4, 4], 4, engine=5),
+               _query([2, 2], 3, hierarchy=1), _query([2, 4, 4], 3), _query([4, 4], 4, n_chunks=32)]
+    single = dict(_query([4], 2), axes=[2, 2], placement=[[2], [2]], card=[4])
+    queries += [dict(single, reduce_axes=[0]), dict(single, axes=[4, 1], placement=[[4], [1]], reduce_axes=[1])]      # (over one device: nothing)
+    together = B.p2_synthesize_batch(queries, MSG)
+    for q, r in zip(queries, together):
+        o = B.p2_synthesize_batch([q], MSG)[0]
+        assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"])
+        for key in COUNTS:
+            assert r["stats"][key] == o["stats"][key], key
+
+
+@pytest.mark.gpu
+def test_lists_too_large_for_the_graphs():
+    """A batch whose graphs would take more room than they may is evaluated by the other engines."""
+    from paper_2110_10548_amd import binding as B
+    q = _query([2, 2, 4, 4], 6, op_mask=1, topk=3)
+    one = B.p2_synthesize_batch([q], MSG)[0]
+    many = B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY)] * 900, MSG)
+    for r in (many[0], many[450], many[-1]):
+        assert np.array_equal(r["programs"], one["programs"]) and np.array_equal(r["cost"], one["cost"])
+        for key in COUNTS:
+            assert r["stats"][key] == one["stats"][key], key
