@@ -159,6 +159,7 @@ struct Ctx {
     HostBuf h_gather;
     DevBuf g_zero, g_mem, g_rows;                           // state-graph engine: what starts from zero, the lists, whose rows are written
     HostBuf h_gctr, h_grows;
+    std::vector<DevBuf> g_large;                            // ... the states of every large group
     DevBuf f_finish;                                        // frontier engine: what every query's rows are written from
     HostBuf h_finish;
     DevBuf f_rank, f_rank_runs, f_share;                                 // frontier engine: ranks of the valid programs, queries of the enumerations
@@ -175,6 +176,7 @@ struct Ctx {
         return e;
     }
     hipEvent_t front_go = nullptr;                          // the call's stream has reached the enumerations
+    hipEvent_t slot_done[kFrontSlots] = {};                 // a slot's stream has got through what it was given
     HostBuf h_rows, h_rows_hdr;
     hipStream_t copy_stream = nullptr;      // uploads that overlap with the kernels of the call's stream
     hipEvent_t copy_done = nullptr;
@@ -253,7 +255,7 @@ struct Prof {
     void release();
     bool on = false;
     bool kernels_only = false;      // p2_set_profiling(2): of the frontier engine's launches, only classification and children
-    hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};     // evaluation begin / end, post end, frontier begin / end
+    hipEvent_t ev[6] = {};          // evaluation begin / end, post end, frontier begin / end, post begin
     p2_profile last = {};
 };
 thread_local Prof g_prof;
@@ -267,7 +269,7 @@ void Ctx::release() {
     DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_control, &topk_pos,
                      &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink, &g_zero, &g_mem, &g_rows};
     for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
-    for (auto* v : {&f_evalid, &f_egsums}) {
+    for (auto* v : {&f_evalid, &f_egsums, &g_large}) {
         for (DevBuf& b : *v) if (b.p) (void)hipFree(b.p);
         v->clear();
     }
@@ -276,6 +278,7 @@ void Ctx::release() {
     HostBuf* host[] = {&h_rows, &h_rows_hdr, &h_blob, &h_counters, &h_progs, &h_costs, &h_pos, &h_post, &h_topk_jobs, &h_topk_nan, &h_fshare, &h_gather, &h_finish, &h_gctr, &h_grows};
     for (HostBuf* b : host) { if (b->p) (void)hipHostFree(b->p); b->p = nullptr; b->cap = 0; }
     if (front_go) { (void)hipEventDestroy(front_go); front_go = nullptr; }
+    for (hipEvent_t& ev : slot_done) { if (ev) (void)hipEventDestroy(ev); ev = nullptr; }
     if (copy_done) { (void)hipEventDestroy(copy_done); copy_done = nullptr; }
     if (copy_stream) { (void)hipStreamDestroy(copy_stream); copy_stream = nullptr; }
 }
@@ -354,6 +357,17 @@ bool graph_applies(const p2::Plan& pl) {
     for (const p2::Pattern& p : pl.patterns)
         if (p2::reg_shape_of(p.g, p.s, p.master, 6) < 0) return false;
     return true;
+}
+// What it takes over from the frontier engine under AUTO: the same size limits, any patterns; the states are worked on by
+// the frontier's kernels, two pairs a device, which must fit in a compute unit's LDS.  The enumeration waits for the host
+// after every level and keeps every program's sums; the graph keeps neither (one query of [3 4 6] 537 us by enumeration,
+// 373 by the graph; [2 4 8 8], 512 devices, 6 814 and 5 025; 35 + 105 queries of [2 4 8 8] 39.5 ms and 20.1).  Past the
+// size limits the counts of a graph no longer fit in LDS: the enumeration goes on there.
+bool large_graph_applies(const p2::Plan& pl) {
+    if (pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.frontier_pairs != P2_FRONTIER_PAIRS_AUTO || pl.alphabet == 0 || pl.R < 2) return false;
+    const size_t n_pat = pl.patterns.size();
+    if (n_pat > (size_t)p2::kGraphPatterns || pl.max_len > (n_pat <= 9 ? 7 : n_pat <= 16 ? 6 : n_pat <= 25 ? 5 : 4)) return false;
+    return p2::frontier_max_pairs(pl.R, graph_rows(pl)) == 2;
 }
 // Room for the states of a structure (see above), first guess; a structure that has more is met with four times as much.
 uint32_t graph_room(const p2::Plan& pl) {
@@ -436,6 +450,8 @@ struct QueryRun {
     bool auto_groups = false;             // its handed-over groups are picked up by the device-driven literal launch
     bool graph = false;                   // evaluated by the state-graph engine (AUTO), reported as the engine it stands in for
     bool graph_frontier = false;          // ... the frontier engine, whose stats count the prefixes' instructions
+    bool graph_flat = false;              // ... (or, where it stands in for a walk, the walk's)
+    bool graph_large = false;             // its states are worked on by the frontier's kernels
     int graph_id = -1, graph_pos = 0;     // ... its graph, and its place among the graph's queries
     bool wave_cost = false;               // valid programs costed by the wavefront-per-program kernel
     int enum_id = -1, share_pos = 0;      // frontier: its enumeration, and its place among the enumeration's queries
@@ -551,16 +567,42 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             runs[i].frontier = runs[i].flat_counts = false;
         }
     }
+    // (once it is settled which groups are enumerated: see below)
+    auto take_large_graphs = [&]() {
+        for (int i = 0; i < n_queries; ++i) {
+            QueryRun& r = runs[i];
+            const int want = queries[i].opt ? queries[i].opt->engine : P2_ENGINE_AUTO;
+            if (!graphs_allowed || want != P2_ENGINE_AUTO || !r.frontier || r.graph || !large_graph_applies(r.plan)) continue;
+            r.graph = r.graph_large = true;
+            r.graph_frontier = true; r.graph_flat = r.flat_counts;
+            r.frontier = r.flat_counts = false;
+        }
+    };
+    {
+        std::vector<const Plan*> large;              // groups of more than 64 devices that AUTO would enumerate, one of each structure
+        for (const QueryRun& r : runs) {
+            if (!r.flat_counts || r.plan.R <= 64) continue;
+            bool seen = false;
+            for (size_t t = 0; t < large.size() && !seen && share_validity; ++t) seen = same_structure(*large[t], r.plan);
+            if (!seen) large.push_back(&r.plan);
+        }
+        if (walks_together(large))
+            for (QueryRun& r : runs)
+                if (r.flat_counts && r.plan.R > 64) r.frontier = r.flat_counts = false;
+    }
+
+    take_large_graphs();
     // queries of one reduction structure are answered from one graph
-    struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t cap_nodes = 0, cap_planes = 0, n_blocks = 0; bool small = false;
-                   size_t off_members = 0, at_table = 0, at_mem = 0; };
+    struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t n_blocks = 0; bool small = false, large = false;
+                   size_t off_members = 0, off_query = 0; };
     std::vector<Graph> graphs;
     for (int i = 0; i < n_queries; ++i) {
         QueryRun& r = runs[i];
         if (!r.graph) continue;
         for (size_t g = 0; g < graphs.size() && r.graph_id < 0 && share_validity; ++g)
-            if (runs[graphs[g].leader].graph_frontier == r.graph_frontier && same_graph(runs[graphs[g].leader].plan, r.plan)) r.graph_id = (int)g;
-        if (r.graph_id < 0) { r.graph_id = (int)graphs.size(); graphs.emplace_back(); graphs.back().leader = i; }
+            if (runs[graphs[g].leader].graph_frontier == r.graph_frontier && runs[graphs[g].leader].graph_flat == r.graph_flat &&
+                runs[graphs[g].leader].graph_large == r.graph_large && same_graph(runs[graphs[g].leader].plan, r.plan)) r.graph_id = (int)g;
+        if (r.graph_id < 0) { r.graph_id = (int)graphs.size(); graphs.emplace_back(); graphs.back().leader = i; graphs.back().large = r.graph_large; }
         r.graph_pos = (int)graphs[r.graph_id].members.size();
         graphs[r.graph_id].members.push_back(i);
     }
@@ -576,18 +618,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             if (r.graph) { const size_t n = graph_rows_guess(r.plan); rows_guess += n; emit_blocks += (n + 255) / 256; }
     bool direct = only_graphs && !any_topk && cap > 0;
 
-    {
-        std::vector<const Plan*> large;              // groups of more than 64 devices that AUTO would enumerate, one of each structure
-        for (const QueryRun& r : runs) {
-            if (!r.flat_counts || r.plan.R <= 64) continue;
-            bool seen = false;
-            for (size_t t = 0; t < large.size() && !seen && share_validity; ++t) seen = same_structure(*large[t], r.plan);
-            if (!seen) large.push_back(&r.plan);
-        }
-        if (walks_together(large))
-            for (QueryRun& r : runs)
-                if (r.flat_counts && r.plan.R > 64) r.frontier = r.flat_counts = false;
-    }
 
     // Validity depends on the reduction group, the chunks, the patterns and the alphabet only (not on the
     // links, nor on where the placement puts the group in the system): a query that equals an earlier one of
@@ -733,7 +763,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     if (!graphs.empty()) {
         uint32_t n_by_size[3] = {0, 0, 0};                // up to two levels, three, more
         auto size_of = [&](const Graph& G) { const size_t n = runs[G.leader].plan.patterns.size(); return n <= 4 ? 0 : n <= 9 ? 1 : 2; };
-        for (Graph& G : graphs) ++n_by_size[size_of(G)];
+        for (Graph& G : graphs) if (!G.large) ++n_by_size[size_of(G)];
         const bool alone = n_by_size[1] + n_by_size[2] == 0;      // (beside larger ones the small ones ride along in their launches)
         for (size_t g = 0; g < graphs.size(); ++g) {
             Graph& G = graphs[g];
@@ -743,14 +773,18 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             G.small = sz == 0 && alone && graph_alone_holds(graph_room(runs[G.leader].plan));
             const uint32_t share = 2048u / std::max(1u, n_by_size[sz]);
             G.n_blocks = G.small ? 1u : sz == 0 ? 12u : sz == 1 ? std::min(std::max(share, 16u), 160u) : std::min(std::max(share, 64u), 768u);
-            if (G.small) gsmall.push_back((uint32_t)g);
+            if (G.large) {
+                glarge.push_back((uint32_t)g);
+                G.off_query = off;
+                off += align_up(sizeof(DevQuery), 256);
+            } else if (G.small) gsmall.push_back((uint32_t)g);
             else {
                 glarge.push_back((uint32_t)g);
                 graph_levels = std::max(graph_levels, runs[G.leader].plan.max_len);
                 for (uint32_t b = 0; b < G.n_blocks; ++b) glevel.push_back(GraphBlock{(uint32_t)g, b, G.n_blocks, 0u});
             }
             // (four edges a block at a time; two levels have some 70 edges on the way to a goal, three 900, four 6 300)
-            const uint32_t nb = sz == 0 ? 18u : std::min(std::max(share, 16u), sz == 1 ? 160u : 512u);
+            const uint32_t nb = G.large ? 512u : sz == 0 ? 18u : std::min(std::max(share, 16u), sz == 1 ? 160u : 512u);
             for (uint32_t b = 0; n_msg > 0 && b < nb; ++b) gsteps.push_back(GraphBlock{(uint32_t)g, b, nb, 0u});
             G.off_members = off;
             off += align_up(sizeof(int32_t) * G.members.size(), 64);
@@ -777,6 +811,22 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         P2_HIP(hipStreamCreateWithFlags(&C.copy_stream, hipStreamNonBlocking));
         P2_HIP(hipEventCreateWithFlags(&C.copy_done, hipEventDisableTiming));
         P2_HIP(hipEventCreateWithFlags(&C.front_go, hipEventDisableTiming));
+    }
+    size_t n_large = 0;
+    for (const Graph& G : graphs) n_large += G.large ? 1 : 0;
+    int large_slots = 1;
+    if (n_large > 1) {
+        bool one_at_a_time = false;
+        for (int i = 0; i < n_queries; ++i)
+            one_at_a_time |= queries[i].opt && (queries[i].opt->flags & P2_FLAG_ONE_ENUMERATION_AT_A_TIME) != 0u;
+        if (!one_at_a_time) large_slots = (int)std::min<size_t>(kFrontSlots, n_large);
+        if (large_slots > 1) {
+            if (!C.slots[1].stream) {                    // (first time: the streams are chosen by timing, on a quiet device)
+                P2_HIP(hipStreamSynchronize(stream));
+                P2_HIP(hipStreamSynchronize(C.copy_stream));
+            }
+            P2_HIP(C.open_slot_streams(large_slots));
+        }
     }
     auto build_and_upload_rows = [&]() -> int32_t {
         if (rows_ready) return P2_OK;
@@ -833,7 +883,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             H.entries = reinterpret_cast<const uint32_t*>(dr + r.off_entries);
         });
         rows_ready = true;
-        if (only_graphs) {
+        if (only_graphs && large_slots == 1) {           // (else the call's stream has the slots to wait for)
             const CopyPart up[2] = {{C.rows.p, C.h_rows.p, bytes}, {C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * (size_t)n_queries}};
             P2_HIP(launch_copies(up, 2, stream));
             return P2_OK;
@@ -902,6 +952,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     auto mask_class = [](int R) { return R <= 32 ? 1 : R <= 64 ? 2 : R <= 128 ? 4 : R <= 256 ? 8 : 16; };
     char* hb = static_cast<char*>(C.h_blob.p);
     char* db = static_cast<char*>(C.blob.p);
+    // what the frontier's kernels build a large group's graph in
+    struct LargeAt {
+        FrontCounters* ctr; FrontMarks* marks; unsigned long long* table[2]; uint32_t table_size[2];
+        uint32_t* states[2]; unsigned long long* hash[2]; uint32_t* rep[2]; uint32_t* pos[2]; uint32_t* reps[2]; uint32_t* walk[2];
+        uint8_t* codes[2]; unsigned long long* row_counts[2]; uint8_t* unknown[2];
+        FrontSurvivor* edges; FrontEntry* literal; uint32_t* literal_parent; uint32_t* rest; void* literal_scratch;
+        uint32_t cap[2], cap_literal;
+    };
+    std::vector<LargeAt> large_at;
     // the lists of the state graphs, one graph after the other (grown and repeated like the others)
     uint32_t graph_scale = 1;
     size_t graph_zero = 0;
@@ -913,6 +972,9 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         auto take = [](size_t& at, size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
         struct Place { size_t table, table_node, planes, state, found, links, use_id, first, use_ends, edges, edge_state, best; };
         std::vector<Place> places(n_graphs);
+        large_at.assign(n_graphs, LargeAt{});
+        if (C.g_large.size() < n_graphs) C.g_large.resize(n_graphs);
+        size_t states_bytes = 0;
         for (size_t g = 0; g < n_graphs; ++g) {
             const Graph& G = graphs[g];
             const Plan& pl = runs[G.leader].plan;
@@ -925,16 +987,44 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.n_members = (int)G.members.size();
             for (int o = 0; o < pl.n_ops; ++o) { D.op_mask |= 1u << pl.ops[o]; D.op_ranks |= (uint32_t)o << (4 * pl.ops[o]); }
             for (int32_t m : G.members) D.split_check |= runs[m].plan.k != D.rows_kept ? 1u : 0u;
-            D.fused = runs[G.leader].graph_frontier ? 0u : 1u;
+            D.fused = runs[G.leader].graph_frontier && !runs[G.leader].graph_flat ? 0u : 1u;
             D.cap_nodes = graph_room(pl) * graph_scale;
-            // (twice as many children as nodes; a wavefront may leave the rest of what it reserved at every level)
-            D.cap_planes = D.cap_nodes * 2 + 16u * 4u * G.n_blocks * (uint32_t)pl.max_len / 2u + 1024u;
+            // (some twice as many children as nodes; a wavefront may leave the rest of what it reserved at every level)
+            D.cap_planes = D.cap_nodes * 2 + graph_planes_left(G.n_blocks, pl.max_len) + 256u;
             D.cap_found = D.cap_nodes * 3;
             D.cap_edges = D.cap_nodes + 256;
             uint32_t slots = 64;
             while (slots < 2 * D.cap_nodes) slots *= 2;
             D.table_mask = slots - 1;
-            for (size_t p = 0; p < pl.patterns.size(); ++p) {
+            if (G.large) {
+                D.cap_planes = 0; D.table_mask = 0;
+                LargeAt& L = large_at[g];
+                L.cap[0] = D.cap_nodes * 2 + 64; L.cap[1] = D.cap_nodes / 2 + 64; L.cap_literal = D.cap_nodes / 8 + 1024;
+                const int kk = D.rows_kept;
+                const size_t plane = frontier_state_words(pl.R, kk) * 4, codes = front_code_stride(pl.alphabet);
+                D.wq = (int)(plane / 16 / (size_t)pl.R); D.qk = (literal_mask_words(kk) + 3) / 4;
+                // (offsets first, pointers once the buffers are there)
+                auto at = [](size_t v) { return reinterpret_cast<char*>(v); };
+                L.ctr = (FrontCounters*)at(take(zero, sizeof(FrontCounters)));
+                L.marks = (FrontMarks*)at(take(mem, sizeof(FrontMarks)));
+                for (int li = 0; li < 2; ++li) {
+                    L.table_size[li] = 1024;
+                    while (L.table_size[li] < 2 * L.cap[li]) L.table_size[li] *= 2;
+                    L.table[li] = (unsigned long long*)at(take(zero, sizeof(unsigned long long) * L.table_size[li]));
+                    L.hash[li] = (unsigned long long*)at(take(mem, sizeof(unsigned long long) * L.cap[li]));
+                    for (uint32_t** p : {&L.rep[li], &L.pos[li], &L.reps[li], &L.walk[li]}) *p = (uint32_t*)at(take(mem, sizeof(uint32_t) * L.cap[li]));
+                    L.codes[li] = (uint8_t*)at(take(mem, codes * L.cap[li]));
+                    L.row_counts[li] = (unsigned long long*)at(take(mem, sizeof(unsigned long long) * L.cap[li]));
+                    L.unknown[li] = (uint8_t*)at(take(mem, L.cap[li]));
+                }
+                L.edges = (FrontSurvivor*)at(take(mem, sizeof(FrontSurvivor) * D.cap_found));
+                L.literal = (FrontEntry*)at(take(mem, sizeof(FrontEntry) * L.cap_literal));
+                L.literal_parent = (uint32_t*)at(take(mem, sizeof(uint32_t) * L.cap_literal));
+                L.rest = (uint32_t*)at(take(mem, sizeof(uint32_t) * L.cap_literal));
+                L.literal_scratch = at(take(mem, pl.max_len >= 6 ? front_literal_goals_scratch_bytes(pl.R, kk, L.cap_literal) : 256));
+                states_bytes += ((size_t)L.cap[0] + 2 * (size_t)L.cap[1]) * plane;
+            }
+            for (size_t p = 0; p < pl.patterns.size() && !G.large; ++p) {
                 const Pattern& pt = pl.patterns[p];
                 D.shape[p] = (uint8_t)reg_shape_of(pt.g, pt.s, 0, 6);
                 for (int d = 0; d < pl.R; ++d)
@@ -942,12 +1032,13 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
             D.all_rows = D.rows_kept >= 64 ? ~0ull : (1ull << D.rows_kept) - 1ull;
             D.all_cols = pl.R >= 64 ? ~0ull : (1ull << pl.R) - 1ull;
+            if (G.large) { slots = 0; D.all_rows = D.all_cols = 0ull; }
             Place& P = places[g];
             P.table = take(zero, sizeof(unsigned long long) * slots);
             P.table_node = take(zero, sizeof(uint32_t) * slots);
             P.planes = take(mem, sizeof(ulonglong2) * (size_t)D.cap_planes * pl.R);
             P.state = take(mem, sizeof(uint32_t) * D.cap_nodes);
-            P.found = take(mem, sizeof(uint4) * D.cap_found);
+            P.found = take(mem, G.large ? 0 : sizeof(uint4) * D.cap_found);
             P.links = take(mem, sizeof(uint2) * D.cap_found);
             P.use_id = take(mem, sizeof(uint32_t) * D.cap_nodes);
             P.first = take(mem, sizeof(uint32_t) * ((size_t)D.cap_nodes + 1));
@@ -956,8 +1047,14 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
             P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
         }
-        if (mem + zero > kGraphBytesMax) return kWithoutGraphs;
-        if (C.g_zero.ensure(zero) != hipSuccess || C.g_mem.ensure(mem) != hipSuccess) {      // (the other engines need less)
+        if (mem + zero + states_bytes > kGraphBytesMax) return kWithoutGraphs;
+        bool room = C.g_zero.ensure(zero) == hipSuccess && C.g_mem.ensure(mem) == hipSuccess;
+        for (size_t g = 0; g < n_graphs && room; ++g) {
+            if (!graphs[g].large) continue;
+            const Plan& pl = runs[graphs[g].leader].plan;
+            room = C.g_large[g].ensure(((size_t)large_at[g].cap[0] + 2 * (size_t)large_at[g].cap[1]) * frontier_state_words(pl.R, graph_rows(pl)) * 4) == hipSuccess;
+        }
+        if (!room) {                                     // (the other engines need less)
             (void)hipGetLastError();
             return kWithoutGraphs;
         }
@@ -977,7 +1074,97 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.edges = reinterpret_cast<uint32_t*>(m + P.edges); D.edge_state = reinterpret_cast<uint32_t*>(m + P.edge_state);
             D.best = reinterpret_cast<double*>(m + P.best);
             D.members = reinterpret_cast<const int32_t*>(static_cast<char*>(C.blob.p) + graphs[g].off_members);
+            if (!graphs[g].large) continue;
+            LargeAt& L = large_at[g];
+            auto shift = [](auto*& p, char* base) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + reinterpret_cast<size_t>(p)); };
+            shift(L.ctr, z); shift(L.marks, m);
+            const Plan& pl = runs[graphs[g].leader].plan;
+            const size_t plane_words = frontier_state_words(pl.R, D.rows_kept);
+            L.states[0] = static_cast<uint32_t*>(C.g_large[g].p);
+            L.states[1] = L.states[0] + (size_t)L.cap[0] * plane_words;
+            for (int li = 0; li < 2; ++li) {
+                shift(L.table[li], z); shift(L.hash[li], m);
+                shift(L.rep[li], m); shift(L.pos[li], m); shift(L.reps[li], m); shift(L.walk[li], m);
+                shift(L.codes[li], m); shift(L.row_counts[li], m); shift(L.unknown[li], m);
+                D.large[li] = reinterpret_cast<const uint4*>(L.states[li]);
+            }
+            shift(L.edges, m); shift(L.literal, m); shift(L.literal_parent, m); shift(L.rest, m);
+            L.literal_scratch = m + reinterpret_cast<size_t>(L.literal_scratch);
         }
+        return P2_OK;
+    };
+    // The graph of a large group: its kernels queued level by level, with nothing to wait for.  (More blocks than a level has
+    // states end at once; a level's states are some 45, 450, 2 000, 5 400, 8 900 with four levels.)
+    auto queue_large = [&](size_t g, hipStream_t on, SpanRec& spans) -> int32_t {
+        const Graph& G = graphs[g];
+        const Plan& pl = runs[G.leader].plan;
+        const LargeAt& L = large_at[g];
+        const DevGraph& D = reinterpret_cast<const DevGraph*>(static_cast<char*>(C.h_blob.p) + off_graphs)[g];
+        const DevQuery* const dq = reinterpret_cast<const DevQuery*>(static_cast<char*>(C.blob.p) + G.off_query);
+        const int kk = D.rows_kept, M = pl.max_len;
+        const size_t sw = frontier_state_words(pl.R, kk);
+        const bool judge_literal = M >= 6;               // (with fewer instructions no child needs a third pair; one that did would be reported)
+        P2_HIP(launch_front_init(dq, 0u, pl.R, kk, L.literal, L.states[0], nullptr, L.rest, 0, on));
+        P2_HIP(launch_front_root(L.ctr, L.marks, L.rep[0], L.pos[0], L.reps[0], on));
+        for (int l = 0; l < M; ++l) {
+            const bool last = l + 1 == M;
+            const int lists = l < 2 ? 1 : 2;             // (the first AllGather that can leave two pairs is the second instruction)
+            const uint32_t most = l == 0 ? 1u : l == 1 ? 160u : l == 2 ? 1024u : 1u << 20;      // (blocks: a bound on the states, for the grid alone)
+            if (l > 0) P2_HIP(launch_front_mark(L.ctr, L.marks, l + 1, on));
+            const uint32_t* list[2]; const uint32_t* n_list[2]; const uint32_t* from[2];
+            for (int li = 0; li < 2; ++li) { list[li] = L.reps[li]; n_list[li] = &L.marks->rep[li][l + 1]; from[li] = &L.marks->rep[li][l]; }
+            if (last && judge_literal) {
+                P2_HIP(spans.begin(SpanRec::kLiteral, on));
+                P2_HIP(launch_front_literal_goals(dq, pl.R, kk, L.literal, L.literal_parent, L.cap_literal, &L.ctr->next_literal, l, L.states[0], L.states[1],
+                                                  L.literal_scratch, nullptr, 0, L.ctr, L.rest, on));
+                P2_HIP(spans.end(on));
+            }
+            if (last) {
+                P2_HIP(spans.begin(SpanRec::kGroup, on));
+                for (int li = 0; li < lists; ++li)
+                    P2_HIP(launch_front_goal_filter(dq, pl.R, kk, L.states[li], std::min(most, L.cap[li]), list[li], n_list[li], from[li], li + 1, L.codes[li],
+                                                    L.row_counts[li], L.unknown[li], L.walk[li], &L.ctr->n_walk[li], on));
+                P2_HIP(spans.end(on));
+            }
+            P2_HIP(spans.begin(SpanRec::kClassify, on, lists));
+            for (int li = 0; li < lists; ++li)
+                P2_HIP(launch_front_classify(dq, pl.R, kk, L.states[li], std::min(most, L.cap[li]), last ? L.walk[li] : list[li],
+                                             last ? &L.ctr->n_walk[li] : n_list[li], last ? &L.marks->edges[0] : from[li], li + 1, 2, last ? 1 : 0, 0, L.codes[li],
+                                             L.row_counts[li], L.unknown[li], L.ctr, on));
+            P2_HIP(spans.end(on));
+            P2_HIP(spans.begin(SpanRec::kGroup, on));
+            FrontEdges E;
+            E.edges = L.edges; E.cap_edges = D.cap_found; E.literal = L.literal; E.literal_parent = L.literal_parent; E.cap_literal = L.cap_literal;
+            E.ctr = L.ctr; E.max_len = M;
+            for (int li = 0; li < lists; ++li)
+                P2_HIP(launch_front_edges(dq, list[li], n_list[li], from[li], L.codes[li], L.unknown[li], li + 1, l, l == 0 ? 1u : l == 1 ? 6u : 320u, E, on));
+            P2_HIP(spans.end(on));
+            if (last) break;
+            FrontLevel lv;
+            std::memset(&lv, 0, sizeof lv);
+            lv.states1 = L.states[0]; lv.states2 = L.states[1];
+            lv.surv = L.edges; lv.n_surv = D.cap_found;
+            lv.lds_planes = l == 0 ? 1 : 2;
+            lv.next_states1 = L.states[0]; lv.next_states2 = L.states[1]; lv.next_hash1 = L.hash[0]; lv.next_hash2 = L.hash[1];
+            lv.surv_from = &L.marks->edges[l + 1]; lv.surv_end = &L.ctr->n_ssurv;
+            lv.cap1 = L.cap[0]; lv.cap2 = L.cap[1]; lv.blocks = l == 0 ? 128u : l == 1 ? 1024u : 4096u;
+            P2_HIP(spans.begin(SpanRec::kMaterialize, on));
+            P2_HIP(launch_front_materialize(dq, pl.R, kk, lv, on));
+            P2_HIP(spans.end(on));
+            P2_HIP(spans.begin(SpanRec::kGroup, on));
+            for (int li = 0; li < (l == 0 ? 1 : 2); ++li)
+                P2_HIP(launch_front_find(L.states[li], sw * (size_t)(li + 1), L.hash[li], &L.marks->child[li][l + 1], &L.ctr->t_next[li], L.cap[li], L.table[li],
+                                         L.table_size[li], L.rep[li], L.pos[li], L.reps[li], &L.ctr->n_reps[li], l == 0 ? 32u : l == 1 ? 256u : 2048u, on));
+            P2_HIP(spans.end(on));
+        }
+        FrontLinks K;
+        std::memset(&K, 0, sizeof K);
+        K.ctr = L.ctr; K.marks = L.marks; K.graph = D.ctr; K.edges = L.edges;
+        for (int li = 0; li < 2; ++li) { K.rep[li] = L.rep[li]; K.pos[li] = L.pos[li]; K.reps[li] = L.reps[li]; }
+        K.links = D.links; K.node_state = D.node_state;
+        K.cap_edges = D.cap_found; K.cap1 = L.cap[0]; K.cap2 = L.cap[1]; K.cap_literal = L.cap_literal; K.cap_nodes = D.cap_nodes;
+        K.max_len = M; K.literal_judged = judge_literal ? 1 : 0;
+        P2_HIP(launch_front_links(K, 64u, on));
         return P2_OK;
     };
     std::vector<char> done(n_queries, 0);
@@ -1060,6 +1247,13 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (!graphs.empty()) {
             const int32_t rc = layout_graphs(reinterpret_cast<DevGraph*>(hb + off_graphs));
             if (rc != P2_OK) return rc;
+            for (size_t g = 0; g < graphs.size(); ++g) {
+                if (!graphs[g].large) continue;
+                DevQuery* dq = reinterpret_cast<DevQuery*>(hb + graphs[g].off_query);
+                std::memcpy(dq, hb + runs[graphs[g].leader].off_query, sizeof(DevQuery));
+                const DevGraph& D = reinterpret_cast<const DevGraph*>(hb + off_graphs)[g];
+                dq->k = D.rows_kept; dq->KW = (D.rows_kept + 31) / 32; dq->n_msg = 0; dq->rows_split = (int32_t)D.split_check;
+            }
             for (int i = 0; i < n_queries; ++i)
                 reinterpret_cast<GraphQuery*>(hb + off_gasked)[i] = GraphQuery{runs[i].graph ? (uint32_t)runs[i].graph_id : ~0u, (uint32_t)runs[i].graph_pos};
             for (const Graph& G : graphs) std::memcpy(hb + G.off_members, G.members.data(), sizeof(int32_t) * G.members.size());
@@ -1087,10 +1281,50 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             for (uint32_t g : gsmall) max_R = std::max(max_R, runs[graphs[g].leader].plan.R);
             P2_HIP(launch_graph_alone(dgs, reinterpret_cast<const uint32_t*>(db + off_gsmall), (unsigned)gsmall.size(), max_R, stream));
         }
-        if (!glarge.empty()) {
-            eval_launches += graph_levels + 1;
+        // large groups: one on the call's stream, several on the slots', the largest first, each to the slot with the least to do
+        size_t n_slots_used = 0;
+        if (n_large > 0) {
+            if (g_prof.on) P2_HIP(hipEventRecord(g_prof.ev[3], stream));
+            for (FrontSlot& S : C.slots) { S.spans.on = g_prof.on; S.spans.kernels_only = g_prof.kernels_only; S.spans.reset(); }
+            std::vector<size_t> order;
+            for (size_t g = 0; g < graphs.size(); ++g) if (graphs[g].large) order.push_back(g);
+            // (512 devices, four levels: 4.1 ms alone; 256: 2.1; 128: 1.3: a chain of launches, and what the devices add)
+            auto weight = [&](size_t g) { const Plan& pl = runs[graphs[g].leader].plan; return (96.0 + pl.R) * (1024.0 + graph_room(pl)); };
+            std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return weight(x) > weight(y); });
+            if (large_slots > 1) {
+                n_slots_used = (size_t)large_slots;
+                P2_HIP(hipEventRecord(C.front_go, stream));
+                for (size_t t = 0; t < n_slots_used; ++t) P2_HIP(hipStreamWaitEvent(C.slots[t].stream, C.front_go, 0));
+            }
+            double load[kFrontSlots] = {};
+            int32_t rc = P2_OK;
+            for (size_t g : order) {
+                size_t t = 0;
+                for (size_t u = 1; u < n_slots_used; ++u) if (load[u] < load[t]) t = u;
+                load[t] += weight(g);
+                rc = queue_large(g, n_slots_used > 0 ? C.slots[t].stream : stream, C.slots[t].spans);
+                if (rc != P2_OK) break;
+            }
+            if (rc != P2_OK) {                           // (what the slots have queued uses this thread's buffers)
+                for (size_t t = 0; t < n_slots_used; ++t) (void)hipStreamSynchronize(C.slots[t].stream);
+                return rc;
+            }
+        }
+        if (!glevel.empty()) {
+            eval_launches += graph_levels;
             for (int level = 0; level < graph_levels; ++level)
                 P2_HIP(launch_graph_level(dgs, reinterpret_cast<const GraphBlock*>(db + off_glevel), (unsigned)glevel.size(), level, graph_levels, stream));
+        }
+        if (n_large > 0) {
+            for (size_t t = 0; t < n_slots_used; ++t) {
+                if (!C.slot_done[t]) P2_HIP(hipEventCreateWithFlags(&C.slot_done[t], hipEventDisableTiming));
+                P2_HIP(hipEventRecord(C.slot_done[t], C.slots[t].stream));
+                P2_HIP(hipStreamWaitEvent(stream, C.slot_done[t], 0));
+            }
+            if (g_prof.on) P2_HIP(hipEventRecord(g_prof.ev[4], stream));
+        }
+        if (!glarge.empty()) {
+            ++eval_launches;
             // (a byte per node, a word for every count of a node inside, two words per digit set of a node on the way to a goal:
             //  less than ten bytes a node together where there are many, three words where there are few)
             uint32_t most = 0;
@@ -1205,7 +1439,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 for (int len = 1; len <= pl.max_len; ++len) valid += gc.n_valid[len];
                 if (valid > 0xffffffffull) return kWithoutGraphs;
                 r.n_valid = (uint32_t)valid; r.n_rerun = r.n_rerun_groups = 0;
-                const unsigned long long applied = r.graph_frontier ? listed : walked;
+                const unsigned long long applied = r.graph_frontier && !r.graph_flat ? listed : walked;
                 r.steps = applied * (unsigned long long)pl.alphabet; r.members = applied * per_alphabet;
                 const bool own = graphs[r.graph_id].leader == i;
                 r.evaluated = own ? (unsigned long long)gc.n_judged * (unsigned long long)pl.alphabet : 0ull;
@@ -1356,7 +1590,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                                                          n_l_literal > 0 ? front_literal_scratch_bytes(pl.R, pl.k, std::max(n_l, n_c2)) : 0)));
                     P2_HIP(S.f_rest.ensure((size_t)n_l * sizeof(uint32_t)));
                     P2_HIP(launch_front_literal_goals(dq, pl.R, pl.k, static_cast<const FrontEntry*>(S.f_literal[cur].p),
-                                                      static_cast<const uint32_t*>(S.f_lit_parent[cur].p), n_l, len,
+                                                      static_cast<const uint32_t*>(S.f_lit_parent[cur].p), n_l, nullptr, len,
                                                       static_cast<const uint32_t*>(S.f_states[cur ^ 1].p), static_cast<const uint32_t*>(S.f_states2[cur ^ 1].p),
                                                       S.lit_scratch.p, static_cast<FrontSurvivor*>(S.f_surv_literal.p), (uint32_t)cap_l, dctr,
                                                       static_cast<uint32_t*>(S.f_rest.p), S.stream));
@@ -1390,7 +1624,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                     if (n_s[li] == 0) continue;
                     P2_HIP(S.f_walk[li].ensure((size_t)n_s[li] * sizeof(uint32_t)));
                     P2_HIP(launch_front_goal_filter(dq, pl.R, pl.k, static_cast<const uint32_t*>(list_states[li]->p), n_s[li], cls_list[li],
-                                                    cls_n[li], li + 1, static_cast<uint8_t*>(S.f_codes[li].p), static_cast<unsigned long long*>(S.f_rowcnt[li].p),
+                                                    cls_n[li], nullptr, li + 1, static_cast<uint8_t*>(S.f_codes[li].p), static_cast<unsigned long long*>(S.f_rowcnt[li].p),
                                                     static_cast<uint8_t*>(S.f_unk[li].p), static_cast<uint32_t*>(S.f_walk[li].p),
                                                     &dctr->n_walk[li], S.stream));
                     cls_list[li] = static_cast<const uint32_t*>(S.f_walk[li].p);
@@ -1401,7 +1635,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             if (n_s[0] + n_s[1] > 0) P2_HIP(S.spans.begin(SpanRec::kClassify, S.stream, (n_s[0] > 0) + (n_s[1] > 0)));
             for (int li = 0; li < 2; ++li)
                 P2_HIP(launch_front_classify(dq, pl.R, pl.k, static_cast<const uint32_t*>(list_states[li]->p), n_s[li], cls_list[li],
-                                             cls_n[li], li + 1, max_pairs, keep ? 0 : 1, (li == 1 && handover) ? 0 : 1,
+                                             cls_n[li], nullptr, li + 1, max_pairs, keep ? 0 : 1, (li == 1 && handover) ? 0 : 1,
                                              static_cast<uint8_t*>(S.f_codes[li].p), static_cast<unsigned long long*>(S.f_rowcnt[li].p),
                                              static_cast<uint8_t*>(S.f_unk[li].p), dctr, S.stream));
             if (n_s[0] + n_s[1] > 0) P2_HIP(S.spans.end(S.stream));
@@ -1618,11 +1852,26 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         return P2_OK;
     };
-    if (g_prof.on) P2_HIP(hipEventRecord(g_prof.ev[3], stream));
     for (FrontSlot& S : C.slots) {       // (also the slots that this call leaves idle: their figures are summed below)
         S.prof_prefixes = S.prof_state_bytes = S.prof_lane_ops = S.prof_children = S.prof_mat_bytes = S.prof_entries = 0.0;
-        S.spans.reset();
+        if (n_large == 0) S.spans.reset();
     }
+    for (size_t g = 0; g < graphs.size() && g_prof.on; ++g) {
+        if (!graphs[g].large) continue;
+        const GraphCounters& gc = static_cast<const GraphCounters*>(C.h_gctr.p)[g];
+        const Plan& pl = runs[graphs[g].leader].plan;
+        FrontSlot& S = C.slots[0];
+        const double words = (double)((graph_rows(pl) + 31) / 32 + (pl.R + 31) / 32);
+        double visited = 0.0;
+        for (const Pattern& p : pl.patterns) visited += (double)p.g * p.n_groups;
+        S.prof_prefixes += gc.n_judged; S.prof_entries += 1.0;
+        for (int len = 1; len < pl.max_len; ++len) S.prof_entries += (double)gc.n_prefixes[len];
+        S.prof_state_bytes += (double)gc.walked_planes * pl.R * words * 4.0;
+        S.prof_lane_ops += (double)gc.walked_planes * visited * words * 4.0;
+        S.prof_children += gc.n_children;
+        S.prof_mat_bytes += ((double)gc.n_children + gc.n_child_planes) * pl.R * words * 4.0;
+    }
+    if (g_prof.on && n_large == 0) P2_HIP(hipEventRecord(g_prof.ev[3], stream));
     if (!enums.empty()) {
         for (size_t e = 0; e < enums.size(); ++e) enums[e].id = (int)e;
         if (C.f_evalid.size() < enums.size()) { C.f_evalid.resize(enums.size()); C.f_egsums.resize(enums.size()); }
@@ -1639,7 +1888,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         for (int t = 0; t < n_slots; ++t) {
             FrontSlot& S = C.slots[t];
             P2_HIP(hipStreamWaitEvent(S.stream, C.front_go, 0));
-            S.spans.on = g_prof.on; S.spans.kernels_only = g_prof.kernels_only; S.spans.reset();
+            S.spans.on = g_prof.on; S.spans.kernels_only = g_prof.kernels_only;
             S.rc = P2_OK; S.err.clear();
         }
         // the long chains first: large reduction groups, large alphabets
@@ -1676,7 +1925,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     }
 
     if (g_prof.on) {
-        P2_HIP(hipEventRecord(g_prof.ev[4], stream));
+        if (n_large == 0 || !enums.empty()) P2_HIP(hipEventRecord(g_prof.ev[4], stream));
+        P2_HIP(hipEventRecord(g_prof.ev[5], stream));
         p2_profile& L = g_prof.last;
         L.front_prefixes = L.front_classify_state_bytes = L.front_classify_lane_ops = L.front_survivors = 0.0;
         L.front_materialize_bytes = L.front_entries = 0.0;
@@ -1963,7 +2213,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     if (g_prof.on) {
         P2_HIP(hipEventElapsedTime(&g_prof.last.eval_ms, g_prof.ev[0], g_prof.ev[1]));
         g_prof.last.post_ms = 0.0f;
-        if (store) P2_HIP(hipEventElapsedTime(&g_prof.last.post_ms, direct ? g_prof.ev[1] : g_prof.ev[4], g_prof.ev[2]));
+        if (store) P2_HIP(hipEventElapsedTime(&g_prof.last.post_ms, direct ? g_prof.ev[1] : g_prof.ev[5], g_prof.ev[2]));
         P2_HIP(hipEventSynchronize(g_prof.ev[4]));      // (a call that only sizes its result has not waited since)
         P2_HIP(hipEventElapsedTime(&g_prof.last.front_ms, g_prof.ev[3], g_prof.ev[4]));
         float ms[SpanRec::kKinds] = {0.f, 0.f, 0.f, 0.f};

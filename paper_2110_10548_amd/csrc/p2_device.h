@@ -132,7 +132,8 @@ struct DevQuery {
     int32_t MW, KW;                // 32-bit words per contribution mask / per chunk set
     int32_t n_patterns, n_ops, alphabet, max_len;
     int32_t n_levels, n_msg;
-    int32_t algo, pad0;            // cost model of AllReduce: 0 ring, 1 tree
+    int32_t algo;                  // cost model of AllReduce: 0 ring, 1 tree
+    int32_t rows_split;            // the rows k stand for blocks of several chunks (the graph's own description of its structure)
     unsigned long long n_candidates;
     unsigned long long base[P2_MAX_LEN + 2];   // base[l]: index of the first program of length l
     uint8_t ops[8];
@@ -230,6 +231,7 @@ hipError_t launch_cost_literal_list(const DevQuery* queries, const DevPostSeg* s
 hipError_t launch_cost(const DevQuery* q, int R, int k, int engine, const unsigned long long* sorted, uint32_t n,
                        p2_program* out_prog, double* out_cost, hipStream_t stream);
 // ---- frontier evaluation (p2_frontier.hip, p2_literal.hip) -------------------------------------
+struct GraphCounters;
 // A prefix of the frontier: instruction digit t at bits [9t, 9t + 9) of `digits`.
 struct FrontEntry {
     uint32_t query;
@@ -292,6 +294,10 @@ struct FrontLevel {
     double* delta1; double* delta2; double* delta_goal;   // [child][n_share][2]: what the step adds to the cost sums;
                                                            // with `factors` [child][n_share][4]: both terms as factors
     int32_t factors;
+    // states only (n_msg = 0): the entries [*surv_from, *surv_end) of surv, which has room for n_surv; children past cap1 /
+    // cap2 are left out.  blocks: of the launch (0: by n_surv)
+    const uint32_t* surv_from; const uint32_t* surv_end;
+    uint32_t cap1, cap2, blocks;
 };
 // For the kernel that writes the prefixes of the next level (and the goals) from the survivors of this level's prefixes:
 struct FrontPrefixes {
@@ -323,6 +329,29 @@ struct FrontFinish {
     unsigned long long out_first;  // first row of the query in the batch-wide buffers
     unsigned long long* sorted; p2_program* progs; double* costs;
 };
+// The graph of an enumeration's states (engine AUTO): what the lists held when a level began.
+struct FrontMarks { uint32_t edges[P2_MAX_LEN + 2], child[2][P2_MAX_LEN + 2], rep[2][P2_MAX_LEN + 2]; };
+struct FrontEdges {
+    FrontSurvivor* edges; uint32_t cap_edges;
+    FrontEntry* literal; uint32_t* literal_parent; uint32_t cap_literal;      // children that need more than two pairs
+    FrontCounters* ctr;
+    int32_t max_len;
+};
+struct FrontLinks {
+    const FrontCounters* ctr; const FrontMarks* marks; GraphCounters* graph;
+    const FrontSurvivor* edges; const uint32_t* rep[2]; const uint32_t* pos[2]; const uint32_t* reps[2];
+    uint2* links; uint32_t* node_state;
+    uint32_t cap_edges, cap1, cap2, cap_literal, cap_nodes;
+    int32_t max_len, literal_judged;
+};
+hipError_t launch_front_root(FrontCounters* ctr, FrontMarks* marks, uint32_t* rep, uint32_t* pos, uint32_t* reps_list, hipStream_t stream);
+hipError_t launch_front_mark(const FrontCounters* ctr, FrontMarks* marks, int level, hipStream_t stream);
+hipError_t launch_front_edges(const DevQuery* q, const uint32_t* list, const uint32_t* n_list, const uint32_t* from, const uint8_t* codes,
+                              const uint8_t* unknown, int np, int level, unsigned blocks, const FrontEdges& A, hipStream_t stream);
+hipError_t launch_front_find(const uint32_t* states, size_t state_words, const unsigned long long* hash, const uint32_t* from, const uint32_t* to,
+                             uint32_t cap, unsigned long long* table, uint32_t table_size, uint32_t* rep, uint32_t* pos, uint32_t* reps_list,
+                             uint32_t* n_reps, unsigned blocks, hipStream_t stream);
+hipError_t launch_front_links(const FrontLinks& A, unsigned blocks, hipStream_t stream);
 // Bytes from one state's row of codes to the next: the alphabet rounded up to whole words, so that the kernels that
 // list survivors and children read four codes at a time (the bytes past the alphabet are never looked at).
 __host__ __device__ inline uint32_t front_code_stride(int alphabet) { return ((uint32_t)alphabet + 3u) & ~3u; }
@@ -340,21 +369,21 @@ hipError_t launch_front_init(const DevQuery* q, uint32_t query, int R, int k, Fr
 hipError_t launch_front_dedup(const uint32_t* states, size_t state_words, const unsigned long long* hash, uint32_t n,
                               unsigned long long* table, uint32_t table_size, uint32_t* rep, uint32_t* reps_list,
                               uint32_t* n_reps, hipStream_t stream);
-// Judges the entries list[0 .. *n_list) of a frontier list (every entry 0 .. n - 1 if list is null) against the
+// Judges the entries list[0 .. *n_list) (from *from on, if it is given) of a frontier list (every entry 0 .. n - 1 if list is null) against the
 // alphabet: codes[e * alphabet + digit] = CODE_* of that extension of entry e, unknown[e] = 1 where the pair form
 // cannot judge the entry.  np: planes per entry (1: the one-pair list, 2: the two-pair list).  max_pairs = 1 sends
 // children that need two pairs to the literal list.  row_counts[e]: how many of the row's codes are survivors, goals
 // (low word, 16 bits each), one-pair and two-pair children (high word).  count_children != 0 adds the children of the
 // entries it could judge to ctr->t_count (by kind).
 hipError_t launch_front_classify(const DevQuery* q, int R, int k, const uint32_t* states, uint32_t n, const uint32_t* list,
-                                 const uint32_t* n_list, int np, int max_pairs, int goals_only, int count_children, uint8_t* codes,
-                                 unsigned long long* row_counts, uint8_t* unknown, FrontCounters* ctr, hipStream_t stream);
+                                 const uint32_t* n_list, const uint32_t* from, int np, int max_pairs, int goals_only, int count_children,
+                                 uint8_t* codes, unsigned long long* row_counts, uint8_t* unknown, FrontCounters* ctr, hipStream_t stream);
 // The last level, before the classification (which then runs with goals_only on the list this leaves): the entries
 // from which no instruction can end at the goal get a row of invalid codes; the others are listed in
 // walk[0 .. *n_walk) (*n_walk zero on entry; any order).
 hipError_t launch_front_goal_filter(const DevQuery* q, int R, int k, const uint32_t* states, uint32_t n, const uint32_t* list,
-                                    const uint32_t* n_list, int np, uint8_t* codes, unsigned long long* row_counts, uint8_t* unknown,
-                                    uint32_t* walk, uint32_t* n_walk, hipStream_t stream);
+                                    const uint32_t* n_list, const uint32_t* from, int np, uint8_t* codes, unsigned long long* row_counts,
+                                    uint8_t* unknown, uint32_t* walk, uint32_t* n_walk, hipStream_t stream);
 // The survivors of every entry of a list from the codes of the entry that stands for its state (rep null: its own):
 // appended to surv with their places in the next frontier; entries that cannot be judged go to unknown_out
 // (counted in n_unknown); handover != 0 treats every entry so (the hand-over path, for tests).
@@ -375,10 +404,10 @@ hipError_t launch_front_classify_literal(const DevQuery* q, int R, int k, const 
                                          const uint32_t* elist_n, hipStream_t stream);
 // The last level's goals among the extensions of literal prefixes that are one AllGather away from a state held in pairs
 // (parents[e] as in FrontPrefixes; states1 / states2: the state lists of the level before); the other entries go on the
-// list rest[0 .. ctr->n_rest).  scratch: front_literal_goals_scratch_bytes(R, k, n) bytes.
+// list rest[0 .. ctr->n_rest).  n_dev (null: n): how many there are, at most n.  scratch: front_literal_goals_scratch_bytes(R, k, n) bytes.
 size_t front_literal_goals_scratch_bytes(int R, int k, uint32_t n);
 hipError_t launch_front_literal_goals(const DevQuery* q, int R, int k, const FrontEntry* entries, const uint32_t* parents, uint32_t n,
-                                      int len, const uint32_t* states1, const uint32_t* states2, void* scratch, FrontSurvivor* surv,
+                                      const uint32_t* n_dev, int len, const uint32_t* states1, const uint32_t* states2, void* scratch, FrontSurvivor* surv,
                                       uint32_t surv_cap, FrontCounters* ctr, uint32_t* rest, hipStream_t stream);
 // The children of the judged states of a list (every state 0 .. n - 1 if list is null), from their codes: counted by
 // kind (write = 0: t_count), or given their places (write = 1: child_of[state * alphabet + digit], t_next) and
@@ -409,9 +438,9 @@ struct GraphCounters {             // zero on entry
     uint32_t flags, n_planes;
     unsigned long long found[P2_MAX_LEN + 1];  // by programs of so many instructions: edges (high half), new states (low half)
     uint32_t n_edges, n_judged;                // edges on the way to a goal; states judged
-    uint32_t n_valid[P2_MAX_LEN + 1], n_total, pad;      // valid programs of so many instructions, of any number
+    uint32_t n_valid[P2_MAX_LEN + 1], n_total, pad[3];      // valid programs of so many instructions, of any number
     unsigned long long n_prefixes[P2_MAX_LEN + 1];   // programs of so many instructions whose rules all hold, short of the goal
-    unsigned long long pad2;       // (whole 16-byte words)
+    uint32_t walked_planes, n_children, n_child_planes, pad2;      // large groups: planes walked by the classification; children built
 };
 constexpr int kGraphPatterns = 36;
 // One reduction structure: what its kernels read and where they write.  A state is plane | pairs << 28, its pairs in
@@ -437,6 +466,10 @@ struct DevGraph {
     uint32_t* use_id; uint32_t* first_edge; uint32_t* use_ends;           // the nodes on the way to a goal, renumbered; [node][8]: programs
                                                                           // of exactly r more instructions that end at the goal
     uint32_t* edges; uint32_t* edge_state;                                // digit << 23 | target; the state it starts from
+    // groups that the frontier's kernels work on: their states [R][wq] quads of 16 bytes, the first qk of a device its rows,
+    // one list of one-pair states and one of two-pair states (two planes each); null: planes
+    const uint4* large[2];
+    int32_t wq, qk;
     double* best;                  // [edge][member]: most loaded uplink, bytes (in chunks) over bandwidth
     const int32_t* members;
     // its patterns: log2 g | log2 s << 4; bit d set iff device d takes part
@@ -450,6 +483,8 @@ struct GraphRows {                 // rows of one query: blocks [first_block, ne
 };
 // Structures of few states (graph_alone_holds; list: numbers of graphs), a block each: levels, counts and edges in one launch.
 bool graph_alone_holds(uint32_t nodes);
+// Planes that the wavefronts of the launches per level may reserve and not use.
+uint32_t graph_planes_left(uint32_t blocks, int max_len);
 hipError_t launch_graph_alone(const DevGraph* graphs, const uint32_t* list, unsigned n, int max_R, hipStream_t stream);
 // The others: a launch per level, then one for the counts and the edges (lds_bytes: for the counts of the largest).
 hipError_t launch_graph_level(const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int level, int max_len, hipStream_t stream);

@@ -871,8 +871,8 @@ __device__ inline uint4 goal_quad_of(const Words<KW>& all_rows, const Words<MW>&
 template <int KW, int MW, int NP>
 __global__ __launch_bounds__(256) void k_front_goal_filter(const DevQuery* __restrict__ qp, const uint32_t* __restrict__ states,
                                                            uint32_t n_entries, const uint32_t* __restrict__ list,
-                                                           const uint32_t* __restrict__ n_list, uint8_t* __restrict__ codes,
-                                                           uint2* __restrict__ row_counts, uint8_t* __restrict__ unknown,
+                                                           const uint32_t* __restrict__ n_list, const uint32_t* __restrict__ from,
+                                                           uint8_t* __restrict__ codes, uint2* __restrict__ row_counts, uint8_t* __restrict__ unknown,
                                                            uint32_t* __restrict__ walk, uint32_t* __restrict__ n_walk) {
     using L = FL<KW, MW>;
     const DevQuery& q = *qp;
@@ -883,7 +883,7 @@ __global__ __launch_bounds__(256) void k_front_goal_filter(const DevQuery* __res
     const uint4 goal_quad = goal_quad_of<KW, MW>(full_mask<KW>(q.k), full_mask<MW>(R), qd, is_row, is_mask);
     const uint32_t wave = (blockIdx.x * 256u + threadIdx.x) >> 6, n_waves = gridDim.x * 4u;
     const uint32_t n_work = list ? *n_list : n_entries;
-    for (uint32_t at = wave; at < n_work; at += n_waves) {
+    for (uint32_t at = wave + (from ? *from : 0u); at < n_work; at += n_waves) {
         const uint32_t e = list ? list[at] : at;
         const uint4* src = reinterpret_cast<const uint4*>(states) + (size_t)e * NP * plane_q;
         bool rows_short = false, cols_short = false, root_short = false;
@@ -922,7 +922,7 @@ template <int KW, int MW, int NP>
 __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify(const DevQuery* __restrict__ qp,
                                                                 const uint32_t* __restrict__ states, uint32_t n_entries,
                                                                 const uint32_t* __restrict__ list, const uint32_t* __restrict__ n_list,
-                                                                int max_pairs, int goals_only, int count_children,
+                                                                const uint32_t* __restrict__ from, int max_pairs, int goals_only, int count_children,
                                                                 uint8_t* __restrict__ codes, uint2* __restrict__ row_counts,
                                                                 uint8_t* __restrict__ unknown, FrontCounters* __restrict__ ctr) {
     extern __shared__ uint4 ldsq[];                      // NP planes of [R][WQ] quads, then R flag bytes
@@ -933,6 +933,7 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
     __shared__ ClsItem s_items[kMaxPatterns * kClsChunks];
     __shared__ __align__(16) uint8_t s_codes[512];        // the row of codes of the state at hand (an alphabet has at most 512 instructions)
     using L = FL<KW, MW>;
+    if (from && blockIdx.x + *from >= *n_list) return;   // (more blocks than the level has states)
     const DevQuery& q = *qp;
     const int R = q.R, I = q.alphabet, n_ops = q.n_ops, n_pat = q.n_patterns;
     const int plane_q = R * L::WQ;                       // quads per plane
@@ -994,7 +995,7 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
     const uint32_t n_work = list ? *n_list : n_entries;
     uint32_t walked = 0;                                 // states whose patterns were walked (thread 0 counts)
     uint32_t kids[3] = {0u, 0u, 0u};                     // one-pair children, two-pair children, goals of this block's states
-    for (uint32_t at = blockIdx.x; at < n_work; at += gridDim.x) {
+    for (uint32_t at = blockIdx.x + (from ? *from : 0u); at < n_work; at += gridDim.x) {
         const uint32_t e = list ? list[at] : at;
         __syncthreads();
         const uint4* src = reinterpret_cast<const uint4*>(states) + (size_t)e * NP * plane_q;
@@ -1078,6 +1079,8 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
             if (lane == 0)
                 cls_codes<KW, MW, NP>(c, P, pid, pf, s_pgoal[pid], s_ptwo[pid], n_goal, n_two, many, bc_pairs, rs_straddles, ops_r, n_ops, max_pairs,
                                       all_rows, all_cols, goal_ops, s_codes, unknown + e);
+            // (a row that stands for several chunks: what would have to cut one in two is not known here)
+            if (lane == 0 && q.rows_split && has_scatter && goal_ops < 0 && (pf & kPfBadRs) && !(pf & (kPfBadRed | kPfBadB)) && (pf & kPfChanged)) unknown[e] = 1;
         }
         // ---- how many of the row's codes are survivors, goals, one-pair and two-pair children (16 bits each), for the
         //      kernel that lists the survivors of the prefixes: it then reads the rows of the prefixes that have any
@@ -1175,6 +1178,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
     __shared__ uint32_t s_count[P2_MAX_DEVICES / 2];     // rows that set a group's bytes
     __shared__ unsigned long long s_hash[NT / 64];       // the wavefronts' shares of the child's hash
     using L = FL<KW, MW>;
+    if (A.surv_end && blockIdx.x + *A.surv_from >= *A.surv_end) return;
     const DevQuery& q = queries[A.query];
     const int R = q.R;
     const int plane_q = R * L::WQ;
@@ -1197,9 +1201,12 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
         c->n_walked_planes = 0u; c->n_walk[0] = 0u; c->n_walk[1] = 0u; c->n_rest = 0u;
     }
     __syncthreads();
-    for (uint32_t i = blockIdx.x; i < A.n_surv; i += gridDim.x) {
+    const uint32_t i_end = A.surv_end ? min(*A.surv_end, A.n_surv) : A.n_surv;
+    for (uint32_t i = blockIdx.x + (A.surv_from ? *A.surv_from : 0u); i < i_end; i += gridDim.x) {
         const FrontSurvivor sv = A.surv[i];
         const int code = sv.code & 0xff;
+        // (states only: the goals have none, and children past the lists' room, which the call will say, are left out)
+        if (A.surv_end && (code == CODE_GOAL || sv.slot >= (code == CODE_PREFIX2 ? A.cap2 : A.cap1))) continue;
         const int np = (sv.code & kFromTwoPair) ? 2 : 1;
         const size_t plane_w = (size_t)plane_q * 4;
         const uint4* parent = reinterpret_cast<const uint4*>(np == 2 ? A.states2 + (size_t)sv.entry * 2 * plane_w
@@ -1367,6 +1374,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
         }
         // ---- the step's time for every query of the enumeration (alpha-beta model: latency steps of the
         //      slowest group's link; bytes through the busiest uplink, from the query's bandwidth rows)
+        if (A.n_msg == 0) continue;
         double* out = (code == CODE_GOAL ? A.delta_goal : code == CODE_PREFIX2 ? A.delta2 : A.delta1) + (size_t)place * (A.factors ? 4 : 2) * A.n_share;
         // Where every group holds the same number of rows c (the usual case), the busiest unit of a hardware level
         // carries c times the largest multiplicity sum of that level's rows, which the row tables carry per pattern:
@@ -1375,7 +1383,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
         bool same = true;
         for (int G = lane; G < ng; G += 64) same &= s_count[G] == c0;
         const bool uniform = __all(same) != 0;
-        if (A.n_msg > 0 && uniform) {
+        if (uniform) {
             for (int j = tid; j < A.n_share; j += NT) {
                 const DevQuery& cq = queries[A.share[j]];
                 const DevRows& rw = *cq.rows;
@@ -1386,7 +1394,7 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                 step_factors(op, P.g, cq.algo, ring_steps, mult);
                 put_terms(out, j, A.factors != 0, ring_steps, cq.alpha[cq.pat[pid].span_level], mult / (double)cq.k, best);
             }
-        } else if (A.n_msg > 0) {
+        } else {
             for (int j = wave; j < A.n_share; j += (NT / 64)) {
                 const DevQuery& cq = queries[A.share[j]];
                 const DevRows& rw = *cq.rows;
@@ -1526,6 +1534,193 @@ __global__ __launch_bounds__(256) void k_front_children(const DevQuery* __restri
     }
 }
 
+// ---- the graph of the states (engine AUTO) ----------------------------------------------------------------
+// The same kernels build the graph of an enumeration's distinct states without the host: all lists go on from level to
+// level (a state keeps its place for good, an equal state of an earlier level is found like one of the same level), what a
+// level starts with is marked on the device, and the edges are handed to the counting that the graphs of small groups
+// use (p2_graph.hip).  Prefixes, their sums and their order are not kept: the counts give them back.
+// Bound by the materialized states of the levels, as the enumeration is, and then by the launches: some 14 a level, 3 us
+// each where a level has few states ([3 4 6]: 283 us of the call's 373; 512 devices in four levels: 1.44 ms in
+// k_front_materialize, 1.5 in k_front_classify, 0.44 in k_front_compare, of 4.4 ms).
+// A wavefront takes kChildChunk states at a time, a lane per four instructions (alphabets of at most 255).
+__global__ __launch_bounds__(256) void k_front_edges(const DevQuery* __restrict__ qp, const uint32_t* __restrict__ list, const uint32_t* __restrict__ n_list,
+                                                     const uint32_t* __restrict__ from, const uint8_t* __restrict__ codes,
+                                                     const uint8_t* __restrict__ unknown, int np, int level, FrontEdges A) {
+    const uint32_t I = (uint32_t)qp->alphabet, CS = front_code_stride((int)I);
+    const int lane = threadIdx.x & 63;
+    const int left = (int)I - lane * 4;
+    const uint32_t in_alphabet = left >= 4 ? 0xffffffffu : left > 0 ? ((1u << (8 * left)) - 1u) : 0u;
+    const uint32_t wave = (blockIdx.x * 256u + threadIdx.x) >> 6, n_waves = gridDim.x * 4u;
+    const uint32_t first = *from, end = *n_list;
+    bool trouble = false;
+    for (uint32_t c0 = first + wave * kChildChunk; c0 < end; c0 += n_waves * kChildChunk) {
+        uint32_t st_of[kChildChunk], four[kChildChunk];
+        uint8_t unk[kChildChunk];
+        // (every load is made, from an entry that exists, and what was not asked for is dropped afterwards)
+#pragma unroll
+        for (int b = 0; b < kChildChunk; ++b) st_of[b] = list[c0 + (uint32_t)b < end ? c0 + (uint32_t)b : c0];
+#pragma unroll
+        for (int b = 0; b < kChildChunk; ++b) {
+            unk[b] = unknown[st_of[b]];
+            four[b] = reinterpret_cast<const uint32_t*>(codes + (size_t)st_of[b] * CS)[(uint32_t)lane < CS / 4u ? lane : 0];
+        }
+        uint32_t mine[4] = {0u, 0u, 0u, 0u};             // one-pair children, two-pair children, goals, children that need more pairs
+#pragma unroll
+        for (int b = 0; b < kChildChunk; ++b) {
+            const bool on = c0 + (uint32_t)b < end;
+            trouble |= on && unk[b] != 0;
+            four[b] = on && (uint32_t)lane < CS / 4u ? four[b] & in_alphabet : 0u;
+#pragma unroll
+            for (uint32_t j = 0; j < 4u; ++j) {
+                const int code = (int)((four[b] >> (8u * j)) & 0xffu);
+                mine[0] += code == CODE_PREFIX ? 1u : 0u; mine[1] += code == CODE_PREFIX2 ? 1u : 0u;
+                mine[2] += code == CODE_GOAL ? 1u : 0u; mine[3] += code == CODE_PREFIX_LITERAL ? 1u : 0u;
+            }
+        }
+        uint32_t before[4], total[4];
+#pragma unroll
+        for (int kd = 0; kd < 4; ++kd) {
+            uint32_t x = mine[kd];
+            for (int o = 1; o < 64; o <<= 1) { const uint32_t y = __shfl_up(x, o, 64); if (lane >= o) x += y; }
+            before[kd] = x - mine[kd];
+            total[kd] = __shfl(x, 63, 64);
+        }
+        const uint32_t all = total[0] + total[1] + total[2] + total[3];
+        if (all == 0u) continue;
+        // (one trip to the counters: lanes 0-1 the places of the children, 2 of the literal list, 3 of the edges)
+        const uint32_t add = lane == 0 ? total[0] : lane == 1 ? total[1] : lane == 2 ? total[3] : lane == 3 ? all : 0u;
+        uint32_t got = 0u;
+        if (lane < 4 && add != 0u) got = atomicAdd(lane < 2 ? &A.ctr->t_next[lane] : lane == 2 ? &A.ctr->next_literal : &A.ctr->n_ssurv, add);
+        uint32_t next[2] = {__shfl(got, 0, 64) + before[0], __shfl(got, 1, 64) + before[1]};
+        uint32_t at_lit = __shfl(got, 2, 64) + before[3], at = __shfl(got, 3, 64) + before[0] + before[1] + before[2] + before[3];
+        // (literal children are judged at the size limit only, from the state that they are one AllGather away from)
+        if (total[3] > 0u && level + 2 != A.max_len) trouble = true;
+#pragma unroll
+        for (int b = 0; b < kChildChunk; ++b) {
+#pragma unroll
+            for (uint32_t j = 0; j < 4u; ++j) {
+                const int code = (int)((four[b] >> (8u * j)) & 0xffu);
+                if (code == CODE_INVALID || code == CODE_UNKNOWN) continue;
+                const uint32_t a = (uint32_t)lane * 4u + j;
+                FrontSurvivor sv;
+                sv.entry = st_of[b]; sv.digit = (uint16_t)a; sv.code = (uint16_t)(code | (np == 2 ? kFromTwoPair : 0));
+                sv.slot = code == CODE_PREFIX ? next[0]++ : code == CODE_PREFIX2 ? next[1]++ : ~0u;
+                if (at < A.cap_edges) A.edges[at] = sv;
+                ++at;
+                if (code == CODE_PREFIX_LITERAL) {
+                    if (at_lit < A.cap_literal) {
+                        FrontEntry ce;
+                        ce.query = 0u; ce.len = (uint32_t)(level + 1); ce.digits = (unsigned long long)a << (9 * level);
+                        A.literal[at_lit] = ce;
+                        A.literal_parent[at_lit] = st_of[b] * 2u + (np == 2 ? 1u : 0u);
+                    }
+                    ++at_lit;
+                }
+            }
+        }
+    }
+    if (__any(trouble) && lane == 0) A.ctr->n_unknown = 1u;      // (any wavefront's word says the same)
+}
+// What the next level starts with: one thread.
+__global__ void k_front_mark(const FrontCounters* __restrict__ ctr, FrontMarks* __restrict__ marks, int level) {
+    marks->edges[level] = ctr->n_ssurv;
+    for (int li = 0; li < 2; ++li) { marks->child[li][level] = ctr->t_next[li]; marks->rep[li][level] = ctr->n_reps[li]; }
+}
+// The children that the level has added, looked up among all states so far (as k_front_dedup and k_front_verify do within
+// a level); pos[p]: a distinct state's place on the list.
+__global__ __launch_bounds__(256) void k_front_find(const unsigned long long* __restrict__ hash, const uint32_t* __restrict__ from,
+                                                    const uint32_t* __restrict__ to, uint32_t cap, unsigned long long* __restrict__ table, uint32_t mask,
+                                                    uint32_t* __restrict__ rep, uint32_t* __restrict__ pos, uint32_t* __restrict__ reps_list,
+                                                    uint32_t* __restrict__ n_reps) {
+    const uint32_t end = min(*to, cap);
+    for (uint32_t p = *from + blockIdx.x * 256u + threadIdx.x; p < end; p += gridDim.x * 256u) {
+        const unsigned long long h = hash[p], key = h >> 24;
+        uint32_t at = (uint32_t)((h * 0x9e3779b97f4a7c15ull) >> 32) & mask, found = p;
+        for (uint32_t probe = 0; probe <= mask; ++probe) {        // (the table, zero on entry, has room for every entry: an empty word turns up)
+            const unsigned long long old = atomicCAS(&table[at], 0ull, (key << 24) | p);
+            if (old == 0ull) break;
+            if ((old >> 24) == key) { found = (uint32_t)(old & 0xffffffull); break; }
+            at = (at + 1u) & mask;
+        }
+        rep[p] = found;
+        if (found == p) { const uint32_t x = atomicAdd(n_reps, 1u); reps_list[x] = p; pos[p] = x; }
+    }
+}
+__global__ __launch_bounds__(256) void k_front_compare(const uint4* __restrict__ states, uint32_t quads, const uint32_t* __restrict__ from,
+                                                       const uint32_t* __restrict__ to, uint32_t cap, uint32_t* __restrict__ rep,
+                                                       uint32_t* __restrict__ pos, uint32_t* __restrict__ reps_list, uint32_t* __restrict__ n_reps) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = (blockIdx.x * 256u + threadIdx.x) >> 6, n_waves = gridDim.x * 4u, end = min(*to, cap);
+    for (uint32_t p = *from + wave; p < end; p += n_waves) {
+        const uint32_t r = rep[p];
+        if (r == p) continue;
+        const uint4* a = states + (size_t)p * quads;
+        const uint4* b = states + (size_t)r * quads;
+        bool differ = false;
+        for (uint32_t i0 = (uint32_t)lane; i0 < quads; i0 += 256u) {
+            uint4 x[4], y[4];                            // (all eight loads in flight, past the end from the last quad again)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t i = min(i0 + 64u * u, quads - 1u);
+                x[u] = a[i]; y[u] = b[i];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) differ |= q_any(q_xor(x[u], y[u]));
+        }
+        if (__any(differ) && lane == 0) { rep[p] = p; const uint32_t x = atomicAdd(n_reps, 1u); reps_list[x] = p; pos[p] = x; }
+    }
+}
+// The first state of an enumeration on its lists.
+__global__ void k_front_root(FrontCounters* __restrict__ ctr, FrontMarks* __restrict__ marks, uint32_t* __restrict__ rep, uint32_t* __restrict__ pos,
+                             uint32_t* __restrict__ reps_list) {
+    rep[0] = 0u; pos[0] = 0u; reps_list[0] = 0u;
+    ctr->t_next[0] = 1u; ctr->n_reps[0] = 1u;
+    marks->edges[0] = 0u;
+    marks->edges[1] = 0u;
+    for (int li = 0; li < 2; ++li) { marks->child[li][0] = marks->rep[li][0] = 0u; marks->child[li][1] = marks->rep[li][1] = li == 0 ? 1u : 0u; }
+}
+// The edges for the counting: nodes numbered level by level, the one-pair states of a level before its two-pair states; all
+// children that need more than two pairs are one node behind the last level's (nothing is asked of it but that it is there).
+__global__ __launch_bounds__(256) void k_front_links(FrontLinks A) {
+    const FrontMarks& m = *A.marks;
+    const int M = A.max_len;
+    const uint32_t n_edges = A.ctr->n_ssurv;
+    // (marks[M] is what the last level started from plus nothing: it adds goals only)
+    auto node_of = [&](int li, uint32_t p) {
+        int l = 0;
+        while (l + 1 < M && p >= m.rep[li][l + 1]) ++l;
+        const uint32_t base = m.rep[0][l] + m.rep[1][l];
+        return base + (li == 0 ? p - m.rep[0][l] : m.rep[0][l + 1] - m.rep[0][l] + p - m.rep[1][l]);
+    };
+    const uint32_t n_nodes = m.rep[0][M] + m.rep[1][M];
+    const uint32_t n_literal = A.ctr->next_literal;
+    const bool full = n_edges > A.cap_edges || A.ctr->t_next[0] > A.cap1 || A.ctr->t_next[1] > A.cap2 || n_literal > A.cap_literal ||
+                      n_nodes + 1u > A.cap_nodes;
+    const bool trouble = A.ctr->n_unknown != 0u || A.ctr->n_goal != 0u || A.ctr->n_rest != 0u || (n_literal > 0u && !A.literal_judged);
+    const uint32_t me = blockIdx.x * 256u + threadIdx.x, all = gridDim.x * 256u;
+    if (me == 0u) {
+        A.graph->flags = trouble ? kGraphPairs : full ? kGraphFull : 0u;
+        for (int d = 1; d <= M; ++d) {
+            const uint32_t nodes = d < M ? m.rep[0][d + 1] + m.rep[1][d + 1] - m.rep[0][d] - m.rep[1][d] : 0u;
+            A.graph->found[d] = ((unsigned long long)(d == 1 ? n_edges : 0u) << 32) | (nodes + (d == M - 1 && n_literal > 0u ? 1u : 0u));
+        }
+        A.graph->walked_planes = A.ctr->n_walked_planes; A.graph->n_children = A.ctr->t_next[0] + A.ctr->t_next[1] - 1u;
+        A.graph->n_child_planes = A.ctr->t_next[0] + 2u * A.ctr->t_next[1] - 1u;
+    }
+    if (trouble || full) return;
+    for (uint32_t e = me; e < n_edges; e += all) {
+        const FrontSurvivor sv = A.edges[e];
+        const int code = sv.code & 0xff, li = (sv.code & kFromTwoPair) ? 1 : 0;
+        uint32_t to = 0x7fffffu;
+        if (code == CODE_PREFIX) to = node_of(0, A.pos[0][A.rep[0][sv.slot]]);
+        else if (code == CODE_PREFIX2) to = node_of(1, A.pos[1][A.rep[1][sv.slot]]);
+        else if (code == CODE_PREFIX_LITERAL) to = n_nodes;
+        A.links[e] = make_uint2(node_of(li, A.pos[li][sv.entry]) | ((uint32_t)sv.digit << 23), to);
+    }
+    for (int li = 0; li < 2; ++li)
+        for (uint32_t p = me; p < m.rep[li][M]; p += all) A.node_state[node_of(li, p)] = A.reps[li][p] | ((uint32_t)(li + 1) << 28);
+}
+
 // ---- the prefixes of the next level and the goals, from the survivors of this level's prefixes ------------
 // A thread per (survivor, cost sum): the child's sums are the parent's plus what the step adds, which the kernel
 // above worked out once per (state, instruction); the thread of the first sum also writes the record.
@@ -1603,7 +1798,8 @@ constexpr int kLgThreads = 512;
 constexpr uint32_t kLgBlocks = 512;
 template <int KW, int MW>
 __global__ __launch_bounds__(kLgThreads) void k_front_literal_goals(const DevQuery* __restrict__ qp, const FrontEntry* __restrict__ entries,
-                                                                    const uint32_t* __restrict__ parents, uint32_t n, int len,
+                                                                    const uint32_t* __restrict__ parents, uint32_t n_most,
+                                                                    const uint32_t* __restrict__ n_dev, int len,
                                                                     const uint32_t* __restrict__ states1, const uint32_t* __restrict__ states2,
                                                                     uint16_t* __restrict__ scratch, unsigned long long per_block,
                                                                     FrontSurvivor* __restrict__ surv, uint32_t surv_cap,
@@ -1618,6 +1814,7 @@ __global__ __launch_bounds__(kLgThreads) void k_front_literal_goals(const DevQue
     const Words<MW> all_cols = full_mask<MW>(R);
     uint16_t* const owner = scratch + (size_t)blockIdx.x * per_block;
     unsigned long long judged = 0;
+    const uint32_t n = n_dev ? min(*n_dev, n_most) : n_most;
     for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
         const uint32_t parent = parents[e];
         const unsigned long long digits = entries[e].digits;
@@ -1917,6 +2114,7 @@ struct FrontArgs {
     const FrontEntry* entries; const uint32_t* states; uint32_t n;
     int np, max_pairs;
     const uint32_t* list; const uint32_t* n_list;
+    const uint32_t* from;
     uint8_t* codes; uint8_t* unknown; int goals_only, count_children; FrontCounters* ctr;
     uint32_t* walk; uint32_t* n_walk; uint2* row_counts;
     double* sums; uint32_t* sid; int n_share;
@@ -1934,32 +2132,32 @@ hipError_t front_go(int what, const FrontArgs& A, hipStream_t stream) {
         const size_t lds = (size_t)A.np * A.R * FL<KW, MW>::WS * 4 + (((size_t)A.R + 15) & ~(size_t)15);
         // (a block keeps going over entries: what it sets up at its start is paid once; with a list of distinct
         //  states the number of entries is only known on the device, at most n)
-        const unsigned want = A.list ? (A.n + 1u) / 2u : A.n;
+        const unsigned want = A.from ? A.n : A.list ? (A.n + 1u) / 2u : A.n;
         const unsigned blocks = want < 2048u ? want : 2048u;
         hipError_t e = A.np == 2 ? allow_lds_f(k_front_classify<KW, MW, 2>, lds) : allow_lds_f(k_front_classify<KW, MW, 1>, lds);
         if (e != hipSuccess) return e;
         if (A.np == 2)
             hipLaunchKernelGGL((k_front_classify<KW, MW, 2>), dim3(blocks), dim3(kClsThreads), lds, stream, A.q, A.states, A.n, A.list,
-                               A.n_list, A.max_pairs, A.goals_only, A.count_children, A.codes, A.row_counts, A.unknown, A.ctr);
+                               A.n_list, A.from, A.max_pairs, A.goals_only, A.count_children, A.codes, A.row_counts, A.unknown, A.ctr);
         else
             hipLaunchKernelGGL((k_front_classify<KW, MW, 1>), dim3(blocks), dim3(kClsThreads), lds, stream, A.q, A.states, A.n, A.list,
-                               A.n_list, A.max_pairs, A.goals_only, A.count_children, A.codes, A.row_counts, A.unknown, A.ctr);
+                               A.n_list, A.from, A.max_pairs, A.goals_only, A.count_children, A.codes, A.row_counts, A.unknown, A.ctr);
     } else if (what == 3) {
         // a wavefront per state, four to a block
         const unsigned want = (A.n + 3u) / 4u;
         const unsigned blocks = want < 16384u ? want : 16384u;
         if (A.np == 2)
-            hipLaunchKernelGGL((k_front_goal_filter<KW, MW, 2>), dim3(blocks), dim3(256), 0, stream, A.q, A.states, A.n, A.list, A.n_list,
+            hipLaunchKernelGGL((k_front_goal_filter<KW, MW, 2>), dim3(blocks), dim3(256), 0, stream, A.q, A.states, A.n, A.list, A.n_list, A.from,
                                A.codes, A.row_counts, A.unknown, A.walk, A.n_walk);
         else
-            hipLaunchKernelGGL((k_front_goal_filter<KW, MW, 1>), dim3(blocks), dim3(256), 0, stream, A.q, A.states, A.n, A.list, A.n_list,
+            hipLaunchKernelGGL((k_front_goal_filter<KW, MW, 1>), dim3(blocks), dim3(256), 0, stream, A.q, A.states, A.n, A.list, A.n_list, A.from,
                                A.codes, A.row_counts, A.unknown, A.walk, A.n_walk);
     } else if (what == 4) {
         hipLaunchKernelGGL((k_front_literal_goals<KW, MW>), dim3(A.n < kLgBlocks ? A.n : kLgBlocks), dim3(kLgThreads), 0, stream, A.q, A.entries,
-                           A.parents, A.n, A.len, A.states, A.states2, A.owner, A.owner_per, A.surv, A.surv_cap, A.ctr, A.rest);
+                           A.parents, A.n, A.n_list, A.len, A.states, A.states2, A.owner, A.owner_per, A.surv, A.surv_cap, A.ctr, A.rest);
     } else {
         const size_t lds = (size_t)A.level->lds_planes * A.R * FL<KW, MW>::WS * 4;
-        const unsigned blocks = A.level->n_surv < 8192u ? A.level->n_surv : 8192u;
+        const unsigned most = A.level->blocks ? A.level->blocks : 8192u, blocks = A.level->n_surv < most ? A.level->n_surv : most;
         if (lds > kMatBigLds) {
             const hipError_t e = allow_lds_f(k_front_materialize<KW, MW, kMatThreadsBig>, lds);
             if (e != hipSuccess) return e;
@@ -2032,20 +2230,22 @@ hipError_t launch_front_prefixes(const DevQuery* queries, const FrontPrefixes& P
 }
 
 hipError_t launch_front_goal_filter(const DevQuery* q, int R, int k, const uint32_t* states, uint32_t n, const uint32_t* list,
-                                    const uint32_t* n_list, int np, uint8_t* codes, unsigned long long* row_counts, uint8_t* unknown,
-                                    uint32_t* walk, uint32_t* n_walk, hipStream_t stream) {
+                                    const uint32_t* n_list, const uint32_t* from, int np, uint8_t* codes, unsigned long long* row_counts,
+                                    uint8_t* unknown, uint32_t* walk, uint32_t* n_walk, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     FrontArgs A{};
+    A.from = from;
     A.q = q; A.states = states; A.n = n; A.np = np; A.list = list; A.n_list = n_list;
     A.codes = codes; A.unknown = unknown; A.R = R; A.walk = walk; A.n_walk = n_walk; A.row_counts = reinterpret_cast<uint2*>(row_counts);
     return front_dispatch(R, k, 3, A, stream);
 }
 
 hipError_t launch_front_classify(const DevQuery* q, int R, int k, const uint32_t* states, uint32_t n, const uint32_t* list,
-                                 const uint32_t* n_list, int np, int max_pairs, int goals_only, int count_children, uint8_t* codes,
-                                 unsigned long long* row_counts, uint8_t* unknown, FrontCounters* ctr, hipStream_t stream) {
+                                 const uint32_t* n_list, const uint32_t* from, int np, int max_pairs, int goals_only, int count_children,
+                                 uint8_t* codes, unsigned long long* row_counts, uint8_t* unknown, FrontCounters* ctr, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     FrontArgs A{};
+    A.from = from;
     A.q = q; A.states = states; A.n = n; A.np = np; A.max_pairs = max_pairs; A.list = list; A.n_list = n_list;
     A.codes = codes; A.unknown = unknown; A.R = R; A.goals_only = goals_only; A.count_children = count_children; A.ctr = ctr; A.row_counts = reinterpret_cast<uint2*>(row_counts);
     return front_dispatch(R, k, 1, A, stream);
@@ -2083,6 +2283,34 @@ hipError_t launch_front_expand(const DevQuery* q, const FrontEntry* entries, uin
     return hipGetLastError();
 }
 
+hipError_t launch_front_root(FrontCounters* ctr, FrontMarks* marks, uint32_t* rep, uint32_t* pos, uint32_t* reps_list, hipStream_t stream) {
+    hipLaunchKernelGGL(k_front_root, dim3(1), dim3(1), 0, stream, ctr, marks, rep, pos, reps_list);
+    return hipGetLastError();
+}
+hipError_t launch_front_mark(const FrontCounters* ctr, FrontMarks* marks, int level, hipStream_t stream) {
+    hipLaunchKernelGGL(k_front_mark, dim3(1), dim3(1), 0, stream, ctr, marks, level);
+    return hipGetLastError();
+}
+hipError_t launch_front_edges(const DevQuery* q, const uint32_t* list, const uint32_t* n_list, const uint32_t* from, const uint8_t* codes,
+                              const uint8_t* unknown, int np, int level, unsigned blocks, const FrontEdges& A, hipStream_t stream) {
+    hipLaunchKernelGGL(k_front_edges, dim3(blocks), dim3(256), 0, stream, q, list, n_list, from, codes, unknown, np, level, A);
+    return hipGetLastError();
+}
+hipError_t launch_front_find(const uint32_t* states, size_t state_words, const unsigned long long* hash, const uint32_t* from, const uint32_t* to,
+                             uint32_t cap, unsigned long long* table, uint32_t table_size, uint32_t* rep, uint32_t* pos, uint32_t* reps_list,
+                             uint32_t* n_reps, unsigned blocks, hipStream_t stream) {
+    hipLaunchKernelGGL(k_front_find, dim3((blocks + 3u) / 4u), dim3(256), 0, stream, hash, from, to, cap, table, table_size - 1u, rep, pos, reps_list, n_reps);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_front_compare, dim3(blocks), dim3(256), 0, stream, reinterpret_cast<const uint4*>(states), (uint32_t)(state_words / 4), from, to,
+                       cap, rep, pos, reps_list, n_reps);
+    return hipGetLastError();
+}
+hipError_t launch_front_links(const FrontLinks& A, unsigned blocks, hipStream_t stream) {
+    hipLaunchKernelGGL(k_front_links, dim3(blocks), dim3(256), 0, stream, A);
+    return hipGetLastError();
+}
+
 hipError_t launch_front_counters_out(FrontCounters* host_dst, FrontCounters* ctr, hipStream_t stream) {
     hipLaunchKernelGGL(k_front_counters_out, dim3(1), dim3(64), 0, stream, host_dst, ctr);
     return hipGetLastError();
@@ -2099,12 +2327,12 @@ size_t front_literal_goals_scratch_bytes(int R, int k, uint32_t n) {
     return (size_t)(n < kLgBlocks ? n : kLgBlocks) * (size_t)(R / 2 > 0 ? R / 2 : 1) * (size_t)k * sizeof(uint16_t);
 }
 hipError_t launch_front_literal_goals(const DevQuery* q, int R, int k, const FrontEntry* entries, const uint32_t* parents, uint32_t n,
-                                      int len, const uint32_t* states1, const uint32_t* states2, void* scratch, FrontSurvivor* surv,
+                                      const uint32_t* n_dev, int len, const uint32_t* states1, const uint32_t* states2, void* scratch, FrontSurvivor* surv,
                                       uint32_t surv_cap, FrontCounters* ctr, uint32_t* rest, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (len < 1 || !scratch) return hipErrorInvalidValue;
     FrontArgs A{};
-    A.q = q; A.entries = entries; A.parents = parents; A.n = n; A.len = len; A.states = states1; A.states2 = states2; A.R = R;
+    A.q = q; A.entries = entries; A.parents = parents; A.n = n; A.n_list = n_dev; A.len = len; A.states = states1; A.states2 = states2; A.R = R;
     A.owner = static_cast<uint16_t*>(scratch); A.owner_per = (unsigned long long)(R / 2 > 0 ? R / 2 : 1) * (unsigned long long)k;
     A.surv = surv; A.surv_cap = surv_cap; A.ctr = ctr; A.rest = rest;
     return front_dispatch(R, k, 4, A, stream);

@@ -22,6 +22,9 @@
 // for a block of k / R consecutive ones.  A ReduceScatter deals blocks out, so this is exact unless it had to cut one
 // in two; that is checked at every ReduceScatter and reported as well.  What is reported is evaluated by the other
 // engines.
+//
+// Groups that are larger or have other patterns bring their edges from the frontier's kernels (p2_frontier.hip) and are
+// counted, costed and listed here.
 #include "p2_compact_dev.h"
 
 #include <type_traits>
@@ -32,7 +35,7 @@ namespace {
 
 using u64 = unsigned long long;
 constexpr int kMostPairs = 4;
-constexpr uint32_t kChunk = 16;         // planes a wavefront reserves at a time (a returning addition to one address takes some 10 ns)
+constexpr uint32_t kChunk = 8;          // planes a wavefront reserves at a time (a returning addition to one address takes some 10 ns)
 constexpr uint32_t kPlaneMask = 0x0fffffffu;
 constexpr uint32_t kGoalEdge = 0x7fffffu;   // target of an edge that ends at the goal
 constexpr int kDigitShift = 23;
@@ -80,6 +83,9 @@ struct Graph {
     uint32_t query;
     int R, rows_kept, n_pat, n_ops, alphabet, max_len, W, n_members;
     uint32_t op_mask, op_ranks, split_check, fused;
+    bool links_ready;
+    P2_GLOBAL const u32x4* large[2];
+    int wq, qk;
     uint32_t cap_nodes, cap_planes, cap_found, cap_edges, table_mask;
     u64 all_rows, all_cols;
     P2_GLOBAL GraphCounters* ctr;
@@ -100,6 +106,8 @@ __device__ __forceinline__ void open_graph(Graph<Where>& G, const DevGraph& D) {
     G.op_mask = D.op_mask; G.op_ranks = D.op_ranks; G.split_check = D.split_check; G.fused = D.fused;
     G.cap_nodes = D.cap_nodes; G.cap_planes = D.cap_planes; G.cap_found = D.cap_found; G.cap_edges = D.cap_edges; G.table_mask = D.table_mask;
     G.all_rows = D.all_rows; G.all_cols = D.all_cols;
+    G.links_ready = D.large[0] != nullptr; G.wq = D.wq; G.qk = D.qk;
+    G.large[0] = in_global<const u32x4>(D.large[0]); G.large[1] = in_global<const u32x4>(D.large[1]);
     G.ctr = in_global<GraphCounters>(D.ctr); G.table = in_global<u64>(D.table);
     G.planes_out = in_global<u64x2>(D.planes);
     G.first_edge = in_global<uint32_t>(D.first_edge); G.use_ends = in_global<uint32_t>(D.use_ends);
@@ -660,6 +668,7 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
     }
     uint8_t* const bytes = reinterpret_cast<uint8_t*>(scratch);
     // (the children by their nodes instead of their slots)
+    if (!G.links_ready)
     for (uint32_t e = tid; e < n_found; e += T) {
         const u32x4 f = G.found[e];
         G.links[e] = u32x2{f.x, f.y == kGoalEdge ? kGoalEdge : G.table_node[f.y] - 1u};
@@ -833,72 +842,93 @@ __global__ __launch_bounds__(kAloneThreads) void k_graph_alone(const DevGraph* _
 constexpr int kStepWaves = 4;
 __global__ __launch_bounds__(kStepWaves * kWave) void k_graph_steps(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
                                                                     const GraphBlock* __restrict__ blocks) {
-    __shared__ uint32_t srows[kStepWaves][kWave];
+    __shared__ uint16_t srows[kStepWaves][P2_MAX_DEVICES];
     const GraphBlock b = blocks[blockIdx.x];
     const Graph<InDevice> G = open_in_device(graphs[b.graph]);
     if (G.ctr->flags != 0u) return;
     const DevQuery& q = queries[G.query];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int R = G.R, dev = lane & (R - 1);
+    const int R = G.R;
+    uint16_t* const rows = srows[wave];                  // (a wavefront's own: no barriers)
     const uint32_t n_edges = G.ctr->n_edges, per_pass = b.count * (uint32_t)kStepWaves;
-    for (uint32_t e0 = b.index * (uint32_t)kStepWaves; e0 < n_edges; e0 += per_pass) {
-        const uint32_t e = e0 + (uint32_t)wave;
-        const bool active = e < n_edges;
-        int pid = 0, op = 0;
-        uint32_t c = 0u;
-        bool uniform = true;
-        if (active) {
-            const uint32_t state = G.edge_state[e];
-            const uint32_t ins = q.instr_of_digit[G.edges[e] >> kDigitShift];
-            pid = (int)(ins >> 3); op = (int)(ins & 7u);
-            const uint32_t shape = q.reg_shape[pid];
-            const int lg = (int)(shape & 15u), ls = (int)((shape >> 4) & 15u), gmask = ((1 << lg) - 1) << ls;
-            const bool in = ((q.reg_part[pid] >> dev) & 1ull) != 0ull;
+    for (uint32_t e = b.index * (uint32_t)kStepWaves + (uint32_t)wave; e < n_edges; e += per_pass) {
+        const uint32_t state = G.edge_state[e];
+        const uint32_t ins = q.instr_of_digit[G.edges[e] >> kDigitShift];
+        const int pid = (int)(ins >> 3), op = (int)(ins & 7u);
+        const int g = q.pat[pid].g, s = q.pat[pid].s, master = q.pat[pid].master, ng = q.pat[pid].n_groups;
+        // rows held by every device (its pairs' rows are disjoint)
+        if (!G.links_ready) {
             const P2_GLOBAL u64x2* const plane = G.planes + (size_t)(state & kPlaneMask) * R;
-            u64 rows = 0ull;
-            for (uint32_t p = 0; p < (state >> 28); ++p) rows |= plane[(size_t)p * R + dev].x;
-            // the chunks that set a group's bytes: the members' common ones, the root's, or all that an AllGather brings together
-            c = (uint32_t)__popcll(rows);
-            if (op == OP_AG)
-                for (int J = ls; J < ls + lg; ++J) c += (uint32_t)__shfl_xor((int)c, 1 << J, kWave);
-            const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);      // (device 0 is a root of every pattern)
-            uniform = !__any(in && (dev & gmask) == 0 && c != c0);
-            srows[wave][lane] = c;
-            c = c0;
-        }
-        __syncthreads();
-        if (active) {
-            P2_GLOBAL double* const out = G.best + (size_t)e * G.n_members;
-            if (uniform) {
-                for (int j = lane; j < G.n_members; j += kWave) {
-                    const DevQuery& cq = queries[G.members[j]];
-                    const DevRows& rw = *cq.rows;
-                    const long long n = (long long)c * (long long)(cq.k / G.rows_kept);
-                    double best = 0.0;
-                    for (int l = 0; l < cq.n_levels; ++l) best = fmax(best, (double)(n * (long long)rw.level_max[pid][l]) * cq.inv_bw[l]);
-                    out[j] = best;
-                }
-            } else {
-                for (int j = 0; j < G.n_members; ++j) {
-                    const DevQuery& cq = queries[G.members[j]];
-                    const DevRows& rw = *cq.rows;
-                    const long long per = (long long)(cq.k / G.rows_kept);
-                    double best = 0.0;
-                    for (int row = rw.pat_begin[pid] + lane; row < rw.pat_begin[pid + 1]; row += kWave) {
-                        long long dot = 0;
-                        const int end = rw.row_ptr[row + 1];
-                        for (int x = rw.row_ptr[row]; x < end; ++x) {
-                            const uint32_t ent = rw.entries[x];
-                            dot += (long long)entry_cnt(ent) * (long long)srows[wave][entry_base(ent)];
-                        }
-                        best = fmax(best, (double)(dot * per) * cq.inv_bw[rw.row_level[row]]);
+            if (lane < R) {
+                int c = 0;
+                for (uint32_t p = 0; p < (state >> 28); ++p) c += __popcll(plane[(size_t)p * R + lane].x);
+                rows[lane] = (uint16_t)c;
+            }
+        } else {
+            const int np = (int)(state >> 28), plane = R * G.wq;
+            const P2_GLOBAL u32x4* const at = G.large[np - 1] + (size_t)(state & kPlaneMask) * (size_t)(np * plane);
+            for (int d = lane; d < R; d += kWave) {
+                int c = 0;
+                for (int p = 0; p < np; ++p)
+                    for (int x = 0; x < G.qk; ++x) {
+                        const u32x4 v = at[p * plane + d * G.wq + x];
+                        c += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
                     }
-                    for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off, kWave));
-                    if (lane == 0) out[j] = best;
-                }
+                rows[d] = (uint16_t)c;
             }
         }
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // the chunks that set a group's bytes, at its first device: the members' common ones, the root's, or all that an
+        // AllGather brings together
+        auto base_of = [&](int i) { return master ? i * g * s : (i / s) * g * s + i % s; };
+        if (op == OP_AG)
+            for (int i = lane; i < ng; i += kWave) {
+                const int base = base_of(i);
+                uint32_t c = 0u;
+                for (int m = 0; m < g; ++m) c += rows[base + m * s];
+                rows[base] = (uint16_t)c;                // (the groups do not meet)
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t c0 = rows[0];                     // (device 0 is a root of every pattern)
+        bool same = true;
+        for (int i = lane; i < ng; i += kWave) same &= rows[base_of(i)] == c0;
+        P2_GLOBAL double* const out = G.best + (size_t)e * G.n_members;
+        if (!__any(!same)) {
+            for (int j = lane; j < G.n_members; j += kWave) {
+                const DevQuery& cq = queries[G.members[j]];
+                const DevRows& rw = *cq.rows;
+                const long long n = (long long)c0 * (long long)(cq.k / G.rows_kept);
+                double best = 0.0;
+                for (int l = 0; l < cq.n_levels; ++l) best = fmax(best, (double)(n * (long long)rw.level_max[pid][l]) * cq.inv_bw[l]);
+                out[j] = best;
+            }
+        } else {
+            for (int j = 0; j < G.n_members; ++j) {
+                const DevQuery& cq = queries[G.members[j]];
+                const DevRows& rw = *cq.rows;
+                const long long per = (long long)(cq.k / G.rows_kept);
+                double best = 0.0;
+                for (int row = rw.pat_begin[pid] + lane; row < rw.pat_begin[pid + 1]; row += kWave) {
+                    long long dot = 0;
+                    int x = rw.row_ptr[row];
+                    const int end = rw.row_ptr[row + 1];
+                    for (; x + 8 <= end; x += 8) {       // (eight entries in flight)
+                        uint32_t ent[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) ent[u] = rw.entries[x + u];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) dot += (long long)entry_cnt(ent[u]) * (long long)rows[entry_base(ent[u])];
+                    }
+                    for (; x < end; ++x) {
+                        const uint32_t ent = rw.entries[x];
+                        dot += (long long)entry_cnt(ent) * (long long)rows[entry_base(ent)];
+                    }
+                    best = fmax(best, (double)(dot * per) * cq.inv_bw[rw.row_level[row]]);
+                }
+                for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off, kWave));
+                if (lane == 0) out[j] = best;
+            }
+        }
     }
 }
 
@@ -1024,6 +1054,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
 
 }  // namespace
 
+uint32_t graph_planes_left(uint32_t blocks, int max_len) { return kChunk * (uint32_t)(kLevelThreads / kWave) * blocks * (uint32_t)(max_len > 1 ? max_len - 1 : 1); }
 bool graph_alone_holds(uint32_t nodes) { return nodes <= kAloneNodes; }
 hipError_t launch_graph_alone(const DevGraph* graphs, const uint32_t* list, unsigned n, int max_R, hipStream_t stream) {
     if (n == 0) return hipSuccess;

@@ -65,6 +65,48 @@ def test_graph_matches_the_enumeration(card, max_len, more):
         assert a["stats"]["valid"] == b["stats"]["valid"] and 0 < a["stats"]["steps_executed"] <= b["stats"]["steps_executed"]
 
 
+# Groups that the frontier's kernels build the graph of: more than 64 devices, levels that are no power of two; rows that are
+# blocks of chunks; children that need a third pair judged at the size limit (six instructions) and left to the enumeration
+# (seven); tree costs
+LARGE = [([3, 4, 6], 4, {}), ([3, 4, 6], 5, dict(algo=1)), ([128], 4, {}), ([2, 8, 8], 4, dict(n_chunks=512)), ([2, 8, 8], 3, dict(n_chunks=96)),
+         ([3, 5, 7], 4, dict(n_chunks=210, op_mask=0b11101)), ([5, 2, 2, 6], 4, dict(form_mask=3)), ([2, 2, 4, 8], 6, {}), ([3, 2, 12], 7, {}), ([6, 6], 6, {})]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,more", LARGE)
+def test_large_graph_matches_the_enumeration(card, max_len, more):
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, **more)
+    alone = B.p2_synthesize_batch([q], MSG)[0]
+    listed, short = B.p2_synthesize_batch([dict(q, bw=q["bw"][::-1]), dict(q, topk=9)], MSG)
+    want, want_b = B.p2_synthesize_batch([dict(q, engine=3), dict(q, engine=3, bw=q["bw"][::-1])], MSG)
+    for a, w in ((alone, want), (listed, want_b)):
+        assert np.array_equal(a["programs"], w["programs"])
+        assert np.allclose(a["cost"], w["cost"], rtol=1e-14, atol=0.0)
+        assert a["stats"]["valid"] == w["stats"]["valid"] and a["stats"]["candidates"] == w["stats"]["candidates"]
+        assert a["stats"]["steps_executed"] > 0
+    kk = min(9, len(want["programs"]))
+    for m in range(len(MSG)):
+        best = np.lexsort((alone["programs"]["index"], alone["cost"][:, m]))[:kk]
+        assert np.array_equal(short["programs"]["index"][m * kk:(m + 1) * kk], alone["programs"]["index"][best])
+
+
+@pytest.mark.gpu
+def test_large_graphs_side_by_side():
+    """Several large groups on streams of their own beside small ones, and one after the other: the same bytes."""
+    from paper_2110_10548_amd import binding as B
+    queries = [_query(c, m, topk=k) for c, m, k in (([3, 4, 6], 4, 0), ([9, 8], 4, 5), ([2, 4, 4], 4, 0), ([2, 8, 8], 4, 7), ([12, 12], 4, 0), ([80], 4, 0),
+                                                    ([4, 4], 4, 3), ([5, 2, 2, 6], 3, 0))]
+    side = B.p2_synthesize_batch(queries, MSG)
+    one = B.p2_synthesize_batch([dict(q, flags=B.FLAG_ONE_ENUMERATION_AT_A_TIME) for q in queries], MSG)
+    for q, a, b in zip(queries, side, one):
+        alone = B.p2_synthesize_batch([q], MSG)[0]
+        for r in (b, alone):
+            assert np.array_equal(a["programs"], r["programs"]) and np.array_equal(a["cost"], r["cost"])
+            for key in COUNTS:
+                assert a["stats"][key] == r["stats"][key], key
+
+
 @pytest.mark.gpu
 def test_graphs_beside_other_engines():
     """Queries answered from graphs, walked and enumerated in one batch, each as alone."""
