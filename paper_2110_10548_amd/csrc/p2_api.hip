@@ -5,7 +5,6 @@
 #include <cstddef>
 #include <cstring>
 #include <atomic>
-#include <functional>
 #include <thread>
 #include <limits>
 #include <string>
@@ -457,6 +456,7 @@ struct QueryRun {
     int enum_id = -1, share_pos = 0;      // frontier: its enumeration, and its place among the enumeration's queries
     int topk = 0;
     size_t off_query = 0, off_rowptr = 0, off_rowlevel = 0, off_entries = 0;
+    int rows_at = 0;                      // its bandwidth rows' place among the distinct ones
     size_t off_goal = 0, off_rank = 0;    // hierarchies other than the collapsed one: goal masks, ranks of members
     int same_as = -1;                     // an earlier query of the batch with the same reduction group, chunks, patterns,
                                           // alphabet and size limit: its valid programs are this query's too
@@ -486,8 +486,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     const auto t_begin = std::chrono::steady_clock::now();
     std::vector<QueryRun> runs(n_queries);
     {
-        // (the bandwidth rows of the cost model are built later, while the GPU evaluates; large batches: the
-        //  queries' plans are independent, a few host threads share them)
+        // (the bandwidth rows of the cost model are built later, while the GPU evaluates; large batches: the queries' plans are
+        //  independent, and host threads share them, one per 64: a plan takes 1 to 2 us, to start a thread some 30)
         std::vector<int32_t> plan_st((size_t)n_queries, P2_OK);
         std::vector<std::string> plan_err((size_t)n_queries);
         auto plan_one = [&](int i) {
@@ -496,7 +496,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                                    runs[i].plan, plan_err[i], false);
         };
         const unsigned hw = std::thread::hardware_concurrency();
-        const int n_threads = n_queries >= 64 ? (int)std::min<unsigned>(std::max(hw, 1u), 8u) : 1;
+        const int n_threads = (int)std::min<unsigned>({std::max(hw, 1u), 8u, (unsigned)n_queries / 64u + 1u});
         if (n_threads <= 1) {
             for (int i = 0; i < n_queries; ++i) plan_one(i);
         } else {
@@ -800,13 +800,23 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     const size_t off_msg = off;
     off += align_up(sizeof(double) * (size_t)std::max(n_msg, 1), 256);
     const size_t blob_bytes = off;
-    // The bandwidth rows (cost model) live in buffers of their own: the rows, and per query a header (DevRows)
-    // that the query descriptor points at.  They are built on the host after the evaluation kernels have been
+    // The bandwidth rows (cost model) live in buffers of their own: the rows, and per distinct set of rows a header
+    // (DevRows) that the query descriptors point at.  They are built on the host after the evaluation kernels have been
     // queued and uploaded on a second stream, so both overlap with the evaluation; the call's stream waits
-    // for the upload before its first cost kernel.
+    // for the upload before its first cost kernel.  Queries whose rows are the same share them, and those of the collapsed
+    // hierarchy follow from the factors; worked out for every query, from the devices under every unit, the rows were most of
+    // a batch's host time (140 queries of [4 8 8]: 1 000 us of the call's 1 590 with eight threads, the call takes 540 now;
+    // 512 queries of [2 4 8 8], 96 distinct sets: 5 600 us, and 400 now without a thread).
+    std::vector<int32_t> row_sets;                       // a query of each
+    for (int i = 0; i < n_queries; ++i) {
+        size_t t = 0;
+        while (t < row_sets.size() && !same_cost_rows(runs[row_sets[t]].plan, runs[i].plan)) ++t;
+        if (t == row_sets.size()) row_sets.push_back(i);
+        runs[i].rows_at = (int)t;
+    }
     bool rows_ready = false;
-    P2_HIP(C.rows_hdr.ensure(sizeof(DevRows) * (size_t)std::max(n_queries, 1)));
-    P2_HIP(C.h_rows_hdr.ensure(sizeof(DevRows) * (size_t)std::max(n_queries, 1)));
+    P2_HIP(C.rows_hdr.ensure(sizeof(DevRows) * row_sets.size()));
+    P2_HIP(C.h_rows_hdr.ensure(sizeof(DevRows) * row_sets.size()));
     if (!C.copy_stream) {
         P2_HIP(hipStreamCreateWithFlags(&C.copy_stream, hipStreamNonBlocking));
         P2_HIP(hipEventCreateWithFlags(&C.copy_done, hipEventDisableTiming));
@@ -831,20 +841,9 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     auto build_and_upload_rows = [&]() -> int32_t {
         if (rows_ready) return P2_OK;
         size_t bytes = 0;
-        // (large batches: the queries' tables are independent, a few host threads share them, for building and for packing)
-        const unsigned hw = std::thread::hardware_concurrency();
-        const int n_threads = n_queries >= 256 ? (int)std::min<unsigned>(std::max(hw, 1u), 16u) : n_queries >= 32 ? (int)std::min<unsigned>(std::max(hw, 1u), 8u) : 1;
-        auto for_every_query = [&](const std::function<void(int)>& f) {
-            if (n_threads <= 1) { for (int i = 0; i < n_queries; ++i) f(i); return; }
-            std::atomic<int> next{0};
-            auto work = [&]() { for (int i = next.fetch_add(1); i < n_queries; i = next.fetch_add(1)) f(i); };
-            std::vector<std::thread> pool;
-            for (int t = 1; t < n_threads; ++t) pool.emplace_back(work);
-            work();
-            for (auto& th : pool) th.join();
-        };
-        if (n_msg > 0) for_every_query([&](int i) { build_cost_tables(runs[i].plan); });    // without message sizes the tables stay empty
-        for (auto& r : runs) {
+        for (int32_t i : row_sets) {
+            QueryRun& r = runs[i];
+            if (n_msg > 0) build_cost_tables(r.plan);    // without message sizes the tables stay empty
             size_t n_rows = 0, n_ent = 0;
             for (const Pattern& p : r.plan.patterns) { n_rows += p.row_level.size(); n_ent += p.entries.size(); }
             r.off_rowptr = bytes; bytes += align_up(sizeof(int32_t) * (n_rows + 1), 16);
@@ -856,13 +855,13 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         char* hr = static_cast<char*>(C.h_rows.p);
         char* dr = static_cast<char*>(C.rows.p);
         DevRows* hdr = static_cast<DevRows*>(C.h_rows_hdr.p);
-        for_every_query([&](int i) {
+        for (int32_t i : row_sets) {
             const QueryRun& r = runs[i];
             const Plan& pl = r.plan;
             int32_t* rp = reinterpret_cast<int32_t*>(hr + r.off_rowptr);
             int32_t* rl = reinterpret_cast<int32_t*>(hr + r.off_rowlevel);
             uint32_t* en = reinterpret_cast<uint32_t*>(hr + r.off_entries);
-            DevRows& H = hdr[i];
+            DevRows& H = hdr[r.rows_at];
             std::memset(&H, 0, sizeof H);
             int row = 0, ent = 0;
             rp[0] = 0;
@@ -881,15 +880,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             H.row_ptr = reinterpret_cast<const int32_t*>(dr + r.off_rowptr);
             H.row_level = reinterpret_cast<const int32_t*>(dr + r.off_rowlevel);
             H.entries = reinterpret_cast<const uint32_t*>(dr + r.off_entries);
-        });
+        }
         rows_ready = true;
         if (only_graphs && large_slots == 1) {           // (else the call's stream has the slots to wait for)
-            const CopyPart up[2] = {{C.rows.p, C.h_rows.p, bytes}, {C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * (size_t)n_queries}};
+            const CopyPart up[2] = {{C.rows.p, C.h_rows.p, bytes}, {C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * row_sets.size()}};
             P2_HIP(launch_copies(up, 2, stream));
             return P2_OK;
         }
         P2_HIP(hipMemcpyAsync(C.rows.p, C.h_rows.p, bytes, hipMemcpyHostToDevice, C.copy_stream));
-        P2_HIP(hipMemcpyAsync(C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * (size_t)n_queries, hipMemcpyHostToDevice, C.copy_stream));
+        P2_HIP(hipMemcpyAsync(C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * row_sets.size(), hipMemcpyHostToDevice, C.copy_stream));
         P2_HIP(hipEventRecord(C.copy_done, C.copy_stream));
         P2_HIP(hipStreamWaitEvent(stream, C.copy_done, 0));
         return P2_OK;
@@ -1217,7 +1216,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 }
                 dq->rank_tbl = reinterpret_cast<const int32_t*>(db + r.off_rank);
             }
-            dq->rows = static_cast<const DevRows*>(C.rows_hdr.p) + i;
+            dq->rows = static_cast<const DevRows*>(C.rows_hdr.p) + runs[i].rows_at;
             dq->reg_sum_part = 0;
             for (size_t pi = 0; pi < pl.patterns.size(); ++pi) {
                 const Pattern& p = pl.patterns[pi];

@@ -127,6 +127,37 @@ inline int group_base(const Pattern& p, int group) {       // local id of the gr
     return p.master ? group * p.g * p.s : (group / p.s) * p.g * p.s + group % p.s;
 }
 
+// The rows of a pattern of the collapsed hierarchy, written down directly: nothing but the factors enters, so placements
+// that agree in them share their rows (same_cost_rows).  A unit of level j fixes the digits of the levels up to j.  It meets
+// the groups whose fixed digits (those outside the varied levels lo..hi; with `master` the ones below hi are zero) agree with
+// its own, whatever its varied digits are, and each of them in the copies that its levels further in hold: units of a level
+// that meet a group in common meet the same groups equally often, and one of them is the row.  In the order of their first
+// units, which is that of the fixed digits.
+void collapsed_cost_rows(const Plan& pl, Pattern& p) {
+    p.row_ptr.assign(1, 0);
+    p.row_level.clear();
+    p.entries.clear();
+    int copies = pl.D / pl.R, heads = 1, tails = 1;             // copies of the reduction group in a unit; rows are heads x tails
+    for (int j = 0; j < p.lo; ++j) heads *= pl.f[j];
+    for (int j = 0; j < pl.n; ++j) {
+        copies /= pl.h[j] / pl.f[j];
+        if (j < p.lo) continue;
+        if (j > p.hi && !p.master) tails *= pl.f[j];
+        const int per = p.master ? 1 : p.s / tails;             // groups of a row
+        const int n_rows = heads * tails;
+        const size_t first_row = p.row_level.size(), first = p.entries.size();
+        p.row_level.resize(first_row + n_rows, j);
+        p.row_ptr.resize(first_row + 1 + n_rows);
+        p.entries.resize(first + (size_t)n_rows * per);
+        for (int row = 0, group = 0; row < n_rows; ++row) {
+            for (int t = 0; t < per; ++t, ++group)
+                p.entries[first + group] = entry_pack((uint32_t)group, (uint32_t)group_base(p, group), (uint32_t)copies);
+            p.row_ptr[first_row + 1 + row] = (int32_t)(first + group);
+        }
+    }
+}
+
+// The rows of a pattern of any hierarchy, from the devices under each unit.
 void build_cost_rows(const Plan& pl, Pattern& p) {
     // scratch kept between calls: this runs for every pattern of every query of every call
     thread_local std::vector<int32_t> stamp, cnt, touched, row_begin, group_of, key_of, table, by_group_at, by_group, fill_at;
@@ -227,6 +258,34 @@ void build_cost_rows(const Plan& pl, Pattern& p) {
             p.row_ptr.push_back((int32_t)p.entries.size());
             p.row_level.push_back(j);
         }
+    }
+}
+
+// The devices of a plan of the collapsed hierarchy: their local ids and copies (asked for where a pattern is described; the
+// tables that the kernels read follow from the factors).
+void number_collapsed(const Plan& pl, std::vector<int32_t>& local_of, std::vector<int32_t>& replica_of) {
+    // Devices: id = mixed radix of hardware coordinates; inside a level the coordinate is a mixed
+    // radix of the axis digits, axis 0 most significant.  Split every coordinate into its
+    // reduce-axis part (-> local id) and the rest (-> replica).
+    local_of.resize(pl.D);
+    replica_of.resize(pl.D);
+    for (int d = 0; d < pl.D; ++d) {
+        int coord[P2_MAX_LEVELS], rest = d;
+        for (int j = pl.n - 1; j >= 0; --j) { coord[j] = rest % pl.h[j]; rest /= pl.h[j]; }
+        int local = 0, rep = 0;
+        for (int j = 0; j < pl.n; ++j) {
+            int c = coord[j], gdig = 0, rdig = 0, gmul = 1, rmul = 1;
+            for (int i = pl.m - 1; i >= 0; --i) {          // least significant axis first
+                int a = c % pl.x[i][j];
+                c /= pl.x[i][j];
+                if (pl.is_reduce[i]) { gdig += a * gmul; gmul *= pl.x[i][j]; }
+                else { rdig += a * rmul; rmul *= pl.x[i][j]; }
+            }
+            local = local * pl.f[j] + gdig;
+            rep = rep * (pl.h[j] / pl.f[j]) + rdig;
+        }
+        local_of[d] = local;
+        replica_of[d] = rep;
     }
 }
 
@@ -412,29 +471,6 @@ int32_t make_plan(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes, co
                 if (pl.is_reduce[i]) pl.f[j] *= pl.x[i][j];
             pl.R *= pl.f[j];
         }
-        // Devices: id = mixed radix of hardware coordinates; inside a level the coordinate is a mixed
-        // radix of the axis digits, axis 0 most significant.  Split every coordinate into its
-        // reduce-axis part (-> local id) and the rest (-> replica).
-        pl.local_of.resize(pl.D);
-        pl.replica_of.resize(pl.D);
-        for (int d = 0; d < pl.D; ++d) {
-            int coord[P2_MAX_LEVELS], rest = d;
-            for (int j = pl.n - 1; j >= 0; --j) { coord[j] = rest % pl.h[j]; rest /= pl.h[j]; }
-            int local = 0, rep = 0;
-            for (int j = 0; j < pl.n; ++j) {
-                int c = coord[j], gdig = 0, rdig = 0, gmul = 1, rmul = 1;
-                for (int i = n_axes - 1; i >= 0; --i) {          // least significant axis first
-                    int a = c % pl.x[i][j];
-                    c /= pl.x[i][j];
-                    if (pl.is_reduce[i]) { gdig += a * gmul; gmul *= pl.x[i][j]; }
-                    else { rdig += a * rmul; rmul *= pl.x[i][j]; }
-                }
-                local = local * pl.f[j] + gdig;
-                rep = rep * (pl.h[j] / pl.f[j]) + rdig;
-            }
-            pl.local_of[d] = local;
-            pl.replica_of[d] = rep;
-        }
         for (int j = 0; j < pl.n; ++j) { lf.push_back(pl.f[j]); lspan.push_back(j); }
     } else {
         st = number_by_levels(pl, lf, lspan, err);
@@ -449,6 +485,7 @@ int32_t make_plan(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes, co
     // first occurrence keeps the id.
     std::vector<int> suffix(sl + 1, 1);                         // suffix[j] = prod lf[j..sl-1]
     for (int j = sl - 1; j >= 0; --j) suffix[j] = suffix[j + 1] * lf[j];
+    pl.patterns.reserve((size_t)sl * sl + sl);
     auto add = [&](int slice, int form, int form_level, int a, int b) {   // synthesis levels a..b vary
         int lo = -1, hi = -1, span = pl.n;
         for (int j = a; j <= b; ++j)
@@ -485,22 +522,32 @@ int32_t make_plan(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes, co
         pl.base[l + 1] = total;
     }
     pl.n_candidates = total;
-    if (with_cost && build_rows)
-        for (Pattern& p : pl.patterns) build_cost_rows(pl, p);
+    if (with_cost && build_rows) build_cost_tables(pl);
     return P2_OK;
 }
 
 void build_cost_tables(Plan& pl) {
-    for (Pattern& p : pl.patterns) build_cost_rows(pl, p);
+    for (Pattern& p : pl.patterns) {
+        if (pl.hierarchy == P2_HIERARCHY_COLLAPSED) collapsed_cost_rows(pl, p);
+        else build_cost_rows(pl, p);
+    }
+}
+
+bool same_cost_rows(const Plan& a, const Plan& b) {
+    if (a.hierarchy != P2_HIERARCHY_COLLAPSED || b.hierarchy != a.hierarchy || a.n != b.n || a.D != b.D || a.R != b.R || a.form_mask != b.form_mask)
+        return false;
+    return std::equal(a.h, a.h + a.n, b.h) && std::equal(a.f, a.f + a.n, b.f);
 }
 
 void describe_pattern(const Plan& pl, int pattern_id, int32_t* group_of_device, int32_t* rank_in_group) {
     const Pattern& p = pl.patterns[pattern_id];
+    std::vector<int32_t> local_of = pl.local_of, replica_of = pl.replica_of;
+    if (local_of.empty()) number_collapsed(pl, local_of, replica_of);
     std::map<std::pair<int, int>, int> ids;
     for (int d = 0; d < pl.D; ++d) {
-        int loc = pl.local_of[d];
+        int loc = local_of[d];
         if (!takes_part(p, loc)) { group_of_device[d] = -1; rank_in_group[d] = -1; continue; }
-        auto key = std::make_pair(pl.replica_of[d], local_group(p, loc));
+        auto key = std::make_pair(replica_of[d], local_group(p, loc));
         auto it = ids.find(key);
         if (it == ids.end()) it = ids.emplace(key, (int)ids.size()).first;
         group_of_device[d] = it->second;

@@ -65,8 +65,8 @@ struct Plan {
     int max_len = 0;
     uint64_t n_candidates = 0;
     uint64_t base[P2_MAX_LEN + 2] = {0};   // base[l] = index of the first program of length l
-    std::vector<int32_t> local_of;         // [D] local id of a device inside its reduction group
-    std::vector<int32_t> replica_of;       // [D] which copy the device belongs to
+    std::vector<int32_t> local_of;         // [D] local id of a device inside its reduction group; empty: collapsed hierarchy
+    std::vector<int32_t> replica_of;       // [D] which copy the device belongs to; empty as well
 };
 
 // Returns P2_OK or an error code; `err` gets the reason.  with_cost: the links must be given, and the
@@ -78,6 +78,8 @@ int32_t make_plan(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes, co
                   Plan& plan, std::string& err, bool build_rows = true);
 // The bandwidth rows of every pattern of a plan made without them (make_plan with with_cost = false).
 void build_cost_tables(Plan& plan);
+// Whether these rows are the same for both plans (which may differ in links, chunks, axes and what is asked).
+bool same_cost_rows(const Plan& a, const Plan& b);
 // Group id / rank of every device of the full system for one canonical pattern.
 void describe_pattern(const Plan& plan, int pattern_id, int32_t* group_of_device, int32_t* rank_in_group);
 
