@@ -169,7 +169,9 @@ constexpr uint32_t kFlagEmpty = 1u, kFlagGoal = 2u, kFlagTwo = 4u;
 constexpr uint32_t kPfBadRed = 1u, kPfBadB = 2u, kPfUnal = 4u, kPfBadRs = 8u, kPfBadAg = 16u, kPfChanged = 32u, kPfAgUneq = 64u,
                    kPfBadBc1 = 128u, kPfBcFail = 256u, kPfAnyTwo = 512u, kPfNgAr = 1024u, kPfNgAg = 2048u, kPfNgBc = 4096u,
                    kPfPatTwo = 8192u;
-constexpr int kClsChunks = 8;          // a pattern's groups go to the wavefronts in at most this many runs
+// ... and the second walks that some patterns need
+constexpr uint32_t kP2Many = 1u, kP2BcBad = 2u, kP2BcTwo = 4u, kP2BcShort = 8u, kP2Straddles = 16u;
+constexpr int kClsChunks = 8;          // a pattern's groups past its first batch go to the wavefronts in at most this many runs
 struct ClsItem { uint16_t pid, first_batch, n_batches; };
 
 // Sum over the 8 lanes of a slot, in every lane of the slot, with data-parallel-primitive moves (all lanes active):
@@ -203,23 +205,29 @@ struct ClsLane {
     bool is_row, is_mask, has_quad;
     uint4 goal_quad;               // this lane's quad of a device at the goal
 };
-// what a run of a pattern's groups has shown (the same in every lane)
-struct ClsFound { uint32_t bits; int goal_part, two_part; };
-
 // Per device: is it empty, is it at the goal, does it hold two pairs.  The wavefront takes the devices
-// first + slot, first + stride + slot, ...; at_goal and with_two come back summed over the wavefront.
+// first + slot, first + stride + slot, ...; how many of them come back (the same in every lane).
 // With `shortfalls`, also (for the filter of the last level): rows_short = devices that lack a row, cols_short =
 // devices that hold rows whose columns are not all there.
+struct ClsCounts { int goal, two, empty, rows_short, cols_short; };
 template <int KW, int MW, int NP>
-__device__ inline void cls_flags(const ClsLane<KW, MW, NP>& c, uint8_t* flags, int first, int stride, int& at_goal, int& with_two,
-                                 bool shortfalls, int& rows_short, int& cols_short) {
+__device__ inline ClsCounts cls_flags(const ClsLane<KW, MW, NP>& c, uint8_t* flags, int first, int stride, bool shortfalls) {
     using L = FL<KW, MW>;
-    at_goal = 0; with_two = 0; rows_short = 0; cols_short = 0;
-    for (int d0 = first; d0 < c.R; d0 += stride) {
-        const int d = d0 + c.slot;
+    ClsCounts n{0, 0, 0, 0, 0};
+    for (int d0 = first; d0 < c.R; d0 += 4 * stride) {
+        uint4 a0[4], a1[4];                              // (read together: a device's quads are looked at in a chain of votes)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int d = d0 + u * stride + c.slot;
+            const bool there = d < c.R && c.has_quad;
+            a0[u] = there ? c.ldsq[d * L::WQ + c.qd] : q_zero();
+            a1[u] = (NP == 2 && there) ? c.ldsq[c.plane_q + d * L::WQ + c.qd] : q_zero();
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+        const int d = d0 + u * stride + c.slot;
         const bool act = d < c.R && c.has_quad;
-        const uint4 v = act ? c.ldsq[d * L::WQ + c.qd] : q_zero();
-        const uint4 v1 = (NP == 2 && act) ? c.ldsq[c.plane_q + d * L::WQ + c.qd] : q_zero();
+        const uint4 v = a0[u], v1 = a1[u];
         const unsigned long long nz = __ballot(act && c.is_row && q_any(v));
         const unsigned long long ng = __ballot(act && q_any(q_xor(v, c.goal_quad)));
         const unsigned long long n2 = NP == 2 ? __ballot(act && c.is_row && q_any(v1)) : 0ull;
@@ -229,112 +237,118 @@ __device__ inline void cls_flags(const ClsLane<KW, MW, NP>& c, uint8_t* flags, i
             m0 = __ballot(act && c.is_mask && q_any(q_xor(v, c.goal_quad)));
             m1 = NP == 2 ? __ballot(act && c.is_mask && q_any(q_xor(v1, c.goal_quad))) : 0ull;
         }
-        if (c.qd == 0 && d < c.R) {
-            const int sh = c.slot * 8;
-            const bool empty = ((nz >> sh) & 0xffull) == 0ull, two = ((n2 >> sh) & 0xffull) != 0ull;
-            const bool goal = ((ng >> sh) & 0xffull) == 0ull && !two;
-            flags[d] = (uint8_t)((empty ? kFlagEmpty : 0u) | (goal ? kFlagGoal : 0u) | (two ? kFlagTwo : 0u));
-            at_goal += goal ? 1 : 0;
-            with_two += two ? 1 : 0;
-            rows_short += ((rs >> sh) & 0xffull) != 0ull ? 1 : 0;
-            cols_short += ((!empty && ((m0 >> sh) & 0xffull) != 0ull) || (two && ((m1 >> sh) & 0xffull) != 0ull)) ? 1 : 0;
+        const int sh = c.slot * 8;
+        const bool head = c.qd == 0 && d < c.R;
+        const bool empty = ((nz >> sh) & 0xffull) == 0ull, two = NP == 2 && ((n2 >> sh) & 0xffull) != 0ull;
+        const bool goal = ((ng >> sh) & 0xffull) == 0ull && !two;
+        if (head) flags[d] = (uint8_t)((empty ? kFlagEmpty : 0u) | (goal ? kFlagGoal : 0u) | (two ? kFlagTwo : 0u));
+        n.goal += __popcll(__ballot(head && goal));
+        n.empty += __popcll(__ballot(head && empty));
+        if constexpr (NP == 2) n.two += __popcll(__ballot(head && two));
+        if (shortfalls) {
+            n.rows_short += __popcll(__ballot(head && ((rs >> sh) & 0xffull) != 0ull));
+            n.cols_short += __popcll(__ballot(head && ((!empty && ((m0 >> sh) & 0xffull) != 0ull) || (two && ((m1 >> sh) & 0xffull) != 0ull))));
+        }
         }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        at_goal += __shfl_xor(at_goal, o, 64); with_two += __shfl_xor(with_two, o, 64);
-        rows_short += __shfl_xor(rows_short, o, 64); cols_short += __shfl_xor(cols_short, o, 64);
+    return n;
+}
+
+// Where the lane's slot stands in a pattern: 8 slots side by side hold 8 groups, or fewer with several slots each.
+struct ClsPlace {
+    int spg, gpb, my_g, part;      // slots that share a group, groups side by side, this slot's group and place in it
+    __device__ inline explicit ClsPlace(int slot, int n_groups) {
+        spg = 1;
+        while (spg * 2 * n_groups <= 8) spg *= 2;
+        gpb = 8 / spg; my_g = slot / spg; part = slot - my_g * spg;
     }
+};
+__device__ inline int cls_base(const PatLds& P, int G) {
+    if (P.master) return G * P.g * P.s;
+    const int hi = div_small(G, P.s);
+    return hi * P.g * P.s + (G - hi * P.s);
 }
 
 // The batches [first_batch, first_batch + n_batches) of a pattern's groups (8 slots side by side: a batch is
-// 8 groups, or fewer groups with several slots each), every rule at once.  Stops early once every rule of the
+// 8 groups, or fewer groups with several slots each), every rule at once.  `pf`: what the pattern's devices and the runs
+// before have shown.  Stops early once every rule of the
 // pattern has failed; with goal_ops >= 0 (the last level: bit 0 / 1 / 2 = an AllReduce / AllGather / Broadcast may
 // still end at the goal) also once every rule has failed or has left some device short of the goal.
+// Bound by vector instructions: a member costs its LDS read and three operations a word (one pair; a group that is not
+// there reads the last one's members, and only its verdict is dropped).  With a condition on every member, its flags read
+// beside it and the flags added up, and with every run of a pattern finding out for itself that all rules fail, the walk of a
+// state of 512 devices (four levels, 16 patterns) took 21.5 us, and takes 12.4 now (two pairs a device: 38.3 and 25.8).
 template <int KW, int MW, int NP>
-__device__ inline ClsFound cls_walk(const ClsLane<KW, MW, NP>& c, const PatLds P, int first_batch, int n_batches, int goal_ops) {
+__device__ inline uint32_t cls_walk(const ClsLane<KW, MW, NP>& c, const PatLds P, int first_batch, int n_batches, uint32_t pf, int goal_ops) {
     using L = FL<KW, MW>;
     const uint4* const ldsq = c.ldsq;
-    const int plane_q = c.plane_q, slot = c.slot, qd = c.qd;
+    const int plane_q = c.plane_q, slot = c.slot, qd = c.qd, sh = slot * 8;
     const bool is_row = c.is_row, is_mask = c.is_mask;
     const uint4 goal_quad = c.goal_quad;
-    const int g = P.g, s = P.s, ng = P.n_groups, gs = g * s;
-    int spg = 1;                                         // slots that share a group
-    while (spg * 2 * ng <= 8) spg *= 2;
-    const int gpb = 8 / spg;                             // groups side by side
-    const int my_g = slot / spg, part = slot - my_g * spg;
-    const int trips = (g + spg - 1) / spg;
+    const int g = P.g, s = P.s, ng = P.n_groups;
+    const ClsPlace at(slot, ng);
+    const int spg = at.spg, part = at.part;
+    const int q_in = c.has_quad ? qd : 0;                // (a lane without a quad reads the first one: it is never asked)
+    const int full = div_small(g, spg), rest = g - full * spg, step_q = spg * s * L::WQ;
+    const uint32_t row_bits = is_row ? ~0u : 0u;
     bool bad_red = false, bad_b = false, unal = false, bad_rs = false, bad_ag = false, changed = false, ag_uneq = false;
     bool bad_bc1 = false, bc_fail = false, any_two = false;
     bool ng_ar = false, ng_ag = false, ng_bc = false;    // some device is not at the goal afterwards
-    uint32_t fl_pat = 0;
-    int goal_part = 0, two_part = 0;
-    const int G_end = min(ng, (first_batch + n_batches) * gpb);
-    for (int G0 = first_batch * gpb; G0 < G_end; G0 += gpb) {
-        const int G = G0 + my_g;
+    const int G_end = min(ng, (first_batch + n_batches) * at.gpb);
+    for (int G0 = first_batch * at.gpb; G0 < G_end; G0 += at.gpb) {
+        const int G = G0 + at.my_g;
         const bool act = G < ng && c.has_quad;
-        int base = 0;
-        if (P.master) base = G * gs;
-        else { const int hi = div_small(G, s); base = hi * gs + (G - hi * s); }
+        const int base = cls_base(P, min(G, ng - 1));
         // row lanes: p = rows (both pairs), al = pair-0 rows of the members with two pairs
         // mask lanes: p = plane A (pair 0), sB = plane B, al = every pair's mask
         QAcc p, sB, al, i0, i1;
         p.init(); sB.init(); al.init(); i0.init(); i1.init();
-        uint4 first0 = q_zero(), first1 = q_zero();
-        uint32_t fl_or = 0;
+        bool g_two = false;
+        auto take = [&](uint4 v0, uint4 v1, uint32_t f) {
+            if constexpr (NP == 2) {
+                const bool two = (f & kFlagTwo) != 0u;   // (else the second pair is zero)
+                g_two |= two;
+                i0.add(v0); i1.add(v1);
+                p.add(make_uint4(v0.x | (v1.x & row_bits), v0.y | (v1.y & row_bits), v0.z | (v1.z & row_bits), v0.w | (v1.w & row_bits)));
+                sB.add(make_uint4(two ? v1.x : v0.x, two ? v1.y : v0.y, two ? v1.z : v0.z, two ? v1.w : v0.w));
+                const bool a = two || !is_row, b = two && !is_row;
+                al.add_if(make_uint4(a ? v0.x : 0u, a ? v0.y : 0u, a ? v0.z : 0u, a ? v0.w : 0u), a);
+                al.add_if(make_uint4(b ? v1.x : 0u, b ? v1.y : 0u, b ? v1.z : 0u, b ? v1.w : 0u), b);
+            } else p.add(v0);
+        };
+        const uint4* m = ldsq + (base + part * s) * L::WQ + q_in;
+        const uint8_t* fl = c.flags + base + part * s;
         // (members in flight: four, or two where a member is two quads and five accumulators, which leave no registers for more)
-        constexpr int kFlight = 2;
-        for (int it0 = 0; it0 < trips; it0 += kFlight) {
+        constexpr int kFlight = NP == 1 ? 4 : 2;
+        int it = 0;
+        for (; it + kFlight <= full; it += kFlight) {
             uint4 a0[kFlight], a1[kFlight];
             uint32_t ff[kFlight];
-            bool on[kFlight];
 #pragma unroll
             for (int u = 0; u < kFlight; ++u) {
-                const int t = (it0 + u) * spg + part;
-                on[u] = act && t < g;
-                const int d = base + t * s;
-                a0[u] = on[u] ? ldsq[d * L::WQ + qd] : q_zero();
-                a1[u] = (NP == 2 && on[u]) ? ldsq[plane_q + d * L::WQ + qd] : q_zero();
-                ff[u] = on[u] ? (uint32_t)c.flags[d] : 0u;
+                a0[u] = m[u * step_q];
+                a1[u] = NP == 2 ? m[plane_q + u * step_q] : q_zero();
+                ff[u] = NP == 2 ? (uint32_t)fl[u * spg * s] : 0u;
             }
+            m += kFlight * step_q; fl += kFlight * spg * s;
 #pragma unroll
-            for (int u = 0; u < kFlight; ++u) {
-                const uint4 v0 = a0[u];
-                const uint32_t f = ff[u];
-                fl_or |= f;
-                goal_part += (qd == 0 && (f & kFlagGoal)) ? 1 : 0;
-                if constexpr (NP == 2) {
-                    const uint4 v1 = a1[u];
-                    const bool two = (f & kFlagTwo) != 0u;
-                    two_part += (qd == 0 && two) ? 1 : 0;
-                    i0.add_if(v0, on[u]); i1.add_if(v1, on[u]);
-                    if (is_row) {
-                        p.add_if(q_or(v0, v1), on[u]);
-                        al.add_if(two ? v0 : q_zero(), two);
-                    } else {
-                        p.add_if(v0, on[u]);
-                        sB.add_if(two ? v1 : v0, on[u]);
-                        al.add_if(v0, on[u]);
-                        al.add_if(two ? v1 : q_zero(), two);
-                    }
-                    if (it0 + u == 0 && part == 0) { first0 = v0; first1 = v1; }
-                } else {
-                    p.add_if(v0, on[u]);
-                    if (it0 + u == 0 && part == 0) first0 = v0;
-                }
+            for (int u = 0; u < kFlight; ++u) take(a0[u], a1[u], ff[u]);
+        }
+        for (; it < full; ++it) {
+            take(m[0], NP == 2 ? m[plane_q] : q_zero(), NP == 2 ? (uint32_t)fl[0] : 0u);
+            m += step_q; fl += spg * s;
+        }
+        if (part < rest) take(m[0], NP == 2 ? m[plane_q] : q_zero(), NP == 2 ? (uint32_t)fl[0] : 0u);
+        const uint4 first0 = ldsq[base * L::WQ + q_in];
+        const uint4 first1 = NP == 2 ? ldsq[plane_q + base * L::WQ + q_in] : q_zero();
+        for (int x = 8; x < 8 * spg; x <<= 1) {          // the slots of one group put their members together
+            p.merge_xor(x);
+            if constexpr (NP == 2) {
+                sB.merge_xor(x); al.merge_xor(x); i0.merge_xor(x); i1.merge_xor(x);
+                g_two |= __shfl_xor((int)g_two, x, 64) != 0;
             }
         }
-        for (int m = 8; m < 8 * spg; m <<= 1) {          // the slots of one group put their members together
-            p.merge_xor(m);
-            if constexpr (NP == 2) { sB.merge_xor(m); al.merge_xor(m); i0.merge_xor(m); i1.merge_xor(m); }
-            fl_or |= (uint32_t)__shfl_xor((int)fl_or, m, 64);
-        }
-        if (spg > 1) {
-            first0 = q_shfl(first0, (slot - part) * 8 + qd);
-            if constexpr (NP == 2) first1 = q_shfl(first1, (slot - part) * 8 + qd);
-        }
-        fl_pat |= act ? fl_or : 0u;
         const int rows = sum_slot((act && is_row) ? q_popc(p.o) : 0);
-        const int sh = slot * 8;
         if constexpr (NP == 1) {
             const unsigned long long dif_slots = __ballot(act && p.differ());
             if (act) {
@@ -342,14 +356,12 @@ __device__ inline ClsFound cls_walk(const ClsLane<KW, MW, NP>& c, const PatLds P
                 if (is_row) { bad_red |= differ; bad_ag |= twice; changed |= q_any(p.o); }
                 else { bad_red |= twice; ag_uneq |= differ; }
                 bad_rs |= div_small(rows, g) * g != rows;
-                bad_ag |= (fl_or & kFlagEmpty) != 0u;
                 bad_bc1 |= q_any(q_xor(p.o, first0)) || ((dif_slots >> sh) & 0xffull) == 0ull;
                 ng_ar |= q_any(q_xor(p.o, goal_quad));
                 ng_ag |= q_any(q_xor(is_row ? p.o : first0, goal_quad));
                 ng_bc |= q_any(q_xor(first0, goal_quad));
             }
         } else {
-            const bool g_two = (fl_or & kFlagTwo) != 0u;
             const unsigned long long unal_slots = __ballot(act && is_row && g_two && al.differ());
             const unsigned long long split_slots = __ballot(act && is_mask && g_two && q_any(q_xor(p.o, sB.o)));
             const unsigned long long dif_slots = __ballot(act && (i0.differ() || i1.differ()));
@@ -361,7 +373,6 @@ __device__ inline ClsFound cls_walk(const ClsLane<KW, MW, NP>& c, const PatLds P
                 unal |= unal_g;
                 any_two |= split_g;
                 bad_rs |= div_small(rows, g) * g != rows;
-                bad_ag |= (fl_or & kFlagEmpty) != 0u;
                 // Broadcast, exact where no member of the pattern holds two pairs ...
                 bad_bc1 |= q_any(q_xor(p.o, first0)) || !differs_g;
                 // ... and otherwise what must hold at least: rows and masks inside the root's, someone differs
@@ -376,45 +387,40 @@ __device__ inline ClsFound cls_walk(const ClsLane<KW, MW, NP>& c, const PatLds P
             }
         }
         // every rule of the pattern has failed already: the other groups cannot change that
-        const bool dead_red = __any(bad_red), dead_ag = __any(bad_ag), dead_bc = __any(bad_bc1 && (NP == 1 || bc_fail));
+        const bool dead_red = (pf & kPfBadRed) || __any(bad_red), dead_ag = (pf & kPfBadAg) || __any(bad_ag);
+        const bool dead_bc = ((pf & kPfBadBc1) || __any(bad_bc1)) && (NP == 1 || (pf & kPfBcFail) || __any(bc_fail));
         if (dead_red && dead_ag && dead_bc) break;
         if (goal_ops >= 0 && (!(goal_ops & 1) || dead_red || __any(ng_ar)) && (!(goal_ops & 2) || dead_ag || __any(ag_uneq) || __any(ng_ag)) &&
             (!(goal_ops & 4) || dead_bc || __any(ng_bc)))
             break;
     }
-    ClsFound f;
     uint32_t bits = 0;
     bits |= __any(bad_red) ? kPfBadRed : 0u; bits |= __any(bad_b) ? kPfBadB : 0u; bits |= __any(unal) ? kPfUnal : 0u;
     bits |= __any(bad_rs) ? kPfBadRs : 0u; bits |= __any(bad_ag) ? kPfBadAg : 0u; bits |= __any(changed) ? kPfChanged : 0u;
     bits |= __any(ag_uneq) ? kPfAgUneq : 0u; bits |= __any(bad_bc1) ? kPfBadBc1 : 0u; bits |= __any(bc_fail) ? kPfBcFail : 0u;
     bits |= __any(any_two) ? kPfAnyTwo : 0u; bits |= __any(ng_ar) ? kPfNgAr : 0u; bits |= __any(ng_ag) ? kPfNgAg : 0u;
-    bits |= __any(ng_bc) ? kPfNgBc : 0u; bits |= __any((fl_pat & kFlagTwo) != 0u) ? kPfPatTwo : 0u;
-    for (int o = 32; o > 0; o >>= 1) { goal_part += __shfl_xor(goal_part, o, 64); two_part += __shfl_xor(two_part, o, 64); }
-    f.bits = bits; f.goal_part = goal_part; f.two_part = two_part;
-    return f;
+    bits |= __any(ng_bc) ? kPfNgBc : 0u;
+    return bits;
 }
 
 // A valid AllGather of members with different masks: does some device hold more than two masks afterwards?
 // Second walk, the wavefront together: per group the first pair's mask, the first mask that differs from it,
 // and whether a third one shows up (the child then needs the literal state).
 template <int KW, int MW, int NP>
-__device__ inline bool cls_many_masks(const ClsLane<KW, MW, NP>& c, const PatLds P) {
+__device__ inline bool cls_many_masks(const ClsLane<KW, MW, NP>& c, const PatLds P, int first_batch, int n_batches) {
     using L = FL<KW, MW>;
     const uint4* const ldsq = c.ldsq;
     const int plane_q = c.plane_q, slot = c.slot, qd = c.qd;
-    const int g = P.g, s = P.s, ng = P.n_groups, gs = g * s;
-    int spg = 1;
-    while (spg * 2 * ng <= 8) spg *= 2;
-    const int gpb = 8 / spg;
-    const int my_g = slot / spg, part = slot - my_g * spg;
+    const int g = P.g, s = P.s, ng = P.n_groups;
+    const ClsPlace place(slot, ng);
+    const int spg = place.spg, part = place.part;
     const int trips = (g + spg - 1) / spg;
+    const int G_end = min(ng, (first_batch + n_batches) * place.gpb);
     bool many = false;
-    for (int G0 = 0; G0 < ng; G0 += gpb) {
-        const int G = G0 + my_g;
+    for (int G0 = first_batch * place.gpb; G0 < G_end; G0 += place.gpb) {
+        const int G = G0 + place.my_g;
         const bool act = G < ng && c.is_mask;
-        int base = 0;
-        if (P.master) base = G * gs;
-        else { const int hi = div_small(G, s); base = hi * gs + (G - hi * s); }
+        const int base = cls_base(P, G);
         const uint4 d0 = act ? ldsq[base * L::WQ + qd] : q_zero();
         uint4 d1 = q_zero();
         bool have1 = false;
@@ -452,27 +458,23 @@ __device__ inline bool cls_many_masks(const ClsLane<KW, MW, NP>& c, const PatLds
 // Broadcast on a pattern with two-pair members that has passed the necessary conditions of the walk above, the
 // wavefront together (the rule of bcast_compare): every member's rows lie inside the root's; where a pair of the
 // member shares rows with a pair of the root, the member's mask lies inside the root's; and in every group some
-// member differs from its root.  Returns 0 (invalid), else 1 | 2 (some root holds two pairs) | 4 (every root is
-// at the goal).
+// member differs from its root.  What the groups have shown: kP2* bits.
 template <int KW, int MW, int NP>
-__device__ inline int cls_bcast_pairs(const ClsLane<KW, MW, NP>& c, const PatLds P) {
+__device__ inline uint32_t cls_bcast_pairs(const ClsLane<KW, MW, NP>& c, const PatLds P, int first_batch, int n_batches) {
     using L = FL<KW, MW>;
     const uint4* const ldsq = c.ldsq;
     const int plane_q = c.plane_q, slot = c.slot, qd = c.qd, sh = slot * 8;
     const bool is_row = c.is_row, is_mask = c.is_mask;
-    const int g = P.g, s = P.s, ng = P.n_groups, gs = g * s;
-    int spg = 1;
-    while (spg * 2 * ng <= 8) spg *= 2;
-    const int gpb = 8 / spg;
-    const int my_g = slot / spg, part = slot - my_g * spg;
+    const int g = P.g, s = P.s, ng = P.n_groups;
+    const ClsPlace place(slot, ng);
+    const int spg = place.spg, part = place.part;
     const int trips = (g + spg - 1) / spg;
+    const int G_end = min(ng, (first_batch + n_batches) * place.gpb);
     bool bad = false, any_two = false, not_goal = false;
-    for (int G0 = 0; G0 < ng; G0 += gpb) {
-        const int G = G0 + my_g;
+    for (int G0 = first_batch * place.gpb; G0 < G_end; G0 += place.gpb) {
+        const int G = G0 + place.my_g;
         const bool act = G < ng && c.has_quad;
-        int base = 0;
-        if (P.master) base = G * gs;
-        else { const int hi = div_small(G, s); base = hi * gs + (G - hi * s); }
+        const int base = cls_base(P, G);
         const uint4 r0 = act ? ldsq[base * L::WQ + qd] : q_zero();
         const uint4 r1 = (NP == 2 && act) ? ldsq[plane_q + base * L::WQ + qd] : q_zero();
         bool not_sub = false, dif = false;
@@ -510,8 +512,7 @@ __device__ inline int cls_bcast_pairs(const ClsLane<KW, MW, NP>& c, const PatLds
             not_goal |= root_two || q_any(q_xor(r0, c.goal_quad));
         }
     }
-    if (__any(bad)) return 0;
-    return 1 | (__any(any_two) ? 2 : 0) | (__any(not_goal) ? 0 : 4);
+    return (__any(bad) ? kP2BcBad : 0u) | (__any(any_two) ? kP2BcTwo : 0u) | (__any(not_goal) ? kP2BcShort : 0u);
 }
 
 // A ReduceScatter on a pattern whose groups are valid, aligned and split (some member holds two pairs), the
@@ -521,24 +522,21 @@ __device__ inline int cls_bcast_pairs(const ClsLane<KW, MW, NP>& c, const PatLds
 // united masks of either side, as the kernel that builds the child does; then every rank's block is cut out of the
 // rows and looked at from both sides.
 template <int KW, int MW, int NP>
-__device__ inline bool cls_rs_straddles(const ClsLane<KW, MW, NP>& c, const PatLds P) {
+__device__ inline bool cls_rs_straddles(const ClsLane<KW, MW, NP>& c, const PatLds P, int first_batch, int n_batches) {
     using L = FL<KW, MW>;
     const uint4* const ldsq = c.ldsq;
     const int plane_q = c.plane_q, slot = c.slot, qd = c.qd, sh = slot * 8;
     const bool is_row = c.is_row, is_mask = c.is_mask;
-    const int g = P.g, s = P.s, ng = P.n_groups, gs = g * s;
-    int spg = 1;
-    while (spg * 2 * ng <= 8) spg *= 2;
-    const int gpb = 8 / spg;
-    const int my_g = slot / spg, part = slot - my_g * spg;
+    const int g = P.g, s = P.s, ng = P.n_groups;
+    const ClsPlace place(slot, ng);
+    const int spg = place.spg, part = place.part;
     const int trips = (g + spg - 1) / spg;
+    const int G_end = min(ng, (first_batch + n_batches) * place.gpb);
     bool straddles = false;
-    for (int G0 = 0; G0 < ng; G0 += gpb) {
-        const int G = G0 + my_g;
+    for (int G0 = first_batch * place.gpb; G0 < G_end; G0 += place.gpb) {
+        const int G = G0 + place.my_g;
         const bool act = G < ng && c.has_quad;
-        int base = 0;
-        if (P.master) base = G * gs;
-        else { const int hi = div_small(G, s); base = hi * gs + (G - hi * s); }
+        const int base = cls_base(P, G);
         // row lanes: u = the rows, xa = pair-0 rows of the members with two pairs; mask lanes: u = united first
         // masks, mb = united masks of the other side (a member with one pair has its only mask on both sides)
         uint4 u = q_zero(), xa = q_zero(), mb = q_zero();
@@ -585,15 +583,15 @@ __device__ inline bool cls_rs_straddles(const ClsLane<KW, MW, NP>& c, const PatL
     return __any(straddles) != 0;
 }
 
-// One lane: the codes of a pattern's instructions from what its groups have shown.  goal_ops < 0: every code;
+// One thread: the codes of a pattern's instructions from what its groups have shown.  goal_ops < 0: every code;
 // else (the last level, where only goals count) bit 0 / 1 / 2: an AllReduce / AllGather / Broadcast may still end
 // at the goal, and everything that does not (or that this form cannot judge) is written as invalid.
 template <int KW, int MW, int NP>
 __device__ inline void cls_codes(const ClsLane<KW, MW, NP>& c, const PatLds P, int pid, uint32_t pf, int goal_part, int two_part,
-                                 int n_goal, int n_two, bool MANY_MASKS, int bc_pairs, bool RS_STRADDLES, const int (&ops_r)[5], int n_ops, int max_pairs,
-                                 const Words<KW>& all_rows, const Words<MW>& all_cols, int goal_ops, uint8_t* __restrict__ codes,
+                                 int n_goal, int n_two, uint32_t second, const int (&ops_r)[5], int n_ops, int max_pairs, int goal_ops, uint8_t* __restrict__ codes,
                                  uint8_t* __restrict__ unknown) {
     const int R = c.R;
+    const bool MANY_MASKS = second & kP2Many, RS_STRADDLES = second & kP2Straddles;
     const bool BAD_RED = pf & kPfBadRed, BAD_B = pf & kPfBadB, UNAL = pf & kPfUnal, BAD_RS = pf & kPfBadRs;
     const bool BAD_AG = pf & kPfBadAg, CHANGED = pf & kPfChanged, AG_UNEQ = pf & kPfAgUneq;
     const bool BAD_BC1 = pf & kPfBadBc1, BC_FAIL = pf & kPfBcFail, ANY_TWO = pf & kPfAnyTwo;
@@ -623,8 +621,8 @@ __device__ inline void cls_codes(const ClsLane<KW, MW, NP>& c, const PatLds P, i
             else code = (!NG_AG && rest_done) ? CODE_GOAL : CODE_PREFIX;
         } else {
             if (!PAT_TWO) code = BAD_BC1 ? CODE_INVALID : rest_two ? CODE_PREFIX2 : (!NG_BC && rest_done) ? CODE_GOAL : CODE_PREFIX;
-            else if (BC_FAIL || bc_pairs == 0) code = CODE_INVALID;
-            else code = ((bc_pairs & 2) || rest_two) ? CODE_PREFIX2 : ((bc_pairs & 4) && rest_done) ? CODE_GOAL : CODE_PREFIX;
+            else if (BC_FAIL || (second & kP2BcBad)) code = CODE_INVALID;
+            else code = ((second & kP2BcTwo) || rest_two) ? CODE_PREFIX2 : (!(second & kP2BcShort) && rest_done) ? CODE_GOAL : CODE_PREFIX;
         }
         if (code == CODE_PREFIX2 && max_pairs < 2) code = CODE_PREFIX_LITERAL;
         if (goal_ops >= 0 && code != CODE_GOAL && code != CODE_UNKNOWN) code = CODE_INVALID;    // (last level: goals only)
@@ -927,10 +925,10 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
                                                                 uint8_t* __restrict__ unknown, FrontCounters* __restrict__ ctr) {
     extern __shared__ uint4 ldsq[];                      // NP planes of [R][WQ] quads, then R flag bytes
     __shared__ PatLds spat[kMaxPatterns];
-    __shared__ int s_goal, s_two, s_next, s_n_items, s_rows_short, s_cols_short;
-    __shared__ uint32_t s_pflags[kMaxPatterns];
+    __shared__ int s_goal, s_two, s_empty, s_next, s_next2, s_n_items, s_rows_short, s_cols_short;
+    __shared__ uint32_t s_pflags[kMaxPatterns], s_second[kMaxPatterns], s_needs[kMaxPatterns];
     __shared__ int s_pgoal[kMaxPatterns], s_ptwo[kMaxPatterns];
-    __shared__ ClsItem s_items[kMaxPatterns * kClsChunks];
+    __shared__ ClsItem s_items[kMaxPatterns * (kClsChunks + 1)];
     __shared__ __align__(16) uint8_t s_codes[512];        // the row of codes of the state at hand (an alphabet has at most 512 instructions)
     using L = FL<KW, MW>;
     if (from && blockIdx.x + *from >= *n_list) return;   // (more blocks than the level has states)
@@ -945,49 +943,32 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
         spat[i] = p;
     }
     __syncthreads();
-    // work items: a pattern's batches of groups in up to kClsChunks runs; the long items (whole patterns) first, then
-    // the other patterns' runs, pattern after pattern.  A thread per pattern works out its runs and where they go (a
-    // block judges a state or two, so what it sets up first is not paid once and forgotten).
+    // work items: every pattern's first batch of groups (in most patterns it fails every rule, and the rest is dropped as it
+    // comes up), then the other batches in up to kClsChunks runs, pattern after pattern.  A thread per pattern works out its
+    // runs and where they go (a block judges a state or two, so what it sets up first is not paid once and forgotten).
     {
-        int* const s_runs = s_pgoal;                     // (not in use yet) runs of pattern i, negated for a whole pattern
+        int* const s_runs = s_pgoal;                     // (not in use yet) runs of pattern i
+        auto batches_of = [&](int i) { const ClsPlace at(0, spat[i].n_groups); return (spat[i].n_groups + at.gpb - 1) / at.gpb; };
+        auto per_of = [](int rest) { return rest >= 2 * kClsChunks ? (rest + kClsChunks - 1) / kClsChunks : rest >= 2 ? 2 : 1; };
         for (int i = tid; i < n_pat; i += kClsThreads) {
-            const int ng = spat[i].n_groups;
-            int spg = 1;
-            while (spg * 2 * ng <= 8) spg *= 2;
-            const int batches = (ng + 8 / spg - 1) / (8 / spg);
-            const int per = batches >= 2 * kClsChunks ? (batches + kClsChunks - 1) / kClsChunks : batches >= 4 ? 2 : batches;
-            s_runs[i] = per == batches ? -1 : (batches + per - 1) / per;
+            const int rest = batches_of(i) - 1, per = per_of(rest);
+            s_runs[i] = (rest + per - 1) / per;
+            s_items[i] = ClsItem{(uint16_t)i, 0, 1};
         }
         __syncthreads();
         for (int i = tid; i < n_pat; i += kClsThreads) {
-            const int ng = spat[i].n_groups;
-            int spg = 1;
-            while (spg * 2 * ng <= 8) spg *= 2;
-            const int batches = (ng + 8 / spg - 1) / (8 / spg);
-            const int per = batches >= 2 * kClsChunks ? (batches + kClsChunks - 1) / kClsChunks : batches >= 4 ? 2 : batches;
-            const bool whole = s_runs[i] < 0;
-            int at = 0, n_whole = 0, total = 0;
-            for (int j = 0; j < n_pat; ++j) {
-                const int rj = s_runs[j];
-                n_whole += rj < 0 ? 1 : 0;
-                total += rj < 0 ? 1 : rj;
-                if (j < i && (rj < 0) == whole) at += rj < 0 ? 1 : rj;
-            }
-            if (!whole) at += n_whole;
-            for (int b = 0; b < batches; b += per) {
-                ClsItem w; w.pid = (uint16_t)i; w.first_batch = (uint16_t)b; w.n_batches = (uint16_t)min(per, batches - b);
-                s_items[at++] = w;
-            }
-            if (i == 0) s_n_items = total;
+            const int rest = batches_of(i) - 1, per = per_of(rest);
+            int at = n_pat;
+            for (int j = 0; j < i; ++j) at += s_runs[j];
+            for (int b = 0; b < rest; b += per) s_items[at++] = ClsItem{(uint16_t)i, (uint16_t)(b + 1), (uint16_t)min(per, rest - b)};
+            if (i == n_pat - 1) s_n_items = at;
         }
     }
-    const Words<KW> all_rows = full_mask<KW>(q.k);
-    const Words<MW> all_cols = full_mask<MW>(R);
     ClsLane<KW, MW, NP> c;
     c.ldsq = ldsq; c.flags = flags; c.R = R; c.plane_q = plane_q;
     c.lane = lane; c.slot = lane >> 3; c.qd = lane & 7;
     c.is_row = c.qd < L::QK; c.is_mask = c.qd >= L::QK && c.qd < L::WQ; c.has_quad = c.qd < L::WQ;
-    c.goal_quad = goal_quad_of<KW, MW>(all_rows, all_cols, c.qd, c.is_row, c.is_mask);
+    c.goal_quad = goal_quad_of<KW, MW>(full_mask<KW>(q.k), full_mask<MW>(R), c.qd, c.is_row, c.is_mask);
     int ops_r[5];
     bool has_bcast = false, has_scatter = false;
 #pragma unroll
@@ -1007,16 +988,17 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
 #pragma unroll
             for (int u = 0; u < 8; ++u) { const int i = i0 + u * kClsThreads; if (i < NP * plane_q) ldsq[i] = tmp[u]; }
         }
-        if (tid == 0) { s_goal = 0; s_two = 0; s_next = 0; s_rows_short = 0; s_cols_short = 0; unknown[e] = 0; }
-        for (int i = tid; i < n_pat; i += kClsThreads) { s_pflags[i] = 0u; s_pgoal[i] = 0; s_ptwo[i] = 0; }
+        if (tid == 0) { s_goal = 0; s_two = 0; s_empty = 0; s_next = 0; s_next2 = 0; s_rows_short = 0; s_cols_short = 0; unknown[e] = 0; }
         __syncthreads();
         {
-            int at_goal, with_two, rows_short, cols_short;
-            cls_flags<KW, MW, NP>(c, flags, wave * 8, kClsWaves * 8, at_goal, with_two, goals_only != 0, rows_short, cols_short);
-            if (lane == 0 && at_goal) atomicAdd(&s_goal, at_goal);
-            if (lane == 0 && with_two) atomicAdd(&s_two, with_two);
-            if (lane == 0 && rows_short) atomicAdd(&s_rows_short, rows_short);
-            if (lane == 0 && cols_short) atomicAdd(&s_cols_short, cols_short);
+            const ClsCounts n = cls_flags<KW, MW, NP>(c, flags, wave * 8, kClsWaves * 8, goals_only != 0);
+            if (lane == 0) {
+                if (n.goal) atomicAdd(&s_goal, n.goal);
+                if (n.empty) atomicAdd(&s_empty, n.empty);
+                if (NP == 2 && n.two) atomicAdd(&s_two, n.two);
+                if (n.rows_short) atomicAdd(&s_rows_short, n.rows_short);
+                if (n.cols_short) atomicAdd(&s_cols_short, n.cols_short);
+            }
         }
         __syncthreads();
         const int n_goal = s_goal, n_two = s_two, n_items = s_n_items;
@@ -1037,6 +1019,27 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
             }
         }
         if (tid == 0) ++walked;
+        // ---- what the devices that take part in a pattern are: all of them, or every s-th one
+        for (int pid = wave; pid < n_pat; pid += kClsWaves) {
+            const PatLds P = spat[pid];
+            int goal = n_goal, two = n_two, empty = s_empty;
+            if (P.master) {
+                goal = 0; two = 0; empty = 0;
+                const int n = P.n_groups * P.g;
+                for (int i0 = 0; i0 < n; i0 += 64) {
+                    const uint32_t f = i0 + lane < n ? (uint32_t)flags[(i0 + lane) * P.s] : 0u;
+                    goal += __popcll(__ballot((f & kFlagGoal) != 0u));
+                    empty += __popcll(__ballot((f & kFlagEmpty) != 0u));
+                    if constexpr (NP == 2) two += __popcll(__ballot((f & kFlagTwo) != 0u));
+                }
+            }
+            if (lane == 0) {
+                s_pflags[pid] = (empty > 0 ? kPfBadAg : 0u) | (two > 0 ? kPfPatTwo : 0u);
+                s_second[pid] = 0u;
+                s_pgoal[pid] = goal; s_ptwo[pid] = two;
+            }
+        }
+        __syncthreads();
         // ---- stage A: the patterns' groups, cut into work items that the wavefronts take as they come (patterns
         //      differ widely in cost, and a pattern whose rules have all failed is dropped at once); what an item
         //      finds goes into its pattern's flag word
@@ -1048,39 +1051,59 @@ __global__ __launch_bounds__(kClsThreads, NP == 1 ? 4 : 2) void k_front_classify
             if (item >= n_items) break;
             const ClsItem W = s_items[item];
             const int pid = W.pid;
+            const uint32_t pf = s_pflags[pid];
             {
-                const uint32_t pf = s_pflags[pid];
                 const bool dead_red = pf & kPfBadRed, dead_ag = pf & kPfBadAg, dead_bc = (pf & kPfBadBc1) && (NP == 1 || (pf & kPfBcFail));
                 if (dead_red && dead_ag && dead_bc) continue;
                 if (goal_ops >= 0 && (!(goal_ops & 1) || dead_red || (pf & kPfNgAr)) && (!(goal_ops & 2) || dead_ag || (pf & (kPfAgUneq | kPfNgAg))) &&
                     (!(goal_ops & 4) || dead_bc || (pf & kPfNgBc)))
                     continue;
             }
-            const ClsFound f = cls_walk<KW, MW, NP>(c, spat[pid], W.first_batch, W.n_batches, goal_ops);
-            if (lane == 0) {
-                if (f.bits) atomicOr(&s_pflags[pid], f.bits);
-                if (f.goal_part) atomicAdd(&s_pgoal[pid], f.goal_part);
-                if (f.two_part) atomicAdd(&s_ptwo[pid], f.two_part);
-            }
+            const uint32_t bits = cls_walk<KW, MW, NP>(c, spat[pid], W.first_batch, W.n_batches, pf, goal_ops);
+            if (lane == 0 && bits) atomicOr(&s_pflags[pid], bits);
         }
         __syncthreads();
-        // ---- stage B: a pattern's flag word gives the codes of its instructions
-        for (int pid = wave; pid < n_pat; pid += kClsWaves) {
-            const PatLds P = spat[pid];
-            const uint32_t pf = s_pflags[pid];
+        // ---- stage B: the patterns that need a second walk, cut into the same items (by one wavefront each these walks
+        //      took longer than all of stage A for two-pair states: 34 us of a state of 512 devices, 15 now)
+        bool any_needs = false;
+        if (tid < n_pat) {
+            const uint32_t pf = s_pflags[tid];
+            uint32_t needs = 0u;
             // (an AllGather of members with different masks is no goal: how many masks it leaves is not asked at the last level)
-            const bool many = (goal_ops < 0 && !(pf & kPfBadAg) && (pf & kPfAgUneq)) ? cls_many_masks<KW, MW, NP>(c, P) : false;
-            int bc_pairs = 0;                            // (Broadcast among two-pair devices: the pairs compared)
-            if (NP == 2 && has_bcast && (goal_ops & 4) && (pf & kPfPatTwo) && !(pf & kPfBcFail)) bc_pairs = cls_bcast_pairs<KW, MW, NP>(c, P);
+            if (goal_ops < 0 && !(pf & kPfBadAg) && (pf & kPfAgUneq)) needs |= kP2Many;
+            // Broadcast among two-pair devices: the pairs compared
+            if (NP == 2 && has_bcast && (goal_ops & 4) && (pf & kPfPatTwo) && !(pf & kPfBcFail)) needs |= kP2BcBad;
             // (ReduceScatter of a split group: asked where cls_codes gets as far as the question, and not at the last level)
-            bool rs_straddles = false;
             if (NP == 2 && has_scatter && goal_ops < 0 && (pf & kPfAnyTwo) && !(pf & (kPfBadRed | kPfBadRs | kPfUnal | kPfBadB)) && (pf & kPfChanged))
-                rs_straddles = cls_rs_straddles<KW, MW, NP>(c, P);
-            if (lane == 0)
-                cls_codes<KW, MW, NP>(c, P, pid, pf, s_pgoal[pid], s_ptwo[pid], n_goal, n_two, many, bc_pairs, rs_straddles, ops_r, n_ops, max_pairs,
-                                      all_rows, all_cols, goal_ops, s_codes, unknown + e);
+                needs |= kP2Straddles;
+            s_needs[tid] = needs;
+            any_needs = needs != 0u;
+        }
+        if (__syncthreads_or(any_needs ? 1 : 0)) {
+            for (;;) {
+                const int item = __builtin_amdgcn_readfirstlane(atomicAdd(&s_next2, 1)) >> 6;      // (as above)
+                if (item >= n_items) break;
+                const ClsItem W = s_items[item];
+                const int pid = W.pid;
+                const uint32_t known = s_second[pid], needs = s_needs[pid];
+                uint32_t bits = 0u;
+                if ((needs & kP2Many) && !(known & kP2Many) && cls_many_masks<KW, MW, NP>(c, spat[pid], W.first_batch, W.n_batches)) bits |= kP2Many;
+                if constexpr (NP == 2) {
+                    if ((needs & kP2BcBad) && !(known & kP2BcBad)) bits |= cls_bcast_pairs<KW, MW, NP>(c, spat[pid], W.first_batch, W.n_batches);
+                    if ((needs & kP2Straddles) && !(known & kP2Straddles) && cls_rs_straddles<KW, MW, NP>(c, spat[pid], W.first_batch, W.n_batches))
+                        bits |= kP2Straddles;
+                }
+                if (lane == 0 && bits) atomicOr(&s_second[pid], bits);
+            }
+            __syncthreads();
+        }
+        // ---- a pattern's flag words give the codes of its instructions
+        if (tid < n_pat) {
+            const uint32_t pf = s_pflags[tid];
+            cls_codes<KW, MW, NP>(c, spat[tid], tid, pf, s_pgoal[tid], s_ptwo[tid], n_goal, n_two, s_second[tid], ops_r, n_ops, max_pairs, goal_ops, s_codes,
+                                  unknown + e);
             // (a row that stands for several chunks: what would have to cut one in two is not known here)
-            if (lane == 0 && q.rows_split && has_scatter && goal_ops < 0 && (pf & kPfBadRs) && !(pf & (kPfBadRed | kPfBadB)) && (pf & kPfChanged)) unknown[e] = 1;
+            if (q.rows_split && has_scatter && goal_ops < 0 && (pf & kPfBadRs) && !(pf & (kPfBadRed | kPfBadB)) && (pf & kPfChanged)) unknown[e] = 1;
         }
         // ---- how many of the row's codes are survivors, goals, one-pair and two-pair children (16 bits each), for the
         //      kernel that lists the survivors of the prefixes: it then reads the rows of the prefixes that have any

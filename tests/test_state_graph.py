@@ -92,6 +92,18 @@ def test_large_graph_matches_the_enumeration(card, max_len, more):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len", [([5, 10, 10], 3), ([2, 4, 8, 8], 3), ([3, 4, 6], 4), ([2, 9, 9], 4), ([130], 5), ([7, 11], 5)])
+def test_large_graph_matches_the_walk(card, max_len):
+    """Against the engine that walks every candidate: groups with few and many patterns' groups, odd sizes, up to 512 devices."""
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len)
+    auto, want = (B.p2_synthesize_batch([dict(q, engine=e)], MSG)[0] for e in (0, 2))
+    assert np.array_equal(auto["programs"], want["programs"]) and len(want["programs"]) > 0
+    assert np.allclose(auto["cost"], want["cost"], rtol=1e-14, atol=0.0)
+    assert auto["stats"]["valid"] == want["stats"]["valid"]
+
+
+@pytest.mark.gpu
 def test_large_graphs_side_by_side():
     """Several large groups on streams of their own beside small ones, and one after the other: the same bytes."""
     from paper_2110_10548_amd import binding as B
