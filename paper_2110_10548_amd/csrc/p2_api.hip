@@ -1143,12 +1143,14 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             std::memset(&lv, 0, sizeof lv);
             lv.states1 = L.states[0]; lv.states2 = L.states[1];
             lv.surv = L.edges; lv.n_surv = D.cap_found;
-            lv.lds_planes = l == 0 ? 1 : 2;
             lv.next_states1 = L.states[0]; lv.next_states2 = L.states[1]; lv.next_hash1 = L.hash[0]; lv.next_hash2 = L.hash[1];
             lv.surv_from = &L.marks->edges[l + 1]; lv.surv_end = &L.ctr->n_ssurv;
             lv.cap1 = L.cap[0]; lv.cap2 = L.cap[1]; lv.blocks = l == 0 ? 128u : l == 1 ? 1024u : 4096u;
-            P2_HIP(spans.begin(SpanRec::kMaterialize, on));
-            P2_HIP(launch_front_materialize(dq, pl.R, kk, lv, on));
+            P2_HIP(spans.begin(SpanRec::kMaterialize, on, lists));
+            for (int li = 0; li < lists; ++li) {         // (a launch of its own for the parents with two pairs, which need twice the LDS)
+                lv.lds_planes = li + 1; lv.only = lists == 1 ? 0 : li + 1;
+                P2_HIP(launch_front_materialize(dq, pl.R, kk, lv, on));
+            }
             P2_HIP(spans.end(on));
             P2_HIP(spans.begin(SpanRec::kGroup, on));
             for (int li = 0; li < (l == 0 ? 1 : 2); ++li)
@@ -1755,7 +1757,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             lv.n_share = n_share; lv.n_msg = n_msg;
             lv.states1 = static_cast<const uint32_t*>(S.f_states[cur].p); lv.states2 = static_cast<const uint32_t*>(S.f_states2[cur].p);
             lv.surv = static_cast<const FrontSurvivor*>(S.f_ssurv.p); lv.n_surv = n_ss;
-            lv.lds_planes = (n_s[1] > 0 || t2 > 0) ? 2 : 1;
+            lv.lds_planes = n_s[1] > 0 ? 2 : 1;
+            lv.only = 0;
             lv.n_reps = &dctr->n_reps[0];
             lv.ctr = dctr;
             ctr_clean = n_ss > 0;                    // (the kernel is launched only if there are children)

@@ -284,7 +284,8 @@ struct FrontLevel {
     const uint32_t* states1; const uint32_t* states2;      // the level's state lists
     const FrontSurvivor* surv; uint32_t n_surv;            // (state, instruction) pairs: entry = state, slot = the child's
                                                            // place in the next state list of its kind / among the goals
-    int32_t lds_planes;            // 2 if a parent or a child of this level has two pairs, else 1
+    int32_t lds_planes;            // 2 if a parent that the launch works on has two pairs, else 1
+    int32_t only;                  // 1, 2: survivors whose parent has one pair, two pairs; 0: all
     FrontCounters* ctr;            // the level's counters: those of its first half (which the host has read) are cleared
                                    // by the kernel for the next level; null: left alone
     uint32_t* n_reps;              // [2] cleared by the kernel (the counts of distinct children, which the search that

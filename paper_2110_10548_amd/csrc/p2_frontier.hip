@@ -1148,9 +1148,10 @@ __device__ inline unsigned long long rank_of(const DevQuery& q, unsigned long lo
 }
 
 // ---- children of the survivors -----------------------------------------------------------------------
-// Threads of a block: 256, or 1024 where the planes in LDS leave room for one or two blocks on a compute unit only
-// (large reduction groups), so that the loads and stores of a child are still the work of many wavefronts.
-constexpr int kMatThreads = 256, kMatThreadsBig = 1024;
+// Threads of a block: 256, or 512 where the planes in LDS leave room for one or two blocks on a compute unit only
+// (large reduction groups), so that the loads and stores of a child are still the work of many wavefronts (1 024 have a
+// compute unit to themselves, for the registers: one query of 512 devices 4 360 us, and 4 130 with 512).
+constexpr int kMatThreads = 256, kMatThreadsBig = 512;
 constexpr size_t kMatBigLds = 60 * 1024;
 
 // Smallest over the 8 lanes of a slot, in every lane of the slot (all lanes active).
@@ -1187,32 +1188,30 @@ __device__ inline void put_terms(double* out, int j, bool factors, double a0, do
     else { out[2 * j] = a0 * a1; out[2 * j + 1] = b0 * b1; }
 }
 
-// A block per survivor of the one-pair and two-pair frontiers at a time: the parent's planes come into LDS with
-// 128-bit loads, the instruction is applied there in place (a lane is (slot, quad) as in the classification; the
-// slots of a wavefront take 8 groups side by side, or share the members of a group where the pattern has fewer
-// groups: first the members are put together, then every member's new pairs are written), and the child's planes
-// go out with 128-bit stores.  Groups are disjoint sets of devices, so the wavefronts do not meet.  The rows that
-// a group's members hold set the bytes of the step (s_count), from which the wavefronts then work out the step's
-// time for every query of the enumeration.
+// A block takes a run of survivors, one at a time: the parent's planes come into LDS with 128-bit loads (and stay for the
+// survivors after it that have the same parent: they lie side by side), and every device's new planes go from there straight
+// to the child's place in device memory with 128-bit stores, hashed on the way.  A lane is (slot, quad) as in the
+// classification; a slot takes a group, or the slots share the members of a group where the pattern has fewer groups than
+// the block has slots: first the members are put together (across wavefronts through s_part), then every slot writes its
+// members.  The rows that a group's members hold set the bytes of the step (s_count), from which the wavefronts then work
+// out the step's time for every query of the enumeration.
+// Bound by the child's bytes going out and by the latency of a survivor's chain of a load, two or three barriers and a store.
+// 26 000 children of 512 devices: 660 us when every survivor fetched its parent again, had the instruction applied in place
+// by the wavefronts that a pattern's groups gave work to, in a block that had its compute unit to itself, and 450 now.
+constexpr int kMatRun = 64;                              // survivors whose records are fetched together
 template <int KW, int MW, int NT>
 __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __restrict__ queries, FrontLevel A) {
-    extern __shared__ uint4 ldsq[];                      // A.lds_planes planes of [R][WQ] quads
+    extern __shared__ uint4 ldsq[];                      // the parent: A.lds_planes planes of [R][WQ] quads
     __shared__ PatLds spat[kMaxPatterns];
     __shared__ uint32_t s_count[P2_MAX_DEVICES / 2];     // rows that set a group's bytes
-    __shared__ unsigned long long s_hash[NT / 64];       // the wavefronts' shares of the child's hash
+    __shared__ unsigned long long s_hash[2][NT / 64];    // the wavefronts' shares of the child's hash
+    __shared__ uint4 s_part[NT / 64][3][8];              // the wavefronts' shares of a group that spans several
+    __shared__ FrontSurvivor s_surv[kMatRun];
     using L = FL<KW, MW>;
-    if (A.surv_end && blockIdx.x + *A.surv_from >= *A.surv_end) return;
-    const DevQuery& q = queries[A.query];
-    const int R = q.R;
-    const int plane_q = R * L::WQ;
+    const uint32_t s_from = A.surv_from ? *A.surv_from : 0u, s_end = A.surv_end ? min(*A.surv_end, A.n_surv) : A.n_surv;
+    const uint32_t run = s_end > s_from ? (s_end - s_from + gridDim.x - 1u) / gridDim.x : 0u;
+    const uint32_t i_begin = s_from + blockIdx.x * run, i_end = min(s_end, i_begin + run);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int slot = lane >> 3, qd = lane & 7, sh = slot * 8;
-    const bool is_row = qd < L::QK, is_mask = qd >= L::QK && qd < L::WQ, has_quad = qd < L::WQ;
-    for (int i = tid; i < q.n_patterns; i += NT) {
-        PatLds p;
-        p.g = q.pat[i].g; p.s = q.pat[i].s; p.master = q.pat[i].master; p.n_groups = q.pat[i].n_groups;
-        spat[i] = p;
-    }
     // (the search for equal states among the children, which follows this kernel, counts the distinct ones from zero;
     //  nothing reads the counts of the level's own lists any more)
     if (A.n_reps && blockIdx.x == 0 && tid < 2) A.n_reps[tid] = 0u;
@@ -1223,69 +1222,116 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
         c->n_overflow = 0u; c->n_unknown = 0u; c->t_count[0] = 0u; c->t_count[1] = 0u; c->t_count[2] = 0u;
         c->n_walked_planes = 0u; c->n_walk[0] = 0u; c->n_walk[1] = 0u; c->n_rest = 0u;
     }
-    __syncthreads();
-    const uint32_t i_end = A.surv_end ? min(*A.surv_end, A.n_surv) : A.n_surv;
-    for (uint32_t i = blockIdx.x + (A.surv_from ? *A.surv_from : 0u); i < i_end; i += gridDim.x) {
-        const FrontSurvivor sv = A.surv[i];
+    if (i_begin >= i_end) return;
+    const DevQuery& q = queries[A.query];
+    const int R = q.R;
+    const int plane_q = R * L::WQ;
+    const int slot = lane >> 3, qd = lane & 7, sh = slot * 8;
+    const bool is_row = qd < L::QK, is_mask = qd >= L::QK && qd < L::WQ, has_quad = qd < L::WQ;
+    for (int i = tid; i < q.n_patterns; i += NT) {
+        PatLds p;
+        p.g = q.pat[i].g; p.s = q.pat[i].s; p.master = q.pat[i].master; p.n_groups = q.pat[i].n_groups;
+        spat[i] = p;
+    }
+    uint32_t held = ~0u;                                 // the parent in LDS: its entry, and its list
+    int held_np = 0;
+    uint32_t turn = 0;
+    for (uint32_t i = i_begin; i < i_end; ++i) {
+        const uint32_t in_run = (i - i_begin) % (uint32_t)kMatRun;
+        if (in_run == 0u) {
+            __syncthreads();
+            if (tid < kMatRun && i + (uint32_t)tid < i_end) s_surv[tid] = A.surv[i + (uint32_t)tid];
+            __syncthreads();
+        }
+        const FrontSurvivor sv = s_surv[in_run];
         const int code = sv.code & 0xff;
         // (states only: the goals have none, and children past the lists' room, which the call will say, are left out)
         if (A.surv_end && (code == CODE_GOAL || sv.slot >= (code == CODE_PREFIX2 ? A.cap2 : A.cap1))) continue;
         const int np = (sv.code & kFromTwoPair) ? 2 : 1;
+        if (A.only != 0 && np != A.only) continue;       // (another launch's, which has the LDS for them)
         const size_t plane_w = (size_t)plane_q * 4;
-        const uint4* parent = reinterpret_cast<const uint4*>(np == 2 ? A.states2 + (size_t)sv.entry * 2 * plane_w
-                                                                      : A.states1 + (size_t)sv.entry * plane_w);
         const int cnp = code == CODE_PREFIX2 ? 2 : 1;
         const uint32_t place = sv.slot;                  // the child's place in the next state list of its kind
-        __syncthreads();                                 // (the block is done with the planes and counts of its last survivor)
-        for (int i0 = tid; i0 < np * plane_q; i0 += 8 * NT) {
-            uint4 tmp[8];
+        if (A.n_msg != 0) __syncthreads();               // (the block is done with the counts of its last survivor)
+        if (sv.entry != held || np != held_np) {         // (everyone has passed the barrier behind the last reads of the planes)
+            const uint4* parent = reinterpret_cast<const uint4*>(np == 2 ? A.states2 + (size_t)sv.entry * 2 * plane_w
+                                                                          : A.states1 + (size_t)sv.entry * plane_w);
+            for (int i0 = tid; i0 < np * plane_q; i0 += 8 * NT) {
+                uint4 tmp[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { const int w = i0 + u * NT; tmp[u] = w < np * plane_q ? parent[w] : q_zero(); }
+                for (int u = 0; u < 8; ++u) { const int w = i0 + u * NT; tmp[u] = w < np * plane_q ? parent[w] : q_zero(); }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { const int w = i0 + u * NT; if (w < np * plane_q) ldsq[w] = tmp[u]; }
+                for (int u = 0; u < 8; ++u) { const int w = i0 + u * NT; if (w < np * plane_q) ldsq[w] = tmp[u]; }
+            }
+            held = sv.entry; held_np = np;
+            __syncthreads();
         }
-        if (np == 1 && cnp == 2)                         // the devices that take no part have no second pair
-            for (int w = tid; w < plane_q; w += NT) ldsq[plane_q + w] = q_zero();
-        __syncthreads();
-        // ---- apply the instruction in LDS
+        // ---- apply the instruction
         const uint32_t ins = q.instr_of_digit[sv.digit];
         const int pid = (int)(ins >> 3);
         const PatLds P = spat[pid];
         const int op = (int)(ins & 7u);
-        const int g = P.g, s = P.s, ng = P.n_groups, gs = g * s;
+        const int g = P.g, s = P.s, ng = P.n_groups;
+        constexpr int kSlots = NT / 8;
         int spg = 1;                                     // slots that share a group
-        while (spg * 2 * ng <= 8) spg *= 2;
-        const int gpb = 8 / spg;                         // groups side by side
-        const int my_g = slot / spg, part = slot - my_g * spg;
-        const int trips = (g + spg - 1) / spg;
+        while (spg * 2 * ng <= kSlots && spg < g) spg *= 2;
+        const int gpb = kSlots / spg;                    // groups side by side
+        const int my_slot = wave * 8 + slot;
+        const int my_g = my_slot / spg, part = my_slot - my_g * spg;
+        const int trips = (g + spg - 1) / spg, in_wave = spg < 8 ? spg : 8;
         const bool both = np == 2;                       // the parent has a second plane
-        for (int G0 = wave * gpb; G0 < ng; G0 += (NT / 64) * gpb) {
+        const bool store = code != CODE_GOAL;
+        uint4* const child = reinterpret_cast<uint4*>(cnp == 2 ? A.next_states2 + (size_t)place * 2 * plane_w
+                                                               : A.next_states1 + (size_t)place * plane_w);
+        unsigned long long h = 0;                        // (what the search for equal states goes by)
+        auto put = [&](int d, uint4 a, uint4 b) {        // a device's new pairs
+            const int w = d * L::WQ + qd;
+            child[w] = a;
+            if (q_any(a)) h += hash_quad(a, (uint32_t)w);
+            if (cnp == 2) { child[plane_q + w] = b; if (q_any(b)) h += hash_quad(b, (uint32_t)(plane_q + w)); }
+        };
+        // what the wavefronts of a group have found, put together (the same number of barriers for the whole block)
+        auto gather = [&](uint4& x, uint4& y, uint4& z) {
+            for (int m = 8; m < 8 * in_wave; m <<= 1) { x = q_or(x, q_shfl_xor(x, m)); y = q_or(y, q_shfl_xor(y, m)); z = q_or(z, q_shfl_xor(z, m)); }
+            if (spg <= 8) return;
+            if (slot == 0) { s_part[wave][0][qd] = x; s_part[wave][1][qd] = y; s_part[wave][2][qd] = z; }
+            __syncthreads();
+            const int n = spg / 8, w0 = wave / n * n;
+            for (int w = w0; w < w0 + n; ++w) { x = q_or(x, s_part[w][0][qd]); y = q_or(y, s_part[w][1][qd]); z = q_or(z, s_part[w][2][qd]); }
+        };
+        for (int G0 = 0; G0 < ng; G0 += gpb) {
             const int G = G0 + my_g;
             const bool act = G < ng && has_quad;
-            int base = 0;
-            if (P.master) base = G * gs;
-            else { const int hi = div_small(G, s); base = hi * gs + (G - hi * s); }
+            const int base = cls_base(P, min(G, ng - 1));
             int rows_held = 0;
             if (op == OP_AR || op == OP_RS || op == OP_RD) {
                 // row lanes: u = the rows (every member holds the same), xa = first-pair rows of the members with two pairs;
                 // mask lanes: u = united first masks, mb = united masks of the other side of the split
                 uint4 u = q_zero(), xa = q_zero(), mb = q_zero();
                 bool split = false;
-                for (int it = 0; it < trips; ++it) {
-                    const int t = it * spg + part;
-                    const bool on = act && t < g;
-                    const int d = base + t * s;
-                    const uint4 v0 = on ? ldsq[d * L::WQ + qd] : q_zero();
-                    const uint4 v1 = (both && on) ? ldsq[plane_q + d * L::WQ + qd] : q_zero();
-                    const bool two = ((__ballot(is_row && q_any(v1)) >> sh) & 0xffull) != 0ull;
-                    split |= two;
-                    if (is_row) { u = q_or(u, q_or(v0, v1)); if (two) xa = q_or(xa, v0); }
-                    else { u = q_or(u, v0); mb = q_or(mb, two ? v1 : v0); }
+                if (!both) {
+#pragma unroll 4
+                    for (int it = 0; it < trips; ++it) {
+                        const int t = it * spg + part;
+                        if (act && t < g) u = q_or(u, ldsq[(base + t * s) * L::WQ + qd]);
+                    }
+                    if (!is_row) mb = u;
+                } else {
+                    for (int it = 0; it < trips; ++it) {
+                        const int t = it * spg + part;
+                        const bool on = act && t < g;
+                        const int d = base + t * s;
+                        const uint4 v0 = on ? ldsq[d * L::WQ + qd] : q_zero();
+                        const uint4 v1 = on ? ldsq[plane_q + d * L::WQ + qd] : q_zero();
+                        const bool two = ((__ballot(is_row && q_any(v1)) >> sh) & 0xffull) != 0ull;
+                        split |= two;
+                        if (is_row) { u = q_or(u, q_or(v0, v1)); if (two) xa = q_or(xa, v0); }
+                        else { u = q_or(u, v0); mb = q_or(mb, two ? v1 : v0); }
+                    }
                 }
-                for (int m = 8; m < 8 * spg; m <<= 1) {
-                    u = q_or(u, q_shfl_xor(u, m)); xa = q_or(xa, q_shfl_xor(xa, m)); mb = q_or(mb, q_shfl_xor(mb, m));
-                    split |= __shfl_xor((int)split, m, 64) != 0;
-                }
+                gather(u, xa, mb);
+                // (a member with two pairs has rows in both: its group is split if some first-pair rows were seen)
+                split = both && ((__ballot(is_row && q_any(xa)) >> sh) & 0xffull) != 0ull;
                 rows_held = sum_slot((act && is_row) ? q_popc(u) : 0);
                 // the group's result: rows xa (or all of them) with the united first masks, the other rows with mb
                 const uint4 ra = is_row ? (split ? xa : u) : u;
@@ -1300,7 +1346,6 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                     for (int it = 0; it < trips; ++it) {
                         const int t = it * spg + part;
                         const bool on = act && t < g;
-                        const int d = base + t * s;
                         const int lo = t * per, hi = lo + per;
                         uint4 blk = q_zero();
                         if (is_row) {
@@ -1312,18 +1357,17 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                         }
                         uint4 a = is_row ? q_and(blk, ra) : ra, b = is_row ? q_and(blk, rb) : rb;
                         canonical_slot(a, b, is_row, is_mask, qd, sh);
-                        if (on) { ldsq[d * L::WQ + qd] = a; if (cnp == 2) ldsq[plane_q + d * L::WQ + qd] = b; }
+                        if (on && store) put(base + t * s, a, b);
                     }
                 } else {
                     uint4 a = ra, b = rb;
                     canonical_slot(a, b, is_row, is_mask, qd, sh);
-                    for (int it = 0; it < trips; ++it) {
-                        const int t = it * spg + part;
-                        const bool on = act && t < g;
-                        const int d = base + t * s;
-                        const bool keeps = op == OP_AR || t == 0;        // Reduce: the root alone keeps the result
-                        if (on) { ldsq[d * L::WQ + qd] = keeps ? a : q_zero(); if (cnp == 2) ldsq[plane_q + d * L::WQ + qd] = keeps ? b : q_zero(); }
-                    }
+                    if (store)
+                        for (int it = 0; it < trips; ++it) {
+                            const int t = it * spg + part;
+                            const bool keeps = op == OP_AR || t == 0;    // Reduce: the root alone keeps the result
+                            if (act && t < g) put(base + t * s, keeps ? a : q_zero(), keeps ? b : q_zero());
+                        }
                 }
             } else if (op == OP_AG) {
                 // the first member's first mask, and whatever differs from it (at most one other mask: the
@@ -1336,7 +1380,8 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                     const int d = base + t * s;
 #pragma unroll
                     for (int pl = 0; pl < 2; ++pl) {
-                        const uint4 v = (on && (pl == 0 || both)) ? ldsq[pl * plane_q + d * L::WQ + qd] : q_zero();
+                        if (pl == 1 && !both) continue;
+                        const uint4 v = on ? ldsq[pl * plane_q + d * L::WQ + qd] : q_zero();
                         const bool there = ((__ballot(is_row && q_any(v)) >> sh) & 0xffull) != 0ull;
                         const bool other = ((__ballot(is_mask && q_any(q_xor(v, d0))) >> sh) & 0xffull) != 0ull;
                         if (there) {
@@ -1345,56 +1390,47 @@ __global__ __launch_bounds__(NT) void k_front_materialize(const DevQuery* __rest
                         }
                     }
                 }
-                for (int m = 8; m < 8 * spg; m <<= 1) {
-                    x0 = q_or(x0, q_shfl_xor(x0, m)); x1 = q_or(x1, q_shfl_xor(x1, m)); d1 = q_or(d1, q_shfl_xor(d1, m));
-                }
+                gather(x0, x1, d1);
                 rows_held = sum_slot((act && is_row) ? q_popc(q_or(x0, x1)) : 0);
                 uint4 a = is_row ? x0 : d0, b = is_row ? x1 : d1;
                 canonical_slot(a, b, is_row, is_mask, qd, sh);
-                for (int it = 0; it < trips; ++it) {
-                    const int t = it * spg + part;
-                    const bool on = act && t < g;
-                    const int d = base + t * s;
-                    if (on) { ldsq[d * L::WQ + qd] = a; if (cnp == 2) ldsq[plane_q + d * L::WQ + qd] = b; }
-                }
+                if (store)
+                    for (int it = 0; it < trips; ++it) {
+                        const int t = it * spg + part;
+                        if (act && t < g) put(base + t * s, a, b);
+                    }
             } else {
                 // Broadcast: the root's pairs, as they are
                 const uint4 a = act ? ldsq[base * L::WQ + qd] : q_zero();
                 const uint4 b = (act && both) ? ldsq[plane_q + base * L::WQ + qd] : q_zero();
                 rows_held = sum_slot((act && is_row) ? q_popc(q_or(a, b)) : 0);
-                for (int it = 0; it < trips; ++it) {
-                    const int t = it * spg + part;
-                    const bool on = act && t < g && t > 0;
-                    const int d = base + t * s;
-                    if (on) { ldsq[d * L::WQ + qd] = a; if (cnp == 2) ldsq[plane_q + d * L::WQ + qd] = b; }
-                }
+                if (store)
+                    for (int it = 0; it < trips; ++it) {
+                        const int t = it * spg + part;
+                        if (act && t < g) put(base + t * s, a, b);
+                    }
             }
             if (qd == 0 && part == 0 && G < ng) s_count[G] = (uint32_t)rows_held;
         }
-        __syncthreads();
-        if (code != CODE_GOAL) {
-            uint4* child = reinterpret_cast<uint4*>(cnp == 2 ? A.next_states2 + (size_t)place * 2 * plane_w
-                                                             : A.next_states1 + (size_t)place * plane_w);
-            unsigned long long h = 0;                    // (what the search for equal states goes by)
-            for (int w = tid; w < cnp * plane_q; w += NT) {
-                const uint4 v = ldsq[w];
-                child[w] = v;
-                if (q_any(v)) h += hash_quad(v, (uint32_t)w);
-            }
+        if (store) {
+            if (P.master && has_quad)                    // the devices that take no part stay as they are
+                for (int d = my_slot; d < R; d += kSlots)
+                    if (div_small(d, s) * s != d) put(d, ldsq[d * L::WQ + qd], both ? ldsq[plane_q + d * L::WQ + qd] : q_zero());
             uint32_t hl = (uint32_t)h, hh = (uint32_t)(h >> 32);
             for (int o = 32; o > 0; o >>= 1) {
                 const unsigned long long other = ((unsigned long long)(uint32_t)__shfl_xor((int)hh, o, 64) << 32) | (uint32_t)__shfl_xor((int)hl, o, 64);
                 h += other;
                 hl = (uint32_t)h; hh = (uint32_t)(h >> 32);
             }
-            if (lane == 0) s_hash[wave] = h;
+            if (lane == 0) s_hash[turn & 1u][wave] = h;
         }
         __syncthreads();
-        if (code != CODE_GOAL && tid == 0) {             // (written, not added up: the list needs no clearing)
-            unsigned long long h = 0;
-            for (int w = 0; w < NT / 64; ++w) h += s_hash[w];
-            (cnp == 2 ? A.next_hash2 : A.next_hash1)[place] = h;
+        if (store && tid == 0) {                         // (written, not added up: the list needs no clearing)
+            unsigned long long all = 0;
+            for (int w = 0; w < NT / 64; ++w) all += s_hash[turn & 1u][w];
+            (cnp == 2 ? A.next_hash2 : A.next_hash1)[place] = all;
         }
+        ++turn;
         // ---- the step's time for every query of the enumeration (alpha-beta model: latency steps of the
         //      slowest group's link; bytes through the busiest uplink, from the query's bandwidth rows)
         if (A.n_msg == 0) continue;
