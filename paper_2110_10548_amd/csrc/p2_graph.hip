@@ -952,6 +952,8 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
     __shared__ uint32_t s_query, s_graph, s_member, s_block, s_count;
     __shared__ u64 s_first;
     __shared__ double s_sum[2][256];
+    __shared__ double s_steps[kGraphPatterns * 5], s_alpha[kGraphPatterns * 5], s_per[kGraphPatterns * 5];   // what a step costs, by digit
+    __shared__ uint8_t s_instr[kGraphPatterns * 5];
     const uint32_t tid = threadIdx.x;
     if (ctrs_out && blockIdx.x == gridDim.x - 1u) {       // (the host reads the counts with the rows)
         const uint4* const from = reinterpret_cast<const uint4*>(ctrs);
@@ -995,6 +997,20 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
     if (row0 + rows > cap_rows) return;                   // (the host sees that there are more, and asks again with room)
     const Graph<InDevice> G = open_in_device(graphs[s_graph]);
     const DevQuery& q = queries[s_query];
+    // (worked out once per block: with two divisions a step in every row, the kernel took 900 us for 8.2 million rows of
+    //  four levels, and takes 780)
+    for (uint32_t d = tid; d < (uint32_t)q.alphabet; d += 256u) {
+        const uint32_t ins = q.instr_of_digit[d];
+        const int pid = (int)(ins >> 3), op = (int)(ins & 7u);
+        s_instr[d] = (uint8_t)(pid * 5 + op);
+        if (q.n_msg > 0) {
+            const DevPattern& P = q.pat[pid];
+            double ring_steps, mult;
+            step_factors(op, P.g, q.algo, ring_steps, mult);
+            s_steps[d] = ring_steps; s_alpha[d] = q.alpha[P.span_level]; s_per[d] = mult / (double)q.k;
+        }
+    }
+    __syncthreads();
     if (tid < rows) {
         const uint32_t member = s_member;
         uint32_t j = t;
@@ -1014,26 +1030,35 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
             pr.instr[s] = 0;
             if (s >= len) continue;
             const int left = len - s;                     // instructions from here on
+            // (four edges' counts in flight: edge after edge, each count a load behind its edge's, the walks were the whole of
+            //  the kernel: 8.2 million rows of four levels 1 050 us, and 900 so)
             uint32_t e = G.first_edge[node], edge = 0u;
             const uint32_t end = G.first_edge[node + 1u];
-            for (; e < end; ++e) {
-                edge = G.edges[e];
-                const uint32_t target = edge & kGoalEdge;
-                const uint32_t n = target == kGoalEdge ? (left == 1 ? 1u : 0u) : left > 1 ? G.use_ends[(size_t)target * 8 + left - 1] : 0u;
-                if (j < n) break;
-                j -= n;
+            for (bool found = false; !found && e < end;) {
+                uint32_t four[4], n[4];
+#pragma unroll
+                for (uint32_t u = 0; u < 4u; ++u) four[u] = G.edges[e + u < end ? e + u : end - 1u];
+#pragma unroll
+                for (uint32_t u = 0; u < 4u; ++u) {
+                    const uint32_t target = four[u] & kGoalEdge;
+                    const uint32_t ends = G.use_ends[(size_t)(target == kGoalEdge ? 0u : target) * 8 + (left > 1 ? left - 1 : 0)];
+                    n[u] = e + u >= end ? 0u : target == kGoalEdge ? (left == 1 ? 1u : 0u) : left > 1 ? ends : 0u;
+                }
+                uint32_t at = e + 4u < end ? e + 4u : end;
+#pragma unroll
+                for (uint32_t u = 0; u < 4u; ++u) {
+                    if (found) continue;
+                    if (j < n[u]) { found = true; edge = four[u]; at = e + u; }
+                    else j -= n[u];
+                }
+                e = at;
             }
             const uint32_t digit = edge >> kDigitShift;
-            const uint32_t ins = q.instr_of_digit[digit];
-            const int pid = (int)(ins >> 3), op = (int)(ins & 7u);
-            pr.instr[s] = (uint8_t)(pid * 5 + op);
+            pr.instr[s] = s_instr[digit];
             number = number * (u64)q.alphabet + digit;
             node = left > 1 && e < end ? edge & kGoalEdge : node;
             if (q.n_msg > 0 && e < end) {
-                const DevPattern& P = q.pat[pid];
-                double ring_steps, mult;
-                step_factors(op, P.g, q.algo, ring_steps, mult);
-                const double alpha = q.alpha[P.span_level], per = mult / (double)q.k, best = G.best[(size_t)e * G.n_members + member];
+                const double ring_steps = s_steps[digit], alpha = s_alpha[digit], per = s_per[digit], best = G.best[(size_t)e * G.n_members + member];
                 // (rounded as in the engines whose place this one takes: the walk's costs are fused, the frontier's steps are not)
                 if (G.fused) { sum_alpha = fma(ring_steps, alpha, sum_alpha); sum_beta = fma(per, best, sum_beta); }
                 else { sum_alpha = add_rounded(sum_alpha, ring_steps, alpha); sum_beta = add_rounded(sum_beta, per, best); }
