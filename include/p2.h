@@ -71,7 +71,8 @@ int32_t p2_enumerate_placements(const p2_hierarchy* h, const int32_t* axes, int3
 #define P2_ENGINE_AUTO 0      /* where the shared-prefix engine applies and the chunks are a multiple of
                                  the group's devices, or at most 64, the graph of the distinct states
                                  that the programs pass through (up to 36 patterns, size limits of 7, 6,
-                                 5, 4 for up to 9, 16, 25, 36); and the same graph in place of the
+                                 5, 4 for up to 9, 16, 25, 36; not for up to 2^14 candidates beside
+                                 queries that are walked); and the same graph in place of the
                                  frontier engine, within these size limits, where two pairs a device
                                  fit in LDS.  Reported as the engine it stands in for: shared-prefix
                                  up to 2^30 candidates, frontier above.  Else the

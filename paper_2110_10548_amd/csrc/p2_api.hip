@@ -368,6 +368,11 @@ bool large_graph_applies(const p2::Plan& pl) {
     if (n_pat > (size_t)p2::kGraphPatterns || pl.max_len > (n_pat <= 9 ? 7 : n_pat <= 16 ? 6 : n_pat <= 25 ? 5 : 4)) return false;
     return p2::frontier_max_pairs(pl.R, graph_rows(pl)) == 2;
 }
+// A call that walks some of its queries in any case has its state graphs' queries walked beside them, in the same launches,
+// if none has more candidates than this: the graphs' chain of launches would come on top (search of 6 x 16 devices, axes 32 x
+// 3, three instructions, 8 420 candidates beside 20: 168 us all walked, 186 with a graph; 3 x 16, axes 4 x 12: 423 and 446;
+// four instructions, 168 420 candidates, 6 x 16: 716 and 546).
+constexpr unsigned long long kWalkedBesideMax = 1ull << 14;
 // Room for the states of a structure (see above), first guess; a structure that has more is met with four times as much.
 uint32_t graph_room(const p2::Plan& pl) {
     static const uint32_t levels[5][P2_MAX_LEN + 1] = {{0, 96, 96, 96, 96, 96, 96, 96},
@@ -592,6 +597,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     }
 
     take_large_graphs();
+    {
+        bool walks = false, few = true;
+        for (const QueryRun& r : runs) {
+            walks |= !r.graph && !r.frontier && r.plan.n_candidates != 0;
+            few &= !r.graph || (!r.graph_large && !r.graph_frontier && r.plan.n_candidates <= kWalkedBesideMax);
+        }
+        if (walks && few)
+            for (QueryRun& r : runs) r.graph = false;
+    }
     // queries of one reduction structure are answered from one graph
     struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t n_blocks = 0; bool small = false, large = false;
                    size_t off_members = 0, off_query = 0; };

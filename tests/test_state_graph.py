@@ -146,3 +146,17 @@ def test_lists_too_large_for_the_graphs():
         assert np.array_equal(r["programs"], one["programs"]) and np.array_equal(r["cost"], one["cost"])
         for key in COUNTS:
             assert r["stats"][key] == one["stats"][key], key
+
+
+@pytest.mark.gpu
+def test_small_spaces_beside_walked_queries():
+    """Spaces just within and beyond what is walked beside a query that no graph answers: the same rows as alone."""
+    from paper_2110_10548_amd import binding as B
+    odd = _query([3], 3)
+    for small in ([_query([2, 16], 3)], [_query([4, 8], 4)], [_query([2, 16], 3), _query([4, 8], 4), _query([4], 2, topk=2)]):
+        together = B.p2_synthesize_batch([odd] + small, MSG)
+        for q, r in zip([odd] + small, together):
+            o = B.p2_synthesize_batch([q], MSG)[0]
+            assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"]) and len(o["programs"]) > 0
+            for key in COUNTS:
+                assert r["stats"][key] == o["stats"][key], key
