@@ -780,6 +780,11 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
     }
 }
 
+// Bound by latency: a state's lane exchanges, then a look at the table and a place in the lists.  Launches per level, not one
+// kernel for all: a level needs the whole chip (17 274 states of 64 devices, six levels: 370 us a launch beside other groups'
+// kernels) and the next one all of it.  The 18 structures of 140 queries of [4 8 8], five levels: 180 us, where walking the
+// stems (k_eval_shared), the groups that it hands over and the programs' costs took 3.5 ms; three queries of [4 2 4]: 54 of
+// 110 us.
 constexpr int kLevelThreads = 256;
 template <int kPairs>
 __global__ __launch_bounds__(kLevelThreads) void k_graph_level(const DevGraph* __restrict__ graphs, const GraphBlock* __restrict__ blocks, int level) {
@@ -806,7 +811,9 @@ __global__ __launch_bounds__(kFinishThreads) void k_graph_finish(const DevGraph*
 }
 
 // Structures of one or two levels: a block goes through all levels and the counts by itself, with everything it works on
-// in LDS, two pairs a device (no such structure needs more).
+// in LDS, two pairs a device (no such structure needs more).  Bound by the chain of the levels in one block; launches per
+// level would add some 5 us each, and their lists' round trips to L2.  [2 4], three levels: 28 us, where the walk, the groups handed
+// over and the costs took 32 in three launches; [4 16], five levels: 68 us, where they took 120.
 __global__ __launch_bounds__(kAloneThreads) void k_graph_alone(const DevGraph* __restrict__ graphs, const uint32_t* __restrict__ list) {
     extern __shared__ __attribute__((aligned(16))) u64x2 planes[];
     __shared__ Found found[kAloneThreads / kWave];
@@ -838,7 +845,8 @@ __global__ __launch_bounds__(kAloneThreads) void k_graph_alone(const DevGraph* _
 // What every edge on the way to a goal adds to the bandwidth sum of each query of its structure: a wavefront per edge.
 // Where all groups of the pattern hold the same number of rows (four fifths of the edges) the busiest unit of a level
 // carries that number times the level's largest sum of multiplicities, and a lane answers for a query; else the
-// queries' bandwidth rows are walked, one query after the other.
+// queries' bandwidth rows are walked, one query after the other.  Bound by L2 latency: an edge is a chain of its state, the
+// pattern's entry and the rows.  [2 4]: 8 us, [4 16], three sizes: 26; 512 queries of [2 4 8 8]: 0.9 ms of the call's 15.5.
 constexpr int kStepWaves = 4;
 __global__ __launch_bounds__(kStepWaves * kWave) void k_graph_steps(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
                                                                     const GraphBlock* __restrict__ blocks) {
