@@ -783,7 +783,7 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
 // Bound by latency: a state's lane exchanges, then a look at the table and a place in the lists.  Launches per level, not one
 // kernel for all: a level needs the whole chip (17 274 states of 64 devices, six levels: 370 us a launch beside other groups'
 // kernels) and the next one all of it.  The 18 structures of 140 queries of [4 8 8], five levels: 180 us, where walking the
-// stems (k_eval_shared), the groups that it hands over and the programs' costs took 3.5 ms; three queries of [4 2 4]: 54 of
+// stems (k_eval_shared), the groups that it hands over and the programs' costs took 3.5 ms; 26 queries of [4 2 4]: 54 of
 // 110 us.
 constexpr int kLevelThreads = 256;
 template <int kPairs>
