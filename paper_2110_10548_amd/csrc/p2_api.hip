@@ -626,12 +626,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // Every query answered from a graph: the whole call is one stream of kernels, tables and results travel by kernels that
     // read and write pinned host memory, and where no shortlist is asked for the rows go straight there.
     const bool only_graphs = n_others == 0 && !graphs.empty();
+    // (rows are dealt out 256 to a block query by query: as many rows as there is room for, however the queries share them, take
+    //  a block per 256 and at most one more per query)
     size_t rows_guess = 0, emit_blocks = 0;
-    if (only_graphs)
+    if (only_graphs) {
         for (const QueryRun& r : runs)
-            if (r.graph) { const size_t n = graph_rows_guess(r.plan); rows_guess += n; emit_blocks += (n + 255) / 256; }
+            if (r.graph) { rows_guess += graph_rows_guess(r.plan); ++emit_blocks; }
+        emit_blocks += rows_guess / 256;
+    }
     bool direct = only_graphs && !any_topk && cap > 0;
-
 
     // Validity depends on the reduction group, the chunks, the patterns and the alphabet only (not on the
     // links, nor on where the placement puts the group in the system): a query that equals an earlier one of

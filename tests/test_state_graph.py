@@ -160,3 +160,19 @@ def test_small_spaces_beside_walked_queries():
             assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"]) and len(o["programs"]) > 0
             for key in COUNTS:
                 assert r["stats"][key] == o["stats"][key], key
+
+
+SIX, FIVE, FEW = _query([2] * 6, 4), _query([2] * 5, 4), _query([2, 4], 5, n_chunks=1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("queries", [[SIX] + [FEW] * 36, [FEW] * 36 + [SIX], [SIX] * 2 + [FIVE] * 9, [FEW] * 12 + [_query([64], 5)] + [SIX] + [FEW] * 30])
+def test_rows_beyond_one_querys_room(queries):
+    """One query has more valid programs than the call makes room for, the others fewer: in all they fit, and every row is there."""
+    from paper_2110_10548_amd import binding as B
+    queries = [dict(q, bw=[b * (1.0 + 0.01 * i) for b in q["bw"]]) for i, q in enumerate(queries)]
+    B.p2_synthesize_batch([dict(q, bw=q["bw"][::-1], algo=1) for q in queries[::-1]], MSG)       # (other rows where these go)
+    together = B.p2_synthesize_batch(queries, MSG)
+    for q, r in zip(queries, together):
+        o = B.p2_synthesize_batch([q], MSG)[0]
+        assert len(o["programs"]) > 0 and np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"])
