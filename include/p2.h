@@ -179,6 +179,14 @@ typedef struct {
     uint8_t instr[7];
 } p2_program;
 
+/* p2_stats.route.  Results do not depend on it; the last two bits hold for every query of a call. */
+#define P2_ROUTE_GRAPH 1        /* answered from a state graph (`engine`: the one that it stands in for)  */
+#define P2_ROUTE_GRAPH_LEFT 2   /* a state graph was given up (no room for it, or a state that it cannot
+                                   hold) and `engine` evaluated the query                                  */
+#define P2_ROUTE_REPEATED 4     /* some list was too short and the evaluation was repeated                 */
+#define P2_ROUTE_ROWS_LATER 8   /* the programs were more than expected, and were written once counted
+                                   instead of with the evaluation                                          */
+
 /* Counters of one query (all optional outputs). */
 typedef struct {
     uint64_t candidates;       /* programs of length <= max_len over the alphabet: the candidate
@@ -208,7 +216,7 @@ typedef struct {
                                   evaluation this one shares (its validity results are that
                                   query's, its costs its own; steps_* and members_* repeat that
                                   query's figures), or -1: evaluated for itself                   */
-    int32_t reserved0;
+    int32_t route;             /* P2_ROUTE_* bits: which way engine AUTO took                      */
 } p2_stats;
 
 /* Sec. 3.5 on one placement: evaluate every program of length <= max_len.  A program is valid

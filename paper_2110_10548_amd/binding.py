@@ -17,6 +17,7 @@ LIB_PATH = os.environ.get("P2_LIB_PATH", os.path.join(HERE, "libp2.so"))
 P2_OK, P2_EINVAL, P2_ENOSPC, P2_EUNSUPPORTED, P2_EDEVICE = 0, -1, -2, -3, -4
 ENGINE_AUTO, ENGINE_LITERAL, ENGINE_COMPACT, ENGINE_FRONTIER, ENGINE_SMALL, ENGINE_SHARED = 0, 1, 2, 3, 4, 5
 OPS = ("AllReduce", "ReduceScatter", "AllGather", "Reduce", "Broadcast")
+ROUTE_GRAPH, ROUTE_GRAPH_LEFT, ROUTE_REPEATED, ROUTE_ROWS_LATER = 1, 2, 4, 8
 FORMS = ("InsideGroup", "Parallel", "Master")
 
 
@@ -45,7 +46,7 @@ class p2_stats(C.Structure):
     _fields_ = [("candidates", C.c_uint64), ("steps_executed", C.c_uint64), ("literal_reruns", C.c_uint64),
                 ("member_visits", C.c_uint64), ("valid", C.c_int64), ("group_size", C.c_int32), ("n_patterns", C.c_int32), ("alphabet", C.c_int32),
                 ("engine", C.c_int32), ("steps_evaluated", C.c_uint64), ("members_evaluated", C.c_uint64),
-                ("evaluated_with", C.c_int32), ("reserved0", C.c_int32)]
+                ("evaluated_with", C.c_int32), ("route", C.c_int32)]
 
 
 class p2_profile(C.Structure):

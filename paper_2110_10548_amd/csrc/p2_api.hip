@@ -473,9 +473,10 @@ struct QueryRun {
     size_t out_first = 0;                 // first row of this query in the sorted/prog/cost buffers
 };
 
-constexpr int32_t kWithoutGraphs = 1;      // (internal) the call is to be repeated without the state-graph engine
+constexpr int32_t kWithoutGraphs = 1;      // (internal) the call is to be repeated without the state graphs that `left` names now
+// left: per query, whether a state graph was given up for it (the other engines evaluate it).
 int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* msg_bytes, int32_t n_msg,
-                     p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset, p2_stats* stats, bool graphs_allowed) {
+                     p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset, p2_stats* stats, std::vector<char>& left) {
     using namespace p2;
     if (!queries || n_queries < 1 || !out_offset) return fail(P2_EINVAL, "null or empty query list");
     if (n_msg < 0 || (n_msg > 0 && !msg_bytes)) return fail(P2_EINVAL, "bad message size list");
@@ -566,7 +567,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         // valid programs of these queries are costed one per wavefront, lanes as devices
         runs[i].wave_cost = runs[i].engine == P2_ENGINE_COMPACT && pl.R <= 64;
         for (const Pattern& p : pl.patterns) runs[i].wave_cost = runs[i].wave_cost && reg_shape_of(p.g, p.s, p.master, 6) >= 0;
-        if (graphs_allowed && want == P2_ENGINE_AUTO && graph_applies(pl)) {
+        if (!left[i] && want == P2_ENGINE_AUTO && graph_applies(pl)) {
             runs[i].graph = true;
             runs[i].graph_frontier = runs[i].frontier;
             runs[i].frontier = runs[i].flat_counts = false;
@@ -577,7 +578,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         for (int i = 0; i < n_queries; ++i) {
             QueryRun& r = runs[i];
             const int want = queries[i].opt ? queries[i].opt->engine : P2_ENGINE_AUTO;
-            if (!graphs_allowed || want != P2_ENGINE_AUTO || !r.frontier || r.graph || !large_graph_applies(r.plan)) continue;
+            if (left[i] || want != P2_ENGINE_AUTO || !r.frontier || r.graph || !large_graph_applies(r.plan)) continue;
             r.graph = r.graph_large = true;
             r.graph_frontier = true; r.graph_flat = r.flat_counts;
             r.frontier = r.flat_counts = false;
@@ -634,8 +635,12 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             if (r.graph) { rows_guess += graph_rows_guess(r.plan); ++emit_blocks; }
         emit_blocks += rows_guess / 256;
     }
-    bool direct = only_graphs && !any_topk && cap > 0;
-
+    const bool rows_at_once = only_graphs && !any_topk && cap > 0;
+    bool direct = rows_at_once;
+    auto leave_graphs = [&]() -> int32_t {
+        for (int i = 0; i < n_queries; ++i) left[i] |= runs[i].graph ? 1 : 0;
+        return kWithoutGraphs;
+    };
     // Validity depends on the reduction group, the chunks, the patterns and the alphabet only (not on the
     // links, nor on where the placement puts the group in the system): a query that equals an earlier one of
     // the batch in these is not evaluated again; it takes over the list of valid programs and the counts, and
@@ -1063,7 +1068,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
             P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
         }
-        if (mem + zero + states_bytes > kGraphBytesMax) return kWithoutGraphs;
+        if (mem + zero + states_bytes > kGraphBytesMax) return leave_graphs();
         bool room = C.g_zero.ensure(zero) == hipSuccess && C.g_mem.ensure(mem) == hipSuccess;
         for (size_t g = 0; g < n_graphs && room; ++g) {
             if (!graphs[g].large) continue;
@@ -1072,7 +1077,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         if (!room) {                                     // (the other engines need less)
             (void)hipGetLastError();
-            return kWithoutGraphs;
+            return leave_graphs();
         }
         P2_HIP(C.h_gctr.ensure(graph_back + 16));
         graph_zero = zero;
@@ -1195,7 +1200,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         P2_HIP(launch_front_links(K, 64u, on));
         return P2_OK;
     };
-    std::vector<char> done(n_queries, 0);
+    bool repeated = false;
     for (int attempt = 0; attempt < 4; ++attempt) {
         auto tot = layout_lists();
         P2_HIP(C.valid.ensure(sizeof(unsigned long long) * std::max<size_t>(tot.first, 1)));
@@ -1413,7 +1418,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         bool again = false;
         const GraphCounters* const hg = static_cast<const GraphCounters*>(C.h_gctr.p);
         for (size_t g = 0; g < graphs.size(); ++g) {
-            if ((hg[g].flags & ~kGraphFull) != 0u || (hg[g].flags != 0u && attempt == 3)) return kWithoutGraphs;
+            if ((hg[g].flags & ~kGraphFull) != 0u || (hg[g].flags != 0u && attempt == 3)) return leave_graphs();
             if (hg[g].flags == 0u) continue;
             again = true;
         }
@@ -1465,7 +1470,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                     listed += prefixes;
                 }
                 for (int len = 1; len <= pl.max_len; ++len) valid += gc.n_valid[len];
-                if (valid > 0xffffffffull) return kWithoutGraphs;
+                if (valid > 0xffffffffull) return leave_graphs();
                 r.n_valid = (uint32_t)valid; r.n_rerun = r.n_rerun_groups = 0;
                 const unsigned long long applied = r.graph_frontier && !r.graph_flat ? listed : walked;
                 r.steps = applied * (unsigned long long)pl.alphabet; r.members = applied * per_alphabet;
@@ -1492,6 +1497,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
         }
         if (!again) break;
+        repeated = true;
         if (attempt == 3) return fail(P2_EDEVICE, "result lists kept overflowing");
     }
 
@@ -2295,7 +2301,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
             s.valid = r.n_valid; s.group_size = r.plan.R; s.n_patterns = (int32_t)r.plan.patterns.size();
             s.evaluated_with = r.graph ? (graphs[r.graph_id].leader != i ? graphs[r.graph_id].leader : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
-            s.reserved0 = 0;
+            s.route = (r.graph ? P2_ROUTE_GRAPH : 0) | (left[i] ? P2_ROUTE_GRAPH_LEFT : 0) | (repeated ? P2_ROUTE_REPEATED : 0) |
+                      (rows_at_once && store && !direct ? P2_ROUTE_ROWS_LATER : 0);
             s.alphabet = r.plan.alphabet; s.engine = r.frontier || r.graph_frontier ? P2_ENGINE_FRONTIER : r.shared ? P2_ENGINE_SHARED : r.regs ? P2_ENGINE_SMALL : r.engine;
         }
     }
@@ -2307,8 +2314,10 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
 
 int32_t run_batch(const p2_query* queries, int32_t n_queries, const double* msg_bytes, int32_t n_msg,
                   p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset, p2_stats* stats) {
-    int32_t rc = run_batch_on(queries, n_queries, msg_bytes, n_msg, out_prog, out_cost, cap, out_offset, stats, true);
-    if (rc == kWithoutGraphs) rc = run_batch_on(queries, n_queries, msg_bytes, n_msg, out_prog, out_cost, cap, out_offset, stats, false);
+    std::vector<char> left((size_t)std::max(n_queries, 0), 0);
+    int32_t rc;
+    do rc = run_batch_on(queries, n_queries, msg_bytes, n_msg, out_prog, out_cost, cap, out_offset, stats, left);
+    while (rc == kWithoutGraphs);                        // (every time without a graph more)
     return rc;
 }
 

@@ -176,3 +176,15 @@ def test_rows_beyond_one_querys_room(queries):
     for q, r in zip(queries, together):
         o = B.p2_synthesize_batch([q], MSG)[0]
         assert len(o["programs"]) > 0 and np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"])
+
+
+@pytest.mark.gpu
+def test_stats_say_which_way_was_taken():
+    """What answered a query: a graph, or another engine since the graph was asked not to be used, or had to be given up."""
+    from paper_2110_10548_amd import binding as B
+    routes = [B.p2_synthesize_batch([q], MSG)[0]["stats"]["route"] for q in (_query([4, 4], 4), _query([3, 4, 6], 4), _query([4, 4], 4, engine=5),
+                                                                             _query([3, 4, 6], 4, frontier_pairs=2), _query([3], 3), _query([2, 2], 3, hierarchy=1))]
+    assert routes == [B.ROUTE_GRAPH, B.ROUTE_GRAPH, 0, 0, 0, 0]
+    q = _query([2, 2, 4, 4], 6, op_mask=1, topk=3)
+    many = B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY)] * 900, MSG)        # (more lists than there is room for)
+    assert {r["stats"]["route"] for r in many} == {B.ROUTE_GRAPH_LEFT}
