@@ -629,14 +629,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     const bool only_graphs = n_others == 0 && !graphs.empty();
     // (rows are dealt out 256 to a block query by query: as many rows as there is room for, however the queries share them, take
     //  a block per 256 and at most one more per query)
-    size_t rows_guess = 0, emit_blocks = 0;
-    if (only_graphs) {
+    size_t rows_room = 0, emit_blocks = 0;
+    if (only_graphs && !any_topk) {
         for (const QueryRun& r : runs)
-            if (r.graph) { rows_guess += graph_rows_guess(r.plan); ++emit_blocks; }
-        emit_blocks += rows_guess / 256;
+            if (r.graph) { rows_room += graph_rows_guess(r.plan); ++emit_blocks; }
+        rows_room = rows_at_once(rows_room, cap, n_msg);
+        emit_blocks += rows_room / 256;
     }
-    const bool rows_at_once = only_graphs && !any_topk && cap > 0;
-    bool direct = rows_at_once;
+    bool direct = rows_room > 0;
+    const bool wanted_direct = direct;
     auto leave_graphs = [&]() -> int32_t {
         for (int i = 0; i < n_queries; ++i) left[i] |= runs[i].graph ? 1 : 0;
         return kWithoutGraphs;
@@ -1402,11 +1403,14 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         if (!gsteps.empty())
             P2_HIP(launch_graph_steps(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gsteps), (unsigned)gsteps.size(), stream));
+        if (direct && (C.h_progs.ensure(sizeof(p2_program) * rows_room) != hipSuccess ||
+                       C.h_costs.ensure(sizeof(double) * rows_room * (size_t)std::max(n_msg, 1)) != hipSuccess)) {
+            (void)hipGetLastError();                     // (the rows themselves may well need less)
+            direct = false;
+        }
         if (direct) {
-            P2_HIP(C.h_progs.ensure(sizeof(p2_program) * rows_guess));
-            P2_HIP(C.h_costs.ensure(sizeof(double) * rows_guess * (size_t)std::max(n_msg, 1)));
             P2_HIP(launch_graph_emit(dqs, dgs, static_cast<const GraphCounters*>(C.g_zero.p), reinterpret_cast<const GraphQuery*>(db + off_gasked),
-                                     n_queries, nullptr, 0, (unsigned)emit_blocks + 1u, rows_guess, nullptr, static_cast<p2_program*>(C.h_progs.p),
+                                     n_queries, nullptr, 0, (unsigned)emit_blocks + 1u, rows_room, nullptr, static_cast<p2_program*>(C.h_progs.p),
                                      static_cast<double*>(C.h_costs.p), C.h_gctr.p, (int)graphs.size(), stream));
             if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = 2; }
         } else {
@@ -1985,7 +1989,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     bool only_shortlists = n_msg > 0;
     for (const auto& r : runs) only_shortlists = only_shortlists && (r.n_valid == 0 || r.topk > 0);
     size_t pos_off = 0;
-    direct = direct && store && total_valid <= rows_guess;       // (the rows are in host memory already)
+    direct = direct && store && total_valid <= rows_room;       // (the rows are in host memory already)
     if (store && !direct) {
     P2_HIP(C.sorted.ensure(sizeof(unsigned long long) * std::max<size_t>(total_valid, 1)));
     P2_HIP(C.progs.ensure(sizeof(p2_program) * std::max<size_t>(total_valid, 1)));
@@ -2302,7 +2306,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             s.valid = r.n_valid; s.group_size = r.plan.R; s.n_patterns = (int32_t)r.plan.patterns.size();
             s.evaluated_with = r.graph ? (graphs[r.graph_id].leader != i ? graphs[r.graph_id].leader : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
             s.route = (r.graph ? P2_ROUTE_GRAPH : 0) | (left[i] ? P2_ROUTE_GRAPH_LEFT : 0) | (repeated ? P2_ROUTE_REPEATED : 0) |
-                      (rows_at_once && store && !direct ? P2_ROUTE_ROWS_LATER : 0);
+                      (wanted_direct && store && !direct ? P2_ROUTE_ROWS_LATER : 0);
             s.alphabet = r.plan.alphabet; s.engine = r.frontier || r.graph_frontier ? P2_ENGINE_FRONTIER : r.shared ? P2_ENGINE_SHARED : r.regs ? P2_ENGINE_SMALL : r.engine;
         }
     }

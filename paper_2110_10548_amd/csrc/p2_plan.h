@@ -20,6 +20,7 @@
 // ranks), and where a hierarchy has levels over non-reduction axes a copy is the whole system and a
 // device's goal is the set of local ids of its own reduction group.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -80,6 +81,15 @@ int32_t make_plan(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes, co
 void build_cost_tables(Plan& plan);
 // Whether these rows are the same for both plans (which may differ in links, chunks, axes and what is asked).
 bool same_cost_rows(const Plan& a, const Plan& b);
+// Rows that a call writes to pinned host memory before their number is known, when some `expected` may come out: never more
+// than the caller can take (a call with more has nowhere to put them), and none (the rows are counted first) where pinned
+// memory for them would pass kRowsAtOnceBytes.  Pinned pages are taken from the whole machine, kept until the thread gives
+// them back and slow to get (some 0.3 ms a megabyte the first time), and what counting first costs, a second wait, is lost in a call of that size.
+constexpr size_t kRowsAtOnceBytes = (size_t)64 << 20;
+inline size_t rows_at_once(size_t expected, int64_t cap, int n_msg) {
+    const size_t rows = cap <= 0 ? 0 : std::min(expected, (size_t)cap);
+    return rows <= kRowsAtOnceBytes / (sizeof(p2_program) + sizeof(double) * (size_t)std::max(n_msg, 1)) ? rows : 0;
+}
 // Group id / rank of every device of the full system for one canonical pattern.
 void describe_pattern(const Plan& plan, int pattern_id, int32_t* group_of_device, int32_t* rank_in_group);
 

@@ -1,7 +1,22 @@
 """The state graph that engine AUTO answers groups of up to 64 devices with power-of-two patterns from, beside the engines
 whose place it takes: the walk of every candidate (compact) and the enumeration by size (frontier)."""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2110_10548_amd", "csrc")
+
+
+def _compiled(tmp_path, code, *sources):
+    """What a host program over the library's host sources prints."""
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    (tmp_path / "main.cpp").write_text(code)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", CSRC, str(tmp_path / "main.cpp"), *(os.path.join(CSRC, s) for s in sources), "-o", str(tmp_path / "main")], check=True)
+    return subprocess.run([str(tmp_path / "main")], check=True, capture_output=True, text=True, timeout=60).stdout
 
 
 def _query(card, max_len, **more):
@@ -188,3 +203,50 @@ def test_stats_say_which_way_was_taken():
     q = _query([2, 2, 4, 4], 6, op_mask=1, topk=3)
     many = B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY)] * 900, MSG)        # (more lists than there is room for)
     assert {r["stats"]["route"] for r in many} == {B.ROUTE_GRAPH_LEFT}
+
+
+ROOM = r"""
+#include "p2_plan.h"
+#include <cstdio>
+int main() {
+    using p2::rows_at_once;
+    // 1 000 queries of four levels and six instructions, eleven sizes: 83.9 million rows at most
+    std::printf("%zu %zu %zu %zu %zu %zu %zu\n", rows_at_once(83920000, 262144, 11), rows_at_once(83920000, 1 << 30, 11), rows_at_once(83920, 1 << 17, 1),
+                rows_at_once(83920, 100, 64), rows_at_once(83920, 1 << 17, 64), rows_at_once(110, 0, 1), rows_at_once(110, 1 << 17, 0));
+}
+"""
+
+
+def test_room_for_rows_not_yet_counted(tmp_path):
+    """Pinned memory for rows whose number is not known: no more than the caller can take, and bounded."""
+    out = _compiled(tmp_path, ROOM).split()
+    assert out == ["262144", "0", "83920", "100", "83920", "0", "110"]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cap", [34, 35, 36, 86, 200])
+def test_rows_as_far_as_the_caller_has_room(cap):
+    """The caller's room below, at and above the rows that come out (35 of at most 110, then all of 86)."""
+    from paper_2110_10548_amd import binding as B
+    for q, n in ((_query([4, 4], 3), 35), (_query([4, 4], 4), 86)):
+        want = B.p2_synthesize_batch([q], MSG)[0]
+        assert len(want["programs"]) == n
+        if cap < n:
+            with pytest.raises(B.P2Error) as e:
+                B.p2_synthesize_batch([q], MSG, cap=cap)
+            assert e.value.code == B.P2_ENOSPC
+            continue
+        got = B.p2_synthesize_batch([q], MSG, cap=cap)[0]
+        assert np.array_equal(got["programs"], want["programs"]) and np.array_equal(got["cost"], want["cost"]) and got["stats"]["route"] == B.ROUTE_GRAPH
+
+
+@pytest.mark.gpu
+def test_more_rows_expected_than_are_pinned():
+    """Lists that would take more pinned memory than is taken beforehand are counted first: the same rows."""
+    from paper_2110_10548_amd import binding as B
+    q = _query([2, 2, 4, 4], 6, op_mask=0b00111)
+    sizes = [2.0 ** 20 * (i + 1) for i in range(64)]
+    many = B.p2_synthesize_batch([dict(q, bw=[b * (1 + 0.1 * i) for b in q["bw"]]) for i in range(3)], sizes, cap=3 * 83920)
+    for i, r in enumerate(many):
+        o = B.p2_synthesize_batch([dict(q, bw=[b * (1 + 0.1 * i) for b in q["bw"]])], sizes[::9])[0]
+        assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"][:, ::9], o["cost"]) and r["stats"]["route"] == B.ROUTE_GRAPH
