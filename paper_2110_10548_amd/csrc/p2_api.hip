@@ -36,6 +36,10 @@ struct DevBuf {
         if (e == hipSuccess) cap = want;
         return e;
     }
+    void release() {
+        if (p) (void)hipFree(p);
+        p = nullptr; cap = 0;
+    }
 };
 // grow a device buffer to `bytes`, keeping its first `keep` bytes
 hipError_t grow_keep(DevBuf& b, size_t bytes, size_t keep, hipStream_t stream) {
@@ -156,9 +160,8 @@ struct Ctx {
     bool topk_control_clear = false;                        // the words that the blocks of a selection share are zero
     DevBuf sel_progs, sel_costs, gather;                    // the rows that shortlists picked, and whose they are
     HostBuf h_gather;
-    DevBuf g_zero, g_mem, g_rows;                           // state-graph engine: what starts from zero, the lists, whose rows are written
+    DevBuf g_zero, g_mem, g_large, g_rows;                  // state-graph engine: what starts from zero, the lists, the states of large groups, whose rows are written
     HostBuf h_gctr, h_grows;
-    std::vector<DevBuf> g_large;                            // ... the states of every large group
     DevBuf f_finish;                                        // frontier engine: what every query's rows are written from
     HostBuf h_finish;
     DevBuf f_rank, f_rank_runs, f_share;                                 // frontier engine: ranks of the valid programs, queries of the enumerations
@@ -266,9 +269,9 @@ const std::thread::id g_loader_thread = std::this_thread::get_id();
 
 void Ctx::release() {
     DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_control, &topk_pos,
-                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink, &g_zero, &g_mem, &g_rows};
+                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink, &g_zero, &g_mem, &g_large, &g_rows};
     for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
-    for (auto* v : {&f_evalid, &f_egsums, &g_large}) {
+    for (auto* v : {&f_evalid, &f_egsums}) {
         for (DevBuf& b : *v) if (b.p) (void)hipFree(b.p);
         v->clear();
     }
@@ -406,8 +409,11 @@ size_t graph_rows_guess(const p2::Plan& pl) {
     return levels[n <= 1 ? 0 : n <= 4 ? 1 : n <= 9 ? 2 : n <= 16 ? 3 : n <= 25 ? 4 : 5][pl.max_len];
 }
 // Lists of the state-graph engine beyond this size are left to the other engines (a batch that asks for every query to be
-// evaluated by itself can have hundreds of large structures).
+// evaluated by itself can have hundreds of large structures), and so are lists that would take more than half of the device
+// memory that is free or held by them: their room is made for every state that there can be, the other engines' and the other
+// queries' lists come later and are made for what there is.
 constexpr size_t kGraphBytesMax = (size_t)32 << 30;
+bool graph_has_room(size_t needed, size_t held, size_t free_bytes) { return needed <= (held + free_bytes) / 2; }
 
 // What decides about validity is the same for both: group, chunks, patterns, alphabet and size limit.
 bool same_structure(const p2::Plan& a, const p2::Plan& b) {
@@ -995,7 +1001,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         struct Place { size_t table, table_node, planes, state, found, links, use_id, first, use_ends, edges, edge_state, best; };
         std::vector<Place> places(n_graphs);
         large_at.assign(n_graphs, LargeAt{});
-        if (C.g_large.size() < n_graphs) C.g_large.resize(n_graphs);
         size_t states_bytes = 0;
         for (size_t g = 0; g < n_graphs; ++g) {
             const Graph& G = graphs[g];
@@ -1044,7 +1049,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 L.literal_parent = (uint32_t*)at(take(mem, sizeof(uint32_t) * L.cap_literal));
                 L.rest = (uint32_t*)at(take(mem, sizeof(uint32_t) * L.cap_literal));
                 L.literal_scratch = at(take(mem, pl.max_len >= 6 ? front_literal_goals_scratch_bytes(pl.R, kk, L.cap_literal) : 256));
-                states_bytes += ((size_t)L.cap[0] + 2 * (size_t)L.cap[1]) * plane;
+                L.states[0] = (uint32_t*)at(take(states_bytes, (size_t)L.cap[0] * plane));
+                L.states[1] = (uint32_t*)at(take(states_bytes, 2 * (size_t)L.cap[1] * plane));
             }
             for (size_t p = 0; p < pl.patterns.size() && !G.large; ++p) {
                 const Pattern& pt = pl.patterns[p];
@@ -1069,15 +1075,17 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
             P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
         }
-        if (mem + zero + states_bytes > kGraphBytesMax) return leave_graphs();
-        bool room = C.g_zero.ensure(zero) == hipSuccess && C.g_mem.ensure(mem) == hipSuccess;
-        for (size_t g = 0; g < n_graphs && room; ++g) {
-            if (!graphs[g].large) continue;
-            const Plan& pl = runs[graphs[g].leader].plan;
-            room = C.g_large[g].ensure(((size_t)large_at[g].cap[0] + 2 * (size_t)large_at[g].cap[1]) * frontier_state_words(pl.R, graph_rows(pl)) * 4) == hipSuccess;
+        // (nothing of the call that uses these is on its way: this attempt has queued nothing, those before were waited for)
+        bool room = mem + zero + states_bytes <= kGraphBytesMax;
+        if (room && (zero > C.g_zero.cap || mem > C.g_mem.cap || states_bytes > C.g_large.cap)) {
+            size_t free_bytes = 0, all = 0;
+            P2_HIP(hipMemGetInfo(&free_bytes, &all));
+            room = graph_has_room(mem + zero + states_bytes, C.g_zero.cap + C.g_mem.cap + C.g_large.cap, free_bytes) && C.g_zero.ensure(zero) == hipSuccess &&
+                   C.g_mem.ensure(mem) == hipSuccess && C.g_large.ensure(states_bytes) == hipSuccess;
         }
-        if (!room) {                                     // (the other engines need less)
+        if (!room) {                                     // (the other engines need less, and get what the graphs had)
             (void)hipGetLastError();
+            C.g_zero.release(); C.g_mem.release(); C.g_large.release();
             return leave_graphs();
         }
         P2_HIP(C.h_gctr.ensure(graph_back + 16));
@@ -1100,11 +1108,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             LargeAt& L = large_at[g];
             auto shift = [](auto*& p, char* base) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + reinterpret_cast<size_t>(p)); };
             shift(L.ctr, z); shift(L.marks, m);
-            const Plan& pl = runs[graphs[g].leader].plan;
-            const size_t plane_words = frontier_state_words(pl.R, D.rows_kept);
-            L.states[0] = static_cast<uint32_t*>(C.g_large[g].p);
-            L.states[1] = L.states[0] + (size_t)L.cap[0] * plane_words;
             for (int li = 0; li < 2; ++li) {
+                shift(L.states[li], static_cast<char*>(C.g_large.p));
                 shift(L.table[li], z); shift(L.hash[li], m);
                 shift(L.rep[li], m); shift(L.pos[li], m); shift(L.reps[li], m); shift(L.walk[li], m);
                 shift(L.codes[li], m); shift(L.row_counts[li], m); shift(L.unknown[li], m);

@@ -250,3 +250,27 @@ def test_more_rows_expected_than_are_pinned():
     for i, r in enumerate(many):
         o = B.p2_synthesize_batch([dict(q, bw=[b * (1 + 0.1 * i) for b in q["bw"]])], sizes[::9])[0]
         assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"][:, ::9], o["cost"]) and r["stats"]["route"] == B.ROUTE_GRAPH
+
+
+@pytest.mark.gpu
+def test_little_device_memory():
+    """With most of the device taken by others, large groups go without their graphs, and what these had got is given back."""
+    import torch
+    from paper_2110_10548_amd import binding as B
+    queries = [_query(card, 6, op_mask=1) for card in ([2, 4, 8, 8], [2, 4, 4, 8], [4, 4, 4, 4], [2, 2, 8, 8])]
+    want = B.p2_synthesize_batch(queries, MSG)
+    assert {r["stats"]["route"] for r in want} == {B.ROUTE_GRAPH}
+    B.p2_release_thread()
+    torch.cuda.empty_cache()
+    others = torch.empty(torch.cuda.mem_get_info()[0] - (5 << 30), dtype=torch.uint8, device="cuda")
+    before = torch.cuda.mem_get_info()[0]
+    got = B.p2_synthesize_batch(queries, MSG)
+    held = before - torch.cuda.mem_get_info()[0]
+    del others
+    torch.cuda.empty_cache()
+    assert {r["stats"]["route"] for r in got} == {B.ROUTE_GRAPH_LEFT} and held < 1 << 30
+    again = B.p2_synthesize_batch(queries, MSG)
+    for w, g, a in zip(want, got, again):
+        assert np.array_equal(w["programs"], g["programs"]) and np.array_equal(w["cost"], g["cost"])
+        assert np.array_equal(w["programs"], a["programs"]) and a["stats"]["route"] == B.ROUTE_GRAPH
+    B.p2_release_thread()
