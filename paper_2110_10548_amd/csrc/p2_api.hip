@@ -348,8 +348,8 @@ bool pruned_is_faster(const p2::Plan& pl) {
 int graph_rows(const p2::Plan& pl) { return pl.k % pl.R == 0 ? pl.R : pl.k; }
 // What the state-graph engine takes over from the others under AUTO: groups of up to 64 devices with power-of-two
 // patterns (a lane plays a device), up to 64 rows (a 64-bit word holds a set of them).  The number of states depends on
-// the levels and the size limit, hardly on the sizes of the levels: at most 42 for two levels, 1 000 for three, 17 300 for
-// four with six instructions, 50 300 for five with five, 29 600 for six with four; past these the counts of a
+// the levels and the size limit, hardly on the sizes of the levels: at most 42 for two levels, 1 008 for three, 17 427 for
+// four with six instructions, 50 647 for five with five, 29 599 for six with four; past these the counts of a
 // graph no longer fit in a compute unit's LDS.
 bool graph_applies(const p2::Plan& pl) {
     if (pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.frontier_pairs != P2_FRONTIER_PAIRS_AUTO || pl.alphabet == 0) return false;
@@ -382,7 +382,7 @@ uint32_t graph_room(const p2::Plan& pl) {
                                                        {0, 64, 64, 256, 640, 1024, 1280, 1536},
                                                        {0, 64, 128, 768, 3072, 10240, 20480, 32768},
                                                        {0, 64, 256, 1536, 12288, 57344, 57344, 57344},
-                                                       {0, 64, 256, 3072, 16384, 16384, 16384, 16384}};
+                                                       {0, 64, 256, 3072, 32768, 32768, 32768, 32768}};
     const size_t n = pl.patterns.size();
     return levels[n <= 4 ? 0 : n <= 9 ? 1 : n <= 16 ? 2 : n <= 25 ? 3 : 4][pl.max_len];
 }
@@ -396,17 +396,6 @@ bool same_graph(const p2::Plan& a, const p2::Plan& b) {
         if (a.patterns[t].g != b.patterns[t].g || a.patterns[t].s != b.patterns[t].s || a.patterns[t].master != b.patterns[t].master)
             return false;
     return true;
-}
-// Valid programs to have room for before they are counted (more cost a second pass over the rows, nothing else).
-size_t graph_rows_guess(const p2::Plan& pl) {
-    static const uint32_t levels[6][P2_MAX_LEN + 1] = {{0, 3, 3, 3, 3, 3, 3, 3},
-                                                       {0, 1, 5, 35, 86, 110, 110, 110},
-                                                       {0, 7, 7, 80, 571, 2549, 6794, 16384},
-                                                       {0, 9, 9, 138, 1646, 16000, 83920, 83920},
-                                                       {0, 11, 11, 256, 4096, 45056, 45056, 45056},
-                                                       {0, 13, 13, 320, 4096, 4096, 4096, 4096}};
-    const size_t n = pl.patterns.size();
-    return levels[n <= 1 ? 0 : n <= 4 ? 1 : n <= 9 ? 2 : n <= 16 ? 3 : n <= 25 ? 4 : 5][pl.max_len];
 }
 // Lists of the state-graph engine beyond this size are left to the other engines (a batch that asks for every query to be
 // evaluated by itself can have hundreds of large structures), and so are lists that would take more than half of the device
@@ -638,7 +627,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     size_t rows_room = 0, emit_blocks = 0;
     if (only_graphs && !any_topk) {
         for (const QueryRun& r : runs)
-            if (r.graph) { rows_room += graph_rows_guess(r.plan); ++emit_blocks; }
+            if (r.graph) { rows_room += most_valid(r.plan); ++emit_blocks; }
         rows_room = rows_at_once(rows_room, cap, n_msg);
         emit_blocks += rows_room / 256;
     }

@@ -539,6 +539,19 @@ bool same_cost_rows(const Plan& a, const Plan& b) {
     return std::equal(a.h, a.h + a.n, b.h) && std::equal(a.f, a.f + a.n, b.f);
 }
 
+size_t most_valid(const Plan& pl) {
+    static const uint32_t by_levels[7][P2_MAX_LEN + 1] = {{0, 0, 0, 0, 0, 0, 0, 0},
+                                                          {0, 1, 3, 3, 3, 3, 3, 3},
+                                                          {0, 1, 5, 35, 86, 110, 110, 110},
+                                                          {0, 1, 7, 80, 571, 2549, 6794, 12580},
+                                                          {0, 1, 9, 138, 1646, 13810, 83920, 83920},
+                                                          {0, 1, 11, 209, 3520, 44182, 44182, 44182},
+                                                          {0, 1, 13, 293, 6423, 6423, 6423, 6423}};
+    int levels = 0;
+    for (int j = 0; j < pl.n; ++j) levels += pl.f[j] > 1 ? 1 : 0;
+    return by_levels[std::min(levels, 6)][pl.max_len];
+}
+
 void describe_pattern(const Plan& pl, int pattern_id, int32_t* group_of_device, int32_t* rank_in_group) {
     const Pattern& p = pl.patterns[pattern_id];
     std::vector<int32_t> local_of = pl.local_of, replica_of = pl.replica_of;

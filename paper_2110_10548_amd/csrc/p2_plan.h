@@ -81,6 +81,10 @@ int32_t make_plan(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes, co
 void build_cost_tables(Plan& plan);
 // Whether these rows are the same for both plans (which may differ in links, chunks, axes and what is asked).
 bool same_cost_rows(const Plan& a, const Plan& b);
+// Valid programs that a plan of the collapsed hierarchy can have: what its levels have with every collective and form, which
+// is the same for all level sizes and the most that any chunks leave.  (Past the size limits that were counted, which only a
+// plan with few forms gets to where this is asked, it is the last one counted, and may be less than there are.)
+size_t most_valid(const Plan& plan);
 // Rows that a call writes to pinned host memory before their number is known, when some `expected` may come out: never more
 // than the caller can take (a call with more has nowhere to put them), and none (the rows are counted first) where pinned
 // memory for them would pass kRowsAtOnceBytes.  Pinned pages are taken from the whole machine, kept until the thread gives

@@ -181,7 +181,8 @@ SIX, FIVE, FEW = _query([2] * 6, 4), _query([2] * 5, 4), _query([2, 4], 5, n_chu
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("queries", [[SIX] + [FEW] * 36, [FEW] * 36 + [SIX], [SIX] * 2 + [FIVE] * 9, [FEW] * 12 + [_query([64], 5)] + [SIX] + [FEW] * 30])
+@pytest.mark.parametrize("queries", [[SIX] + [FEW] * 36, [FEW] * 36 + [SIX], [SIX] * 2 + [FIVE] * 9, [FEW] * 12 + [_query([64], 5)] + [SIX] + [FEW] * 30,
+                                     [_query([2] * 6, 5, form_mask=2)] + [FEW] * 520])
 def test_rows_beyond_one_querys_room(queries):
     """One query has more valid programs than the call makes room for, the others fewer: in all they fit, and every row is there."""
     from paper_2110_10548_amd import binding as B
@@ -274,3 +275,53 @@ def test_little_device_memory():
         assert np.array_equal(w["programs"], g["programs"]) and np.array_equal(w["cost"], g["cost"])
         assert np.array_equal(w["programs"], a["programs"]) and a["stats"]["route"] == B.ROUTE_GRAPH
     B.p2_release_thread()
+
+
+MOST = r"""
+#include "p2_plan.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char** argv) {
+    using namespace p2;
+    for (int levels = 1; levels <= 6; ++levels)
+        for (int len = 1; len <= P2_MAX_LEN; ++len) {
+            std::vector<int32_t> card(levels, 2);
+            const int32_t axes[1] = {1 << levels}, reduce[1] = {0};
+            const p2_hierarchy h = {levels, card.data(), nullptr, nullptr};
+            Plan pl;
+            std::string err;
+            if (make_plan(&h, axes, 1, card.data(), reduce, 1, len, nullptr, false, pl, err) != P2_OK) return 1;
+            std::printf("%zu ", most_valid(pl));
+        }
+    return 0;
+}
+"""
+
+
+def test_expected_rows_are_what_the_oracle_counts(tmp_path, oracle):
+    most = np.array(list(map(int, _compiled(tmp_path, MOST, "p2_plan.cpp").split()))).reshape(6, 7)
+    for levels, upto in enumerate((7, 6, 5, 4, 4, 3), start=1):
+        o = oracle.Query([2] * levels, [2 ** levels], [[2] * levels], [0]).synthesize(upto)
+        for n in range(1, upto + 1):
+            assert most[levels - 1, n - 1] == int(np.count_nonzero(o["len"] <= n)), (levels, n)
+
+
+# levels, size limits and the states behind them: room for all at the first attempt, rows with the evaluation
+STATES = [([2, 32], 7, 42), ([2, 4, 8], 7, 1008), ([2, 2, 4, 4], 6, 17274), ([4, 2, 2, 2, 2], 5, 50567), ([2] * 6, 3, 2513), ([2] * 6, 4, 29586),
+          ([12, 12], 7, 42), ([3, 4, 6], 6, 938), ([2, 3, 2, 4], 6, 17427), ([2, 2, 2, 4, 4], 5, 50647), ([2, 2, 2, 2, 2, 3], 4, 29599)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,states", STATES)
+def test_room_for_every_state(card, max_len, states):
+    from paper_2110_10548_amd import binding as B
+    s = B.p2_synthesize_batch([_query(card, max_len)], MSG)[0]["stats"]
+    assert s["route"] == B.ROUTE_GRAPH and s["steps_evaluated"] == states * s["alphabet"]
+
+
+@pytest.mark.gpu
+def test_few_forms_have_no_more_rows():
+    """Patterns of one form are as few as those of fewer levels, their programs are not."""
+    from paper_2110_10548_amd import binding as B
+    for q in (_query([2] * 5, 4, form_mask=2), _query([2, 2, 2, 4, 4], 3, form_mask=3, n_chunks=256), _query([2, 2, 2, 2, 3], 5, form_mask=3, n_chunks=48)):
+        assert B.p2_synthesize_batch([q], MSG)[0]["stats"]["route"] == B.ROUTE_GRAPH
