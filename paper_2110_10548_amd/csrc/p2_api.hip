@@ -364,11 +364,15 @@ bool graph_applies(const p2::Plan& pl) {
 // the frontier's kernels, two pairs a device, which must fit in a compute unit's LDS.  The enumeration waits for the host
 // after every level and keeps every program's sums; the graph keeps neither (one query of [3 4 6] 537 us by enumeration,
 // 373 by the graph; [2 4 8 8], 512 devices, 6 814 and 5 025; 35 + 105 queries of [2 4 8 8] 39.5 ms and 20.1).  Past the
-// size limits the counts of a graph no longer fit in LDS: the enumeration goes on there.
+// size limits the counts of a graph no longer fit in LDS: the enumeration goes on there, and also for three levels and seven
+// instructions with AllGathers among them, which lead to states of three pairs before the last two levels, where the graph
+// would be given up ([3 4 6]: 1.24 ms enumerated, 1.80 with the graph tried first).
 bool large_graph_applies(const p2::Plan& pl) {
     if (pl.hierarchy != P2_HIERARCHY_COLLAPSED || pl.frontier_pairs != P2_FRONTIER_PAIRS_AUTO || pl.alphabet == 0 || pl.R < 2) return false;
     const size_t n_pat = pl.patterns.size();
-    if (n_pat > (size_t)p2::kGraphPatterns || pl.max_len > (n_pat <= 9 ? 7 : n_pat <= 16 ? 6 : n_pat <= 25 ? 5 : 4)) return false;
+    const bool gathers = std::find(pl.ops, pl.ops + pl.n_ops, (int)p2::OP_AG) != pl.ops + pl.n_ops;
+    const int nine = n_pat <= 4 || !gathers ? 7 : 6;
+    if (n_pat > (size_t)p2::kGraphPatterns || pl.max_len > (n_pat <= 9 ? nine : n_pat <= 16 ? 6 : n_pat <= 25 ? 5 : 4)) return false;
     return p2::frontier_max_pairs(pl.R, graph_rows(pl)) == 2;
 }
 // A call that walks some of its queries in any case has its state graphs' queries walked beside them, in the same launches,

@@ -325,3 +325,11 @@ def test_few_forms_have_no_more_rows():
     from paper_2110_10548_amd import binding as B
     for q in (_query([2] * 5, 4, form_mask=2), _query([2, 2, 2, 4, 4], 3, form_mask=3, n_chunks=256), _query([2, 2, 2, 2, 3], 5, form_mask=3, n_chunks=48)):
         assert B.p2_synthesize_batch([q], MSG)[0]["stats"]["route"] == B.ROUTE_GRAPH
+
+
+@pytest.mark.gpu
+def test_no_graph_is_begun_in_vain():
+    """Seven instructions of three levels are enumerated from the start, unless no AllGather can lead to a third pair."""
+    from paper_2110_10548_amd import binding as B
+    for card, more, route in (([3, 4, 6], {}, 0), ([2, 8, 8], dict(n_chunks=256), 0), ([3, 4, 6], dict(op_mask=0b11011), B.ROUTE_GRAPH), ([6, 12], {}, B.ROUTE_GRAPH)):
+        assert B.p2_synthesize_batch([_query(card, 7, **more)], MSG)[0]["stats"]["route"] == route
