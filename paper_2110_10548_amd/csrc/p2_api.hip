@@ -637,10 +637,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     }
     bool direct = rows_room > 0;
     const bool wanted_direct = direct;
-    auto leave_graphs = [&]() -> int32_t {
-        for (int i = 0; i < n_queries; ++i) left[i] |= runs[i].graph ? 1 : 0;
-        return kWithoutGraphs;
-    };
+    auto leave_graph = [&](const Graph& G) { for (int32_t i : G.members) left[i] = 1; };
     // Validity depends on the reduction group, the chunks, the patterns and the alphabet only (not on the
     // links, nor on where the placement puts the group in the system): a query that equals an earlier one of
     // the batch in these is not evaluated again; it takes over the list of valid programs and the counts, and
@@ -1079,7 +1076,10 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (!room) {                                     // (the other engines need less, and get what the graphs had)
             (void)hipGetLastError();
             C.g_zero.release(); C.g_mem.release(); C.g_large.release();
-            return leave_graphs();
+            bool any_large = false;                      // (they take the most: without them the others may well have room)
+            for (const Graph& G : graphs) any_large |= G.large;
+            for (const Graph& G : graphs) if (G.large || !any_large) leave_graph(G);
+            return kWithoutGraphs;
         }
         P2_HIP(C.h_gctr.ensure(graph_back + 16));
         graph_zero = zero;
@@ -1419,11 +1419,17 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         P2_HIP(hipStreamSynchronize(stream));
         bool again = false;
         const GraphCounters* const hg = static_cast<const GraphCounters*>(C.h_gctr.p);
+        // (a graph that failed costs its own queries their place, not the others': they stay with theirs when the call is repeated)
+        bool failed = false;
         for (size_t g = 0; g < graphs.size(); ++g) {
-            if ((hg[g].flags & ~kGraphFull) != 0u || (hg[g].flags != 0u && attempt == 3)) return leave_graphs();
-            if (hg[g].flags == 0u) continue;
-            again = true;
+            unsigned long long valid = 0;
+            for (int len = 1; len <= P2_MAX_LEN; ++len) valid += hg[g].n_valid[len];
+            if ((hg[g].flags & ~kGraphFull) != 0u || (hg[g].flags != 0u && attempt == 3) || valid > 0xffffffffull) {
+                leave_graph(graphs[g]);
+                failed = true;
+            } else again |= hg[g].flags != 0u;
         }
+        if (failed) return kWithoutGraphs;
         if (again) graph_scale *= 4;
         const DevCounters* hc = static_cast<const DevCounters*>(C.h_counters.p);
         // candidates whose state the compact engine could not hold go through the literal engine:
@@ -1472,7 +1478,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                     listed += prefixes;
                 }
                 for (int len = 1; len <= pl.max_len; ++len) valid += gc.n_valid[len];
-                if (valid > 0xffffffffull) return leave_graphs();
                 r.n_valid = (uint32_t)valid; r.n_rerun = r.n_rerun_groups = 0;
                 const unsigned long long applied = r.graph_frontier && !r.graph_flat ? listed : walked;
                 r.steps = applied * (unsigned long long)pl.alphabet; r.members = applied * per_alphabet;
