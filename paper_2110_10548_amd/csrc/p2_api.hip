@@ -826,9 +826,13 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // hierarchy follow from the factors; worked out for every query, from the devices under every unit, the rows were most of
     // a batch's host time (140 queries of [4 8 8]: 1 000 us of the call's 1 590 with eight threads, the call takes 540 now;
     // 512 queries of [2 4 8 8], 96 distinct sets: 5 600 us, and 400 now without a thread).
+    // (The rows of the other hierarchies are every query's own and built from its devices; host threads share them, as many as
+    //  before: 2 000 queries of eight devices take 17.5 ms so, and 20.3 in one thread.)
     std::vector<int32_t> row_sets;                       // a query of each
+    size_t n_built_sets = 0;                             // ... of another hierarchy
     for (int i = 0; i < n_queries; ++i) {
         size_t t = 0;
+        if (runs[i].plan.hierarchy != P2_HIERARCHY_COLLAPSED) { t = row_sets.size(); ++n_built_sets; }
         while (t < row_sets.size() && !same_cost_rows(runs[row_sets[t]].plan, runs[i].plan)) ++t;
         if (t == row_sets.size()) row_sets.push_back(i);
         runs[i].rows_at = (int)t;
@@ -860,9 +864,20 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     auto build_and_upload_rows = [&]() -> int32_t {
         if (rows_ready) return P2_OK;
         size_t bytes = 0;
+        const unsigned hw = std::thread::hardware_concurrency();
+        const int n_threads = n_built_sets >= 256 ? (int)std::min<unsigned>(std::max(hw, 1u), 16u) : n_built_sets >= 32 ? (int)std::min<unsigned>(std::max(hw, 1u), 8u) : 1;
+        auto for_every_set = [&](const auto& f) {
+            if (n_threads <= 1) { for (int32_t i : row_sets) f(i); return; }
+            std::atomic<size_t> next{0};
+            auto work = [&]() { for (size_t t = next.fetch_add(1); t < row_sets.size(); t = next.fetch_add(1)) f(row_sets[t]); };
+            std::vector<std::thread> pool;
+            for (int t = 1; t < n_threads; ++t) pool.emplace_back(work);
+            work();
+            for (auto& th : pool) th.join();
+        };
+        if (n_msg > 0) for_every_set([&](int32_t i) { build_cost_tables(runs[i].plan); });      // without message sizes the tables stay empty
         for (int32_t i : row_sets) {
             QueryRun& r = runs[i];
-            if (n_msg > 0) build_cost_tables(r.plan);    // without message sizes the tables stay empty
             size_t n_rows = 0, n_ent = 0;
             for (const Pattern& p : r.plan.patterns) { n_rows += p.row_level.size(); n_ent += p.entries.size(); }
             r.off_rowptr = bytes; bytes += align_up(sizeof(int32_t) * (n_rows + 1), 16);
@@ -874,7 +889,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         char* hr = static_cast<char*>(C.h_rows.p);
         char* dr = static_cast<char*>(C.rows.p);
         DevRows* hdr = static_cast<DevRows*>(C.h_rows_hdr.p);
-        for (int32_t i : row_sets) {
+        for_every_set([&](int32_t i) {
             const QueryRun& r = runs[i];
             const Plan& pl = r.plan;
             int32_t* rp = reinterpret_cast<int32_t*>(hr + r.off_rowptr);
@@ -899,7 +914,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             H.row_ptr = reinterpret_cast<const int32_t*>(dr + r.off_rowptr);
             H.row_level = reinterpret_cast<const int32_t*>(dr + r.off_rowlevel);
             H.entries = reinterpret_cast<const uint32_t*>(dr + r.off_entries);
-        }
+        });
         rows_ready = true;
         if (only_graphs && large_slots == 1) {           // (else the call's stream has the slots to wait for)
             const CopyPart up[2] = {{C.rows.p, C.h_rows.p, bytes}, {C.rows_hdr.p, C.h_rows_hdr.p, sizeof(DevRows) * row_sets.size()}};

@@ -333,3 +333,18 @@ def test_no_graph_is_begun_in_vain():
     from paper_2110_10548_amd import binding as B
     for card, more, route in (([3, 4, 6], {}, 0), ([2, 8, 8], dict(n_chunks=256), 0), ([3, 4, 6], dict(op_mask=0b11011), B.ROUTE_GRAPH), ([6, 12], {}, B.ROUTE_GRAPH)):
         assert B.p2_synthesize_batch([_query(card, 7, **more)], MSG)[0]["stats"]["route"] == route
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [40, 300])
+def test_rows_of_other_hierarchies_built_by_several_threads(n):
+    """Batches whose queries each have bandwidth rows of their own beside some that share theirs."""
+    from paper_2110_10548_amd import binding as B
+    queries = []
+    for i in range(n):
+        q = _query([2, 2, 2], 1 + i % 2, axes=[2, 4], placement=[[2, 1, 1], [1, 2, 2]] if i % 3 else [[1, 2, 1], [2, 1, 2]], reduce_axes=[i % 2], hierarchy=(0, 1, 2, 3, 4)[i % 5])
+        queries.append(dict(q, bw=[b * (1 + 0.001 * i) for b in q["bw"]]))
+    together = B.p2_synthesize_batch(queries, MSG)
+    for i in range(0, n, 7):
+        o = B.p2_synthesize_batch([queries[i]], MSG)[0]
+        assert np.array_equal(together[i]["programs"], o["programs"]) and np.array_equal(together[i]["cost"], o["cost"]) and len(o["programs"]) > 0
