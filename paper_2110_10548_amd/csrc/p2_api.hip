@@ -376,10 +376,15 @@ bool large_graph_applies(const p2::Plan& pl) {
     return p2::frontier_max_pairs(pl.R, graph_rows(pl)) == 2;
 }
 // A call that walks some of its queries in any case has its state graphs' queries walked beside them, in the same launches,
-// if none has more candidates than this: the graphs' chain of launches would come on top (search of 6 x 16 devices, axes 32 x
-// 3, three instructions, 8 420 candidates beside 20: 168 us all walked, 186 with a graph; 3 x 16, axes 4 x 12: 423 and 446;
-// four instructions, 168 420 candidates, 6 x 16: 716 and 546).
-constexpr unsigned long long kWalkedBesideMax = 1ull << 14;
+// if none has more candidates (times devices: a walk's cost) or patterns than this: the graphs' chain of launches would come
+// on top.  Beside [3], three instructions, walked with it and with a graph: [4 4], four (2.7 million) 112 us and 126; ten
+// groups of two and three levels, three (up to 0.8 million), 137 and 157; [2 4 4], three (3 million) 124 and 126; but [4 4 4], three (6
+// million) 135 and 128, [2 2], five (14 million) 143 and 121, and with 16 patterns, two instructions, 167 and 119, with 25 216 and 120.
+constexpr unsigned long long kWalkedBesideMax = 1ull << 22;
+constexpr size_t kWalkedBesidePatterns = 9;
+bool walks_beside(const p2::Plan& pl) {
+    return pl.n_candidates <= kWalkedBesideMax / (unsigned long long)pl.R && pl.patterns.size() <= kWalkedBesidePatterns;
+}
 // Room for the states of a structure (see above), first guess; a structure that has more is met with four times as much.
 uint32_t graph_room(const p2::Plan& pl) {
     static const uint32_t levels[5][P2_MAX_LEN + 1] = {{0, 96, 96, 96, 96, 96, 96, 96},
@@ -601,7 +606,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         bool walks = false, few = true;
         for (const QueryRun& r : runs) {
             walks |= !r.graph && !r.frontier && r.plan.n_candidates != 0;
-            few &= !r.graph || (!r.graph_large && !r.graph_frontier && r.plan.n_candidates <= kWalkedBesideMax);
+            few &= !r.graph || (!r.graph_large && !r.graph_frontier && walks_beside(r.plan));
         }
         if (walks && few)
             for (QueryRun& r : runs) r.graph = false;

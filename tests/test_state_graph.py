@@ -168,8 +168,11 @@ def test_small_spaces_beside_walked_queries():
     """Spaces just within and beyond what is walked beside a query that no graph answers: the same rows as alone."""
     from paper_2110_10548_amd import binding as B
     odd = _query([3], 3)
-    for small in ([_query([2, 16], 3)], [_query([4, 8], 4)], [_query([2, 16], 3), _query([4, 8], 4), _query([4], 2, topk=2)]):
+    graph = B.ROUTE_GRAPH
+    for small, routes in (([_query([2, 16], 3)], [0]), ([_query([4, 4], 4)], [0]), ([_query([4, 8], 4)], [graph]), ([_query([2, 2, 4, 4], 2)], [graph]),
+                          ([_query([2, 16], 3), _query([4, 8], 4), _query([4], 2, topk=2)], [graph] * 3), ([_query([2, 16], 3), _query([4, 4], 4), _query([4], 2, topk=2)], [0] * 3)):
         together = B.p2_synthesize_batch([odd] + small, MSG)
+        assert [r["stats"]["route"] for r in together] == [0] + routes
         for q, r in zip([odd] + small, together):
             o = B.p2_synthesize_batch([q], MSG)[0]
             assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"]) and len(o["programs"]) > 0
