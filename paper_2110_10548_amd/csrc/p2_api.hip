@@ -448,6 +448,31 @@ bool walks_together(const std::vector<const p2::Plan*>& plans) {
     return walk + 2.5 * devices < pruned;
 }
 
+// A call that enumerates some of its structures in any case (E: past the graphs' size limits, or asked for) may do better to
+// enumerate the large groups beside them (L) than to build their graphs first, since the enumerations run kFrontSlots side by
+// side and wait for the graphs.  What an enumeration takes by itself, us, within some 40 % for groups from 36 to 512 devices:
+// its levels' waits and what its states add; a graph takes 0.55 of that; side by side the enumerations take the longest or
+// 1 / 3.6 of their sum, the graphs 1 / 2.4.  Both ways measured: [3 4 6], seven instructions (E), and three groups of 72 to 128
+// devices, four: 1 328 us enumerated, 1 660 with graphs; [3 4 6], four (E), and eight groups: 1 315 and 1 517; [100], three (E), and
+// five groups: 765 and 938, and 13: 1 845 and 1 848; and [2 4 8 8], five: 2 864 and 1 760.
+double enumerated_us(const p2::Plan& pl) {
+    int levels = 0;
+    for (int j = 0; j < pl.n; ++j) levels += pl.f[j] > 1 ? 1 : 0;
+    return 115.0 * std::min(pl.max_len, 2 * levels) + 0.62e-3 * (double)graph_room(pl) * pl.R;
+}
+bool enumerates_beside(const std::vector<const p2::Plan*>& enumerated, const std::vector<const p2::Plan*>& graphs) {
+    if (enumerated.empty() || graphs.empty()) return false;
+    double longest[2] = {0.0, 0.0}, sum[2] = {0.0, 0.0};
+    for (int which = 0; which < 2; ++which)
+        for (const p2::Plan* pl : which == 0 ? enumerated : graphs) {
+            const double t = enumerated_us(*pl);
+            longest[which] = std::max(longest[which], t);
+            sum[which] += t;
+        }
+    const double after = 0.55 * std::max(longest[1], sum[1] / 2.4) + std::max(longest[0], sum[0] / 3.6);
+    return std::max({longest[0], longest[1], (sum[0] + sum[1]) / 3.6}) < 0.97 * after;
+}
+
 struct QueryRun {
     p2::Plan plan;
     int engine = P2_ENGINE_LITERAL;       // engine evaluating the bulk (LITERAL or COMPACT)
@@ -602,6 +627,19 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     }
 
     take_large_graphs();
+    {
+        std::vector<const Plan*> enumerated, large;      // one of each structure
+        for (const QueryRun& r : runs) {
+            if (!(r.frontier || r.graph_large) || r.plan.n_candidates == 0) continue;
+            std::vector<const Plan*>& list = r.frontier ? enumerated : large;
+            bool seen = false;
+            for (size_t t = 0; t < list.size() && !seen && share_validity; ++t) seen = same_structure(*list[t], r.plan);
+            if (!seen) list.push_back(&r.plan);
+        }
+        if (enumerates_beside(enumerated, large))
+            for (QueryRun& r : runs)
+                if (r.graph_large) { r.frontier = true; r.flat_counts = r.graph_flat; r.graph = r.graph_large = r.graph_frontier = r.graph_flat = false; }
+    }
     {
         bool walks = false, few = true;
         for (const QueryRun& r : runs) {

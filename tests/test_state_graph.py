@@ -351,3 +351,19 @@ def test_rows_of_other_hierarchies_built_by_several_threads(n):
     for i in range(0, n, 7):
         o = B.p2_synthesize_batch([queries[i]], MSG)[0]
         assert np.array_equal(together[i]["programs"], o["programs"]) and np.array_equal(together[i]["cost"], o["cost"]) and len(o["programs"]) > 0
+
+
+@pytest.mark.gpu
+def test_large_groups_beside_enumerations():
+    """Groups enumerated beside others that are in any case, or from graphs after them where that is less: as each by itself."""
+    from paper_2110_10548_amd import binding as B
+    seven = _query([3, 4, 6], 7)
+    few, many = [_query([2, 8, 8], 4), _query([9, 8], 4, topk=6)], [_query([2, 4, 8, 8], 5, topk=3)]
+    for queries, routes in (([seven] + few, [0] * 3), (few + [_query([3, 5, 7], 4, engine=3)], [0] * 3), ([seven] + many, [0, B.ROUTE_GRAPH])):
+        together = B.p2_synthesize_batch(queries, MSG)
+        assert [r["stats"]["route"] for r in together] == routes
+        for q, r in zip(queries, together):
+            o = B.p2_synthesize_batch([q], MSG)[0]
+            assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"]) and len(o["programs"]) > 0
+            for key in COUNTS:
+                assert r["stats"][key] == o["stats"][key], key
