@@ -4,6 +4,7 @@
 #include <chrono>
 #include <cstddef>
 #include <cstring>
+#include <exception>
 #include <atomic>
 #include <thread>
 #include <limits>
@@ -295,24 +296,32 @@ int32_t fail(int32_t code, const std::string& msg) {
     g_err = msg;
     return code;
 }
-// Stream of the call in progress on this thread.  When a HIP call fails, what the call has queued so far
-// (kernels and copies that use the cached pinned and device buffers) is waited for before the error goes
-// back to the caller, so that the next call does not reuse buffers that are still in flight.
+// Stream of the call in progress on this thread.  When a HIP call fails or the host throws, what the call has
+// queued so far on this stream, the uploads' and the slots' (kernels and copies that use the cached pinned and
+// device buffers) is waited for before the error goes back to the caller, so that the next call does not reuse
+// buffers that are still in flight.
 thread_local hipStream_t g_call_stream = nullptr;
 thread_local bool g_call_active = false;
+void wait_for_call() {
+    if (!g_call_active) return;
+    (void)hipStreamSynchronize(g_call_stream);
+    if (g_ctx.copy_stream) (void)hipStreamSynchronize(g_ctx.copy_stream);
+    for (const FrontSlot& sl : g_ctx.slots) if (sl.stream) (void)hipStreamSynchronize(sl.stream);
+    (void)hipGetLastError();
+}
 int32_t hip_fail(hipError_t e, const char* what) {
     g_err = std::string(what) + ": " + hipGetErrorString(e);
     (void)hipGetLastError();
-    if (g_call_active) {
-        (void)hipStreamSynchronize(g_call_stream);
-        if (g_ctx.copy_stream) (void)hipStreamSynchronize(g_ctx.copy_stream);
-        (void)hipGetLastError();
-    }
+    wait_for_call();
     return P2_EDEVICE;
 }
 struct CallScope {
+    int thrown = std::uncaught_exceptions();
     explicit CallScope(hipStream_t s) { g_call_stream = s; g_call_active = true; }
-    ~CallScope() { g_call_active = false; g_call_stream = nullptr; }
+    ~CallScope() {
+        if (std::uncaught_exceptions() > thrown) wait_for_call();
+        g_call_active = false; g_call_stream = nullptr;
+    }
 };
 #define P2_HIP(call)                                      \
     do {                                                  \
@@ -1387,17 +1396,12 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 for (size_t t = 0; t < n_slots_used; ++t) P2_HIP(hipStreamWaitEvent(C.slots[t].stream, C.front_go, 0));
             }
             double load[kFrontSlots] = {};
-            int32_t rc = P2_OK;
             for (size_t g : order) {
                 size_t t = 0;
                 for (size_t u = 1; u < n_slots_used; ++u) if (load[u] < load[t]) t = u;
                 load[t] += weight(g);
-                rc = queue_large(g, n_slots_used > 0 ? C.slots[t].stream : stream, C.slots[t].spans);
-                if (rc != P2_OK) break;
-            }
-            if (rc != P2_OK) {                           // (what the slots have queued uses this thread's buffers)
-                for (size_t t = 0; t < n_slots_used; ++t) (void)hipStreamSynchronize(C.slots[t].stream);
-                return rc;
+                const int32_t rc = queue_large(g, n_slots_used > 0 ? C.slots[t].stream : stream, C.slots[t].spans);
+                if (rc != P2_OK) return rc;
             }
         }
         if (!glevel.empty()) {
