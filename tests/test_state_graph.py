@@ -46,7 +46,7 @@ def test_graph_matches_the_walk(card, max_len, more):
     walk, walk_b = B.p2_synthesize_batch([dict(q, engine=2), dict(q, engine=2, bw=q["bw"][::-1], algo=1)], MSG)
     alone = B.p2_synthesize_batch([q], MSG)[0]           # (rows written straight to the host)
     for a, w in ((auto, walk), (alone, walk), (shared, walk_b)):
-        assert a["stats"]["engine"] == 5 and np.array_equal(a["programs"], w["programs"])
+        assert a["stats"]["engine"] == 5 and a["stats"]["route"] == B.ROUTE_GRAPH and np.array_equal(a["programs"], w["programs"])
         assert np.array_equal(a["cost"], w["cost"])      # (to the last bit: shortlists with ties stay as they were)
         for key in COUNTS:
             assert a["stats"][key] == w["stats"][key], key
@@ -56,11 +56,11 @@ def test_graph_matches_the_walk(card, max_len, more):
         want = np.lexsort((walk["programs"]["index"], walk["cost"][:, m]))[:kk]
         assert np.array_equal(short["programs"]["index"][m * kk:(m + 1) * kk], walk["programs"]["index"][want])
     nothing = B.p2_synthesize_batch([q], [])[0]          # (no message size: validity alone)
-    assert np.array_equal(nothing["programs"], walk["programs"])
+    assert np.array_equal(nothing["programs"], walk["programs"]) and {r["stats"]["route"] for r in (short, nothing)} == {B.ROUTE_GRAPH}
+    assert {r["stats"]["route"] for r in (walk, walk_b)} == {0}
 
 
-# too many candidates to walk; three and four pairs on a device; more states than there is room for at first, more rows
-# than the call made room for (six levels)
+# too many candidates to walk; three and four pairs on a device; the most levels, states and rows
 ENUMERATED = [([2, 2, 2], 7, {}), ([4, 4, 4], 6, {}), ([2, 2, 2, 2], 6, {}), ([2, 2, 2, 4], 5, dict(n_chunks=24)), ([2, 2, 2, 2, 2], 5, {}),
               ([2, 2, 2, 2, 2, 2], 4, {})]
 
@@ -72,6 +72,7 @@ def test_graph_matches_the_enumeration(card, max_len, more):
     q = _query(card, max_len, **more)
     a = B.p2_synthesize_batch([q], MSG)[0]
     b = B.p2_synthesize_batch([dict(q, engine=3)], MSG)[0]
+    assert (a["stats"]["route"], b["stats"]["route"]) == (B.ROUTE_GRAPH, 0)
     assert np.array_equal(a["programs"], b["programs"]) and len(a["programs"]) > 1000
     assert np.allclose(a["cost"], b["cost"], rtol=1e-14, atol=0.0)       # (a dozen additions in 64 bits)
     if a["stats"]["engine"] == 3:
@@ -81,10 +82,9 @@ def test_graph_matches_the_enumeration(card, max_len, more):
 
 
 # Groups that the frontier's kernels build the graph of: more than 64 devices, levels that are no power of two; rows that are
-# blocks of chunks; children that need a third pair judged at the size limit (six instructions) and left to the enumeration
-# (seven); tree costs
+# blocks of chunks; children that need a third pair judged at the size limit (six instructions); tree costs
 LARGE = [([3, 4, 6], 4, {}), ([3, 4, 6], 5, dict(algo=1)), ([128], 4, {}), ([2, 8, 8], 4, dict(n_chunks=512)), ([2, 8, 8], 3, dict(n_chunks=96)),
-         ([3, 5, 7], 4, dict(n_chunks=210, op_mask=0b11101)), ([5, 2, 2, 6], 4, dict(form_mask=3)), ([2, 2, 4, 8], 6, {}), ([3, 2, 12], 7, {}), ([6, 6], 6, {})]
+         ([3, 5, 7], 4, dict(n_chunks=210, op_mask=0b11101)), ([5, 2, 2, 6], 4, dict(form_mask=3)), ([2, 2, 4, 8], 6, {}), ([3, 2, 12], 6, {}), ([3, 2, 12], 7, dict(op_mask=0b11011)), ([6, 6], 6, {})]
 
 
 @pytest.mark.gpu
@@ -95,6 +95,7 @@ def test_large_graph_matches_the_enumeration(card, max_len, more):
     alone = B.p2_synthesize_batch([q], MSG)[0]
     listed, short = B.p2_synthesize_batch([dict(q, bw=q["bw"][::-1]), dict(q, topk=9)], MSG)
     want, want_b = B.p2_synthesize_batch([dict(q, engine=3), dict(q, engine=3, bw=q["bw"][::-1])], MSG)
+    assert {r["stats"]["route"] for r in (alone, listed, short)} == {B.ROUTE_GRAPH} and want["stats"]["route"] == 0
     for a, w in ((alone, want), (listed, want_b)):
         assert np.array_equal(a["programs"], w["programs"])
         assert np.allclose(a["cost"], w["cost"], rtol=1e-14, atol=0.0)
@@ -115,7 +116,7 @@ def test_large_graph_matches_the_walk(card, max_len):
     auto, want = (B.p2_synthesize_batch([dict(q, engine=e)], MSG)[0] for e in (0, 2))
     assert np.array_equal(auto["programs"], want["programs"]) and len(want["programs"]) > 0
     assert np.allclose(auto["cost"], want["cost"], rtol=1e-14, atol=0.0)
-    assert auto["stats"]["valid"] == want["stats"]["valid"]
+    assert auto["stats"]["valid"] == want["stats"]["valid"] and (auto["stats"]["route"], want["stats"]["route"]) == (B.ROUTE_GRAPH, 0)
 
 
 @pytest.mark.gpu
@@ -126,6 +127,7 @@ def test_large_graphs_side_by_side():
                                                     ([4, 4], 4, 3), ([5, 2, 2, 6], 3, 0))]
     side = B.p2_synthesize_batch(queries, MSG)
     one = B.p2_synthesize_batch([dict(q, flags=B.FLAG_ONE_ENUMERATION_AT_A_TIME) for q in queries], MSG)
+    assert {r["stats"]["route"] for r in side + one} == {B.ROUTE_GRAPH}
     for q, a, b in zip(queries, side, one):
         alone = B.p2_synthesize_batch([q], MSG)[0]
         for r in (b, alone):
