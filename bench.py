@@ -293,7 +293,9 @@ def main():
                 "algorithmic_hbm_bytes_per_launch": run["front_materialize_bytes"] / n_mat,
                 "children_per_step": run["front_survivors"] / steps}
         else:
-            kernel = KERNEL[main_engine]
+            # (AUTO answers most of these from a state graph, reported as the engine that it stands in for)
+            graph = all(r["stats"]["route"] & B.ROUTE_GRAPH for r in own if r["stats"]["engine"] == main_engine)
+            kernel = "k_graph_alone / k_graph_level / k_graph_finish" if graph else KERNEL[main_engine]
             ops_launch, launch_ms, achieved = flat_summary(run, "members_evaluated")
             flat_ops_launch, _, flat_rate = flat_summary(run, "member_visits")
             out["steps_executed_per_step"] = sum(r["stats"]["steps_executed"] for r in own)

@@ -67,15 +67,20 @@ typedef struct {
 int32_t p2_enumerate_placements(const p2_hierarchy* h, const int32_t* axes, int32_t n_axes,
                                 int32_t* out, int64_t cap, int64_t* out_count);
 
-/* Evaluation engines.  All give identical results; they differ in the state they keep. */
+/* Evaluation engines.  All give the same programs and counts; they differ in the state they keep.  Costs of
+ * different engines may differ in the last bits (the same terms added up in another order or with other
+ * roundings between); those of AUTO do not depend on the way that it takes nor on a batch's other queries. */
 #define P2_ENGINE_AUTO 0      /* where the shared-prefix engine applies and the chunks are a multiple of
                                  the group's devices, or at most 64, the graph of the distinct states
                                  that the programs pass through (up to 36 patterns, size limits of 7, 6,
-                                 5, 4 for up to 9, 16, 25, 36; not for up to 2^14 candidates beside
-                                 queries that are walked); and the same graph in place of the
-                                 frontier engine, within these size limits, where two pairs a device
-                                 fit in LDS.  Reported as the engine it stands in for: shared-prefix
-                                 up to 2^30 candidates, frontier above.  Else the
+                                 5, 4 for up to 9, 16, 25, 36; not beside queries that are walked
+                                 where it would not save anything); and the same graph in place of
+                                 the frontier engine, within these size limits (6 for five to nine
+                                 patterns with AllGather), where two pairs a device fit in LDS (not
+                                 beside enumerations that take place in any case where enumerating
+                                 all is faster), if there is device memory for it.  Reported as the
+                                 engine it stands in for: shared-prefix up to 2^30 candidates,
+                                 frontier above; p2_stats.route tells.  Else the
                                  shared-prefix engine where it applies, else the compact engine; the
                                  literal engine for the candidates they cannot hold; the frontier
                                  engine above 2^30 candidates, and in place of the compact engine
@@ -195,7 +200,9 @@ typedef struct {
                                   although nothing was evaluated for it                           */
     uint64_t steps_executed;   /* instructions applied, counted per candidate (a candidate stops at
                                   its first bad step): what evaluating every candidate on its own
-                                  executes, whichever engine ran                                  */
+                                  executes, whichever engine ran; where a space is pruned instead of
+                                  walked, the alphabet once per valid prefix (the enumeration adds what
+                                  it applies again to rebuild a prefix, a state graph does not)   */
     uint64_t literal_reruns;   /* candidates the compact engine handed to the literal engine; frontier
                                   engine: prefixes judged outside the pair form (none under AUTO where a
                                   state graph stands in for it), plus, where the

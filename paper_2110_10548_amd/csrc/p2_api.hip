@@ -371,8 +371,8 @@ bool graph_applies(const p2::Plan& pl) {
 }
 // What it takes over from the frontier engine under AUTO: the same size limits, any patterns; the states are worked on by
 // the frontier's kernels, two pairs a device, which must fit in a compute unit's LDS.  The enumeration waits for the host
-// after every level and keeps every program's sums; the graph keeps neither (one query of [3 4 6] 537 us by enumeration,
-// 373 by the graph; [2 4 8 8], 512 devices, 6 814 and 5 025; 35 + 105 queries of [2 4 8 8] 39.5 ms and 20.1).  Past the
+// after every level and keeps every program's sums; the graph keeps neither (one query of [3 4 6] 527 us by enumeration,
+// 352 by the graph; [2 4 8 8], 512 devices, 6 300 and 3 230; 512 queries of [2 4 8 8] 39.7 ms and 15.5).  Past the
 // size limits the counts of a graph no longer fit in LDS: the enumeration goes on there, and also for three levels and seven
 // instructions with AllGathers among them, which lead to states of three pairs before the last two levels, where the graph
 // would be given up ([3 4 6]: 1.24 ms enumerated, 1.80 with the graph tried first).
@@ -876,7 +876,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // queued and uploaded on a second stream, so both overlap with the evaluation; the call's stream waits
     // for the upload before its first cost kernel.  Queries whose rows are the same share them, and those of the collapsed
     // hierarchy follow from the factors; worked out for every query, from the devices under every unit, the rows were most of
-    // a batch's host time (140 queries of [4 8 8]: 1 000 us of the call's 1 590 with eight threads, the call takes 540 now;
+    // a batch's host time (140 queries of [4 8 8]: 1 000 us of a call's 1 590 with eight threads, and 540 for the call so;
     // 512 queries of [2 4 8 8], 96 distinct sets: 5 600 us, and 400 now without a thread).
     // (The rows of the other hierarchies are every query's own and built from its devices; host threads share them, as many as
     //  before: 2 000 queries of eight devices take 17.5 ms so, and 20.3 in one thread.)
@@ -1387,7 +1387,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             for (FrontSlot& S : C.slots) { S.spans.on = g_prof.on; S.spans.kernels_only = g_prof.kernels_only; S.spans.reset(); }
             std::vector<size_t> order;
             for (size_t g = 0; g < graphs.size(); ++g) if (graphs[g].large) order.push_back(g);
-            // (512 devices, four levels: 4.1 ms alone; 256: 2.1; 128: 1.3: a chain of launches, and what the devices add)
+            // (512 devices, four levels, six instructions: 3.3 ms alone; 256: 2.0; 128: 1.5: a chain of launches, and what the devices add)
             auto weight = [&](size_t g) { const Plan& pl = runs[graphs[g].leader].plan; return (96.0 + pl.R) * (1024.0 + graph_room(pl)); };
             std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return weight(x) > weight(y); });
             if (large_slots > 1) {

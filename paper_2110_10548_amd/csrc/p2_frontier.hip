@@ -1599,8 +1599,9 @@ __global__ __launch_bounds__(256) void k_front_children(const DevQuery* __restri
 // level starts with is marked on the device, and the edges are handed to the counting that the graphs of small groups
 // use (p2_graph.hip).  Prefixes, their sums and their order are not kept: the counts give them back.
 // Bound by the materialized states of the levels, as the enumeration is, and then by the launches: some 14 a level, 3 us
-// each where a level has few states ([3 4 6]: 283 us of the call's 373; 512 devices in four levels: 1.44 ms in
-// k_front_materialize, 1.5 in k_front_classify, 0.44 in k_front_compare, of 4.4 ms).
+// each where a level has few states ([3 4 6], four instructions: 246 us of the call's 352, wavefronts waiting for four fifths of their
+// time in the small kernels; 512 devices in four levels, six: 0.99 ms in k_front_materialize, 1.0 in k_front_classify, 0.46 in
+// k_front_compare, of 3.7 ms).
 // A wavefront takes kChildChunk states at a time, a lane per four instructions (alphabets of at most 255).
 __global__ __launch_bounds__(256) void k_front_edges(const DevQuery* __restrict__ qp, const uint32_t* __restrict__ list, const uint32_t* __restrict__ n_list,
                                                      const uint32_t* __restrict__ from, const uint8_t* __restrict__ codes,

@@ -369,3 +369,15 @@ def test_large_groups_beside_enumerations():
             assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"]) and len(o["programs"]) > 0
             for key in COUNTS:
                 assert r["stats"][key] == o["stats"][key], key
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,more", [([3, 4, 6], 5, {}), ([3, 4, 6], 6, dict(algo=1)), ([2, 2, 4, 8], 6, {}), ([2, 4, 8, 8], 5, {}), ([2, 2, 2], 7, {}), ([2, 2, 2, 2], 6, {}),
+                                               ([2, 2, 2, 2, 2], 5, {})])
+def test_costs_to_the_bit_whichever_way(card, max_len, more):
+    """From a graph or enumerated, what AUTO hands out is the same: a query's shortlist does not depend on its batch."""
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, **more)
+    a, b = (B.p2_synthesize_batch([x], MSG)[0] for x in (q, dict(q, frontier_pairs=2)))
+    assert (a["stats"]["route"], b["stats"]["route"]) == (B.ROUTE_GRAPH, 0)
+    assert np.array_equal(a["programs"], b["programs"]) and np.array_equal(a["cost"], b["cost"])
