@@ -878,8 +878,9 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // hierarchy follow from the factors; worked out for every query, from the devices under every unit, the rows were most of
     // a batch's host time (140 queries of [4 8 8]: 1 000 us of a call's 1 590 with eight threads, and 540 for the call so;
     // 512 queries of [2 4 8 8], 96 distinct sets: 5 600 us, and 400 now without a thread).
-    // (The rows of the other hierarchies are every query's own and built from its devices; host threads share them, as many as
-    //  before: 2 000 queries of eight devices take 17.5 ms so, and 20.3 in one thread.)
+    // (The rows of the other hierarchies are every query's own and built from its devices; host threads share them, one per
+    //  128, as a set takes 1 to 3 us and a thread some 30, twice: 2 000 queries of eight devices take 17.5 ms so, and 20.3 in one
+    //  thread; with eight threads from 32 sets on, 48 queries took 635 us, and 510 in one thread.)
     std::vector<int32_t> row_sets;                       // a query of each
     size_t n_built_sets = 0;                             // ... of another hierarchy
     for (int i = 0; i < n_queries; ++i) {
@@ -917,7 +918,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (rows_ready) return P2_OK;
         size_t bytes = 0;
         const unsigned hw = std::thread::hardware_concurrency();
-        const int n_threads = n_built_sets >= 256 ? (int)std::min<unsigned>(std::max(hw, 1u), 16u) : n_built_sets >= 32 ? (int)std::min<unsigned>(std::max(hw, 1u), 8u) : 1;
+        const int n_threads = (int)std::min<unsigned>({std::max(hw, 1u), 16u, (unsigned)n_built_sets / 128u + 1u});
         auto for_every_set = [&](const auto& f) {
             if (n_threads <= 1) { for (int32_t i : row_sets) f(i); return; }
             std::atomic<size_t> next{0};

@@ -341,7 +341,7 @@ def test_no_graph_is_begun_in_vain():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [40, 300])
+@pytest.mark.parametrize("n", [40, 300, 900])
 def test_rows_of_other_hierarchies_built_by_several_threads(n):
     """Batches whose queries each have bandwidth rows of their own beside some that share theirs."""
     from paper_2110_10548_amd import binding as B
@@ -380,4 +380,15 @@ def test_costs_to_the_bit_whichever_way(card, max_len, more):
     q = _query(card, max_len, **more)
     a, b = (B.p2_synthesize_batch([x], MSG)[0] for x in (q, dict(q, frontier_pairs=2)))
     assert (a["stats"]["route"], b["stats"]["route"]) == (B.ROUTE_GRAPH, 0)
+    assert np.array_equal(a["programs"], b["programs"]) and np.array_equal(a["cost"], b["cost"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,more,route", [([2] * 5, 6, dict(form_mask=4), 5), ([2] * 6, 5, dict(form_mask=2), 9)])
+def test_lists_that_were_too_short(card, max_len, more, route):
+    """More states, or more rows, than was expected of so few forms: evaluated or written again with room."""
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, **more)
+    a, b = (B.p2_synthesize_batch([x], MSG)[0] for x in (q, dict(q, frontier_pairs=2)))
+    assert a["stats"]["route"] == route and len(a["programs"]) > 10000          # (a graph, with its lists enlarged; with its rows written later)
     assert np.array_equal(a["programs"], b["programs"]) and np.array_equal(a["cost"], b["cost"])
