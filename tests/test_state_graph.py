@@ -268,7 +268,10 @@ def test_little_device_memory():
     assert {r["stats"]["route"] for r in want} == {B.ROUTE_GRAPH}
     B.p2_release_thread()
     torch.cuda.empty_cache()
-    others = torch.empty(torch.cuda.mem_get_info()[0] - (5 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        others = torch.empty(torch.cuda.mem_get_info()[0] - (5 << 30), dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        pytest.skip("the device's free memory is not to be had in one piece")
     before = torch.cuda.mem_get_info()[0]
     got = B.p2_synthesize_batch(queries, MSG)
     held = before - torch.cuda.mem_get_info()[0]
