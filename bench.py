@@ -258,7 +258,7 @@ def main():
                "engine": ENGINE_NAMES[engine_asked], "engines_used": engines,
                "device_ms_per_step": {"evaluate": run["eval_ms"] / steps, "frontier": run["front_ms"] / steps,
                                       "order_cost_topk": run["post_ms"] / steps}}
-        if main_engine == 3:
+        if main_engine == 3 and run["front_classify_launches"] > 0:
             cls_s = run["front_classify_ms"] * 1e-3
             n_launch = max(run["front_classify_launches"], 1)
             rate = run["front_classify_lane_ops"] / cls_s
@@ -353,12 +353,11 @@ def main():
         # a kernel that shares the chip.  The same batch with the enumerations one after the other, a few steps: what
         # the kernels reach with the chip to themselves.
         alone = report(timed(queries, msg, args.engine, max(args.steps // 5, 2), 1, B.FLAG_ONE_ENUMERATION_AT_A_TIME), args.config, args.engine)
-        out["one_enumeration_at_a_time"] = {"ms_per_step": alone["ms_per_step"], "steps": alone["steps"],
-                                            "device_ms_per_step": alone["device_ms_per_step"], "roofline": alone["roofline"],
-                                            "materialize": alone["materialize"]}
+        out["one_enumeration_at_a_time"] = {key: alone[key] for key in ("ms_per_step", "steps", "device_ms_per_step", "roofline", "materialize") if key in alone}
         # (beside the timed figure, for a reader of the roofline object alone)
-        out["roofline"]["frac_one_enumeration_at_a_time"] = alone["roofline"]["frac"]
-        out["roofline"]["enumerations_side_by_side"] = 4
+        if "materialize" in alone:
+            out["roofline"]["frac_one_enumeration_at_a_time"] = alone["roofline"]["frac"]
+            out["roofline"]["enumerations_side_by_side"] = 4
 
     if not args.no_compare:
         # the other configurations, a few steps each with the default engine, and where that is the shared-prefix

@@ -394,6 +394,38 @@ constexpr size_t kWalkedBesidePatterns = 9;
 bool walks_beside(const p2::Plan& pl) {
     return pl.n_candidates <= kWalkedBesideMax / (unsigned long long)pl.R && pl.patterns.size() <= kWalkedBesidePatterns;
 }
+// Whether a structure's graph is that of its skeleton, the structure of as many levels of two devices each.  With rows that
+// ReduceScatters cut into whole blocks, a rule sees of a state which chunk sets and masks are equal, disjoint or contained in
+// each other, and these relations do not depend on how many devices a level has; where chunk sets of different shapes
+// overlap (a ReduceScatter after an AllGather over an outer level, its blocks as large as the levels' sizes say) they do, but
+// with three levels not before the sixth instruction, which only counts if it ends at the goal.  That is not a proof for every
+// size, but there are finitely many: for all 15 407 lists of one to six levels with up to 512 devices and the size limits
+// below, the programs, their number by length, the prefixes' and every cost are those of the graph of the devices
+// themselves, and of the enumeration.  (Seven instructions of three levels are not: 3 x 4 x 2 has fewer prefixes.)
+// Checked with all collectives and forms, and used with these; and for single instructions, which the first state decides.
+constexpr int kSkeletonMaxLen[p2::kSkeletonLevels + 1] = {0, 7, 7, 6, 6, 5, 4};
+int group_levels(const p2::Plan& pl) {
+    int n = 0;
+    for (int j = 0; j < pl.n; ++j) n += pl.f[j] > 1 ? 1 : 0;
+    return n;
+}
+bool has_skeleton(const p2::Plan& pl) {
+    const int levels = group_levels(pl);
+    return ((pl.op_mask == 31u && pl.form_mask == 7u) || pl.max_len == 1) && pl.k % pl.R == 0 && levels <= p2::kSkeletonLevels && pl.max_len <= kSkeletonMaxLen[levels];
+}
+// What a query's costs need beside the skeleton's graph.
+void describe_member(const p2::Plan& pl, p2::DevMember& m) {
+    std::memset(&m, 0, sizeof m);
+    m.R = (uint16_t)pl.R; m.k = (uint16_t)pl.k;
+    for (int l = 0; l < p2::kSkeletonLevels; ++l) m.size[l] = 1;
+    int copies = pl.D / pl.R, inside = group_levels(pl);
+    for (int j = 0; j < pl.n; ++j) {
+        copies /= pl.h[j] / pl.f[j];
+        if (pl.f[j] > 1) m.size[--inside] = (uint16_t)pl.f[j];
+        m.inv_bw[j] = 1.0 / pl.bw[j]; m.copies[j] = (uint32_t)copies;
+        m.inside |= (uint32_t)inside << (4 * j);
+    }
+}
 // Room for the states of a structure (see above), first guess; a structure that has more is met with four times as much.
 uint32_t graph_room(const p2::Plan& pl) {
     static const uint32_t levels[5][P2_MAX_LEN + 1] = {{0, 96, 96, 96, 96, 96, 96, 96},
@@ -495,6 +527,7 @@ struct QueryRun {
     bool graph_flat = false;              // ... (or, where it stands in for a walk, the walk's)
     bool graph_large = false;             // its states are worked on by the frontier's kernels
     int graph_id = -1, graph_pos = 0;     // ... its graph, and its place among the graph's queries
+    int graph_first = -1;                 // ... the first query of the graph with the same group
     bool wave_cost = false;               // valid programs costed by the wavefront-per-program kernel
     int enum_id = -1, share_pos = 0;      // frontier: its enumeration, and its place among the enumeration's queries
     int topk = 0;
@@ -658,19 +691,38 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (walks && few)
             for (QueryRun& r : runs) r.graph = false;
     }
-    // queries of one reduction structure are answered from one graph
-    struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t n_blocks = 0; bool small = false, large = false;
-                   size_t off_members = 0, off_query = 0; };
+    // queries of one reduction structure are answered from one graph, and so are the structures of one skeleton
+    struct Graph { int leader = -1; std::vector<int32_t> members, structures; uint32_t n_blocks = 0; bool small = false, large = false, skeleton = false;
+                   int R = 0, rows = 0; size_t off_members = 0, off_query = 0, off_sizes = 0; };
     std::vector<Graph> graphs;
+    auto fused_sums = [](const QueryRun& r) { return r.graph_frontier && !r.graph_flat ? 0u : 1u; };
     for (int i = 0; i < n_queries; ++i) {
         QueryRun& r = runs[i];
         if (!r.graph) continue;
-        for (size_t g = 0; g < graphs.size() && r.graph_id < 0 && share_validity; ++g)
-            if (runs[graphs[g].leader].graph_frontier == r.graph_frontier && runs[graphs[g].leader].graph_flat == r.graph_flat &&
-                runs[graphs[g].leader].graph_large == r.graph_large && same_graph(runs[graphs[g].leader].plan, r.plan)) r.graph_id = (int)g;
-        if (r.graph_id < 0) { r.graph_id = (int)graphs.size(); graphs.emplace_back(); graphs.back().leader = i; graphs.back().large = r.graph_large; }
-        r.graph_pos = (int)graphs[r.graph_id].members.size();
-        graphs[r.graph_id].members.push_back(i);
+        const Plan& pl = r.plan;
+        const bool skeleton = share_validity && has_skeleton(pl);      // (else every query's graph is that of its own devices)
+        const int R = skeleton ? 1 << group_levels(pl) : pl.R;
+        auto same_group = [&](const QueryRun& o) {
+            return o.graph_frontier == r.graph_frontier && o.graph_flat == r.graph_flat && o.graph_large == r.graph_large && same_graph(o.plan, pl);
+        };
+        for (size_t g = 0; g < graphs.size() && r.graph_id < 0 && share_validity; ++g) {
+            const Graph& G = graphs[g];
+            if (G.skeleton != skeleton || G.R != R) continue;
+            const Plan& lead = runs[G.leader].plan;
+            if (skeleton ? lead.max_len == pl.max_len && lead.op_mask == pl.op_mask && lead.form_mask == pl.form_mask : same_group(runs[G.leader])) r.graph_id = (int)g;
+        }
+        if (r.graph_id < 0) {
+            r.graph_id = (int)graphs.size();
+            graphs.emplace_back();
+            Graph& G = graphs.back();
+            G.leader = i; G.skeleton = skeleton; G.large = r.graph_large && !skeleton; G.R = R; G.rows = skeleton ? R : graph_rows(pl);
+        }
+        Graph& G = graphs[r.graph_id];
+        for (size_t t = 0; t < G.structures.size() && r.graph_first < 0; ++t)
+            if (same_group(runs[G.structures[t]])) r.graph_first = G.structures[t];
+        if (r.graph_first < 0) { r.graph_first = i; G.structures.push_back(i); }
+        r.graph_pos = (int)G.members.size();
+        G.members.push_back(i);
     }
     size_t n_others = 0;                 // queries that other engines evaluate
     bool any_topk = false;
@@ -827,8 +879,9 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         off += align_up(sizeof(int32_t) * n_rank, 256);
     }
     // the state graphs: their descriptions, which blocks work on which, and the queries that share each
-    size_t off_gasked = 0, off_graphs = 0, off_glevel = 0, off_gsteps = 0, off_gsmall = 0, off_glarge = 0;
-    std::vector<GraphBlock> glevel, gsteps;
+    size_t off_gasked = 0, off_graphs = 0, off_glevel = 0, off_gsteps = 0, off_gcosts = 0, off_gsmall = 0, off_glarge = 0;
+    std::vector<GraphBlock> glevel, gsteps, gcosts;
+    int skeleton_levels = 0;
     std::vector<uint32_t> gsmall, glarge;
     int graph_levels = 0;
     if (!graphs.empty()) {
@@ -856,15 +909,24 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
             // (four edges a block at a time; two levels have some 70 edges on the way to a goal, three 900, four 6 300)
             const uint32_t nb = G.large ? 512u : sz == 0 ? 18u : std::min(std::max(share, 16u), sz == 1 ? 160u : 512u);
-            for (uint32_t b = 0; n_msg > 0 && b < nb; ++b) gsteps.push_back(GraphBlock{(uint32_t)g, b, nb, 0u});
+            const uint32_t chunks = ((uint32_t)G.members.size() + 63u) / 64u, nc = sz == 0 ? 24u * chunks : sz == 1 ? 240u * chunks : 1600u * std::min(chunks, 4u);
+            if (G.skeleton) for (uint32_t b = 0; n_msg > 0 && b < nc; ++b) gcosts.push_back(GraphBlock{(uint32_t)g, b, nc, 0u});
+            else for (uint32_t b = 0; n_msg > 0 && b < nb; ++b) gsteps.push_back(GraphBlock{(uint32_t)g, b, nb, 0u});
+            if (G.skeleton) skeleton_levels = std::max(skeleton_levels, group_levels(runs[G.leader].plan));
             G.off_members = off;
             off += align_up(sizeof(int32_t) * G.members.size(), 64);
+            if (G.skeleton) {
+                off = align_up(off, 128);
+                G.off_sizes = off;
+                off += sizeof(DevMember) * G.members.size();
+            }
         }
         off = align_up(off, 256);
         off_gasked = off; off += align_up(sizeof(GraphQuery) * (size_t)n_queries, 256);
         off_graphs = off; off += align_up(sizeof(DevGraph) * graphs.size(), 256);
         off_glevel = off; off += align_up(sizeof(GraphBlock) * glevel.size(), 256);
         off_gsteps = off; off += align_up(sizeof(GraphBlock) * gsteps.size(), 256);
+        off_gcosts = off; off += align_up(sizeof(GraphBlock) * gcosts.size(), 256);
         off_gsmall = off; off += align_up(sizeof(uint32_t) * gsmall.size(), 256);
         off_glarge = off; off += align_up(sizeof(uint32_t) * glarge.size(), 256);
     }
@@ -885,6 +947,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     size_t n_built_sets = 0;                             // ... of another hierarchy
     for (int i = 0; i < n_queries; ++i) {
         size_t t = 0;
+        if (runs[i].graph && graphs[runs[i].graph_id].skeleton) continue;            // (costed from its sizes)
         if (runs[i].plan.hierarchy != P2_HIERARCHY_COLLAPSED) { t = row_sets.size(); ++n_built_sets; }
         while (t < row_sets.size() && !same_cost_rows(runs[row_sets[t]].plan, runs[i].plan)) ++t;
         if (t == row_sets.size()) row_sets.push_back(i);
@@ -915,7 +978,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
     }
     auto build_and_upload_rows = [&]() -> int32_t {
-        if (rows_ready) return P2_OK;
+        if (rows_ready || row_sets.empty()) return P2_OK;
         size_t bytes = 0;
         const unsigned hw = std::thread::hardware_concurrency();
         const int n_threads = (int)std::min<unsigned>({std::max(hw, 1u), 16u, (unsigned)n_built_sets / 128u + 1u});
@@ -1056,7 +1119,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         const size_t n_graphs = graphs.size();
         size_t zero = align_up(graph_nan + sizeof(uint32_t) * (size_t)n_queries, 256), mem = 0;
         auto take = [](size_t& at, size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
-        struct Place { size_t table, table_node, planes, state, found, links, use_id, first, use_ends, edges, edge_state, best; };
+        struct Place { size_t table, table_node, planes, state, path, edge_path, found, links, use_id, first, use_ends, edges, edge_state, best; };
         std::vector<Place> places(n_graphs);
         large_at.assign(n_graphs, LargeAt{});
         size_t states_bytes = 0;
@@ -1066,13 +1129,12 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             DevGraph& D = out[g];
             std::memset(&D, 0, sizeof D);
             D.query = (uint32_t)G.leader;
-            D.R = pl.R; D.rows_kept = graph_rows(pl);
+            D.R = G.R; D.rows_kept = G.rows;
             D.n_pat = (int)pl.patterns.size(); D.n_ops = pl.n_ops; D.alphabet = pl.alphabet; D.max_len = pl.max_len;
             D.digit_words = (pl.alphabet + 63) / 64;
             D.n_members = (int)G.members.size();
             for (int o = 0; o < pl.n_ops; ++o) { D.op_mask |= 1u << pl.ops[o]; D.op_ranks |= (uint32_t)o << (4 * pl.ops[o]); }
-            for (int32_t m : G.members) D.split_check |= runs[m].plan.k != D.rows_kept ? 1u : 0u;
-            D.fused = runs[G.leader].graph_frontier && !runs[G.leader].graph_flat ? 0u : 1u;
+            for (int32_t m : G.members) D.split_check |= !G.skeleton && runs[m].plan.k != D.rows_kept ? 1u : 0u;
             D.cap_nodes = graph_room(pl) * graph_scale;
             // (some twice as many children as nodes; a wavefront may leave the rest of what it reserved at every level)
             D.cap_planes = D.cap_nodes * 2 + graph_planes_left(G.n_blocks, pl.max_len) + 256u;
@@ -1112,18 +1174,22 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
             for (size_t p = 0; p < pl.patterns.size() && !G.large; ++p) {
                 const Pattern& pt = pl.patterns[p];
-                D.shape[p] = (uint8_t)reg_shape_of(pt.g, pt.s, 0, 6);
-                for (int d = 0; d < pl.R; ++d)
-                    if (!pt.master || d % pt.s == 0) D.part[p] |= 1ull << d;
+                int lg = 0, ls = 0;                      // (a skeleton's levels have two devices each)
+                for (int j = pt.lo; j < pl.n && G.skeleton; ++j) (j <= pt.hi ? lg : ls) += pl.f[j] > 1 ? 1 : 0;
+                const int shape = G.skeleton ? lg | ls << 4 : reg_shape_of(pt.g, pt.s, 0, 6);
+                D.shape[p] = (uint8_t)shape;
+                for (int d = 0; d < G.R; ++d)
+                    if (!pt.master || (d & ((1 << (shape >> 4)) - 1)) == 0) D.part[p] |= 1ull << d;
             }
             D.all_rows = D.rows_kept >= 64 ? ~0ull : (1ull << D.rows_kept) - 1ull;
-            D.all_cols = pl.R >= 64 ? ~0ull : (1ull << pl.R) - 1ull;
+            D.all_cols = G.R >= 64 ? ~0ull : (1ull << G.R) - 1ull;
             if (G.large) { slots = 0; D.all_rows = D.all_cols = 0ull; }
             Place& P = places[g];
             P.table = take(zero, sizeof(unsigned long long) * slots);
             P.table_node = take(zero, sizeof(uint32_t) * slots);
-            P.planes = take(mem, sizeof(ulonglong2) * (size_t)D.cap_planes * pl.R);
+            P.planes = take(mem, sizeof(ulonglong2) * (size_t)D.cap_planes * G.R);
             P.state = take(mem, sizeof(uint32_t) * D.cap_nodes);
+            P.path = take(mem, G.large ? 0 : sizeof(unsigned long long) * D.cap_nodes);
             P.found = take(mem, G.large ? 0 : sizeof(uint4) * D.cap_found);
             P.links = take(mem, sizeof(uint2) * D.cap_found);
             P.use_id = take(mem, sizeof(uint32_t) * D.cap_nodes);
@@ -1131,6 +1197,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             P.use_ends = take(mem, sizeof(uint32_t) * 8 * (size_t)D.cap_nodes);
             P.edges = take(mem, sizeof(uint32_t) * D.cap_edges);
             P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
+            P.edge_path = take(mem, G.skeleton ? sizeof(unsigned long long) * D.cap_edges : 0);
             P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
         }
         // (nothing of the call that uses these is on its way: this attempt has queued nothing, those before were waited for)
@@ -1164,7 +1231,9 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.use_ends = reinterpret_cast<uint32_t*>(m + P.use_ends);
             D.edges = reinterpret_cast<uint32_t*>(m + P.edges); D.edge_state = reinterpret_cast<uint32_t*>(m + P.edge_state);
             D.best = reinterpret_cast<double*>(m + P.best);
+            D.node_path = reinterpret_cast<unsigned long long*>(m + P.path); D.edge_path = reinterpret_cast<unsigned long long*>(m + P.edge_path);
             D.members = reinterpret_cast<const int32_t*>(static_cast<char*>(C.blob.p) + graphs[g].off_members);
+            D.sizes = graphs[g].skeleton ? reinterpret_cast<const DevMember*>(static_cast<char*>(C.blob.p) + graphs[g].off_sizes) : nullptr;
             if (!graphs[g].large) continue;
             LargeAt& L = large_at[g];
             auto shift = [](auto*& p, char* base) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + reinterpret_cast<size_t>(p)); };
@@ -1355,10 +1424,14 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 dq->k = D.rows_kept; dq->KW = (D.rows_kept + 31) / 32; dq->n_msg = 0; dq->rows_split = (int32_t)D.split_check;
             }
             for (int i = 0; i < n_queries; ++i)
-                reinterpret_cast<GraphQuery*>(hb + off_gasked)[i] = GraphQuery{runs[i].graph ? (uint32_t)runs[i].graph_id : ~0u, (uint32_t)runs[i].graph_pos};
-            for (const Graph& G : graphs) std::memcpy(hb + G.off_members, G.members.data(), sizeof(int32_t) * G.members.size());
+                reinterpret_cast<GraphQuery*>(hb + off_gasked)[i] = GraphQuery{runs[i].graph ? (uint32_t)runs[i].graph_id : ~0u, (uint32_t)runs[i].graph_pos, fused_sums(runs[i]), 0u};
+            for (const Graph& G : graphs) {
+                std::memcpy(hb + G.off_members, G.members.data(), sizeof(int32_t) * G.members.size());
+                for (size_t t = 0; t < G.members.size() && G.skeleton; ++t) describe_member(runs[G.members[t]].plan, reinterpret_cast<DevMember*>(hb + G.off_sizes)[t]);
+            }
             if (!glevel.empty()) std::memcpy(hb + off_glevel, glevel.data(), sizeof(GraphBlock) * glevel.size());
             if (!gsteps.empty()) std::memcpy(hb + off_gsteps, gsteps.data(), sizeof(GraphBlock) * gsteps.size());
+            if (!gcosts.empty()) std::memcpy(hb + off_gcosts, gcosts.data(), sizeof(GraphBlock) * gcosts.size());
             if (!gsmall.empty()) std::memcpy(hb + off_gsmall, gsmall.data(), sizeof(uint32_t) * gsmall.size());
             if (!glarge.empty()) std::memcpy(hb + off_glarge, glarge.data(), sizeof(uint32_t) * glarge.size());
         }
@@ -1378,7 +1451,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (!gsmall.empty()) {
             ++eval_launches;
             int max_R = 1;
-            for (uint32_t g : gsmall) max_R = std::max(max_R, runs[graphs[g].leader].plan.R);
+            for (uint32_t g : gsmall) max_R = std::max(max_R, graphs[g].R);
             P2_HIP(launch_graph_alone(dgs, reinterpret_cast<const uint32_t*>(db + off_gsmall), (unsigned)gsmall.size(), max_R, stream));
         }
         // large groups: one on the call's stream, several on the slots', the largest first, each to the slot with the least to do
@@ -1464,6 +1537,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         if (!gsteps.empty())
             P2_HIP(launch_graph_steps(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gsteps), (unsigned)gsteps.size(), stream));
+        P2_HIP(launch_graph_costs(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gcosts), (unsigned)gcosts.size(), skeleton_levels, stream));
         if (direct && (C.h_progs.ensure(sizeof(p2_program) * rows_room) != hipSuccess ||
                        C.h_costs.ensure(sizeof(double) * rows_room * (size_t)std::max(n_msg, 1)) != hipSuccess)) {
             (void)hipGetLastError();                     // (the rows themselves may well need less)
@@ -1544,9 +1618,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 r.n_valid = (uint32_t)valid; r.n_rerun = r.n_rerun_groups = 0;
                 const unsigned long long applied = r.graph_frontier && !r.graph_flat ? listed : walked;
                 r.steps = applied * (unsigned long long)pl.alphabet; r.members = applied * per_alphabet;
-                const bool own = graphs[r.graph_id].leader == i;
-                r.evaluated = own ? (unsigned long long)gc.n_judged * (unsigned long long)pl.alphabet : 0ull;
-                r.evaluated_members = own ? (unsigned long long)gc.n_judged * per_alphabet : 0ull;
+                // (carried out for the graph's first query, on the devices that its states are of)
+                const Graph& G = graphs[r.graph_id];
+                const DevGraph& D = reinterpret_cast<const DevGraph*>(hb + off_graphs)[r.graph_id];
+                unsigned long long judged_on = 0;
+                for (size_t p = 0; p < pl.patterns.size(); ++p)
+                    judged_on += (unsigned long long)pl.n_ops * (unsigned long long)(G.skeleton ? __builtin_popcountll(D.part[p]) : pl.patterns[p].g * pl.patterns[p].n_groups);
+                const unsigned long long judged = G.leader == i ? gc.n_judged : 0u;
+                r.evaluated = judged * (unsigned long long)pl.alphabet;
+                r.evaluated_members = judged * judged_on;
                 continue;
             }
             r.n_valid = hc[i].n_valid; r.n_rerun = hc[i].n_rerun; r.n_rerun_groups = hc[i].n_rerun_groups;
@@ -2081,7 +2161,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (r.n_valid == 0) continue;
         if (r.graph && only_graphs) continue;            // (one after the other, as the counts on the device say)
         if (r.graph) {                                   // (the rows come out in order and costed)
-            graph_rows_of.push_back(GraphRows{graph_row_blocks, (uint32_t)i, (uint32_t)r.graph_id, (uint32_t)r.graph_pos, r.n_valid, 0u,
+            graph_rows_of.push_back(GraphRows{graph_row_blocks, (uint32_t)i, (uint32_t)r.graph_id, (uint32_t)r.graph_pos, r.n_valid, fused_sums(r),
                                               (unsigned long long)r.out_first});
             graph_row_blocks += (r.n_valid + 255u) / 256u;
             continue;
@@ -2370,7 +2450,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 s.member_visits = enums[r.enum_id].flat_instr * per_alphabet;
             }
             s.valid = r.n_valid; s.group_size = r.plan.R; s.n_patterns = (int32_t)r.plan.patterns.size();
-            s.evaluated_with = r.graph ? (graphs[r.graph_id].leader != i ? graphs[r.graph_id].leader : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
+            s.evaluated_with = r.graph ? (r.graph_first != i ? r.graph_first : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
             s.route = (r.graph ? P2_ROUTE_GRAPH : 0) | (left[i] ? P2_ROUTE_GRAPH_LEFT : 0) | (repeated ? P2_ROUTE_REPEATED : 0) |
                       (wanted_direct && store && !direct ? P2_ROUTE_ROWS_LATER : 0);
             s.alphabet = r.plan.alphabet; s.engine = r.frontier || r.graph_frontier ? P2_ENGINE_FRONTIER : r.shared ? P2_ENGINE_SHARED : r.regs ? P2_ENGINE_SMALL : r.engine;

@@ -444,6 +444,16 @@ struct GraphCounters {             // zero on entry
     uint32_t walked_planes, n_children, n_child_planes, pad2;      // large groups: planes walked by the classification; children built
 };
 constexpr int kGraphPatterns = 36;
+constexpr int kSkeletonLevels = 6;
+// What the cost of a program over a skeleton (two devices a level, see p2_graph.hip) needs to know of a query's own sizes.
+struct DevMember {
+    double inv_bw[P2_MAX_LEVELS];              // of the hardware levels
+    uint32_t copies[P2_MAX_LEVELS];            // of the reduction group in a unit of the level; 0: no such level
+    uint16_t size[kSkeletonLevels];            // devices of the group's levels, innermost first (1: no such level)
+    uint16_t R, k;                             // the group's devices, its chunks
+    uint32_t inside;                           // four bits a hardware level: levels of the group further in
+    uint32_t pad[3];
+};
 // One reduction structure: what its kernels read and where they write.  A state is plane | pairs << 28, its pairs in
 // consecutive planes [R] of (rows, mask).
 struct DevGraph {
@@ -453,7 +463,6 @@ struct DevGraph {
     int32_t n_members;             // queries that share the structure
     uint32_t op_mask, op_ranks;    // enabled ops; four bits per op: its rank among them
     uint32_t split_check;          // rows stand for blocks of several chunks
-    uint32_t fused;                // how a program's step costs are added up (see k_graph_emit)
     uint32_t cap_nodes, cap_planes, cap_found, cap_edges, table_mask;
     unsigned long long all_rows, all_cols;
     GraphCounters* ctr;
@@ -473,13 +482,17 @@ struct DevGraph {
     int32_t wq, qk;
     double* best;                  // [edge][member]: most loaded uplink, bytes (in chunks) over bandwidth
     const int32_t* members;
+    // skeletons: the members' sizes (else null); the instructions that lead to a node and to where an edge on the way to a goal
+    // starts, a byte each (digit + 1), the last one lowest
+    const DevMember* sizes;
+    unsigned long long* node_path; unsigned long long* edge_path;
     // its patterns: log2 g | log2 s << 4; bit d set iff device d takes part
     uint8_t shape[kGraphPatterns + 4];
     unsigned long long part[kGraphPatterns];
 };
 struct GraphBlock { uint32_t graph, index, count, pad; };                 // block `index` of the `count` that work on the graph
 struct GraphRows {                 // rows of one query: blocks [first_block, next segment's first_block), 256 rows each
-    uint32_t first_block, query, graph, member, count, pad;
+    uint32_t first_block, query, graph, member, count, fused;
     unsigned long long out_first;
 };
 // Structures of few states (graph_alone_holds; list: numbers of graphs), a block each: levels, counts and edges in one launch.
@@ -490,12 +503,14 @@ hipError_t launch_graph_alone(const DevGraph* graphs, const uint32_t* list, unsi
 // The others: a launch per level, then one for the counts and the edges (lds_bytes: for the counts of the largest).
 hipError_t launch_graph_level(const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int level, int max_len, hipStream_t stream);
 hipError_t launch_graph_finish(const DevGraph* graphs, const uint32_t* list, unsigned n, size_t lds_bytes, hipStream_t stream);
-// What the edges add to the bandwidth sums of every query (needs the bandwidth rows).
+// What the edges add to the bandwidth sums of every query: of skeletons of at most max_levels levels, from the queries' sizes; of the
+// others, from the bandwidth rows.
+hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int max_levels, hipStream_t stream);
 hipError_t launch_graph_steps(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream);
 // The rows of the valid programs.  Without segs every query of the call (asked[0 .. n_queries)) is answered from a graph:
 // the rows come one query after the other in that order, as far as cap_rows, and ctrs_out (may be null, host memory) gets
 // the counts of all graphs.  sorted may be null.
-struct GraphQuery { uint32_t graph, member; };           // graph ~0: a query without candidates
+struct GraphQuery { uint32_t graph, member, fused, pad; };           // graph ~0: a query without candidates; fused: how a program's step costs are added up (see k_graph_emit)
 hipError_t launch_graph_emit(const DevQuery* queries, const DevGraph* graphs, const GraphCounters* ctrs, const GraphQuery* asked, int n_queries,
                              const GraphRows* segs, int n_segs, unsigned n_blocks, unsigned long long cap_rows, unsigned long long* sorted,
                              p2_program* progs, double* costs, void* ctrs_out, int n_graphs, hipStream_t stream);

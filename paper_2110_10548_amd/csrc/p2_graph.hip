@@ -23,8 +23,12 @@
 // in two; that is checked at every ReduceScatter and reported as well.  What is reported is evaluated by the other
 // engines.
 //
-// Groups that are larger or have other patterns bring their edges from the frontier's kernels (p2_frontier.hip) and are
-// counted, costed and listed here.
+// What follows a state depends on the levels and not on how many devices each has (has_skeleton in p2_api.hip says how far
+// and how that was checked), so the graph is that of the skeleton, two devices a level: two to 64 devices, whatever the sizes,
+// and one graph for all structures of as many levels in a call.  [2 4 8 8], 512 devices, six instructions: 3 740 us with its
+// own devices, 1 300 so; 512 queries of it, 48 structures: 15.5 ms and 3.5.  Groups that no skeleton is used for are evaluated
+// on their own devices, and those among them that are larger or have other patterns bring their edges from the frontier's
+// kernels (p2_frontier.hip) and are counted, costed and listed here.
 #include "p2_compact_dev.h"
 
 #include <type_traits>
@@ -48,6 +52,7 @@ constexpr uint32_t kAloneSlots = 256, kAloneNodes = 96, kAlonePlanes = 112, kAlo
 // The edges a wavefront has found and not yet written to the lists.
 struct Found {
     u64 hash[kWave];                    // of the child's state; 0: the goal
+    u64 path[kWave];                    // instructions that lead to the child
     uint32_t state[kWave], from[kWave]; // child: plane | pairs << 28; node | digit << 23
 };
 // What a block that works on a graph alone keeps with it instead of in device memory.
@@ -57,6 +62,7 @@ struct AloneShared {
     u64 found[P2_MAX_LEN + 1];
     uint32_t n_planes, flags;
     uint32_t node_state[kAloneNodes], use_id[kAloneNodes];
+    u64 node_path[kAloneNodes];
     uint4 edges[kAloneFound];
     uint2 links[kAloneFound];
 };
@@ -72,18 +78,18 @@ template <typename To, typename From>
 __device__ __forceinline__ P2_GLOBAL To* in_global(From* p) { return (P2_GLOBAL To*)p; }
 // The lists that a graph is worked out in: device memory, or the LDS of the one block that does it.
 struct InDevice {
-    using planes = P2_GLOBAL u64x2*; using words = P2_GLOBAL uint32_t*; using found = P2_GLOBAL u32x4*; using links = P2_GLOBAL u32x2*;
+    using planes = P2_GLOBAL u64x2*; using words = P2_GLOBAL uint32_t*; using found = P2_GLOBAL u32x4*; using links = P2_GLOBAL u32x2*; using paths = P2_GLOBAL u64*;
 };
 #define P2_LOCAL __attribute__((address_space(3)))
 struct InBlock {
-    using planes = P2_LOCAL u64x2*; using words = P2_LOCAL uint32_t*; using found = P2_LOCAL u32x4*; using links = P2_LOCAL u32x2*;
+    using planes = P2_LOCAL u64x2*; using words = P2_LOCAL uint32_t*; using found = P2_LOCAL u32x4*; using links = P2_LOCAL u32x2*; using paths = P2_LOCAL u64*;
 };
 template <class Where>
 struct Graph {
     uint32_t query;
     int R, rows_kept, n_pat, n_ops, alphabet, max_len, W, n_members;
-    uint32_t op_mask, op_ranks, split_check, fused;
-    bool links_ready;
+    uint32_t op_mask, op_ranks, split_check;
+    bool links_ready, skeleton;
     P2_GLOBAL const u32x4* large[2];
     int wq, qk;
     uint32_t cap_nodes, cap_planes, cap_found, cap_edges, table_mask;
@@ -94,6 +100,8 @@ struct Graph {
     typename Where::planes planes;
     typename Where::found found;
     typename Where::links links;
+    typename Where::paths node_path;
+    P2_GLOBAL u64* edge_path;
     P2_GLOBAL u64x2* planes_out;
     P2_GLOBAL uint32_t *first_edge, *use_ends, *edges, *edge_state;
     P2_GLOBAL double* best;
@@ -103,13 +111,13 @@ template <class Where>
 __device__ __forceinline__ void open_graph(Graph<Where>& G, const DevGraph& D) {
     G.query = D.query; G.R = D.R; G.rows_kept = D.rows_kept; G.n_pat = D.n_pat; G.n_ops = D.n_ops; G.alphabet = D.alphabet;
     G.max_len = D.max_len; G.W = D.digit_words; G.n_members = D.n_members;
-    G.op_mask = D.op_mask; G.op_ranks = D.op_ranks; G.split_check = D.split_check; G.fused = D.fused;
+    G.op_mask = D.op_mask; G.op_ranks = D.op_ranks; G.split_check = D.split_check;
     G.cap_nodes = D.cap_nodes; G.cap_planes = D.cap_planes; G.cap_found = D.cap_found; G.cap_edges = D.cap_edges; G.table_mask = D.table_mask;
     G.all_rows = D.all_rows; G.all_cols = D.all_cols;
-    G.links_ready = D.large[0] != nullptr; G.wq = D.wq; G.qk = D.qk;
+    G.links_ready = D.large[0] != nullptr; G.skeleton = D.sizes != nullptr; G.wq = D.wq; G.qk = D.qk;
     G.large[0] = in_global<const u32x4>(D.large[0]); G.large[1] = in_global<const u32x4>(D.large[1]);
     G.ctr = in_global<GraphCounters>(D.ctr); G.table = in_global<u64>(D.table);
-    G.planes_out = in_global<u64x2>(D.planes);
+    G.planes_out = in_global<u64x2>(D.planes); G.edge_path = in_global<u64>(D.edge_path);
     G.first_edge = in_global<uint32_t>(D.first_edge); G.use_ends = in_global<uint32_t>(D.use_ends);
     G.edges = in_global<uint32_t>(D.edges); G.edge_state = in_global<uint32_t>(D.edge_state);
     G.best = in_global<double>(D.best); G.members = in_global<const int32_t>(D.members);
@@ -119,6 +127,7 @@ __device__ __forceinline__ Graph<InDevice> open_in_device(const DevGraph& D) {
     open_graph(G, D);
     G.table_node = in_global<uint32_t>(D.table_node); G.node_state = in_global<uint32_t>(D.node_state); G.use_id = in_global<uint32_t>(D.use_id);
     G.planes = in_global<u64x2>(D.planes); G.found = in_global<u32x4>(D.found); G.links = in_global<u32x2>(D.links);
+    G.node_path = in_global<u64>(D.node_path);
     return G;
 }
 __device__ __forceinline__ Graph<InBlock> open_in_block(const DevGraph& D, AloneShared& A, u64x2* planes) {
@@ -126,6 +135,7 @@ __device__ __forceinline__ Graph<InBlock> open_in_block(const DevGraph& D, Alone
     open_graph(G, D);
     G.table_node = (P2_LOCAL uint32_t*)A.table_node; G.node_state = (P2_LOCAL uint32_t*)A.node_state; G.use_id = (P2_LOCAL uint32_t*)A.use_id;
     G.planes = (P2_LOCAL u64x2*)planes; G.found = (P2_LOCAL u32x4*)A.edges; G.links = (P2_LOCAL u32x2*)A.links;
+    G.node_path = (P2_LOCAL u64*)A.node_path;
     if (G.cap_nodes > kAloneNodes) G.cap_nodes = kAloneNodes;
     if (G.cap_planes > kAlonePlanes) G.cap_planes = kAlonePlanes;
     if (G.cap_found > kAloneFound) G.cap_found = kAloneFound;
@@ -462,6 +472,7 @@ __device__ void graph_level(const Graph<Where>& G, const uint32_t* shape, const 
         const bool mine = (uint32_t)t.lane < n_found;
         const u64 h = mine ? F.hash[t.lane] : 0ull;
         const uint32_t state = mine ? F.state[t.lane] : 0u, from = mine ? F.from[t.lane] : 0u;
+        const u64 path = mine ? F.path[t.lane] : 0ull;
         const uint32_t slots = ALONE ? kAloneSlots - 1u : G.table_mask;
         uint32_t slot = kGoalEdge;
         bool fresh = false;
@@ -488,6 +499,7 @@ __device__ void graph_level(const Graph<Where>& G, const uint32_t* shape, const 
             const uint32_t node = next_first + (uint32_t)at + (uint32_t)__popcll(firsts & below);
             if (node < G.cap_nodes) {
                 G.node_state[node] = state;
+                G.node_path[node] = path;
                 G.table_node[slot] = node + 1u;
             } else flags |= kGraphFull;
         }
@@ -507,12 +519,14 @@ __device__ void graph_level(const Graph<Where>& G, const uint32_t* shape, const 
         const int pat0 = (int)((use - i * per_node) * pats), pat1 = pat0 + (int)pats < n_pat ? pat0 + (int)pats : n_pat;
         Pairs<kPairs> st;
         int np = 1;
+        u64 path = 0ull;
         st.r[0] = G.all_rows; st.m[0] = 1ull << t.dev;   // Sec. 3.5: device i holds column i in every row
 #pragma unroll
         for (int p = 1; p < kPairs; ++p) { st.r[p] = 0ull; st.m[p] = 0ull; }
         if (!ALONE && !last && chunk_left == 0u && t.lane == 0) chunk = more_planes(kChunk);      // (asked for before it is needed)
         if (level > 0) {
             const uint32_t state = G.node_state[node];
+            path = G.node_path[node];
             np = (int)(state >> 28);
             const typename Where::planes plane = G.planes + (size_t)(state & kPlaneMask) * R;
             const u64x2 v = plane[t.dev];
@@ -522,7 +536,7 @@ __device__ void graph_level(const Graph<Where>& G, const uint32_t* shape, const 
                 if (p < np) { const u64x2 u = plane[(size_t)p * R + t.dev]; st.r[p] = u.x; st.m[p] = u.y; }
         } else if (i0 == 0u && team == 0u) {
             G.planes[t.dev] = u64x2{st.r[0], st.m[0]};
-            if (t.dev == 0) G.node_state[0] = 1u << 28;
+            if (t.dev == 0) { G.node_state[0] = 1u << 28; G.node_path[0] = 0ull; }
         }
         if (!ALONE && !last && chunk_left == 0u) { chunk = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk); chunk_left = kChunk; }
         // The goal can only come from an AllReduce on devices that all hold every row, an AllGather on devices whose rows all
@@ -592,7 +606,9 @@ __device__ void graph_level(const Graph<Where>& G, const uint32_t* shape, const 
                 const uint32_t at = n_found + (uint32_t)__popcll(adders & (t.lane == 0 ? 0ull : ~0ull >> (kWave - t.lane)));
                 F.hash[at] = h;
                 F.state[at] = place | (cp << 28);
-                F.from[at] = node | (((uint32_t)pat * (uint32_t)G.n_ops + ((G.op_ranks >> (4 * op)) & 15u)) << kDigitShift);
+                const uint32_t digit = (uint32_t)pat * (uint32_t)G.n_ops + ((G.op_ranks >> (4 * op)) & 15u);
+                F.from[at] = node | (digit << kDigitShift);
+                F.path[at] = path << 8 | (digit + 1u);
             }
             n_found += (uint32_t)__popcll(adders);
         }
@@ -776,7 +792,8 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
         uint32_t to = G.first_edge[u] + (uint32_t)__popcll(sets[(size_t)u * W + (d >> 6)] & ((1ull << (d & 63u)) - 1ull));
         for (uint32_t x = 0; x < (d >> 6); ++x) to += (uint32_t)__popcll(sets[(size_t)u * W + x]);
         G.edges[to] = (d << kDigitShift) | (l.y == kGoalEdge ? kGoalEdge : G.use_id[l.y]);
-        G.edge_state[to] = G.node_state[from];
+        if (G.skeleton) G.edge_path[to] = G.node_path[from];
+        else G.edge_state[to] = G.node_state[from];
     }
 }
 
@@ -940,6 +957,141 @@ __global__ __launch_bounds__(kStepWaves * kWave) void k_graph_steps(const DevQue
     }
 }
 
+// The same for a skeleton, from the instructions that lead to an edge's state: a wavefront per edge, a lane per query.
+// Devices whose digits are zero at the same levels hold equally many rows, so a query's rows are followed through the
+// instructions as one number for each of the skeleton's devices, a digit other than zero standing for all of them, and a
+// unit's load is the largest sum over the levels further in.  No state, no bandwidth rows and no device but the skeleton's is
+// looked at; the lanes share the instructions and differ in sizes alone.  Bound by the chain of one edge, a trip to memory and up to
+// six instructions followed: [2 4 8 8] 12.5 us, where k_graph_steps took 81; 512 queries of it 39 us, and 830.
+template <int LOG>
+__global__ __launch_bounds__(kStepWaves * kWave) void k_graph_costs(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
+                                                                    const GraphBlock* __restrict__ blocks) {
+    constexpr int N = 1 << LOG;
+    // (the tables in LDS: an edge is one trip to memory)
+    __shared__ uint32_t s_shape[kGraphPatterns];
+    __shared__ u64 s_part[kGraphPatterns];
+    __shared__ uint16_t s_instr[kGraphPatterns * 5];
+    const GraphBlock b = blocks[blockIdx.x];
+    const DevGraph& D = graphs[b.graph];
+    const Graph<InDevice> G = open_in_device(D);
+    if (G.ctr->flags != 0u) return;
+    const P2_GLOBAL DevMember* const sizes = in_global<const DevMember>(D.sizes);
+    const uint32_t n_edges = G.ctr->n_edges;
+    if ((int)threadIdx.x < G.n_pat) { s_shape[threadIdx.x] = D.shape[threadIdx.x]; s_part[threadIdx.x] = D.part[threadIdx.x]; }
+    if ((int)threadIdx.x < G.alphabet) s_instr[threadIdx.x] = queries[G.query].instr_of_digit[threadIdx.x];
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t chunks = ((uint32_t)G.n_members + kWave - 1u) / kWave, items = n_edges * chunks, per_pass = b.count * (uint32_t)kStepWaves;
+    for (uint32_t it = b.index * (uint32_t)kStepWaves + wave; it < items; it += per_pass) {
+        const uint32_t e = it / chunks, member = (it - e * chunks) * kWave + (uint32_t)lane;
+        const bool mine = member < (uint32_t)G.n_members;
+        const P2_GLOBAL DevMember& own = sizes[mine ? member : 0u];
+        const u64 path = G.edge_path[e];
+        const uint32_t digit = G.edges[e] >> kDigitShift;
+        uint32_t size[LOG], cnt[N];
+#pragma unroll
+        for (int l = 0; l < LOG; ++l) size[l] = own.size[l];
+        const uint32_t R = own.R, k = own.k, inside = own.inside;
+#pragma unroll
+        for (int d = 0; d < N; ++d) cnt[d] = d < G.R ? R : 0u;
+        // an instruction's levels and the devices that take part in it (the same for all lanes)
+        auto open = [&](uint32_t digit, int& op, int& lg, int& ls, uint32_t& range, u64& part) {
+            const uint32_t ins = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_instr[digit]);
+            const uint32_t shape = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_shape[ins >> 3]);
+            const u64 p = s_part[ins >> 3];
+            op = (int)(ins & 7u); lg = (int)(shape & 15u); ls = (int)((shape >> 4) & 15u);
+            range = ((1u << lg) - 1u) << ls;
+            part = (u64)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) | (u64)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32;
+        };
+        int op, lg, ls;
+        uint32_t range;
+        u64 part;
+        // every member's rows together, at every device of the group
+        auto gather = [&](uint32_t range, u64 part) {
+#pragma unroll
+            for (int l = 0; l < LOG; ++l) {
+                if (((range >> l) & 1u) == 0u) continue;
+#pragma unroll
+                for (int d = 0; d < N; ++d) {
+                    if ((d >> l) & 1) continue;
+                    const uint32_t sum = cnt[d] + cnt[d | 1 << l] * (size[l] - 1u);
+                    if ((part >> d) & 1ull) { cnt[d] = sum; cnt[d | 1 << l] = sum; }
+                }
+            }
+        };
+        for (int at = 8 * (P2_MAX_LEN - 1); at >= 0; at -= 8) {
+            const uint32_t code = (uint32_t)(path >> at) & 255u;
+            if (code == 0u) continue;
+            open(code - 1u, op, lg, ls, range, part);
+            if (op == OP_RS) {
+                uint32_t g = 1u;
+#pragma unroll
+                for (int l = 0; l < LOG; ++l) g *= ((range >> l) & 1u) != 0u ? size[l] : 1u;
+                const float share = 1.0f / (float)g;     // (at most 512 rows, and they divide: the nearest whole number is the quotient)
+#pragma unroll
+                for (int d = 0; d < N; ++d)
+                    if ((part >> d) & 1ull) cnt[d] = (uint32_t)((float)cnt[d] * share + 0.5f);
+            } else if (op == OP_AG) {
+                gather(range, part);
+            } else if (op == OP_RD) {
+#pragma unroll
+                for (int d = 0; d < N; ++d)
+                    if (((part >> d) & 1ull) != 0ull && ((uint32_t)d & range) != 0u) cnt[d] = 0u;
+            } else if (op == OP_BC) {
+#pragma unroll
+                for (int l = 0; l < LOG; ++l) {
+                    if (((range >> l) & 1u) == 0u) continue;
+#pragma unroll
+                    for (int d = 0; d < N; ++d)
+                        if (((d >> l) & 1) != 0 && ((part >> d) & 1ull) != 0ull) cnt[d] = cnt[d & ~(1 << l)];
+                }
+            }
+        }
+        open(digit, op, lg, ls, range, part);
+        // at the groups' first devices the rows that set their bytes: the members' common ones, the root's, or all together
+        uint32_t w[N], busiest[LOG + 1];
+#pragma unroll
+        for (int d = 0; d < N; ++d) w[d] = cnt[d];
+        if (op == OP_AG) {
+#pragma unroll
+            for (int l = 0; l < LOG; ++l)
+                if (((range >> l) & 1u) != 0u)
+#pragma unroll
+                    for (int d = 0; d < N; ++d)
+                        if (((d >> l) & 1) == 0) w[d] += w[d | 1 << l] * (size[l] - 1u);
+        }
+#pragma unroll
+        for (int d = 0; d < N; ++d)
+            if (((part >> d) & 1ull) == 0ull || ((uint32_t)d & range) != 0u) w[d] = 0u;
+        // the busiest unit of a level: it holds all digits of the levels further in, as far as they number groups
+#pragma unroll
+        for (int t = 0; t <= LOG; ++t) {
+            uint32_t most = 0u;
+            if (t <= ls) {
+#pragma unroll
+                for (int d = 0; d < N; ++d) most = w[d] > most ? w[d] : most;
+            }
+            busiest[t] = most * k / R;
+            if (t < LOG && t < ls) {
+#pragma unroll
+                for (int d = 0; d < N; ++d)
+                    if (((d >> t) & 1) == 0) { w[d] += w[d | 1 << t] * (size[t] - 1u); w[d | 1 << t] = 0u; }
+            }
+        }
+        double best = 0.0;
+#pragma unroll
+        for (int j = 0; j < P2_MAX_LEVELS; ++j) {
+            const int t = (int)((inside >> (4 * j)) & 15u), at = t < ls ? t : ls;
+            uint32_t load = 0u;
+#pragma unroll
+            for (int x = 0; x <= LOG; ++x) load = x == at ? busiest[x] : load;
+            if (t < ls + lg) best = fmax(best, (double)(load * own.copies[j]) * own.inv_bw[j]);
+        }
+        if (mine) G.best[(size_t)e * G.n_members + member] = best;
+    }
+}
+
 // a + b * c with the product rounded first, whatever the compiler may contract elsewhere.
 __device__ __forceinline__ double add_rounded(double a, double b, double c) {
 #pragma clang fp contract(off)
@@ -957,7 +1109,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
                                                     const GraphRows* __restrict__ segs, int n_segs, u64 cap_rows, u64* __restrict__ sorted,
                                                     p2_program* __restrict__ progs, double* __restrict__ costs, uint4* __restrict__ ctrs_out, int n_graphs) {
     __shared__ u64 wave_sums[256 / kWave];
-    __shared__ uint32_t s_query, s_graph, s_member, s_block, s_count;
+    __shared__ uint32_t s_query, s_graph, s_member, s_block, s_count, s_fused;
     __shared__ u64 s_first;
     __shared__ double s_sum[2][256];
     __shared__ double s_steps[kGraphPatterns * 5], s_alpha[kGraphPatterns * 5], s_per[kGraphPatterns * 5];   // what a step costs, by digit
@@ -975,7 +1127,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
         }
         if (tid == 0) {
             const GraphRows seg = segs[a];
-            s_query = seg.query; s_graph = seg.graph; s_member = seg.member; s_count = seg.count; s_first = seg.out_first;
+            s_query = seg.query; s_graph = seg.graph; s_member = seg.member; s_count = seg.count; s_first = seg.out_first; s_fused = seg.fused;
             s_block = blockIdx.x - seg.first_block;
         }
     } else {
@@ -991,6 +1143,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
             const u64 before = run + block_scan<256>(mine, total, wave_sums);
             if (n > 0u && blockIdx.x >= (uint32_t)before && blockIdx.x < (uint32_t)(before + mine)) {
                 s_query = (uint32_t)q; s_graph = g; s_member = asked[q].member; s_count = n; s_first = before >> 32;
+                s_fused = asked[q].fused;
                 s_block = blockIdx.x - (uint32_t)before;
             }
             run += total;
@@ -1068,7 +1221,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
             if (q.n_msg > 0 && e < end) {
                 const double ring_steps = s_steps[digit], alpha = s_alpha[digit], per = s_per[digit], best = G.best[(size_t)e * G.n_members + member];
                 // (rounded as in the engines whose place this one takes: the walk's costs are fused, the frontier's steps are not)
-                if (G.fused) { sum_alpha = fma(ring_steps, alpha, sum_alpha); sum_beta = fma(per, best, sum_beta); }
+                if (s_fused != 0u) { sum_alpha = fma(ring_steps, alpha, sum_alpha); sum_beta = fma(per, best, sum_beta); }
                 else { sum_alpha = add_rounded(sum_alpha, ring_steps, alpha); sum_beta = add_rounded(sum_beta, per, best); }
             }
         }
@@ -1120,6 +1273,13 @@ hipError_t launch_graph_finish(const DevGraph* graphs, const uint32_t* list, uns
 hipError_t launch_graph_steps(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream) {
     if (n_blocks == 0) return hipSuccess;
     hipLaunchKernelGGL(k_graph_steps, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
+    return hipGetLastError();
+}
+hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int max_levels, hipStream_t stream) {
+    if (n_blocks == 0) return hipSuccess;
+    if (max_levels <= 2) hipLaunchKernelGGL(k_graph_costs<2>, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
+    else if (max_levels <= 4) hipLaunchKernelGGL(k_graph_costs<4>, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
+    else hipLaunchKernelGGL(k_graph_costs<kSkeletonLevels>, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
     return hipGetLastError();
 }
 hipError_t launch_graph_emit(const DevQuery* queries, const DevGraph* graphs, const GraphCounters* ctrs, const GraphQuery* asked, int n_queries,

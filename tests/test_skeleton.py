@@ -1,0 +1,101 @@
+"""Structures answered from the graph of their skeleton (as many levels, two devices each) beside their own devices' graphs and the
+oracle: the same programs, costs and counts whatever the sizes of the levels."""
+import random
+
+import numpy as np
+import pytest
+
+MOST = {1: 7, 2: 7, 3: 6, 4: 6, 5: 5, 6: 4}              # the size limits up to which skeletons are used, by levels
+MSG = [2.0 ** 20, 3.0e8]
+
+
+def _query(card, max_len, seed, **more):
+    rng, L, n = random.Random(seed), len(card), int(np.prod(card))
+    return dict(dict(card=card, axes=[n], placement=[card], reduce_axes=[0], max_len=max_len, bw=[rng.uniform(1e9, 4e11) for _ in range(L)],
+                     alpha=[rng.uniform(1e-6, 3e-5) for _ in range(L)]), **more)
+
+
+def _same(a, b):
+    assert np.array_equal(a["programs"], b["programs"]) and len(a["programs"]) > 0
+    assert np.array_equal(a["cost"], b["cost"])          # (to the last bit: loads are whole numbers on either side, and added up in one order)
+    for key in ("candidates", "steps_executed", "member_visits", "valid", "engine"):
+        assert a["stats"][key] == b["stats"][key], key
+
+
+# one level to six, twos, odd and prime sizes, sizes that divide their neighbours and such that do not, up to 512 devices; blocks of chunks
+SIZES = [([2], 7, {}), ([511], 7, {}), ([2, 2], 7, {}), ([3, 170], 7, {}), ([17, 30], 6, dict(algo=1)), ([2, 2, 2], 6, {}), ([3, 4, 2], 6, {}), ([5, 3, 7], 5, dict(n_chunks=210)),
+         ([8, 8, 8], 6, {}), ([3, 2, 85], 6, {}), ([2, 2, 2, 2], 6, {}), ([3, 4, 5, 2], 6, dict(n_chunks=480)), ([2, 4, 8, 8], 6, {}), ([5, 2, 3, 17], 4, {}),
+         ([3, 4, 3, 4], 2, {}), ([2, 3, 2, 5, 2], 5, {}), ([2] * 6, 4, dict(algo=1)), ([3, 2, 2, 3, 2, 7], 4, {}), ([4, 3], 1, {})]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,more", SIZES)
+def test_skeleton_matches_the_devices(card, max_len, more):
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, 1, **more)
+    # (every query by itself, which no skeleton is used for; small odd groups are walked, large ones enumerated)
+    own = B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY)], MSG)[0]
+    auto, short = B.p2_synthesize_batch([q, dict(q, topk=3)], MSG)
+    alone = B.p2_synthesize_batch([q], MSG)[0]           # (rows written straight to the host)
+    for a in (auto, alone):
+        _same(a, own)
+    kk = min(3, len(own["programs"]))
+    for m in range(len(MSG)):
+        best = np.lexsort((own["programs"]["index"], own["cost"][:, m]))[:kk]
+        assert np.array_equal(short["programs"]["index"][m * kk:(m + 1) * kk], own["programs"]["index"][best])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("levels", [2, 3, 4, 5, 6])
+def test_structures_of_one_skeleton(levels):
+    """Groups of many sizes in one batch, more than a wavefront's lanes of them, among other axes and with levels of one device: each as alone."""
+    from paper_2110_10548_amd import binding as B
+    rng = random.Random(levels)
+    queries = []
+    while len(queries) < (70 if levels <= 3 else 12):
+        f = [rng.choice((2, 2, 3, 4, 5, 6, 8, 11)) for _ in range(levels)]
+        for _ in range(rng.randrange(3)):
+            f.insert(rng.randrange(len(f) + 1), 1)       # (a hardware level that the group does not span)
+        g = [rng.choice((1, 1, 2, 3)) for _ in f]        # the other axis
+        if len(f) > 8 or np.prod(f) * np.prod(g) > 512 or np.prod(f) < 66:
+            continue
+        card = [a * b for a, b in zip(f, g)]
+        q = _query(card, min(MOST[levels], 4), len(queries), axes=[int(np.prod(f)), int(np.prod(g))], placement=[f, g], algo=rng.randrange(2), topk=rng.choice((0, 0, 4)))
+        queries.append(q)
+    together = B.p2_synthesize_batch(queries, MSG)
+    apart = B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY) for q in queries[:24]], MSG)
+    for q, r, o in zip(queries, together, apart):
+        _same(r, o)
+    for q, r in list(zip(queries, together))[24:]:
+        _same(r, B.p2_synthesize_batch([q], MSG)[0])
+    assert {r["stats"]["route"] for r in together} <= {0, B.ROUTE_GRAPH} and sum(r["stats"]["steps_evaluated"] > 0 for r in together) < len(queries)
+
+
+@pytest.mark.gpu
+def test_sizes_drawn_from_all():
+    """A draw of the 15 407 lists of one to six levels with up to 512 devices, at the largest size limits."""
+    from paper_2110_10548_amd import binding as B
+    rng = random.Random(11)
+    for levels, n in ((1, 12), (2, 40), (3, 40), (4, 16), (5, 6), (6, 10)):
+        cards = []
+        while len(cards) < n:
+            c = [min(int(2.0 ** rng.uniform(1.0, 10.0 - levels)), 512) for _ in range(levels)]
+            if np.prod(c) <= 512:
+                cards.append(c)
+        queries = [_query(c, MOST[levels], i) for i, c in enumerate(cards)]
+        for a in range(0, n, 2):
+            own = B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY) for q in queries[a:a + 2]], MSG[:1])
+            for r, o in zip(B.p2_synthesize_batch(queries[a:a + 2], MSG[:1]), own):
+                _same(r, o)
+
+
+@pytest.mark.parametrize("levels,max_len,cards", [(1, 6, [[3], [8], [97]]), (2, 4, [[2, 3], [3, 2], [4, 6], [5, 5], [9, 2]]), (3, 3, [[2, 3, 2], [3, 2, 4], [2, 2, 5], [3, 3, 3]])])
+def test_programs_do_not_depend_on_the_sizes(oracle, levels, max_len, cards):
+    """What skeletons rest on, as the oracle sees it: programs and prefixes of any sizes are those of twos."""
+    def of(card):
+        o = oracle.Query(card, [int(np.prod(card))], [card], [0])
+        r = o.synthesize(max_len)
+        return r["index"].tolist(), o.eval_indices(max_len, start=0, count=o.num_candidates(max_len))[2]
+    want = of([2] * levels)
+    for card in cards:
+        assert of(card) == want, card

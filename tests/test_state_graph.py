@@ -314,9 +314,10 @@ def test_expected_rows_are_what_the_oracle_counts(tmp_path, oracle):
             assert most[levels - 1, n - 1] == int(np.count_nonzero(o["len"] <= n)), (levels, n)
 
 
-# levels, size limits and the states behind them: room for all at the first attempt, rows with the evaluation
-STATES = [([2, 32], 7, 42), ([2, 4, 8], 7, 1008), ([2, 2, 4, 4], 6, 17274), ([4, 2, 2, 2, 2], 5, 50567), ([2] * 6, 3, 2513), ([2] * 6, 4, 29586),
-          ([12, 12], 7, 42), ([3, 4, 6], 6, 938), ([2, 3, 2, 4], 6, 17427), ([2, 2, 2, 4, 4], 5, 50647), ([2, 2, 2, 2, 2, 3], 4, 29599)]
+# levels, size limits and the states behind them (of a skeleton, whatever the sizes, those of as many levels of two: 905, 16 798, 50 275 and 29 586,
+# which the devices themselves have some more of; three levels and seven instructions have none): room for all at the first attempt, rows with the evaluation
+STATES = [([2, 32], 7, 42), ([2, 4, 8], 7, 1008), ([2, 2, 4, 4], 6, 16798), ([4, 2, 2, 2, 2], 5, 50275), ([2] * 6, 3, 2513), ([2] * 6, 4, 29586),
+          ([12, 12], 7, 42), ([3, 4, 6], 6, 905), ([2, 3, 2, 4], 6, 16798), ([2, 2, 2, 4, 4], 5, 50275), ([2, 2, 2, 2, 2, 3], 4, 29586)]
 
 
 @pytest.mark.gpu
