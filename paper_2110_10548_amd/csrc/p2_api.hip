@@ -411,7 +411,8 @@ int group_levels(const p2::Plan& pl) {
 }
 bool has_skeleton(const p2::Plan& pl) {
     const int levels = group_levels(pl);
-    return ((pl.op_mask == 31u && pl.form_mask == 7u) || pl.max_len == 1) && pl.k % pl.R == 0 && levels <= p2::kSkeletonLevels && pl.max_len <= kSkeletonMaxLen[levels];
+    return ((pl.op_mask == 31u && pl.form_mask == 7u) || pl.max_len == 1) && levels <= p2::kSkeletonLevels && pl.max_len <= kSkeletonMaxLen[levels] &&
+           (pl.k % pl.R == 0 || levels <= p2::kNarrowLevels);
 }
 // What a query's costs need beside the skeleton's graph.
 void describe_member(const p2::Plan& pl, p2::DevMember& m) {
@@ -692,7 +693,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             for (QueryRun& r : runs) r.graph = false;
     }
     // queries of one reduction structure are answered from one graph, and so are the structures of one skeleton
-    struct Graph { int leader = -1; std::vector<int32_t> members, structures; uint32_t n_blocks = 0; bool small = false, large = false, skeleton = false;
+    struct Graph { int leader = -1; std::vector<int32_t> members, structures; uint32_t n_blocks = 0; bool small = false, large = false, skeleton = false, narrow = false;
                    int R = 0, rows = 0; size_t off_members = 0, off_query = 0, off_sizes = 0; };
     std::vector<Graph> graphs;
     auto fused_sums = [](const QueryRun& r) { return r.graph_frontier && !r.graph_flat ? 0u : 1u; };
@@ -702,6 +703,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         const Plan& pl = r.plan;
         const bool skeleton = share_validity && has_skeleton(pl);      // (else every query's graph is that of its own devices)
         const int R = skeleton ? 1 << group_levels(pl) : pl.R;
+        const bool split = pl.k % pl.R != 0;             // (how far rows can be cut is the group's own)
         auto same_group = [&](const QueryRun& o) {
             return o.graph_frontier == r.graph_frontier && o.graph_flat == r.graph_flat && o.graph_large == r.graph_large && same_graph(o.plan, pl);
         };
@@ -709,13 +711,14 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             const Graph& G = graphs[g];
             if (G.skeleton != skeleton || G.R != R) continue;
             const Plan& lead = runs[G.leader].plan;
-            if (skeleton ? lead.max_len == pl.max_len && lead.op_mask == pl.op_mask && lead.form_mask == pl.form_mask : same_group(runs[G.leader])) r.graph_id = (int)g;
+            if (skeleton && !split ? lead.k % lead.R == 0 && lead.max_len == pl.max_len && lead.op_mask == pl.op_mask && lead.form_mask == pl.form_mask : same_group(runs[G.leader]))
+                r.graph_id = (int)g;
         }
         if (r.graph_id < 0) {
             r.graph_id = (int)graphs.size();
             graphs.emplace_back();
             Graph& G = graphs.back();
-            G.leader = i; G.skeleton = skeleton; G.large = r.graph_large && !skeleton; G.R = R; G.rows = skeleton ? R : graph_rows(pl);
+            G.leader = i; G.skeleton = skeleton; G.narrow = skeleton && group_levels(pl) <= kNarrowLevels; G.large = r.graph_large && !skeleton; G.R = R; G.rows = skeleton ? R : graph_rows(pl);
         }
         Graph& G = graphs[r.graph_id];
         for (size_t t = 0; t < G.structures.size() && r.graph_first < 0; ++t)
@@ -723,6 +726,21 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (r.graph_first < 0) { r.graph_first = i; G.structures.push_back(i); }
         r.graph_pos = (int)G.members.size();
         G.members.push_back(i);
+    }
+    // those that p2_skeleton.hip works on come first; of one and two levels a block each, unless there are larger ones, whose launches
+    // they ride along in
+    unsigned n_alone = 0, n_narrow = 0;
+    {
+        bool larger = false;
+        for (const Graph& G : graphs) larger |= G.narrow && G.R > 4;
+        std::vector<int> at(graphs.size());
+        std::vector<Graph> in_order;
+        in_order.reserve(graphs.size());
+        for (int k = 0; k < 3; ++k)
+            for (size_t g = 0; g < graphs.size(); ++g)
+                if ((!graphs[g].narrow ? 2 : larger ? 1 : 0) == k) { at[g] = (int)in_order.size(); in_order.push_back(graphs[g]); (k == 0 ? n_alone : n_narrow) += k < 2 ? 1u : 0u; }
+        graphs.swap(in_order);
+        for (QueryRun& r : runs) if (r.graph_id >= 0) r.graph_id = at[r.graph_id];
     }
     size_t n_others = 0;                 // queries that other engines evaluate
     bool any_topk = false;
@@ -881,9 +899,9 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // the state graphs: their descriptions, which blocks work on which, and the queries that share each
     size_t off_gasked = 0, off_graphs = 0, off_glevel = 0, off_gsteps = 0, off_gcosts = 0, off_gsmall = 0, off_glarge = 0;
     std::vector<GraphBlock> glevel, gsteps, gcosts;
-    int skeleton_levels = 0;
+    unsigned most_members = 0;
     std::vector<uint32_t> gsmall, glarge;
-    int graph_levels = 0;
+    int graph_levels = 0, narrow_levels = 0, narrow_size = 0;
     if (!graphs.empty()) {
         uint32_t n_by_size[3] = {0, 0, 0};                // up to two levels, three, more
         auto size_of = [&](const Graph& G) { const size_t n = runs[G.leader].plan.patterns.size(); return n <= 4 ? 0 : n <= 9 ? 1 : 2; };
@@ -897,7 +915,10 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             G.small = sz == 0 && alone && graph_alone_holds(graph_room(runs[G.leader].plan));
             const uint32_t share = 2048u / std::max(1u, n_by_size[sz]);
             G.n_blocks = G.small ? 1u : sz == 0 ? 12u : sz == 1 ? std::min(std::max(share, 16u), 160u) : std::min(std::max(share, 64u), 768u);
-            if (G.large) {
+            if (G.narrow) {
+                narrow_levels = std::max(narrow_levels, runs[G.leader].plan.max_len);
+                narrow_size = std::max(narrow_size, G.R);
+            } else if (G.large) {
                 glarge.push_back((uint32_t)g);
                 G.off_query = off;
                 off += align_up(sizeof(DevQuery), 256);
@@ -909,10 +930,10 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
             // (four edges a block at a time; two levels have some 70 edges on the way to a goal, three 900, four 6 300)
             const uint32_t nb = G.large ? 512u : sz == 0 ? 18u : std::min(std::max(share, 16u), sz == 1 ? 160u : 512u);
-            const uint32_t chunks = ((uint32_t)G.members.size() + 63u) / 64u, nc = sz == 0 ? 24u * chunks : sz == 1 ? 240u * chunks : 1600u * std::min(chunks, 4u);
-            if (G.skeleton) for (uint32_t b = 0; n_msg > 0 && b < nc; ++b) gcosts.push_back(GraphBlock{(uint32_t)g, b, nc, 0u});
+            const uint32_t nc = 1600u * std::min(((uint32_t)G.members.size() + 63u) / 64u, 4u);
+            if (G.narrow) most_members = std::max(most_members, (unsigned)G.members.size());
+            else if (G.skeleton) for (uint32_t b = 0; n_msg > 0 && b < nc; ++b) gcosts.push_back(GraphBlock{(uint32_t)g, b, nc, 0u});
             else for (uint32_t b = 0; n_msg > 0 && b < nb; ++b) gsteps.push_back(GraphBlock{(uint32_t)g, b, nb, 0u});
-            if (G.skeleton) skeleton_levels = std::max(skeleton_levels, group_levels(runs[G.leader].plan));
             G.off_members = off;
             off += align_up(sizeof(int32_t) * G.members.size(), 64);
             if (G.skeleton) {
@@ -1119,7 +1140,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         const size_t n_graphs = graphs.size();
         size_t zero = align_up(graph_nan + sizeof(uint32_t) * (size_t)n_queries, 256), mem = 0;
         auto take = [](size_t& at, size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
-        struct Place { size_t table, table_node, planes, state, path, edge_path, found, links, use_id, first, use_ends, edges, edge_state, best; };
+        struct Place { size_t table, table_node, planes, state, path, edge_path, narrow, node_edges, nearest, found, links, use_id, first, use_ends, edges, edge_state, best; };
         std::vector<Place> places(n_graphs);
         large_at.assign(n_graphs, LargeAt{});
         size_t states_bytes = 0;
@@ -1134,7 +1155,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.digit_words = (pl.alphabet + 63) / 64;
             D.n_members = (int)G.members.size();
             for (int o = 0; o < pl.n_ops; ++o) { D.op_mask |= 1u << pl.ops[o]; D.op_ranks |= (uint32_t)o << (4 * pl.ops[o]); }
-            for (int32_t m : G.members) D.split_check |= !G.skeleton && runs[m].plan.k != D.rows_kept ? 1u : 0u;
+            for (int32_t m : G.members) D.split_check |= (G.skeleton ? runs[m].plan.k % runs[m].plan.R != 0 : runs[m].plan.k != D.rows_kept) ? 1u : 0u;
             D.cap_nodes = graph_room(pl) * graph_scale;
             // (some twice as many children as nodes; a wavefront may leave the rest of what it reserved at every level)
             D.cap_planes = D.cap_nodes * 2 + graph_planes_left(G.n_blocks, pl.max_len) + 256u;
@@ -1184,20 +1205,29 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.all_rows = D.rows_kept >= 64 ? ~0ull : (1ull << D.rows_kept) - 1ull;
             D.all_cols = G.R >= 64 ? ~0ull : (1ull << G.R) - 1ull;
             if (G.large) { slots = 0; D.all_rows = D.all_cols = 0ull; }
+            if (G.narrow) {
+                D.cap_planes = 0;
+                D.cap_found = D.cap_edges = std::min(D.cap_found, (1u << 18) - 1u);        // (a node's first edge is kept in 18 bits)
+                D.own_chunks = (uint32_t)pl.k;
+                for (int j = pl.n - 1, l = 0; j >= 0; --j) if (pl.f[j] > 1) D.own_size[l++] = (uint32_t)pl.f[j];
+            }
             Place& P = places[g];
             P.table = take(zero, sizeof(unsigned long long) * slots);
             P.table_node = take(zero, sizeof(uint32_t) * slots);
             P.planes = take(mem, sizeof(ulonglong2) * (size_t)D.cap_planes * G.R);
             P.state = take(mem, sizeof(uint32_t) * D.cap_nodes);
             P.path = take(mem, G.large ? 0 : sizeof(unsigned long long) * D.cap_nodes);
-            P.found = take(mem, G.large ? 0 : sizeof(uint4) * D.cap_found);
+            P.found = take(mem, G.large || G.narrow ? 0 : sizeof(uint4) * D.cap_found);
+            P.narrow = take(mem, G.narrow ? sizeof(uint32_t) * (size_t)skeleton_state_words(group_levels(pl)) * D.cap_found : 0);
+            P.nearest = take(mem, G.narrow ? D.cap_nodes : 0);
+            P.node_edges = take(mem, G.narrow ? sizeof(uint32_t) * D.cap_nodes : 0);
             P.links = take(mem, sizeof(uint2) * D.cap_found);
             P.use_id = take(mem, sizeof(uint32_t) * D.cap_nodes);
-            P.first = take(mem, sizeof(uint32_t) * ((size_t)D.cap_nodes + 1));
+            P.first = take(mem, sizeof(uint2) * (size_t)D.cap_nodes);
             P.use_ends = take(mem, sizeof(uint32_t) * 8 * (size_t)D.cap_nodes);
             P.edges = take(mem, sizeof(uint32_t) * D.cap_edges);
             P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
-            P.edge_path = take(mem, G.skeleton ? sizeof(unsigned long long) * D.cap_edges : 0);
+            P.edge_path = take(mem, G.skeleton && !G.narrow ? sizeof(unsigned long long) * D.cap_edges : 0);
             P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
         }
         // (nothing of the call that uses these is on its way: this attempt has queued nothing, those before were waited for)
@@ -1227,11 +1257,13 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.table = reinterpret_cast<unsigned long long*>(z + P.table); D.table_node = reinterpret_cast<uint32_t*>(z + P.table_node);
             D.planes = reinterpret_cast<ulonglong2*>(m + P.planes); D.node_state = reinterpret_cast<uint32_t*>(m + P.state);
             D.found = reinterpret_cast<uint4*>(m + P.found); D.links = reinterpret_cast<uint2*>(m + P.links);
-            D.use_id = reinterpret_cast<uint32_t*>(m + P.use_id); D.first_edge = reinterpret_cast<uint32_t*>(m + P.first);
+            D.use_id = reinterpret_cast<uint32_t*>(m + P.use_id); D.first_edge = reinterpret_cast<uint2*>(m + P.first);
             D.use_ends = reinterpret_cast<uint32_t*>(m + P.use_ends);
             D.edges = reinterpret_cast<uint32_t*>(m + P.edges); D.edge_state = reinterpret_cast<uint32_t*>(m + P.edge_state);
             D.best = reinterpret_cast<double*>(m + P.best);
             D.node_path = reinterpret_cast<unsigned long long*>(m + P.path); D.edge_path = reinterpret_cast<unsigned long long*>(m + P.edge_path);
+            D.narrow_planes = reinterpret_cast<uint32_t*>(m + P.narrow); D.node_edges = reinterpret_cast<uint32_t*>(m + P.node_edges);
+            D.nearest = reinterpret_cast<uint8_t*>(m + P.nearest);
             D.members = reinterpret_cast<const int32_t*>(static_cast<char*>(C.blob.p) + graphs[g].off_members);
             D.sizes = graphs[g].skeleton ? reinterpret_cast<const DevMember*>(static_cast<char*>(C.blob.p) + graphs[g].off_sizes) : nullptr;
             if (!graphs[g].large) continue;
@@ -1454,6 +1486,10 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             for (uint32_t g : gsmall) max_R = std::max(max_R, graphs[g].R);
             P2_HIP(launch_graph_alone(dgs, reinterpret_cast<const uint32_t*>(db + off_gsmall), (unsigned)gsmall.size(), max_R, stream));
         }
+        if (n_alone > 0) {
+            ++eval_launches;
+            P2_HIP(launch_skeleton_alone(dgs, n_alone, stream));
+        }
         // large groups: one on the call's stream, several on the slots', the largest first, each to the slot with the least to do
         size_t n_slots_used = 0;
         if (n_large > 0) {
@@ -1490,6 +1526,21 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 P2_HIP(hipStreamWaitEvent(stream, C.slot_done[t], 0));
             }
             if (g_prof.on) P2_HIP(hipEventRecord(g_prof.ev[4], stream));
+        }
+        for (int l = 0; n_narrow > 0 && l < narrow_levels; ++l) {
+            // (blocks: of four states with four levels, which have some 45, 450, 2 000, 5 400 and 8 900, and of eight with three, at
+            //  most some 330; a block for every 64 or 128 edges that led there)
+            static const unsigned states[2][P2_MAX_LEN] = {{1, 4, 32, 44, 44, 44, 44}, {1, 12, 128, 512, 768, 768, 768}}, links[2][P2_MAX_LEN] = {{0, 1, 2, 4, 8, 8, 8}, {0, 2, 8, 32, 96, 192, 192}};
+            const int z = narrow_size > 8 ? 1 : 0;
+            ++eval_launches;
+            P2_HIP(launch_skeleton_level(dgs + n_alone, n_narrow, l, states[z][l], links[z][l], stream));
+        }
+        if (n_narrow > 0) {
+            ++eval_launches;
+            // (for every node three bytes, for every edge two, for the nodes further in words)
+            uint32_t most = 0;
+            for (unsigned g = n_alone; g < n_alone + n_narrow; ++g) most = std::max(most, reinterpret_cast<const DevGraph*>(hb + off_graphs)[g].cap_nodes);
+            P2_HIP(launch_skeleton_finish(dgs + n_alone, n_narrow, most <= 2048 ? (size_t)most * 16 + 4096 : (size_t)160 * 1024, stream));
         }
         if (!glarge.empty()) {
             ++eval_launches;
@@ -1537,7 +1588,10 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         if (!gsteps.empty())
             P2_HIP(launch_graph_steps(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gsteps), (unsigned)gsteps.size(), stream));
-        P2_HIP(launch_graph_costs(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gcosts), (unsigned)gcosts.size(), skeleton_levels, stream));
+        P2_HIP(launch_graph_costs(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gcosts), (unsigned)gcosts.size(), stream));
+        if (n_alone + n_narrow > 0)
+            P2_HIP(launch_skeleton_costs(dqs, dgs, n_alone + n_narrow, narrow_size <= 4 ? 64u : narrow_size == 8 ? 1024u : 2048u, most_members,
+                                         narrow_size <= 4 ? 2 : narrow_size == 8 ? 3 : kNarrowLevels, n_msg > 0 ? 1 : 0, stream));
         if (direct && (C.h_progs.ensure(sizeof(p2_program) * rows_room) != hipSuccess ||
                        C.h_costs.ensure(sizeof(double) * rows_room * (size_t)std::max(n_msg, 1)) != hipSuccess)) {
             (void)hipGetLastError();                     // (the rows themselves may well need less)

@@ -473,8 +473,9 @@ struct DevGraph {
     uint4* found;                  // every edge: node | digit << 23, slot of the child in the table (0x7fffff: the goal), child's
                                    // state, 1 if it is the first with its hash
     uint2* links;                  // ... node | digit << 23, node of the child
-    uint32_t* use_id; uint32_t* first_edge; uint32_t* use_ends;           // the nodes on the way to a goal, renumbered; [node][8]: programs
-                                                                          // of exactly r more instructions that end at the goal
+    uint32_t* use_id; uint2* first_edge; uint32_t* use_ends;              // the nodes on the way to a goal, renumbered (skeletons of up to four levels:
+                                                                          // as they are); where the edges begin and end; [node][8]: programs of
+                                                                          // exactly r more instructions that end at the goal
     uint32_t* edges; uint32_t* edge_state;                                // digit << 23 | target; the state it starts from
     // groups that the frontier's kernels work on: their states [R][wq] quads of 16 bytes, the first qk of a device its rows,
     // one list of one-pair states and one of two-pair states (two planes each); null: planes
@@ -486,6 +487,11 @@ struct DevGraph {
     // starts, a byte each (digit + 1), the last one lowest
     const DevMember* sizes;
     unsigned long long* node_path; unsigned long long* edge_path;
+    // skeletons of up to four levels (p2_skeleton.hip; use_id: the nodes on the way to a goal, n_edges of them): the child's state of every
+    // edge; a node's edges, the first << 14 | how many << 7 | goals; how near the goal is (instructions; 255: out of reach); where rows are not blocks of chunks (split_check), the group's own chunks and levels, innermost first
+    uint32_t* narrow_planes; uint32_t* node_edges;
+    uint8_t* nearest;
+    uint32_t own_chunks, own_size[4];
     // its patterns: log2 g | log2 s << 4; bit d set iff device d takes part
     uint8_t shape[kGraphPatterns + 4];
     unsigned long long part[kGraphPatterns];
@@ -503,9 +509,20 @@ hipError_t launch_graph_alone(const DevGraph* graphs, const uint32_t* list, unsi
 // The others: a launch per level, then one for the counts and the edges (lds_bytes: for the counts of the largest).
 hipError_t launch_graph_level(const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int level, int max_len, hipStream_t stream);
 hipError_t launch_graph_finish(const DevGraph* graphs, const uint32_t* list, unsigned n, size_t lds_bytes, hipStream_t stream);
-// What the edges add to the bandwidth sums of every query: of skeletons of at most max_levels levels, from the queries' sizes; of the
-// others, from the bandwidth rows.
-hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int max_levels, hipStream_t stream);
+// Skeletons of up to four levels, the n that begin at `graphs`: of at most two, a block each; the others a launch per level (blocks for
+// its states, and for the edges that led to them), then one for the counts and the edges (lds_bytes: for the counts of the largest).
+constexpr int kNarrowLevels = 4;
+int skeleton_state_words(int levels);
+hipError_t launch_skeleton_alone(const DevGraph* graphs, unsigned n, hipStream_t stream);
+hipError_t launch_skeleton_level(const DevGraph* graphs, unsigned n, int level, unsigned blocks, unsigned link_blocks, hipStream_t stream);
+hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, size_t lds_bytes, hipStream_t stream);
+// Of all of them, the edges on the way to a goal and what these add to the bandwidth sums (blocks: for the states of the largest;
+// members: the most queries of one).
+hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, unsigned n, unsigned blocks, unsigned members, int max_levels, int with_costs,
+                                 hipStream_t stream);
+// What the edges add to the bandwidth sums of every query: of larger skeletons, from the queries' sizes; of the others, from the
+// bandwidth rows.
+hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream);
 hipError_t launch_graph_steps(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream);
 // The rows of the valid programs.  Without segs every query of the call (asked[0 .. n_queries)) is answered from a graph:
 // the rows come one query after the other in that order, as far as cap_rows, and ctrs_out (may be null, host memory) gets

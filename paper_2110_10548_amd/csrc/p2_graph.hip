@@ -29,23 +29,15 @@
 // own devices, 1 300 so; 512 queries of it, 48 structures: 15.5 ms and 3.5.  Groups that no skeleton is used for are evaluated
 // on their own devices, and those among them that are larger or have other patterns bring their edges from the frontier's
 // kernels (p2_frontier.hip) and are counted, costed and listed here.
-#include "p2_compact_dev.h"
-
-#include <type_traits>
+#include "p2_graph_dev.h"
 
 namespace p2 {
 
 namespace {
 
-using u64 = unsigned long long;
 constexpr int kMostPairs = 4;
 constexpr uint32_t kChunk = 8;          // planes a wavefront reserves at a time (a returning addition to one address takes some 10 ns)
 constexpr uint32_t kPlaneMask = 0x0fffffffu;
-constexpr uint32_t kGoalEdge = 0x7fffffu;   // target of an edge that ends at the goal
-constexpr int kDigitShift = 23;
-constexpr uint32_t kMostTries = 256;    // slots looked at before a table counts as full
-constexpr int kFinishThreads = 1024;
-constexpr int kAloneThreads = 1024;
 // a structure of one or two levels has at most 42 states and 93 edges
 constexpr uint32_t kAloneSlots = 256, kAloneNodes = 96, kAlonePlanes = 112, kAloneFound = 160, kAloneScratch = 512;
 
@@ -68,19 +60,11 @@ struct AloneShared {
 };
 
 // A description of a graph for a kernel to work with: a copy, so that the kernel's stores do not make it read again, with
-// pointers to the global address space.  (Through plain pointers the accesses would be flat ones, which count as LDS
-// accesses too: every lane exchange would wait for the stores before it.)
-#define P2_GLOBAL __attribute__((address_space(1)))
-typedef u64 u64x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-template <typename To, typename From>
-__device__ __forceinline__ P2_GLOBAL To* in_global(From* p) { return (P2_GLOBAL To*)p; }
+// pointers to the global address space.
 // The lists that a graph is worked out in: device memory, or the LDS of the one block that does it.
 struct InDevice {
     using planes = P2_GLOBAL u64x2*; using words = P2_GLOBAL uint32_t*; using found = P2_GLOBAL u32x4*; using links = P2_GLOBAL u32x2*; using paths = P2_GLOBAL u64*;
 };
-#define P2_LOCAL __attribute__((address_space(3)))
 struct InBlock {
     using planes = P2_LOCAL u64x2*; using words = P2_LOCAL uint32_t*; using found = P2_LOCAL u32x4*; using links = P2_LOCAL u32x2*; using paths = P2_LOCAL u64*;
 };
@@ -103,7 +87,8 @@ struct Graph {
     typename Where::paths node_path;
     P2_GLOBAL u64* edge_path;
     P2_GLOBAL u64x2* planes_out;
-    P2_GLOBAL uint32_t *first_edge, *use_ends, *edges, *edge_state;
+    P2_GLOBAL u32x2* first_edge;
+    P2_GLOBAL uint32_t *use_ends, *edges, *edge_state;
     P2_GLOBAL double* best;
     P2_GLOBAL const int32_t* members;
 };
@@ -118,7 +103,7 @@ __device__ __forceinline__ void open_graph(Graph<Where>& G, const DevGraph& D) {
     G.large[0] = in_global<const u32x4>(D.large[0]); G.large[1] = in_global<const u32x4>(D.large[1]);
     G.ctr = in_global<GraphCounters>(D.ctr); G.table = in_global<u64>(D.table);
     G.planes_out = in_global<u64x2>(D.planes); G.edge_path = in_global<u64>(D.edge_path);
-    G.first_edge = in_global<uint32_t>(D.first_edge); G.use_ends = in_global<uint32_t>(D.use_ends);
+    G.first_edge = in_global<u32x2>(D.first_edge); G.use_ends = in_global<uint32_t>(D.use_ends);
     G.edges = in_global<uint32_t>(D.edges); G.edge_state = in_global<uint32_t>(D.edge_state);
     G.best = in_global<double>(D.best); G.members = in_global<const int32_t>(D.members);
 }
@@ -141,8 +126,6 @@ __device__ __forceinline__ Graph<InBlock> open_in_block(const DevGraph& D, Alone
     if (G.cap_found > kAloneFound) G.cap_found = kAloneFound;
     return G;
 }
-__device__ __forceinline__ uint32_t add_global(P2_GLOBAL uint32_t* p, uint32_t v) { return atomicAdd((uint32_t*)p, v); }
-__device__ __forceinline__ u64 add_global(P2_GLOBAL u64* p, u64 v) { return atomicAdd((u64*)p, v); }
 __device__ __forceinline__ u64 shfl64(u64 v, int src) { return __shfl(v, src, kWave); }
 
 __device__ __forceinline__ u64 lowest64(u64 x, int n) {
@@ -389,15 +372,6 @@ __device__ __forceinline__ bool make_child(Pairs<kPairs>& st, const Verdict& V, 
     return full;
 }
 
-__device__ __forceinline__ u64 mix(u64 r, u64 m, uint32_t where) {
-    u64 x = (r + 0x5851f42d4c957f2dull * (where + 1u)) * 0xd1342543de82ef95ull;
-    x ^= x >> 31;
-    x = (x ^ (m + (m << 21) + (m >> 35))) * 0xaf251af3b0f025b5ull;
-    x ^= x >> 28;
-    x *= 0xb564ef22ec7aece5ull;
-    return x ^ (x >> 32);
-}
-
 // One level of one graph by wavefront w of nw: the states first reached by `level` instructions are judged against every
 // pattern, a team of R lanes per (state, pattern), and the children of what holds are built and looked up.  The wavefronts
 // do not meet: each collects the edges it finds and writes them to the lists some dozens at a time, so that a level is one
@@ -628,25 +602,6 @@ struct FinishShared {
     uint32_t n_found, n_words;
 };
 
-// Exclusive sums over the block of two counts at once (each below 2^31 in total).
-template <int T>
-__device__ u64 block_scan(u64 v, u64& total, u64* wave_sums) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    u64 s = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const u64 o = __shfl_up(s, off, kWave);
-        if (lane >= off) s += o;
-    }
-    if (lane == kWave - 1) wave_sums[wave] = s;
-    __syncthreads();
-    u64 before = 0ull, all = 0ull;
-    for (int w = 0; w < T / kWave; ++w) { const u64 x = wave_sums[w]; if (w < wave) before += x; all += x; }
-    __syncthreads();
-    total = all;
-    return before + s - v;
-}
-
 // The counts of every node, from one instruction left to the size limit, and the edges that lie on the way to a goal, by
 // one block with a thread per edge.  Count r of a node that `d` instructions reach first is asked for up to r = max_len - d,
 // so the lists of counts get short quickly (17 274 nodes: 7 976 counts for r = 2, then 2 519, 495, 48 and 1) and stay in LDS,
@@ -769,7 +724,7 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
             for (int x = 0; x < W; ++x) n += (uint32_t)__popcll(sets[(size_t)u * W + x]);
         u64 total;
         const uint32_t first = n_edges + (uint32_t)block_scan<T>(n, total, wave_sums);
-        if (u < n_use) G.first_edge[u] = first;
+        if (u < n_use) G.first_edge[u] = u32x2{first, first + n};
         n_edges += (uint32_t)total;
     }
     if (n_edges > G.cap_edges) {                         // (the same for every thread)
@@ -777,7 +732,6 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
         return;
     }
     if (tid == 0) {
-        G.first_edge[n_use] = n_edges;
         ctr->n_edges = n_edges;
         ctr->n_judged = n_nodes;
         uint32_t n = 0u;
@@ -789,7 +743,7 @@ __device__ void graph_finish(const Graph<Where>& G, const Found found, uint32_t 
         const u32x2 l = G.links[e];
         if (l.x == ~0u) continue;
         const uint32_t from = l.x & kGoalEdge, d = l.x >> kDigitShift, u = G.use_id[from];
-        uint32_t to = G.first_edge[u] + (uint32_t)__popcll(sets[(size_t)u * W + (d >> 6)] & ((1ull << (d & 63u)) - 1ull));
+        uint32_t to = G.first_edge[u].x + (uint32_t)__popcll(sets[(size_t)u * W + (d >> 6)] & ((1ull << (d & 63u)) - 1ull));
         for (uint32_t x = 0; x < (d >> 6); ++x) to += (uint32_t)__popcll(sets[(size_t)u * W + x]);
         G.edges[to] = (d << kDigitShift) | (l.y == kGoalEdge ? kGoalEdge : G.use_id[l.y]);
         if (G.skeleton) G.edge_path[to] = G.node_path[from];
@@ -957,28 +911,18 @@ __global__ __launch_bounds__(kStepWaves * kWave) void k_graph_steps(const DevQue
     }
 }
 
-// The same for a skeleton, from the instructions that lead to an edge's state: a wavefront per edge, a lane per query.
-// Devices whose digits are zero at the same levels hold equally many rows, so a query's rows are followed through the
-// instructions as one number for each of the skeleton's devices, a digit other than zero standing for all of them, and a
-// unit's load is the largest sum over the levels further in.  No state, no bandwidth rows and no device but the skeleton's is
-// looked at; the lanes share the instructions and differ in sizes alone.  Bound by the chain of one edge, a trip to memory and up to
-// six instructions followed: [2 4 8 8] 12.5 us, where k_graph_steps took 81; 512 queries of it 39 us, and 830.
-template <int LOG>
+// The same for a skeleton of five or six levels (p2_skeleton.hip has the smaller ones), from the instructions that lead to an edge's
+// state: a wavefront per edge, a lane per query.
 __global__ __launch_bounds__(kStepWaves * kWave) void k_graph_costs(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
                                                                     const GraphBlock* __restrict__ blocks) {
-    constexpr int N = 1 << LOG;
-    // (the tables in LDS: an edge is one trip to memory)
-    __shared__ uint32_t s_shape[kGraphPatterns];
-    __shared__ u64 s_part[kGraphPatterns];
-    __shared__ uint16_t s_instr[kGraphPatterns * 5];
+    __shared__ PatternTable T;
     const GraphBlock b = blocks[blockIdx.x];
     const DevGraph& D = graphs[b.graph];
     const Graph<InDevice> G = open_in_device(D);
     if (G.ctr->flags != 0u) return;
     const P2_GLOBAL DevMember* const sizes = in_global<const DevMember>(D.sizes);
     const uint32_t n_edges = G.ctr->n_edges;
-    if ((int)threadIdx.x < G.n_pat) { s_shape[threadIdx.x] = D.shape[threadIdx.x]; s_part[threadIdx.x] = D.part[threadIdx.x]; }
-    if ((int)threadIdx.x < G.alphabet) s_instr[threadIdx.x] = queries[G.query].instr_of_digit[threadIdx.x];
+    T.open(D, queries[G.query]);
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -986,108 +930,10 @@ __global__ __launch_bounds__(kStepWaves * kWave) void k_graph_costs(const DevQue
     for (uint32_t it = b.index * (uint32_t)kStepWaves + wave; it < items; it += per_pass) {
         const uint32_t e = it / chunks, member = (it - e * chunks) * kWave + (uint32_t)lane;
         const bool mine = member < (uint32_t)G.n_members;
-        const P2_GLOBAL DevMember& own = sizes[mine ? member : 0u];
-        const u64 path = G.edge_path[e];
-        const uint32_t digit = G.edges[e] >> kDigitShift;
-        uint32_t size[LOG], cnt[N];
-#pragma unroll
-        for (int l = 0; l < LOG; ++l) size[l] = own.size[l];
-        const uint32_t R = own.R, k = own.k, inside = own.inside;
-#pragma unroll
-        for (int d = 0; d < N; ++d) cnt[d] = d < G.R ? R : 0u;
-        // an instruction's levels and the devices that take part in it (the same for all lanes)
-        auto open = [&](uint32_t digit, int& op, int& lg, int& ls, uint32_t& range, u64& part) {
-            const uint32_t ins = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_instr[digit]);
-            const uint32_t shape = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_shape[ins >> 3]);
-            const u64 p = s_part[ins >> 3];
-            op = (int)(ins & 7u); lg = (int)(shape & 15u); ls = (int)((shape >> 4) & 15u);
-            range = ((1u << lg) - 1u) << ls;
-            part = (u64)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) | (u64)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32;
-        };
-        int op, lg, ls;
-        uint32_t range;
-        u64 part;
-        // every member's rows together, at every device of the group
-        auto gather = [&](uint32_t range, u64 part) {
-#pragma unroll
-            for (int l = 0; l < LOG; ++l) {
-                if (((range >> l) & 1u) == 0u) continue;
-#pragma unroll
-                for (int d = 0; d < N; ++d) {
-                    if ((d >> l) & 1) continue;
-                    const uint32_t sum = cnt[d] + cnt[d | 1 << l] * (size[l] - 1u);
-                    if ((part >> d) & 1ull) { cnt[d] = sum; cnt[d | 1 << l] = sum; }
-                }
-            }
-        };
-        for (int at = 8 * (P2_MAX_LEN - 1); at >= 0; at -= 8) {
-            const uint32_t code = (uint32_t)(path >> at) & 255u;
-            if (code == 0u) continue;
-            open(code - 1u, op, lg, ls, range, part);
-            if (op == OP_RS) {
-                uint32_t g = 1u;
-#pragma unroll
-                for (int l = 0; l < LOG; ++l) g *= ((range >> l) & 1u) != 0u ? size[l] : 1u;
-                const float share = 1.0f / (float)g;     // (at most 512 rows, and they divide: the nearest whole number is the quotient)
-#pragma unroll
-                for (int d = 0; d < N; ++d)
-                    if ((part >> d) & 1ull) cnt[d] = (uint32_t)((float)cnt[d] * share + 0.5f);
-            } else if (op == OP_AG) {
-                gather(range, part);
-            } else if (op == OP_RD) {
-#pragma unroll
-                for (int d = 0; d < N; ++d)
-                    if (((part >> d) & 1ull) != 0ull && ((uint32_t)d & range) != 0u) cnt[d] = 0u;
-            } else if (op == OP_BC) {
-#pragma unroll
-                for (int l = 0; l < LOG; ++l) {
-                    if (((range >> l) & 1u) == 0u) continue;
-#pragma unroll
-                    for (int d = 0; d < N; ++d)
-                        if (((d >> l) & 1) != 0 && ((part >> d) & 1ull) != 0ull) cnt[d] = cnt[d & ~(1 << l)];
-                }
-            }
-        }
-        open(digit, op, lg, ls, range, part);
-        // at the groups' first devices the rows that set their bytes: the members' common ones, the root's, or all together
-        uint32_t w[N], busiest[LOG + 1];
-#pragma unroll
-        for (int d = 0; d < N; ++d) w[d] = cnt[d];
-        if (op == OP_AG) {
-#pragma unroll
-            for (int l = 0; l < LOG; ++l)
-                if (((range >> l) & 1u) != 0u)
-#pragma unroll
-                    for (int d = 0; d < N; ++d)
-                        if (((d >> l) & 1) == 0) w[d] += w[d | 1 << l] * (size[l] - 1u);
-        }
-#pragma unroll
-        for (int d = 0; d < N; ++d)
-            if (((part >> d) & 1ull) == 0ull || ((uint32_t)d & range) != 0u) w[d] = 0u;
-        // the busiest unit of a level: it holds all digits of the levels further in, as far as they number groups
-#pragma unroll
-        for (int t = 0; t <= LOG; ++t) {
-            uint32_t most = 0u;
-            if (t <= ls) {
-#pragma unroll
-                for (int d = 0; d < N; ++d) most = w[d] > most ? w[d] : most;
-            }
-            busiest[t] = most * k / R;
-            if (t < LOG && t < ls) {
-#pragma unroll
-                for (int d = 0; d < N; ++d)
-                    if (((d >> t) & 1) == 0) { w[d] += w[d | 1 << t] * (size[t] - 1u); w[d | 1 << t] = 0u; }
-            }
-        }
-        double best = 0.0;
-#pragma unroll
-        for (int j = 0; j < P2_MAX_LEVELS; ++j) {
-            const int t = (int)((inside >> (4 * j)) & 15u), at = t < ls ? t : ls;
-            uint32_t load = 0u;
-#pragma unroll
-            for (int x = 0; x <= LOG; ++x) load = x == at ? busiest[x] : load;
-            if (t < ls + lg) best = fmax(best, (double)(load * own.copies[j]) * own.inv_bw[j]);
-        }
+        HeldRows<kSkeletonLevels> rows;
+        rows.start(sizes[mine ? member : 0u], G.R);
+        rows.follow(G.edge_path[e], T);
+        const double best = rows.busiest(T.of(G.edges[e] >> kDigitShift), sizes[mine ? member : 0u]);
         if (mine) G.best[(size_t)e * G.n_members + member] = best;
     }
 }
@@ -1193,8 +1039,9 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
             const int left = len - s;                     // instructions from here on
             // (four edges' counts in flight: edge after edge, each count a load behind its edge's, the walks were the whole of
             //  the kernel: 8.2 million rows of four levels 1 050 us, and 900 so)
-            uint32_t e = G.first_edge[node], edge = 0u;
-            const uint32_t end = G.first_edge[node + 1u];
+            const u32x2 own = G.first_edge[node];
+            uint32_t e = own.x, edge = 0u;
+            const uint32_t end = own.y;
             for (bool found = false; !found && e < end;) {
                 uint32_t four[4], n[4];
 #pragma unroll
@@ -1275,11 +1122,9 @@ hipError_t launch_graph_steps(const DevQuery* queries, const DevGraph* graphs, c
     hipLaunchKernelGGL(k_graph_steps, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
     return hipGetLastError();
 }
-hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int max_levels, hipStream_t stream) {
+hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream) {
     if (n_blocks == 0) return hipSuccess;
-    if (max_levels <= 2) hipLaunchKernelGGL(k_graph_costs<2>, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
-    else if (max_levels <= 4) hipLaunchKernelGGL(k_graph_costs<4>, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
-    else hipLaunchKernelGGL(k_graph_costs<kSkeletonLevels>, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
+    hipLaunchKernelGGL(k_graph_costs, dim3(n_blocks), dim3(kStepWaves * kWave), 0, stream, queries, graphs, blocks);
     return hipGetLastError();
 }
 hipError_t launch_graph_emit(const DevQuery* queries, const DevGraph* graphs, const GraphCounters* ctrs, const GraphQuery* asked, int n_queries,

@@ -71,6 +71,20 @@ def test_structures_of_one_skeleton(levels):
     assert {r["stats"]["route"] for r in together} <= {0, B.ROUTE_GRAPH} and sum(r["stats"]["steps_evaluated"] > 0 for r in together) < len(queries)
 
 
+# chunks that are no multiple of the group's devices: how often rows can be cut is the group's own; chunks that divide for some levels, for none, one chunk
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,chunks", [([80], 4, 16), ([8, 9], 5, 12), ([16, 8], 4, 8), ([4, 4], 5, 4), ([3, 4, 6], 4, 6), ([2, 4, 8], 5, 1), ([4, 4, 8], 4, 8), ([4, 2, 4], 6, 48),
+                                                 ([2, 2, 2, 2], 5, 8), ([2, 3, 4, 5], 4, 30), ([2, 4, 8, 8], 4, 64)])
+def test_rows_that_do_not_divide(card, max_len, chunks):
+    from paper_2110_10548_amd import binding as B
+    q = _query(card, max_len, 2, n_chunks=chunks)
+    other = dict(q, n_chunks=int(np.prod(card)))         # (the whole skeleton beside it)
+    own = B.p2_synthesize_batch([dict(x, flags=B.FLAG_EVALUATE_EVERY_QUERY) for x in (q, other)], MSG)
+    for a, o in zip(B.p2_synthesize_batch([q, other], MSG), own):
+        _same(a, o)
+    _same(B.p2_synthesize_batch([q], MSG)[0], own[0])
+
+
 @pytest.mark.gpu
 def test_sizes_drawn_from_all():
     """A draw of the 15 407 lists of one to six levels with up to 512 devices, at the largest size limits."""
