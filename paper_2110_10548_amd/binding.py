@@ -7,6 +7,7 @@ or __graft_entry__.build()).
 import bisect
 import ctypes as C
 import os
+import sys
 import threading
 
 import numpy as np
@@ -222,7 +223,8 @@ _FIRST_ROWS_PER_QUERY = 4096           # (in a batch: three levels, five instruc
 _MAX_MSG, _MAX_TOPK = 64, 1024         # what a call may ask for: the library refuses more, and no room is made for it
 _PIECE_BYTES = 1 << 20                 # rows of several queries of a batch share copies of at most this size
 _KEEP_BYTES = 1 << 24                  # buffers that a call has filled further than this are not kept
-_own = threading.local()               # where this thread's single-query calls have their rows put: results are copies
+_VIEW_BYTES = 1 << 18                  # results of a single query larger than this are its buffers, smaller ones are copies
+_own = threading.local()               # where this thread's single-query calls have their rows put
 
 
 def _first_rows(topks, n_msg, otherwise):
@@ -234,11 +236,38 @@ def _first_rows(topks, n_msg, otherwise):
     return otherwise
 
 
+def _copy_rows(to, rows):
+    """Program rows as they are in memory (field by field, as numpy copies structures, a megabyte takes 700 us, and so 25)."""
+    to.view(np.uint8)[:] = rows.view(np.uint8)
+    return to
+
+
+def _refs(array):
+    return sys.getrefcount(array)
+
+
+_held_once = (np.zeros(1),)
+_REFS_OF_ONE = _refs(_held_once[0])    # (what asking adds differs between interpreters)
+
+
+def _unused(array, pointers=0):
+    """Whether nothing but the one holder that asks, and pointers made of it, refers to an array, so that its memory can be written
+    again (every view of it refers to it)."""
+    return sys.getrefcount(array) == _REFS_OF_ONE + pointers
+
+
 def _take_room(rows, n_msg):
-    """Buffers for so many rows, and pointers to them: the thread's, where they are large enough (a fresh mapping of the
-    first call's room costs more than evaluating a small query, and making a pointer 4 us).  They are the caller's until
-    it hands them to _keep_room."""
+    """Buffers for so many rows, and pointers to them: the thread's, where they are large enough (a fresh mapping costs a page
+    fault for every 4 KiB written, more than a copy of it, and making a pointer takes 4 us): those that its last call was done
+    with, or some that earlier results were handed out of and that nobody refers to any more.  They are the caller's until it
+    hands them to _keep_room or _lend_room."""
     progs, cost, *at = _own.__dict__.pop("room", (None, None)) if rows <= _FIRST_ROWS else (None, None)
+    if progs is None and rows <= _FIRST_ROWS:
+        lent = _own.__dict__.get("lent", [])
+        for i in range(len(lent)):
+            if len(lent[i][0]) >= rows and len(lent[i][1]) >= rows * n_msg and _unused(lent[i][0], 1) and _unused(lent[i][1], 1):
+                progs, cost, *at = lent.pop(i)
+                break
     if progs is None or len(progs) < rows:
         progs, at = np.zeros(rows, dtype=PROGRAM_DTYPE), None
     if cost is None or len(cost) < rows * n_msg:
@@ -246,10 +275,20 @@ def _take_room(rows, n_msg):
     return (progs, cost, *(at or (progs.ctypes.data_as(C.c_void_p), _p(cost, C.c_double))))
 
 
+def _is_kept(room, filled):
+    return len(room[0]) <= _FIRST_ROWS and len(room[1]) <= _FIRST_ROWS * _MAX_MSG and filled <= _KEEP_BYTES
+
+
 def _keep_room(room, filled):
     """The buffers for the thread's next call (until p2_release_thread), unless they are large."""
-    if len(room[0]) <= _FIRST_ROWS and len(room[1]) <= _FIRST_ROWS * _MAX_MSG and filled <= _KEEP_BYTES:
+    if _is_kept(room, filled):
         _own.room = room
+
+
+def _lend_room(room, filled):
+    """Buffers that a result is handed out of, for one of the thread's next calls once nobody refers to them; the last two."""
+    if _is_kept(room, filled):
+        _own.lent = [room, *_own.__dict__.get("lent", [])][:2]
 
 
 class Batch:
@@ -273,6 +312,7 @@ class Batch:
         self.n_msg = len(self._msg)
         self._offs = np.zeros(self.nq + 1, dtype=np.int64)
         self._stats = (p2_stats * self.nq)()
+        self._pieces = []                                # (copies that earlier results were handed out of)
         self._alloc(_first_rows([int(q.get("topk", 0)) for q in queries], self.n_msg,
                                 min(_FIRST_ROWS_PER_QUERY * self.nq, 2 * _FIRST_ROWS)))
 
@@ -300,15 +340,28 @@ class Batch:
         offs = self._offs.tolist()
         limit = _PIECE_BYTES // (PROGRAM_DTYPE.itemsize + 8 * self.n_msg)
         stats = np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist()
-        out, i = [], 0
+        out, i, pieces = [], 0, []
         while i < self.nq:
             first = offs[i]
             j = max(i + 1, bisect.bisect_right(offs, first + limit) - 1)       # (queries i .. j - 1 share a copy)
-            progs, cost = self._progs[first:offs[j]].copy(), self._cost[first:offs[j], :self.n_msg].copy()
+            progs, cost = self._piece(len(pieces), offs[j] - first)
+            _copy_rows(progs, self._progs[first:offs[j]])
+            cost[:] = self._cost[first:offs[j], :self.n_msg]
+            pieces.append((progs, cost))
             out += [{"programs": progs[a - first:b - first], "cost": cost[a - first:b - first], "stats": dict(zip(_STATS_FIELDS, row))}
                     for a, b, row in zip(offs[i:j], offs[i + 1:j + 1], stats[i:j])]
             i = j
+        self._pieces = pieces
         return out
+
+    def _piece(self, at, rows):
+        """Memory for the copies of one piece: that of the results before, where nobody refers to them any more."""
+        if at < len(self._pieces):
+            progs, cost = self._pieces[at]
+            self._pieces[at] = None
+            if len(progs) == rows and _unused(progs) and _unused(cost):
+                return progs, cost
+        return np.empty(rows, dtype=PROGRAM_DTYPE), np.empty((rows, self.n_msg), dtype=np.float64)
 
     def run(self):
         self.run_raw()
@@ -349,8 +402,16 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
         room = _take_room(max(rows, 1), max(n_msg, 1))
         rc = call(room[2], room[3], rows)
         n = count.value if rc == P2_OK else 0
-        out = room[0][:n].copy(), room[1][:n * n_msg].reshape(n, n_msg).copy()
-        _keep_room(room, n * (PROGRAM_DTYPE.itemsize + 8 * n_msg))
+        filled = n * (PROGRAM_DTYPE.itemsize + 8 * n_msg)
+        out = room[0][:n], room[1][:n * n_msg].reshape(n, n_msg)
+        # (a long list is handed out as it is, and its buffers are written again when nobody refers to it any more; a short one
+        #  would keep many times its size)
+        if filled < _VIEW_BYTES or 8 * n < len(room[0]):
+            out = _copy_rows(np.empty(n, dtype=PROGRAM_DTYPE), out[0]), out[1].copy()
+            _keep_room(room, filled)
+        else:
+            _lend_room(room, filled)
+        del room
         if rc != P2_ENOSPC or cap is not None:
             break
         rows = count.value

@@ -178,3 +178,53 @@ def test_room_for_rows_is_kept_per_thread_and_bounded(B):
     assert wide[0] is first[0] and wide[1] is not first[1] and len(wide[1]) == 5 << 17
     for progs, cost, progs_at, cost_at in (first, wide, large):
         assert progs_at.value == progs.ctypes.data and ctypes.addressof(cost_at.contents) == cost.ctypes.data
+
+
+def test_rooms_that_are_lent_are_written_again_only_when_unused(B):
+    """Buffers that a result is a view of: the thread's again once nobody refers to them, or to anything made of them."""
+    B._own.__dict__.clear()
+
+    def call():                                         # (as a call with a long list does)
+        room = B._take_room(1 << 17, 1)
+        room[0]["index"][:3] += 1
+        B._lend_room(room, 1 << 21)
+        return room[0][:50_000], room[1][:50_000].reshape(50_000, 1)
+
+    first = call()
+    at = first[0].ctypes.data
+    column = first[0]["index"][5:]                      # (a view of a view)
+    del first
+    second = call()
+    assert second[0].ctypes.data != at and second[0]["index"][0] == 1
+    del column
+    third = call()                                      # (now the first one's are free)
+    assert third[0].ctypes.data == at and third[0]["index"][0] == 2 and second[0]["index"][0] == 1
+    kept = [call() for _ in range(4)]                   # (each its own, two of them remembered)
+    assert len({r[0].ctypes.data for r in kept + [second, third]}) == 6 and len(B._own.lent) == 2
+    del third, second, kept
+    B._own.__dict__.clear()
+
+
+def test_pieces_of_results_are_written_again_only_when_unused(B):
+    q = dict(card=[2, 2], axes=[4], placement=[[2, 2]], reduce_axes=[0], max_len=2)
+    b = B.Batch([q] * 3, [1.0])
+    b._alloc(300)
+    b._offs[:] = [0, 100, 150, 300]
+
+    def run(value):
+        b._progs["index"], b._cost[:] = value, value
+        return b.results()
+
+    first = run(1)
+    column = first[1]["cost"][:, 0]
+    del first
+    second = run(2)
+    assert (column == 1.0).all() and (second[1]["cost"] == 2.0).all()
+    del second, column
+    third = run(3)
+    assert (third[2]["programs"]["index"] == 3).all() and all(len(r["programs"]) == n for r, n in zip(third, (100, 50, 150)))
+    del third
+    fourth = run(4)
+    b._offs[:] = [0, 100, 150, 250]                     # (another number of rows: other memory)
+    fifth = run(5)
+    assert (fourth[2]["programs"]["index"] == 4).all() and (fifth[2]["programs"]["index"] == 5).all() and len(fifth[2]["programs"]) == 100
