@@ -497,7 +497,7 @@ struct DevGraph {
     unsigned long long part[kGraphPatterns];
 };
 struct GraphBlock { uint32_t graph, index, count, pad; };                 // block `index` of the `count` that work on the graph
-struct GraphRows {                 // rows of one query: blocks [first_block, next segment's first_block), 256 rows each
+struct GraphRows {                 // rows of one query, at most count: blocks [first_block, next segment's first_block), 256 rows each
     uint32_t first_block, query, graph, member, count, fused;
     unsigned long long out_first;
 };
@@ -541,7 +541,14 @@ struct DevTopkJob {
     long long n;
     long long stride;
     int k;
-    int pad;
+    int n_cost;
+    // where the number of entries is known on the device only: n is the most that there can be, and the rows that are picked are
+    // written out at once (progs null: neither); nan_flag gets 2 where a selection came back short
+    const uint32_t* n_from;
+    const p2_program* progs;       // [n], with the costs [n][n_cost] of which `cost` is a column
+    const double* costs;
+    p2_program* out_progs;         // [min(k, n)], may be host memory
+    double* out_costs;
 };
 // Block b of the launch does jobs[b] alone (at most max_n entries, at most max_k kept).
 hipError_t launch_topk_jobs(const DevTopkJob* jobs, unsigned n_jobs, int max_k, long long max_n, hipStream_t stream);

@@ -998,7 +998,9 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
     }
     __syncthreads();
     const uint32_t t0 = s_block * 256u, t = t0 + tid;
-    if (s_count == 0u) return;
+    if (segs && tid == 0) { const uint32_t n = graphs[s_graph].ctr->n_total; if (n < s_count) s_count = n; }
+    if (segs) __syncthreads();
+    if (t0 >= s_count) return;
     const uint32_t rows = s_count - t0 < 256u ? s_count - t0 : 256u;
     const u64 row0 = s_first + t0;
     if (row0 + rows > cap_rows) return;                   // (the host sees that there are more, and asks again with room)

@@ -113,3 +113,22 @@ def test_programs_do_not_depend_on_the_sizes(oracle, levels, max_len, cards):
     want = of([2] * levels)
     for card in cards:
         assert of(card) == want, card
+
+
+# selections by wavefronts (up to ten), by blocks of 64, 256 and 1 024 threads; more asked for than there is; nothing valid; a graph of the devices themselves
+@pytest.mark.gpu
+@pytest.mark.parametrize("queries", [[([2, 2], 3, 1, {})], [([3, 4, 6], 4, 10, {}), ([2, 2], 5, 10, {}), ([7], 2, 3, {}), ([12, 12], 1, 4, {})], [([2, 2], 4, 64, {}), ([2, 3, 2], 3, 50, {})],
+                                     [([2, 2, 2], 5, 200, {}), ([4, 4], 2, 7, {})], [([2, 2, 2, 2], 5, 1024, {}), ([4, 4], 5, 1024, {})],
+                                     [([2, 4], 3, 5, dict(op_mask=2)), ([2, 4], 3, 5, {}), ([4, 4], 4, 3, dict(op_mask=0b10101))], [([2] * 5, 4, 9, {}), ([2, 2, 2], 7, 6, {})]])
+def test_shortlists_selected_before_the_count(queries):
+    """Calls whose queries all ask for shortlists: the cheapest of the lists that they have without, by (cost, index)."""
+    from paper_2110_10548_amd import binding as B
+    asked = [_query(c, m, i, topk=k, **more) for i, (c, m, k, more) in enumerate(queries)]
+    for msg in (MSG, [1.0, 2.0 ** 22, 5e9]):
+        for q, r in zip(asked, B.p2_synthesize_batch(asked, msg)):
+            full = B.p2_synthesize_batch([dict(q, topk=0)], msg)[0]
+            kk = min(q["topk"], len(full["programs"]))
+            assert r["stats"]["valid"] == len(full["programs"]) and len(r["programs"]) == kk * len(msg)
+            for m in range(len(msg)):
+                best = np.lexsort((full["programs"]["index"], full["cost"][:, m]))[:kk]
+                assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], full["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], full["cost"][best])
