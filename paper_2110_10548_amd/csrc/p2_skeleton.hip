@@ -95,7 +95,7 @@ __device__ __forceinline__ uint32_t across(uint32_t v) {
         return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);
     else return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);                          // row_ror 8
 }
-// f(bit's number) for every bit of the device number that `range` has
+// f(bit's number) for every bit of the device number that `range` has, unrolled
 template <int L, class F>
 __device__ __forceinline__ void for_bits(uint32_t range, const F& f) {
     if constexpr (L > 0) if (range & 1u) f(std::integral_constant<int, 0>());
@@ -146,63 +146,81 @@ struct Team {
     uint32_t range;                         // varied bits of the device number
     int lg, ls;
     bool in;                                // the device takes part
-    __device__ __forceinline__ bool any(bool x) const { return ((__ballot(x) >> base) & ((1ull << (1 << L)) - 1ull)) != 0ull; }
+    // f(bit) for the varied bits, and the word of the lane whose device differs in it.  Four levels: unrolled, DPP moves, for a level
+    // there is bound by its instructions.  Fewer: a loop and LDS exchanges, since what counts there is one block's time, and most of
+    // that goes into fetching instructions for the first time ([3 4 6]: 11.1 us a level unrolled, 9.9 so).
+    template <class F>
+    __device__ __forceinline__ void each(const F& f) const {
+        if constexpr (L == 4) for_bits<L>(range, f);
+        else {
+#pragma unroll 1
+            for (int b = ls; b < ls + lg; ++b) f(b);
+        }
+    }
+    template <int B>
+    __device__ __forceinline__ uint32_t over(uint32_t v, std::integral_constant<int, B>) const { return across<B>(v); }
+    __device__ __forceinline__ uint32_t over(uint32_t v, int b) const { return (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << b)) << 2, (int)v); }
     // the first group member's word
     __device__ __forceinline__ uint32_t root(uint32_t v) const {
-        for_bits<L>(range, [&](auto b) { const uint32_t o = across<b.value>(v); v = (dev >> b.value) & 1 ? o : v; });
-        return v;
+        if constexpr (L == 4) {
+            for_bits<L>(range, [&](auto b) { const uint32_t o = across<b.value>(v); v = (dev >> b.value) & 1 ? o : v; });
+            return v;
+        } else return (uint32_t)__builtin_amdgcn_ds_bpermute((int)((uint32_t)lane & ~range) << 2, (int)v);
     }
 };
 struct Verdict { uint32_t kids, goals; };   // by op: the rule holds and the child is not the goal; it is the goal
 
+// The same bits for all devices of a state: those that any of them has.
+template <int L>
+__device__ __forceinline__ uint32_t together(uint32_t bits) {
+    for_bits<L>(0xfu, [&](auto b) { bits |= across<b.value>(bits); });
+    return bits;
+}
 // A state and a pattern, by the state's lanes together (the rules of Sec. 3.2).  all: the group's members together, the masks and
-// the rows; first: the group's first member.
+// the rows; first: the group's first member.  What a device has against a rule is a bit of a word, and the words are put together
+// once.
 template <int L, class Where>
 __device__ __forceinline__ Verdict judge(const Skeleton<Where>& G, const Team<L>& t, const Device<L>& own, Device<L>& all, Device<L>& first, bool active, bool last) {
     using Dev = Device<L>;
-    bool ar_bad = !active, ag_bad = !active || (t.in && own.rows == 0u);
-    all = own;
-    first.rows = own.rows;
-    uint32_t beyond = 0u, differ = 0u;
-    for_bits<L>(t.range, [&](auto b) {
-        uint32_t overlap = 0u;
-#pragma unroll
-        for (int i = 0; i < Dev::W; ++i) {
-            const uint32_t o = across<b.value>(all.w[i]);
-            overlap |= o & all.w[i];
-            all.w[i] |= t.in ? o : 0u;
-        }
-        const uint32_t o = across<b.value>(all.rows);
-        ar_bad |= t.in && (o != all.rows || overlap != 0u);
-        ag_bad |= t.in && (o & all.rows) != 0u;
-        all.rows |= t.in ? o : 0u;
-    });
+    uint32_t beyond = 0u, differ = 0u;                   // of the first member's: something that it has not, anything
 #pragma unroll
     for (int i = 0; i < Dev::W; ++i) {
         first.w[i] = t.root(own.w[i]);
         beyond |= own.w[i] & ~first.w[i];
         differ |= own.w[i] ^ first.w[i];
     }
-    const bool ar = t.any(t.in && own.rows != 0u) && !t.any(ar_bad), ag = !t.any(ag_bad);
-    // in every group some member must differ from the first
-    uint32_t told = (uint32_t)(__ballot(t.in && differ != 0u) >> t.base) & Dev::kRows;
-    for_bits<L>(t.range, [&](auto b) { told |= told >> (1 << b.value); });
-    const bool idle = t.in && ((uint32_t)t.dev & t.range) == 0u && ((told >> t.dev) & 1u) == 0u;
-    const bool bc = !t.any(!active || (t.in && beyond != 0u) || idle);
-    Verdict V{0u, 0u};
-    if (!__any(ar || ag || bc)) return V;
-    const bool goal = !t.any(t.in ? !all.full() : !own.full()), goal_bc = !t.any(t.in ? !first.full() : !own.full());
-    bool uneven = t.in && (__popc(own.rows) & ((1 << t.lg) - 1)) != 0;
+    first.rows = t.root(own.rows);
+    all = own;
+    uint32_t against = 0u, shared = 0u;                  // AllReduce: rows that differ, contributions in common; AllGather: rows in common
+    t.each([&](auto b) {
+#pragma unroll
+        for (int i = 0; i < Dev::W; ++i) {
+            const uint32_t o = t.over(all.w[i], b);
+            against |= o & all.w[i];
+            all.w[i] |= t.in ? o : 0u;
+        }
+        const uint32_t o = t.over(all.rows, b);
+        against |= o ^ all.rows; shared |= o & all.rows;
+        all.rows |= t.in ? o : 0u;
+        differ |= t.over(differ, b);                     // (in every group some member must differ from the first)
+    });
+    bool uneven = (__popc(own.rows) & ((1 << t.lg) - 1)) != 0;
     if (G.split) {                                       // (a group's chunks may not divide where its rows, as many as devices, do)
         uint32_t g = 1u;
         for_bits<L>(t.range, [&](auto b) { g *= G.size[b.value]; });
-        uneven |= t.in && own.held % g != 0u;
+        uneven |= own.held % g != 0u;
     }
-    const bool rs = !t.any(uneven);
-    const uint32_t holds = (ar ? 1u << OP_AR | 1u << OP_RD | (rs ? 1u << OP_RS : 0u) : 0u) | (ag ? 1u << OP_AG : 0u) | (bc ? 1u << OP_BC : 0u);
+    const bool own_full = own.full(), all_full = all.full(), first_full = first.full();
+    uint32_t f = t.in ? (against != 0u ? 1u : 0u) | (shared != 0u || own.rows == 0u ? 2u : 0u) | (beyond != 0u || differ == 0u ? 4u : 0u) | (own.rows != 0u ? 8u : 0u) |
+                            (all_full ? 0u : 16u) | (first_full ? 0u : 32u) | (uneven ? 64u : 0u)
+                      : own_full ? 0u : 48u;
+    f = together<L>(f);
+    const uint32_t holds = ((f & 9u) == 8u ? 1u << OP_AR | 1u << OP_RD | ((f & 64u) == 0u ? 1u << OP_RS : 0u) : 0u) | ((f & 2u) == 0u ? 1u << OP_AG : 0u) |
+                           ((f & 4u) == 0u ? 1u << OP_BC : 0u);
+    Verdict V;
     // (a Reduce leaves devices with nothing and a ReduceScatter with a part: neither ends at the goal)
-    V.goals = holds & G.op_mask & ((goal ? 1u << OP_AR | 1u << OP_AG : 0u) | (goal_bc ? 1u << OP_BC : 0u));
-    V.kids = last ? 0u : holds & G.op_mask & ~V.goals;
+    V.goals = active ? holds & G.op_mask & (((f & 16u) == 0u ? 1u << OP_AR | 1u << OP_AG : 0u) | ((f & 32u) == 0u ? 1u << OP_BC : 0u)) : 0u;
+    V.kids = active && !last ? holds & G.op_mask & ~V.goals : 0u;
     return V;
 }
 
@@ -230,7 +248,7 @@ __device__ __forceinline__ void make_child(Device<L>& ch, const Skeleton<Where>&
         if (part) v &= Dev::word_of(keep, i);
         ch.w[i] = t.in ? v : own.w[i];
     }
-    const uint32_t rows = (bc ? t.root(own.rows) : all.rows) & keep;
+    const uint32_t rows = (bc ? first.rows : all.rows) & keep;
     ch.rows = t.in ? rows : own.rows;
     ch.held = own.held;
     if (G.split) {
@@ -344,7 +362,7 @@ __device__ void skeleton_level(const Skeleton<Where>& G, LevelShared& S, int lev
 #pragma unroll
                 for (int i = 0; i < Dev::W; ++i) bits += (uint32_t)__popc(own.w[i]);
                 const bool r_off = own.rows != Dev::kRows, m_off = own.rows == 0u || bits != (uint32_t)__popc(own.rows) * N;
-                go = active && (!t.any(r_off) || !t.any(m_off) || !t.any(t.dev == 0 && (r_off || m_off)));
+                go = active && together<L>((r_off ? 1u : 0u) | (m_off ? 2u : 0u) | (t.dev == 0 && (r_off || m_off) ? 4u : 0u)) != 7u;
             }
             if (__any(go)) V = judge<L>(G, t, own, all, root, go, last);
             if (t.dev == 0) {
@@ -376,87 +394,82 @@ __device__ void skeleton_level(const Skeleton<Where>& G, LevelShared& S, int lev
             return (uint32_t)__shfl((int)sums, (int)(e >> 2), kWave) + (p & 15u) + (p & 0xf0000u);
         };
         const uint32_t both = V.kids | V.goals, at = before(judges ? entry : 0u) & 0xffffu;
-        if (n_edges != 0u) {
+        uint32_t base = 0u;
+        // built twice, for the hash and, once every edge has its place, for the lists (a child is a few selections)
+#pragma unroll 1
+        for (int pass = 0; pass < 2 && n_edges != 0u; ++pass) {
+            if (pass == 1) {
+                __syncthreads();
+                // the children looked up, a lane each (a second one where a block of small states has more edges than threads)
+                uint32_t slot[2] = {kGoalEdge, kGoalEdge};
+                bool fresh[2] = {false, false};
+                uint32_t n_fresh = 0u;
+    #pragma unroll
+                for (uint32_t x = 0; x < 2u; ++x) {
+                    if ((uint32_t)wave * kWave + x * kLevelThreads >= n_edges) continue;
+                    const uint32_t le = tid + x * kLevelThreads;
+                    const u64 h = le < n_edges ? S.hash[le] : 0ull;
+                    if (h != 0ull) {
+                        uint32_t s = (uint32_t)h & G.table_mask, tries = 0u;
+#pragma unroll 1
+                        for (; tries < kMostTries; ++tries) {  // (the table is at most half full while the nodes have room)
+                            u64 old = 0ull;
+                            fresh[x] = __hip_atomic_compare_exchange_strong(G.table + s, &old, h, __ATOMIC_RELAXED, __ATOMIC_RELAXED, Where::scope);
+                            if (fresh[x] || old == h) break;
+                            s = (s + 1u) & G.table_mask;
+                        }
+                        if (tries >= kMostTries) { flags |= kGraphFull; fresh[x] = false; s = 0u; }
+                        slot[x] = s;
+                    }
+                    n_fresh += (uint32_t)__popcll(__ballot(fresh[x]));
+                }
+                if (t.lane == 0) S.fresh[wave] = n_fresh;
+                __syncthreads();
+                // (one addition a block: those to one address take turns, some 18 ns each)
+                uint32_t rank = 0u;
+                if (wave == 0) {
+                    const uint32_t v = t.lane < kLevelWaves ? S.fresh[t.lane] : 0u, upto = wave_scan(v);
+                    if (t.lane < kLevelWaves) S.fresh[t.lane] = upto - v;
+                    if (t.lane == kLevelWaves - 1) {
+                        const u64 was = __hip_atomic_fetch_add(G.found + level + 1, (u64)n_edges << 32 | upto, __ATOMIC_RELAXED, Where::scope);
+                        S.base = range.next_edge + (uint32_t)(was >> 32); S.node0 = range.next_first + (uint32_t)was;
+                    }
+                }
+                __syncthreads();
+                base = S.base;
+                rank = S.node0 + S.fresh[wave];
+    #pragma unroll
+                for (uint32_t x = 0; x < 2u; ++x) {
+                    if ((uint32_t)wave * kWave + x * kLevelThreads >= n_edges) continue;
+                    const uint32_t le = tid + x * kLevelThreads, e = base + le;
+                    const u64 firsts = __ballot(fresh[x]);
+                    const uint32_t n = rank + (uint32_t)__popcll(firsts & ((1ull << t.lane) - 1ull));
+                    rank += (uint32_t)__popcll(firsts);
+                    if (le >= n_edges) continue;
+                    const uint32_t edge = S.edge[le], digit = edge >> 16, from = edge & 0xffffu;
+                    if (fresh[x] && n < G.cap_nodes) {
+                        G.node_state[n] = e < G.cap_found ? e : 0u;
+                        G.node_path[n] = S.path[from] << 8 | (digit + 1u);
+                        G.table_node[slot[x]] = n + 1u;
+                    } else if (fresh[x]) flags |= kGraphFull;
+                    if (e < G.cap_found) G.links[e] = u32x2{(first + g0 + from) | digit << kDigitShift, slot[x] | (fresh[x] ? kFreshEdge : 0u)};
+                    else flags |= kGraphFull;
+                }
+            }
 #pragma unroll 1
             for (int op = 0; op < 5; ++op) {
                 const bool kid = ((V.kids >> op) & 1u) != 0u, edge = ((both >> op) & 1u) != 0u;
-                if (!__any(edge)) continue;
-                u64 h = 0ull;
-                if (__any(kid)) {
-                    Dev ch;
-                    make_child<L>(ch, G, t, own, all, root, op);
-                    h = hash_of<L>(ch, t.dev);
-                }
-                if (leader && edge) {
-                    const uint32_t le = at + (uint32_t)__popc(both & ((1u << op) - 1u));
-                    S.hash[le] = kid ? h : 0ull;
-                    S.edge[le] = local | ((uint32_t)pat * (uint32_t)G.n_ops + ((G.op_ranks >> (4 * op)) & 15u)) << 16;
-                }
-            }
-            __syncthreads();
-            // the children looked up, a lane each (a second one where a block of small states has more edges than threads)
-            uint32_t slot[2] = {kGoalEdge, kGoalEdge};
-            bool fresh[2] = {false, false};
-            uint32_t n_fresh = 0u;
-#pragma unroll
-            for (uint32_t x = 0; x < 2u; ++x) {
-                if ((uint32_t)wave * kWave + x * kLevelThreads >= n_edges) continue;
-                const uint32_t le = tid + x * kLevelThreads;
-                const u64 h = le < n_edges ? S.hash[le] : 0ull;
-                if (h != 0ull) {
-                    uint32_t s = (uint32_t)h & G.table_mask, tries = 0u;
-                    for (; tries < kMostTries; ++tries) {  // (the table is at most half full while the nodes have room)
-                        u64 old = 0ull;
-                        fresh[x] = __hip_atomic_compare_exchange_strong(G.table + s, &old, h, __ATOMIC_RELAXED, __ATOMIC_RELAXED, Where::scope);
-                        if (fresh[x] || old == h) break;
-                        s = (s + 1u) & G.table_mask;
-                    }
-                    if (tries >= kMostTries) { flags |= kGraphFull; fresh[x] = false; s = 0u; }
-                    slot[x] = s;
-                }
-                n_fresh += (uint32_t)__popcll(__ballot(fresh[x]));
-            }
-            if (t.lane == 0) S.fresh[wave] = n_fresh;
-            __syncthreads();
-            // (one addition a block: those to one address take turns, some 18 ns each)
-            uint32_t rank = 0u;
-            if (wave == 0) {
-                const uint32_t v = t.lane < kLevelWaves ? S.fresh[t.lane] : 0u, upto = wave_scan(v);
-                if (t.lane < kLevelWaves) S.fresh[t.lane] = upto - v;
-                if (t.lane == kLevelWaves - 1) {
-                    const u64 was = __hip_atomic_fetch_add(G.found + level + 1, (u64)n_edges << 32 | upto, __ATOMIC_RELAXED, Where::scope);
-                    S.base = range.next_edge + (uint32_t)(was >> 32); S.node0 = range.next_first + (uint32_t)was;
-                }
-            }
-            __syncthreads();
-            const uint32_t base = S.base;
-            rank = S.node0 + S.fresh[wave];
-#pragma unroll
-            for (uint32_t x = 0; x < 2u; ++x) {
-                if ((uint32_t)wave * kWave + x * kLevelThreads >= n_edges) continue;
-                const uint32_t le = tid + x * kLevelThreads, e = base + le;
-                const u64 firsts = __ballot(fresh[x]);
-                const uint32_t n = rank + (uint32_t)__popcll(firsts & ((1ull << t.lane) - 1ull));
-                rank += (uint32_t)__popcll(firsts);
-                if (le >= n_edges) continue;
-                const uint32_t edge = S.edge[le], digit = edge >> 16, from = edge & 0xffffu;
-                if (fresh[x] && n < G.cap_nodes) {
-                    G.node_state[n] = e < G.cap_found ? e : 0u;
-                    G.node_path[n] = S.path[from] << 8 | (digit + 1u);
-                    G.table_node[slot[x]] = n + 1u;
-                } else if (fresh[x]) flags |= kGraphFull;
-                if (e < G.cap_found) G.links[e] = u32x2{(first + g0 + from) | digit << kDigitShift, slot[x] | (fresh[x] ? kFreshEdge : 0u)};
-                else flags |= kGraphFull;
-            }
-            // (built a second time: by now every edge has its place, and a child is a few selections)
-#pragma unroll 1
-            for (int op = 0; op < 5; ++op) {
-                const bool kid = ((V.kids >> op) & 1u) != 0u;
-                if (!__any(kid)) continue;
+                if (!__any(pass == 0 ? edge : kid)) continue;
+                const uint32_t le = at + (uint32_t)__popc(both & ((1u << op) - 1u));
                 Dev ch;
                 make_child<L>(ch, G, t, own, all, root, op);
-                const uint32_t e = base + at + (uint32_t)__popc(both & ((1u << op) - 1u));
-                if (kid && e < G.cap_found) ch.store(G.planes + (size_t)e * Dev::kStride, t.dev);
+                if (pass == 0) {
+                    const u64 h = hash_of<L>(ch, t.dev);
+                    if (leader && edge) {
+                        S.hash[le] = kid ? h : 0ull;
+                        S.edge[le] = local | ((uint32_t)pat * (uint32_t)G.n_ops + ((G.op_ranks >> (4 * op)) & 15u)) << 16;
+                    }
+                } else if (kid && base + le < G.cap_found) ch.store(G.planes + (size_t)(base + le) * Dev::kStride, t.dev);
             }
         }
         // where a state's edges are: the first, how many, how many of them goals
@@ -660,8 +673,8 @@ __device__ __forceinline__ void open_level(LevelShared& S, const DevGraph& D) {
     __syncthreads();
 }
 // One level of the graphs, one of them a y: the last n_links blocks of a graph work on the edges that led to the level, the others on
-// its states.  Bound by the chain of one block's steps where a level has few states (three levels: some 11 us a launch) and by the
-// instructions where it has many: [2 4 8 8], six levels, 215 us, where a team of lanes per (state, pattern) in p2_graph.hip takes
+// its states.  Bound by the chain of one block's steps where a level has few states (three levels: some 10 us a launch) and by the
+// instructions where it has many: [2 4 8 8], six levels, 194 us, where a team of lanes per (state, pattern) in p2_graph.hip takes
 // 382; half of that is the fifth level, 5 400 states.
 template <int L>
 __device__ void level_of(const Skeleton<InDevice>& G, LevelShared& S, int level, uint32_t n_links) {
