@@ -1168,7 +1168,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         const size_t n_graphs = graphs.size();
         size_t zero = align_up(graph_nan + sizeof(uint32_t) * (size_t)n_queries, 256), mem = 0;
         auto take = [](size_t& at, size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
-        struct Place { size_t table, table_node, planes, state, path, edge_path, narrow, node_edges, nearest, found, links, use_id, first, use_ends, edges, edge_state, best; };
+        struct Place { size_t table, table_node, planes, state, path, edge_path, narrow, node_edges, nearest, count2, found, links, use_id, first, use_ends, edges, edge_state, best; };
         std::vector<Place> places(n_graphs);
         large_at.assign(n_graphs, LargeAt{});
         size_t states_bytes = 0;
@@ -1248,6 +1248,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             P.found = take(mem, G.large || G.narrow ? 0 : sizeof(uint4) * D.cap_found);
             P.narrow = take(mem, G.narrow ? sizeof(uint32_t) * (size_t)skeleton_state_words(group_levels(pl)) * D.cap_found : 0);
             P.nearest = take(mem, G.narrow ? D.cap_nodes : 0);
+            P.count2 = take(mem, G.narrow ? sizeof(uint2) * D.cap_nodes : 0);
             P.node_edges = take(mem, G.narrow ? sizeof(uint32_t) * D.cap_nodes : 0);
             P.links = take(mem, sizeof(uint2) * D.cap_found);
             P.use_id = take(mem, sizeof(uint32_t) * D.cap_nodes);
@@ -1292,6 +1293,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             D.node_path = reinterpret_cast<unsigned long long*>(m + P.path); D.edge_path = reinterpret_cast<unsigned long long*>(m + P.edge_path);
             D.narrow_planes = reinterpret_cast<uint32_t*>(m + P.narrow); D.node_edges = reinterpret_cast<uint32_t*>(m + P.node_edges);
             D.nearest = reinterpret_cast<uint8_t*>(m + P.nearest);
+            D.count2 = reinterpret_cast<uint2*>(m + P.count2);
             D.members = reinterpret_cast<const int32_t*>(static_cast<char*>(C.blob.p) + graphs[g].off_members);
             D.sizes = graphs[g].skeleton ? reinterpret_cast<const DevMember*>(static_cast<char*>(C.blob.p) + graphs[g].off_sizes) : nullptr;
             if (!graphs[g].large) continue;
@@ -1595,10 +1597,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         if (n_narrow > 0) {
             ++eval_launches;
-            // (for every node three bytes, for every edge two, for the nodes further in words)
-            uint32_t most = 0;
-            for (unsigned g = n_alone; g < n_alone + n_narrow; ++g) most = std::max(most, reinterpret_cast<const DevGraph*>(hb + off_graphs)[g].cap_nodes);
-            P2_HIP(launch_skeleton_finish(dgs + n_alone, n_narrow, most <= 2048 ? (size_t)most * 16 + 4096 : (size_t)160 * 1024, stream));
+            uint32_t most_nodes = 0, most_edges = 0;
+            int most_len = 0;
+            for (unsigned g = n_alone; g < n_alone + n_narrow; ++g) {
+                const DevGraph& D = reinterpret_cast<const DevGraph*>(hb + off_graphs)[g];
+                most_nodes = std::max(most_nodes, D.cap_nodes);
+                most_edges = std::max(most_edges, D.cap_found);
+                most_len = std::max(most_len, (int)D.max_len);
+            }
+            P2_HIP(launch_skeleton_finish(dgs + n_alone, n_narrow, most_nodes, most_edges, most_len, stream));
         }
         if (!glarge.empty()) {
             ++eval_launches;

@@ -488,9 +488,11 @@ struct DevGraph {
     const DevMember* sizes;
     unsigned long long* node_path; unsigned long long* edge_path;
     // skeletons of up to four levels (p2_skeleton.hip; use_id: the nodes on the way to a goal, n_edges of them): the child's state of every
-    // edge; a node's edges, the first << 14 | how many << 7 | goals; how near the goal is (instructions; 255: out of reach); where rows are not blocks of chunks (split_check), the group's own chunks and levels, innermost first
+    // edge; a node's edges, the first << 14 | how many << 7 | goals; how near the goal is (instructions; 255: out of reach);
+    // the programs of two instructions from a node, to the goal and short of it; where rows are not blocks of chunks (split_check),
+    // the group's own chunks and levels, innermost first
     uint32_t* narrow_planes; uint32_t* node_edges;
-    uint8_t* nearest;
+    uint8_t* nearest; uint2* count2;
     uint32_t own_chunks, own_size[4];
     // its patterns: log2 g | log2 s << 4; bit d set iff device d takes part
     uint8_t shape[kGraphPatterns + 4];
@@ -515,7 +517,7 @@ constexpr int kNarrowLevels = 4;
 int skeleton_state_words(int levels);
 hipError_t launch_skeleton_alone(const DevGraph* graphs, unsigned n, hipStream_t stream);
 hipError_t launch_skeleton_level(const DevGraph* graphs, unsigned n, int level, unsigned blocks, unsigned link_blocks, hipStream_t stream);
-hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, size_t lds_bytes, hipStream_t stream);
+hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, uint32_t most_nodes, uint32_t most_edges, int max_len, hipStream_t stream);      // (the most that one of them has room for)
 // Of all of them, the edges on the way to a goal and what these add to the bandwidth sums (blocks: for the states of the largest;
 // members: the most queries of one).
 hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, unsigned n, unsigned blocks, unsigned members, int max_levels, int with_costs,

@@ -52,6 +52,7 @@ struct Skeleton {
     typename Where::template at<uint32_t> table_node, node_state, node_edges, planes;
     typename Where::template at<u32x2> links;
     P2_GLOBAL uint32_t *use_ends, *use_list;
+    P2_GLOBAL u32x2* count2;
     P2_GLOBAL uint8_t* nearest;
 };
 template <class Where>
@@ -63,7 +64,7 @@ __device__ __forceinline__ void open_skeleton(Skeleton<Where>& G, const DevGraph
 #pragma unroll
     for (int l = 0; l < kNarrowLevels; ++l) G.size[l] = D.own_size[l];
     G.ctr = in_global<GraphCounters>(D.ctr);
-    G.use_ends = in_global<uint32_t>(D.use_ends); G.nearest = in_global<uint8_t>(D.nearest); G.use_list = in_global<uint32_t>(D.use_id);
+    G.use_ends = in_global<uint32_t>(D.use_ends); G.nearest = in_global<uint8_t>(D.nearest); G.use_list = in_global<uint32_t>(D.use_id); G.count2 = in_global<u32x2>(D.count2);
 }
 __device__ __forceinline__ Skeleton<InDevice> open_in_device(const DevGraph& D) {
     Skeleton<InDevice> G;
@@ -515,17 +516,21 @@ __device__ void skeleton_links(const Skeleton<Where>& G, LevelShared& S, int lev
 
 struct FinishShared {
     uint32_t end[P2_MAX_LEN + 1], lim[P2_MAX_LEN + 1], at[P2_MAX_LEN + 1];       // nodes first reached by at most d instructions; how many nodes count r is kept for, and where
-    uint32_t edges, used;
+    uint32_t edges, used, targets;
 };
-constexpr int kFinishOwn = 8;                // nodes whose edges a thread keeps in registers
-constexpr uint32_t kFewEdges = 4;
+
+constexpr uint32_t kFewEdges = 4;            // edges of a thread where they are counted edge by edge
 
 // The counts of every node, from one instruction left to the size limit, by one block.  Count r of a node that `d` instructions
 // reach first is asked for up to r = max_len - d, so the lists of counts get short quickly (16 798 nodes: 7 880 counts for r =
-// 2, then 2 500, 495, 48 and 1).  They stay in LDS with the edges' targets, the first one (goals, at most 80) as bytes, and every
-// round is a walk of each node along its own edges, with no trip to memory; first for the programs whose rules all hold, short
-// of the goal, then for those that end there.
-template <int T, class Where>
+// 2, then 2 500, 495, 48 and 1).  They stay in LDS, the first one (goals, at most 80) as bytes.
+//  `few` (every graph of the launch has room for at most kFewEdges * T edges; [3 4 6] has some 1 200): a thread for every edge and
+// both kinds of count at once.  The additions to a node's count take turns, up to some forty of a cycle or two, where its walk
+// along as many edges would be a chain of LDS reads.
+//  Otherwise k_skeleton_two has left count 2, and every further round is a walk of each node along its own edges, whose targets
+// stay in LDS as well; first for the programs whose rules all hold, short of the goal, then for those that end there.
+// [2 4 8 8], six levels: 37 us and 8 of k_skeleton_two; 71 us where the block did all of it.
+template <int T, bool few, class Where>
 __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint32_t* scratch, uint32_t words) {
     const uint32_t tid = threadIdx.x;
     P2_GLOBAL GraphCounters* const ctr = G.ctr;
@@ -536,11 +541,14 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
         const uint32_t mirror = __shfl(end, M - (int)tid < 0 ? 0 : M - (int)tid, kWave), lim = tid >= 2u && tid <= (uint32_t)M ? mirror : 0u, at = wave_scan(lim);
         if (tid <= P2_MAX_LEN) { S.end[tid] = end; S.lim[tid] = lim; S.at[tid] = at - lim; }
         if (tid == P2_MAX_LEN) { S.edges = edges; S.used = 0u; }
+        if ((int)tid == (M > 2 ? M - 2 : 0)) S.targets = edges;
     }
     __syncthreads();
     const uint32_t n_nodes = S.end[P2_MAX_LEN], n_edges = S.edges, n_words = S.at[P2_MAX_LEN] + S.lim[P2_MAX_LEN];
-    const uint32_t byte_words = (n_nodes + 3u) / 4u, target_words = (n_edges + 1u) / 2u + 4u;
-    if (3u * byte_words + target_words + n_words > words || n_nodes > 0xfff0u) {
+    // (the rounds after the second follow the edges of nodes that at most max_len - 3 instructions reach)
+    const uint32_t n_targets = few ? 0u : S.targets;
+    const uint32_t byte_words = (n_nodes + 3u) / 4u, target_words = (n_targets + 1u) / 2u;
+    if (3u * byte_words + target_words + (few ? 2u : 1u) * n_words > words || n_nodes > 0xfff0u || (few && n_edges > kFewEdges * T)) {
         if (tid == 0) ctr->flags = kGraphPairs;          // (no structure that has_skeleton lets through has as many states)
         return;
     }
@@ -549,32 +557,25 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
     uint8_t* const nearest = reinterpret_cast<uint8_t*>(scratch + 2u * byte_words);    // instructions of the shortest program to the goal; 255: none
     uint16_t* const target = reinterpret_cast<uint16_t*>(scratch + 3u * byte_words);
     uint32_t* const count = scratch + 3u * byte_words + target_words;
-    uint32_t rec[kFinishOwn];
-#pragma unroll
-    for (int j = 0; j < kFinishOwn; ++j) { const uint32_t n = tid + (uint32_t)j * T; rec[j] = n < n_nodes ? G.node_edges[n] : 0u; }
     auto note = [&](uint32_t n, uint32_t r) {
         goal1[n] = (uint8_t)(r & 127u); prefix1[n] = (uint8_t)((r >> 7 & 127u) - (r & 127u)); nearest[n] = (r & 127u) != 0u ? 1 : 255;
     };
-    for (uint32_t n0 = tid + kFinishOwn * T; n0 < n_nodes; n0 += 8u * T) {
+    for (uint32_t n0 = tid; n0 < n_nodes; n0 += 8u * T) {
         uint32_t r[8];
 #pragma unroll
         for (uint32_t j = 0; j < 8u; ++j) r[j] = n0 + j * T < n_nodes ? G.node_edges[n0 + j * T] : 0u;
 #pragma unroll
         for (uint32_t j = 0; j < 8u; ++j) if (n0 + j * T < n_nodes) note(n0 + j * T, r[j]);
     }
-    for (uint32_t e0 = tid; e0 < n_edges; e0 += 8u * T) {
+    for (uint32_t e0 = tid; e0 < n_targets; e0 += 8u * T) {
         uint32_t to[8];
 #pragma unroll
-        for (uint32_t j = 0; j < 8u; ++j) to[j] = e0 + j * T < n_edges ? G.links[e0 + j * T].y : kGoalEdge;
+        for (uint32_t j = 0; j < 8u; ++j) to[j] = e0 + j * T < n_targets ? G.links[e0 + j * T].y : kGoalEdge;
 #pragma unroll
-        for (uint32_t j = 0; j < 8u; ++j) if (e0 + j * T < n_edges) target[e0 + j * T] = (uint16_t)(to[j] == kGoalEdge ? 0xffffu : to[j]);
+        for (uint32_t j = 0; j < 8u; ++j) if (e0 + j * T < n_targets) target[e0 + j * T] = (uint16_t)(to[j] == kGoalEdge ? 0xffffu : to[j]);
     }
-#pragma unroll
-    for (int j = 0; j < kFinishOwn; ++j) { const uint32_t n = tid + (uint32_t)j * T; if (n < n_nodes) note(n, rec[j]); }
     __syncthreads();
-    // (few edges: a thread for every one, and both kinds at once; the additions to a node's count take turns, up to some forty of a
-    //  cycle or two, where its walk along as many edges would be a chain of LDS reads)
-    if (n_edges <= kFewEdges * T && 3u * byte_words + target_words + 2u * n_words <= words) {
+    if constexpr (few) {
         uint32_t* const prefixes = count + n_words;
         for (uint32_t x = tid; x < 2u * n_words; x += T) count[x] = 0u;
         uint32_t from[kFewEdges], to[kFewEdges];
@@ -603,33 +604,43 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
             ctr->n_valid[tid] = tid == 1u ? (uint32_t)goal1[0] : count[S.at[tid]];
             if (tid < (uint32_t)M) ctr->n_prefixes[tid] = tid == 1u ? (uint32_t)prefix1[0] : prefixes[S.at[tid]];
         }
-    } else
-    for (int kind = 0; kind < 2; ++kind) {
+    } else for (int kind = 0; kind < 2; ++kind) {
         const uint8_t* const one = kind == 0 ? prefix1 : goal1;
-        for (int r = 2; r <= M; ++r) {
+        for (uint32_t n0 = tid; n0 < S.lim[2]; n0 += 8u * T) {
+            u32x2 c[8];
+#pragma unroll
+            for (uint32_t j = 0; j < 8u; ++j) c[j] = n0 + j * T < S.lim[2] ? G.count2[n0 + j * T] : u32x2{0u, 0u};
+#pragma unroll
+            for (uint32_t j = 0; j < 8u; ++j) {
+                const uint32_t n = n0 + j * T;
+                if (n >= S.lim[2]) continue;
+                count[n] = kind == 0 ? c[j].y : c[j].x;
+                if (kind == 1 && c[j].x != 0u && nearest[n] == 255) nearest[n] = 2;
+            }
+        }
+        __syncthreads();
+        for (int r = 3; r <= M; ++r) {
             const uint32_t lim = S.lim[r], at = S.at[r], before = S.at[r - 1];
-            auto sum = [&](uint32_t n, uint32_t own) {
+            // (the nodes of the first levels have up to forty edges: sixteen lanes to one)
+            const uint32_t lanes = r >= 4 ? 16u : 1u, own_lane = tid & (lanes - 1u);
+            for (uint32_t n = tid / lanes; n < lim; n += T / lanes) {
+                const uint32_t own = G.node_edges[n], end = (own >> 14) + (own >> 7 & 127u);
                 uint32_t s = 0u;
-                const uint32_t end = (own >> 14) + (own >> 7 & 127u);
-                for (uint32_t e = own >> 14; e < end; e += 4u) {     // (four edges in flight; there is room behind the last one)
+                for (uint32_t e = (own >> 14) + own_lane; e < end; e += 4u * lanes) {     // (four edges in flight)
                     uint32_t to[4], n_to[4];
 #pragma unroll
-                    for (uint32_t x = 0; x < 4u; ++x) to[x] = target[e + x];
+                    for (uint32_t x = 0; x < 4u; ++x) to[x] = e + x * lanes < end ? (uint32_t)target[e + x * lanes] : 0xffffu;
 #pragma unroll
-                    for (uint32_t x = 0; x < 4u; ++x) {
-                        const bool counts = e + x < end && to[x] != 0xffffu;
-                        const uint32_t c = counts ? to[x] : 0u;
-                        n_to[x] = r == 2 ? (uint32_t)one[c] : count[before + c];
-                        n_to[x] = counts ? n_to[x] : 0u;
-                    }
-                    s += n_to[0] + n_to[1] + n_to[2] + n_to[3];
+                    for (uint32_t x = 0; x < 4u; ++x) n_to[x] = count[before + (to[x] != 0xffffu ? to[x] : 0u)];
+#pragma unroll
+                    for (uint32_t x = 0; x < 4u; ++x) s += to[x] != 0xffffu ? n_to[x] : 0u;
                 }
-                count[at + n] = s;
-                if (kind == 1 && s != 0u && nearest[n] == 255) nearest[n] = (uint8_t)r;
-            };
-#pragma unroll
-            for (int j = 0; j < kFinishOwn; ++j) { const uint32_t n = tid + (uint32_t)j * T; if (n < lim) sum(n, rec[j]); }
-            for (uint32_t n = tid + kFinishOwn * T; n < lim; n += T) sum(n, G.node_edges[n]);
+                if (lanes > 1u) { s += across<0>(s); s += across<1>(s); s += across<2>(s); s += across<3>(s); }
+                if (own_lane == 0u) {
+                    count[at + n] = s;
+                    if (kind == 1 && s != 0u && nearest[n] == 255) nearest[n] = (uint8_t)r;
+                }
+            }
             __syncthreads();
         }
         if (tid >= 1u && tid <= (uint32_t)M) {
@@ -698,13 +709,39 @@ __global__ __launch_bounds__(kLevelThreads) void k_skeleton_level(const DevGraph
     if (threadIdx.x == 0 && S.flags != 0u) atomicOr(&D.ctr->flags, S.flags);
 }
 
+// The programs of two instructions from every node, to the goal and short of it, which the edges of its children are enough for: by
+// many blocks, for with four levels two thirds of the counting is this.
+__global__ __launch_bounds__(256) void k_skeleton_two(const DevGraph* __restrict__ graphs) {
+    const Skeleton<InDevice> G = open_in_device(graphs[blockIdx.y]);
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    if (G.ctr->flags != 0u) return;
+    // (count 2 is asked for where two instructions are left)
+    const u64 f = lane >= 1 && lane <= G.max_len - 2 ? G.found[lane] : 0ull;
+    const uint32_t lim = G.max_len < 2 ? 0u : 1u + (uint32_t)__builtin_amdgcn_readlane((int)wave_scan((uint32_t)f), kWave - 1);
+    for (uint32_t n = blockIdx.x * 256u + threadIdx.x; n < lim; n += gridDim.x * 256u) {
+        const uint32_t own = G.node_edges[n], end = (own >> 14) + (own >> 7 & 127u);
+        uint32_t goals = 0u, prefixes = 0u;
+        for (uint32_t e = own >> 14; e < end; e += 4u) {
+            uint32_t to[4], rec[4];
+#pragma unroll
+            for (uint32_t x = 0; x < 4u; ++x) to[x] = e + x < end ? G.links[e + x].y : kGoalEdge;
+#pragma unroll
+            for (uint32_t x = 0; x < 4u; ++x) rec[x] = to[x] != kGoalEdge ? G.node_edges[to[x]] : 0u;
+#pragma unroll
+            for (uint32_t x = 0; x < 4u; ++x) { goals += rec[x] & 127u; prefixes += (rec[x] >> 7 & 127u) - (rec[x] & 127u); }
+        }
+        G.count2[n] = u32x2{goals, prefixes};
+    }
+}
+
+template <bool few>
 __global__ __launch_bounds__(kFinishThreads) void k_skeleton_finish(const DevGraph* __restrict__ graphs, uint32_t words) {
     extern __shared__ __attribute__((aligned(16))) uint32_t scratch[];
     __shared__ FinishShared S;
     const Skeleton<InDevice> G = open_in_device(graphs[blockIdx.x]);
     const uint32_t trouble = G.ctr->flags;
     __syncthreads();                                     // (every thread has read it before the block can set it)
-    if (trouble == 0u) skeleton_finish<kFinishThreads>(G, S, scratch, words);
+    if (trouble == 0u) skeleton_finish<kFinishThreads, few>(G, S, scratch, words);
 }
 
 // Skeletons of one or two levels: a block goes through all levels and the counts by itself, with everything in LDS.  Bound by the chain
@@ -732,7 +769,7 @@ __global__ __launch_bounds__(kAloneThreads) void k_skeleton_alone(const DevGraph
         if (threadIdx.x == 0) G.ctr->flags = S.flags;
         return;
     }
-    skeleton_finish<kAloneThreads>(G, F, scratch, kAloneScratch);
+    skeleton_finish<kAloneThreads, true>(G, F, scratch, kAloneScratch);
     // (for the costs)
     if (threadIdx.x < F.end[P2_MAX_LEN]) {
         in_global<uint32_t>(D.node_edges)[threadIdx.x] = A.node_edges[threadIdx.x];
@@ -821,16 +858,23 @@ hipError_t launch_skeleton_level(const DevGraph* graphs, unsigned n, int level, 
     hipLaunchKernelGGL(k_skeleton_level, dim3(blocks + link_blocks, n), dim3(kLevelThreads), 0, stream, graphs, level, link_blocks);
     return hipGetLastError();
 }
-hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, size_t lds_bytes, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    const size_t most = 160 * 1024 - 1024;               // (beside what the block shares)
-    const size_t bytes = lds_bytes < most ? lds_bytes : most;
+static constexpr size_t kMostLds = 160 * 1024 - 1024;     // (beside what the block shares)
+template <bool few>
+static hipError_t launch_finish(const DevGraph* graphs, unsigned n, size_t bytes, hipStream_t stream) {
     if (bytes > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_skeleton_finish), hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_skeleton_finish<few>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMostLds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_skeleton_finish, dim3(n), dim3(kFinishThreads), bytes, stream, graphs, (uint32_t)(bytes / 4));
+    hipLaunchKernelGGL(k_skeleton_finish<few>, dim3(n), dim3(kFinishThreads), bytes, stream, graphs, (uint32_t)(bytes / 4));
     return hipGetLastError();
+}
+hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, uint32_t most_nodes, uint32_t most_edges, int max_len, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    // (edge by edge: for a node three bytes and two lists of counts, from two instructions)
+    const size_t few = ((size_t)most_nodes + 3) / 4 * 12 + sizeof(uint32_t) * 2 * (size_t)(max_len > 1 ? max_len - 1 : 0) * most_nodes;
+    if (most_edges <= kFewEdges * (uint32_t)kFinishThreads && few <= kMostLds) return launch_finish<true>(graphs, n, few, stream);
+    hipLaunchKernelGGL(k_skeleton_two, dim3(64, n), dim3(256), 0, stream, graphs);
+    return launch_finish<false>(graphs, n, kMostLds, stream);
 }
 
 hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, unsigned n, unsigned blocks, unsigned members, int max_levels, int with_costs,
