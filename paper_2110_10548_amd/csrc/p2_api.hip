@@ -159,6 +159,7 @@ struct Ctx {
     DevBuf rows, rows_hdr;
     DevBuf blob, valid, rerun, sorted, progs, costs, counters, topk_scratch, topk_control, topk_pos, topk_in, topk_jobs, lit_scratch, post;
     bool topk_control_clear = false;                        // the words that the blocks of a selection share are zero
+    DevBuf walks;                                           // the edges of rows that several queries share
     DevBuf sel_progs, sel_costs, gather;                    // the rows that shortlists picked, and whose they are
     HostBuf h_gather;
     DevBuf g_zero, g_mem, g_large, g_rows;                  // state-graph engine: what starts from zero, the lists, the states of large groups, whose rows are written
@@ -270,7 +271,7 @@ const std::thread::id g_loader_thread = std::this_thread::get_id();
 
 void Ctx::release() {
     DevBuf* dev[] = {&rows, &rows_hdr, &blob, &valid, &rerun, &sorted, &progs, &costs, &counters, &topk_scratch, &topk_control, &topk_pos,
-                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink, &g_zero, &g_mem, &g_large, &g_rows};
+                     &topk_in, &topk_jobs, &lit_scratch, &post, &f_rank, &f_rank_runs, &f_share, &walks, &sel_progs, &sel_costs, &gather, &f_finish, &probe_sink, &g_zero, &g_mem, &g_large, &g_rows};
     for (DevBuf* b : dev) { if (b->p) (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
     for (auto* v : {&f_evalid, &f_egsums}) {
         for (DevBuf& b : *v) if (b.p) (void)hipFree(b.p);
@@ -335,6 +336,11 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // tiles of 8192; the 11 of 83 920 programs take 32 us with 10 kept, 100 with 1024); longer lists are selected from by the
 // whole chip, one after the other (371 970 programs: 50 and 135 us).
 constexpr size_t kTopkJobMax = 1 << 18;
+// Queries of one graph from which on their rows are written once for all of them: as many as a block of k_graph_sums takes side by
+// side.  Whole calls, us, a walk per row and query / the rows once: queries of [2 4 8 8], six instructions, 83 920 rows each: 8
+// 411 / 426, 16 472 / 464, 32 603 / 535; of [4 8 8], five instructions, 2 549 rows: 16 192 / 201, 32 270 / 272, 140 737 to 753 / 706 to 750; three
+// instructions, 80 rows: 32 222 / 223.
+constexpr size_t kSharedQueries = p2::kSumMembers;
 
 // Room for the rows that shortlists may be selected from before their number is known.
 constexpr size_t kShortlistBytes = (size_t)4 << 30;
@@ -766,7 +772,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // each takes their number from the graph's counts, and the rows that are picked are written to the host by the selections:
     // one wait instead of two, and four launches fewer ([3 4 6], ten of 571: 147 us, and 118 so).
     size_t shortlist_rows = 0, shortlist_out = 0;
-    unsigned shortlist_blocks = 0;
     bool shortlists = only_graphs && n_msg > 0;
     int shortlist_k = 0;
     size_t shortlist_most = 0;
@@ -774,15 +779,37 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (!r.graph) continue;
         const size_t most = most_valid(r.plan);
         shortlists = shortlists && r.topk > 0 && most <= kTopkJobMax;
-        shortlist_rows += most; shortlist_blocks += (unsigned)((most + 255) / 256);
+        shortlist_rows += most;
         shortlist_out += (size_t)n_msg * (size_t)r.topk;
         shortlist_k = std::max(shortlist_k, r.topk);
         shortlist_most = std::max(shortlist_most, most);
     }
     shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && shortlist_rows <= kShortlistBytes / (sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1));
-    size_t off_jobs = 0, off_rows = 0;
-    size_t n_jobs = 0, n_segs = 0;
-    if (shortlists) for (const QueryRun& r : runs) if (r.graph) { n_jobs += (size_t)n_msg; ++n_segs; }
+    // Of a graph with several queries the rows are written once, and their costs worked out for all of them side by side (k_graph_sums).
+    auto shares_rows = [&](const Graph& G) {
+        return G.narrow && G.members.size() >= kSharedQueries && runs[G.leader].plan.n_ops == 5 && runs[G.leader].plan.alphabet <= (int)kSumDigits;
+    };
+    size_t off_jobs = 0, off_rows = 0, off_sums = 0, off_columns = 0;
+    size_t n_jobs = 0, n_segs = 0, n_sums = 0, n_columns = 0;
+    size_t shared_rows = 0, listed_rows = 0;             // rows of graphs that share them; those and the other queries'
+    size_t shared_costs = 0;
+    unsigned shortlist_blocks = 0, sums_blocks = 0, most_columns = 0, sum_rows = 64;
+    auto add_rows = [&](const Plan& pl) { ++n_segs; listed_rows += most_valid(pl); shortlist_blocks += (unsigned)((most_valid(pl) + 255) / 256); };
+    if (shortlists) {
+        for (const Graph& G : graphs) {
+            n_jobs += (size_t)n_msg * G.members.size();
+            if (!shares_rows(G)) continue;
+            ++n_sums; n_columns += G.members.size();
+            add_rows(runs[G.leader].plan);
+            shared_costs += most_valid(runs[G.leader].plan) * G.members.size();
+            most_columns = std::max(most_columns, (unsigned)G.members.size());
+        }
+        shared_rows = listed_rows;
+        // (a block sets up tables of its queries first: 64 rows each while the chip is not full, and 512 otherwise)
+        if (shared_rows / 64 * ((most_columns + kSumMembers - 1) / kSumMembers) > 1024) sum_rows = 512;
+        for (const Graph& G : graphs) if (shares_rows(G)) sums_blocks += (unsigned)((most_valid(runs[G.leader].plan) + sum_rows - 1) / sum_rows);
+        for (const QueryRun& r : runs) if (r.graph && !shares_rows(graphs[r.graph_id])) add_rows(r.plan);
+    }
     auto leave_graph = [&](const Graph& G) { for (int32_t i : G.members) left[i] = 1; };
     // Validity depends on the reduction group, the chunks, the patterns and the alphabet only (not on the
     // links, nor on where the placement puts the group in the system): a query that equals an earlier one of
@@ -978,6 +1005,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     if (shortlists) {
         off_jobs = off; off += align_up(sizeof(DevTopkJob) * n_jobs, 256);
         off_rows = off; off += align_up(sizeof(GraphRows) * n_segs, 256);
+        off_sums = off; off += align_up(sizeof(GraphSums) * n_sums, 256);
+        off_columns = off; off += align_up(sizeof(GraphColumn) * n_columns, 256);
     }
     const size_t off_msg = off;
     off += align_up(sizeof(double) * (size_t)std::max(n_msg, 1), 256);
@@ -1498,25 +1527,49 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             if (!glarge.empty()) std::memcpy(hb + off_glarge, glarge.data(), sizeof(uint32_t) * glarge.size());
         }
         if (shortlists) {
-            P2_HIP(C.sorted.ensure(sizeof(unsigned long long) * shortlist_rows));
-            P2_HIP(C.progs.ensure(sizeof(p2_program) * shortlist_rows));
-            P2_HIP(C.costs.ensure(sizeof(double) * shortlist_rows * (size_t)n_msg));
+            // (rows: the shared ones, the other queries' own; costs: behind those, the columns of the queries that share)
+            P2_HIP(C.sorted.ensure(sizeof(unsigned long long) * listed_rows));
+            P2_HIP(C.progs.ensure(sizeof(p2_program) * listed_rows));
+            P2_HIP(C.walks.ensure(2 * sizeof(uint4) * shared_rows));
+            P2_HIP(C.costs.ensure(sizeof(double) * (listed_rows + shared_costs) * (size_t)n_msg));
             P2_HIP(C.topk_pos.ensure(sizeof(long long) * shortlist_out));
             P2_HIP(C.h_progs.ensure(sizeof(p2_program) * shortlist_out));
             P2_HIP(C.h_costs.ensure(sizeof(double) * shortlist_out * (size_t)n_msg));
-            DevTopkJob* J = reinterpret_cast<DevTopkJob*>(hb + off_jobs);
             GraphRows* seg = reinterpret_cast<GraphRows*>(hb + off_rows);
-            size_t first = 0, out = 0;
-            uint32_t block = 0;
+            GraphSums* sum = reinterpret_cast<GraphSums*>(hb + off_sums);
+            GraphColumn* const columns = reinterpret_cast<GraphColumn*>(hb + off_columns);
+            size_t first = 0, out = 0, own_costs = listed_rows;
+            uint32_t block = 0, sum_block = 0, column = 0;
+            std::vector<std::pair<size_t, uint32_t>> shared(graphs.size(), {0, 0u});     // a graph's rows, and its first column
+            auto queue_rows = [&](const QueryRun& r, int i, uint32_t member) {
+                const size_t most = most_valid(r.plan);
+                *seg++ = GraphRows{block, (uint32_t)i, (uint32_t)r.graph_id, member, (uint32_t)most, fused_sums(r), (unsigned long long)first};
+                block += (uint32_t)((most + 255) / 256);
+                first += most;
+                return first - most;
+            };
+            for (size_t g = 0; g < graphs.size(); ++g) {
+                const Graph& G = graphs[g];
+                if (!shares_rows(G)) continue;
+                const size_t most = most_valid(runs[G.leader].plan), at = queue_rows(runs[G.leader], G.leader, ~0u);
+                *sum++ = GraphSums{sum_block, (uint32_t)g, (uint32_t)most, (uint32_t)G.members.size(), column, fused_sums(runs[G.leader]), (unsigned long long)at};
+                shared[g] = {at, column};
+                sum_block += (uint32_t)((most + sum_rows - 1) / sum_rows); column += (uint32_t)G.members.size();
+            }
+            DevTopkJob* J = reinterpret_cast<DevTopkJob*>(hb + off_jobs);
             for (int i = 0; i < n_queries; ++i) {
                 const QueryRun& r = runs[i];
                 if (!r.graph) continue;
                 const size_t most = most_valid(r.plan);
-                *seg++ = GraphRows{block, (uint32_t)i, (uint32_t)r.graph_id, (uint32_t)r.graph_pos, (uint32_t)most, fused_sums(r), (unsigned long long)first};
-                block += (uint32_t)((most + 255) / 256);
+                size_t rows, costs_at;
+                if (shares_rows(graphs[r.graph_id])) {
+                    rows = shared[r.graph_id].first; costs_at = own_costs;
+                    columns[shared[r.graph_id].second + (uint32_t)r.graph_pos] = GraphColumn{(unsigned long long)costs_at, (uint32_t)i, 0u};
+                    own_costs += most;
+                } else rows = costs_at = queue_rows(r, i, (uint32_t)r.graph_pos);
                 for (int m = 0; m < n_msg; ++m, ++J) {
-                    J->costs = static_cast<double*>(C.costs.p) + first * (size_t)n_msg;
-                    J->cost = J->costs + m; J->index = static_cast<unsigned long long*>(C.sorted.p) + first; J->progs = static_cast<p2_program*>(C.progs.p) + first;
+                    J->costs = static_cast<double*>(C.costs.p) + costs_at * (size_t)n_msg;
+                    J->cost = J->costs + m; J->index = static_cast<unsigned long long*>(C.sorted.p) + rows; J->progs = static_cast<p2_program*>(C.progs.p) + rows;
                     J->nan_flag = reinterpret_cast<uint32_t*>(static_cast<char*>(C.g_zero.p) + graph_nan) + i;
                     J->n = (long long)most; J->stride = n_msg; J->k = r.topk; J->n_cost = n_msg;
                     J->n_from = &reinterpret_cast<const GraphCounters*>(C.g_zero.p)[r.graph_id].n_total;
@@ -1524,7 +1577,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                     J->out_progs = static_cast<p2_program*>(C.h_progs.p) + out; J->out_costs = static_cast<double*>(C.h_costs.p) + out * (size_t)n_msg;
                     out += (size_t)r.topk;
                 }
-                first += most;
             }
         }
         if (only_graphs) {
@@ -1664,16 +1716,19 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         }
         if (shortlists) {
             P2_HIP(launch_graph_emit(dqs, dgs, nullptr, nullptr, 0, reinterpret_cast<const GraphRows*>(db + off_rows), (int)n_segs, shortlist_blocks,
-                                     shortlist_rows, static_cast<unsigned long long*>(C.sorted.p), static_cast<p2_program*>(C.progs.p),
-                                     static_cast<double*>(C.costs.p), nullptr, 0, stream));
+                                     listed_rows, static_cast<unsigned long long*>(C.sorted.p), static_cast<p2_program*>(C.progs.p),
+                                     static_cast<double*>(C.costs.p), nullptr, 0, C.walks.p, stream));
+            if (sums_blocks > 0)
+                P2_HIP(launch_graph_sums(dqs, dgs, reinterpret_cast<const GraphSums*>(db + off_sums), (int)n_sums, reinterpret_cast<const GraphColumn*>(db + off_columns),
+                                         sums_blocks, most_columns, sum_rows, C.walks.p, static_cast<double*>(C.costs.p), stream));
             P2_HIP(launch_topk_jobs(reinterpret_cast<const DevTopkJob*>(db + off_jobs), (unsigned)n_jobs, shortlist_k, (long long)shortlist_most, stream));
-            if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = 2; }
+            if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = sums_blocks > 0 ? 3 : 2; }
             const CopyPart back[1] = {{C.h_gctr.p, C.g_zero.p, graph_back}};
             P2_HIP(launch_copies(back, 1, stream));
         } else if (direct) {
             P2_HIP(launch_graph_emit(dqs, dgs, static_cast<const GraphCounters*>(C.g_zero.p), reinterpret_cast<const GraphQuery*>(db + off_gasked),
                                      n_queries, nullptr, 0, (unsigned)emit_blocks + 1u, rows_room, nullptr, static_cast<p2_program*>(C.h_progs.p),
-                                     static_cast<double*>(C.h_costs.p), C.h_gctr.p, (int)graphs.size(), stream));
+                                     static_cast<double*>(C.h_costs.p), C.h_gctr.p, (int)graphs.size(), nullptr, stream));
             if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = 2; }
         } else {
             const CopyPart back[2] = {{C.h_counters.p, C.counters.p, n_others > 0 ? sizeof(DevCounters) * (size_t)n_queries : 0},
@@ -2364,7 +2419,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         ++post_launches;
         P2_HIP(launch_graph_emit(reinterpret_cast<const DevQuery*>(db), reinterpret_cast<const DevGraph*>(db + off_graphs),
                                  static_cast<const GraphCounters*>(C.g_zero.p), reinterpret_cast<const GraphQuery*>(db + off_gasked), n_queries,
-                                 nullptr, 0, (unsigned)blocks, total_valid, sorted_base, progs_base, costs_base, nullptr, 0, stream));
+                                 nullptr, 0, (unsigned)blocks, total_valid, sorted_base, progs_base, costs_base, nullptr, 0, nullptr, stream));
     }
     if (!graph_rows_of.empty()) {
         const size_t bytes = sizeof(GraphRows) * graph_rows_of.size();
@@ -2375,7 +2430,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         ++post_launches;
         P2_HIP(launch_graph_emit(reinterpret_cast<const DevQuery*>(db), reinterpret_cast<const DevGraph*>(db + off_graphs),
                                  nullptr, nullptr, 0, static_cast<const GraphRows*>(C.g_rows.p), (int)graph_rows_of.size(), graph_row_blocks,
-                                 total_valid, sorted_base, progs_base, costs_base, nullptr, 0, stream));
+                                 total_valid, sorted_base, progs_base, costs_base, nullptr, 0, nullptr, stream));
     }
     // frontier enumerations: the place of every program in ascending index order, once per enumeration; then
     // every query of the enumeration writes its rows (programs, and costs from its own sums)

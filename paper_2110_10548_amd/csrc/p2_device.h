@@ -500,9 +500,13 @@ struct DevGraph {
 };
 struct GraphBlock { uint32_t graph, index, count, pad; };                 // block `index` of the `count` that work on the graph
 struct GraphRows {                 // rows of one query, at most count: blocks [first_block, next segment's first_block), 256 rows each
-    uint32_t first_block, query, graph, member, count, fused;
+    uint32_t first_block, query, graph, member, count, fused;      // (member ~0: no costs, but the edges of every row, for launch_graph_sums)
     unsigned long long out_first;
 };
+// The costs of one graph's rows for all of its queries: rows_of_block rows a block, from the edges of row first_row on.
+struct GraphSums { uint32_t first_block, graph, most, n_columns, first_column, fused; unsigned long long first_row; };
+struct GraphColumn { unsigned long long out_first; uint32_t query, pad; };       // (of the graph's members, in their order)
+constexpr unsigned kSumDigits = 80, kSumMembers = 32;
 // Structures of few states (graph_alone_holds; list: numbers of graphs), a block each: levels, counts and edges in one launch.
 bool graph_alone_holds(uint32_t nodes);
 // Planes that the wavefronts of the launches per level may reserve and not use.
@@ -512,7 +516,7 @@ hipError_t launch_graph_alone(const DevGraph* graphs, const uint32_t* list, unsi
 hipError_t launch_graph_level(const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, int level, int max_len, hipStream_t stream);
 hipError_t launch_graph_finish(const DevGraph* graphs, const uint32_t* list, unsigned n, size_t lds_bytes, hipStream_t stream);
 // Skeletons of up to four levels, the n that begin at `graphs`: of at most two, a block each; the others a launch per level (blocks for
-// its states, and for the edges that led to them), then one for the counts and the edges (lds_bytes: for the counts of the largest).
+// its states, and for the edges that led to them), then those of the counts.
 constexpr int kNarrowLevels = 4;
 int skeleton_state_words(int levels);
 hipError_t launch_skeleton_alone(const DevGraph* graphs, unsigned n, hipStream_t stream);
@@ -532,7 +536,9 @@ hipError_t launch_graph_steps(const DevQuery* queries, const DevGraph* graphs, c
 struct GraphQuery { uint32_t graph, member, fused, pad; };           // graph ~0: a query without candidates; fused: how a program's step costs are added up (see k_graph_emit)
 hipError_t launch_graph_emit(const DevQuery* queries, const DevGraph* graphs, const GraphCounters* ctrs, const GraphQuery* asked, int n_queries,
                              const GraphRows* segs, int n_segs, unsigned n_blocks, unsigned long long cap_rows, unsigned long long* sorted,
-                             p2_program* progs, double* costs, void* ctrs_out, int n_graphs, hipStream_t stream);
+                             p2_program* progs, double* costs, void* ctrs_out, int n_graphs, void* walks, hipStream_t stream);
+hipError_t launch_graph_sums(const DevQuery* queries, const DevGraph* graphs, const GraphSums* sums, int n_sums, const GraphColumn* columns,
+                             unsigned n_blocks, unsigned most_columns, unsigned rows_of_block, const void* walks, double* costs, hipStream_t stream);
 // One selection of launch_topk_jobs: the k best of (cost[i * stride], index[i]), i < n, ties by index;
 // positions go to out_pos[min(k, n)], nan_flag is set to 1 when a cost is NaN.  All device pointers.
 struct DevTopkJob {

@@ -953,7 +953,8 @@ __device__ __forceinline__ double add_rounded(double a, double b, double c) {
 __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
                                                     const GraphCounters* __restrict__ ctrs, const GraphQuery* __restrict__ asked, int n_queries,
                                                     const GraphRows* __restrict__ segs, int n_segs, u64 cap_rows, u64* __restrict__ sorted,
-                                                    p2_program* __restrict__ progs, double* __restrict__ costs, uint4* __restrict__ ctrs_out, int n_graphs) {
+                                                    p2_program* __restrict__ progs, double* __restrict__ costs, uint4* __restrict__ ctrs_out, int n_graphs,
+                                                    u32x4* __restrict__ walks) {
     __shared__ u64 wave_sums[256 / kWave];
     __shared__ uint32_t s_query, s_graph, s_member, s_block, s_count, s_fused;
     __shared__ u64 s_first;
@@ -1006,13 +1007,14 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
     if (row0 + rows > cap_rows) return;                   // (the host sees that there are more, and asks again with room)
     const Graph<InDevice> G = open_in_device(graphs[s_graph]);
     const DevQuery& q = queries[s_query];
+    const bool with_costs = q.n_msg > 0 && s_member != ~0u;
     // (worked out once per block: with two divisions a step in every row, the kernel took 900 us for 8.2 million rows of
     //  four levels, and takes 780)
     for (uint32_t d = tid; d < (uint32_t)q.alphabet; d += 256u) {
         const uint32_t ins = q.instr_of_digit[d];
         const int pid = (int)(ins >> 3), op = (int)(ins & 7u);
         s_instr[d] = (uint8_t)(pid * 5 + op);
-        if (q.n_msg > 0) {
+        if (with_costs) {
             const DevPattern& P = q.pat[pid];
             double ring_steps, mult;
             step_factors(op, P.g, q.algo, ring_steps, mult);
@@ -1033,10 +1035,12 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
         pr.len = (uint8_t)len;
         u64 number = 0ull;
         double sum_alpha = 0.0, sum_beta = 0.0;
-        uint32_t node = 0u;
+        uint32_t node = 0u, walk[8];
+        walk[7] = ~0u;
 #pragma unroll
         for (int s = 0; s < P2_MAX_LEN; ++s) {
             pr.instr[s] = 0;
+            walk[s] = ~0u;
             if (s >= len) continue;
             const int left = len - s;                     // instructions from here on
             // (four edges' counts in flight: edge after edge, each count a load behind its edge's, the walks were the whole of
@@ -1067,7 +1071,8 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
             pr.instr[s] = s_instr[digit];
             number = number * (u64)q.alphabet + digit;
             node = left > 1 && e < end ? edge & kGoalEdge : node;
-            if (q.n_msg > 0 && e < end) {
+            if (e < end) walk[s] = digit << kDigitShift | e;
+            if (with_costs && e < end) {
                 const double ring_steps = s_steps[digit], alpha = s_alpha[digit], per = s_per[digit], best = G.best[(size_t)e * G.n_members + member];
                 // (rounded as in the engines whose place this one takes: the walk's costs are fused, the frontier's steps are not)
                 if (s_fused != 0u) { sum_alpha = fma(ring_steps, alpha, sum_alpha); sum_beta = fma(per, best, sum_beta); }
@@ -1078,12 +1083,105 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
         if (sorted) sorted[row0 + tid] = pr.index;
         progs[row0 + tid] = pr;
         s_sum[0][tid] = sum_alpha; s_sum[1][tid] = sum_beta;
+        if (member == ~0u) {
+            walks[(row0 + tid) * 2] = u32x4{walk[0], walk[1], walk[2], walk[3]};
+            walks[(row0 + tid) * 2 + 1] = u32x4{walk[4], walk[5], walk[6], walk[7]};
+        }
     }
+    if (!with_costs) return;
     __syncthreads();
     const uint32_t n_msg = (uint32_t)q.n_msg;
     for (uint32_t x = tid; x < rows * n_msg; x += 256u) {
         const uint32_t r = x / n_msg, m = x - r * n_msg;
         costs[row0 * n_msg + x] = fma(q.msg_bytes[m], s_sum[1][r], s_sum[0][r]);
+    }
+}
+
+// The costs of a graph's rows for every query that shares it, where the rows themselves have been written once (k_graph_emit, member
+// ~0, with the edges of each).  Half a wavefront holds 32 queries of one row, so that what an edge adds is read in runs of 256
+// bytes; what a step costs each query lies in LDS; 64 rows at a time are turned round there, so that the costs leave in runs of 512
+// bytes.  With a walk per row and query, lanes on rows, the gathers along the edges were the whole cost: 512 queries of [2 4 8 8],
+// 8.2 million rows, 690 us, and 125 so with 27 for the rows.
+constexpr int kSumThreads = 512, kSumTile = 64;
+__global__ __launch_bounds__(kSumThreads) void k_graph_sums(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
+                                                            const GraphSums* __restrict__ sums, int n_sums, const GraphColumn* __restrict__ columns,
+                                                            const u32x4* __restrict__ walks, double* __restrict__ costs, uint32_t rows_of_block) {
+    constexpr uint32_t C = kSumMembers, kTeams = kSumThreads / C, kOwn = kSumTile / kTeams;
+    __shared__ double s_steps[kSumDigits][C], s_per[kSumDigits][C], s_alpha[kSumDigits / 5][C], s_tile[kSumTile][C + 1];
+    __shared__ u64 s_out[C];
+    int a = 0, z = n_sums - 1;
+    while (a < z) {
+        const int mid = (a + z + 1) >> 1;
+        if (sums[mid].first_block <= blockIdx.x) a = mid; else z = mid - 1;
+    }
+    const GraphSums J = sums[a];
+    const DevGraph& D = graphs[J.graph];
+    const uint32_t n_total = D.ctr->n_total, n_rows = n_total < J.most ? n_total : J.most, c0 = blockIdx.y * C;
+    const uint32_t begin = (blockIdx.x - J.first_block) * rows_of_block, end = begin + rows_of_block < n_rows ? begin + rows_of_block : n_rows;
+    if (c0 >= J.n_columns || begin >= n_rows) return;
+    const uint32_t tid = threadIdx.x, col = tid % C, team = tid / C, n_cols = J.n_columns - c0 < C ? J.n_columns - c0 : C;
+    // (the lanes behind the last query do its work again, and leave nothing)
+    const uint32_t member = c0 + (col < n_cols ? col : n_cols - 1u);
+    const GraphColumn own = columns[J.first_column + member];
+    const DevQuery& q = queries[own.query];
+    for (uint32_t pid = team; pid < (uint32_t)q.n_patterns; pid += kTeams) {
+        const DevPattern& P = q.pat[pid];
+        const int g = P.g;
+        s_alpha[pid][col] = q.alpha[P.span_level];
+        for (uint32_t op = 0; op < 5u; ++op) {           // (skeletons have all five operations)
+            double ring_steps, mult;
+            step_factors((int)q.ops[op], g, q.algo, ring_steps, mult);
+            s_steps[pid * 5u + op][col] = ring_steps; s_per[pid * 5u + op][col] = mult / (double)q.k;
+        }
+    }
+    if (team == 0u) s_out[col] = own.out_first;
+    __syncthreads();
+    const P2_GLOBAL double* const best = in_global<const double>(D.best);
+    const uint32_t n_members = (uint32_t)D.n_members, n_msg = (uint32_t)q.n_msg;
+    const double* const msg_bytes = q.msg_bytes;
+    const int max_len = D.max_len;
+    const bool fused = J.fused != 0u;
+    for (uint32_t row0 = begin; row0 < end; row0 += kSumTile) {
+        double sum_alpha[kOwn], sum_beta[kOwn];
+        u32x4 walk[kOwn][2];
+#pragma unroll
+        for (uint32_t x = 0; x < kOwn; ++x) {
+            const uint32_t row = row0 + team + x * kTeams;
+            const u32x4* const at = walks + (J.first_row + (row < end ? row : end - 1u)) * 2u;
+            walk[x][0] = at[0]; walk[x][1] = at[1];
+            sum_alpha[x] = sum_beta[x] = 0.0;
+        }
+#pragma unroll
+        for (int s = 0; s < P2_MAX_LEN; ++s) {
+            if (s >= max_len) break;
+            double b[kOwn];
+#pragma unroll
+            for (uint32_t x = 0; x < kOwn; ++x) {
+                const uint32_t step = walk[x][s / 4][s % 4];
+                b[x] = best[(size_t)(step != ~0u ? step & ((1u << kDigitShift) - 1u) : 0u) * n_members + member];
+            }
+#pragma unroll
+            for (uint32_t x = 0; x < kOwn; ++x) {
+                const uint32_t step = walk[x][s / 4][s % 4], digit = step != ~0u ? step >> kDigitShift : 0u;
+                const double ring_steps = s_steps[digit][col], alpha = s_alpha[digit / 5u][col], per = s_per[digit][col];
+                // (rounded as k_graph_emit rounds)
+                double next_alpha, next_beta;
+                if (fused) { next_alpha = fma(ring_steps, alpha, sum_alpha[x]); next_beta = fma(per, b[x], sum_beta[x]); }
+                else { next_alpha = add_rounded(sum_alpha[x], ring_steps, alpha); next_beta = add_rounded(sum_beta[x], per, b[x]); }
+                if (step != ~0u) { sum_alpha[x] = next_alpha; sum_beta[x] = next_beta; }
+            }
+        }
+        for (uint32_t m = 0; m < n_msg; ++m) {
+            const double bytes = msg_bytes[m];
+#pragma unroll
+            for (uint32_t x = 0; x < kOwn; ++x) s_tile[team + x * kTeams][col] = fma(bytes, sum_beta[x], sum_alpha[x]);
+            __syncthreads();
+            for (uint32_t x = tid; x < n_cols * kSumTile; x += kSumThreads) {
+                const uint32_t c = x / kSumTile, r = x % kSumTile;
+                if (row0 + r < end) costs[(s_out[c] + row0 + r) * n_msg + m] = s_tile[r][c];
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -1131,11 +1229,18 @@ hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, c
 }
 hipError_t launch_graph_emit(const DevQuery* queries, const DevGraph* graphs, const GraphCounters* ctrs, const GraphQuery* asked, int n_queries,
                              const GraphRows* segs, int n_segs, unsigned n_blocks, unsigned long long cap_rows, unsigned long long* sorted,
-                             p2_program* progs, double* costs, void* ctrs_out, int n_graphs, hipStream_t stream) {
+                             p2_program* progs, double* costs, void* ctrs_out, int n_graphs, void* walks, hipStream_t stream) {
     if (n_blocks == 0) return hipSuccess;
     static_assert(sizeof(GraphCounters) % 16 == 0, "copied in 16-byte words");
     hipLaunchKernelGGL(k_graph_emit, dim3(n_blocks), dim3(256), 0, stream, queries, graphs, ctrs, asked, n_queries, segs, n_segs, cap_rows, sorted,
-                       progs, costs, static_cast<uint4*>(ctrs_out), n_graphs);
+                       progs, costs, static_cast<uint4*>(ctrs_out), n_graphs, static_cast<u32x4*>(walks));
+    return hipGetLastError();
+}
+hipError_t launch_graph_sums(const DevQuery* queries, const DevGraph* graphs, const GraphSums* sums, int n_sums, const GraphColumn* columns,
+                             unsigned n_blocks, unsigned most_columns, unsigned rows_of_block, const void* walks, double* costs, hipStream_t stream) {
+    if (n_blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_graph_sums, dim3(n_blocks, (most_columns + kSumMembers - 1) / kSumMembers), dim3(kSumThreads), 0, stream, queries, graphs, sums, n_sums,
+                       columns, static_cast<const u32x4*>(walks), costs, rows_of_block);
     return hipGetLastError();
 }
 

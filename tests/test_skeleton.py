@@ -132,3 +132,23 @@ def test_shortlists_selected_before_the_count(queries):
             for m in range(len(msg)):
                 best = np.lexsort((full["programs"]["index"], full["cost"][:, m]))[:kk]
                 assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], full["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], full["cost"][best])
+
+
+# rows of one graph written once for its queries, 32 to a block: two blocks and three, costs fused and not; beside queries with rows of their own
+@pytest.mark.gpu
+@pytest.mark.parametrize("large,n", [(False, 33), (True, 65)])
+def test_rows_written_once_for_many_queries(large, n):
+    from paper_2110_10548_amd import binding as B
+    rng = random.Random(n)
+    cards = [c for c in ([a, b, c, d] for a in (2, 3, 4) for b in (2, 4, 5) for c in (2, 3, 8) for d in (2, 4, 6, 8)) if (300 if large else 16) <= np.prod(c) <= (512 if large else 64)]
+    queries = [_query(rng.choice(cards), 6, i, topk=rng.choice((1, 7, 40)), algo=i % 2) for i in range(n)]
+    queries += [_query([3, 4, 6], 4, 99, topk=5), _query([2, 2], 5, 98, topk=5)]
+    rng.shuffle(queries)
+    for msg in (MSG[:1], MSG + [7.0]):
+        full = B.p2_synthesize_batch([dict(q, topk=0) for q in queries], msg)
+        for q, f, r in zip(queries, full, B.p2_synthesize_batch(queries, msg)):
+            kk = q["topk"]
+            assert r["stats"]["valid"] == len(f["programs"]) and len(r["programs"]) == kk * len(msg)
+            for m in range(len(msg)):
+                best = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:kk]
+                assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], f["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], f["cost"][best])
