@@ -955,6 +955,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
                                                     const GraphRows* __restrict__ segs, int n_segs, u64 cap_rows, u64* __restrict__ sorted,
                                                     p2_program* __restrict__ progs, double* __restrict__ costs, uint4* __restrict__ ctrs_out, int n_graphs,
                                                     u32x4* __restrict__ walks) {
+    constexpr uint32_t kAhead = 8u;
     __shared__ u64 wave_sums[256 / kWave];
     __shared__ uint32_t s_query, s_graph, s_member, s_block, s_count, s_fused;
     __shared__ u64 s_first;
@@ -1043,26 +1044,27 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
             walk[s] = ~0u;
             if (s >= len) continue;
             const int left = len - s;                     // instructions from here on
-            // (four edges' counts in flight: edge after edge, each count a load behind its edge's, the walks were the whole of
-            //  the kernel: 8.2 million rows of four levels 1 050 us, and 900 so)
+            // (eight edges' counts in flight: edge after edge, each count a load behind its edge's, the walks were the whole of
+            //  the kernel.  571 rows of three levels and 83 920 of four, us: four edges 15.5 and 27.3, eight 13.8 and 22.9, sixteen
+            //  14.7 and 23.2)
             const u32x2 own = G.first_edge[node];
             uint32_t e = own.x, edge = 0u;
             const uint32_t end = own.y;
             for (bool found = false; !found && e < end;) {
-                uint32_t four[4], n[4];
+                uint32_t some[kAhead], n[kAhead];
 #pragma unroll
-                for (uint32_t u = 0; u < 4u; ++u) four[u] = G.edges[e + u < end ? e + u : end - 1u];
+                for (uint32_t u = 0; u < kAhead; ++u) some[u] = G.edges[e + u < end ? e + u : end - 1u];
 #pragma unroll
-                for (uint32_t u = 0; u < 4u; ++u) {
-                    const uint32_t target = four[u] & kGoalEdge;
+                for (uint32_t u = 0; u < kAhead; ++u) {
+                    const uint32_t target = some[u] & kGoalEdge;
                     const uint32_t ends = G.use_ends[(size_t)(target == kGoalEdge ? 0u : target) * 8 + (left > 1 ? left - 1 : 0)];
                     n[u] = e + u >= end ? 0u : target == kGoalEdge ? (left == 1 ? 1u : 0u) : left > 1 ? ends : 0u;
                 }
-                uint32_t at = e + 4u < end ? e + 4u : end;
+                uint32_t at = e + kAhead < end ? e + kAhead : end;
 #pragma unroll
-                for (uint32_t u = 0; u < 4u; ++u) {
+                for (uint32_t u = 0; u < kAhead; ++u) {
                     if (found) continue;
-                    if (j < n[u]) { found = true; edge = four[u]; at = e + u; }
+                    if (j < n[u]) { found = true; edge = some[u]; at = e + u; }
                     else j -= n[u];
                 }
                 e = at;
@@ -1101,7 +1103,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
 // ~0, with the edges of each).  Half a wavefront holds 32 queries of one row, so that what an edge adds is read in runs of 256
 // bytes; what a step costs each query lies in LDS; 64 rows at a time are turned round there, so that the costs leave in runs of 512
 // bytes.  With a walk per row and query, lanes on rows, the gathers along the edges were the whole cost: 512 queries of [2 4 8 8],
-// 8.2 million rows, 690 us, and 125 so with 27 for the rows.
+// 8.2 million rows, 690 us, and 125 so with 23 for the rows.
 constexpr int kSumThreads = 512, kSumTile = 64;
 __global__ __launch_bounds__(kSumThreads) void k_graph_sums(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
                                                             const GraphSums* __restrict__ sums, int n_sums, const GraphColumn* __restrict__ columns,
