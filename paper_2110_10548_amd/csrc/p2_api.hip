@@ -1526,15 +1526,19 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             if (!gsmall.empty()) std::memcpy(hb + off_gsmall, gsmall.data(), sizeof(uint32_t) * gsmall.size());
             if (!glarge.empty()) std::memcpy(hb + off_glarge, glarge.data(), sizeof(uint32_t) * glarge.size());
         }
+        // (rows: the shared ones, the other queries' own; costs: behind those, the columns of the queries that share.  Without the room,
+        //  the programs are counted first, as for other lists: there may be fewer)
+        if (shortlists && (C.sorted.ensure(sizeof(unsigned long long) * listed_rows) != hipSuccess ||
+                           C.progs.ensure(sizeof(p2_program) * listed_rows) != hipSuccess ||
+                           C.walks.ensure(2 * sizeof(uint4) * shared_rows) != hipSuccess ||
+                           C.costs.ensure(sizeof(double) * (listed_rows + shared_costs) * (size_t)n_msg) != hipSuccess ||
+                           C.topk_pos.ensure(sizeof(long long) * shortlist_out) != hipSuccess ||
+                           C.h_progs.ensure(sizeof(p2_program) * shortlist_out) != hipSuccess ||
+                           C.h_costs.ensure(sizeof(double) * shortlist_out * (size_t)n_msg) != hipSuccess)) {
+            (void)hipGetLastError();
+            shortlists = false;
+        }
         if (shortlists) {
-            // (rows: the shared ones, the other queries' own; costs: behind those, the columns of the queries that share)
-            P2_HIP(C.sorted.ensure(sizeof(unsigned long long) * listed_rows));
-            P2_HIP(C.progs.ensure(sizeof(p2_program) * listed_rows));
-            P2_HIP(C.walks.ensure(2 * sizeof(uint4) * shared_rows));
-            P2_HIP(C.costs.ensure(sizeof(double) * (listed_rows + shared_costs) * (size_t)n_msg));
-            P2_HIP(C.topk_pos.ensure(sizeof(long long) * shortlist_out));
-            P2_HIP(C.h_progs.ensure(sizeof(p2_program) * shortlist_out));
-            P2_HIP(C.h_costs.ensure(sizeof(double) * shortlist_out * (size_t)n_msg));
             GraphRows* seg = reinterpret_cast<GraphRows*>(hb + off_rows);
             GraphSums* sum = reinterpret_cast<GraphSums*>(hb + off_sums);
             GraphColumn* const columns = reinterpret_cast<GraphColumn*>(hb + off_columns);
