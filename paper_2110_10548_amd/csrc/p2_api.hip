@@ -1534,7 +1534,8 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                            C.costs.ensure(sizeof(double) * (listed_rows + shared_costs) * (size_t)n_msg) != hipSuccess ||
                            C.topk_pos.ensure(sizeof(long long) * shortlist_out) != hipSuccess ||
                            C.h_progs.ensure(sizeof(p2_program) * shortlist_out) != hipSuccess ||
-                           C.h_costs.ensure(sizeof(double) * shortlist_out * (size_t)n_msg) != hipSuccess)) {
+                           C.h_costs.ensure(sizeof(double) * shortlist_out * (size_t)n_msg) != hipSuccess ||
+                           C.h_pos.ensure(sizeof(uint32_t) * n_jobs) != hipSuccess)) {
             (void)hipGetLastError();
             shortlists = false;
         }
@@ -1561,6 +1562,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 sum_block += (uint32_t)((most + sum_rows - 1) / sum_rows); column += (uint32_t)G.members.size();
             }
             DevTopkJob* J = reinterpret_cast<DevTopkJob*>(hb + off_jobs);
+            uint32_t* own_flag = static_cast<uint32_t*>(C.h_pos.p);
             for (int i = 0; i < n_queries; ++i) {
                 const QueryRun& r = runs[i];
                 if (!r.graph) continue;
@@ -1574,7 +1576,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 for (int m = 0; m < n_msg; ++m, ++J) {
                     J->costs = static_cast<double*>(C.costs.p) + costs_at * (size_t)n_msg;
                     J->cost = J->costs + m; J->index = static_cast<unsigned long long*>(C.sorted.p) + rows; J->progs = static_cast<p2_program*>(C.progs.p) + rows;
-                    J->nan_flag = reinterpret_cast<uint32_t*>(static_cast<char*>(C.g_zero.p) + graph_nan) + i;
+                    J->nan_flag = nullptr; J->own_flag = own_flag++;
                     J->n = (long long)most; J->stride = n_msg; J->k = r.topk; J->n_cost = n_msg;
                     J->n_from = &reinterpret_cast<const GraphCounters*>(C.g_zero.p)[r.graph_id].n_total;
                     J->out_pos = static_cast<long long*>(C.topk_pos.p) + out;
@@ -1719,16 +1721,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             direct = false;
         }
         if (shortlists) {
-            P2_HIP(launch_graph_emit(dqs, dgs, nullptr, nullptr, 0, reinterpret_cast<const GraphRows*>(db + off_rows), (int)n_segs, shortlist_blocks,
-                                     listed_rows, static_cast<unsigned long long*>(C.sorted.p), static_cast<p2_program*>(C.progs.p),
-                                     static_cast<double*>(C.costs.p), nullptr, 0, C.walks.p, stream));
+            // (the last block hands the counts to the host)
+            P2_HIP(launch_graph_emit(dqs, dgs, static_cast<const GraphCounters*>(C.g_zero.p), nullptr, 0, reinterpret_cast<const GraphRows*>(db + off_rows), (int)n_segs,
+                                     shortlist_blocks + 1u, listed_rows, static_cast<unsigned long long*>(C.sorted.p), static_cast<p2_program*>(C.progs.p),
+                                     static_cast<double*>(C.costs.p), C.h_gctr.p, (int)graphs.size(), C.walks.p, stream));
             if (sums_blocks > 0)
                 P2_HIP(launch_graph_sums(dqs, dgs, reinterpret_cast<const GraphSums*>(db + off_sums), (int)n_sums, reinterpret_cast<const GraphColumn*>(db + off_columns),
                                          sums_blocks, most_columns, sum_rows, C.walks.p, static_cast<double*>(C.costs.p), stream));
             P2_HIP(launch_topk_jobs(reinterpret_cast<const DevTopkJob*>(db + off_jobs), (unsigned)n_jobs, shortlist_k, (long long)shortlist_most, stream));
             if (g_prof.on) { P2_HIP(hipEventRecord(g_prof.ev[2], stream)); g_prof.last.post_launches = sums_blocks > 0 ? 3 : 2; }
-            const CopyPart back[1] = {{C.h_gctr.p, C.g_zero.p, graph_back}};
-            P2_HIP(launch_copies(back, 1, stream));
         } else if (direct) {
             P2_HIP(launch_graph_emit(dqs, dgs, static_cast<const GraphCounters*>(C.g_zero.p), reinterpret_cast<const GraphQuery*>(db + off_gasked),
                                      n_queries, nullptr, 0, (unsigned)emit_blocks + 1u, rows_room, nullptr, static_cast<p2_program*>(C.h_progs.p),
@@ -2324,10 +2325,12 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     direct = direct && store && total_valid <= rows_room;       // (the rows are in host memory already)
     for (const QueryRun& r : runs) shortlists = shortlists && (!r.graph || r.n_valid <= most_valid(r.plan));      // (else as if it had not been tried)
     if (shortlists) {
-        const uint32_t* gn = reinterpret_cast<const uint32_t*>(static_cast<const char*>(C.h_gctr.p) + graph_nan);
+        const uint32_t* trouble = static_cast<const uint32_t*>(C.h_pos.p);
         for (int i = 0; i < n_queries; ++i) {
-            if (gn[i] & 1u) return fail(P2_EINVAL, "query " + std::to_string(i) + ": NaN cost (a message size that is not finite?)");
-            if (gn[i] != 0u) return fail(P2_EDEVICE, "top-k returned a bad position");
+            uint32_t t = 0;
+            for (int m = 0; m < n_msg && runs[i].graph; ++m) t |= *trouble++;
+            if (t & 1u) return fail(P2_EINVAL, "query " + std::to_string(i) + ": NaN cost (a message size that is not finite?)");
+            if (t != 0u) return fail(P2_EDEVICE, "top-k returned a bad position");
         }
     }
     if (store && !direct && !shortlists) {

@@ -551,7 +551,9 @@ struct DevTopkJob {
     int k;
     int n_cost;
     // where the number of entries is known on the device only: n is the most that there can be, and the rows that are picked are
-    // written out at once (progs null: neither); nan_flag gets 2 where a selection came back short
+    // written out at once (progs null: neither), with a word of the job's own instead of nan_flag, written in any case and may be
+    // host memory: 1 a cost is NaN, 2 the selection came back short
+    uint32_t* own_flag;
     const uint32_t* n_from;
     const p2_program* progs;       // [n], with the costs [n][n_cost] of which `cost` is a column
     const double* costs;
