@@ -152,3 +152,20 @@ def test_rows_written_once_for_many_queries(large, n):
             for m in range(len(msg)):
                 best = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:kk]
                 assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], f["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], f["cost"][best])
+
+
+# selections by wavefronts, by blocks of 64, 256 and 1 024 threads; the first size or a later one; a query that has no program beside them
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", [2, 9, 20, 200, 1024])
+@pytest.mark.parametrize("msg", [[float("inf")], [1e6, float("inf"), 1e7]])
+def test_shortlists_of_costs_that_are_no_numbers(k, msg):
+    """Links that take no time and a size without end: every selection reports for itself, the call is refused, and the next one finds nothing of it."""
+    from paper_2110_10548_amd import binding as B
+    no_time = lambda n: [float("inf")] * n
+    asked = [_query([2, 2], 3, 1, topk=k, bw=no_time(2)), _query([3, 4, 6], 4, 2, topk=k, bw=no_time(3)), _query([2, 4], 3, 3, topk=k, op_mask=2, bw=no_time(2))]
+    with pytest.raises(Exception, match="NaN cost"):
+        B.p2_synthesize_batch(asked, msg)
+    for q, r in zip(asked, B.p2_synthesize_batch(asked, [1e6])):
+        full = B.p2_synthesize_batch([dict(q, topk=0)], [1e6])[0]
+        best = np.lexsort((full["programs"]["index"], full["cost"][:, 0]))[:k]
+        assert np.array_equal(r["programs"], full["programs"][best])
