@@ -328,6 +328,19 @@ def test_room_for_every_state(card, max_len, states):
     assert s["route"] == B.ROUTE_GRAPH and s["steps_evaluated"] == states * s["alphabet"]
 
 
+# the same on the devices themselves, which states of masks and forms that no skeleton serves are of, and those of queries each by itself
+OWN_STATES = [([2, 32], 7, 42), ([2, 4, 8], 7, 1008), ([2, 2, 4, 4], 6, 17274), ([4, 2, 2, 2, 2], 5, 50567), ([2] * 6, 3, 2513), ([2] * 6, 4, 29586),
+              ([12, 12], 7, 42), ([3, 4, 6], 6, 938), ([2, 3, 2, 4], 6, 17427), ([2, 2, 2, 4, 4], 5, 50647), ([2, 2, 2, 2, 2, 3], 4, 29599)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("card,max_len,states", OWN_STATES)
+def test_room_for_every_state_of_the_devices(card, max_len, states):
+    from paper_2110_10548_amd import binding as B
+    s = B.p2_synthesize_batch([_query(card, max_len, flags=B.FLAG_EVALUATE_EVERY_QUERY)], MSG)[0]["stats"]
+    assert s["route"] == B.ROUTE_GRAPH and s["steps_evaluated"] == states * s["alphabet"]
+
+
 @pytest.mark.gpu
 def test_few_forms_have_no_more_rows():
     """Patterns of one form are as few as those of fewer levels, their programs are not."""
