@@ -340,11 +340,13 @@ class Batch:
         offs = self._offs.tolist()
         limit = _PIECE_BYTES // (PROGRAM_DTYPE.itemsize + 8 * self.n_msg)
         stats = np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist()
+        # (another thread that asks meanwhile finds none, nor does the next call if this one is interrupted)
+        kept = self.__dict__.pop("_pieces", [])
         out, i, pieces = [], 0, []
         while i < self.nq:
             first = offs[i]
             j = max(i + 1, bisect.bisect_right(offs, first + limit) - 1)       # (queries i .. j - 1 share a copy)
-            progs, cost = self._piece(len(pieces), offs[j] - first)
+            progs, cost = self._piece(kept, offs[j] - first)
             _copy_rows(progs, self._progs[first:offs[j]])
             cost[:] = self._cost[first:offs[j], :self.n_msg]
             pieces.append((progs, cost))
@@ -354,11 +356,10 @@ class Batch:
         self._pieces = pieces
         return out
 
-    def _piece(self, at, rows):
+    def _piece(self, kept, rows):
         """Memory for the copies of one piece: that of the results before, where nobody refers to them any more."""
-        if at < len(self._pieces):
-            progs, cost = self._pieces[at]
-            self._pieces[at] = None
+        if kept:
+            progs, cost = kept.pop(0)
             if len(progs) == rows and _unused(progs) and _unused(cost):
                 return progs, cost
         return np.empty(rows, dtype=PROGRAM_DTYPE), np.empty((rows, self.n_msg), dtype=np.float64)

@@ -5,6 +5,8 @@ import ctypes
 import itertools
 import os
 import re
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -228,3 +230,60 @@ def test_pieces_of_results_are_written_again_only_when_unused(B):
     b._offs[:] = [0, 100, 150, 250]                     # (another number of rows: other memory)
     fifth = run(5)
     assert (fourth[2]["programs"]["index"] == 4).all() and (fifth[2]["programs"]["index"] == 5).all() and len(fifth[2]["programs"]) == 100
+
+
+def _ready_batch(B, offs, n_msg=1):
+    """A batch as a call leaves it, `offs` its queries' rows."""
+    q = dict(card=[2, 2], axes=[4], placement=[[2, 2]], reduce_axes=[0], max_len=2)
+    b = B.Batch([q] * (len(offs) - 1), [1.0] * n_msg)
+    b._alloc(offs[-1])
+    b._offs[:] = offs
+    b._progs["index"] = np.arange(offs[-1])
+    b._cost[:] = np.arange(offs[-1])[:, None]
+    return b
+
+
+def test_results_that_were_interrupted_can_be_asked_for_again(B, monkeypatch):
+    b = _ready_batch(B, [0, 60_000, 120_000, 180_000])
+    first = b.results()
+    del first
+    copy, left = B._copy_rows, [1]
+
+    def interrupted(to, rows):
+        left[0] -= 1
+        if left[0] < 0:
+            raise KeyboardInterrupt
+        return copy(to, rows)
+
+    monkeypatch.setattr(B, "_copy_rows", interrupted)
+    with pytest.raises(KeyboardInterrupt):
+        b.results()
+    monkeypatch.setattr(B, "_copy_rows", copy)
+    for _ in range(2):
+        again = b.results()
+        assert [r["programs"]["index"][0] for r in again] == [0, 60_000, 120_000]
+
+
+def test_results_asked_for_by_several_threads(B):
+    b = _ready_batch(B, [0, 30_000, 60_000, 90_000])
+    trouble = []
+
+    def ask(me):
+        try:
+            for _ in range(60):
+                out = b.results()
+                column = out[1]["cost"][:, 0]
+                del out
+                assert column[0] == 30_000.0 and column[-1] == 59_999.0
+                column[:] = me                          # (what is handed out is the caller's own)
+                time.sleep(0)
+                assert (column == me).all()
+        except BaseException as e:
+            trouble.append(e)
+
+    threads = [threading.Thread(target=ask, args=(-i - 1.0,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not trouble
