@@ -406,8 +406,8 @@ def p2_synthesize(card, axes, placement, reduce_axes, max_len, msg_bytes=(), bw=
         filled = n * (PROGRAM_DTYPE.itemsize + 8 * n_msg)
         out = room[0][:n], room[1][:n * n_msg].reshape(n, n_msg)
         # (a long list is handed out as it is, and its buffers are written again when nobody refers to it any more; a short one
-        #  would keep many times its size)
-        if filled < _VIEW_BYTES or 8 * n < len(room[0]):
+        #  would keep many times its size, and so would one whose buffer of costs an earlier call wanted wide)
+        if filled < _VIEW_BYTES or 8 * filled < room[0].nbytes + room[1].nbytes:
             out = _copy_rows(np.empty(n, dtype=PROGRAM_DTYPE), out[0]), out[1].copy()
             _keep_room(room, filled)
         else:

@@ -287,3 +287,32 @@ def test_results_asked_for_by_several_threads(B):
     for t in threads:
         t.join()
     assert not trouble
+
+
+def test_a_result_keeps_no_more_than_some_times_its_size(B, monkeypatch):
+    """A long list is handed out in the buffers that the library wrote, unless they are many times its size, the costs' buffer among them."""
+    rows, real = [0], B.lib()
+
+    class Library:
+        def p2_synthesize(self, *a):
+            a[-3]._obj.value = rows[0]
+            return B.P2_OK
+
+        def __getattr__(self, name):
+            return getattr(real, name)
+
+    monkeypatch.setattr(B, "lib", Library)
+    B._own.__dict__.clear()
+
+    def kept(n, n_msg):
+        rows[0] = n
+        r = B.p2_synthesize([2, 2], [4], [[2, 2]], [0], 2, [1.0] * n_msg)
+        assert r["programs"].shape == (n,) and r["cost"].shape == (n, n_msg)
+        whole = [a if a.base is None else a.base for a in (r["programs"], r["cost"])]
+        return sum(a.nbytes for a in whole) / (n * (16 + 8 * n_msg)), r["programs"].base is not None
+
+    assert kept(100_000, 1)[1]                           # (the buffers themselves)
+    kept(100, 64)                                        # (a short list: the thread's buffers are as wide as this from now on)
+    for n in (16_384, 20_000, 100_000):
+        assert kept(n, 1)[0] <= 8.0, n
+    B._own.__dict__.clear()
