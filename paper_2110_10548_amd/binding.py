@@ -312,7 +312,7 @@ class Batch:
         self.n_msg = len(self._msg)
         self._offs = np.zeros(self.nq + 1, dtype=np.int64)
         self._stats = (p2_stats * self.nq)()
-        self._pieces = []                                # (copies that earlier results were handed out of)
+        self._pieces = []                                # (copies that earlier results were handed out of, up to _KEEP_BYTES)
         self._alloc(_first_rows([int(q.get("topk", 0)) for q in queries], self.n_msg,
                                 min(_FIRST_ROWS_PER_QUERY * self.nq, 2 * _FIRST_ROWS)))
 
@@ -342,14 +342,16 @@ class Batch:
         stats = np.frombuffer(self._stats, dtype=_STATS_DTYPE).tolist()
         # (another thread that asks meanwhile finds none, nor does the next call if this one is interrupted)
         kept = self.__dict__.pop("_pieces", [])
-        out, i, pieces = [], 0, []
+        out, i, pieces, held = [], 0, [], 0
         while i < self.nq:
             first = offs[i]
             j = max(i + 1, bisect.bisect_right(offs, first + limit) - 1)       # (queries i .. j - 1 share a copy)
             progs, cost = self._piece(kept, offs[j] - first)
             _copy_rows(progs, self._progs[first:offs[j]])
             cost[:] = self._cost[first:offs[j], :self.n_msg]
-            pieces.append((progs, cost))
+            held += progs.nbytes + cost.nbytes
+            if held <= _KEEP_BYTES:
+                pieces.append((progs, cost))
             out += [{"programs": progs[a - first:b - first], "cost": cost[a - first:b - first], "stats": dict(zip(_STATS_FIELDS, row))}
                     for a, b, row in zip(offs[i:j], offs[i + 1:j + 1], stats[i:j])]
             i = j

@@ -316,3 +316,17 @@ def test_a_result_keeps_no_more_than_some_times_its_size(B, monkeypatch):
     for n in (16_384, 20_000, 100_000):
         assert kept(n, 1)[0] <= 8.0, n
     B._own.__dict__.clear()
+
+
+def test_copies_that_a_batch_keeps_are_bounded(B):
+    """Memory of earlier results is kept for the next ones as far as buffers are kept elsewhere."""
+    def kept(b):
+        return sum(progs.nbytes + cost.nbytes for progs, cost in b._pieces)
+
+    b = _ready_batch(B, list(range(0, 130_001, 1000)), n_msg=1)
+    b.results()
+    assert kept(b) == 130_000 * 24
+    b = _ready_batch(B, list(range(0, 130_001, 1000)), n_msg=30)
+    for _ in range(2):
+        out = b.results()
+        assert all((r["cost"][0] == 1000.0 * i).all() for i, r in enumerate(out)) and 0 < kept(b) <= B._KEEP_BYTES < 130_000 * 256
