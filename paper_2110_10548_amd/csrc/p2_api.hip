@@ -1264,7 +1264,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             if (G.large) { slots = 0; D.all_rows = D.all_cols = 0ull; }
             if (G.narrow) {
                 D.cap_planes = 0;
-                D.cap_found = D.cap_edges = std::min(D.cap_found, (1u << 18) - 1u);        // (a node's first edge is kept in 18 bits)
+                D.cap_found = std::min(D.cap_found, (1u << 18) - 1u);        // (a node's first edge is kept in 18 bits)
                 D.own_chunks = (uint32_t)pl.k;
                 for (int j = pl.n - 1, l = 0; j >= 0; --j) if (pl.f[j] > 1) D.own_size[l++] = (uint32_t)pl.f[j];
             }
@@ -1284,7 +1284,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             P.first = take(mem, sizeof(uint2) * (size_t)D.cap_nodes);
             P.use_ends = take(mem, sizeof(uint32_t) * 8 * (size_t)D.cap_nodes);
             P.edges = take(mem, sizeof(uint32_t) * D.cap_edges);
-            P.edge_state = take(mem, sizeof(uint32_t) * D.cap_edges);
+            P.edge_state = take(mem, G.skeleton ? 0 : sizeof(uint32_t) * D.cap_edges);
             P.edge_path = take(mem, G.skeleton && !G.narrow ? sizeof(unsigned long long) * D.cap_edges : 0);
             P.best = take(mem, sizeof(double) * (size_t)D.cap_edges * G.members.size());
         }

@@ -44,7 +44,7 @@ struct InBlock {
 template <class Where>
 struct Skeleton {
     int n_pat, n_ops, max_len;
-    uint32_t op_mask, op_ranks, cap_nodes, cap_found, table_mask;
+    uint32_t op_mask, op_ranks, cap_nodes, cap_found, cap_edges, table_mask;
     uint32_t k, size[kNarrowLevels];        // split: the group's own chunks and levels
     bool split;
     P2_GLOBAL GraphCounters* ctr;
@@ -52,19 +52,20 @@ struct Skeleton {
     typename Where::template at<uint32_t> table_node, node_state, node_edges, planes;
     typename Where::template at<u32x2> links;
     P2_GLOBAL uint32_t *use_ends, *use_list;
-    P2_GLOBAL u32x2* count2;
+    P2_GLOBAL u32x2 *count2, *first_edge;
     P2_GLOBAL uint8_t* nearest;
 };
 template <class Where>
 __device__ __forceinline__ void open_skeleton(Skeleton<Where>& G, const DevGraph& D) {
     G.n_pat = D.n_pat; G.n_ops = D.n_ops; G.max_len = D.max_len; G.op_mask = D.op_mask; G.op_ranks = D.op_ranks;
-    G.cap_nodes = D.cap_nodes; G.cap_found = D.cap_found; G.table_mask = D.table_mask;
+    G.cap_nodes = D.cap_nodes; G.cap_found = D.cap_found; G.cap_edges = D.cap_edges; G.table_mask = D.table_mask;
     G.split = D.split_check != 0u;
     G.k = D.own_chunks;
 #pragma unroll
     for (int l = 0; l < kNarrowLevels; ++l) G.size[l] = D.own_size[l];
     G.ctr = in_global<GraphCounters>(D.ctr);
     G.use_ends = in_global<uint32_t>(D.use_ends); G.nearest = in_global<uint8_t>(D.nearest); G.use_list = in_global<uint32_t>(D.use_id); G.count2 = in_global<u32x2>(D.count2);
+    G.first_edge = in_global<u32x2>(D.first_edge);
 }
 __device__ __forceinline__ Skeleton<InDevice> open_in_device(const DevGraph& D) {
     Skeleton<InDevice> G;
@@ -516,7 +517,8 @@ __device__ void skeleton_links(const Skeleton<Where>& G, LevelShared& S, int lev
 
 struct FinishShared {
     uint32_t end[P2_MAX_LEN + 1], lim[P2_MAX_LEN + 1], at[P2_MAX_LEN + 1];       // nodes first reached by at most d instructions; how many nodes count r is kept for, and where
-    uint32_t edges, used, targets;
+    uint32_t edges, targets, valid;
+    u64 used;                               // nodes on the way to a goal | their edges << 32
 };
 
 constexpr uint32_t kFewEdges = 4;            // edges of a thread where they are counted edge by edge
@@ -540,7 +542,7 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
         const uint32_t end = wave_scan(tid == 0u ? 1u : tid < (uint32_t)M ? (uint32_t)f : 0u), edges = wave_scan((uint32_t)(f >> 32));
         const uint32_t mirror = __shfl(end, M - (int)tid < 0 ? 0 : M - (int)tid, kWave), lim = tid >= 2u && tid <= (uint32_t)M ? mirror : 0u, at = wave_scan(lim);
         if (tid <= P2_MAX_LEN) { S.end[tid] = end; S.lim[tid] = lim; S.at[tid] = at - lim; }
-        if (tid == P2_MAX_LEN) { S.edges = edges; S.used = 0u; }
+        if (tid == P2_MAX_LEN) { S.edges = edges; S.used = 0ull; }
         if ((int)tid == (M > 2 ? M - 2 : 0)) S.targets = edges;
     }
     __syncthreads();
@@ -652,18 +654,24 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
     }
     if (tid < kWave) {
         const uint32_t all = wave_scan(tid == 1u ? (uint32_t)goal1[0] : tid >= 2u && tid <= (uint32_t)M ? count[S.at[tid]] : 0u);
-        if (tid == kWave - 1) { ctr->n_total = all; ctr->n_judged = n_nodes; }
+        if (tid == kWave - 1) { S.valid = all; ctr->n_judged = n_nodes; }
     }
-    // the nodes on the way to a goal, in any order, and what lies behind them
+    // the nodes on the way to a goal, in any order, what lies behind them, and room for their edges (one after the other: what is kept of
+    // every edge and query is sized by these, 8 765 of the 31 660 edges of four levels and six instructions)
     for (uint32_t n = tid; n < (n_nodes + kWave - 1u) / kWave * kWave; n += T) {
+        const uint32_t lane = tid & (kWave - 1u);
         const uint8_t near = n < n_nodes ? nearest[n] : 255;
         const u64 used = __ballot(near != 255);
-        uint32_t at = 0u;
-        if ((tid & (kWave - 1u)) == 0u && used != 0ull) at = atomicAdd(&S.used, (uint32_t)__popcll(used));
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(used & ((1ull << (tid & (kWave - 1u))) - 1ull));
+        const uint32_t own = near != 255 ? (uint32_t)goal1[n] + (uint32_t)prefix1[n] : 0u, upto = wave_scan(own);
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+        u64 was = 0ull;
+        if (lane == 0u && used != 0ull) was = atomicAdd(&S.used, (u64)__popcll(used) | (u64)all << 32);
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)was) + (uint32_t)__popcll(used & ((1ull << lane) - 1ull));
+        const uint32_t place = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(was >> 32)) + upto - own;
         if (n < n_nodes) G.nearest[n] = near;
         if (near == 255) continue;
         G.use_list[at] = n;
+        G.first_edge[n] = u32x2{place, place};
         u32x4 lo = {0u, goal1[n], 0u, 0u}, hi = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int r = 2; r <= P2_MAX_LEN; ++r) {
@@ -674,7 +682,11 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
         out[0] = lo; out[1] = hi;
     }
     __syncthreads();
-    if (tid == 0) ctr->n_edges = S.used;
+    if (tid == 0) {
+        // (no rows are written before the number of valid programs is)
+        if ((uint32_t)(S.used >> 32) > G.cap_edges) ctr->flags = kGraphFull;
+        else { ctr->n_edges = (uint32_t)S.used; ctr->n_total = S.valid; }
+    }
 }
 
 __device__ __forceinline__ void open_level(LevelShared& S, const DevGraph& D) {
@@ -778,7 +790,7 @@ __global__ __launch_bounds__(kAloneThreads) void k_skeleton_alone(const DevGraph
     if (threadIdx.x < F.edges) in_global<u32x2>(D.links)[threadIdx.x] = A.links[threadIdx.x];
 }
 
-// The edges on the way to a goal, moved to the front of their state's, and what each adds to the bandwidth sum of every query: a
+// The edges on the way to a goal, at the front of the room that their state's have, and what each adds to the bandwidth sum of every query: a
 // block per state on the way to a goal, a wavefront for every fourth or eighth edge, a lane per query.  An edge is kept if the goal can be
 // reached behind it with the instructions that are left there.
 template <int LOG>
@@ -805,7 +817,7 @@ __global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(cons
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     __syncthreads();
     for (uint32_t u = blockIdx.x; u < n_use; u += gridDim.x) {
-        const uint32_t node = list[u], rec = node_edges[node], first = rec >> 14, count = rec >> 7 & 127u;
+        const uint32_t node = list[u], rec = node_edges[node], first = rec >> 14, count = rec >> 7 & 127u, place = first_edge[node].x;
         const u64 path = node_path[node];
         int left = M - 1;
         for (u64 p = path; p != 0ull; p >>= 8) --left;
@@ -823,9 +835,9 @@ __global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(cons
         const uint32_t n0 = (uint32_t)__popcll(keepers[0]), n_kept = n0 + (uint32_t)__popcll(keepers[1]);
         if (wave == 0u && blockIdx.z == 0u) {
             const u64 below = (1ull << lane) - 1ull;
-            if (kept[0]) edges[first + (uint32_t)__popcll(keepers[0] & below)] = (link[0].x & ~kGoalEdge) | link[0].y;
-            if (kept[1]) edges[first + n0 + (uint32_t)__popcll(keepers[1] & below)] = (link[1].x & ~kGoalEdge) | link[1].y;
-            if (lane == 0u) first_edge[node] = u32x2{first, first + n_kept};
+            if (kept[0]) edges[place + (uint32_t)__popcll(keepers[0] & below)] = (link[0].x & ~kGoalEdge) | link[0].y;
+            if (kept[1]) edges[place + n0 + (uint32_t)__popcll(keepers[1] & below)] = (link[1].x & ~kGoalEdge) | link[1].y;
+            if (lane == 0u) ((P2_GLOBAL uint32_t*)(first_edge + node))[1] = place + n_kept;      // (the blocks of the other queries read the place)
         }
         if (with_costs == 0 || wave >= n_kept) continue;
         HeldRows<LOG> rows;
@@ -838,7 +850,7 @@ __global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(cons
                 if (at % kCostWaves<LOG> != wave) continue;
                 const uint32_t digit = (uint32_t)__builtin_amdgcn_readlane((int)link[x].x, __ffsll((long long)rest) - 1) >> kDigitShift;
                 const double b = rows.busiest(T.of(digit), own);
-                if (mine) best[(size_t)(first + at) * n_members + member] = b;
+                if (mine) best[(size_t)(place + at) * n_members + member] = b;
             }
     }
 }

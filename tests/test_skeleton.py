@@ -169,3 +169,22 @@ def test_shortlists_of_costs_that_are_no_numbers(k, msg):
         full = B.p2_synthesize_batch([dict(q, topk=0)], [1e6])[0]
         best = np.lexsort((full["programs"]["index"], full["cost"][:, 0]))[:k]
         assert np.array_equal(r["programs"], full["programs"][best])
+
+
+@pytest.mark.gpu
+def test_room_for_the_costs_of_many_queries():
+    """What each query keeps beside a skeleton's graph: a cost for every edge of the states on the way to a goal that there can be (at most as many as states
+    and 256 more), its rows' costs and its description."""
+    import torch
+    from paper_2110_10548_amd import binding as B
+    n, max_len, states, rows = 4096, 3, 768, 138
+    queries = [_query([2, 2, 2, 2], max_len, i, topk=1) for i in range(n)]
+    B.p2_synthesize_batch(queries[:1], MSG[:1])          # (the runtime's own memory)
+    B.p2_release_thread()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    results = B.p2_synthesize_batch(queries, MSG[:1])
+    held = before - torch.cuda.mem_get_info()[0]
+    assert {r["stats"]["route"] for r in results} == {B.ROUTE_GRAPH} and [r["stats"]["valid"] for r in results] == [rows] * n
+    assert held < n * (8 * (states + 256) + 8 * rows + 4096) + (16 << 20)
+    B.p2_release_thread()
