@@ -780,11 +780,12 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         const size_t most = most_valid(r.plan);
         shortlists = shortlists && r.topk > 0 && most <= kTopkJobMax;
         shortlist_rows += most;
-        shortlist_out += (size_t)n_msg * (size_t)r.topk;
+        shortlist_out += shortlist_rows_of(r.plan, r.topk, n_msg);
         shortlist_k = std::max(shortlist_k, r.topk);
         shortlist_most = std::max(shortlist_most, most);
     }
-    shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && shortlist_rows <= kShortlistBytes / (sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1));
+    // (the rows that are picked go to pinned memory, which is bounded as for lists)
+    shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && rows_at_once(shortlist_out, cap, n_msg) > 0 && shortlist_rows <= kShortlistBytes / (sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1));
     // Of a graph with several queries the rows are written once, and their costs worked out for all of them side by side (k_graph_sums).
     auto shares_rows = [&](const Graph& G) {
         return G.narrow && G.members.size() >= kSharedQueries && runs[G.leader].plan.n_ops == 5 && runs[G.leader].plan.alphabet <= (int)kSumDigits;
@@ -1581,7 +1582,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                     J->n_from = &reinterpret_cast<const GraphCounters*>(C.g_zero.p)[r.graph_id].n_total;
                     J->out_pos = static_cast<long long*>(C.topk_pos.p) + out;
                     J->out_progs = static_cast<p2_program*>(C.h_progs.p) + out; J->out_costs = static_cast<double*>(C.h_costs.p) + out * (size_t)n_msg;
-                    out += (size_t)r.topk;
+                    out += shortlist_rows_of(r.plan, r.topk, 1);
                 }
             }
         }
@@ -2620,7 +2621,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (r.topk > 0) {
             const size_t kk = std::min<size_t>(r.topk, r.n_valid);
             if (!store) w += (int64_t)n_msg * (int64_t)kk;
-            for (int m = 0; m < n_msg && store; ++m, short_at += (size_t)(r.graph ? r.topk : 0))
+            for (int m = 0; m < n_msg && store; ++m, short_at += r.graph ? shortlist_rows_of(r.plan, r.topk, 1) : 0)
                 for (size_t t = 0; t < kk; ++t, ++w) {
                     const size_t sel = pos_off;
                     if (shortlists) {

@@ -85,6 +85,8 @@ bool same_cost_rows(const Plan& a, const Plan& b);
 // is the same for all level sizes and the most that any chunks leave.  (Past the size limits that were counted, which only a
 // plan with few forms gets to where this is asked, it is the last one counted, and may be less than there are.)
 size_t most_valid(const Plan& plan);
+// Rows that a query's shortlists can have: for every size as many as it asks for, or as it has programs.
+inline size_t shortlist_rows_of(const Plan& plan, int topk, int n_msg) { return (size_t)n_msg * std::min((size_t)topk, most_valid(plan)); }
 // Rows that a call writes to pinned host memory before their number is known, when some `expected` may come out: never more
 // than the caller can take (a call with more has nowhere to put them), and none (the rows are counted first) where pinned
 // memory for them would pass kRowsAtOnceBytes.  Pinned pages are taken from the whole machine, kept until the thread gives

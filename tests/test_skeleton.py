@@ -188,3 +188,15 @@ def test_room_for_the_costs_of_many_queries():
     assert {r["stats"]["route"] for r in results} == {B.ROUTE_GRAPH} and [r["stats"]["valid"] for r in results] == [rows] * n
     assert held < n * (8 * (states + 256) + 8 * rows + 4096) + (16 << 20)
     B.p2_release_thread()
+
+
+@pytest.mark.gpu
+def test_shortlists_beyond_the_bound_of_pinned_memory():
+    """More rows to pick than are written to the host before they are counted: 400 queries of 86 programs, all of them asked for, 64 sizes."""
+    from paper_2110_10548_amd import binding as B
+    queries = [_query([2, 2 + i % 3], 4, i, topk=1024) for i in range(400)]
+    msg = [2.0 ** (10 + 0.25 * m) for m in range(64)]
+    for i, r in list(enumerate(B.p2_synthesize_batch(queries, msg)))[::57]:
+        o = B.p2_synthesize_batch(queries[i:i + 1], msg)[0]
+        assert r["stats"]["valid"] == 86 and len(o["programs"]) == 64 * 86
+        assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"])

@@ -229,6 +229,27 @@ def test_room_for_rows_not_yet_counted(tmp_path):
     assert out == ["262144", "0", "83920", "100", "83920", "0", "110"]
 
 
+SHORT_ROOM = r"""
+#include "p2_plan.h"
+#include <cstdio>
+int main() {
+    using namespace p2;
+    const int32_t card[2] = {2, 8}, axes[1] = {16}, reduce[1] = {0};
+    const p2_hierarchy h = {2, card, nullptr, nullptr};
+    Plan pl;
+    std::string err;
+    if (make_plan(&h, axes, 1, card, reduce, 1, 3, nullptr, false, pl, err) != P2_OK) return 1;
+    const size_t one = shortlist_rows_of(pl, 1024, 64);
+    std::printf("%zu %zu %zu %zu\n", shortlist_rows_of(pl, 10, 11), one, rows_at_once(50 * one, 1 << 30, 64), rows_at_once(200 * one, 1 << 30, 64));
+}
+"""
+
+
+def test_room_for_shortlists_not_yet_counted(tmp_path):
+    """Shortlists of more than there can be take room for what there can be (35 programs), and pinned memory for them is bounded too."""
+    assert _compiled(tmp_path, SHORT_ROOM, "p2_plan.cpp").split() == ["110", "2240", "112000", "0"]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("cap", [34, 35, 36, 86, 200])
 def test_rows_as_far_as_the_caller_has_room(cap):
