@@ -2,6 +2,7 @@
 // copy-back.  All arithmetic of the method runs in the kernels; this file only moves data.
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstddef>
 #include <cstring>
 #include <exception>
@@ -2788,7 +2789,10 @@ int32_t p2_search_placements(const p2_hierarchy* h, const int32_t* axes, int32_t
         if (opt) main_opt = *opt;
         main_opt.topk = 1;
         p2_options base_opt = main_opt;
-        base_opt.form_mask = 1; base_opt.op_mask = 1;      // (a list of one program, asked for as a shortlist like the others)
+        base_opt.form_mask = 1; base_opt.op_mask = 1;
+        // (a list of one program, asked for as a shortlist like the others unless its cost may be no number, which a selection refuses: a
+        //  size without end over links that take no time, or no bytes over links that take for ever)
+        base_opt.topk = msg_bytes > 0.0 && std::isfinite(msg_bytes) ? 1 : 0;
         base_opt.engine = P2_ENGINE_AUTO;
         const int n_q = (int)(n_pl * n_sets * 2);
         std::vector<p2_query> qs((size_t)n_q);

@@ -200,3 +200,15 @@ def test_shortlists_beyond_the_bound_of_pinned_memory():
         o = B.p2_synthesize_batch(queries[i:i + 1], msg)[0]
         assert r["stats"]["valid"] == 86 and len(o["programs"]) == 64 * 86
         assert np.array_equal(r["programs"], o["programs"]) and np.array_equal(r["cost"], o["cost"])
+
+
+# a size without end over links that take no time, and no bytes over links that take for ever; the last one has numbers
+@pytest.mark.gpu
+@pytest.mark.parametrize("bytes_, bw, none", [(float("inf"), float("inf"), True), (0.0, 1e-310, True), (float("inf"), 1e9, False)])
+def test_baselines_that_are_no_numbers(bytes_, bw, none):
+    """A search whose own programs are none: the AllReduce beside them is reported whatever its cost."""
+    from paper_2110_10548_amd import binding as B
+    r = B.p2_search_placements([2, 4], [4, 2], [[0], [1]], 3, bytes_, bw=[bw] * 2, alpha=[1e-5, 1e-6], op_mask=2)
+    for row in r["rows"].values():
+        assert row["valid"] == 0 and row["best_cost"] == float("inf")
+        assert np.isnan(row["allreduce_cost"]) if none else row["allreduce_cost"] == float("inf")
