@@ -217,12 +217,19 @@ typedef struct {
     uint64_t steps_evaluated;  /* instruction applications the engine carried out; an application
                                   shared by several candidates counts once (P2_ENGINE_SHARED: the
                                   candidates handed to the literal engine not included), so it is
-                                  at most steps_executed                                          */
-    uint64_t members_evaluated;/* devices taking part in those applications, summed               */
+                                  at most steps_executed.  State graphs: the alphabet once per
+                                  distinct state of the graph; with all collectives and forms that
+                                  is a graph of two devices per level of the group, whatever its
+                                  sizes (up to six levels; P2_FLAG_EVALUATE_EVERY_QUERY: of the
+                                  group's own devices)                                            */
+    uint64_t members_evaluated;/* devices taking part in those applications, summed: of the devices
+                                  that the states are of                                          */
     int32_t evaluated_with;    /* p2_synthesize_batch: index of the earlier query of the batch whose
                                   evaluation this one shares (its validity results are that
-                                  query's, its costs its own; steps_* and members_* repeat that
-                                  query's figures), or -1: evaluated for itself                   */
+                                  query's, its costs its own; steps_executed repeats that query's
+                                  figure, and steps_evaluated is 0 where a graph answered; groups
+                                  that differ in the sizes of their levels may share one), or -1:
+                                  evaluated for itself                                            */
     int32_t route;             /* P2_ROUTE_* bits: which way engine AUTO took                      */
 } p2_stats;
 
@@ -261,17 +268,19 @@ typedef struct {
  * out_offset has n_queries + 1 entries; stats (optional) has n_queries entries.
  * Whether a program is valid depends on the reduction group, the chunks, the patterns, the alphabet
  * and the size limit only, not on the links nor on where the placement puts the group: queries of
- * the batch that agree in these are evaluated once and then costed each with its own links (the
- * later ones report the first one's per-candidate counts in their stats, and steps_evaluated = 0
- * under the shared-prefix engine).  P2_FLAG_EVALUATE_EVERY_QUERY in the options of any query of the
- * batch switches this off for the whole batch, on every engine.
- * The kernels of all queries share their launches; the call waits for the device twice: after
- * the evaluation (to size the result lists) and for the results (once where engine AUTO answers every
- * query from a state graph and none asks for a shortlist).  Queries on the frontier engine
- * run on streams of the library's own, up to four enumerations side by side, and the call waits
- * for them; the first call of a host thread with more than one enumeration also waits for the
- * caller's stream and spends a few milliseconds timing short kernels on a handful of new streams,
- * to pick four that do not share a hardware queue. */
+ * the batch that agree in these, and those that one state graph answers, are evaluated once and then
+ * costed each with its own links (the later ones report the first one's per-candidate counts in their
+ * stats, and steps_evaluated = 0 under the shared-prefix engine and state graphs).
+ * P2_FLAG_EVALUATE_EVERY_QUERY in the options of any query of the batch switches this off for the
+ * whole batch, on every engine.
+ * The kernels of all queries share their launches; the call waits for the device twice: after the
+ * evaluation (to size the result lists) and for the results (once where engine AUTO answers every query
+ * from a state graph, all of them ask for shortlists or none does, and the caller and 64 MiB of pinned
+ * memory have room for all rows that there can be).  Queries on the frontier engine run on streams of
+ * the library's own, up to four enumerations side by side, and the call waits for them; the first call
+ * of a host thread with more than one enumeration also waits for the caller's stream and spends a few
+ * milliseconds timing short kernels on a handful of new streams, to pick four that do not share a
+ * hardware queue. */
 int32_t p2_synthesize_batch(const p2_query* queries, int32_t n_queries, const double* msg_bytes, int32_t n_msg,
                             p2_program* out_prog, double* out_cost, int64_t cap, int64_t* out_offset,
                             p2_stats* stats);

@@ -538,7 +538,6 @@ struct QueryRun {
     bool graph_flat = false;              // ... (or, where it stands in for a walk, the walk's)
     bool graph_large = false;             // its states are worked on by the frontier's kernels
     int graph_id = -1, graph_pos = 0;     // ... its graph, and its place among the graph's queries
-    int graph_first = -1;                 // ... the first query of the graph with the same group
     bool wave_cost = false;               // valid programs costed by the wavefront-per-program kernel
     int enum_id = -1, share_pos = 0;      // frontier: its enumeration, and its place among the enumeration's queries
     int topk = 0;
@@ -703,7 +702,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             for (QueryRun& r : runs) r.graph = false;
     }
     // queries of one reduction structure are answered from one graph, and so are the structures of one skeleton
-    struct Graph { int leader = -1; std::vector<int32_t> members, structures; uint32_t n_blocks = 0; bool small = false, large = false, skeleton = false, narrow = false;
+    struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t n_blocks = 0; bool small = false, large = false, skeleton = false, narrow = false;
                    int R = 0, rows = 0; size_t off_members = 0, off_query = 0, off_sizes = 0; };
     std::vector<Graph> graphs;
     auto fused_sums = [](const QueryRun& r) { return r.graph_frontier && !r.graph_flat ? 0u : 1u; };
@@ -731,9 +730,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             G.leader = i; G.skeleton = skeleton; G.narrow = skeleton && group_levels(pl) <= kNarrowLevels; G.large = r.graph_large && !skeleton; G.R = R; G.rows = skeleton ? R : graph_rows(pl);
         }
         Graph& G = graphs[r.graph_id];
-        for (size_t t = 0; t < G.structures.size() && r.graph_first < 0; ++t)
-            if (same_group(runs[G.structures[t]])) r.graph_first = G.structures[t];
-        if (r.graph_first < 0) { r.graph_first = i; G.structures.push_back(i); }
         r.graph_pos = (int)G.members.size();
         G.members.push_back(i);
     }
@@ -2656,7 +2652,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
                 s.member_visits = enums[r.enum_id].flat_instr * per_alphabet;
             }
             s.valid = r.n_valid; s.group_size = r.plan.R; s.n_patterns = (int32_t)r.plan.patterns.size();
-            s.evaluated_with = r.graph ? (r.graph_first != i ? r.graph_first : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
+            s.evaluated_with = r.graph ? (graphs[r.graph_id].leader != i ? graphs[r.graph_id].leader : -1) : r.frontier ? (r.enum_id >= 0 && enums[r.enum_id].leader != i ? enums[r.enum_id].leader : -1) : r.same_as;
             s.route = (r.graph ? P2_ROUTE_GRAPH : 0) | (left[i] ? P2_ROUTE_GRAPH_LEFT : 0) | (repeated ? P2_ROUTE_REPEATED : 0) |
                       (wanted_direct && store && !direct ? P2_ROUTE_ROWS_LATER : 0);
             s.alphabet = r.plan.alphabet; s.engine = r.frontier || r.graph_frontier ? P2_ENGINE_FRONTIER : r.shared ? P2_ENGINE_SHARED : r.regs ? P2_ENGINE_SMALL : r.engine;

@@ -212,3 +212,19 @@ def test_baselines_that_are_no_numbers(bytes_, bw, none):
     for row in r["rows"].values():
         assert row["valid"] == 0 and row["best_cost"] == float("inf")
         assert np.isnan(row["allreduce_cost"]) if none else row["allreduce_cost"] == float("inf")
+
+
+@pytest.mark.gpu
+def test_who_was_evaluated_for_itself():
+    """evaluated_with names the query that a graph was built for, whatever the sizes of its levels; what is -1 was evaluated."""
+    from paper_2110_10548_amd import binding as B
+    cards = [[2, 4, 8, 8], [4, 16], [2, 2, 2, 2], [3, 4, 6], [8, 9], [2, 4, 8, 8], [5, 2, 7], [3, 2, 4, 5]]
+    queries = [_query(c, 4, i) for i, c in enumerate(cards)] + [_query([4, 4], 4, 9, n_chunks=6), _query([4, 4], 4, 8, n_chunks=6)]
+    results = B.p2_synthesize_batch(queries, MSG)
+    assert [r["stats"]["evaluated_with"] for r in results] == [-1, -1, 0, -1, 1, 0, 3, 0, -1, 8]
+    for r in results:
+        s = r["stats"]
+        assert s["route"] == B.ROUTE_GRAPH and (s["steps_evaluated"] > 0) == (s["members_evaluated"] > 0) == (s["evaluated_with"] < 0)
+        if s["evaluated_with"] >= 0:
+            first = results[s["evaluated_with"]]
+            assert np.array_equal(r["programs"], first["programs"]) and s["steps_executed"] == first["stats"]["steps_executed"]
