@@ -126,3 +126,17 @@ def programs(edges, max_len):
                 walk(to, before + (digit,))
     walk(0, ())
     return out
+
+
+def prefixes(edges, max_len):
+    """How many programs of 0, 1, .. max_len - 1 instructions have all their rules hold, short of the goal."""
+    out, at = [], {0: 1}
+    for _ in range(max_len):
+        out.append(sum(at.values()))
+        behind = {}
+        for node, n in at.items():
+            for _, to in edges[node]:
+                if to >= 0:
+                    behind[to] = behind.get(to, 0) + n
+        at = behind
+    return out

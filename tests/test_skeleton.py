@@ -1,9 +1,12 @@
 """Structures answered from the graph of their skeleton (as many levels, two devices each) beside their own devices' graphs and the
 oracle: the same programs, costs and counts whatever the sizes of the levels."""
+import itertools
+import math
 import random
 
 import numpy as np
 import pytest
+import skeleton_rules
 
 MOST = {1: 7, 2: 7, 3: 6, 4: 6, 5: 5, 6: 4}              # the size limits up to which skeletons are used, by levels
 MSG = [2.0 ** 20, 3.0e8]
@@ -228,3 +231,24 @@ def test_who_was_evaluated_for_itself():
         if s["evaluated_with"] >= 0:
             first = results[s["evaluated_with"]]
             assert np.array_equal(r["programs"], first["programs"]) and s["steps_executed"] == first["stats"]["steps_executed"]
+
+
+# every list of so many levels with at most so many devices, every number of chunks up to one and a half times as many: those that are no multiple of the
+# group's devices, where how often rows can be cut is the group's own, and the multiple
+@pytest.mark.parametrize("levels,devices,max_len", [(1, 30, 7), (2, 20, 4), (2, 12, 7), (3, 12, 4), (3, 8, 6), (4, 24, 2), (4, 16, 3), (4, 16, 4)])
+def test_rules_of_skeletons(oracle, levels, devices, max_len):
+    """What the kernels of skeletons go by (tests/skeleton_rules.py) beside the oracle on the devices themselves: programs and prefixes."""
+    for card in itertools.product(range(2, devices + 1), repeat=levels):
+        R = math.prod(card)
+        for k in range(1, R * 3 // 2 + 1) if R <= devices else ():
+            split = k % R != 0
+            if levels == 4 and max_len == 4 and k not in (2, 8, 16, 24):
+                continue
+            edges, _ = skeleton_rules.graph(levels, max_len, card[::-1] if split else None, k if split else 0)
+            mine = sorted(skeleton_rules.programs(edges, max_len))
+            o = oracle.Query(card, [R], [card], [0], n_chunks=k)
+            r = o.synthesize(max_len)
+            assert mine == sorted(tuple(i[:n]) for i, n in zip(r["instr"].tolist(), r["len"].tolist())), (card, k)
+            # (the oracle tries the alphabet behind every prefix and every program that is not at the limit)
+            tried = sum(skeleton_rules.prefixes(edges, max_len)) + sum(len(p) < max_len for p in mine)
+            assert tried * o.alphabet == r["steps_tried"], (card, k)
