@@ -409,10 +409,16 @@ bool walks_beside(const p2::Plan& pl) {
 // each other, and these relations do not depend on how many devices a level has; where chunk sets of different shapes
 // overlap (a ReduceScatter after an AllGather over an outer level, its blocks as large as the levels' sizes say) they do, but
 // with three levels not before the sixth instruction, which only counts if it ends at the goal.  That is not a proof for every
-// size, but there are finitely many: for all 15 407 lists of one to six levels with up to 512 devices and the size limits
-// below, the programs, their number by length, the prefixes' and every cost are those of the graph of the devices
-// themselves, and of the enumeration.  (Seven instructions of three levels are not: 3 x 4 x 2 has fewer prefixes.)
-// Checked with all collectives and forms, and used with these; and for single instructions, which the first state decides.
+// size, but there are finitely many, and tests/sweep_skeletons.py has compared programs, counts and costs with those of the devices' own
+// graphs or enumerations, to the bit: all 15 407 lists of one to six levels with up to 512 devices, at the size limits below and at a
+// smaller one each.  (Seven instructions of three levels are not the same: 3 x 4 x 2 has fewer prefixes.)
+// Chunks that are no multiple of the devices (up to kNarrowLevels levels): with R / gcd(k, R) finer chunks for each the rows are
+// blocks of a whole number of them, the programs are those of the full rows whose ReduceScatters all divide, and a state's rule
+// needs no more than how many chunks a device holds, which the states keep.  Compared in the same way for the lists of one to four
+// levels with every number of chunks that divides the devices and one that does not, 325 000 queries; and by
+// tests/test_skeleton.py with the oracle, for few devices with every number of chunks.
+// Used with all collectives and forms, with which it was checked (a narrowed alphabet's programs are among these, but how many
+// prefixes it has was not compared), and for single instructions, which the first state decides.
 constexpr int kSkeletonMaxLen[p2::kSkeletonLevels + 1] = {0, 7, 7, 6, 6, 5, 4};
 int group_levels(const p2::Plan& pl) {
     int n = 0;
