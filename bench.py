@@ -5,12 +5,15 @@ p2_synthesize_batch call.
 
 Prints ONE JSON line.  The default workload is configuration 5, the largest (512 devices, 512
 queries, programs of up to six instructions): its candidate spaces (up to 2.65e11 programs per
-query) are resolved by enumeration by program size with pruning (Sec. 3.5), the frontier engine.
+query) are resolved without walking them, from the graphs of the distinct states that programs pass
+through (engine AUTO), or by enumeration by program size with pruning (Sec. 3.5, the frontier engine).
 `value` counts the candidate programs whose status (valid or not; cost and rank for the valid
 ones) one step settles, per second, and counts a query's candidate space only where the library
 evaluated that query itself: queries of the batch whose validity results are equal by construction
-(same reduction group, chunks, patterns, alphabet, size limit) are enumerated once and only costed
-on their own (`config.queries_evaluated` of `config.queries`; `value_all_queries` counts every query).
+are evaluated once and only costed on their own (`config.queries_evaluated` of `config.queries`).
+Those are the queries with the same reduction group, chunks, patterns, alphabet and size limit
+(`value_distinct_structures` counts one space for each of these) and, where a graph answers, also those
+whose groups have as many levels, whatever their sizes; `value_all_queries` counts every query.
 
 `roofline` prices the dominant kernel family of the step.  For the frontier engine that is the
 classification of the states of valid prefixes against every instruction of the alphabet
@@ -30,8 +33,9 @@ side, so those are times of kernels that share the chip, and an event pair on on
 the time its kernel waits for a turn behind the other streams' kernels, which a profiler's kernel
 duration does not; `one_enumeration_at_a_time` gives the same objects for a few steps with the
 enumerations one after the other (there the two agree), and `--one-at-a-time` times the whole run so.
-For the flat engines (configurations 1-4 with the default engine) the roofline is the lane-operation
-rate of the evaluation kernel, as `other_configs` reports per configuration.
+For the flat engines the roofline is the lane-operation rate of the evaluation kernel.  Queries that AUTO
+answers from state graphs have neither: there it is that of the graphs' kernels together (a chain of
+launches of a few blocks each), priced with the states that they keep, and `kernel` names them.
 `cpu_baseline` times the plain CPU oracle on a bounded sample of the same workload.
 """
 import argparse
@@ -67,6 +71,26 @@ def algorithmic_lane_ops(stats, n_chunks, key="member_visits"):
     executes); key = "members_evaluated": applications the engine really carried out."""
     words = -(-n_chunks // 32) + -(-stats["group_size"] // 32)
     return 4.0 * words * stats[key]
+
+
+# What AUTO answers from the graph of a skeleton, two devices for every level of the group, whatever its sizes: words that a
+# device of a state has by the number of levels (the masks of all rows, and a word of rows and chunks; more levels: a pair)
+SKELETON_KERNELS = "k_skeleton_alone / k_skeleton_level / k_skeleton_two / k_skeleton_finish / k_skeleton_costs"
+SKELETON_WORDS = {1: 2, 2: 2, 3: 3, 4: 9, 5: 4, 6: 4}
+
+
+def group_sizes(query):
+    """Devices of the reduction group at every hardware level that it spans."""
+    out = [1] * len(query["card"])
+    for a in query["reduce_axes"]:
+        out = [f * x for f, x in zip(out, query["placement"][a])]
+    return tuple(f for f in out if f > 1)
+
+
+def skeleton_lane_ops(stats, query):
+    """Lane-operations of the instruction applications that building a skeleton's graph takes: as above, 4 for every word of every
+    device of the state that takes part."""
+    return 4.0 * SKELETON_WORDS.get(len(group_sizes(query)), 0) * stats["members_evaluated"]
 
 
 def measured_traffic(kernel, cfg_index):
@@ -231,10 +255,11 @@ def main():
         dt = time.perf_counter() - t0
         return dict(acc, dt=dt, results=batch.results(), steps=steps, queries=queries)
 
-    def flat_summary(run, key):
-        """Lane-operation rate of the flat engines' evaluation kernel; key selects which applications count."""
+    def flat_summary(run, key, skeletons=False):
+        """Lane-operation rate of the flat engines' evaluation kernel; key selects which applications count (skeletons: those on
+        the states that the graphs' kernels keep)."""
         results, queries = run["results"], run["queries"]
-        ops = sum(algorithmic_lane_ops(r["stats"], q["n_chunks"] or int(torch.tensor(q["card"]).prod()), key)
+        ops = sum(skeleton_lane_ops(r["stats"], q) if skeletons else algorithmic_lane_ops(r["stats"], q["n_chunks"] or int(torch.tensor(q["card"]).prod()), key)
                   for q, r in zip(queries, results))
         launches = max(run["eval_launches"], 1)
         launch_ms = run["eval_ms"] / launches
@@ -245,14 +270,15 @@ def main():
         """The figures of one timed run: throughput, device times, roofline of its dominant kernel family."""
         results, steps = run["results"], run["steps"]
         step_s = run["dt"] / steps
-        own = [r for r in results if r["stats"]["evaluated_with"] < 0]
+        own = [r for r in results if r["stats"]["evaluated_with"] < 0 and r["stats"]["candidates"] > 0]
         candidates_all = sum(r["stats"]["candidates"] for r in results)
         candidates = sum(r["stats"]["candidates"] for r in own)
+        structures = {(group_sizes(q), q["n_chunks"], q["max_len"]): r["stats"]["candidates"] for q, r in zip(run["queries"], results) if r["stats"]["candidates"] > 0}
         engines = sorted({r["stats"]["engine"] for r in results})
         main_engine = max(engines, key=lambda e: sum(r["stats"]["candidates"] for r in own if r["stats"]["engine"] == e))
         out = {"value": candidates / step_s, "unit": "candidates/s", "value_all_queries": candidates_all / step_s,
-               "ms_per_step": step_s * 1e3, "steps": steps,
-               "queries": len(results), "queries_evaluated": len(own),
+               "value_distinct_structures": sum(structures.values()) / step_s, "ms_per_step": step_s * 1e3, "steps": steps,
+               "queries": len(results), "distinct_structures": len(structures), "queries_evaluated": len(own),
                "candidates_per_step": candidates, "candidates_per_step_all_queries": candidates_all,
                "valid_per_step": sum(r["stats"]["valid"] for r in results),
                "engine": ENGINE_NAMES[engine_asked], "engines_used": engines,
@@ -293,21 +319,22 @@ def main():
                 "algorithmic_hbm_bytes_per_launch": run["front_materialize_bytes"] / n_mat,
                 "children_per_step": run["front_survivors"] / steps}
         else:
-            # (AUTO answers most of these from a state graph, reported as the engine that it stands in for)
+            # (AUTO answers most of these from a state graph, reported as the engine that it stands in for; the workloads' queries have
+            #  all collectives and forms, so that the graph is a skeleton's)
             graph = all(r["stats"]["route"] & B.ROUTE_GRAPH for r in own if r["stats"]["engine"] == main_engine)
-            kernel = "k_graph_alone / k_graph_level / k_graph_finish" if graph else KERNEL[main_engine]
-            ops_launch, launch_ms, achieved = flat_summary(run, "members_evaluated")
-            flat_ops_launch, _, flat_rate = flat_summary(run, "member_visits")
+            kernel = SKELETON_KERNELS if graph else KERNEL[main_engine]
+            ops_launch, launch_ms, achieved = flat_summary(run, "members_evaluated", skeletons=graph)
             out["steps_executed_per_step"] = sum(r["stats"]["steps_executed"] for r in own)
             out["steps_evaluated_per_step"] = sum(r["stats"]["steps_evaluated"] for r in own)
             # lane-operations of the instruction applications the kernel carried out (shared ones once)
             out["roofline"] = {"bound": "alu", "kernel": kernel, "achieved": achieved / 1e12, "peak": ALU_PEAK_LANE_OPS / 1e12,
                                "unit": "Tlane-op/s", "frac": achieved / ALU_PEAK_LANE_OPS,
                                "traffic": measured_traffic(kernel, cfg_index),
-                               "launch_ms": launch_ms, "algorithmic_lane_ops_per_launch": ops_launch,
-                               # the same launch priced with every candidate's applications counted on their own
-                               "per_candidate_lane_ops_per_launch": flat_ops_launch,
-                               "per_candidate_equivalent_frac": flat_rate / ALU_PEAK_LANE_OPS}
+                               "launch_ms": launch_ms, "algorithmic_lane_ops_per_launch": ops_launch}
+            if not graph:
+                # the same launch priced with every candidate's applications counted on their own
+                flat_ops_launch, _, flat_rate = flat_summary(run, "member_visits")
+                out["roofline"].update({"per_candidate_lane_ops_per_launch": flat_ops_launch, "per_candidate_equivalent_frac": flat_rate / ALU_PEAK_LANE_OPS})
         return out
 
     cfg, queries = load(args.config)
@@ -332,11 +359,11 @@ def main():
         "dtype": "u32", "data": "synthetic",
         "config": {"workload": "%s: hierarchy %s, axes %s, %s, max_len %d, top-%d, %d message size(s)"
                                % (cfg["name"], cfg["card"], cfg["axes"], what, cfg["max_len"], cfg["topk"], len(msg)),
-                   "queries": head["queries"], "queries_evaluated": head["queries_evaluated"],
+                   "queries": head["queries"], "distinct_structures": head["distinct_structures"], "queries_evaluated": head["queries_evaluated"],
                    "candidates_per_step": head["candidates_per_step"],
                    "candidates_per_step_all_queries": head["candidates_per_step_all_queries"],
                    "valid_per_step": head["valid_per_step"], "engine": head["engine"], "engines_used": head["engines_used"]},
-        "value_all_queries": head["value_all_queries"],
+        "value_all_queries": head["value_all_queries"], "value_distinct_structures": head["value_distinct_structures"],
         "device_ms_per_step": head["device_ms_per_step"],
         "roofline": dict(head["roofline"], peak_measured=peak_measured / 1e12),
     }
@@ -348,16 +375,15 @@ def main():
             out[key] = head[key]
     if args.one_at_a_time:
         out["config"]["enumerations"] = "one at a time"
-    if 3 in head["engines_used"] and not args.no_compare and not args.one_at_a_time:
+    if run["front_classify_launches"] > 0 and not args.no_compare and not args.one_at_a_time:
         # The timed steps run up to four enumerations side by side, so the event time of a launch there is the time of
         # a kernel that shares the chip.  The same batch with the enumerations one after the other, a few steps: what
         # the kernels reach with the chip to themselves.
         alone = report(timed(queries, msg, args.engine, max(args.steps // 5, 2), 1, B.FLAG_ONE_ENUMERATION_AT_A_TIME), args.config, args.engine)
-        out["one_enumeration_at_a_time"] = {key: alone[key] for key in ("ms_per_step", "steps", "device_ms_per_step", "roofline", "materialize") if key in alone}
+        out["one_enumeration_at_a_time"] = {key: alone[key] for key in ("ms_per_step", "steps", "device_ms_per_step", "roofline", "materialize")}
         # (beside the timed figure, for a reader of the roofline object alone)
-        if "materialize" in alone:
-            out["roofline"]["frac_one_enumeration_at_a_time"] = alone["roofline"]["frac"]
-            out["roofline"]["enumerations_side_by_side"] = 4
+        out["roofline"]["frac_one_enumeration_at_a_time"] = alone["roofline"]["frac"]
+        out["roofline"]["enumerations_side_by_side"] = 4
 
     if not args.no_compare:
         # the other configurations, a few steps each with the default engine, and where that is the shared-prefix
@@ -369,7 +395,7 @@ def main():
             c2, q2 = load(ci)
             steps2 = 3 if ci == 5 else 10
             r2 = report(timed(q2, c2["msg_bytes"], 0, steps2, 2), ci, 0)
-            entry = {k: r2[k] for k in ("value", "unit", "value_all_queries", "ms_per_step", "steps", "queries", "queries_evaluated",
+            entry = {k: r2[k] for k in ("value", "unit", "value_all_queries", "value_distinct_structures", "ms_per_step", "steps", "queries", "queries_evaluated",
                                         "candidates_per_step", "valid_per_step", "engines_used", "device_ms_per_step", "roofline")}
             if r2["engines_used"] == [5] and r2["candidates_per_step"] <= 1 << 30:
                 every_q = B.FLAG_EVALUATE_EVERY_QUERY           # (this leg is about the kernel: every candidate is visited)
