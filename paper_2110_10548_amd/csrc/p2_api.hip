@@ -791,7 +791,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && rows_at_once(shortlist_out, cap, n_msg) > 0 && shortlist_rows <= kShortlistBytes / (sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1));
     // Of a graph with several queries the rows are written once, and their costs worked out for all of them side by side (k_graph_sums).
     auto shares_rows = [&](const Graph& G) {
-        return G.narrow && G.members.size() >= kSharedQueries && runs[G.leader].plan.n_ops == 5 && runs[G.leader].plan.alphabet <= (int)kSumDigits;
+        return G.narrow && G.members.size() >= kSharedQueries && runs[G.leader].plan.n_ops == 5;
     };
     size_t off_jobs = 0, off_rows = 0, off_sums = 0, off_columns = 0;
     size_t n_jobs = 0, n_segs = 0, n_sums = 0, n_columns = 0;

@@ -506,7 +506,7 @@ struct GraphRows {                 // rows of one query, at most count: blocks [
 // The costs of one graph's rows for all of its queries: rows_of_block rows a block, from the edges of row first_row on.
 struct GraphSums { uint32_t first_block, graph, most, n_columns, first_column, fused; unsigned long long first_row; };
 struct GraphColumn { unsigned long long out_first; uint32_t query, pad; };       // (of the graph's members, in their order)
-constexpr unsigned kSumDigits = 80, kSumMembers = 32;
+constexpr unsigned kSumDigits = 80, kSumMembers = 32;        // (five operations on the 16 patterns of four levels)
 // Structures of few states (graph_alone_holds; list: numbers of graphs), a block each: levels, counts and edges in one launch.
 bool graph_alone_holds(uint32_t nodes);
 // Planes that the wavefronts of the launches per level may reserve and not use.

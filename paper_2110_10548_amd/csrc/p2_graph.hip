@@ -126,6 +126,8 @@ __device__ __forceinline__ Graph<InBlock> open_in_block(const DevGraph& D, Alone
     if (G.cap_found > kAloneFound) G.cap_found = kAloneFound;
     return G;
 }
+__device__ __forceinline__ uint32_t add_global(P2_GLOBAL uint32_t* p, uint32_t v) { return atomicAdd((uint32_t*)p, v); }
+__device__ __forceinline__ u64 add_global(P2_GLOBAL u64* p, u64 v) { return atomicAdd((u64*)p, v); }
 __device__ __forceinline__ u64 shfl64(u64 v, int src) { return __shfl(v, src, kWave); }
 
 __device__ __forceinline__ u64 lowest64(u64 x, int n) {
@@ -372,6 +374,15 @@ __device__ __forceinline__ bool make_child(Pairs<kPairs>& st, const Verdict& V, 
     return full;
 }
 
+__device__ __forceinline__ u64 mix(u64 r, u64 m, uint32_t where) {
+    u64 x = (r + 0x5851f42d4c957f2dull * (where + 1u)) * 0xd1342543de82ef95ull;
+    x ^= x >> 31;
+    x = (x ^ (m + (m << 21) + (m >> 35))) * 0xaf251af3b0f025b5ull;
+    x ^= x >> 28;
+    x *= 0xb564ef22ec7aece5ull;
+    return x ^ (x >> 32);
+}
+
 // One level of one graph by wavefront w of nw: the states first reached by `level` instructions are judged against every
 // pattern, a team of R lanes per (state, pattern), and the children of what holds are built and looked up.  The wavefronts
 // do not meet: each collects the edges it finds and writes them to the lists some dozens at a time, so that a level is one
@@ -601,6 +612,25 @@ struct FinishShared {
     uint32_t end[P2_MAX_LEN + 1], lim[P2_MAX_LEN + 1], at[P2_MAX_LEN + 1];
     uint32_t n_found, n_words;
 };
+
+// Exclusive sums over the block of two counts at once (each below 2^31 in total).
+template <int T>
+__device__ u64 block_scan(u64 v, u64& total, u64* wave_sums) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    u64 s = v;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const u64 o = __shfl_up(s, off, kWave);
+        if (lane >= off) s += o;
+    }
+    if (lane == kWave - 1) wave_sums[wave] = s;
+    __syncthreads();
+    u64 before = 0ull, all = 0ull;
+    for (int w = 0; w < T / kWave; ++w) { const u64 x = wave_sums[w]; if (w < wave) before += x; all += x; }
+    __syncthreads();
+    total = all;
+    return before + s - v;
+}
 
 // The counts of every node, from one instruction left to the size limit, and the edges that lie on the way to a goal, by
 // one block with a thread per edge.  Count r of a node that `d` instructions reach first is asked for up to r = max_len - d,

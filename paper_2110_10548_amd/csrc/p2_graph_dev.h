@@ -23,36 +23,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <typename To, typename From>
 __device__ __forceinline__ P2_GLOBAL To* in_global(From* p) { return (P2_GLOBAL To*)p; }
-__device__ __forceinline__ uint32_t add_global(P2_GLOBAL uint32_t* p, uint32_t v) { return atomicAdd((uint32_t*)p, v); }
-__device__ __forceinline__ u64 add_global(P2_GLOBAL u64* p, u64 v) { return atomicAdd((u64*)p, v); }
-
-__device__ __forceinline__ u64 mix(u64 r, u64 m, uint32_t where) {
-    u64 x = (r + 0x5851f42d4c957f2dull * (where + 1u)) * 0xd1342543de82ef95ull;
-    x ^= x >> 31;
-    x = (x ^ (m + (m << 21) + (m >> 35))) * 0xaf251af3b0f025b5ull;
-    x ^= x >> 28;
-    x *= 0xb564ef22ec7aece5ull;
-    return x ^ (x >> 32);
-}
-
-// Exclusive sums over the block of two counts at once (each below 2^31 in total).
-template <int T>
-__device__ u64 block_scan(u64 v, u64& total, u64* wave_sums) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    u64 s = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const u64 o = __shfl_up(s, off, kWave);
-        if (lane >= off) s += o;
-    }
-    if (lane == kWave - 1) wave_sums[wave] = s;
-    __syncthreads();
-    u64 before = 0ull, all = 0ull;
-    for (int w = 0; w < T / kWave; ++w) { const u64 x = wave_sums[w]; if (w < wave) before += x; all += x; }
-    __syncthreads();
-    total = all;
-    return before + s - v;
-}
 
 // A skeleton's instructions by digit, in LDS: their levels and the devices that take part.
 struct Instr {
