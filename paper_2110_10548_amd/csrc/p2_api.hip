@@ -739,21 +739,23 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         r.graph_pos = (int)G.members.size();
         G.members.push_back(i);
     }
-    // those that p2_skeleton.hip works on come first; of one and two levels a block each, unless there are larger ones, whose launches
-    // they ride along in
-    unsigned n_alone = 0, n_narrow = 0;
+    // those that p2_skeleton.hip works on come first, by levels; of one and two levels a block each, unless there are larger ones, whose
+    // launches they ride along in
+    uint32_t n_narrow[3] = {0, 0, 0};
+    bool alone_skeletons = false;
     {
-        bool larger = false;
-        for (const Graph& G : graphs) larger |= G.narrow && G.R > 4;
+        auto class_of = [](const Graph& G) { return !G.narrow ? 3 : G.R <= 4 ? 0 : G.R == 8 ? 1 : 2; };
         std::vector<int> at(graphs.size());
         std::vector<Graph> in_order;
         in_order.reserve(graphs.size());
-        for (int k = 0; k < 3; ++k)
+        for (int c = 0; c <= 3; ++c)
             for (size_t g = 0; g < graphs.size(); ++g)
-                if ((!graphs[g].narrow ? 2 : larger ? 1 : 0) == k) { at[g] = (int)in_order.size(); in_order.push_back(graphs[g]); (k == 0 ? n_alone : n_narrow) += k < 2 ? 1u : 0u; }
+                if (class_of(graphs[g]) == c) { at[g] = (int)in_order.size(); in_order.push_back(graphs[g]); if (c < 3) ++n_narrow[c]; }
         graphs.swap(in_order);
         for (QueryRun& r : runs) if (r.graph_id >= 0) r.graph_id = at[r.graph_id];
+        alone_skeletons = n_narrow[0] > 0 && n_narrow[1] + n_narrow[2] == 0;
     }
+    const uint32_t n_skeletons = n_narrow[0] + n_narrow[1] + n_narrow[2];
     size_t n_others = 0;                 // queries that other engines evaluate
     bool any_topk = false;
     for (const QueryRun& r : runs) { n_others += r.graph || r.plan.n_candidates == 0 ? 0 : 1; any_topk |= r.topk > 0; }
@@ -956,7 +958,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     std::vector<GraphBlock> glevel, gsteps, gcosts;
     unsigned most_members = 0;
     std::vector<uint32_t> gsmall, glarge;
-    int graph_levels = 0, narrow_levels = 0, narrow_size = 0;
+    int graph_levels = 0, narrow_levels = 0;
     if (!graphs.empty()) {
         uint32_t n_by_size[3] = {0, 0, 0};                // up to two levels, three, more
         auto size_of = [&](const Graph& G) { const size_t n = runs[G.leader].plan.patterns.size(); return n <= 4 ? 0 : n <= 9 ? 1 : 2; };
@@ -972,7 +974,6 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             G.n_blocks = G.small ? 1u : sz == 0 ? 12u : sz == 1 ? std::min(std::max(share, 16u), 160u) : std::min(std::max(share, 64u), 768u);
             if (G.narrow) {
                 narrow_levels = std::max(narrow_levels, runs[G.leader].plan.max_len);
-                narrow_size = std::max(narrow_size, G.R);
             } else if (G.large) {
                 glarge.push_back((uint32_t)g);
                 G.off_query = off;
@@ -1608,10 +1609,21 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             for (uint32_t g : gsmall) max_R = std::max(max_R, graphs[g].R);
             P2_HIP(launch_graph_alone(dgs, reinterpret_cast<const uint32_t*>(db + off_gsmall), (unsigned)gsmall.size(), max_R, stream));
         }
-        if (n_alone > 0) {
+        if (alone_skeletons) {
             ++eval_launches;
-            P2_HIP(launch_skeleton_alone(dgs, n_alone, stream));
+            P2_HIP(launch_skeleton_alone(dgs, n_skeletons, stream));
         }
+        // (the blocks of a launch: what a graph of each size can do with, and less to each where there are many.  Three hundred of three
+        //  levels, some 1 024 blocks a launch for them: 720 us a call, 2 048: 740, 4 096: 757, 44 to each: 845; for the costs no more than
+        //  4 096, where 1 024 to each took 221 us of device time)
+        auto skeleton_grid = [&](const uint32_t (&blocks)[3], const uint32_t (&links)[3], uint32_t least, uint32_t all) {
+            SkeletonGrid grid;
+            for (int c = 0; c < 3; ++c) {
+                const uint32_t share = std::max(least, all / std::max(1u, n_narrow[c]));
+                grid.graphs[c] = n_narrow[c]; grid.blocks[c] = std::min(blocks[c], share); grid.links[c] = std::min(links[c], share);
+            }
+            return grid;
+        };
         // large groups: one on the call's stream, several on the slots', the largest first, each to the slot with the least to do
         size_t n_slots_used = 0;
         if (n_large > 0) {
@@ -1649,25 +1661,25 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
             }
             if (g_prof.on) P2_HIP(hipEventRecord(g_prof.ev[4], stream));
         }
-        for (int l = 0; n_narrow > 0 && l < narrow_levels; ++l) {
-            // (blocks: of four states with four levels, which have some 45, 450, 2 000, 5 400 and 8 900, and of eight with three, at
-            //  most some 330; a block for every 64 or 128 edges that led there)
-            static const unsigned states[2][P2_MAX_LEN] = {{1, 4, 32, 44, 44, 44, 44}, {1, 12, 128, 512, 768, 768, 768}}, links[2][P2_MAX_LEN] = {{0, 1, 2, 4, 8, 8, 8}, {0, 2, 8, 32, 96, 192, 192}};
-            const int z = narrow_size > 8 ? 1 : 0;
-            ++eval_launches;
-            P2_HIP(launch_skeleton_level(dgs + n_alone, n_narrow, l, states[z][l], links[z][l], stream));
-        }
-        if (n_narrow > 0) {
+        if (n_skeletons > 0 && !alone_skeletons) {
+            for (int l = 0; l < narrow_levels; ++l) {
+                // (blocks: of four states with four levels, which have some 45, 450, 2 000, 5 400 and 8 900, of eight with three, at most
+                //  some 330, and one with fewer; a block for every 64 or 128 edges that led there)
+                static const uint32_t states[P2_MAX_LEN][3] = {{1, 1, 1}, {1, 4, 12}, {1, 32, 128}, {1, 44, 512}, {1, 44, 768}, {1, 44, 768}, {1, 44, 768}};
+                static const uint32_t links[P2_MAX_LEN][3] = {{0, 0, 0}, {1, 1, 2}, {1, 2, 8}, {1, 4, 32}, {1, 8, 96}, {1, 8, 192}, {1, 8, 192}};
+                ++eval_launches;
+                P2_HIP(launch_skeleton_level(dgs, skeleton_grid(states[l], links[l], 4, 1024), l, stream));
+            }
             ++eval_launches;
             uint32_t most_nodes = 0, most_edges = 0;
             int most_len = 0;
-            for (unsigned g = n_alone; g < n_alone + n_narrow; ++g) {
+            for (uint32_t g = 0; g < n_skeletons; ++g) {
                 const DevGraph& D = reinterpret_cast<const DevGraph*>(hb + off_graphs)[g];
                 most_nodes = std::max(most_nodes, D.cap_nodes);
                 most_edges = std::max(most_edges, D.cap_found);
                 most_len = std::max(most_len, (int)D.max_len);
             }
-            P2_HIP(launch_skeleton_finish(dgs + n_alone, n_narrow, most_nodes, most_edges, most_len, stream));
+            P2_HIP(launch_skeleton_finish(dgs, skeleton_grid({1, 4, 64}, {0, 0, 0}, 64, 64), most_nodes, most_edges, most_len, stream));
         }
         if (!glarge.empty()) {
             ++eval_launches;
@@ -1716,9 +1728,11 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         if (!gsteps.empty())
             P2_HIP(launch_graph_steps(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gsteps), (unsigned)gsteps.size(), stream));
         P2_HIP(launch_graph_costs(dqs, dgs, reinterpret_cast<const GraphBlock*>(db + off_gcosts), (unsigned)gcosts.size(), stream));
-        if (n_alone + n_narrow > 0)
-            P2_HIP(launch_skeleton_costs(dqs, dgs, n_alone + n_narrow, narrow_size <= 4 ? 64u : narrow_size == 8 ? 1024u : 2048u, most_members,
-                                         narrow_size <= 4 ? 2 : narrow_size == 8 ? 3 : kNarrowLevels, n_msg > 0 ? 1 : 0, stream));
+        if (n_skeletons > 0) {
+            // (a block for every state on the way to a goal)
+            static const uint32_t used[P2_MAX_LEN + 1][3] = {{1, 1, 1}, {1, 1, 1}, {5, 7, 9}, {17, 33, 51}, {23, 97, 229}, {24, 171, 662}, {24, 230, 1419}, {24, 230, 1419}};
+            P2_HIP(launch_skeleton_costs(dqs, dgs, skeleton_grid(used[narrow_levels], {0, 0, 0}, 16, 4096), most_members, n_msg > 0 ? 1 : 0, stream));
+        }
         if (direct && (C.h_progs.ensure(sizeof(p2_program) * rows_room) != hipSuccess ||
                        C.h_costs.ensure(sizeof(double) * rows_room * (size_t)std::max(n_msg, 1)) != hipSuccess)) {
             (void)hipGetLastError();                     // (the rows themselves may well need less)

@@ -519,13 +519,17 @@ hipError_t launch_graph_finish(const DevGraph* graphs, const uint32_t* list, uns
 // its states, and for the edges that led to them), then those of the counts.
 constexpr int kNarrowLevels = 4;
 int skeleton_state_words(int levels);
+// How a launch's blocks are dealt out to graphs that stand in this order: of up to two levels, of three, of four; so many graphs of
+// each, and so many blocks to one of them (level: for its states, and behind them for the edges).
+struct SkeletonGrid {
+    uint32_t graphs[3], blocks[3], links[3];
+};
 hipError_t launch_skeleton_alone(const DevGraph* graphs, unsigned n, hipStream_t stream);
-hipError_t launch_skeleton_level(const DevGraph* graphs, unsigned n, int level, unsigned blocks, unsigned link_blocks, hipStream_t stream);
-hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, uint32_t most_nodes, uint32_t most_edges, int max_len, hipStream_t stream);      // (the most that one of them has room for)
-// Of all of them, the edges on the way to a goal and what these add to the bandwidth sums (blocks: for the states of the largest;
+hipError_t launch_skeleton_level(const DevGraph* graphs, const SkeletonGrid& grid, int level, hipStream_t stream);
+hipError_t launch_skeleton_finish(const DevGraph* graphs, const SkeletonGrid& grid, uint32_t most_nodes, uint32_t most_edges, int max_len, hipStream_t stream);      // (the most that one of them has room for)
+// Of all of them, the edges on the way to a goal and what these add to the bandwidth sums (blocks: for the states of one;
 // members: the most queries of one).
-hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, unsigned n, unsigned blocks, unsigned members, int max_levels, int with_costs,
-                                 hipStream_t stream);
+hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, const SkeletonGrid& grid, unsigned members, int with_costs, hipStream_t stream);
 // What the edges add to the bandwidth sums of every query: of larger skeletons, from the queries' sizes; of the others, from the
 // bandwidth rows.
 hipError_t launch_graph_costs(const DevQuery* queries, const DevGraph* graphs, const GraphBlock* blocks, unsigned n_blocks, hipStream_t stream);

@@ -689,33 +689,49 @@ __device__ void skeleton_finish(const Skeleton<Where>& G, FinishShared& S, uint3
     }
 }
 
+// A block's graph, and its place among the graph's blocks.
+struct Place { uint32_t graph, block, blocks, links; };
+__device__ __forceinline__ Place place_of(const SkeletonGrid& grid, uint32_t at) {
+    Place p{0u, at, 0u, 0u};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const uint32_t per = grid.blocks[c] + grid.links[c], all = grid.graphs[c] * per;
+        if (p.blocks != 0u) continue;
+        if (p.block >= all) { p.block -= all; p.graph += grid.graphs[c]; continue; }
+        if (grid.graphs[c] > 1u) { const uint32_t g = p.block / per; p.graph += g; p.block -= g * per; }
+        p.blocks = grid.blocks[c]; p.links = grid.links[c];
+    }
+    return p;
+}
+
 __device__ __forceinline__ void open_level(LevelShared& S, const DevGraph& D) {
     if ((int)threadIdx.x < kEntryPatterns) { S.shape[threadIdx.x] = D.shape[threadIdx.x]; S.part[threadIdx.x] = (uint32_t)D.part[threadIdx.x]; }
     if (threadIdx.x < kEntries) S.code[threadIdx.x] = 0;
     if (threadIdx.x == 0) S.flags = 0u;
     __syncthreads();
 }
-// One level of the graphs, one of them a y: the last n_links blocks of a graph work on the edges that led to the level, the others on
-// its states.  Bound by the chain of one block's steps where a level has few states (three levels: some 10 us a launch) and by the
+// One level of the graphs: the last blocks of a graph work on the edges that led to the level, the others on its states.  Bound by the chain of one block's steps where a level has few states (three levels: some 10 us a launch) and by the
 // instructions where it has many: [2 4 8 8], six levels, 194 us, where a team of lanes per (state, pattern) in p2_graph.hip takes
 // 382; half of that is the fifth level, 5 400 states.
+// Every graph gets the blocks that its levels can do with: with those of the largest for all of them, 300 of three levels beside one
+// of four took 2 270 us a call, and 949 on their own devices.
 template <int L>
-__device__ void level_of(const Skeleton<InDevice>& G, LevelShared& S, int level, uint32_t n_links) {
-    const uint32_t judging = gridDim.x - n_links;
-    if (blockIdx.x < judging) skeleton_level<L>(G, S, level, blockIdx.x, judging);
-    else skeleton_links<L>(G, S, level, (blockIdx.x - judging) * kLevelThreads + threadIdx.x, n_links * kLevelThreads);
+__device__ void level_of(const Skeleton<InDevice>& G, LevelShared& S, int level, const Place& p) {
+    if (p.block < p.blocks) skeleton_level<L>(G, S, level, p.block, p.blocks);
+    else skeleton_links<L>(G, S, level, (p.block - p.blocks) * kLevelThreads + threadIdx.x, p.links * kLevelThreads);
 }
-__global__ __launch_bounds__(kLevelThreads) void k_skeleton_level(const DevGraph* __restrict__ graphs, int level, uint32_t n_links) {
+__global__ __launch_bounds__(kLevelThreads) void k_skeleton_level(const DevGraph* __restrict__ graphs, SkeletonGrid grid, int level) {
     __shared__ LevelShared S;
-    const DevGraph& D = graphs[blockIdx.y];
+    const Place p = place_of(grid, blockIdx.x);
+    const DevGraph& D = graphs[p.graph];
     const Skeleton<InDevice> G = open_in_device(D);
     if (level >= G.max_len) return;
     open_level(S, D);
     switch (D.R) {
-    case 2: level_of<1>(G, S, level, n_links); break;
-    case 4: level_of<2>(G, S, level, n_links); break;
-    case 8: level_of<3>(G, S, level, n_links); break;
-    default: level_of<4>(G, S, level, n_links); break;
+    case 2: level_of<1>(G, S, level, p); break;
+    case 4: level_of<2>(G, S, level, p); break;
+    case 8: level_of<3>(G, S, level, p); break;
+    default: level_of<4>(G, S, level, p); break;
     }
     __syncthreads();
     if (threadIdx.x == 0 && S.flags != 0u) atomicOr(&D.ctr->flags, S.flags);
@@ -723,14 +739,15 @@ __global__ __launch_bounds__(kLevelThreads) void k_skeleton_level(const DevGraph
 
 // The programs of two instructions from every node, to the goal and short of it, which the edges of its children are enough for: by
 // many blocks, for with four levels two thirds of the counting is this.
-__global__ __launch_bounds__(256) void k_skeleton_two(const DevGraph* __restrict__ graphs) {
-    const Skeleton<InDevice> G = open_in_device(graphs[blockIdx.y]);
+__global__ __launch_bounds__(256) void k_skeleton_two(const DevGraph* __restrict__ graphs, SkeletonGrid grid) {
+    const Place p = place_of(grid, blockIdx.x);
+    const Skeleton<InDevice> G = open_in_device(graphs[p.graph]);
     const int lane = (int)(threadIdx.x & (kWave - 1));
     if (G.ctr->flags != 0u) return;
     // (count 2 is asked for where two instructions are left)
     const u64 f = lane >= 1 && lane <= G.max_len - 2 ? G.found[lane] : 0ull;
     const uint32_t lim = G.max_len < 2 ? 0u : 1u + (uint32_t)__builtin_amdgcn_readlane((int)wave_scan((uint32_t)f), kWave - 1);
-    for (uint32_t n = blockIdx.x * 256u + threadIdx.x; n < lim; n += gridDim.x * 256u) {
+    for (uint32_t n = p.block * 256u + threadIdx.x; n < lim; n += p.blocks * 256u) {
         const uint32_t own = G.node_edges[n], end = (own >> 14) + (own >> 7 & 127u);
         uint32_t goals = 0u, prefixes = 0u;
         for (uint32_t e = own >> 14; e < end; e += 4u) {
@@ -796,12 +813,13 @@ __global__ __launch_bounds__(kAloneThreads) void k_skeleton_alone(const DevGraph
 template <int LOG>
 constexpr int kCostWaves = LOG <= 3 ? 8 : 4;      // (four levels: 17.5 us with four, 23 with eight; three: 11 and 9)
 template <int LOG>
-__global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs, int with_costs) {
+__global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs, SkeletonGrid grid, int with_costs) {
     __shared__ PatternTable T;
-    const DevGraph& D = graphs[blockIdx.y];
+    const Place p = place_of(grid, blockIdx.x);
+    const DevGraph& D = graphs[p.graph];
     const P2_GLOBAL GraphCounters* const ctr = in_global<const GraphCounters>(D.ctr);
-    const uint32_t n_use = ctr->n_edges, n_members = (uint32_t)D.n_members, member = blockIdx.z * kWave + (threadIdx.x & (kWave - 1));
-    if (ctr->flags != 0u || blockIdx.x >= n_use || blockIdx.z * kWave >= n_members) return;
+    const uint32_t n_use = ctr->n_edges, n_members = (uint32_t)D.n_members, member = blockIdx.y * kWave + (threadIdx.x & (kWave - 1));
+    if (ctr->flags != 0u || p.block >= n_use || blockIdx.y * kWave >= n_members) return;
     T.open(D, queries[D.query]);
     const P2_GLOBAL uint8_t* const nearest = in_global<const uint8_t>(D.nearest);
     const P2_GLOBAL uint32_t* const list = in_global<const uint32_t>(D.use_id);
@@ -816,11 +834,11 @@ __global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(cons
     const int M = D.max_len, R = D.R;
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     __syncthreads();
-    for (uint32_t u = blockIdx.x; u < n_use; u += gridDim.x) {
+    for (uint32_t u = p.block; u < n_use; u += p.blocks) {
         const uint32_t node = list[u], rec = node_edges[node], first = rec >> 14, count = rec >> 7 & 127u, place = first_edge[node].x;
         const u64 path = node_path[node];
         int left = M - 1;
-        for (u64 p = path; p != 0ull; p >>= 8) --left;
+        for (u64 x = path; x != 0ull; x >>= 8) --left;
         bool kept[2];
         u32x2 link[2];
         u64 keepers[2];
@@ -833,7 +851,7 @@ __global__ __launch_bounds__(kCostWaves<LOG> * kWave) void k_skeleton_costs(cons
             keepers[x] = __ballot(kept[x]);
         }
         const uint32_t n0 = (uint32_t)__popcll(keepers[0]), n_kept = n0 + (uint32_t)__popcll(keepers[1]);
-        if (wave == 0u && blockIdx.z == 0u) {
+        if (wave == 0u && blockIdx.y == 0u) {
             const u64 below = (1ull << lane) - 1ull;
             if (kept[0]) edges[place + (uint32_t)__popcll(keepers[0] & below)] = (link[0].x & ~kGoalEdge) | link[0].y;
             if (kept[1]) edges[place + n0 + (uint32_t)__popcll(keepers[1] & below)] = (link[1].x & ~kGoalEdge) | link[1].y;
@@ -865,9 +883,14 @@ hipError_t launch_skeleton_alone(const DevGraph* graphs, unsigned n, hipStream_t
     hipLaunchKernelGGL(k_skeleton_alone, dim3(n), dim3(kAloneThreads), 0, stream, graphs);
     return hipGetLastError();
 }
-hipError_t launch_skeleton_level(const DevGraph* graphs, unsigned n, int level, unsigned blocks, unsigned link_blocks, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_skeleton_level, dim3(blocks + link_blocks, n), dim3(kLevelThreads), 0, stream, graphs, level, link_blocks);
+static unsigned blocks_of(const SkeletonGrid& grid) {
+    unsigned n = 0;
+    for (int c = 0; c < 3; ++c) n += grid.graphs[c] * (grid.blocks[c] + grid.links[c]);
+    return n;
+}
+hipError_t launch_skeleton_level(const DevGraph* graphs, const SkeletonGrid& grid, int level, hipStream_t stream) {
+    if (blocks_of(grid) == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_skeleton_level, dim3(blocks_of(grid)), dim3(kLevelThreads), 0, stream, graphs, grid, level);
     return hipGetLastError();
 }
 static constexpr size_t kMostLds = 160 * 1024 - 1024;     // (beside what the block shares)
@@ -880,22 +903,22 @@ static hipError_t launch_finish(const DevGraph* graphs, unsigned n, size_t bytes
     hipLaunchKernelGGL(k_skeleton_finish<few>, dim3(n), dim3(kFinishThreads), bytes, stream, graphs, (uint32_t)(bytes / 4));
     return hipGetLastError();
 }
-hipError_t launch_skeleton_finish(const DevGraph* graphs, unsigned n, uint32_t most_nodes, uint32_t most_edges, int max_len, hipStream_t stream) {
+hipError_t launch_skeleton_finish(const DevGraph* graphs, const SkeletonGrid& grid, uint32_t most_nodes, uint32_t most_edges, int max_len, hipStream_t stream) {
+    const unsigned n = grid.graphs[0] + grid.graphs[1] + grid.graphs[2];
     if (n == 0) return hipSuccess;
     // (edge by edge: for a node three bytes and two lists of counts, from two instructions)
     const size_t few = ((size_t)most_nodes + 3) / 4 * 12 + sizeof(uint32_t) * 2 * (size_t)(max_len > 1 ? max_len - 1 : 0) * most_nodes;
     if (most_edges <= kFewEdges * (uint32_t)kFinishThreads && few <= kMostLds) return launch_finish<true>(graphs, n, few, stream);
-    hipLaunchKernelGGL(k_skeleton_two, dim3(64, n), dim3(256), 0, stream, graphs);
+    hipLaunchKernelGGL(k_skeleton_two, dim3(blocks_of(grid)), dim3(256), 0, stream, graphs, grid);
     return launch_finish<false>(graphs, n, kMostLds, stream);
 }
 
-hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, unsigned n, unsigned blocks, unsigned members, int max_levels, int with_costs,
-                                 hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    const dim3 grid(blocks, n, (members + kWave - 1) / kWave);
-    if (max_levels <= 2) hipLaunchKernelGGL(k_skeleton_costs<2>, grid, dim3(kCostWaves<2> * kWave), 0, stream, queries, graphs, with_costs);
-    else if (max_levels == 3) hipLaunchKernelGGL(k_skeleton_costs<3>, grid, dim3(kCostWaves<3> * kWave), 0, stream, queries, graphs, with_costs);
-    else hipLaunchKernelGGL(k_skeleton_costs<kNarrowLevels>, grid, dim3(kCostWaves<kNarrowLevels> * kWave), 0, stream, queries, graphs, with_costs);
+hipError_t launch_skeleton_costs(const DevQuery* queries, const DevGraph* graphs, const SkeletonGrid& grid, unsigned members, int with_costs, hipStream_t stream) {
+    if (blocks_of(grid) == 0) return hipSuccess;
+    const dim3 blocks(blocks_of(grid), (members + kWave - 1) / kWave);
+    if (grid.graphs[2] > 0) hipLaunchKernelGGL(k_skeleton_costs<kNarrowLevels>, blocks, dim3(kCostWaves<kNarrowLevels> * kWave), 0, stream, queries, graphs, grid, with_costs);
+    else if (grid.graphs[1] > 0) hipLaunchKernelGGL(k_skeleton_costs<3>, blocks, dim3(kCostWaves<3> * kWave), 0, stream, queries, graphs, grid, with_costs);
+    else hipLaunchKernelGGL(k_skeleton_costs<2>, blocks, dim3(kCostWaves<2> * kWave), 0, stream, queries, graphs, grid, with_costs);
     return hipGetLastError();
 }
 

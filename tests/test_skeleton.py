@@ -252,3 +252,19 @@ def test_rules_of_skeletons(oracle, levels, devices, max_len):
             # (the oracle tries the alphabet behind every prefix and every program that is not at the limit)
             tried = sum(skeleton_rules.prefixes(edges, max_len)) + sum(len(p) < max_len for p in mine)
             assert tried * o.alphabet == r["steps_tried"], (card, k)
+
+
+# graphs of their own for many numbers of chunks: more than a launch has blocks for every state of, with and without one of four levels; two of four levels
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,four", [(3, 1), (40, 0), (130, 2)])
+def test_many_skeletons_in_one_launch(n, four):
+    from paper_2110_10548_amd import binding as B
+    cards = [[2, 4, 8], [4, 16], [3, 4, 5], [8, 2, 4], [80], [2, 8, 4]]
+    queries = [_query(cards[i % 6], 4, i, n_chunks=3 + i // 6, topk=(0, 5)[i % 2]) for i in range(n)] + [_query([2, 2, 2, 2], 5, 900 + i, n_chunks=(16, 6)[i]) for i in range(four)]
+    together = B.p2_synthesize_batch(queries, MSG)
+    assert sum(r["stats"]["route"] == B.ROUTE_GRAPH and r["stats"]["evaluated_with"] < 0 for r in together) > n // 2
+    for i in list(range(0, n, 7)) + list(range(n, n + four)):
+        own = B.p2_synthesize_batch([dict(queries[i], flags=B.FLAG_EVALUATE_EVERY_QUERY)], MSG)[0]
+        # (many groups of more than 64 devices may be walked, and say so; the results are the same)
+        assert np.array_equal(together[i]["programs"], own["programs"]) and np.array_equal(together[i]["cost"], own["cost"]) and len(own["programs"]) > 0
+        assert together[i]["stats"]["valid"] == own["stats"]["valid"]
