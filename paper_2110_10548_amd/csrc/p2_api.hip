@@ -425,9 +425,10 @@ int group_levels(const p2::Plan& pl) {
     for (int j = 0; j < pl.n; ++j) n += pl.f[j] > 1 ? 1 : 0;
     return n;
 }
+bool whole_alphabet(const p2::Plan& pl) { return pl.op_mask == 31u && pl.form_mask == 7u; }
 bool has_skeleton(const p2::Plan& pl) {
     const int levels = group_levels(pl);
-    return ((pl.op_mask == 31u && pl.form_mask == 7u) || pl.max_len == 1) && levels <= p2::kSkeletonLevels && pl.max_len <= kSkeletonMaxLen[levels] &&
+    return (whole_alphabet(pl) || pl.max_len == 1) && levels <= p2::kSkeletonLevels && pl.max_len <= kSkeletonMaxLen[levels] &&
            (pl.k % pl.R == 0 || levels <= p2::kNarrowLevels);
 }
 // What a query's costs need beside the skeleton's graph.
@@ -711,12 +712,16 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     struct Graph { int leader = -1; std::vector<int32_t> members; uint32_t n_blocks = 0; bool small = false, large = false, skeleton = false, narrow = false;
                    int R = 0, rows = 0; size_t off_members = 0, off_query = 0, off_sizes = 0; };
     std::vector<Graph> graphs;
+    bool any_whole = false;              // some skeleton is there in any case
+    for (const QueryRun& r : runs) any_whole |= r.graph && whole_alphabet(r.plan) && has_skeleton(r.plan);
     auto fused_sums = [](const QueryRun& r) { return r.graph_frontier && !r.graph_flat ? 0u : 1u; };
     for (int i = 0; i < n_queries; ++i) {
         QueryRun& r = runs[i];
         if (!r.graph) continue;
         const Plan& pl = r.plan;
-        const bool skeleton = share_validity && has_skeleton(pl);      // (else every query's graph is that of its own devices)
+        // (else every query's graph is that of its own devices; single instructions of a narrowed alphabet are no reason for skeletons'
+        //  launches beside those of small groups)
+        const bool skeleton = share_validity && has_skeleton(pl) && (whole_alphabet(pl) || r.graph_large || any_whole);
         const int R = skeleton ? 1 << group_levels(pl) : pl.R;
         const bool split = pl.k % pl.R != 0;             // (how far rows can be cut is the group's own)
         auto same_group = [&](const QueryRun& o) {
