@@ -796,6 +796,11 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     }
     // (the rows that are picked go to pinned memory, which is bounded as for lists)
     shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && rows_at_once(shortlist_out, cap, n_msg) > 0 && shortlist_rows <= kShortlistBytes / (sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1));
+    // (the shortlist of what has one program at most is its list, unless a cost may be no number, which a list takes and a shortlist does
+    //  not: less to select and to gather.  Walked searches ask for as many of these as for others: on 3 x 6, 215 us a call with, 195 without)
+    const bool costs_are_numbers = n_msg == 1 && msg_bytes[0] > 0.0 && std::isfinite(msg_bytes[0]);
+    for (QueryRun& r : runs)
+        if (!shortlists && costs_are_numbers && r.topk > 0 && r.plan.hierarchy == P2_HIERARCHY_COLLAPSED && most_valid(r.plan) == 1) r.topk = 0;
     // Of a graph with several queries the rows are written once, and their costs worked out for all of them side by side (k_graph_sums).
     auto shares_rows = [&](const Graph& G) {
         return G.narrow && G.members.size() >= kSharedQueries && runs[G.leader].plan.n_ops == 5;
