@@ -454,6 +454,12 @@ uint32_t graph_room(const p2::Plan& pl) {
     const size_t n = pl.patterns.size();
     return levels[n <= 4 ? 0 : n <= 9 ? 1 : n <= 16 ? 2 : n <= 25 ? 3 : 4][pl.max_len];
 }
+// Queries and room of a graph of five or six levels of two devices up to which, and from which, its edges are costed from bandwidth
+// rows.  Whole calls, us, from the sizes / from the rows: five levels, five instructions: one query 1 254 / 1 199, eight 1 284 / 1 242,
+// sixteen 1 306 / 1 322, 64 1 525 / 1 738; six levels, four: one 853 / 825, eight 885 / 876, 32 948 / 993; five levels, four: one
+// 378 / 371, eight 402 / 407; three: 108 / 116.
+constexpr size_t kQueriesByRows = 8;
+constexpr uint32_t kRoomByRows = 32768;
 bool same_graph(const p2::Plan& a, const p2::Plan& b) {
     if (a.R != b.R || graph_rows(a) != graph_rows(b) || a.max_len != b.max_len || a.alphabet != b.alphabet || a.n_ops != b.n_ops ||
         a.patterns.size() != b.patterns.size())
@@ -743,6 +749,13 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         Graph& G = graphs[r.graph_id];
         r.graph_pos = (int)G.members.size();
         G.members.push_back(i);
+    }
+    // (a skeleton of five or six levels whose queries' groups all have two devices a level is their own graph: where it has many edges
+    //  and few queries these are costed from the bandwidth rows, a wavefront's lanes the devices, instead of a lane to a query)
+    for (Graph& G : graphs) {
+        bool own = G.skeleton && !G.narrow && G.members.size() <= kQueriesByRows && graph_room(runs[G.leader].plan) >= kRoomByRows;
+        for (size_t t = 0; t < G.members.size() && own; ++t) own = runs[G.members[t]].plan.R == G.R;
+        if (own) G.skeleton = false;
     }
     // those that p2_skeleton.hip works on come first, by levels; of one and two levels a block each, unless there are larger ones, whose
     // launches they ride along in

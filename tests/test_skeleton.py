@@ -268,3 +268,14 @@ def test_many_skeletons_in_one_launch(n, four):
         # (many groups of more than 64 devices may be walked, and say so; the results are the same)
         assert np.array_equal(together[i]["programs"], own["programs"]) and np.array_equal(together[i]["cost"], own["cost"]) and len(own["programs"]) > 0
         assert together[i]["stats"]["valid"] == own["stats"]["valid"]
+
+
+# skeletons of five and six levels that are their queries' own graphs: up to eight queries costed from bandwidth rows, with one of other sizes among them not
+@pytest.mark.gpu
+@pytest.mark.parametrize("levels,max_len,n,other", [(5, 5, 8, []), (5, 5, 9, []), (6, 4, 3, []), (5, 5, 2, [[3, 2, 2, 2, 2]]), (6, 4, 1, [[2, 2, 2, 2, 2, 3]])])
+def test_large_skeletons_of_few_queries(levels, max_len, n, other):
+    from paper_2110_10548_amd import binding as B
+    queries = [_query([2] * levels, max_len, i, algo=i % 2, topk=(0, 30)[i % 3 == 1], n_chunks=(0, 2 ** levels * 2)[i % 2]) for i in range(n)] + [_query(c, max_len, 50) for c in other]
+    for q, r in zip(queries, B.p2_synthesize_batch(queries, MSG)):
+        _same(r, B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY)], MSG)[0])
+        assert r["stats"]["route"] == B.ROUTE_GRAPH
