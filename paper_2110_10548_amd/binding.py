@@ -361,9 +361,11 @@ class Batch:
     def _piece(self, kept, rows):
         """Memory for the copies of one piece: that of the results before, where nobody refers to them any more."""
         if kept:
-            progs, cost = kept.pop(0)
-            if len(progs) == rows and _unused(progs) and _unused(cost):
-                return progs, cost
+            # (asked of the list's own elements, as _REFS_OF_ONE was: what a local variable adds is the interpreter's)
+            free = len(kept[0][0]) == rows and _unused(kept[0][0]) and _unused(kept[0][1])
+            piece = kept.pop(0)
+            if free:
+                return piece
         return np.empty(rows, dtype=PROGRAM_DTYPE), np.empty((rows, self.n_msg), dtype=np.float64)
 
     def run(self):
