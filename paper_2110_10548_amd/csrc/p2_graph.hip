@@ -1133,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_graph_emit(const DevQuery* __restrict__
 // ~0, with the edges of each).  Half a wavefront holds 32 queries of one row, so that what an edge adds is read in runs of 256
 // bytes; what a step costs each query lies in LDS; 64 rows at a time are turned round there, so that the costs leave in runs of 512
 // bytes.  With a walk per row and query, lanes on rows, the gathers along the edges were the whole cost: 512 queries of [2 4 8 8],
-// 8.2 million rows, 690 us, and 125 so with 23 for the rows.
+// 8.2 million rows, 690 us, and 114 so with 22 for the rows: half of it instructions to issue, 1.6 TB/s between the caches and memory.
 constexpr int kSumThreads = 512, kSumTile = 64;
 __global__ __launch_bounds__(kSumThreads) void k_graph_sums(const DevQuery* __restrict__ queries, const DevGraph* __restrict__ graphs,
                                                             const GraphSums* __restrict__ sums, int n_sums, const GraphColumn* __restrict__ columns,

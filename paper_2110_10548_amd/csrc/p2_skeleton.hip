@@ -149,7 +149,7 @@ struct Team {
     int lg, ls;
     bool in;                                // the device takes part
     // f(bit) for the varied bits, and the word of the lane whose device differs in it.  Four levels: unrolled, DPP moves, for a level
-    // there is bound by its instructions.  Fewer: a loop and LDS exchanges, since what counts there is one block's time, and most of
+    // there has instructions to issue for a third of its time.  Fewer: a loop and LDS exchanges, since what counts there is one block's time, and most of
     // that goes into fetching instructions for the first time ([3 4 6]: 11.1 us a level unrolled, 9.9 so).
     template <class F>
     __device__ __forceinline__ void each(const F& f) const {
@@ -710,9 +710,11 @@ __device__ __forceinline__ void open_level(LevelShared& S, const DevGraph& D) {
     if (threadIdx.x == 0) S.flags = 0u;
     __syncthreads();
 }
-// One level of the graphs: the last blocks of a graph work on the edges that led to the level, the others on its states.  Bound by the chain of one block's steps where a level has few states (three levels: some 10 us a launch) and by the
-// instructions where it has many: [2 4 8 8], six levels, 194 us, where a team of lanes per (state, pattern) in p2_graph.hip takes
-// 382; half of that is the fifth level, 5 400 states.
+// One level of the graphs: the last blocks of a graph work on the edges that led to the level, the others on its states.  Bound by the
+// chain of one block's steps where a level has few states (three levels: some 10 us a launch).  Where it has many, vector instructions
+// take a third of the time to issue and the wavefronts wait for 60 to 70 % of theirs, for the block's barriers, the table and the nodes'
+// states: [2 4 8 8], six levels, 193 us, where a team of lanes per (state, pattern) in p2_graph.hip takes 382; a third of that is the
+// fifth level, 5 400 states.
 // Every graph gets the blocks that its levels can do with: with those of the largest for all of them, 300 of three levels beside one
 // of four took 2 270 us a call, and 949 on their own devices.
 template <int L>
