@@ -137,7 +137,7 @@ def test_shortlists_selected_before_the_count(queries):
                 assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], full["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], full["cost"][best])
 
 
-# rows of one graph written once for its queries, 32 to a block: two blocks and three, costs fused and not; beside queries with rows of their own
+# rows of one graph written once for its queries, 32 to a block: two blocks and three, step costs not fused (more than 2^30 candidates); beside queries with rows of their own
 @pytest.mark.gpu
 @pytest.mark.parametrize("large,n", [(False, 33), (True, 65)])
 def test_rows_written_once_for_many_queries(large, n):
@@ -153,6 +153,24 @@ def test_rows_written_once_for_many_queries(large, n):
             kk = q["topk"]
             assert r["stats"]["valid"] == len(f["programs"]) and len(r["programs"]) == kk * len(msg)
             for m in range(len(msg)):
+                best = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:kk]
+                assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], f["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], f["cost"][best])
+
+
+# the same with step costs that are fused (spaces of up to 2^30 candidates are costed as their walk is): three and four levels, small groups and large among them; one block more or less than full
+@pytest.mark.gpu
+@pytest.mark.parametrize("levels,max_len,n", [(4, 4, 32), (4, 4, 33), (3, 5, 70), (2, 5, 64)])
+def test_rows_written_once_with_fused_costs(levels, max_len, n):
+    from paper_2110_10548_amd import binding as B
+    rng = random.Random(n)
+    cards = [c for c in itertools.product((2, 3, 4, 5, 8, 11), repeat=levels) if 66 <= math.prod(c) <= 512] + [(2,) * levels, (2,) * (levels - 1) + (4,)]
+    queries = [_query(list(rng.choice(cards)), max_len, i, topk=rng.choice((1, 7, 40)), algo=i % 2) for i in range(n)]
+    for msg in (MSG[:1], MSG + [7.0]):
+        full = B.p2_synthesize_batch([dict(q, topk=0) for q in queries], msg)
+        for q, f, r in zip(queries, full, B.p2_synthesize_batch(queries, msg)):
+            assert r["stats"]["candidates"] <= 1 << 30 and r["stats"]["route"] == B.ROUTE_GRAPH and r["stats"]["valid"] == len(f["programs"])
+            for m in range(len(msg)):
+                kk = min(q["topk"], len(f["programs"]))
                 best = np.lexsort((f["programs"]["index"], f["cost"][:, m]))[:kk]
                 assert np.array_equal(r["programs"][m * kk:(m + 1) * kk], f["programs"][best]) and np.array_equal(r["cost"][m * kk:(m + 1) * kk], f["cost"][best])
 
