@@ -343,8 +343,9 @@ constexpr size_t kTopkJobMax = 1 << 18;
 // instructions, 80 rows: 32 222 / 223.
 constexpr size_t kSharedQueries = p2::kSumMembers;
 
-// Room for the rows that shortlists may be selected from before their number is known.
-constexpr size_t kShortlistBytes = (size_t)4 << 30;
+// Room for the rows that shortlists may be selected from before their number is known: with all collectives and forms a query has
+// as many as there is room for, with a narrowed alphabet it may have a handful of 83 920.
+constexpr size_t kShortlistBytes = (size_t)4 << 30, kNarrowedShortlistBytes = (size_t)64 << 20;
 
 // Engine AUTO walks candidate spaces of at most this many programs index by index ...
 constexpr unsigned long long kWalkMax = 1ull << 30;
@@ -794,7 +795,7 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
     // Shortlists of every query, answered from graphs: the rows and the selections are queued for as many programs as there can be,
     // each takes their number from the graph's counts, and the rows that are picked are written to the host by the selections:
     // one wait instead of two, and four launches fewer ([3 4 6], ten of 571: 147 us, and 118 so).
-    size_t shortlist_rows = 0, shortlist_out = 0;
+    size_t shortlist_rows = 0, narrowed_rows = 0, shortlist_out = 0;
     bool shortlists = only_graphs && n_msg > 0;
     int shortlist_k = 0;
     size_t shortlist_most = 0;
@@ -803,12 +804,15 @@ int32_t run_batch_on(const p2_query* queries, int32_t n_queries, const double* m
         const size_t most = most_valid(r.plan);
         shortlists = shortlists && r.topk > 0 && most <= kTopkJobMax;
         shortlist_rows += most;
+        narrowed_rows += whole_alphabet(r.plan) ? 0 : most;
         shortlist_out += shortlist_rows_of(r.plan, r.topk, n_msg);
         shortlist_k = std::max(shortlist_k, r.topk);
         shortlist_most = std::max(shortlist_most, most);
     }
     // (the rows that are picked go to pinned memory, which is bounded as for lists)
-    shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && rows_at_once(shortlist_out, cap, n_msg) > 0 && shortlist_rows <= kShortlistBytes / (sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1));
+    const size_t row_bytes = sizeof(p2_program) + 8 + 8 * (size_t)std::max(n_msg, 1);
+    shortlists = shortlists && cap > 0 && shortlist_out <= (size_t)cap && rows_at_once(shortlist_out, cap, n_msg) > 0 &&
+                 shortlist_rows <= kShortlistBytes / row_bytes && narrowed_rows <= kNarrowedShortlistBytes / row_bytes;
     // (the shortlist of what has one program at most is its list, unless a cost may be no number, which a list takes and a shortlist does
     //  not: less to select and to gather.  Walked searches ask for as many of these as for others: on 3 x 6, 215 us a call with, 195 without)
     const bool costs_are_numbers = n_msg == 1 && msg_bytes[0] > 0.0 && std::isfinite(msg_bytes[0]);

@@ -297,3 +297,21 @@ def test_large_skeletons_of_few_queries(levels, max_len, n, other):
     for q, r in zip(queries, B.p2_synthesize_batch(queries, MSG)):
         _same(r, B.p2_synthesize_batch([dict(q, flags=B.FLAG_EVALUATE_EVERY_QUERY)], MSG)[0])
         assert r["stats"]["route"] == B.ROUTE_GRAPH
+
+
+@pytest.mark.gpu
+def test_room_for_shortlists_of_narrowed_alphabets():
+    """Queries that have a handful of the programs that their levels can have take no room for all of them."""
+    import torch
+    from paper_2110_10548_amd import binding as B
+    queries = [_query([2, 2, 2, 2], 6, i, topk=3, op_mask=1) for i in range(200)]
+    B.p2_synthesize_batch(queries[:1], MSG[:1])
+    B.p2_release_thread()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    results = B.p2_synthesize_batch(queries, MSG[:1])
+    held = before - torch.cuda.mem_get_info()[0]
+    B.p2_release_thread()
+    assert {r["stats"]["route"] for r in results} == {B.ROUTE_GRAPH} and all(0 < r["stats"]["valid"] < 1000 for r in results)
+    # (200 times 83 920 rows of 32 bytes would be 537 MB)
+    assert held < 200 << 20
